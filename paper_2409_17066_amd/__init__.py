@@ -7,6 +7,8 @@ memory and streams only.  There is no CPU fallback: a missing library raises.
 import ctypes
 import os
 
+import numpy
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libvq.so")
 
@@ -194,6 +196,10 @@ class DeviceLayer:
             up("idx_out", layer.idx_out), stride(layer.idx_out), up("scale", layer.scale), up("bias", layer.bias),
             int(getattr(layer, "group_vectors", 0)), int(getattr(layer, "orientation", 0)),
             up("col_perm", getattr(layer, "col_perm", None)))
+        # whether vq_dequant writes every column: col_perm names each of them (no permutation: the identity)
+        perm = getattr(layer, "col_perm", None)
+        inside = None if perm is None else perm[(perm >= 0) & (perm < layer.in_features)]
+        self.places_every_column = perm is None or bool((numpy.bincount(inside, minlength=layer.in_features) > 0).all())
 
 
 def _stream():
@@ -206,7 +212,14 @@ def dequant(dl: DeviceLayer, ldw=None):
     import torch
     L = dl.layer
     ldw = L.in_features if ldw is None else ldw
-    W = torch.zeros((L.out_features, ldw), dtype=torch.float16, device="cuda")
+    # vq_dequant writes every weight, so only what it leaves alone is filled: the padding columns, or all of W when col_perm
+    # is no permutation (filling all of an 11008 x 4096 W took 12.7 of 48.5 us)
+    if dl.places_every_column:
+        W = torch.empty((L.out_features, ldw), dtype=torch.float16, device="cuda")
+        if ldw > L.in_features:
+            W[:, L.in_features:].zero_()
+    else:
+        W = torch.zeros((L.out_features, ldw), dtype=torch.float16, device="cuda")
     rc = vq_dequant(dl.desc, W.data_ptr(), ldw, _stream())
     if rc != VQ_OK:
         raise VQError(rc, "vq_dequant")
