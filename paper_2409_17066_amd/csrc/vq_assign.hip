@@ -4,19 +4,585 @@
 //
 // The distance decides an integer, so its arithmetic is fixed (include/vq.h): binary32, t_j = W - B as one
 // subtraction, per element one subtraction and one fused multiply-add into a sum that starts at +0, elements in
-// ascending order, the first of equal distances wins.  That is 2 v + 3 vector-ALU instructions per (vector,
-// centroid) pair and nothing else in the inner loop: the kernel is bound by the vector ALUs.
+// ascending order, the first of equal distances wins.
 //
-// Work split: a lane owns `seg` consecutive vectors of a row, seg = 8, 16 or 32 chosen so that they fill whole dwords of
-// the row's index stream (lanes never share an output dword), and takes them VB at a time against the whole table, which sits in LDS as
-// binary32 and is read with wave-uniform addresses (one broadcast read feeds VB x 64 distances).  Tables larger than
-// the LDS chunk (k = 65536) are walked chunk by chunk with the running minimum kept in registers.  A row's last
-// vector, when the row length is not a multiple of v, is compared over its own elements only; those few vectors
-// go through a second, plain kernel (a wave per row) that inserts their bits into the stream afterwards.
+// Three kernels.  assign_screen_kernel (v <= 13, tables of 64 entries and more) finds for every vector the 16 centroids among
+// which the nearest one must be, on the matrix cores, and computes the distances as defined for those only.  The other two
+// compute every distance on the vector ALUs, 2 v + 3 instructions per (vector, centroid) pair: assign_short_kernel for
+// tables of fewer entries, assign_kernel for longer vectors.
 #include "vq_common.hpp"
 
 namespace vq {
 namespace {
+
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef float float16v __attribute__((ext_vector_type(16)));
+typedef unsigned uint4v __attribute__((ext_vector_type(4)));
+
+// Which vectors a launch takes and where their indices go.  Vector u of row o: element j at
+// W[o * row_step + u * vec_step + j * elem_step] (along the rows of W: ld, v, 1; down its columns: v * ld, 1, ld).  Only the first
+// `len` elements of vectors and centroids are compared; the rest counts as zeros on both sides, which adds nothing to a distance.
+struct Vectors {
+  const __half *W, *B;
+  long long row_step, vec_step, elem_step;
+  int rows, per_row, len;
+  unsigned char *idx;
+  long long idx_stride;
+  // Indices of a row fill its stream from bit 0; the bits of the last dword past them are zeroed, except that bits from
+  // `spare_from` on (the index of a cut-off last vector and what follows it) are somebody else's to write.
+  long long spare_from;
+  // scatter_bit >= 0: there is one row, and the index of its vector u goes into stream u at this bit, the rest of its last
+  // dword being zeroed (the cut-off last vectors of all rows).
+  long long scatter_bit;
+};
+
+// Writes `count` bits of a dword that another lane may be writing other bits of.
+__device__ __forceinline__ void put_bits(unsigned *w, unsigned value, int from, int count) {
+  const unsigned mask = (count >= 32 ? 0xFFFFFFFFu : (1u << count) - 1u) << from;
+  atomicAnd(w, ~mask | (value << from));
+  atomicOr(w, value << from);
+}
+
+// The index of a cut-off last vector: its bits and the zeros up to the end of its last dword.
+__device__ __forceinline__ void scatter_index(const Vectors &a, int u, unsigned index, int bits) {
+  unsigned *w = reinterpret_cast<unsigned *>(a.idx + (long long)u * a.idx_stride) + (a.scatter_bit >> 5);
+  const int sh = (int)(a.scatter_bit & 31);
+  put_bits(w, index, sh, 32 - sh);
+  if (sh + bits > 32) w[1] = index >> (32 - sh);
+}
+
+// A row's dword number d: all of it, or below the bits that are somebody else's.
+__device__ __forceinline__ void store_dword(const Vectors &a, unsigned *w, long long d, unsigned value) {
+  const long long left = a.spare_from - 32 * d;
+  if (left >= 32) *w = value;
+  else put_bits(w, value, 0, (int)left);
+}
+
+// Vectors are dealt out in row order, every row's count rounded up to whole segments of seg_len, whose indices fill whole dwords.
+__host__ __device__ inline int items_per_row(const Vectors &a, int seg_len) { return (a.per_row + seg_len - 1) / seg_len * seg_len; }
+__host__ __device__ inline long long items_of(const Vectors &a, int seg_len) { return (long long)a.rows * items_per_row(a, seg_len); }
+
+// Row and position of the items from number g0 (the same in all lanes of a wave) on; up to 64 of them.
+struct Place {
+  int row_items, o0, p0;
+  __device__ Place(const Vectors &a, long long g0, long long items, int seg_len) : row_items(items_per_row(a, seg_len)) {
+    o0 = items <= 0x7fffffffLL ? (int)((unsigned)g0 / (unsigned)row_items) : (int)(g0 / row_items);
+    p0 = (int)(g0 - (long long)o0 * row_items);
+  }
+  __device__ void item(int x, int &o, int &p) const {
+    const unsigned q = row_items >= 64 ? (p0 + x >= row_items ? 1u : 0u) : (unsigned)(p0 + x) / (unsigned)row_items;
+    o = o0 + (int)q;
+    p = p0 + x - (int)q * row_items;
+  }
+};
+
+// The indices of `count` items (whole segments) from number x0 of a wave's place on, a lane per dword.
+__device__ __forceinline__ void pack_items(const Vectors &a, const Place &place, int x0, int count, int seg_len, int bits, const unsigned *codes, int lane) {
+  const int dwords = count * bits / 32, per_seg = seg_len * bits / 32;
+  for (int d = lane; d < dwords; d += 64) {
+    const int sg = d / per_seg;
+    int o, p;
+    place.item(x0 + sg * seg_len, o, p);
+    const long long at = (long long)(p / seg_len) * per_seg + (d - sg * per_seg);
+    if (o >= a.rows || 32 * at >= (long long)a.per_row * bits) continue;
+    unsigned w = 0;
+    for (int i = 32 * d / bits; i * bits < 32 * d + 32; ++i) {         // (past a row's end the codes are zero)
+      const int sh = i * bits - 32 * d;
+      w |= sh >= 0 ? codes[i] << sh : codes[i] >> -sh;
+    }
+    store_dword(a, reinterpret_cast<unsigned *>(a.idx + (long long)o * a.idx_stride) + at, at, w);
+  }
+}
+
+// The distance of the definition from t to one centroid.
+template <int V, typename Get>
+__device__ __forceinline__ float distance(const float (&t)[V], Get element) {
+  float d = 0.0f;
+#pragma unroll
+  for (int j = 0; j < V; ++j) {
+    // t - c as one fused operation (the same single rounding: the product c * -1 is exact), which takes a binary16 c as it is
+    const float diff = __fmaf_rn(element(j), -1.0f, t[j]);
+    d = __fmaf_rn(diff, diff, d);
+  }
+  return d;
+}
+
+// The lanes' candidates meet: the smaller distance, else the smaller index.  Distances are sums of squares, so their bits order
+// like the numbers.
+__device__ __forceinline__ void wave_arg_min(float &d, unsigned &i) {
+  const unsigned lowest = wave_min_u32(__float_as_uint(d));
+  i = wave_min_u32(__float_as_uint(d) == lowest ? i : 0xFFFFFFFFu);
+  d = __uint_as_float(lowest);
+}
+
+// ---- screening on the matrix cores ------------------------------------------------------------------------------------
+//
+// The nearest centroid has the largest score s_i = t . c_i - |c_i|^2 / 2.  One v_mfma_f32_32x32x16_f16 gives the scores of 32
+// centroids with 32 vectors: the centroid's row of operand A holds its elements and |c|^2 / 2, scaled by a power of two and
+// split into three binary16 parts; the vector's column of operand B holds t and the matching negative power of two.  A t that is
+// a difference W - B is no binary16 number: it is scaled and split into two (v <= 6: both in one instruction's 16 k slots,
+// against the same elements twice; longer vectors: a second instruction with the same A).  A lane sees 16 rows of every result:
+// it keeps the largest score of any such block of 16, that block's number, and the largest score of every other block.
+//
+// Scores carry rounding errors, so the winning block is only trusted when it wins by more than they can be.  With T = |t|, the
+// nearest centroid and whichever centroid has the largest computed score have norms of at most R = T + sqrt(d), d their
+// squared distance; |c|^2 / 2 is kept to 2^-39, or 2^-30 of the largest; the products are exact in binary32 and the sum of one instruction was measured to be within 2^-23 of the
+// sum of its terms' magnitudes (2^-19 is allowed for; operands below the normal range count as 2^-14, which the hardware's
+// alignment of their products needs); the definition's own roundings move d by (v + 2) 2^-24.  Vectors that fail the test
+// -- about 0.3 % with 4096 Gaussian entries --, and all of them when a table has entries that are not finite or huge, are
+// compared with every centroid by the wave together.
+//
+// What bounds it: two blocks of 16 scores (one result) cost 32 matrix-core clocks and 12 vector instructions of 4 clocks, 0.75
+// instructions per pair instead of 2 v + 3, and the two kinds of instruction hardly overlap on a SIMD (four waves of each, apart
+// 0.32 and 0.28 ms, together 0.55 ms).  Measured: 11008 x 4096, v = 6, k = 4096: 8.42 -> 1.15 ms, of which the distances of the
+// winning blocks, loads and packing are about a third; 1947 x 6656, v = 12: 0.23 ms; 107 x 7160, v = 8, k = 65536: 0.44 ms.
+constexpr int WAVES = 16;
+constexpr int SCREEN_ROWS = 4096;                       // table rows in LDS at once: two planes of 16 bytes each
+constexpr int screen_instructions(int v, bool base) { return base && v > 6 ? 2 : 1; }
+constexpr int screen_rows(int k) { return k >= SCREEN_ROWS ? SCREEN_ROWS : (k + 127) & ~127; }   // a wave takes up to four tiles of 32 at once
+
+struct TableScale { int f; float h_max; bool fine; };
+
+// Centroids [c0, c0 + rows) into the two planes, rows past the table repeating its last entry; returns the scale.
+template <int V>
+__device__ TableScale stage_screen_table(const __half *__restrict__ codebook, int stride, int len, int k, int c0, int rows, half8 *plane, float *red) {
+  constexpr int PER = SCREEN_ROWS / (WAVES * 64);
+  const int tid = threadIdx.x, wave = tid >> 6;
+  float h[PER], most = 0.0f;
+  bool fine = true;
+#pragma unroll
+  for (int r = 0; r < PER; ++r) {
+    const int e = tid + r * (WAVES * 64);
+    h[r] = 0.0f;
+    if (e < rows) {
+      const __half *src = codebook + (long long)min(c0 + e, k - 1) * stride;
+      _Float16 c[V];
+#pragma unroll
+      for (int j = 0; j < V; ++j) c[j] = __builtin_bit_cast(_Float16, src[j]);
+#pragma unroll
+      for (int j = 0; j < V; ++j) c[j] = j < len ? c[j] : (_Float16)0.0f;
+      float q = 0.0f;
+#pragma unroll
+      for (int j = 0; j < V; ++j) q = __fmaf_rn((float)c[j], (float)c[j], q);
+      h[r] = 0.5f * q;
+      fine = fine && h[r] < 0x1p28f;                      // (false for entries that are not numbers)
+      most = fmaxf(most, h[r]);
+      half8 lo = {}, hi = {};
+      if constexpr (V <= 6) {
+#pragma unroll
+        for (int j = 0; j < V; ++j) { lo[j] = c[j]; hi[j] = c[j]; }
+      } else {
+#pragma unroll
+        for (int j = 0; j < V; ++j) { if (j < 8) lo[j & 7] = c[j]; else hi[j & 7] = c[j]; }
+      }
+      plane[e] = lo;
+      plane[rows + e] = hi;
+    }
+  }
+  for (int s = 32; s > 0; s >>= 1) most = fmaxf(most, __shfl_xor(most, s, 64));
+  const bool wave_fine = __all(fine);
+  if ((tid & 63) == 0) { red[wave] = most; red[WAVES + wave] = wave_fine ? 1.0f : 0.0f; }
+  __syncthreads();
+  TableScale t;
+  t.h_max = 0.0f; t.fine = true;
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) { t.h_max = fmaxf(t.h_max, red[w]); t.fine = t.fine && red[WAVES + w] != 0.0f; }
+  // |c|^2 / 2 * 2^f below 2^15 and its parts' factor 2^-f a normal binary16 number
+  t.f = t.h_max > 0.0f ? min(14, max(-14, 15 - __builtin_amdgcn_frexp_expf(t.h_max))) : 14;
+#pragma unroll
+  for (int r = 0; r < PER; ++r) {
+    const int e = tid + r * (WAVES * 64);
+    if (e < rows) {
+      const float x = ldexpf(h[r], t.f);
+      const _Float16 n1 = (_Float16)x;
+      const float x1 = x - (float)n1;
+      const _Float16 n2 = (_Float16)x1;
+      const _Float16 n3 = (_Float16)(x1 - (float)n2);
+      if constexpr (V <= 6) {
+        plane[e][6] = n1; plane[e][7] = n2; plane[rows + e][6] = n3;
+      } else {
+        plane[rows + e][5] = n1; plane[rows + e][6] = n2; plane[rows + e][7] = n3;
+      }
+    }
+  }
+  __syncthreads();
+  return t;
+}
+
+template <int V, bool BASE>
+__device__ __forceinline__ void load_vector(const Vectors &a, int o, int u, bool on, float (&t)[V]) {
+  const long long at = on ? (long long)o * a.row_step + (long long)u * a.vec_step : 0;
+  if (a.elem_step == 1 && a.len == V) {
+#pragma unroll
+    for (int j = 0; j < V; ++j) {
+      float x = __half2float(a.W[at + j]);
+      if (BASE) x = __fsub_rn(x, __half2float(a.B[at + j]));
+      t[j] = on ? x : 0.0f;
+    }
+    return;
+  }
+#pragma unroll
+  for (int j = 0; j < V; ++j) {
+    const long long c = at + (long long)(j < a.len ? j : 0) * a.elem_step;
+    float x = __half2float(a.W[c]);
+    if (BASE) x = __fsub_rn(x, __half2float(a.B[c]));
+    t[j] = on && j < a.len ? x : 0.0f;
+  }
+}
+
+// The power of two that scales a difference's elements to below 2^14 (as far as the |c|^2 slots' factor allows).
+template <int V>
+__device__ __forceinline__ int vector_scale(const float (&t)[V], int f) {
+  float most = 0.0f;
+#pragma unroll
+  for (int j = 0; j < V; ++j) most = fmaxf(most, fabsf(t[j]));
+  return most > 0.0f ? min(f + 15, max(f - 14, 14 - __builtin_amdgcn_frexp_expf(most))) : f;
+}
+
+// The factor of the |c|^2 slots, -2^(e - f), as binary16; 0 when that is out of its range (the vector is then not trusted).
+__device__ __forceinline__ _Float16 slot_factor(int e, int f) {
+  const int x = e - f;
+  return x >= -14 && x <= 15 ? (_Float16)(-ldexpf(1.0f, x)) : (_Float16)0.0f;
+}
+
+template <int V>
+__device__ __forceinline__ void set_slots(half8 &b, int half, _Float16 factor) {
+  if constexpr (V <= 6) { b[6] = factor; b[7] = half ? (_Float16)0.0f : factor; }
+  else if (half) { b[5] = factor; b[6] = factor; b[7] = factor; }
+}
+
+// NT: tiles of 32 vectors a wave holds.  SPLIT: `split` waves (a power of two) share a tile of vectors, each taking its share
+// of the table.  The first last_wgs workgroups take `last`, the others `first`.
+template <int V, bool BASE, int NT, bool SPLIT>
+__global__ __launch_bounds__(WAVES * 64, 4) void assign_screen_kernel(Vectors first, Vectors last, int last_wgs, const __half *__restrict__ codebook,
+                                                                       int stride, int k, int bits, int seg_len, int split) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int rows_lds = screen_rows(k);
+  half8 *plane = reinterpret_cast<half8 *>(smem);                                     // [2][rows_lds]
+  float *red = reinterpret_cast<float *>(smem + (size_t)rows_lds * 32);               // [2 * WAVES]
+  unsigned *codes = reinterpret_cast<unsigned *>(red + 2 * WAVES);                    // [WAVES][NT * 32]
+  float *meet = reinterpret_cast<float *>(codes + WAVES * NT * 32);                   // SPLIT: [3][WAVES][64]
+  int *list = reinterpret_cast<int *>(meet + (SPLIT ? 3 * WAVES * 64 : 0));           // tables of several chunks: how many, then which
+  constexpr bool TWO = screen_instructions(V, BASE) == 2;
+  constexpr int TU = 2;                                         // tiles of the table taken at once
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 31, half = lane >> 5;
+  const bool is_last = (int)blockIdx.x < last_wgs;
+  const Vectors a = is_last ? last : first;
+  const int n_chunks = (k + SCREEN_ROWS - 1) / SCREEN_ROWS;
+  const long long items = items_of(a, seg_len);
+  const int groups = SPLIT ? WAVES / split : WAVES, group = SPLIT ? wave / split : wave, part = SPLIT ? wave % split : 0;
+  const int block_items = groups * NT * 32;
+  const int n_blocks = (int)((items + block_items - 1) / block_items);
+  unsigned *my_codes = codes + wave * (NT * 32);
+  TableScale ts = {0, 0.0f, true};
+  if (n_chunks == 1) ts = stage_screen_table<V>(codebook, stride, a.len, k, 0, rows_lds, plane, red);
+
+  const int wg0 = is_last ? blockIdx.x : blockIdx.x - last_wgs, wgs = is_last ? last_wgs : gridDim.x - last_wgs;
+  for (int blk = wg0; blk < n_blocks; blk += wgs) {
+    const long long g0 = (long long)blk * block_items + group * (NT * 32);
+    const Place place(a, g0, items, seg_len);
+    half8 b[NT], b_lo[TWO ? NT : 1];
+    constexpr bool KEEP = BASE && V <= 6;                    // (short enough to stay in registers across the search)
+    float kept[KEEP ? NT : 1][V];
+    int e_of[BASE ? NT : 1];
+    float b1[NT], b2[NT];
+    int id[NT];
+    bool trusted = true;                                     // (of this lane's vectors: every chunk's factor was in range)
+    float h_max = 0.0f;
+    for (int ch = 0; ch < n_chunks; ++ch) {
+      if (n_chunks > 1) {
+        __syncthreads();
+        ts = stage_screen_table<V>(codebook, stride, a.len, k, ch * SCREEN_ROWS, rows_lds, plane, red);
+      }
+      h_max = fmaxf(h_max, ts.h_max);
+      trusted = trusted && ts.fine;
+      if (ch == 0) {
+#pragma unroll
+        for (int u = 0; u < NT; ++u) {
+          int o, p;
+          place.item(u * 32 + n, o, p);
+          float t[V];
+          load_vector<V, BASE>(a, o, p, o < a.rows && p < a.per_row, t);
+          if constexpr (KEEP) {
+#pragma unroll
+            for (int j = 0; j < V; ++j) kept[u][j] = t[j];
+          }
+          int e = 0;
+          if constexpr (BASE) { e = vector_scale<V>(t, ts.f); e_of[u] = e; }
+          half8 hi = {}, lo = {};
+#pragma unroll
+          for (int j = 0; j < V; ++j) {
+            const float x = BASE ? ldexpf(t[j], e) : t[j];
+            const _Float16 xh = (_Float16)x, xl = BASE ? (_Float16)(x - (float)xh) : (_Float16)0.0f;     // (without a base: x is a binary16 number)
+            if constexpr (V <= 6) hi[j] = half ? xl : xh;
+            else if ((j >= 8) == (half != 0)) { hi[j & 7] = xh; lo[j & 7] = xl; }
+          }
+          b[u] = hi;
+          if constexpr (TWO) b_lo[u] = lo;
+          b1[u] = -__builtin_inff(); b2[u] = -__builtin_inff(); id[u] = 0;
+        }
+      }
+      if (ch == 0 || n_chunks > 1) {
+#pragma unroll
+        for (int u = 0; u < NT; ++u) {
+          const _Float16 factor = slot_factor(BASE ? e_of[u] : 0, ts.f);
+          trusted = trusted && factor != (_Float16)0.0f;
+          set_slots<V>(b[u], half, factor);
+        }
+      }
+      const int tiles = (min(k - ch * SCREEN_ROWS, SCREEN_ROWS) + 31) >> 5, rounds = (tiles + TU - 1) / TU;
+      const int step = SPLIT ? split : 1, tile0 = ch * (SCREEN_ROWS / 32);
+      const half8 *mine = plane + (half ? rows_lds : 0) + n;
+      half8 cur[TU];
+#pragma unroll
+      for (int x = 0; x < TU; ++x) cur[x] = mine[(min(part, rounds - 1) * TU + x) * 32];
+      for (int round = part; round < rounds; round += step) {
+        half8 next[TU];
+#pragma unroll
+        for (int x = 0; x < TU; ++x) next[x] = mine[(min(round + step, rounds - 1) * TU + x) * 32];
+        float16v s[TU][NT];
+#pragma unroll
+        for (int x = 0; x < TU; ++x)
+#pragma unroll
+          for (int u = 0; u < NT; ++u) {
+            float16v z;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) z[r] = 0.0f;
+            s[x][u] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cur[x], b[u], z, 0, 0, 0);
+            if constexpr (TWO) s[x][u] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cur[x], b_lo[u], s[x][u], 0, 0, 0);
+          }
+#pragma unroll
+        for (int x = 0; x < TU; ++x)
+#pragma unroll
+          for (int u = 0; u < NT; ++u) {
+            auto max3 = [](float p_, float q_, float r_) { return fmaxf(fmaxf(p_, q_), r_); };
+            const float16v &v = s[x][u];
+            const float m0 = max3(v[0], v[1], v[2]), m1 = max3(v[3], v[4], v[5]), m2 = max3(v[6], v[7], v[8]);
+            const float m3 = max3(v[9], v[10], v[11]), m4 = max3(v[12], v[13], v[14]);
+            const float m = max3(max3(m0, m1, m2), max3(m3, m4, v[15]), m0);
+            const bool up = m > b1[u];
+            b2[u] = __builtin_amdgcn_fmed3f(b1[u], b2[u], m);
+            id[u] = up ? tile0 + round * TU + x : id[u];
+            b1[u] = up ? m : b1[u];
+          }
+#pragma unroll
+        for (int x = 0; x < TU; ++x) {
+          asm volatile("" : "+v"(next[x]));                  // (keeps the reads up there: the compiler would turn them into reads of `cur`)
+          cur[x] = next[x];
+        }
+      }
+    }
+    int my_block[NT];
+#pragma unroll
+    for (int u = 0; u < NT; ++u) my_block[u] = 2 * id[u] + half;
+    if constexpr (SPLIT) {                                   // the waves of a group meet in their first one
+      float *m1 = meet, *m2 = meet + WAVES * 64, *mb = meet + 2 * WAVES * 64;
+      m1[wave * 64 + lane] = b1[0]; m2[wave * 64 + lane] = b2[0]; mb[wave * 64 + lane] = __int_as_float(my_block[0]);
+      __syncthreads();
+      if (part == 0) {
+        for (int w = 1; w < split; ++w) {
+          const float o1 = m1[(wave + w) * 64 + lane], o2 = m2[(wave + w) * 64 + lane];
+          const int ob = __float_as_int(mb[(wave + w) * 64 + lane]);
+          b2[0] = fmaxf(fminf(b1[0], o1), fmaxf(b2[0], o2));
+          if (o1 > b1[0]) { b1[0] = o1; my_block[0] = ob; }
+        }
+      }
+      __syncthreads();
+    }
+    if (n_chunks > 1) {
+      if (threadIdx.x == 0) list[0] = 0;
+      __syncthreads();
+    }
+
+    // the distances as defined, for the 16 centroids of the winning block: eight per lane, the two lanes of a vector then meet
+    const float c_max = __builtin_amdgcn_sqrtf(2.0f * h_max) * 1.001f;
+#pragma unroll
+    for (int u = 0; u < NT; ++u) {
+      if (part != 0) break;
+      __builtin_amdgcn_sched_barrier(0);                     // (one tile's vectors in registers at a time)
+      int o, p;
+      place.item(u * 32 + n, o, p);
+      const bool live = o < a.rows && p < a.per_row;
+      float t[V];
+      if constexpr (KEEP) {
+#pragma unroll
+        for (int j = 0; j < V; ++j) t[j] = kept[u][j];
+      } else if constexpr (BASE) {
+        load_vector<V, BASE>(a, o, p, live, t);
+      } else {                                               // the operand still holds the vector: elements 0 .. 7 in the lower lanes
+        const uint4v mine = __builtin_bit_cast(uint4v, b[u]);
+#pragma unroll
+        for (int d = 0; d < (V + 1) / 2; ++d) {
+          const unsigned w = __shfl(d & 2 ? (d & 1 ? mine.w : mine.z) : (d & 1 ? mine.y : mine.x), d < 4 ? n : n + 32, 64);
+          t[2 * d] = __half2float(__ushort_as_half((unsigned short)(w & 0xFFFFu)));
+          if (2 * d + 1 < V) t[2 * d + 1 < V ? 2 * d + 1 : 0] = __half2float(__ushort_as_half((unsigned short)(w >> 16)));
+        }
+      }
+      const float other = __shfl_xor(b1[u], 32, 64);
+      const bool keep = b1[u] > other || (b1[u] == other && half == 0);
+      const float best_s = fmaxf(b1[u], other);
+      const float second = fmaxf(fminf(b1[u], other), fmaxf(b2[u], __shfl_xor(b2[u], 32, 64)));
+      const int other_block = __shfl_xor(my_block[u], 32, 64);
+      const int block = keep ? my_block[u] : other_block;
+      bool sure = trusted;
+      {
+        float tt = 0.0f;
+#pragma unroll
+        for (int j = 0; j < V; ++j) tt = __fmaf_rn(t[j], t[j], tt);
+        const int e = BASE ? e_of[u] : 0;
+        const float T = __builtin_amdgcn_sqrtf(tt) * 1.001f, down = BASE ? ldexpf(1.0f, -e) : 1.0f, q = 0x1p-12f, qt = 0x1p-12f * down;
+        const float dist = fmaxf(0.0f, tt - 2.0f * best_s * down) + 0x1p-13f * (tt + c_max * c_max);
+        const float R = T + __builtin_amdgcn_sqrtf(dist) * 1.001f;
+        const float eps = 0x1p-20f * ((T + qt) * (R + q) + 0.5f * R * R + 0x1p-26f * (1.0f + down)) + (V + 3) * 0x1p-23f * dist +
+                          0x1p-28f * h_max + 0x1p-37f + 0x1p-21f * down * R;
+        const float gap = (best_s - second) * down;
+        sure = sure && gap > eps;                            // (false when anything is not a number)
+      }
+      float best = __builtin_inff();
+      unsigned arg = 0u;
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        // rows of a lane's results: registers r & 3 of quads of rows 8 apart, the upper lanes' quads 4 below
+        // (rows past the table repeat its last entry, which is never preferred to the entry itself)
+        int row = (block >> 1) * 32 + (block & 1) * 4 + half * 16 + (r & 3) + 8 * (r >> 2);
+        float d;
+        if (n_chunks == 1) {
+          const half8 c0 = plane[row], c1 = plane[V > 8 ? rows_lds + row : row];
+          d = distance<V>(t, [&](int j) -> float { return j < 8 ? (float)c0[j & 7] : (float)c1[j & 7]; });
+        } else {
+          row = min(row, k - 1);
+          const __half *c = codebook + (long long)row * stride;
+          d = distance<V>(t, [&](int j) -> float { const float x = __half2float(c[j < a.len ? j : 0]); return j < a.len ? x : 0.0f; });
+        }
+        if (d < best) { best = d; arg = (unsigned)row; }
+      }
+      {
+        const float od = __shfl_xor(best, 32, 64);
+        const unsigned oa = __shfl_xor(arg, 32, 64);
+        if (od < best || (od == best && oa < arg)) { best = od; arg = oa; }
+      }
+      // vectors whose block is not sure: the wave takes them one at a time, its lanes the centroids in turn
+      if (n_chunks > 1) {
+        if (live && !sure && half == 0) list[1 + atomicAdd(&list[0], 1)] = group * (NT * 32) + u * 32 + n;
+      } else {
+        for (unsigned long long todo = __ballot(live && !sure && half == 0); todo; todo &= todo - 1) {
+          const int w = __builtin_ctzll(todo);
+          float tv[V];
+#pragma unroll
+          for (int j = 0; j < V; ++j) tv[j] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t[j]), w));
+          float bd = __builtin_inff();
+          unsigned bi = 0xFFFFFFFFu;
+#pragma unroll 4
+          for (int i = lane; i < rows_lds; i += 64) {
+            const half8 c0 = plane[i], c1 = plane[V > 8 ? rows_lds + i : i];
+            const float d = distance<V>(tv, [&](int j) -> float { return j < 8 ? (float)c0[j & 7] : (float)c1[j & 7]; });
+            if (d < bd) { bd = d; bi = (unsigned)i; }
+          }
+          wave_arg_min(bd, bi);
+          if (n == w) arg = bi == 0xFFFFFFFFu ? 0u : bi;       // (no distance below infinity: the first centroid)
+        }
+      }
+      if (half == 0) my_codes[u * 32 + n] = live ? arg : 0u;
+    }
+    if (n_chunks > 1) {
+      // the vectors that are not sure, against the whole table: every wave takes a share of it
+      __syncthreads();
+      const int n_list = list[0], share = (k + WAVES * 64 - 1) / (WAVES * 64) * 64, from = wave * share, to = min(k, from + share);
+      float *found_d = reinterpret_cast<float *>(plane);                    // [n_list][WAVES], over the last chunk
+      unsigned *found_i = reinterpret_cast<unsigned *>(plane) + NT * 32 * WAVES * WAVES;
+      for (int x = 0; x < n_list; ++x) {
+        const int which = list[1 + x];                                       // group and item of the group
+        const Place where(a, (long long)blk * block_items + which / (NT * 32) * (NT * 32), items, seg_len);
+        int o, p;
+        where.item(which % (NT * 32), o, p);
+        float t[V];
+        load_vector<V, BASE>(a, o, p, true, t);
+        float bd = __builtin_inff();
+        unsigned bi = 0xFFFFFFFFu;
+#pragma unroll 4
+        for (int i0 = from; i0 < to; i0 += 64) {
+          const int i = min(i0 + lane, k - 1);
+          const __half *c = codebook + (long long)i * stride;
+          const float d = distance<V>(t, [&](int j) -> float { const float y = __half2float(c[j]); return j < a.len ? y : 0.0f; });
+          if (d < bd) { bd = d; bi = (unsigned)i; }
+        }
+        wave_arg_min(bd, bi);
+        if (lane == 0) { found_d[x * WAVES + wave] = bd; found_i[x * WAVES + wave] = bi; }
+      }
+      __syncthreads();
+      if ((int)threadIdx.x < n_list) {
+        float bd = __builtin_inff();
+        unsigned bi = 0u;                                    // (no distance below infinity: the first centroid)
+        for (int w = 0; w < WAVES; ++w) {                    // ascending shares of the table: the first of equal distances stays
+          const float d = found_d[threadIdx.x * WAVES + w];
+          if (d < bd) { bd = d; bi = found_i[threadIdx.x * WAVES + w]; }
+        }
+        const int which = list[1 + threadIdx.x];
+        codes[which / (NT * 32) * (SPLIT ? split : 1) * (NT * 32) + which % (NT * 32)] = bi;
+      }
+      __syncthreads();
+    }
+    if (part != 0) continue;                                 // (every wave passes the same barriers: they are all above)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    if (a.scatter_bit >= 0) {
+      for (int x = lane; x < NT * 32; x += 64) {
+        int o, p;
+        place.item(x, o, p);
+        if (o < a.rows && p < a.per_row) scatter_index(a, p, my_codes[x], bits);
+      }
+    } else {
+      pack_items(a, place, 0, NT * 32, seg_len, bits, my_codes, lane);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+}
+
+// ---- every distance on the vector ALUs ------------------------------------------------------------------------------------
+//
+// Short tables: a lane per vector, the table in LDS as binary32 and read with wave-uniform addresses.  Bound by the loads of W and
+// by how many waves there are to wait for them (127 x 1408, v = 2, k = 16, with a base: 23 us at a lane per 8 vectors and 1024
+// lanes a workgroup).
+constexpr int SHORT_TABLE = 64, SHORT_THREADS = 256;
+
+template <int V>
+__global__ __launch_bounds__(SHORT_THREADS) void assign_short_kernel(Vectors first, Vectors last, int last_wgs, const __half *__restrict__ codebook,
+                                                                     int stride, int k, int bits, int seg_len) {
+  __shared__ __attribute__((aligned(16))) float table[SHORT_TABLE * V];
+  __shared__ unsigned codes[SHORT_THREADS];
+  const bool is_last = (int)blockIdx.x < last_wgs;
+  const Vectors a = is_last ? last : first;
+  const long long items = items_of(a, seg_len), g0 = (long long)(is_last ? blockIdx.x : blockIdx.x - last_wgs) * SHORT_THREADS;
+  const int lane = threadIdx.x & 63, wave0 = threadIdx.x & ~63;
+  const Place place(a, g0 + wave0, items, seg_len);
+  int o, p;
+  place.item(lane, o, p);
+  const bool live = o < a.rows && p < a.per_row;
+  float t[V];
+  if (a.B) load_vector<V, true>(a, o, p, live, t);
+  else load_vector<V, false>(a, o, p, live, t);
+  for (int e = threadIdx.x; e < k * V; e += SHORT_THREADS)
+    table[e] = e % V < a.len ? __half2float(codebook[(long long)(e / V) * stride + e % V]) : 0.0f;
+  __syncthreads();
+  float best = __builtin_inff();
+  unsigned arg = 0u;
+#pragma unroll 4
+  for (int i = 0; i < k; ++i) {
+    const float d = distance<V>(t, [&](int j) -> float { return table[i * V + j]; });
+    if (d < best) { best = d; arg = (unsigned)i; }
+  }
+  if (a.scatter_bit >= 0) {
+    if (live) scatter_index(a, p, arg, bits);
+    return;
+  }
+  codes[threadIdx.x] = live ? arg : 0u;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  pack_items(a, place, 0, 64, seg_len, bits, codes + wave0, lane);
+}
+
+// Long vectors.  A lane owns `seg` consecutive vectors of a row, seg = 8, 16 or 32 chosen so that they fill whole dwords of
+// the row's index stream (lanes never share an output dword), and takes them VB at a time against the whole table, which sits in LDS as
+// binary32 and is read with wave-uniform addresses (one broadcast read feeds VB x 64 distances).  Tables larger than
+// the LDS chunk are walked chunk by chunk with the running minimum kept in registers.
 
 constexpr int AT = 1024;                 // threads per workgroup
 constexpr unsigned LDS_TABLE_BYTES = 128u * 1024u;
@@ -24,27 +590,26 @@ constexpr unsigned LDS_TABLE_BYTES = 128u * 1024u;
 constexpr int table_stride(int v) { return v <= 2 ? v : v <= 4 ? 4 : v <= 8 ? 8 : 16; }
 
 template <int V, int VB>
-__global__ __launch_bounds__(AT) void assign_kernel(const __half *__restrict__ W, const __half *__restrict__ B, long long ld, int rows,
-                                                    int p_full, int p_all, const __half *__restrict__ codebook, int k, int bits,
-                                                    int chunk, int seg_len, unsigned char *__restrict__ idx, long long idx_stride, int down_rows) {
+__global__ __launch_bounds__(AT) void assign_kernel(Vectors first, Vectors last, int last_wgs, const __half *__restrict__ codebook, int stride, int k,
+                                                    int bits, int chunk, int seg_len) {
   extern __shared__ __attribute__((aligned(16))) float table[];       // [chunk][TS]: rows padded to 16-byte reads
   constexpr int TS = table_stride(V);
-  const int segs = (p_all + seg_len - 1) / seg_len;
-  const long long item = (long long)blockIdx.x * AT + threadIdx.x;
-  const bool live = item < (long long)rows * segs;
+  const bool is_last = (int)blockIdx.x < last_wgs;
+  const Vectors a = is_last ? last : first;
+  const int segs = (a.per_row + seg_len - 1) / seg_len;
+  const long long item = (long long)(is_last ? blockIdx.x : blockIdx.x - last_wgs) * AT + threadIdx.x;
+  const bool live = item < (long long)a.rows * segs;
   const int o = live ? (int)(item / segs) : 0;
   const int seg = live ? (int)(item - (long long)o * segs) : 0;
-  // down_rows > 0: the vectors run down the columns of a matrix of down_rows rows (Sec. 3.1, Algorithm 1).  "Row" o is then
-  // the index stream of rows [o V, o V + V), its vector u is column u, element j of it sits in row o V + j; a stream whose
-  // block of rows is cut off at the end of the matrix is left to the second kernel as a whole.
-  const bool whole = down_rows == 0 || (o + 1) * V <= down_rows;
-  unsigned *out = reinterpret_cast<unsigned *>(idx + (long long)o * idx_stride) + (long long)seg * (seg_len * bits / 32);
+  unsigned *row = reinterpret_cast<unsigned *>(a.idx + (long long)o * a.idx_stride);
+  long long at = (long long)seg * (seg_len * bits / 32);
   unsigned long long buf = 0;
   int fill = 0;
   const int n_chunks = (k + chunk - 1) / chunk;
   auto stage = [&](int c0) {             // centroids [c0, c0 + chunk) as binary32; past k: never read
     const int n = min(chunk, k - c0) * V;
-    for (int e = threadIdx.x; e < n; e += AT) table[(e / V) * TS + e % V] = __half2float(codebook[(long long)c0 * V + e]);
+    for (int e = threadIdx.x; e < n; e += AT)
+      table[(e / V) * TS + e % V] = e % V < a.len ? __half2float(codebook[(long long)(c0 + e / V) * stride + e % V]) : 0.0f;
   };
   if (n_chunks == 1) { stage(0); __syncthreads(); }
   for (int r = 0; r < seg_len / VB; ++r) {                   // every lane walks every round: the barriers below need all of them
@@ -54,14 +619,9 @@ __global__ __launch_bounds__(AT) void assign_kernel(const __half *__restrict__ W
 #pragma unroll
     for (int u = 0; u < VB; ++u) {
       best[u] = __builtin_inff(); arg[u] = 0;
-      const bool on = live && whole && p0 + u < p_full;
-#pragma unroll
-      for (int j = 0; j < V; ++j) {
-        const long long c = down_rows ? ((long long)o * V + j) * ld + (p0 + u) : (long long)o * ld + (long long)(p0 + u) * V + j;
-        float x = on ? __half2float(W[c]) : 0.0f;
-        if (on && B) x = __fsub_rn(x, __half2float(B[c]));
-        t[u][j] = x;
-      }
+      const bool on = live && p0 + u < a.per_row;
+      if (a.B) load_vector<V, true>(a, o, p0 + u, on, t[u]);
+      else load_vector<V, false>(a, o, p0 + u, on, t[u]);
     }
     for (int ch = 0; ch < n_chunks; ++ch) {
       if (n_chunks > 1) { __syncthreads(); stage(ch * chunk); __syncthreads(); }
@@ -73,158 +633,128 @@ __global__ __launch_bounds__(AT) void assign_kernel(const __half *__restrict__ W
         for (int j = 0; j < V; ++j) c[j] = table[i * TS + j];
 #pragma unroll
         for (int u = 0; u < VB; ++u) {
-          float d = 0.0f;
-#pragma unroll
-          for (int j = 0; j < V; ++j) {
-            const float diff = __fsub_rn(t[u][j], c[j]);
-            d = __fmaf_rn(diff, diff, d);
-          }
+          const float d = distance<V>(t[u], [&](int j) -> float { return c[j]; });
           if (d < best[u]) { best[u] = d; arg[u] = ch * chunk + i; }
         }
       }
     }
-    // append the round's indices to the lane's bit stream; a row's cut-off last vector gets zero bits here
+    // append the round's indices to the lane's bit stream
 #pragma unroll
     for (int u = 0; u < VB; ++u) {
-      if (live && p0 + u < p_all) {
-        const unsigned code = whole && p0 + u < p_full ? (unsigned)arg[u] : 0u;
-        buf |= (unsigned long long)code << fill;
+      if (live && p0 + u < a.per_row) {
+        if (a.scatter_bit >= 0) { scatter_index(a, p0 + u, (unsigned)arg[u], bits); continue; }
+        buf |= (unsigned long long)arg[u] << fill;
         fill += bits;
-        if (fill >= 32) { *out++ = (unsigned)buf; buf >>= 32; fill -= 32; }
+        if (fill >= 32) { store_dword(a, row + at, at, (unsigned)buf); ++at; buf >>= 32; fill -= 32; }
       }
     }
   }
-  if (live && fill > 0) *out = (unsigned)buf;              // the row's last, partly filled dword: upper bits zero
+  if (live && fill > 0) store_dword(a, row + at, at, (unsigned)buf);              // the row's last, partly filled dword: upper bits zero
 }
 
-// The cut-off last vector of every row (row length not a multiple of v): distance over its `len` elements only.
-// One wave per row: lane l takes centroids l, l + 64, ... in ascending order (strict "less" keeps the lowest index of
-// equal distances among its own), then the lanes meet with the same rule -- smaller distance, else smaller index.
-// Runs after assign_kernel on the same stream and sets the vector's bits, which that kernel left zero.
-__global__ __launch_bounds__(256) void assign_tail_kernel(const __half *__restrict__ W, const __half *__restrict__ B, long long ld, int rows,
-                                                          int p_full, int v, int len, const __half *__restrict__ codebook, int k, int bits,
-                                                          unsigned char *__restrict__ idx, long long idx_stride) {
-  const int o = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (o >= rows) return;
-  float t[16];
-  for (int j = 0; j < len; ++j) {
-    const long long c = (long long)o * ld + (long long)p_full * v + j;
-    float x = __half2float(W[c]);
-    if (B) x = __fsub_rn(x, __half2float(B[c]));
-    t[j] = x;
-  }
-  float best = __builtin_inff();
-  unsigned arg = 0xFFFFFFFFu;                                // a lane without centroids (k < 64) never wins
-  for (int i = lane; i < k; i += 64) {
-    float d = 0.0f;
-    for (int j = 0; j < len; ++j) {
-      const float diff = __fsub_rn(t[j], __half2float(codebook[(long long)i * v + j]));
-      d = __fmaf_rn(diff, diff, d);
-    }
-    if (d < best || arg == 0xFFFFFFFFu) { best = d; arg = (unsigned)i; }
-  }
-  for (int s = 32; s > 0; s >>= 1) {
-    const float od = __shfl_xor(best, s, 64);
-    const unsigned oa = __shfl_xor(arg, s, 64);
-    if (oa != 0xFFFFFFFFu && (arg == 0xFFFFFFFFu || od < best || (od == best && oa < arg))) { best = od; arg = oa; }
-  }
-  if (lane != 0) return;
-  unsigned *row = reinterpret_cast<unsigned *>(idx + (long long)o * idx_stride);
-  const long long bit = (long long)p_full * bits;
-  const int sh = (int)(bit & 31);
-  row[bit >> 5] |= arg << sh;
-  if (sh + bits > 32) row[(bit >> 5) + 1] |= arg >> (32 - sh);
-}
-
-// The cut-off last block of rows when the vectors run down the columns: every vector of the last index stream has only
-// `len` elements.  One wave per column, as above; the streams' bits are set with an atomic OR because neighbouring columns
-// share dwords (integer, so the result does not depend on the order).
-__global__ __launch_bounds__(256) void assign_tail_down_kernel(const __half *__restrict__ W, const __half *__restrict__ B, long long ld, int cols,
-                                                               int row0, int v, int len, const __half *__restrict__ codebook, int k, int bits,
-                                                               unsigned *__restrict__ stream) {
-  const int n = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (n >= cols) return;
-  float t[16];
-  for (int j = 0; j < len; ++j) {
-    const long long c = (long long)(row0 + j) * ld + n;
-    float x = __half2float(W[c]);
-    if (B) x = __fsub_rn(x, __half2float(B[c]));
-    t[j] = x;
-  }
-  float best = __builtin_inff();
-  unsigned arg = 0xFFFFFFFFu;
-  for (int i = lane; i < k; i += 64) {
-    float d = 0.0f;
-    for (int j = 0; j < len; ++j) {
-      const float diff = __fsub_rn(t[j], __half2float(codebook[(long long)i * v + j]));
-      d = __fmaf_rn(diff, diff, d);
-    }
-    if (d < best || arg == 0xFFFFFFFFu) { best = d; arg = (unsigned)i; }
-  }
-  for (int s = 32; s > 0; s >>= 1) {
-    const float od = __shfl_xor(best, s, 64);
-    const unsigned oa = __shfl_xor(arg, s, 64);
-    if (oa != 0xFFFFFFFFu && (arg == 0xFFFFFFFFu || od < best || (od == best && oa < arg))) { best = od; arg = oa; }
-  }
-  if (lane != 0) return;
-  const long long bit = (long long)n * bits;
-  const int sh = (int)(bit & 31);
-  atomicOr(stream + (bit >> 5), arg << sh);
-  if (sh + bits > 32) atomicOr(stream + (bit >> 5) + 1, arg >> (32 - sh));
-}
+// vectors per segment: the fewest whose bits fill whole dwords
+int segment(int bits) { return bits % 4 == 0 ? 8 : bits % 2 == 0 ? 16 : 32; }
 
 template <int V>
-int launch_v(const __half *W, const __half *B, long long ld, int rows, int p_full, int p_all, const __half *codebook, int k, int bits,
-             unsigned char *idx, long long idx_stride, hipStream_t s, int down_rows = 0) {
+int launch_plain(const Vectors &first, const Vectors &last, const __half *codebook, int k, int bits, hipStream_t s) {
   constexpr int VB = V <= 8 ? 8 : 4;       // vectors a lane holds at once: each centroid read from LDS serves VB x 64 distances
   auto kernel = assign_kernel<V, VB>;
   VQ_ALLOW_FULL_LDS(kernel);
   const int chunk = min(k, (int)(LDS_TABLE_BYTES / (table_stride(V) * sizeof(float))));
-  // vectors per lane: the fewest (most lanes) whose bits fill whole dwords
-  const int seg_len = bits % 4 == 0 ? 8 : bits % 2 == 0 ? 16 : 32;
-  const long long items = (long long)rows * ((p_all + seg_len - 1) / seg_len);
-  const long long blocks = (items + AT - 1) / AT;
+  const int seg_len = segment(bits);
+  auto wgs = [&](const Vectors &a) { return (items_of(a, seg_len) / seg_len + AT - 1) / AT; };
+  const long long blocks = wgs(first) + wgs(last);
   if (blocks > 0x7fffffffLL) return VQ_ERR_UNSUPPORTED;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(AT), (size_t)chunk * table_stride(V) * sizeof(float), s, W, B, ld, rows, p_full, p_all,
-                     codebook, k, bits, chunk, seg_len, idx, idx_stride, down_rows);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(AT), (size_t)chunk * table_stride(V) * sizeof(float), s, first, last, (int)wgs(last),
+                     codebook, V, k, bits, chunk, seg_len);
   return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
+}
+
+template <int V>
+int launch_short(const Vectors &first, const Vectors &last, const __half *codebook, int k, int bits, hipStream_t s) {
+  const int seg_len = segment(bits);
+  const long long last_wgs = (items_of(last, seg_len) + SHORT_THREADS - 1) / SHORT_THREADS;
+  const long long blocks = (items_of(first, seg_len) + SHORT_THREADS - 1) / SHORT_THREADS + last_wgs;
+  if (blocks > 0x7fffffffLL) return VQ_ERR_UNSUPPORTED;
+  hipLaunchKernelGGL((assign_short_kernel<V>), dim3((unsigned)blocks), dim3(SHORT_THREADS), 0, s, first, last, (int)last_wgs, codebook, V, k, bits, seg_len);
+  return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
+}
+
+template <int V, bool BASE, int NT, bool SPLIT>
+int launch_screen_nt(const Vectors &first, const Vectors &last, const __half *codebook, int k, int bits, int split, hipStream_t s) {
+  auto kernel = assign_screen_kernel<V, BASE, NT, SPLIT>;
+  VQ_ALLOW_FULL_LDS(kernel);
+  const int seg_len = segment(bits), block_items = WAVES / split * NT * 32;
+  const size_t lds = (size_t)screen_rows(k) * 32 + 2 * WAVES * sizeof(float) + WAVES * NT * 32 * sizeof(unsigned) + (SPLIT ? 3 * WAVES * 64 * sizeof(float) : 0) +
+                     (k > SCREEN_ROWS ? (WAVES / split * NT * 32 + 1) * sizeof(int) : 0);
+  const long long blocks = (items_of(first, seg_len) + block_items - 1) / block_items;
+  long long last_wgs = (items_of(last, seg_len) + block_items - 1) / block_items, wgs = blocks;
+  if (blocks > 0x7fffffffLL || last_wgs > 0x7fffffffLL) return VQ_ERR_UNSUPPORTED;
+  // one workgroup fits a compute unit; it keeps its table and walks the blocks (tables of several chunks are staged anew for
+  // every block anyway).  The cut-off vectors' workgroups come first, the others share what is left.
+  if (k <= SCREEN_ROWS && blocks + last_wgs > cu_count()) {
+    last_wgs = min(last_wgs, (long long)max(1, cu_count() / 4));
+    if (items_of(last, seg_len) == 0) last_wgs = 0;
+    wgs = min(blocks, cu_count() - last_wgs);
+  }
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(wgs + last_wgs)), dim3(WAVES * 64), lds, s, first, last, (int)last_wgs, codebook, V, k, bits, seg_len, split);
+  return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
+}
+
+template <int V, bool BASE>
+int launch_screen(const Vectors &first, const Vectors &last, const __half *codebook, int k, int bits, hipStream_t s) {
+  const long long tiles = (items_of(first, segment(bits)) + items_of(last, segment(bits))) / 32;
+  // 64 vectors of a wave share every table read, 32 where that leaves fewer waves idle in the last round (a round of the
+  // smaller blocks takes about 0.6 of the time), and with less than one round of those the waves of a workgroup
+  // share the table's rows until there is about one
+  const long long waves = (long long)cu_count() * WAVES, rounds2 = (tiles + 2 * waves - 1) / (2 * waves), rounds1 = (tiles + waves - 1) / waves;
+  if (10 * rounds2 <= 6 * rounds1) return launch_screen_nt<V, BASE, 2, false>(first, last, codebook, k, bits, 1, s);
+  int split = 1;
+  while (split < WAVES && tiles * split * 2 <= waves && split * 128 < min(k, SCREEN_ROWS)) split *= 2;
+  return launch_screen_nt<V, BASE, 1, true>(first, last, codebook, k, bits, split, s);
+}
+
+template <int V>
+int launch_v(const Vectors &first, const Vectors &last, const __half *codebook, int k, int bits, hipStream_t s) {
+  // (a table of one or two blocks of 32 is compared as fast as it is screened; 13: three slots for |c|^2 beside the elements)
+  if (k < SHORT_TABLE) return launch_short<V>(first, last, codebook, k, bits, s);
+  if constexpr (V <= 13) {
+    return first.B ? launch_screen<V, true>(first, last, codebook, k, bits, s) : launch_screen<V, false>(first, last, codebook, k, bits, s);
+  } else {
+    return launch_plain<V>(first, last, codebook, k, bits, s);
+  }
+}
+
+int launch(int v, const Vectors &first, const Vectors &last, const __half *codebook, int k, int bits, hipStream_t s) {
+  switch (v) {
+#define VQ_V(N) case N: return launch_v<N>(first, last, codebook, k, bits, s);
+    VQ_V(1) VQ_V(2) VQ_V(3) VQ_V(4) VQ_V(5) VQ_V(6) VQ_V(7) VQ_V(8) VQ_V(9) VQ_V(10) VQ_V(11) VQ_V(12) VQ_V(13) VQ_V(14) VQ_V(15) VQ_V(16)
+#undef VQ_V
+    default: return VQ_ERR_UNSUPPORTED;
+  }
 }
 
 }  // namespace
 
 int launch_assign(const __half *W, const __half *B, long long ld, int rows, int cols, const __half *codebook, int v, int k,
                   unsigned char *idx, long long idx_stride, hipStream_t s) {
-  const int bits = index_bits(k);
-  const int p_full = cols / v, p_all = (cols + v - 1) / v;
-  int rc = VQ_ERR_UNSUPPORTED;
-  switch (v) {
-#define VQ_V(N) case N: rc = launch_v<N>(W, B, ld, rows, p_full, p_all, codebook, k, bits, idx, idx_stride, s); break;
-    VQ_V(1) VQ_V(2) VQ_V(3) VQ_V(4) VQ_V(5) VQ_V(6) VQ_V(7) VQ_V(8) VQ_V(9) VQ_V(10) VQ_V(11) VQ_V(12) VQ_V(13) VQ_V(14) VQ_V(15) VQ_V(16)
-#undef VQ_V
-    default: break;
-  }
-  if (rc != VQ_OK || p_all == p_full) return rc;
-  hipLaunchKernelGGL(assign_tail_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, W, B, ld, rows, p_full, v, cols - p_full * v,
-                     codebook, k, bits, idx, idx_stride);
-  return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
+  const int bits = index_bits(k), full = cols / v, len = cols % v;
+  const long long at = (long long)full * v, end = (long long)full * bits;
+  const Vectors whole = {W, B, ld, v, 1, full ? rows : 0, full, v, idx, idx_stride, len ? end : (end + 31) / 32 * 32, -1};
+  // the cut-off last vector of every row, compared over its own elements
+  const Vectors last = {W + at, B ? B + at : nullptr, 0, ld, 1, len ? 1 : 0, rows, len, idx, idx_stride, 0, end};
+  return launch(v, whole, last, codebook, k, bits, s);
 }
 
-// Vectors down the columns of W [rows][ld]: index streams [ceil(rows / v)][idx_stride], one index per column.
+// Vectors down the columns of W [rows][ld] (Sec. 3.1, Algorithm 1): index streams [ceil(rows / v)][idx_stride], one index per column.
 int launch_assign_down(const __half *W, const __half *B, long long ld, int rows, int cols, const __half *codebook, int v, int k,
                        unsigned char *idx, long long idx_stride, hipStream_t s) {
-  const int bits = index_bits(k);
-  const int streams = (rows + v - 1) / v;
-  int rc = VQ_ERR_UNSUPPORTED;
-  switch (v) {
-#define VQ_V(N) case N: rc = launch_v<N>(W, B, ld, streams, cols, cols, codebook, k, bits, idx, idx_stride, s, rows); break;
-    VQ_V(1) VQ_V(2) VQ_V(3) VQ_V(4) VQ_V(5) VQ_V(6) VQ_V(7) VQ_V(8) VQ_V(9) VQ_V(10) VQ_V(11) VQ_V(12) VQ_V(13) VQ_V(14) VQ_V(15) VQ_V(16)
-#undef VQ_V
-    default: break;
-  }
-  if (rc != VQ_OK || rows % v == 0) return rc;
-  hipLaunchKernelGGL(assign_tail_down_kernel, dim3((unsigned)((cols + 3) / 4)), dim3(256), 0, s, W, B, ld, cols, (streams - 1) * v, v,
-                     rows - (streams - 1) * v, codebook, k, bits, reinterpret_cast<unsigned *>(idx + (long long)(streams - 1) * idx_stride));
-  return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
+  const int bits = index_bits(k), full = rows / v, len = rows % v;
+  const long long at = (long long)full * v * ld, end = ((long long)cols * bits + 31) / 32 * 32;
+  const Vectors whole = {W, B, v * ld, 1, ld, full, cols, v, idx, idx_stride, end, -1};
+  // the cut-off last block of rows: one stream of shorter vectors
+  const Vectors last = {W + at, B ? B + at : nullptr, 0, 1, ld, len ? 1 : 0, cols, len, idx + (long long)full * idx_stride, idx_stride, end, -1};
+  return launch(v, whole, last, codebook, k, bits, s);
 }
 
 }  // namespace vq

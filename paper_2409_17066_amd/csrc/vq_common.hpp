@@ -139,6 +139,20 @@ __device__ __forceinline__ float wave_sum(float x) {
 #undef VQ_DPP_ADD
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 63));
 }
+
+// Minimum of an unsigned value over the wave, in every lane: shifts within rows of 16 lanes, then the row broadcasts
+// (lanes without a source keep the identity), then the last lane's value read back.
+__device__ __forceinline__ unsigned wave_min_u32(unsigned v) {
+#define VQ_DPP_MIN(CTRL, ROWS) v = min(v, (unsigned)__builtin_amdgcn_update_dpp((int)0xFFFFFFFFu, (int)v, CTRL, ROWS, 0xF, false))
+  VQ_DPP_MIN(0x111, 0xF);      // row_shr:1
+  VQ_DPP_MIN(0x112, 0xF);      // row_shr:2
+  VQ_DPP_MIN(0x114, 0xF);      // row_shr:4
+  VQ_DPP_MIN(0x118, 0xF);      // row_shr:8  -> lane 15 of every row holds the row's minimum
+  VQ_DPP_MIN(0x142, 0xA);      // row_bcast:15 into rows 1 and 3
+  VQ_DPP_MIN(0x143, 0xC);      // row_bcast:31 into rows 2 and 3 -> lane 63 holds the wave's minimum
+#undef VQ_DPP_MIN
+  return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
 #endif
 
 }  // namespace vq

@@ -134,3 +134,52 @@ def test_encode_then_decode_in_the_papers_orientation(gpu_lib):
     again = gpu_lib.assign(What, torch.from_numpy(L.codebook).cuda(), orientation=1)
     torch.cuda.synchronize()
     assert torch.equal(again, idx)
+
+
+# rows, cols, v, k, base, values: the matrix-core screening at its edges -- one block of 32 centroids more or less, the last
+# chunk of a table, the vector lengths at which operands change their layout, both tile counts a wave takes, and values that
+# its rounding bounds have to hold for
+SCREEN = {
+    "k63_vector_alus": (40, 600, 6, 63, False, "normal"),
+    "k64": (40, 600, 6, 64, False, "normal"),
+    "k65_one_row_past_a_block": (40, 600, 6, 65, True, "normal"),
+    "k4095": (20, 606, 6, 4095, False, "normal"),
+    "k4097_second_chunk_of_one": (9, 603, 6, 4097, False, "normal"),
+    "v7_base_two_instructions": (33, 700, 7, 300, True, "normal"),
+    "v13_base_longest": (20, 650, 13, 1000, True, "normal"),
+    "v14_vector_alus": (20, 650, 14, 300, False, "normal"),
+    "many_vectors": (1100, 1000, 2, 64, False, "normal"),
+    "many_vectors_base_v8": (2100, 1003, 8, 64, True, "normal"),
+    "equal_entries": (60, 600, 6, 512, False, "ties"),
+    "equal_entries_base": (60, 600, 6, 512, True, "ties"),
+    "nearly_equal_entries": (60, 600, 6, 512, False, "close"),
+    "subnormal_values": (40, 600, 6, 256, False, "tiny"),
+    "subnormal_values_base": (40, 600, 8, 256, True, "tiny"),
+    "values_near_the_top": (40, 600, 6, 256, False, "huge"),
+    "spread_over_magnitudes": (60, 600, 6, 1024, False, "spread"),
+    "spread_over_magnitudes_base": (60, 600, 12, 1024, True, "spread"),
+}
+
+
+@pytest.mark.parametrize("name", list(SCREEN))
+def test_assign_screening_edges(gpu_lib, name):
+    import torch
+    rows, cols, v, k, with_base, values = SCREEN[name]
+    seed = 7300 + list(SCREEN).index(name)
+    scale = {"tiny": 2e-6, "huge": 9000.0}.get(values, 0.02)
+    W, C, B = (s.normal(seed + 100 * i, n, scale) for i, n in enumerate((rows * cols, k * v, rows * cols)))
+    if values == "spread":
+        W, C, B = (a * np.exp(2.0 * s.normal(seed + 100 * i + 50, a.size, 1.0)) for i, a in enumerate((W, C, B)))
+    W, C = s.to_fp16(W).reshape(rows, cols), s.to_fp16(C).reshape(k, v)
+    if values == "ties":
+        C[k // 2:] = C[: k - k // 2][::-1]
+    if values == "close":              # the second half differs from the first by one unit in the last place of one element
+        C[k // 2:] = C[: k - k // 2]
+        C[k // 2:, 0] = np.nextafter(C[k // 2:, 0], np.float16(1))
+    B = s.to_fp16(B).reshape(rows, cols) if with_base else None
+    for orientation in (0, 1):
+        idx = gpu_lib.assign(torch.from_numpy(W).cuda(), torch.from_numpy(C).cuda(), base=torch.from_numpy(B).cuda() if with_base else None,
+                             orientation=orientation)
+        torch.cuda.synchronize()
+        want = oracle.assign(W, C, base=B, orientation=orientation)
+        assert np.array_equal(idx.cpu().numpy(), s.pack_indices(want, oracle.index_bits(k), idx.shape[1])), (name, orientation)
