@@ -4,6 +4,9 @@
 // 3.2.2) -- and the column's error, divided by the diagonal entry of the matrix the algorithm calls H^-1, is spread over
 // the later columns: inside a block of B columns at once, over the rest of the matrix at the end of the block.
 //
+// vq_quantize_loop.hip takes tables of up to 4096 entries (and most pairs of them) in one launch; the kernels here take the rest: larger
+// tables, two large ones of long vectors.
+//
 // The rows of the matrix never meet in this loop: a vector's v rows only ever read their own weights and rows of H^-1.
 // So one wave owns one stack position (v rows) for a whole block of columns and keeps its v x B tile of running weights
 // in registers (lane l holds columns l and l + 64 of the block).  The columns of a position are a dependent chain, so what
@@ -11,17 +14,13 @@
 // centroid, as in vq_assign, whose distance arithmetic this follows): four waves share it, each a quarter of the
 // centroids over its 64 lanes, and meet through LDS.  The end-of-block update W[:, rest] -= E * Hinv[block, rest] is a
 // dense binary32 product and runs on the matrix cores (v_mfma_f32_32x32x2_f32) from LDS tiles.
-#include "vq_common.hpp"
+#include "vq_quantize.hpp"
 
 namespace vq {
 namespace {
 
-typedef float float16v __attribute__((ext_vector_type(16)));
-
 constexpr int QS = 3;            // stack positions per workgroup of the column kernel
 constexpr int SW = 4;            // waves that share the search of one position
-constexpr int QB = 128;          // most columns per block: two per lane
-constexpr int CPL = QB / 64;
 
 constexpr int entry_halfs(int v) { return v <= 4 ? 4 : v <= 8 ? 8 : 16; }     // table entries padded to 8, 16 or 32 bytes
 
@@ -35,51 +34,6 @@ struct QArgs {
   float *T; long long ldt;
   float *E;                                                   // [rows][QB]: the block's scaled errors
 };
-
-// smaller distance, else smaller index: the rule by which the lanes' candidates meet.  Distances are sums of squares, so
-// their bit patterns order like the numbers: the smallest pattern first, then the smallest index among its holders.
-__device__ __forceinline__ void wave_arg_min(float &d, unsigned &i) {
-  const unsigned bits = __float_as_uint(d);
-  const unsigned lowest = wave_min_u32(bits);
-  i = wave_min_u32(bits == lowest ? i : 0xFFFFFFFFu);
-  d = __uint_as_float(lowest);
-}
-
-typedef unsigned uint4v __attribute__((ext_vector_type(4)));
-typedef unsigned uint2v __attribute__((ext_vector_type(2)));
-
-// One padded table entry (EH halfs) as EH / 2 dwords.  From LDS the read is issued from inline assembly as one or two whole
-// 16-byte reads (8 bytes for the smallest entries): left to the compiler, a read whose tail is unused is narrowed and
-// split into 2- and 8-byte reads at odd offsets, which the LDS serves many times slower.  The caller waits
-// (lds_reads_done) before it looks at the registers.
-template <int EH>
-__device__ __forceinline__ void read_entry_lds(unsigned (&dst)[EH / 2], unsigned lds_addr) {
-  if constexpr (EH == 4) {
-    uint2v r;
-    asm volatile("ds_read_b64 %0, %1" : "=v"(r) : "v"(lds_addr));
-    dst[0] = r.x; dst[1] = r.y;
-  } else {
-#pragma unroll
-    for (int q = 0; q < EH / 8; ++q) {
-      uint4v r;
-      if (q == 0) asm volatile("ds_read_b128 %0, %1" : "=v"(r) : "v"(lds_addr));
-      else asm volatile("ds_read_b128 %0, %1 offset:16" : "=v"(r) : "v"(lds_addr));
-      dst[4 * q] = r.x; dst[4 * q + 1] = r.y; dst[4 * q + 2] = r.z; dst[4 * q + 3] = r.w;
-    }
-  }
-}
-template <int N>
-__device__ __forceinline__ void lds_reads_done(unsigned (&regs)[N]) {
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-  for (int i = 0; i < N; ++i) asm volatile("" : "+v"(regs[i]));      // nothing reads them ahead of the wait
-}
-template <int EH>
-__device__ __forceinline__ void read_entry_global(unsigned (&dst)[EH / 2], const __half *entry) {
-#pragma unroll
-  for (int q = 0; q < EH / 2; ++q) dst[q] = reinterpret_cast<const unsigned *>(entry)[q];
-}
-__device__ __forceinline__ float half_of(unsigned dword, int hi) { return __half2float(__ushort_as_half((unsigned short)(hi ? dword >> 16 : dword & 0xFFFFu))); }
 
 // Candidate of one wave for the nearest of `count` centroids to t[0 .. len): the wave is search wave `sw` of SW, its lane
 // l takes centroids 64 sw + l, + 64 SW, ... in ascending order (strict "less" keeps the lowest index of equal distances
@@ -123,11 +77,6 @@ __device__ __forceinline__ void nearest(unsigned lds_table, const __half *table,
       if (i0 + 64 * SW * u < count && d[u] < best) { best = d[u]; arg = (unsigned)(i0 + 64 * SW * u); }
   }
   wave_arg_min(best, arg);
-}
-
-// workgroup barrier that waits for LDS traffic only (the owner waves keep a row of H^-1 on its way across it)
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 // One workgroup: QS stack positions (v rows each), SW waves per position.  Wave 0 of a position owns its v x B tile of
@@ -414,8 +363,6 @@ int launch_quantize_columns(float *W, long long ldw, int rows, int cols, const f
   const int S = (rows + v - 1) / v;
   float *E = static_cast<float *>(workspace);
   __half *padded = reinterpret_cast<__half *>(static_cast<unsigned char *>(workspace) + ((size_t)rows * QB * sizeof(float) + 255) / 256 * 256);
-  const int n_pad = (k + k_res) * eh;
-  hipLaunchKernelGGL(pad_tables_kernel, dim3((unsigned)((n_pad + 255) / 256)), dim3(256), 0, st, cb, k, cb_res, k_res, v, eh, padded);
   // every dword that holds one of a stream's cols * bits bits starts at zero (the column kernel ORs its indices in)
   const int dw = (int)(((long long)cols * bits + 31) / 32), dw_res = (int)(((long long)cols * bits_res + 31) / 32);
   hipLaunchKernelGGL(clear_dwords_kernel, dim3((unsigned)(((long long)S * dw + 255) / 256)), dim3(256), 0, st, reinterpret_cast<unsigned *>(idx),
@@ -424,6 +371,19 @@ int launch_quantize_columns(float *W, long long ldw, int rows, int cols, const f
     hipLaunchKernelGGL(clear_dwords_kernel, dim3((unsigned)(((long long)S * dw_res + 255) / 256)), dim3(256), 0, st,
                        reinterpret_cast<unsigned *>(idx_res), idx_res_stride / 4, dw_res, S);
   if (hipGetLastError() != hipSuccess) return VQ_ERR_HIP;
+  {
+    // one launch for the whole loop where the tables fit registers and LDS
+    LoopArgs a{};
+    a.W = W; a.ldw = ldw; a.rows = rows; a.cols = cols; a.Hinv = Hinv; a.ldh = ldh;
+    a.cb = cb; a.k = k; a.cb_res = cb_res; a.k_res = k_res; a.v = v; a.block = block;
+    a.idx = reinterpret_cast<unsigned *>(idx); a.idx_dwords = idx_stride / 4; a.bits = bits;
+    a.idx_res = reinterpret_cast<unsigned *>(idx_res); a.idx_res_dwords = idx_res_stride / 4; a.bits_res = bits_res;
+    a.T = T; a.ldt = ldt;
+    const int rc = launch_quantize_loop(a, st);
+    if (rc != VQ_ERR_UNSUPPORTED) return rc;
+  }
+  const int n_pad = (k + k_res) * eh;
+  hipLaunchKernelGGL(pad_tables_kernel, dim3((unsigned)((n_pad + 255) / 256)), dim3(256), 0, st, cb, k, cb_res, k_res, v, eh, padded);
   const size_t table_bytes = (size_t)n_pad * sizeof(__half);
   const bool in_lds = table_bytes <= 150 * 1024;
   QArgs a{};

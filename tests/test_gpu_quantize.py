@@ -24,6 +24,16 @@ CASES = {
     "v12_k4096": dict(M=40, N=50, v=12, k=4096, k_res=0, B=128),
     "v1_scalar": dict(M=70, N=40, v=1, k=16, k_res=0, B=7),
     "v6_res4096_one_block": dict(M=60, N=100, v=6, k=4096, k_res=4096, B=128),
+    # the one-launch loop: two and four positions a workgroup beside a cut-off one, every number of groups of 64 centroids a wave
+    # holds, tables that end inside a group, entries of 8, 16 and 32 operand slots, an odd block of several
+    "v6_two_positions_a_workgroup": dict(M=1603, N=40, v=6, k=256, k_res=0, B=32),
+    "v2_four_positions_a_workgroup": dict(M=2051, N=24, v=2, k=16, k_res=0, B=9),
+    "v6_k1025": dict(M=50, N=70, v=6, k=1025, k_res=1023, B=64),
+    "v4_k300": dict(M=34, N=50, v=4, k=300, k_res=0, B=25),
+    "v10_k4095_res60": dict(M=45, N=60, v=10, k=4095, k_res=60, B=31),
+    "v16_k1000_res100": dict(M=40, N=40, v=16, k=1000, k_res=100, B=128),
+    "v15_k4096_not_in_registers": dict(M=31, N=30, v=15, k=4096, k_res=0, B=128),
+    "v5_k4000_res3000": dict(M=23, N=60, v=5, k=4000, k_res=3000, B=128),
 }
 
 
