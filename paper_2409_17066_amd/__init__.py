@@ -171,6 +171,23 @@ def vq_version():
 
 
 # ---- conveniences over torch tensors (allocation and pointer extraction only) ----------------------------
+_bound = None
+
+
+def _native():
+    """The C++ binding (csrc/binding.cpp), which makes the calls below for plain arguments and returns None for others."""
+    global _bound
+    if _bound is None:
+        import torch  # noqa: F401  -- before the binding: it uses torch's libraries
+        L = load()
+        from . import _binding as b
+        b.bind({name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value
+                for name in ("vq_gemv", "vq_gemv_with_workspace", "vq_gemv_multi", "vq_gemm", "vq_gemm_workspace_bytes", "vq_dequant", "vq_assign",
+                             "vq_assign_down")})
+        _bound = b
+    return _bound
+
+
 class DeviceLayer:
     """Device copies of one layer's arrays plus the descriptor that points at them."""
 
@@ -209,6 +226,12 @@ def _stream():
 
 def dequant(dl: DeviceLayer, ldw=None):
     """fp16 [out][ldw] restored weights on the device (columns >= in_features are zero-initialised, never written)."""
+    if ldw is None:
+        W = (_bound or _native()).dequant(dl)
+        if W.__class__ is int:
+            raise VQError(W, "vq_dequant")
+        if W is not None:
+            return W
     import torch
     L = dl.layer
     ldw = L.in_features if ldw is None else ldw
@@ -229,6 +252,11 @@ def dequant(dl: DeviceLayer, ldw=None):
 def gemv(dl: DeviceLayer, x, out=None, workspace=None):
     """x: fp16 [batch][>=in] device tensor -> fp16 [batch][out].  workspace: a uint8 device tensor, or "fast" to allocate
     the one vq_gemv_workspace_bytes asks for (layers with codebook groups), or None."""
+    y = (_bound or _native()).gemv(dl, x, out, workspace)
+    if y.__class__ is int:
+        raise VQError(y, "vq_gemv")
+    if y is not None:
+        return y
     import torch
     assert x.is_cuda and x.dtype == torch.float16 and x.dim() == 2 and x.stride(1) == 1
     y = out if out is not None else torch.empty((x.shape[0], dl.layer.out_features), dtype=torch.float16, device="cuda")
@@ -247,6 +275,12 @@ def gemv(dl: DeviceLayer, x, out=None, workspace=None):
 
 def gemv_multi(dls, x, outs=None):
     """Several layers on the same x (fp16 [batch][>=in] device tensor) in one call -> list of fp16 [batch][out_i]."""
+    if outs is None:
+        ys = (_bound or _native()).gemv_multi(dls, x)
+        if ys.__class__ is int:
+            raise VQError(ys, "vq_gemv_multi")
+        if ys is not None:
+            return ys
     import torch
     assert x.is_cuda and x.dtype == torch.float16 and x.dim() == 2 and x.stride(1) == 1
     ys = outs if outs is not None else [torch.empty((x.shape[0], dl.layer.out_features), dtype=torch.float16, device="cuda")
@@ -262,6 +296,12 @@ def assign(W, codebook, base=None, cols=None, orientation=0):
     """W (and base): fp16 [rows][>= cols] device tensors, codebook: fp16 [k][v] device tensor -> uint8 [streams][stride]
     packed indices of the nearest centroids (stride: a stream's bits rounded up to 16 bytes, padding zero).  orientation 0:
     vectors along the rows, a stream per row; 1: vectors down the columns, a stream per block of v rows."""
+    if cols is None:
+        idx = (_bound or _native()).assign(W, codebook, base, orientation)
+        if idx.__class__ is int:
+            raise VQError(idx, "vq_assign_down" if orientation else "vq_assign")
+        if idx is not None:
+            return idx
     import torch
     assert W.is_cuda and W.dtype == torch.float16 and W.dim() == 2 and W.stride(1) == 1
     assert base is None or (base.dtype == torch.float16 and base.shape == W.shape and base.stride() == W.stride())
@@ -318,6 +358,11 @@ def quantize_columns(W, Hinv, codebook, codebook_res=None, block=128, want_T=Tru
 def gemm(dl: DeviceLayer, X, out=None, workspace=None):
     """X: fp16 [tokens][>=in] device tensor -> fp16 [tokens][out].  workspace: a uint8 device tensor, or "fast" to
     allocate the one vq_gemm_fast_workspace_bytes asks for (the restore-then-multiply route), or None."""
+    Y = (_bound or _native()).gemm(dl, X, out, workspace)
+    if Y.__class__ is int:
+        raise VQError(Y, "vq_gemm")
+    if Y is not None:
+        return Y
     import torch
     assert X.is_cuda and X.dtype == torch.float16 and X.dim() == 2 and X.stride(1) == 1
     Y = out if out is not None else torch.empty((X.shape[0], dl.layer.out_features), dtype=torch.float16, device="cuda")

@@ -12,6 +12,7 @@ except ImportError:                      # run as a script
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libvq.so")
+BINDING = os.path.join(HERE, "_binding.so")
 SOURCES = ["vq_api.hip", "vq_dequant.hip", "vq_dequant_fast.hip", "vq_gemv.hip", "vq_gemv_fast.hip", "vq_gemv_res8.hip", "vq_gemv_mfma.hip", "vq_gemm.hip", "vq_gemm_fused.hip", "vq_assign.hip", "vq_gemv_down.hip", "vq_gemv_down_mfma.hip", "vq_gemv_v8.hip", "vq_colperm.hip", "vq_quantize.hip", "vq_quantize_loop.hip", "vq_gemm_v6.hip", "vq_gemv_lds.hip", "vq_dequant_lds.hip", "vq_gemv_down_lds.hip"]
 # packed-FP32 VALU forms are switched off for every device compile (they are not trusted on the test machines)
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
@@ -66,10 +67,27 @@ def check_no_spills(src: str, remarks: str) -> None:
                 raise RuntimeError("%s: kernel %s uses %d bytes of scratch memory per lane; it must not" % (src, name, n))
 
 
+def build_binding() -> None:
+    """_binding.so: the torch conveniences of the package in C++ (host code only)."""
+    import sysconfig
+
+    import torch
+    root = os.path.join(os.path.dirname(torch.__file__))
+    include = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"), "/opt/rocm/include",
+               sysconfig.get_paths()["include"]]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI]
+    cmd += [flag for d in include for flag in ("-isystem", d)] + [os.path.join(CSRC, "binding.cpp"), "-o", BINDING]
+    # (torch's own libraries are in the process before this one is imported, so no path to them is recorded)
+    cmd += ["-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_hip", "-ltorch_cpu", "-lc10_hip", "-lc10"]
+    subprocess.check_call(cmd)
+
+
 def build(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     objs = []
     procs = []
+    binding = ThreadPoolExecutor(max_workers=1).submit(build_binding)
     os.makedirs(os.path.join(HERE, "_build"), exist_ok=True)
     for src in SOURCES:
         obj = os.path.join(HERE, "_build", src.replace(".hip", ".o"))
@@ -107,6 +125,7 @@ def build(verbose: bool = False) -> str:
     # no rpath: inside a PyTorch process the already-loaded HIP runtime (same soname) is the one used
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
     subprocess.check_call(cmd)
+    binding.result()
     return LIB
 
 
