@@ -182,7 +182,7 @@ def _native():
         L = load()
         from . import _binding as b
         b.bind({name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value
-                for name in ("vq_gemv", "vq_gemv_with_workspace", "vq_gemv_multi", "vq_gemm", "vq_gemm_workspace_bytes", "vq_dequant", "vq_assign",
+                for name in ("vq_gemv", "vq_gemv_with_workspace", "vq_gemv_multi", "vq_gemm", "vq_gemm_workspace_bytes", "vq_gemm_fast_workspace_bytes", "vq_dequant", "vq_assign",
                              "vq_assign_down")})
         _bound = b
     return _bound
@@ -357,7 +357,9 @@ def quantize_columns(W, Hinv, codebook, codebook_res=None, block=128, want_T=Tru
 
 def gemm(dl: DeviceLayer, X, out=None, workspace=None):
     """X: fp16 [tokens][>=in] device tensor -> fp16 [tokens][out].  workspace: a uint8 device tensor, or "fast" to
-    allocate the one vq_gemm_fast_workspace_bytes asks for (the restore-then-multiply route), or None."""
+    allocate the one vq_gemm_fast_workspace_bytes asks for (the restore-then-multiply route), or None, which from nine
+    tokens on does the same: torch's allocator hands the memory out and takes it back in stream order.  (An empty tensor
+    leaves the library without one.)"""
     Y = (_bound or _native()).gemm(dl, X, out, workspace)
     if Y.__class__ is int:
         raise VQError(Y, "vq_gemm")
@@ -366,10 +368,14 @@ def gemm(dl: DeviceLayer, X, out=None, workspace=None):
     import torch
     assert X.is_cuda and X.dtype == torch.float16 and X.dim() == 2 and X.stride(1) == 1
     Y = out if out is not None else torch.empty((X.shape[0], dl.layer.out_features), dtype=torch.float16, device="cuda")
-    if isinstance(workspace, str):
-        assert workspace == "fast"
+    if isinstance(workspace, str) or (workspace is None and X.shape[0] > 8):
+        assert workspace in (None, "fast")
         fast = vq_gemm_fast_workspace_bytes(dl.desc, X.shape[0])
-        workspace = torch.empty(fast, dtype=torch.uint8, device="cuda") if fast else None
+        try:
+            workspace = torch.empty(fast, dtype=torch.uint8, device="cuda") if fast else None
+        except torch.OutOfMemoryError:
+            if workspace is not None:
+                raise
     need = vq_gemm_workspace_bytes(dl.desc, X.shape[0])
     if need and (workspace is None or workspace.numel() * workspace.element_size() < need):
         workspace = torch.empty(need, dtype=torch.uint8, device="cuda")

@@ -18,7 +18,7 @@ decltype(&vq_gemv) p_gemv;
 decltype(&vq_gemv_with_workspace) p_gemv_ws;
 decltype(&vq_gemv_multi) p_gemv_multi;
 decltype(&vq_gemm) p_gemm;
-decltype(&vq_gemm_workspace_bytes) p_gemm_workspace_bytes;
+decltype(&vq_gemm_workspace_bytes) p_gemm_workspace_bytes, p_gemm_fast_workspace_bytes;
 decltype(&vq_dequant) p_dequant;
 decltype(&vq_assign) p_assign, p_assign_down;
 
@@ -148,13 +148,21 @@ PyObject *gemm(PyObject *, PyObject *const *args, Py_ssize_t n) {
   if (n != 4 || !(x = half_matrix(args[1])) || !(d = desc.get(args[0]))) Py_RETURN_NONE;
   void *wp = nullptr;
   size_t bytes = 0;
+  at::TensorBase scratch;
+  const int32_t tokens = (int32_t)x->size(0);
   if (args[3] != Py_None) {
     if (!THPVariable_Check(args[3])) Py_RETURN_NONE;
     const at::Tensor &ws = THPVariable_Unpack(args[3]);
     wp = ws.data_ptr();
     bytes = (size_t)ws.numel() * ws.element_size();
+  } else if (tokens > 8 && (bytes = p_gemm_fast_workspace_bytes(d, tokens)) != 0) {
+    try {
+      scratch = empty({(int64_t)bytes}, at::kByte);
+      wp = scratch.data_ptr();
+    } catch (const c10::OutOfMemoryError &) {      // (there is a route without)
+      bytes = 0;
+    }
   }
-  const int32_t tokens = (int32_t)x->size(0);
   if (p_gemm_workspace_bytes(d, tokens) > bytes) Py_RETURN_NONE;
   at::TensorBase fresh;
   const at::TensorBase *y = &fresh;
@@ -231,7 +239,8 @@ PyObject *bind(PyObject *, PyObject *addresses) {
     return f != nullptr;
   };
   if (!at("vq_gemv", p_gemv) || !at("vq_gemv_with_workspace", p_gemv_ws) || !at("vq_gemv_multi", p_gemv_multi) || !at("vq_gemm", p_gemm) ||
-      !at("vq_gemm_workspace_bytes", p_gemm_workspace_bytes) || !at("vq_dequant", p_dequant) || !at("vq_assign", p_assign) || !at("vq_assign_down", p_assign_down)) {
+      !at("vq_gemm_workspace_bytes", p_gemm_workspace_bytes) || !at("vq_gemm_fast_workspace_bytes", p_gemm_fast_workspace_bytes) ||
+       !at("vq_dequant", p_dequant) || !at("vq_assign", p_assign) || !at("vq_assign_down", p_assign_down)) {
     if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "an entry point is missing");
     return nullptr;
   }

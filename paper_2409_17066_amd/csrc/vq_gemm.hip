@@ -161,6 +161,8 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(Params p, const __half *
 }
 
 size_t gemm_workspace_bytes(const Params &, int) { return 0; }
+bool gemm_dense_applicable(const Params &p);
+float gemm_dense_us(const Params &p, int tokens);
 
 // Bytes of the FP16 weight matrix [out][in] that the two-step route below writes; 0 when that route does not apply.
 // For a layer with a permuted column order (Sec. 3.2.3) the activations, gathered into stored order, come first: tokens
@@ -169,7 +171,7 @@ static size_t permuted_x_bytes(const Params &p, int tokens) { return ((size_t)to
 
 size_t gemm_fast_workspace_bytes(const Params &p, int tokens) {
   const size_t head = p.perm ? permuted_x_bytes(p, tokens) : 0;
-  if (p.in_features % 256 != 0) return head;                 // the dense kernel walks the columns in groups of 8 x 32
+  if (!gemm_dense_applicable(p)) return head;
   return head + (size_t)p.out_features * (size_t)p.in_features * sizeof(__half);
 }
 
@@ -177,21 +179,40 @@ bool gemm_fused_applicable(const Params &p);
 bool gemv_has_lds_kernel(const Params &p, const __half *x, long long ldx);
 bool gemm_v6_applicable(const Params &p);
 int launch_gemm_v6(const Params &p, const __half *X, long long ldx, int tokens, __half *Y, long long ldy, hipStream_t s);
-int launch_gemm_fused(const Params &p, const __half *X, long long ldx, int tokens, __half *Y, long long ldy, const __half *Wd,
+int launch_gemm_fused(const Params &p, const __half *X, long long ldx, int tokens, __half *Y, long long ldy, hipStream_t s);
+int launch_gemm_dense(const Params &p, const __half *X, long long ldx, int tokens, __half *Y, long long ldy, const __half *Wd,
                       long long ldw, hipStream_t s);
 
+// Row-wise v = 6 layers have the matrix-core GEMV, whose sixteen rows cost little more than one: it still beats restoring the
+// matrix for the first sixteens of tokens.  Estimates in microseconds from 130 random layers: a launch of it 5 + 1.2 per thousand
+// columns and a little per million weights; restoring 5 + 0.4 per million weights (0.8 with a residual table), then the dense
+// product.  10496 x 3328, 28 tokens: 18 against 38 us; 4096 + 4096 tables, 4960 x 3072, 45 tokens: 39 against 38 us.
+static bool rows_beat_restoring(const Params &p, int tokens) {
+  const float weights = (float)((double)p.out_features * p.in_features * 1e-6);
+  const float launch = 5.0f + 1.2e-3f * (float)p.in_features + (p.k_res ? 1.5f + 0.06f * weights : 0.03f * weights) + (p.n_groups > 1 ? 8.0f : 0.0f);
+  const float restore = 5.0f + (p.k_res ? 0.8f : 0.4f) * weights + (p.n_out ? 5.0f : 0.0f);
+  return (float)((tokens + 15) / 16) * launch < restore + gemm_dense_us(p, tokens);
+}
+
 // Routes, in this order:
-//  1. a workspace of gemm_fast_workspace_bytes() is there: vq_dequant into it, then the MFMA kernel with plain
-//     tile copies as its producers.  This is the paper's prompt-phase scheme (restore to FP16, then a dense
-//     product); on gfx950 it beats restoring on the fly because every 16-byte centroid gather drags a 128-byte
-//     line out of L2 and a tile is gathered again for every token tile, while the restored matrix is read in
-//     full lines.  Any layer the library can dequantize qualifies (in_features a multiple of 256).
-//  2. v = 8 / 16-bit indices: restore on the fly inside the MFMA kernel (no workspace, W never in memory).
-//  3. v = 6 / 12-bit indices without outlier columns or groups: restore on the fly from tables in LDS (vq_gemm_v6.hip), when
-//     there is no workspace and more than 64 tokens (fewer go through vq_gemv's kernels, sixteen rows at a time).
-//  4. the generic tile kernel.
-// Switch gemm=g forces 4, =f skips 1, =w takes 1 whenever a workspace is there, =6 takes 3 for every token count
-// (measurement and tests).
+//  1. a workspace of gemm_fast_workspace_bytes() is there: vq_dequant into it, then the dense product (vq_gemm_dense.hip).  This
+//     is the paper's prompt-phase scheme; on gfx950 it beats restoring on the fly at every token count measured (17 to 2048),
+//     because tables are looked up once and not once for every token tile, and the restored matrix is read in full lines.
+//     Any layer the library can dequantize qualifies (in_features a multiple of 8).  It leaves to vq_gemv's kernels, up to
+//     sixteen rows at a time, what they do faster: row-wise v = 6 layers by the estimates above, other layers up to eight tokens
+//     (v = 2, 3435 x 5224, 5 tokens: 17 against 45 us; v = 12 with two tables, 6208 x 1024, 9 tokens: 43 against 23 us).
+//  2. no workspace, and a layer whose only tile kernel is the generic one: vq_gemv's kernels where that was measured faster.
+//     Row-wise v = 6 layers: always (512 tokens 322 against 700 us); layers with another specialised kernel (orientation 1), whose
+//     cost grows faster with the rows: up to 128 tokens; layers of the LDS-table decode kernels, which take four rows a launch:
+//     up to 32 (v = 12 with two tables, 16 tokens: 239 against 987 us).
+//  3. v = 6 / 12-bit indices, one codebook group, no workspace, more than 64 tokens: restored on the fly from tables in LDS
+//     (vq_gemm_v6.hip; up to 128 tokens only where its 128 x 128 tiles give 80 workgroups -- 8192 x 28672 at 128 tokens: 64
+//     workgroups, 612 us against 515 us for eight passes of the GEMV).
+//  4. v = 8 / 16-bit indices, no workspace: restored on the fly inside the MFMA kernel (vq_gemm_fused.hip), up to 16 tokens vq_gemv
+//     (461 x 8448, 7 tokens: 25 against 146 us).
+//  5. the generic tile kernel.
+// Switch gemm=g forces 5, =f skips 1, =w takes 1 whenever a workspace is there, =6 takes 3 for every token count, =r takes
+// vq_gemv's kernels (measurement and tests).
 int launch_gemm(const Params &p, const __half *X, long long ldx, int tokens, __half *Y, long long ldy,
                 void *workspace, size_t workspace_bytes, hipStream_t s) {
   if (p.perm && tokens <= 65535 && workspace && workspace_bytes >= permuted_x_bytes(p, tokens) && (reinterpret_cast<uintptr_t>(workspace) & 15) == 0 &&
@@ -214,49 +235,33 @@ int launch_gemm(const Params &p, const __half *X, long long ldx, int tokens, __h
   }
   const char forced = switches().gemm;
   const size_t fast = gemm_fast_workspace_bytes(p, tokens);
-  // measured on the 8192 x 8192 v=8 layer: up to 512 tokens restoring on the fly is still ahead (167 vs 184 us), from
-  // 1024 tokens on the restored matrix wins (215 vs 267 us, 365 vs 407 us at 2048); gemm=w takes it always
-  const bool worth_it = forced == 'w' || !gemm_fused_applicable(p) || tokens > 512;
   const bool have_ws = fast && workspace && workspace_bytes >= fast && (reinterpret_cast<uintptr_t>(workspace) & 15) == 0;
-  // Layers that only the generic tile kernel would take (no workspace and not the v = 8 layout of the fused kernel), and
-  // token counts too small for the restored-matrix route to fill the chip with tiles, go through vq_gemv's kernels sixteen
-  // rows at a time where that was measured faster.  Row-wise v = 6 layers (the matrix-core GEMV, whose sixteen rows cost
-  // little more than one): always without a workspace, up to 96 tokens with one -- 4096 x 4096, 64 tokens 42 us against
-  // 83 us with a workspace and 667 us without; 512 tokens without a workspace 322 against 700 us.  The other layers with
-  // a specialised GEMV kernel (v = 8; orientation 1), whose cost grows faster with the rows: only without a workspace and
-  // up to 128 tokens (v = 8, k = 65536 with a residual, 64 tokens: 191 against 848 us; 512 tokens would be 1480 against 880).
-  // gemm=r: always.
-  // (the on-the-fly kernel for v = 6 from 65 tokens on; up to 128 tokens only where its 128 x 128 tiles give 80 workgroups --
-  // 8192 x 28672 at 128 tokens: 64 workgroups, 612 us against 515 us for eight passes of the GEMV)
   const bool v6_tiles_fill = tokens > 128 || (long long)((p.out_features + 127) / 128) * ((tokens + 127) / 128) >= 80;
   if (gemm_v6_applicable(p) && (forced == '6' || (forced == '\0' && !have_ws && tokens > 64 && v6_tiles_fill))) {
     const int rc = launch_gemm_v6(p, X, ldx, tokens, Y, ldy, s);
     if (rc != VQ_ERR_UNSUPPORTED) return rc;
   }
-  const bool rows_cheap = p.orientation == 0 && p.v == 6;
-  // (layers of the LDS-table decode kernels, whose only tile kernel is the generic one -- about 1 ms for any token count up to
-  // 128 on 11008 x 4096 -- and whose decode kernels take four rows a launch: up to 32 tokens, 4 with a workspace; v = 12 with two
-  // tables, 16 tokens: 239 against 987 us, with a workspace 164 us)
-  const bool lds_rows = forced == '\0' && !gemm_fused_applicable(p) && !gemm_v6_applicable(p) && gemv_has_lds_kernel(p, X, ldx) &&
-                        tokens <= (have_ws ? 4 : 32);
-  if (forced == 'r' || lds_rows ||
-      (forced == '\0' && !gemm_fused_applicable(p) && gemv_has_fast_kernel(p, X, ldx) &&
-       (rows_cheap ? (!have_ws || tokens <= 96) : (!have_ws && tokens <= 128)))) {
+  bool rows = forced == 'r';
+  if (forced == '\0') {
+    if (p.orientation == 0 && p.v == 6 && gemv_has_fast_kernel(p, X, ldx)) rows = !have_ws || rows_beat_restoring(p, tokens);
+    else if (have_ws || gemm_fused_applicable(p)) rows = tokens <= (have_ws ? 8 : 16) && (gemv_has_fast_kernel(p, X, ldx) || gemv_has_lds_kernel(p, X, ldx));
+    else rows = (tokens <= 128 && gemv_has_fast_kernel(p, X, ldx)) || (tokens <= 32 && !gemm_v6_applicable(p) && gemv_has_lds_kernel(p, X, ldx));
+  }
+  if (rows) {
     for (int t0 = 0; t0 < tokens; t0 += 16) {
       const int rc = launch_gemv(p, X + (long long)t0 * ldx, ldx, tokens - t0 < 16 ? tokens - t0 : 16, Y + (long long)t0 * ldy, ldy, s);
       if (rc != VQ_OK) return rc;
     }
     return VQ_OK;
   }
-  if (forced != 'g' && forced != 'f' && worth_it && fast && workspace && workspace_bytes >= fast &&
-      (reinterpret_cast<uintptr_t>(workspace) & 15) == 0) {
+  if (forced != 'g' && forced != 'f' && have_ws) {
     __half *Wd = static_cast<__half *>(workspace);
     int rc = launch_dequant(p, Wd, p.in_features, s);
-    if (rc == VQ_OK) rc = launch_gemm_fused(p, X, ldx, tokens, Y, ldy, Wd, p.in_features, s);
+    if (rc == VQ_OK) rc = launch_gemm_dense(p, X, ldx, tokens, Y, ldy, Wd, p.in_features, s);
     if (rc != VQ_ERR_UNSUPPORTED) return rc;
   }
   if (forced != 'g' && gemm_fused_applicable(p)) {
-    const int rc = launch_gemm_fused(p, X, ldx, tokens, Y, ldy, nullptr, 0, s);
+    const int rc = launch_gemm_fused(p, X, ldx, tokens, Y, ldy, s);
     if (rc != VQ_ERR_UNSUPPORTED) return rc;
   }
   const unsigned gx = (unsigned)((p.out_features + BN - 1) / BN), gy = (unsigned)((tokens + BM - 1) / BM);

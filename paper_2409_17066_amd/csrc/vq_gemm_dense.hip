@@ -1,0 +1,274 @@
+// The dense product of vq_gemm's restore-then-multiply route: Y = X * W^T with the FP16 W that vq_dequant has written to the
+// caller's workspace (the paper's own prompt-phase scheme).
+//
+// A workgroup of four waves (2 x 2) owns 64 MB tokens x 64 NB channels, a wave 32 MB x 32 NB in blocks of
+// v_mfma_f32_16x16x32_f16.  Both tiles come by asynchronous global->LDS copies, NST steps of 64 columns ahead, in 128-byte rows:
+// whole cache lines (half as many L2 requests as with 64-byte rows).  The loop is pipelined by half steps: the operand reads
+// of the next half step and the copies are issued between the products of the current one, and one barrier a step sits between
+// its two halves.  A column count that is no multiple of 64 ends in a step whose missing chunks are fetched from past the end
+// of the buffers, where copies read zeros.
+//
+// What bounds it: at 256 x 256 tiles the matrix cores, and their power.  2048 x 8192 x 8192 runs at 1.4 to 1.5 GHz with the
+// matrix cores busy about 90% of the clocks, so energy counts: the 16x16x32 instruction in place of 32x32x16 took 219 -> 197 us at
+// the same traffic (1395 TFLOP/s); before, issuing reads and copies between the products instead of ahead of them 250 -> 221 us
+// (a wave that has its SIMD to itself issues nothing else meanwhile).  Deeper stages or other placements of the reads changed
+// nothing.  The smaller tiles are bound by LDS traffic per product and, with few workgroups, by the latency of a step.
+#include "vq_gemm_tiles.hpp"
+#include <algorithm>
+#include <type_traits>
+#include <utility>
+
+namespace vq {
+
+namespace {
+
+using namespace gemm_tiles;
+
+typedef float float4v __attribute__((ext_vector_type(4)));
+
+struct DenseArgs {
+  const __half *X; long long ldx; int tokens;
+  const __half *W; long long ldw; int out_features, in_features;
+  __half *Y; long long ldy;
+  int gx, gy;                  // tiles along the channels and the tokens
+};
+
+constexpr int DBK = 64;                                                  // columns per step: 128-byte rows in LDS
+template <int MB, int NB, int NST> constexpr unsigned dense_lds() { return NST * (MB + NB) * 64u * (DBK * 2u); }
+template <int MB, int NB, int NST> constexpr int dense_workgroups() {     // per compute unit: one where the accumulators take half the registers
+  return MB * NB >= 16 ? 1 : dense_lds<MB, NB, NST>() > 80 * 1024 ? 1 : dense_lds<MB, NB, NST>() > 40 * 1024 ? 2 : 4;
+}
+
+// 16 bytes of each lane, from byte `offset` of the buffer to 1 KB of LDS at `to`  (kept out of the template: the host pass does
+// not accept the builtin where it has to instantiate it)
+__device__ __forceinline__ void copy16(const __amdgpu_buffer_rsrc_t &from, unsigned char *to, unsigned offset) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(from, (__attribute__((address_space(3))) void *)to, 16, offset, 0, 0, 0);
+}
+
+// operand block I (blocks are 16 rows, 2 KB, apart) of the tile whose first one is at LDS byte address `at`.  The reads are issued
+// from inline assembly, in program order, and waited for explicitly: left to itself the compiler gives both sets of operands the
+// same registers and so has to issue a set's reads after the other set's products.
+template <int I> __device__ __forceinline__ void read_block(half8 &f, unsigned at) {
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(f) : "v"(at), "n"(I * 2048) : "memory");
+}
+
+template <class F, int... I> __device__ __forceinline__ void static_for(F &&f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, class F> __device__ __forceinline__ void static_for(F &&f) { static_for(f, std::make_integer_sequence<int, N>{}); }
+
+__device__ __forceinline__ void keep_in_agprs(float4v &v) { asm volatile("" : "+a"(v)); }
+
+template <int MB, int NB, int NST>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(dense_workgroups<MB, NB, NST>(), dense_workgroups<MB, NB, NST>())))
+void gemm_dense_kernel(DenseArgs a) {
+  constexpr int TM = 64 * MB, TN = 64 * NB, PX = 2 * MB, PER = 2 * (MB + NB);      // copies of a wave and step: PX of the X tile, PER in all
+  constexpr unsigned ROW = DBK * 2u, XTILE = TM * ROW, STAGE = (TM + TN) * ROW;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // [NST][X tile | W tile]
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = (wave >> 1) * (32 * MB), wn = (wave & 1) * (32 * NB);
+  // Workgroups go round robin over the eight XCDs, each with an L2 of its own: an XCD takes a run of tiles, token tiles first,
+  // whose W rows it then fetches once
+  const int tiles = a.gx * a.gy, run = (tiles + 7) / 8, tile = (int)(blockIdx.x & 7) * run + (int)(blockIdx.x >> 3);
+  if (tile >= tiles) return;
+  const int n0 = tile / a.gy * TN, m0 = tile % a.gy * TM;
+  const int ksteps = (a.in_features + DBK - 1) / DBK;
+  // range-checked against the end of the last row: rows past the matrix read zeros
+  const __amdgpu_buffer_rsrc_t r_x = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<__half *>(a.X), 0, (unsigned)(((long long)(a.tokens - 1) * a.ldx + a.in_features) * 2), 0x00020000);
+  const __amdgpu_buffer_rsrc_t r_w = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<__half *>(a.W), 0, (unsigned)(((long long)(a.out_features - 1) * a.ldw + a.in_features) * 2), 0x00020000);
+
+  // A step's copies, 8 rows x 128 bytes each: byte offsets of the lane's 16-byte chunk at step 0.  LDS slot (r, cs) holds chunk
+  // cs ^ (r / 2 mod 8): then the 16-byte chunks that a group of 16 lanes reads from consecutive rows fall into all 64 banks.
+  const unsigned even = ((unsigned)lane & 7u) ^ ((unsigned)lane >> 4);      // the chunk in pieces of even number; ^ 4: odd
+  unsigned from[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const unsigned chunk = even ^ (i & 1 ? 4u : 0u);
+    from[i] = i < PX ? (unsigned)(((long long)(m0 + (wave * PX + i) * 8 + (lane >> 3)) * a.ldx + chunk * 8) * 2)
+                     : (unsigned)(((long long)(n0 + (wave * (PER - PX) + i - PX) * 8 + (lane >> 3)) * a.ldw + chunk * 8) * 2);
+  }
+  // byte offset of a step's columns; chunks past the last column, and the steps past the last one, go past the end of the
+  // buffers (which end below 2 GiB: see the launcher), where copies read zeros and fetch nothing
+  const int steps_even = (a.in_features - (int)even * 8 + DBK - 1) / DBK, steps_odd = (a.in_features - (int)(even ^ 4u) * 8 + DBK - 1) / DBK;
+  auto copy_piece = [&](int i, unsigned stage, unsigned step_even, unsigned step_odd) {
+    unsigned char *to = smem + stage + (i < PX ? (unsigned)(wave * PX + i) * 1024u : XTILE + (unsigned)(wave * (PER - PX) + i - PX) * 1024u);
+    copy16(i < PX ? r_x : r_w, to, from[i] + (i & 1 ? step_odd : step_even));
+  };
+  // operand addresses: row (block base + lane & 15), whose swizzle depends on the lane only, chunk 4 h + (lane >> 4) of half h
+  const unsigned lds0 = (unsigned)reinterpret_cast<size_t>((const __attribute__((address_space(3))) void *)smem);
+  const unsigned half0 = lds0 + (unsigned)(lane & 15) * ROW + ((((unsigned)lane >> 4) ^ (((unsigned)lane >> 1) & 7u)) << 4), half1 = half0 ^ 64u;
+  const unsigned x_base = (unsigned)wm * ROW, w_base = XTILE + (unsigned)wn * ROW;
+
+  constexpr int AB = 2 * MB, BB = 2 * NB;      // blocks of 16 rows in the wave's tile
+  float4v acc[AB][BB];
+#pragma unroll
+  for (int i = 0; i < AB; ++i)
+#pragma unroll
+    for (int c = 0; c < BB; ++c) acc[i][c] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
+  half8 a0[AB], b0[BB], a1[AB], b1[BB];
+  auto operands_in = [&](half8 (&af)[AB], half8 (&bf)[BB]) {       // behind a wait: the values are there
+#pragma unroll
+    for (int i = 0; i < AB; ++i) settle(af[i]);
+#pragma unroll
+    for (int i = 0; i < BB; ++i) settle(bf[i]);
+  };
+  // The products of half a step (32 columns), with the operand reads of the next half (and, COPY, the copies of a step) issued
+  // between them: a wave that has its SIMD to itself issues nothing else meanwhile, and a block of products keeps the matrix
+  // core busy for 16 clocks, in which it can issue three instructions.
+  auto half_step = [&](auto copies, const half8 (&af)[AB], const half8 (&bf)[BB], unsigned at, half8 (&an)[AB], half8 (&bn)[BB],
+                       unsigned stage, int kt) {
+    constexpr bool COPY = decltype(copies)::value;
+    constexpr int N = AB * BB, R = AB + BB;
+    unsigned xa = at + x_base, wa = at + w_base;
+    asm volatile("" : "+v"(xa), "+v"(wa));      // both addresses in registers of their own before the first read goes out
+    const unsigned step_even = COPY ? (kt < steps_even ? (unsigned)kt * ROW : 0x80000000u) : 0u;
+    const unsigned step_odd = COPY ? (kt < steps_odd ? (unsigned)kt * ROW : 0x80000000u) : 0u;
+    static_for<N>([&](auto index) {
+      constexpr int n = decltype(index)::value, i = n / BB, c = n % BB;
+      acc[i][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af[i], bf[c], acc[i][c], 0, 0, 0);
+      static_for<R>([&](auto read) {
+        constexpr int r = decltype(read)::value;
+        if constexpr (r * N * 2 / (R * 3) == n) {
+          if constexpr (r < AB) read_block<r>(an[r], xa);
+          else read_block<r - AB>(bn[r - AB], wa);
+        }
+      });
+      if constexpr (COPY) {
+        static_for<PER>([&](auto piece) {
+          constexpr int r = decltype(piece)::value;
+          if constexpr (r * N / (PER * 2) == n) copy_piece(r, stage, step_even, step_odd);
+        });
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+
+  // Copies run NST steps ahead: step kt + NST goes to the stage that the barrier of step kt has freed.  A wave waits for its
+  // own by count (PER per step), the barrier covers the others'.
+  static_for<NST>([&](auto index) {
+    constexpr int j = decltype(index)::value;
+    const unsigned step_even = j < steps_even ? j * ROW : 0x80000000u, step_odd = j < steps_odd ? j * ROW : 0x80000000u;
+    static_for<PER>([&](auto piece) { copy_piece(decltype(piece)::value, j * STAGE, step_even, step_odd); });
+  });
+  wait_vmem_at_most<(NST - 1) * PER>();
+  step_barrier();
+  {
+    unsigned xa = half0 + x_base, wa = half0 + w_base;
+    static_for<AB>([&](auto i) { read_block<decltype(i)::value>(a0[decltype(i)::value], xa); });
+    static_for<BB>([&](auto i) { read_block<decltype(i)::value>(b0[decltype(i)::value], wa); });
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  operands_in(a0, b0);
+  unsigned stage = 0;
+  for (int kt = 0; kt < ksteps; ++kt) {
+    const unsigned next = stage + STAGE == NST * STAGE ? 0u : stage + STAGE;
+    half_step(std::false_type{}, a0, b0, half1 + stage, a1, b1, 0u, 0);
+    // this wave's copies of step kt + 1 are in when no more are out than those of the steps after it
+    wait_vmem_at_most<(NST - 2) * PER>();
+    step_barrier();                                           // (waits for the operand reads above as well: they are LDS traffic)
+    operands_in(a1, b1);
+    // (past the last step these read a stage that nobody needs: the loop stays one straight line)
+    half_step(std::true_type{}, a1, b1, half0 + next, a0, b0, stage, kt + NST);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    operands_in(a0, b0);
+    stage = next;
+  }
+  if constexpr (MB * NB >= 16) {       // (the accumulators fill the AGPRs; left alone, the compiler moves blocks of them to VGPRs inside the loop)
+#pragma unroll
+    for (int i = 0; i < AB; ++i)
+#pragma unroll
+      for (int c = 0; c < BB; ++c) keep_in_agprs(acc[i][c]);
+  }
+  wait_vmem_at_most<0>();      // the copies issued past the last step write to LDS too: they end before the workgroup does
+
+  // ---- store: a lane holds channel (lane & 15) of four tokens of block (i, c).  Range-checked 2-byte buffer stores with 32-bit
+  // offsets: rows past the last token fall off the end of the buffer, channels past the last one are sent there on purpose.
+  // (8-byte stores of four channels of a token, from the transposed product, were slower: 16 rows a store instead of 4.)
+  const __amdgpu_buffer_rsrc_t r_y = __builtin_amdgcn_make_buffer_rsrc(a.Y, 0, (unsigned)(((long long)(a.tokens - 1) * a.ldy + a.out_features) * 2), 0x00020000);
+  const unsigned ldy2 = (unsigned)a.ldy * 2u;
+  const unsigned y_lane = (unsigned)(m0 + wm + 4 * (lane >> 4)) * ldy2 + (unsigned)(n0 + wn + (lane & 15)) * 2u;
+#pragma unroll
+  for (int i = 0; i < AB; ++i) {
+#pragma unroll
+    for (int c = 0; c < BB; ++c) {
+      const bool o_on = n0 + wn + c * 16 + (lane & 15) < a.out_features;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const __half h = __float2half_rn(acc[i][c][r]);
+        __builtin_amdgcn_raw_buffer_store_b16((short)__half_as_ushort(h), r_y, o_on ? y_lane + (unsigned)(i * 16 + r) * ldy2 + (unsigned)(c * 32) : 0xFFFFFFF0u, 0, 0);
+      }
+    }
+    asm volatile("" ::: "memory");
+  }
+}
+
+template <int MB, int NB, int NST>
+int launch_tiles(DenseArgs a, hipStream_t s) {
+  auto kernel = gemm_dense_kernel<MB, NB, NST>;
+  VQ_ALLOW_FULL_LDS(kernel);
+  a.gx = (a.out_features + 64 * NB - 1) / (64 * NB);
+  a.gy = (a.tokens + 64 * MB - 1) / (64 * MB);
+  const long long tiles = (long long)a.gx * a.gy;
+  if (tiles > (1 << 24)) return VQ_ERR_UNSUPPORTED;
+  constexpr unsigned lds = dense_lds<MB, NB, NST>();
+  hipLaunchKernelGGL(kernel, dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(256), lds, s, a);
+  return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
+}
+
+// Tile shapes and what they cost, in microseconds at the clocks that full load leaves: a fixed part per round of workgroups, and per
+// 64-column step with one or two workgroups on a compute unit.  Fitted to 60 random shapes (17 to 2048 tokens, 256 to 11008 channels,
+// 512 to 11008 columns), whose times the sums below meet within 4% on average.
+struct TileKind {
+  int mb, nb, per_cu;
+  float round, step[2];
+  int (*launch)(DenseArgs, hipStream_t);
+};
+const TileKind kTiles[] = {
+    {4, 4, 1, 9.9f, {1.12f, 0.0f}, launch_tiles<4, 4, 2>},  {4, 3, 1, 7.6f, {0.90f, 0.0f}, launch_tiles<4, 3, 2>},
+    {2, 2, 1, 4.2f, {0.383f, 0.0f}, launch_tiles<2, 2, 3>}, {1, 3, 2, 2.1f, {0.478f, 0.767f}, launch_tiles<1, 3, 2>},
+    {1, 2, 2, 2.3f, {0.273f, 0.558f}, launch_tiles<1, 2, 3>}, {1, 1, 2, 1.2f, {0.190f, 0.384f}, launch_tiles<1, 1, 4>},
+};
+
+float tile_cost(const TileKind &t, int tokens, int out_features, int in_features, int cus) {
+  const long long tiles = (long long)((tokens + 64 * t.mb - 1) / (64 * t.mb)) * ((out_features + 64 * t.nb - 1) / (64 * t.nb));
+  const long long most = (tiles + cus - 1) / cus, rounds = most / t.per_cu, rest = most % t.per_cu;
+  const float steps = (float)((in_features + DBK - 1) / DBK);
+  return (float)rounds * (t.round + steps * t.step[t.per_cu - 1]) + (rest ? t.round + steps * t.step[rest - 1] : 0.0f);
+}
+
+}  // namespace
+
+bool gemm_dense_applicable(const Params &p) { return p.in_features % 8 == 0; }       // (16-byte chunks of W's rows)
+
+// The tile shape with the least estimated time.  Switch dense=0 / =1: always the smallest / the largest one, for tests.
+int launch_gemm_dense(const Params &p, const __half *X, long long ldx, int tokens, __half *Y, long long ldy, const __half *Wd, long long ldw, hipStream_t s) {
+  if (!gemm_dense_applicable(p)) return VQ_ERR_UNSUPPORTED;
+  // Buffer offsets have 32 bits and the copies of missing chunks start 2 GiB up, so one launch covers at most 2 GiB of X and of W
+  // and 4 GiB of Y (with room for a tile of rows past the end); more goes in several.
+  const long long room = 1LL << 31, pad = 256;
+  const long long most_tokens = std::min(room / (ldx * 2), (room * 2 - 4096) / (ldy * 2)) - pad, most_out = room / (ldw * 2) - pad;
+  if (most_tokens < 1 || most_out < 1) return VQ_ERR_UNSUPPORTED;
+  const int force = switches().dense;
+  for (long long o = 0; o < p.out_features; o += most_out)
+    for (long long t = 0; t < tokens; t += most_tokens) {
+      const int nt = (int)std::min<long long>(most_tokens, tokens - t), no = (int)std::min<long long>(most_out, p.out_features - o);
+      const TileKind *best = force == 1 ? &kTiles[0] : &kTiles[sizeof(kTiles) / sizeof(kTiles[0]) - 1];
+      if (force != 0 && force != 1)
+        for (const TileKind &k : kTiles)
+          if (tile_cost(k, nt, no, p.in_features, cu_count()) < tile_cost(*best, nt, no, p.in_features, cu_count())) best = &k;
+      const int rc = best->launch({X + t * ldx, ldx, nt, Wd + o * ldw, ldw, no, p.in_features, Y + t * ldy + o, ldy, 0, 0}, s);
+      if (rc != VQ_OK) return rc;
+    }
+  return VQ_OK;
+}
+
+// Estimated time of launch_gemm_dense in microseconds, at least that of reading W at 4.5 TB/s (the route rules of vq_gemm compare
+// it with other kernels').
+float gemm_dense_us(const Params &p, int tokens) {
+  float best = 1e30f;
+  for (const TileKind &k : kTiles) best = std::min(best, tile_cost(k, tokens, p.out_features, p.in_features, cu_count()));
+  return std::max(best, 3.0f + (float)((double)p.out_features * p.in_features * 2 / 4.5e6));
+}
+
+}  // namespace vq

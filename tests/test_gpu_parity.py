@@ -97,6 +97,42 @@ def test_gemm_small(gpu_lib, monkeypatch, name, tokens, workspace):
     _check_matmul(Y, oracle.gemm(L, x), "%s tokens %d workspace %s" % (name, tokens, workspace))
 
 
+DENSE_SHAPES = [(1, 1, 8), (17, 300, 520), (64, 64, 64), (65, 129, 120), (128, 192, 192), (191, 257, 1032), (256, 256, 128), (300, 513, 136), (513, 768, 320)]
+
+
+@pytest.mark.parametrize("tokens,out_features,in_features", DENSE_SHAPES)
+@pytest.mark.parametrize("tiles", ["auto", "smallest", "largest"])
+def test_gemm_dense_tile_edges(gpu_lib, monkeypatch, tokens, out_features, in_features, tiles):
+    """The dense product of the restore-then-multiply route around the edges of its tiles (64 to 256 tokens and channels) and
+    steps (64 columns; the last one may hold as few as 8), NaN in the padding of X and a sentinel in the padding of Y."""
+    import torch
+    monkeypatch.setenv("VQ_SWITCHES", "gemm=w" + {"auto": "", "smallest": ",dense=0", "largest": ",dense=1"}[tiles])
+    L = s.make_layer(7, "dense", out_features, in_features, v=4, k=16)
+    dl = gpu_lib.DeviceLayer(L)
+    x = s.make_activations(300, L, tokens)
+    X = torch.full((tokens, in_features + 8), float("nan"), dtype=torch.float16, device="cuda")
+    X[:, :in_features] = torch.from_numpy(x).cuda()
+    Y = torch.full((tokens, out_features + 3), 7.0, dtype=torch.float16, device="cuda")
+    gpu_lib.gemm(dl, X, out=Y, workspace="fast")
+    torch.cuda.synchronize()
+    _check_matmul(Y[:, :out_features], oracle.gemm(L, x), "%s %s" % ((tokens, out_features, in_features), tiles))
+    assert (Y[:, out_features:] == 7.0).all()
+
+
+@pytest.mark.parametrize("name", list(SMALL))
+@pytest.mark.parametrize("tokens", [9, 37, 300])
+def test_gemm_without_workspace(gpu_lib, name, tokens):
+    """An empty workspace tensor: the routes that never write W to memory."""
+    import torch
+    L = small_layer(name)
+    x = s.make_activations(300, L, tokens)
+    X = torch.full((tokens, (L.in_features + 7) // 8 * 8), float("nan"), dtype=torch.float16, device="cuda")
+    X[:, : L.in_features] = torch.from_numpy(x).cuda()
+    Y = gpu_lib.gemm(gpu_lib.DeviceLayer(L), X, workspace=torch.empty(0, dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    _check_matmul(Y, oracle.gemm(L, x), "%s tokens %d" % (name, tokens))
+
+
 V6_GEMM = ["v6_gemm_plain", "v6_gemm_res8", "v6_gemm_res12", "single_row", "v6_exact_fit", "v6_gemm_outlier32", "v6_gemm_outlier48",
            "v6_gemm_outlier16_res12"]
 
