@@ -16,6 +16,7 @@ namespace {
 
 decltype(&vq_gemv) p_gemv;
 decltype(&vq_gemv_with_workspace) p_gemv_ws;
+decltype(&vq_gemv_workspace_bytes) p_gemv_workspace_bytes;
 decltype(&vq_gemv_multi) p_gemv_multi;
 decltype(&vq_gemm) p_gemm;
 decltype(&vq_gemm_workspace_bytes) p_gemm_workspace_bytes, p_gemm_fast_workspace_bytes;
@@ -74,6 +75,10 @@ PyObject *tensor_or_status(int rc, at::TensorBase &&fresh, PyObject *given) {
     return nullptr;                                         \
   }
 
+// Whether gemv() without a workspace borrows one: not for layers with codebook groups, nor for v = 6 / 12-bit layers in stored order:
+// their kernels without one are good, and sum in the same order with gemv_multi() or a workspace that is too small.
+bool lends_workspace(const vq_layer_desc &d) { return !d.group_vectors && (d.v != 6 || d.k <= 2048 || d.col_perm); }
+
 // gemv(layer, x, out or None, workspace or None)
 PyObject *gemv(PyObject *, PyObject *const *args, Py_ssize_t n) {
   VQ_TRY
@@ -102,6 +107,15 @@ PyObject *gemv(PyObject *, PyObject *const *args, Py_ssize_t n) {
     void *wp = ws.data_ptr();
     const size_t bytes = (size_t)ws.numel();
     rc = released([&] { return p_gemv_ws(d, xp, ldx, batch, yp, ldy, wp, bytes, s); });
+  } else if (const size_t bytes = lends_workspace(*d) ? p_gemv_workspace_bytes(d, batch) : 0) {
+    at::TensorBase scratch;
+    void *wp = nullptr;
+    try {
+      scratch = empty({(int64_t)bytes}, at::kByte);
+      wp = scratch.data_ptr();
+    } catch (const c10::OutOfMemoryError &) {      // (there is a route without)
+    }
+    rc = released([&] { return p_gemv_ws(d, xp, ldx, batch, yp, ldy, wp, wp ? bytes : 0, s); });
   } else {
     rc = released([&] { return p_gemv(d, xp, ldx, batch, yp, ldy, s); });
   }
@@ -239,7 +253,7 @@ PyObject *bind(PyObject *, PyObject *addresses) {
     return f != nullptr;
   };
   if (!at("vq_gemv", p_gemv) || !at("vq_gemv_with_workspace", p_gemv_ws) || !at("vq_gemv_multi", p_gemv_multi) || !at("vq_gemm", p_gemm) ||
-      !at("vq_gemm_workspace_bytes", p_gemm_workspace_bytes) || !at("vq_gemm_fast_workspace_bytes", p_gemm_fast_workspace_bytes) ||
+      !at("vq_gemm_workspace_bytes", p_gemm_workspace_bytes) || !at("vq_gemv_workspace_bytes", p_gemv_workspace_bytes) || !at("vq_gemm_fast_workspace_bytes", p_gemm_fast_workspace_bytes) ||
        !at("vq_dequant", p_dequant) || !at("vq_assign", p_assign) || !at("vq_assign_down", p_assign_down)) {
     if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "an entry point is missing");
     return nullptr;

@@ -10,7 +10,7 @@ namespace {
 typedef unsigned uint4v __attribute__((ext_vector_type(4)));
 
 // dst[t][c] = src[t][perm[c]]: the activations in the stored order of the columns.  One thread per pair of columns;
-// entries of perm outside the row read as zero; the pad columns [cols, ld_dst) of dst are cleared when ld_dst - cols < 8.
+// entries of perm outside the row read as zero, no perm is the identity; the pad columns [cols, ld_dst) of dst are cleared when ld_dst - cols < 8.
 __global__ __launch_bounds__(256) void gather_cols_kernel(const __half *__restrict__ src, long long ld_src, int cols, const int *__restrict__ perm,
                                                           __half *__restrict__ dst, long long ld_dst, int dst_cols) {
   const int c = (blockIdx.x * 256 + threadIdx.x) * 2;
@@ -20,7 +20,7 @@ __global__ __launch_bounds__(256) void gather_cols_kernel(const __half *__restri
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     if (c + j < cols) {
-      const int t = perm[c + j];
+      const int t = perm ? perm[c + j] : c + j;
       if ((unsigned)t < (unsigned)cols) h[j] = __half_as_ushort(srow[t]);
     }
   }

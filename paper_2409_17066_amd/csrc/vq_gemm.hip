@@ -177,6 +177,8 @@ size_t gemm_fast_workspace_bytes(const Params &p, int tokens) {
 
 bool gemm_fused_applicable(const Params &p);
 bool gemv_has_lds_kernel(const Params &p, const __half *x, long long ldx);
+bool gemv_rows_applicable(const Params &p);
+bool gemv_rows_takes(const Params &p, const __half *x, long long ldx, int batch);
 bool gemm_v6_applicable(const Params &p);
 int launch_gemm_v6(const Params &p, const __half *X, long long ldx, int tokens, __half *Y, long long ldy, hipStream_t s);
 int launch_gemm_fused(const Params &p, const __half *X, long long ldx, int tokens, __half *Y, long long ldy, hipStream_t s);
@@ -198,17 +200,18 @@ static bool rows_beat_restoring(const Params &p, int tokens) {
 //  1. a workspace of gemm_fast_workspace_bytes() is there: vq_dequant into it, then the dense product (vq_gemm_dense.hip).  This
 //     is the paper's prompt-phase scheme; on gfx950 it beats restoring on the fly at every token count measured (17 to 2048),
 //     because tables are looked up once and not once for every token tile, and the restored matrix is read in full lines.
-//     Any layer the library can dequantize qualifies (in_features a multiple of 8).  It leaves to vq_gemv's kernels, up to
-//     sixteen rows at a time, what they do faster: row-wise v = 6 layers by the estimates above, other layers up to eight tokens
-//     (v = 2, 3435 x 5224, 5 tokens: 17 against 45 us; v = 12 with two tables, 6208 x 1024, 9 tokens: 43 against 23 us).
+//     Any layer the library can dequantize qualifies (in_features a multiple of 8).  It leaves to vq_gemv's kernels, sixteen rows
+//     at a time, what they do faster: row-wise v = 6 layers by the estimates above; layers of vq_gemv_rows.hip up to 32 tokens
+//     (v = 12 with two tables, 8960 x 8192, 10 tokens: 22 against 121 us; v = 4, 8064 x 8448, 17 tokens: 34 against 73 us; level from
+//     33 on), 16 with codebook groups; others up to eight.
 //  2. no workspace, and a layer whose only tile kernel is the generic one: vq_gemv's kernels where that was measured faster.
-//     Row-wise v = 6 layers: always (512 tokens 322 against 700 us); layers with another specialised kernel (orientation 1), whose
-//     cost grows faster with the rows: up to 128 tokens; layers of the LDS-table decode kernels, which take four rows a launch:
-//     up to 32 (v = 12 with two tables, 16 tokens: 239 against 987 us).
+//     Row-wise v = 6 layers and those of vq_gemv_rows.hip: always (512 tokens 322 against 700 us); layers with another specialised
+//     kernel (orientation 1), whose cost grows faster with the rows: up to 128 tokens; layers of the LDS-table decode kernels, which
+//     take four rows a launch: up to 32 (v = 12 with two tables, 16 tokens: 239 against 987 us).
 //  3. v = 6 / 12-bit indices, one codebook group, no workspace, more than 64 tokens: restored on the fly from tables in LDS
 //     (vq_gemm_v6.hip; up to 128 tokens only where its 128 x 128 tiles give 80 workgroups -- 8192 x 28672 at 128 tokens: 64
 //     workgroups, 612 us against 515 us for eight passes of the GEMV).
-//  4. v = 8 / 16-bit indices, no workspace: restored on the fly inside the MFMA kernel (vq_gemm_fused.hip), up to 16 tokens vq_gemv
+//  4. v = 8 / 16-bit indices, no workspace: restored on the fly inside the MFMA kernel (vq_gemm_fused.hip), up to 32 tokens vq_gemv
 //     (461 x 8448, 7 tokens: 25 against 146 us).
 //  5. the generic tile kernel.
 // Switch gemm=g forces 5, =f skips 1, =w takes 1 whenever a workspace is there, =6 takes 3 for every token count, =r takes
@@ -243,13 +246,18 @@ int launch_gemm(const Params &p, const __half *X, long long ldx, int tokens, __h
   }
   bool rows = forced == 'r';
   if (forced == '\0') {
-    if (p.orientation == 0 && p.v == 6 && gemv_has_fast_kernel(p, X, ldx)) rows = !have_ws || rows_beat_restoring(p, tokens);
-    else if (have_ws || gemm_fused_applicable(p)) rows = tokens <= (have_ws ? 8 : 16) && (gemv_has_fast_kernel(p, X, ldx) || gemv_has_lds_kernel(p, X, ldx));
-    else rows = (tokens <= 128 && gemv_has_fast_kernel(p, X, ldx)) || (tokens <= 32 && !gemm_v6_applicable(p) && gemv_has_lds_kernel(p, X, ldx));
+    const bool fast_rows = gemv_has_fast_kernel(p, X, ldx), lds_rows = gemv_has_lds_kernel(p, X, ldx);
+    if (p.orientation == 0 && p.v == 6 && fast_rows) rows = !have_ws || rows_beat_restoring(p, tokens);
+    else if (gemv_rows_applicable(p) && gemv_rows_takes(p, X, ldx, 16))
+      rows = have_ws ? tokens <= (p.n_groups > 1 ? 16 : 32) : tokens <= 32 || !gemm_fused_applicable(p);
+    else if (have_ws || gemm_fused_applicable(p)) rows = tokens <= (have_ws ? 8 : 16) && (fast_rows || lds_rows);
+    else rows = (tokens <= 128 && fast_rows) || (tokens <= 32 && !gemm_v6_applicable(p) && lds_rows);
   }
   if (rows) {
+    const bool lend = have_ws && (reinterpret_cast<uintptr_t>(workspace) & 255) == 0;      // (vq_gemv cuts the columns into parts with it)
     for (int t0 = 0; t0 < tokens; t0 += 16) {
-      const int rc = launch_gemv(p, X + (long long)t0 * ldx, ldx, tokens - t0 < 16 ? tokens - t0 : 16, Y + (long long)t0 * ldy, ldy, s);
+      const int rc = launch_gemv_ws(p, X + (long long)t0 * ldx, ldx, tokens - t0 < 16 ? tokens - t0 : 16, Y + (long long)t0 * ldy, ldy,
+                                    lend ? workspace : nullptr, lend ? workspace_bytes : 0, s);
       if (rc != VQ_OK) return rc;
     }
     return VQ_OK;

@@ -168,6 +168,37 @@ static bool down_mfma_alone_wanted(const Params &p, const __half *x, long long l
   return batch >= 5 || (batch >= 3 && (p.S >= 64 * 16 || (p.k_res && p.bits_res == 12))) || forced_kernel() == 'm';
 }
 
+bool gemv_rows_applicable(const Params &p);
+bool gemv_rows_takes(const Params &p, const __half *x, long long ldx, int batch);
+int gemv_rows_parts(const Params &p);
+size_t gemv_rows_workspace_bytes(const Params &p, int batch);
+int launch_gemv_rows(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, float *part, float *part_xs,
+                     int parts_per_group, hipStream_t s);
+// When vq_gemv_rows.hip's kernel takes over from the ones that run four (v = 8: eight) rows a launch.  Its lookups do for any number
+// of rows, but a single row needs no matrix cores: from three rows on (two tables of v = 12, 6739 x 9664, 10 rows: 174 -> 22 us;
+// v = 4, 448 x 1872, 3 rows: 7.7 -> 5.5 us; 2 rows: level), and
+//  * for every number of rows where two tables do not fit LDS together, which the other kernels pay for in every launch (v = 12,
+//    6208 x 1856, 1 row: 11.0 -> 10.5 us; 467 x 6956, 2 rows: 20 -> 12 us) -- but not with codebook groups (1 row: 12 against 18 us);
+//  * orientation 1, whose workgroups take 16 streams, i.e. 16 v rows, over all the columns: with a workspace, whose parts fill the
+//    chip, from two rows on (v = 12, 12275 x 1728: 18 -> 13 us), one row of at least 16384 columns (644 x 22848: 26 -> 18 us);
+//    without, from two rows on where the workgroups alone are half as many as compute units, else from five (v = 12, 717 x 5520,
+//    2 rows: 18 against 37 us);
+//  * v = 8 with 16-bit indices, orientation 1, whose lookups go through L2: with a workspace from five rows, or two of at least
+//    4096 columns, on (768 x 7872, 5 rows: 35 -> 13 us), without from nine (5 rows: 60 us).
+// Switch rows=0 / rows=1: never / wherever it can.
+static bool rows_wanted(const Params &p, int batch, bool workspace) {
+  if (switches().rows == 0 || forced_kernel() != '\0' || !gemv_rows_applicable(p)) return false;
+  if (switches().rows == 1) return true;
+  if (p.orientation == 1 && p.bits == 16) return batch >= (!workspace ? 9 : p.P >= 4096 ? 2 : 5);
+  if (p.n_groups > 1) return batch >= 3;
+  if (p.orientation == 1) {
+    if (workspace) return batch >= 2 || p.P >= 16384;
+    return batch >= (2 * ((p.S + 15) / 16) >= cu_count() ? 2 : 5);
+  }
+  if (p.v == 12) return true;
+  return batch >= 3;
+}
+
 // Whether vq_gemv would run this layer on the kernels that keep one table in LDS at a time (no kernel of its own, tables that fit).
 bool gemv_has_lds_kernel(const Params &p, const __half *x, long long ldx) {
   if (forced_kernel() != '\0') return false;
@@ -201,6 +232,7 @@ static int gemv_through_lds_tables(const Params &p, const __half *x, long long l
 }
 
 int launch_gemv(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, hipStream_t s) {
+  if (rows_wanted(p, batch, false) && gemv_rows_takes(p, x, ldx, batch)) return launch_gemv_rows(p, x, ldx, batch, y, ldy, nullptr, nullptr, 0, s);
   if (p.perm) {
     // Permuted column order without a workspace: the dot-product kernels for v = 6 gather the activations while they stage
     // them in LDS (or load them into registers: long rows); everything else runs on the generic kernels, which look every
@@ -351,13 +383,15 @@ static bool permuted_in_kernel(const Params &p, const __half *x, long long ldx, 
   return batch == 1 && p.orientation == 0 && p.n_groups == 1 && forced_kernel() != 'm' && p.in_features < 16384 && gemv_fast_applicable(p, x, ldx);
 }
 
-size_t gemv_workspace_bytes(const Params &p, const __half *x, long long ldx, int batch) {
-  if (force_generic()) return 0;
-  if (p.perm) {
-    if (permuted_in_kernel(p, x, ldx, batch)) return 0;
-    Params q = p;
-    q.perm = nullptr;
-    return permuted_x_bytes(p, batch) + gemv_workspace_bytes(q, nullptr, (p.in_features + 7) & ~7, batch);
+// Rows of an odd width start between dwords for all but the first: the kernel that wants dwords has them copied, which costs 2 us
+// (v = 12, 305 x 1281, 2 rows: 10.4 us, 11.1 with the copy).
+static bool rows_gathered(const Params &p, int batch) { return batch >= 5 && (p.in_features & 1) && rows_wanted(p, batch, true); }
+
+static size_t stored_order_workspace_bytes(const Params &p, const __half *x, long long ldx, int batch) {
+  if (rows_wanted(p, batch, true) && (batch == 1 || !(ldx & 1))) {
+    // (with codebook groups a caller may count on a slot for each, also where the kernel walks the groups by itself)
+    const size_t need = gemv_rows_workspace_bytes(p, batch), slots = p.n_groups > 1 ? ((size_t)p.n_groups * ((size_t)batch * (size_t)p.out_features + 16) * sizeof(float) + 255) / 256 * 256 : 0;
+    return need ? need : slots;
   }
   if (p.orientation == 1 && down_mfma_parts_wanted(p, x, ldx, batch)) {   // the matrix cores: the workspace lets parts of the columns run side by side
     const int parts = gemv_down_mfma_parts(p);            // the outlier columns are one more set of sums to add up
@@ -375,10 +409,21 @@ size_t gemv_workspace_bytes(const Params &p, const __half *x, long long ldx, int
   return gemv_mfma_groups_workspace_bytes(p, batch);
 }
 
+size_t gemv_workspace_bytes(const Params &p, const __half *x, long long ldx, int batch) {
+  if (force_generic()) return 0;
+  if (p.perm || rows_gathered(p, batch)) {
+    if (p.perm && permuted_in_kernel(p, x, ldx, batch)) return 0;
+    Params q = p;
+    q.perm = nullptr;
+    return permuted_x_bytes(p, batch) + stored_order_workspace_bytes(q, nullptr, (p.in_features + 7) & ~7, batch);
+  }
+  return stored_order_workspace_bytes(p, x, ldx, batch);
+}
+
 int launch_gemv_ws(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, void *workspace,
                    size_t workspace_bytes, hipStream_t s) {
   const size_t need = gemv_workspace_bytes(p, x, ldx, batch);
-  if (p.perm) {
+  if (p.perm || (rows_gathered(p, batch) && !gemv_rows_takes(p, x, ldx, batch))) {
     if (!need || !workspace || workspace_bytes < need) return launch_gemv(p, x, ldx, batch, y, ldy, s);
     // gather the activations into stored order, then the layer is an unpermuted one
     Params q = p;
@@ -389,6 +434,13 @@ int launch_gemv_ws(const Params &p, const __half *x, long long ldx, int batch, _
     if (rc != VQ_OK) return rc;
     const size_t head = permuted_x_bytes(p, batch);
     return launch_gemv_ws(q, xp, ldxp, batch, y, ldy, static_cast<unsigned char *>(workspace) + head, workspace_bytes - head, s);
+  }
+  if (rows_wanted(p, batch, workspace != nullptr) && gemv_rows_takes(p, x, ldx, batch)) {
+    const int per_group = workspace && workspace_bytes >= gemv_rows_workspace_bytes(p, batch) ? gemv_rows_parts(p) : 0, parts = per_group * p.n_groups;
+    if (parts == 0) return launch_gemv_rows(p, x, ldx, batch, y, ldy, nullptr, nullptr, 0, s);
+    float *part = static_cast<float *>(workspace), *part_xs = part + (size_t)parts * (size_t)batch * (size_t)p.out_features;
+    const int rc = launch_gemv_rows(p, x, ldx, batch, nullptr, 0, part, part_xs, per_group, s);
+    return rc == VQ_OK ? launch_groups_finish(part, part_xs, parts, batch, p, y, ldy, s) : rc;
   }
   if (need && workspace && workspace_bytes >= need && p.orientation == 1 && down_mfma_parts_wanted(p, x, ldx, batch)) {
     const int parts = gemv_down_mfma_parts(p), slots = parts + (p.Q ? 1 : 0);

@@ -133,6 +133,43 @@ def test_gemm_without_workspace(gpu_lib, name, tokens):
     _check_matmul(Y, oracle.gemm(L, x), "%s tokens %d" % (name, tokens))
 
 
+ROWS_LAYERS = {
+    "v2": dict(out_features=65, in_features=1000, v=2, k=16), "v2_odd": dict(out_features=17, in_features=333, v=2, k=13),
+    "v4": dict(out_features=4200, in_features=130, v=4, k=256), "v4_12bit": dict(out_features=33, in_features=515, v=4, k=4096),
+    "v6_outliers": dict(out_features=100, in_features=2054, v=6, k=256, n_outlier_cols=12, v_out=4, k_out=4096),
+    "v8": dict(out_features=49, in_features=700, v=8, k=200), "v8_12bit": dict(out_features=48, in_features=264, v=8, k=4096, k_res=4096),
+    "v8_16bit": dict(out_features=40, in_features=1023, v=8, k=65536), "v8_16bit_many": dict(out_features=4201, in_features=72, v=8, k=65000),
+    "v12": dict(out_features=31, in_features=4100, v=12, k=4096, k_res=3000), "v12_tiny": dict(out_features=1, in_features=5, v=12, k=4000),
+    "v12_many": dict(out_features=9000, in_features=60, v=12, k=4096, k_res=4096),
+    "v12_groups": dict(out_features=70, in_features=2300, v=12, k=4096, k_res=4096, n_outlier_cols=44, v_out=4, k_out=8192, group_vectors=40),
+    "v12_permuted": dict(out_features=50, in_features=1201, v=12, k=4096, k_res=4096, n_outlier_cols=8, v_out=4, k_out=500, permute=True),
+    "v4_bare": dict(out_features=60, in_features=600, v=4, k=256, with_scale=False, with_bias=False),
+}
+
+
+@pytest.mark.parametrize("workspace", ["none", "fast"])
+@pytest.mark.parametrize("batch", [1, 3, 16])
+@pytest.mark.parametrize("orientation", [0, 1])
+@pytest.mark.parametrize("name", list(ROWS_LAYERS))
+def test_gemv_rows(gpu_lib, monkeypatch, name, orientation, batch, workspace):
+    """The matrix-core kernel for layers looked up entry by entry: ragged rows, streams, steps and groups, with NaN in the padding
+    of x and a sentinel in that of y."""
+    import torch
+    monkeypatch.setenv("VQ_SWITCHES", "rows=1")
+    kw = dict(ROWS_LAYERS[name], orientation=orientation)
+    if orientation and kw.get("group_vectors"):
+        kw["group_vectors"] = 600
+    L = s.make_layer(60 + list(ROWS_LAYERS).index(name), name, kw.pop("out_features"), kw.pop("in_features"), kw.pop("v"), kw.pop("k"), **kw)
+    x = s.make_activations(300, L, batch)
+    X = torch.full((batch, L.in_features + 4), float("nan"), dtype=torch.float16, device="cuda")
+    X[:, : L.in_features] = torch.from_numpy(x).cuda()
+    Y = torch.full((batch, L.out_features + 3), 7.0, dtype=torch.float16, device="cuda")
+    gpu_lib.gemv(gpu_lib.DeviceLayer(L), X, out=Y, workspace="fast" if workspace == "fast" else torch.empty(0, dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    _check_matmul(Y[:, : L.out_features], oracle.gemv(L, x), "%s orientation %d batch %d workspace %s" % (name, orientation, batch, workspace))
+    assert (Y[:, L.out_features:] == 7.0).all()
+
+
 V6_GEMM = ["v6_gemm_plain", "v6_gemm_res8", "v6_gemm_res12", "single_row", "v6_exact_fit", "v6_gemm_outlier32", "v6_gemm_outlier48",
            "v6_gemm_outlier16_res12"]
 
