@@ -42,7 +42,7 @@
  * The environment variable VQ_SWITCHES ("name=value,..."; read once at the
  * start of every call) forces kernel choices for tests and measurements:
  * gemv=g|m|d (generic / matrix-core / dot-product kernels), groups=loop, multi=0,
- * gemm=g|f|w|r|6, dense=0|1, dequant=g|s; unset, every choice is the library's own.
+ * gemm=g|f|w|r|6, dense=0|1, dequant=g; unset, every choice is the library's own.
  */
 #ifndef VQ_H
 #define VQ_H

@@ -45,8 +45,7 @@ int cu_count();
 //   gemm=g|f|w|r|6 vq_gemm: generic tile kernel / no restore-then-multiply / restore-then-multiply whenever a workspace is
 //                there / rows through vq_gemv / the on-the-fly kernel for v = 6 layers at every token count
 //   dense=0|1    the dense product of the restore-then-multiply route: always the smallest / the largest tiles
-//   dequant=g|s  vq_dequant: generic kernel / never the wide-store kernel (v = 6); two passes with a read-back instead of residual
-//                entries from memory where two tables do not fit LDS together (the other settings)
+//   dequant=g    vq_dequant: generic kernels
 struct Switches {
   char gemv = 0, gemm = 0, dequant = 0;
   bool groups_loop = false, multi_off = false;
@@ -62,7 +61,6 @@ int make_params(const vq_layer_desc *d, Params *p);
 
 // Kernel launchers (each returns a vq_status).
 int launch_dequant(const Params &p, __half *W, long long ldw, hipStream_t s);
-int launch_dequant_outliers(const Params &p, __half *W, long long ldw, hipStream_t s);   // generic kernel, outlier columns of a row-wise layer only
 int launch_gemv(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, hipStream_t s);
 bool gemv_has_fast_kernel(const Params &p, const __half *x, long long ldx);
 size_t gemv_workspace_bytes(const Params &p, const __half *x, long long ldx, int batch);

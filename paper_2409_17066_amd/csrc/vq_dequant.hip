@@ -82,25 +82,11 @@ __global__ __launch_bounds__(256) void dequant_down_kernel(Params p, __half *W, 
   }
 }
 
-// The outlier columns of a row-wise layer only (the main columns were restored by a fast kernel).
-int launch_dequant_outliers(const Params &p, __half *W, long long ldw, hipStream_t s) {
-  Params q = p;
-  q.P = 0;                                   // the generic kernel's slots are outlier vectors first, then main vectors
-  const int blocks_per_row = (q.Q + 255) / 256;
-  const long long blocks = (long long)blocks_per_row * q.out_features;
-  if (blocks > 0x7fffffffLL) return VQ_ERR_UNSUPPORTED;
-  hipLaunchKernelGGL(dequant_generic_kernel, dim3((unsigned)blocks), dim3(256), 0, s, q, W, ldw, blocks_per_row);
-  return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
-}
-
-int launch_dequant_fast(const Params &p, __half *W, long long ldw, hipStream_t s);
-int launch_dequant_down_fast(const Params &p, __half *W, long long ldw, hipStream_t s);
-int launch_dequant_lds(const Params &p, __half *W, long long ldw, hipStream_t s);
-int launch_dequant_down_lds(const Params &p, __half *W, long long ldw, hipStream_t s);
+int launch_dequant_tables(const Params &p, __half *W, long long ldw, hipStream_t s);
 
 int launch_dequant(const Params &p, __half *W, long long ldw, hipStream_t s) {
   if (p.perm && switches().dequant != 'g') {
-    // Permuted column order: restore in stored order with whatever kernel takes the layer, then move every row's values to
+    // Permuted column order: restore in stored order, then move every row's values to
     // their columns, in place, through LDS.  (Rows too long for LDS: the generic kernels below, which scatter their stores.)
     Params q = p;
     q.perm = nullptr;
@@ -109,32 +95,16 @@ int launch_dequant(const Params &p, __half *W, long long ldw, hipStream_t s) {
       return rc == VQ_OK ? launch_place_cols(W, ldw, p.out_features, p.in_features, p.perm, s) : rc;
     }
   }
+  const int rc = launch_dequant_tables(p, W, ldw, s);
+  if (rc != VQ_ERR_UNSUPPORTED) return rc;
   if (p.orientation == 1) {
     const int bps_main = (p.P + 255) / 256, bps_out = p.Q ? (p.Q + 255) / 256 : 1;
-    long long main_blocks = (long long)bps_main * p.S;
-    int rc = p.perm ? VQ_ERR_UNSUPPORTED : launch_dequant_down_fast(p, W, ldw, s);          // the main columns, when a fast kernel takes them
-    if (rc == VQ_ERR_UNSUPPORTED && !p.perm) rc = launch_dequant_down_lds(p, W, ldw, s);      // (the other settings: tables in LDS)
-    if (rc == VQ_OK) {
-      if (!p.Q) return VQ_OK;
-      main_blocks = 0;                                               // the generic kernel below: outlier streams only
-    } else if (rc != VQ_ERR_UNSUPPORTED) {
-      return rc;
-    }
-    const long long blocks = main_blocks + (long long)bps_out * p.S_out;
+    const long long main_blocks = (long long)bps_main * p.S, blocks = main_blocks + (long long)bps_out * p.S_out;
     if (blocks > 0x7fffffffLL) return VQ_ERR_UNSUPPORTED;
     hipLaunchKernelGGL(dequant_down_kernel, dim3((unsigned)blocks), dim3(256), 0, s, p, W, ldw, bps_main, main_blocks, bps_out);
     return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
   }
-  const int rc = p.perm ? VQ_ERR_UNSUPPORTED : launch_dequant_fast(p, W, ldw, s);
-  if (rc != VQ_ERR_UNSUPPORTED) return rc;
-  if (!p.perm) {
-    // the other (v, k) settings: main columns with the tables in LDS, the few outlier columns by the generic kernel
-    const int rl = launch_dequant_lds(p, W, ldw, s);
-    if (rl == VQ_OK) return p.Q ? launch_dequant_outliers(p, W, ldw, s) : VQ_OK;
-    if (rl != VQ_ERR_UNSUPPORTED) return rl;
-  }
-  const int slots = p.P + p.Q;
-  const int blocks_per_row = (slots + 255) / 256;
+  const int blocks_per_row = (p.P + p.Q + 255) / 256;
   const long long blocks = (long long)blocks_per_row * p.out_features;
   if (blocks > 0x7fffffffLL) return VQ_ERR_UNSUPPORTED;
   hipLaunchKernelGGL(dequant_generic_kernel, dim3((unsigned)blocks), dim3(256), 0, s, p, W, ldw, blocks_per_row);

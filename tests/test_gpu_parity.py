@@ -411,6 +411,29 @@ def test_dequant_permuted_columns_by_the_scattering_kernels(gpu_lib, monkeypatch
     assert np.array_equal(W.cpu().numpy().view(np.uint16), oracle.dequant(L, L.in_features + 5).view(np.uint16)), name
 
 
+@pytest.mark.parametrize("orientation", [0, 1])
+@pytest.mark.parametrize("out_features,in_features,v,k,more", [
+    (3, 24, 6, 4096, {}), (65, 513, 6, 256, dict(k_res=200)), (515, 1030, 6, 4096, dict(k_res=4096)), (66, 3077, 2, 16, dict(k_res=16)),
+    (1030, 520, 4, 256, {}), (130, 2056, 4, 4096, dict(k_res=3001, group_vectors=129)), (40, 9000, 8, 4096, dict(k_res=4096)),
+    (96, 600, 8, 65536, {}), (1040, 5000, 8, 65536, {}), (64, 520, 8, 65536, dict(k_res=300, group_vectors=31)), (64, 512, 8, 200, dict(k_res=65536)),
+    (70, 1029, 12, 4096, dict(k_res=4096)), (70, 1029, 12, 4096, dict(k_res=2722)), (600, 1500, 12, 4096, dict(k_res=4096, group_vectors=41)),
+    (133, 1207, 6, 4096, dict(k_res=256, n_outlier_cols=28, v_out=4, k_out=4096)), (133, 1207, 12, 4000, dict(n_outlier_cols=12, v_out=4, k_out=9, group_vectors=300)),
+])
+def test_dequant_tables_edges(gpu_lib, out_features, in_features, v, k, more, orientation):
+    """Runs that end with a row or a group, groups that begin anywhere, residual tables in LDS, split and in memory, W at any half."""
+    import torch
+    L = s.make_layer(8200, "edges", out_features, in_features, v, k, orientation=orientation, **more)
+    dl, want = gpu_lib.DeviceLayer(L), oracle.dequant(L).view(np.uint16)
+    for offset, ldw in ((0, (in_features + 7) // 8 * 8 + 8), (1, in_features)):
+        buf = torch.full((out_features * ldw + offset + 8,), 3.0, dtype=torch.float16, device="cuda")
+        assert gpu_lib.vq_dequant(dl.desc, buf.data_ptr() + 2 * offset, ldw, torch.cuda.current_stream().cuda_stream) == 0
+        torch.cuda.synchronize()
+        got = buf.cpu().numpy()
+        W = got[offset: offset + out_features * ldw].reshape(out_features, ldw)
+        assert np.array_equal(W[:, :in_features].view(np.uint16), want), offset
+        assert (W[:, in_features:] == 3.0).all() and (got[:offset] == 3.0).all() and (got[offset + out_features * ldw:] == 3.0).all()
+
+
 @pytest.mark.parametrize("name", ["lds_v12_two_tables", "lds_v12_groups_res_outlier", "down_lds_v12_two_tables", "down_lds_v12_odd_groups"])
 def test_dequant_two_tables_beyond_lds_in_two_passes(gpu_lib, monkeypatch, name):
     """Two tables that do not fit LDS together: by default the residual entries come from memory; dequant=s is the scheme
