@@ -119,6 +119,7 @@ bool gemv_res8_applicable(const Params &p, const __half *x);
 bool gemv_lds_applicable(const Params &p, int batch);
 int launch_gemv_lds(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, hipStream_t s);
 size_t gemv_lds_slots_workspace_bytes(const Params &p, int batch);
+int gemv_lds_slots(const Params &p);
 bool gemv_down_lds_applicable(const Params &p, int batch);
 size_t gemv_down_lds_slots_workspace_bytes(const Params &p, int batch);
 int launch_gemv_down_lds_slots(const Params &p, const __half *x, long long ldx, int batch, float *part, float *part_xs, hipStream_t s);
@@ -470,8 +471,9 @@ int launch_gemv_ws(const Params &p, const __half *x, long long ldx, int batch, _
     if (rc == VQ_OK) return launch_groups_finish(part, part_xs, slots, batch, p, y, ldy, s);
     if (rc != VQ_ERR_UNSUPPORTED || done != 0) return rc;
   } else if (need && workspace && workspace_bytes >= need && !gemv_fast_applicable(p, x, ldx)) {
-    if (!switches().groups_loop) {
-      const int slots = p.n_groups;                         // (the first group's workgroups also take the outlier columns)
+    const size_t slot_bytes = gemv_lds_slots_workspace_bytes(p, batch);
+    if (!switches().groups_loop && slot_bytes && workspace_bytes >= slot_bytes) {
+      const int slots = gemv_lds_slots(p);                  // (the outlier columns as a rule are one more)
       float *part = static_cast<float *>(workspace), *part_xs = part + (size_t)slots * (size_t)batch * (size_t)p.out_features;
       const int rc = launch_gemv_lds_slots(p, x, ldx, batch, part, part_xs, s);
       if (rc == VQ_OK) return launch_groups_finish(part, part_xs, slots, batch, p, y, ldy, s);

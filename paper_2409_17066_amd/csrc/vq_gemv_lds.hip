@@ -11,6 +11,7 @@
 // y = scale * sum(d x) + bias * sum(x), as in the other decode kernels.  No layout tricks: this kernel's job is to keep
 // every such layer off the generic kernel, whose table reads go through the caches (about 90 GB/s).
 #include "vq_lds_tables.hpp"
+#include <algorithm>
 
 namespace vq {
 
@@ -348,10 +349,11 @@ struct PassPlan {
   unsigned off_x, off_xo, off_xsum, off_ypart, bytes;     // byte offsets in dynamic LDS (the pass's table at 0)
   unsigned x_pitch, xo_pitch;                             // bytes per staged row of main / outlier columns
   int rows_per_wg;
-  // With a workspace on loan a workgroup takes one "slot" -- a codebook group (its main and residual table; the first group's
-  // workgroups also the outlier columns) -- and a block of rows, and leaves its sums in the workspace for the kernel that adds
-  // the slots up:
-  int n_slots, batch_total;                               // 0: every workgroup walks all passes and writes y
+  // With a workspace on loan a workgroup takes one "slot" -- a codebook group (its main and residual table) or the outlier
+  // columns -- and a block of rows, and leaves its sums in the workspace for the kernel that adds the slots up:
+  int n_slots, batch_total;                               // groups among the slots; 0: every workgroup walks all passes and writes y
+  int out_first, out_rows;                                // first of the workgroups for the outlier columns and the rows each takes; 0: the
+                                                          // first group's workgroups take the outlier columns as well
   float *part, *part_xs;                                  // [n_slots][batch_total][out_features] sums, [n_slots][16] activation sums
 };
 
@@ -359,15 +361,18 @@ template <int V, int BITS, int B>
 __global__ __launch_bounds__(LW * 64) void gemv_lds_passes_kernel(Params p, PassPlan plan, const __half *__restrict__ x, long long ldx,
                                                                   __half *__restrict__ y, long long ldy) {
   constexpr int U = win_vectors(BITS), ND = U * BITS / 32, EH = entry_halfs(V), ED = EH / 2, VD = V / 2;
+  constexpr bool XREGS = B == 1;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   float *xsum = reinterpret_cast<float *>(lds + plan.off_xsum);          // [B], then the waves' parts [B][LW]
   float *xpart = xsum + B;
   float *ypart = reinterpret_cast<float *>(lds + plan.off_ypart);        // row sums of the passes so far [rows_per_wg][B]
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const bool slots = plan.n_slots != 0;
-  const int slot = slots ? (int)blockIdx.x % plan.n_slots : 0;
-  const int row0 = (slots ? (int)blockIdx.x / plan.n_slots : (int)blockIdx.x) * plan.rows_per_wg;
-  const int row1 = min(p.out_features, row0 + plan.rows_per_wg);
+  const bool only_outliers = slots && plan.out_first && (int)blockIdx.x >= plan.out_first;
+  const int slot = only_outliers ? plan.n_slots : slots ? (int)blockIdx.x % plan.n_slots : 0;
+  const int rows_per_wg = only_outliers ? plan.out_rows : plan.rows_per_wg;
+  const int row0 = (only_outliers ? (int)blockIdx.x - plan.out_first : slots ? (int)blockIdx.x / plan.n_slots : (int)blockIdx.x) * rows_per_wg;
+  const int row1 = min(p.out_features, row0 + rows_per_wg);
   const int windows = (p.P + U - 1) / U;
   const __amdgpu_buffer_rsrc_t r_i = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(p.idx), 0, (unsigned)((long long)p.out_features * p.stride), 0x00020000);
   const __amdgpu_buffer_rsrc_t r_r = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(p.k_res ? p.idx_res : p.idx), 0,
@@ -380,9 +385,10 @@ __global__ __launch_bounds__(LW * 64) void gemv_lds_passes_kernel(Params p, Pass
     return (unsigned)src < (unsigned)p.in_features ? x[(long long)t * ldx + src] : __float2half_rn(0.0f);
   };
 
-  // ---- once: the activations of the outlier columns and their sum (with slots: the first slot's workgroups only); the main
+  // ---- once: the activations of the outlier columns and their sum (with slots: one slot's workgroups only); the main
   // columns are added to the sums as the passes restage them
-  const int once_cols = slot == 0 ? p.n_out : 0;
+  const bool with_outliers = plan.out_first ? only_outliers : slot == 0;
+  const int once_cols = with_outliers ? p.n_out : 0;
 #pragma unroll
   for (int t = 0; t < B; ++t) {
     __half *xo = reinterpret_cast<__half *>(lds + plan.off_xo + t * plan.xo_pitch);
@@ -399,8 +405,8 @@ __global__ __launch_bounds__(LW * 64) void gemv_lds_passes_kernel(Params p, Pass
   const int tables_per_group = p.k_res ? 2 : 1;
   const int table_passes = p.n_groups * tables_per_group;
   const int pass_begin = slots ? slot * tables_per_group : 0;
-  const int my_table_passes = slots ? tables_per_group : table_passes;
-  const int my_passes = my_table_passes + (p.Q && slot == 0 ? 1 : 0);
+  const int my_table_passes = only_outliers ? 0 : slots ? tables_per_group : table_passes;
+  const int my_passes = my_table_passes + (p.Q && with_outliers ? 1 : 0);
   for (int ip = 0; ip < my_passes; ++ip) {
     const int pass = ip < my_table_passes ? pass_begin + ip : table_passes;
     const bool outlier = pass == table_passes;
@@ -470,6 +476,18 @@ __global__ __launch_bounds__(LW * 64) void gemv_lds_passes_kernel(Params p, Pass
     }
     __syncthreads();
 
+    // ---- one activation row: a lane keeps those of its window in registers; where a row takes one round the window is the same for
+    // all rows of the pass (read from LDS in every round they took as many LDS cycles as the table lookups)
+    unsigned xr[XREGS ? U * VD : 1];
+    auto load_x = [&](int w) {
+      if constexpr (XREGS) {
+        const unsigned *from = reinterpret_cast<const unsigned *>(lds + plan.off_x) + (unsigned)min(w, w_hi - 1) * (unsigned)(U * VD);
+#pragma unroll
+        for (int d = 0; d < U * VD; ++d) xr[d] = from[d];
+      }
+    };
+    if (!outlier && w_hi > w_lo) load_x(w_lo + lane_w);
+
     // ---- the wave's rows, 64 windows a round, the next round's words loaded before the current ones are used
     float acc[B];
 #pragma unroll
@@ -495,6 +513,7 @@ __global__ __launch_bounds__(LW * 64) void gemv_lds_passes_kernel(Params p, Pass
           }
         } else {
           const unsigned xbase = plan.off_x + (unsigned)wdx * (U * V * 2u);
+          if (ipr > 1) load_x(wdx);
 #pragma unroll
           for (int u = 0; u < U; ++u) {
             const unsigned i = min(window_field<BITS, ND < 2 ? 2 : ND>(wm, u), (unsigned)k_a - 1u);
@@ -504,7 +523,7 @@ __global__ __launch_bounds__(LW * 64) void gemv_lds_passes_kernel(Params p, Pass
             for (int t = 0; t < B; ++t) {
 #pragma unroll
               for (int d = 0; d < VD; ++d) {
-                const unsigned xv = *reinterpret_cast<const unsigned *>(lds + xbase + t * plan.x_pitch + (unsigned)(u * V + 2 * d) * 2u);
+                const unsigned xv = XREGS ? xr[XREGS ? u * VD + d : 0] : *reinterpret_cast<const unsigned *>(lds + xbase + t * plan.x_pitch + (unsigned)(u * V + 2 * d) * 2u);
                 acc[t] = dot2(e[d], xv, acc[t]);
               }
             }
@@ -550,6 +569,11 @@ __global__ __launch_bounds__(LW * 64) void gemv_lds_passes_kernel(Params p, Pass
   }
 }
 
+// Whether the outlier columns get a slot, and workgroups, of their own: a sixteenth of the chip, which takes about as long over
+// them as the others over two tables of a group.  (The 2.26-bit 7B layer: the first group's workgroups, a third table after their
+// two, kept everybody waiting.)  With more groups the rows of a group are shared out among so few workgroups that one less counts more.
+bool outlier_slot(const Params &p) { return p.Q > 0 && p.n_groups <= 16 && cu_count() >= 64; }
+
 bool make_pass_plan(const Params &p, int batch, int u, int eh, PassPlan *plan, int n_slots = 0) {
   auto up16 = [](size_t v) { return (v + 15) / 16 * 16; };
   size_t table = up16((size_t)p.k * eh * 2);
@@ -557,12 +581,20 @@ bool make_pass_plan(const Params &p, int batch, int u, int eh, PassPlan *plan, i
   if (p.Q && up16((size_t)p.k_out * 8) > table) table = up16((size_t)p.k_out * 8);
   const size_t windows = ((size_t)p.P + u - 1) / u;
   const size_t pitch = up16(windows * u * p.v * 2), xo_pitch = up16((size_t)p.n_out * 2);
-  const int wgs = n_slots ? (cu_count() / n_slots > 0 ? cu_count() / n_slots : 1) : cu_count();     // workgroups per slot
+  const int out_wgs = n_slots && outlier_slot(p) ? cu_count() / 16 : 0;                       // workgroups for the outlier columns
+  const int group_wgs = n_slots ? (cu_count() - out_wgs) / n_slots : cu_count();              // and per group
+  const int wgs = group_wgs > 0 ? group_wgs : 1;
   plan->rows_per_wg = (p.out_features + wgs - 1) / wgs;
   if (plan->rows_per_wg < LW) plan->rows_per_wg = LW;
+  plan->out_first = 0; plan->out_rows = 0;
+  if (out_wgs) {
+    plan->out_first = (p.out_features + plan->rows_per_wg - 1) / plan->rows_per_wg * n_slots;
+    plan->out_rows = (p.out_features + out_wgs - 1) / out_wgs;
+    if (plan->out_rows < LW) plan->out_rows = LW;
+  }
   plan->n_slots = n_slots; plan->batch_total = 0; plan->part = nullptr; plan->part_xs = nullptr;
   const size_t sums = up16(4 * 4 * (1 + LW));
-  const size_t total = table + (pitch + xo_pitch) * batch + sums + (size_t)plan->rows_per_wg * batch * 4;
+  const size_t total = table + (pitch + xo_pitch) * batch + sums + (size_t)std::max(plan->rows_per_wg, plan->out_rows) * batch * 4;
   if (total > 160 * 1024) return false;
   if ((long long)p.out_features * p.stride >= (1LL << 32) || (long long)p.out_features * p.stride_res >= (1LL << 32) ||
       (long long)p.out_features * p.stride_out >= (1LL << 32)) return false;
@@ -596,7 +628,8 @@ int launch_slots(const Params &p, const __half *x, long long ldx, int n_slots, i
   plan.batch_total = batch_total; plan.part = part; plan.part_xs = part_xs;
   auto kernel = gemv_lds_passes_kernel<V, BITS, B>;
   VQ_ALLOW_FULL_LDS(kernel);
-  const unsigned grid = (unsigned)((p.out_features + plan.rows_per_wg - 1) / plan.rows_per_wg) * (unsigned)n_slots;
+  const unsigned grid = (unsigned)((p.out_features + plan.rows_per_wg - 1) / plan.rows_per_wg) * (unsigned)n_slots +
+                        (plan.out_first ? (unsigned)((p.out_features + plan.out_rows - 1) / plan.out_rows) : 0u);
   hipLaunchKernelGGL(kernel, dim3(grid), dim3(LW * 64), plan.bytes, s, p, plan, x, ldx, static_cast<__half *>(nullptr), 0LL);
   return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
 }
@@ -688,12 +721,14 @@ int launch_gemv_lds(const Params &p, const __half *x, long long ldx, int batch, 
 
 // Layers that the pass kernel takes and that have at least two codebook groups: with a workspace of
 // slots x (batch x out_features + 16) binary32 sums every workgroup takes one slot; 0 when that does not apply.
+int gemv_lds_slots(const Params &p) { return p.n_groups + (outlier_slot(p) ? 1 : 0); }
+
 size_t gemv_lds_slots_workspace_bytes(const Params &p, int batch) {
   PassPlan plan;
   const int n_slots = p.n_groups;
   if (p.orientation != 0 || n_slots < 2 || n_slots > 64 || !pass_pair(p)) return 0;
   if (!make_pass_plan(p, 1, win_vectors(p.bits), entry_halfs(p.v), &plan, n_slots)) return 0;
-  return ((size_t)n_slots * ((size_t)batch * (size_t)p.out_features + 16) * sizeof(float) + 255) / 256 * 256;
+  return ((size_t)gemv_lds_slots(p) * ((size_t)batch * (size_t)p.out_features + 16) * sizeof(float) + 255) / 256 * 256;
 }
 
 // The slots' sums into part [slots][batch][out_features] and part_xs [slots][16]; the caller adds them up.
