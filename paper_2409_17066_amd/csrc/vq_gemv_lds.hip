@@ -361,7 +361,6 @@ template <int V, int BITS, int B>
 __global__ __launch_bounds__(LW * 64) void gemv_lds_passes_kernel(Params p, PassPlan plan, const __half *__restrict__ x, long long ldx,
                                                                   __half *__restrict__ y, long long ldy) {
   constexpr int U = win_vectors(BITS), ND = U * BITS / 32, EH = entry_halfs(V), ED = EH / 2, VD = V / 2;
-  constexpr bool XREGS = B == 1;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   float *xsum = reinterpret_cast<float *>(lds + plan.off_xsum);          // [B], then the waves' parts [B][LW]
   float *xpart = xsum + B;
@@ -476,18 +475,6 @@ __global__ __launch_bounds__(LW * 64) void gemv_lds_passes_kernel(Params p, Pass
     }
     __syncthreads();
 
-    // ---- one activation row: a lane keeps those of its window in registers; where a row takes one round the window is the same for
-    // all rows of the pass (read from LDS in every round they took as many LDS cycles as the table lookups)
-    unsigned xr[XREGS ? U * VD : 1];
-    auto load_x = [&](int w) {
-      if constexpr (XREGS) {
-        const unsigned *from = reinterpret_cast<const unsigned *>(lds + plan.off_x) + (unsigned)min(w, w_hi - 1) * (unsigned)(U * VD);
-#pragma unroll
-        for (int d = 0; d < U * VD; ++d) xr[d] = from[d];
-      }
-    };
-    if (!outlier && w_hi > w_lo) load_x(w_lo + lane_w);
-
     // ---- the wave's rows, 64 windows a round, the next round's words loaded before the current ones are used
     float acc[B];
 #pragma unroll
@@ -512,8 +499,9 @@ __global__ __launch_bounds__(LW * 64) void gemv_lds_passes_kernel(Params p, Pass
             acc[t] = dot2(e.y, xv.y, acc[t]);
           }
         } else {
+          // (from LDS in every round: a lane's activations of the window kept in registers, restaged in every pass, made one row
+          // without a workspace 41 -> 64 us, 11008 x 4096 in the 2.26-bit setting, and 28 -> 30 with one)
           const unsigned xbase = plan.off_x + (unsigned)wdx * (U * V * 2u);
-          if (ipr > 1) load_x(wdx);
 #pragma unroll
           for (int u = 0; u < U; ++u) {
             const unsigned i = min(window_field<BITS, ND < 2 ? 2 : ND>(wm, u), (unsigned)k_a - 1u);
@@ -523,7 +511,7 @@ __global__ __launch_bounds__(LW * 64) void gemv_lds_passes_kernel(Params p, Pass
             for (int t = 0; t < B; ++t) {
 #pragma unroll
               for (int d = 0; d < VD; ++d) {
-                const unsigned xv = XREGS ? xr[XREGS ? u * VD + d : 0] : *reinterpret_cast<const unsigned *>(lds + xbase + t * plan.x_pitch + (unsigned)(u * V + 2 * d) * 2u);
+                const unsigned xv = *reinterpret_cast<const unsigned *>(lds + xbase + t * plan.x_pitch + (unsigned)(u * V + 2 * d) * 2u);
                 acc[t] = dot2(e[d], xv, acc[t]);
               }
             }
@@ -570,8 +558,9 @@ __global__ __launch_bounds__(LW * 64) void gemv_lds_passes_kernel(Params p, Pass
 }
 
 // Whether the outlier columns get a slot, and workgroups, of their own: a sixteenth of the chip, which takes about as long over
-// them as the others over two tables of a group.  (The 2.26-bit 7B layer: the first group's workgroups, a third table after their
-// two, kept everybody waiting.)  With more groups the rows of a group are shared out among so few workgroups that one less counts more.
+// them as the others over two tables of a group.  (Else the first group's workgroups, a third table after their two, keep everybody
+// waiting: the 2.26-bit setting, one row, 11008 x 4096 31.7 -> 28.0 us, 4096 x 4096 18.6 -> 16.2, 8192 x 8192 39.7 -> 34.6; two rows 38.5
+// -> 35.1.)  With more groups the rows of a group are shared out among so few workgroups that one less counts more.
 bool outlier_slot(const Params &p) { return p.Q > 0 && p.n_groups <= 16 && cu_count() >= 64; }
 
 bool make_pass_plan(const Params &p, int batch, int u, int eh, PassPlan *plan, int n_slots = 0) {

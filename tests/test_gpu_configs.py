@@ -192,3 +192,30 @@ def test_the_2_26_bit_setting_at_full_size(gpu_lib, orientation):
     torch.cuda.synchronize()
     rows = np.arange(0, L.out_features, 16).astype(np.int32)
     _matmul_ok(Y[:, torch.from_numpy(rows.astype(np.int64)).cuda()], oracle.gemm(L, x, rows=rows), "2.26-bit setting, 300 tokens")
+
+
+@pytest.mark.parametrize("out,inp", [(11008, 4096), (4096, 11008)])
+def test_one_row_of_the_2_26_bit_setting_takes_no_longer_than_two(gpu_lib, out, inp):
+    """Without a workspace both go through the kernel that keeps one table in LDS at a time, and two rows do all that one does
+    and the products of the second besides (41 and 49 us for 11008 x 4096)."""
+    import torch
+    n_out = int(inp * 0.01 / 4 + 0.5) * 4
+    P = -(-(inp - n_out) // 12)
+    L = s.make_layer(1, "up", out, inp, 12, 4096, 4096, n_outlier_cols=n_out, v_out=4, k_out=8192, group_vectors=-(-P // 32) * 8)
+    dl = gpu_lib.DeviceLayer(L)
+    x = torch.from_numpy(s.make_activations(1, L, 2)).cuda()
+    none = torch.empty(0, dtype=torch.uint8, device="cuda")
+
+    def microseconds(batch):
+        y = torch.empty((batch, out), dtype=torch.float16, device="cuda")
+        begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        begin.record()
+        for _ in range(50):
+            gpu_lib.gemv(dl, x[:batch], out=y, workspace=none)
+        end.record()
+        torch.cuda.synchronize()
+        return begin.elapsed_time(end) * 20.0
+    microseconds(1), microseconds(2)
+    times = sorted((microseconds(1), microseconds(2)) for _ in range(7))
+    one, two = sorted(t[0] for t in times)[3], sorted(t[1] for t in times)[3]
+    assert one <= 1.1 * two, "one row %.1f us, two rows %.1f us" % (one, two)
