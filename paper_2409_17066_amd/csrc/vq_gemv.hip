@@ -119,7 +119,7 @@ bool gemv_res8_applicable(const Params &p, const __half *x);
 bool gemv_lds_applicable(const Params &p, int batch);
 int launch_gemv_lds(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, hipStream_t s);
 size_t gemv_lds_slots_workspace_bytes(const Params &p, int batch);
-int gemv_lds_slots(const Params &p);
+int gemv_lds_slots(const Params &p, int batch);
 bool gemv_down_lds_applicable(const Params &p, int batch);
 size_t gemv_down_lds_slots_workspace_bytes(const Params &p, int batch);
 int launch_gemv_down_lds_slots(const Params &p, const __half *x, long long ldx, int batch, float *part, float *part_xs, hipStream_t s);
@@ -385,14 +385,16 @@ static bool permuted_in_kernel(const Params &p, const __half *x, long long ldx, 
 }
 
 // Rows of an odd width start between dwords for all but the first: the kernel that wants dwords has them copied, which costs 2 us
-// (v = 12, 305 x 1281, 2 rows: 10.4 us, 11.1 with the copy).
-static bool rows_gathered(const Params &p, int batch) { return batch >= 5 && (p.in_features & 1) && rows_wanted(p, batch, true); }
+// (v = 12, 305 x 1281, 2 rows: 10.4 us, 11.1 with the copy).  (The copy counts as workspace, and of rows beyond 2^18 columns it could ask
+// for more than vq_gemv_static_workspace has, which would refuse a layer that needs none.)
+static bool rows_gathered(const Params &p, int batch) { return batch >= 5 && (p.in_features & 1) && p.in_features < (1 << 18) && rows_wanted(p, batch, true); }
 
 static size_t stored_order_workspace_bytes(const Params &p, const __half *x, long long ldx, int batch) {
   if (rows_wanted(p, batch, true) && (batch == 1 || !(ldx & 1))) {
-    // (with codebook groups a caller may count on a slot for each, also where the kernel walks the groups by itself)
-    const size_t need = gemv_rows_workspace_bytes(p, batch), slots = p.n_groups > 1 ? ((size_t)p.n_groups * ((size_t)batch * (size_t)p.out_features + 16) * sizeof(float) + 255) / 256 * 256 : 0;
-    return need ? need : slots;
+    // (0 with codebook groups that the kernel walks by itself: the slots of the kernels below are asked for instead, which run where
+    // this one does not take x)
+    const size_t need = gemv_rows_workspace_bytes(p, batch);
+    if (need) return need;
   }
   if (p.orientation == 1 && down_mfma_parts_wanted(p, x, ldx, batch)) {   // the matrix cores: the workspace lets parts of the columns run side by side
     const int parts = gemv_down_mfma_parts(p);            // the outlier columns are one more set of sums to add up
@@ -416,7 +418,9 @@ size_t gemv_workspace_bytes(const Params &p, const __half *x, long long ldx, int
     if (p.perm && permuted_in_kernel(p, x, ldx, batch)) return 0;
     Params q = p;
     q.perm = nullptr;
-    return permuted_x_bytes(p, batch) + stored_order_workspace_bytes(q, nullptr, (p.in_features + 7) & ~7, batch);
+    const size_t head = permuted_x_bytes(p, batch), rest = stored_order_workspace_bytes(q, nullptr, (p.in_features + 7) & ~7, batch);
+    // (the column parts of vq_gemv_rows.hip are done without where the two together are more than vq_gemv_static_workspace has)
+    return rows_wanted(q, batch, true) && head + rest > VQ_GEMV_STATIC_WORKSPACE_BYTES ? head : head + rest;
   }
   return stored_order_workspace_bytes(p, x, ldx, batch);
 }
@@ -473,7 +477,7 @@ int launch_gemv_ws(const Params &p, const __half *x, long long ldx, int batch, _
   } else if (need && workspace && workspace_bytes >= need && !gemv_fast_applicable(p, x, ldx)) {
     const size_t slot_bytes = gemv_lds_slots_workspace_bytes(p, batch);
     if (!switches().groups_loop && slot_bytes && workspace_bytes >= slot_bytes) {
-      const int slots = gemv_lds_slots(p);                  // (the outlier columns as a rule are one more)
+      const int slots = gemv_lds_slots(p, batch);                  // (the outlier columns as a rule are one more)
       float *part = static_cast<float *>(workspace), *part_xs = part + (size_t)slots * (size_t)batch * (size_t)p.out_features;
       const int rc = launch_gemv_lds_slots(p, x, ldx, batch, part, part_xs, s);
       if (rc == VQ_OK) return launch_groups_finish(part, part_xs, slots, batch, p, y, ldy, s);

@@ -561,16 +561,22 @@ __global__ __launch_bounds__(LW * 64) void gemv_lds_passes_kernel(Params p, Pass
 // them as the others over two tables of a group.  (Else the first group's workgroups, a third table after their two, keep everybody
 // waiting: the 2.26-bit setting, one row, 11008 x 4096 31.7 -> 28.0 us, 4096 x 4096 18.6 -> 16.2, 8192 x 8192 39.7 -> 34.6; two rows 38.5
 // -> 35.1.)  With more groups the rows of a group are shared out among so few workgroups that one less counts more.
-bool outlier_slot(const Params &p) { return p.Q > 0 && p.n_groups <= 16 && cu_count() >= 64; }
+// And as long as the sums, one slot more, fit the library's own workspace: vq_gemv_static_workspace refuses layers that ask for more.
+size_t slots_bytes(const Params &p, int slots, int batch) {
+  return ((size_t)slots * ((size_t)batch * (size_t)p.out_features + 16) * sizeof(float) + 255) / 256 * 256;
+}
+bool outlier_slot(const Params &p, int batch) {
+  return p.Q > 0 && p.n_groups <= 16 && cu_count() >= 64 && slots_bytes(p, p.n_groups + 1, batch) <= VQ_GEMV_STATIC_WORKSPACE_BYTES;
+}
 
-bool make_pass_plan(const Params &p, int batch, int u, int eh, PassPlan *plan, int n_slots = 0) {
+bool make_pass_plan(const Params &p, int batch, int u, int eh, PassPlan *plan, int n_slots = 0, bool out_slot = false) {
   auto up16 = [](size_t v) { return (v + 15) / 16 * 16; };
   size_t table = up16((size_t)p.k * eh * 2);
   if (up16((size_t)p.k_res * eh * 2) > table) table = up16((size_t)p.k_res * eh * 2);
   if (p.Q && up16((size_t)p.k_out * 8) > table) table = up16((size_t)p.k_out * 8);
   const size_t windows = ((size_t)p.P + u - 1) / u;
   const size_t pitch = up16(windows * u * p.v * 2), xo_pitch = up16((size_t)p.n_out * 2);
-  const int out_wgs = n_slots && outlier_slot(p) ? cu_count() / 16 : 0;                       // workgroups for the outlier columns
+  const int out_wgs = out_slot ? cu_count() / 16 : 0;                                          // workgroups for the outlier columns
   const int group_wgs = n_slots ? (cu_count() - out_wgs) / n_slots : cu_count();              // and per group
   const int wgs = group_wgs > 0 ? group_wgs : 1;
   plan->rows_per_wg = (p.out_features + wgs - 1) / wgs;
@@ -613,7 +619,7 @@ int launch_passes(const Params &p, const __half *x, long long ldx, __half *y, lo
 template <int V, int BITS, int B>
 int launch_slots(const Params &p, const __half *x, long long ldx, int n_slots, int batch_total, float *part, float *part_xs, hipStream_t s) {
   PassPlan plan;
-  if (!make_pass_plan(p, B, win_vectors(BITS), entry_halfs(V), &plan, n_slots)) return VQ_ERR_UNSUPPORTED;
+  if (!make_pass_plan(p, B, win_vectors(BITS), entry_halfs(V), &plan, n_slots, outlier_slot(p, batch_total))) return VQ_ERR_UNSUPPORTED;
   plan.batch_total = batch_total; plan.part = part; plan.part_xs = part_xs;
   auto kernel = gemv_lds_passes_kernel<V, BITS, B>;
   VQ_ALLOW_FULL_LDS(kernel);
@@ -710,14 +716,14 @@ int launch_gemv_lds(const Params &p, const __half *x, long long ldx, int batch, 
 
 // Layers that the pass kernel takes and that have at least two codebook groups: with a workspace of
 // slots x (batch x out_features + 16) binary32 sums every workgroup takes one slot; 0 when that does not apply.
-int gemv_lds_slots(const Params &p) { return p.n_groups + (outlier_slot(p) ? 1 : 0); }
+int gemv_lds_slots(const Params &p, int batch) { return p.n_groups + (outlier_slot(p, batch) ? 1 : 0); }
 
 size_t gemv_lds_slots_workspace_bytes(const Params &p, int batch) {
   PassPlan plan;
   const int n_slots = p.n_groups;
   if (p.orientation != 0 || n_slots < 2 || n_slots > 64 || !pass_pair(p)) return 0;
-  if (!make_pass_plan(p, 1, win_vectors(p.bits), entry_halfs(p.v), &plan, n_slots)) return 0;
-  return ((size_t)gemv_lds_slots(p) * ((size_t)batch * (size_t)p.out_features + 16) * sizeof(float) + 255) / 256 * 256;
+  if (!make_pass_plan(p, 1, win_vectors(p.bits), entry_halfs(p.v), &plan, n_slots, outlier_slot(p, batch))) return 0;
+  return slots_bytes(p, gemv_lds_slots(p, batch), batch);
 }
 
 // The slots' sums into part [slots][batch][out_features] and part_xs [slots][16]; the caller adds them up.

@@ -139,6 +139,36 @@ def test_gemv_with_workspace_rejects_bad_arguments_before_any_launch():
     assert vq.vq_gemv_workspace_bytes(_desc(in_features=5 * 64, idx_row_stride=96, v=5, k=4096, group_vectors=12), 2) == 0    # no kernel of v = 5 uses one
 
 
+# (layer, rows): what vq_gemv_static_workspace takes, and of what size at most
+FIT_THE_STATIC_WORKSPACE = [
+    # 67 codebook groups that the kernel walks by itself (more workgroups than the chip has room for): no workspace at all
+    (dict(out_features=28672, in_features=4288 * 4, v=4, k=256, group_vectors=64), 16, 0),
+    (dict(out_features=4096, in_features=28672, v=4, k=256, group_vectors=72), 16, 0),
+    (dict(out_features=27520, in_features=56038, v=12, k=4096, k_res=4096, group_vectors=704, orientation=1), 4, 0),
+    # rows of an odd width whose copy alone would take more; the same where a column permutation asks for nearly all of it
+    (dict(out_features=256, in_features=(1 << 20) + 1, v=6, k=256), 16, 1 << 24),
+    (dict(out_features=1544, in_features=516012, v=2, k=16, orientation=1, col_perm=0x10000), 16, 1 << 24),
+    # sixteen codebook groups whose sums fit, and would not with a seventeenth set of sums for the outlier columns
+    (dict(out_features=16000, in_features=16 * 48 + 40, v=6, k=4096, n_outlier_cols=40, v_out=4, k_out=8192, group_vectors=8), 16, 1 << 24),
+]
+
+
+@pytest.mark.parametrize("layer,batch,most", FIT_THE_STATIC_WORKSPACE)
+def test_no_more_workspace_than_the_library_has_where_none_was_needed(layer, batch, most):
+    """vq_gemv_static_workspace refuses a layer whose vq_gemv_workspace_bytes exceeds its array: a kernel that does without, or
+    with less, must not ask for more."""
+    import vq_synth as s
+    f = dict(layer, out=layer["out_features"], inp=layer["in_features"], n=layer.get("n_outlier_cols", 0))
+    main = f["inp"] - f["n"] if f.get("orientation") else -(-(f["inp"] - f["n"]) // f["v"])
+    d = _desc(**layer, idx_row_stride=s.row_stride_bytes(main, s.index_bits(f["k"])))
+    if f.get("k_res"):
+        d.codebook_res, d.idx_res, d.idx_res_row_stride = 0x10000, 0x10000, s.row_stride_bytes(main, s.index_bits(f["k_res"]))
+    if f["n"]:
+        d.codebook_out, d.idx_out, d.idx_out_row_stride = 0x10000, 0x10000, s.row_stride_bytes(f["n"] // 4, s.index_bits(f["k_out"]))
+    assert vq.vq_validate(d) == vq.VQ_OK
+    assert vq.vq_gemv_workspace_bytes(d, batch) <= min(most, vq.VQ_GEMV_STATIC_WORKSPACE_BYTES)
+
+
 def test_gemv_workspace_for_vectors_down_the_output_dimension():
     """Orientation 1 on the matrix cores cuts the columns into parts when a workspace is there: asked for from two rows
     on (one row stays on the kernel that needs none), sized parts x (rows x tokens + 16) floats, parts >= 2."""

@@ -60,3 +60,20 @@ def test_static_workspace_layer_without_groups_is_plain_gemv(gpu_lib):
     y_static, ref, need = _run(gpu_lib, torch, L, 3, "static")
     assert need == 0
     assert np.abs(y_static.astype(np.float64) - ref).max() <= TOL * float(np.sqrt((ref ** 2).mean()))
+
+
+@pytest.mark.parametrize("name,args,kw,batch", [
+    # codebook groups that the kernel walks by itself: 67 of them, nothing from the workspace
+    ("many groups", (2048, 4288 * 4, 4, 256), dict(group_vectors=64), 16),
+    # sixteen groups whose sums nearly fill the array: the outlier columns go to the first group's workgroups
+    ("full", (16000, 16 * 48 + 40, 6, 4096, 0, 40, 4, 8192), dict(group_vectors=8), 16),
+    # permuted columns, and vectors down the outputs in parts
+    ("permuted", (600, 9001, 12, 4096, 4096), dict(orientation=1, permute=True), 7),
+])
+def test_static_workspace_of_layers_at_its_limits(gpu_lib, name, args, kw, batch):
+    L = s.make_layer(934, "static_ws_" + name, *args, **kw)
+    y_static, ref, need = _run(gpu_lib, __import__("torch"), L, batch, "static")
+    assert need <= gpu_lib.VQ_GEMV_STATIC_WORKSPACE_BYTES
+    assert np.abs(y_static.astype(np.float64) - ref).max() <= TOL * float(np.sqrt((ref ** 2).mean()))
+    y_ws, _, _ = _run(gpu_lib, __import__("torch"), L, batch, "workspace")
+    assert np.array_equal(y_static.view(np.uint16), y_ws.view(np.uint16))
