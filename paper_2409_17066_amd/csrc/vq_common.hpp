@@ -117,11 +117,18 @@ template <int LINES = 4>
 __device__ __forceinline__ void warm_kernel_arguments() {      // the first LINES (4 or 5) lines of 64 bytes
 #if defined(__HIP_DEVICE_COMPILE__)
   const auto ka = __builtin_amdgcn_kernarg_segment_ptr();
-  unsigned a, b, c, d, e;
-  if constexpr (LINES >= 5) asm volatile("s_load_dword %0, %1, 0x100" : "=&s"(e) : "s"(ka) : "memory");
-  asm volatile("s_load_dword %0, %4, 0x0\n\ts_load_dword %1, %4, 0x40\n\ts_load_dword %2, %4, 0x80\n\t"
-               "s_load_dword %3, %4, 0xc0\n\ts_waitcnt lgkmcnt(0)"
-               : "=&s"(a), "=&s"(b), "=&s"(c), "=&s"(d) : "s"(ka) : "memory");
+  // (loads and wait in one statement: the compiler may reuse the registers of a statement behind it at once)
+  unsigned a, b, c, d;
+  if constexpr (LINES >= 5) {
+    unsigned e;
+    asm volatile("s_load_dword %0, %5, 0x0\n\ts_load_dword %1, %5, 0x40\n\ts_load_dword %2, %5, 0x80\n\t"
+                 "s_load_dword %3, %5, 0xc0\n\ts_load_dword %4, %5, 0x100\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&s"(a), "=&s"(b), "=&s"(c), "=&s"(d), "=&s"(e) : "s"(ka) : "memory");
+  } else {
+    asm volatile("s_load_dword %0, %4, 0x0\n\ts_load_dword %1, %4, 0x40\n\ts_load_dword %2, %4, 0x80\n\t"
+                 "s_load_dword %3, %4, 0xc0\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&s"(a), "=&s"(b), "=&s"(c), "=&s"(d) : "s"(ka) : "memory");
+  }
 #endif
 }
 

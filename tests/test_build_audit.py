@@ -89,3 +89,20 @@ def test_a_younger_load_of_the_same_queue_may_reuse_the_destination():
     assert len(check_async.audit(_asm(other))) == 1                    # another queue: no order between the two
     addr = ["#ASMSTART", "ds_read_b32 v40, v1", "#ASMEND", "#ASMSTART", "ds_read_b32 v41, v40", "#ASMEND"]
     assert len(check_async.audit(_asm(addr))) == 1                     # an address register must have landed
+
+
+def _statements_with_loads_on_their_way(text):
+    """Inline-assembly statements that issue a load and do not wait for it themselves."""
+    import re
+    found = []
+    for m in re.finditer(r"\basm(?:\s+volatile)?\s*\(\s*((?:\"(?:[^\"\\]|\\.)*\"\s*)+)", text):
+        if re.search(r"\b(ds_read|buffer_load|global_load|flat_load|scratch_load|s_load|s_buffer_load)", m.group(1)) and "s_waitcnt" not in m.group(1):
+            found.append(m.group(1))
+    return found
+
+
+def test_the_common_header_waits_for_its_loads():
+    """Every kernel includes it, so no build check looks at what its statements leave on their way."""
+    import build
+    assert _statements_with_loads_on_their_way('asm volatile("s_load_dword %0, %1, 0x0" : "=s"(e))')
+    assert not _statements_with_loads_on_their_way(open(os.path.join(build.CSRC, "vq_common.hpp")).read())
