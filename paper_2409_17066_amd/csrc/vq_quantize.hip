@@ -22,6 +22,37 @@ namespace {
 constexpr int QS = 3;            // stack positions per workgroup of the column kernel
 constexpr int SW = 4;            // waves that share the search of one position
 
+// One padded table entry (EH halfs) as EH / 2 dwords.  From LDS the read is issued from inline assembly as one or two whole
+// 16-byte reads (8 bytes for the smallest entries): left to the compiler, a read whose tail is unused is narrowed and
+// split into 2- and 8-byte reads at odd offsets, which the LDS serves many times slower.  The caller waits
+// (lds_reads_done) before it looks at the registers.
+template <int EH>
+__device__ __forceinline__ void read_entry_lds(unsigned (&dst)[EH / 2], unsigned lds_addr) {
+  if constexpr (EH == 4) {
+    uint2v r;
+    asm volatile("ds_read_b64 %0, %1" : "=v"(r) : "v"(lds_addr));
+    dst[0] = r.x; dst[1] = r.y;
+  } else {
+#pragma unroll
+    for (int q = 0; q < EH / 8; ++q) {
+      uint4v r;
+      if (q == 0) asm volatile("ds_read_b128 %0, %1" : "=v"(r) : "v"(lds_addr));
+      else asm volatile("ds_read_b128 %0, %1 offset:16" : "=v"(r) : "v"(lds_addr));
+      dst[4 * q] = r.x; dst[4 * q + 1] = r.y; dst[4 * q + 2] = r.z; dst[4 * q + 3] = r.w;
+    }
+  }
+}
+template <int N>
+__device__ __forceinline__ void lds_reads_done(unsigned (&regs)[N]) {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+  for (int i = 0; i < N; ++i) asm volatile("" : "+v"(regs[i]));      // nothing reads them ahead of the wait
+}
+template <int EH>
+__device__ __forceinline__ void read_entry_global(unsigned (&dst)[EH / 2], const __half *entry) {
+#pragma unroll
+  for (int q = 0; q < EH / 2; ++q) dst[q] = reinterpret_cast<const unsigned *>(entry)[q];
+}
 constexpr int entry_halfs(int v) { return v <= 4 ? 4 : v <= 8 ? 8 : 16; }     // table entries padded to 8, 16 or 32 bytes
 
 struct QArgs {

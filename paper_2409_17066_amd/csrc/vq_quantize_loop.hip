@@ -155,6 +155,27 @@ __device__ __forceinline__ void post_vector(LoopExchange &x, int p, float t, con
   }
 }
 
+// One padded table entry (EH halfs) from LDS, in whole 16-byte reads (8 bytes for the smallest entries; the compiler narrows and splits
+// a read whose tail is unused).  The wait stands in the same statement: this file's larger variants spill, and a register must not be
+// saved while a read into it is on its way.
+template <int EH>
+__device__ __forceinline__ void read_entry(unsigned (&dst)[EH / 2], unsigned lds_addr) {
+  if constexpr (EH == 4) {
+    uint2v a;
+    asm volatile("ds_read_b64 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(a) : "v"(lds_addr) : "memory");
+    dst[0] = a.x; dst[1] = a.y;
+  } else if constexpr (EH == 8) {
+    uint4v a;
+    asm volatile("ds_read_b128 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(a) : "v"(lds_addr) : "memory");
+    dst[0] = a.x; dst[1] = a.y; dst[2] = a.z; dst[3] = a.w;
+  } else {
+    uint4v a, b;
+    asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %2 offset:16\n\ts_waitcnt lgkmcnt(0)" : "=&v"(a), "=v"(b) : "v"(lds_addr) : "memory");
+    dst[0] = a.x; dst[1] = a.y; dst[2] = a.z; dst[3] = a.w;
+    dst[4] = b.x; dst[5] = b.y; dst[6] = b.z; dst[7] = b.w;
+  }
+}
+
 // One search of all P posted vectors over a table of `count` entries; every wave of the workgroup takes part.
 template <int VP, int G>
 __device__ __forceinline__ void search_table(LoopExchange &x, const half8v (&A)[G][group_tiles(VP)], unsigned lds_entries, int count, int P, int par,
@@ -213,8 +234,7 @@ __device__ __forceinline__ void search_table(LoopExchange &x, const half8v (&A)[
       if (from == (lane & 3)) ask &= ask - 1u;
       const int i = min((g / TILES * waves + wave) * 64 + (g % TILES * SW + from) * 16 + (lane >> 4) * 4 + (lane & 3), count - 1);
       unsigned c[EH / 2];
-      read_entry_lds<EH>(c, lds_entries + (unsigned)i * (EH * 2u));
-      lds_reads_done(c);
+      read_entry<EH>(c, lds_entries + (unsigned)i * (EH * 2u));
       float d = 0.0f;
 #pragma unroll
       for (int j = 0; j < VP; ++j) {

@@ -106,3 +106,25 @@ def test_the_common_header_waits_for_its_loads():
     import build
     assert _statements_with_loads_on_their_way('asm volatile("s_load_dword %0, %1, 0x0" : "=s"(e))')
     assert not _statements_with_loads_on_their_way(open(os.path.join(build.CSRC, "vq_common.hpp")).read())
+
+
+def test_files_with_loads_on_their_way_may_not_spill_and_are_audited():
+    """A register that is the target of such a load must not be saved, copied or reused before the wait, and only the build's two
+    checks see to that: the file, and every file that includes it, has to be subject to both."""
+    import re
+
+    import build
+    names = sorted(os.listdir(build.CSRC))
+    text = {n: open(os.path.join(build.CSRC, n)).read() for n in names if n.endswith((".hip", ".hpp"))}
+
+    def closure(n, seen):
+        if n in text and n not in seen:
+            seen.add(n)
+            for h in re.findall(r'#include "([^"]+)"', text[n]):
+                closure(h, seen)
+        return seen
+    sources = [n for n in text if n.endswith(".hip")]
+    assert sorted(sources) == sorted(build.SOURCES)
+    with_loads = {n for n in sources if any(_statements_with_loads_on_their_way(text[f]) for f in closure(n, set()))}
+    assert len(with_loads) >= 8
+    assert with_loads <= set(build.AUDITED) and with_loads <= set(build.NO_SPILL), sorted(with_loads - (set(build.AUDITED) & set(build.NO_SPILL)))
