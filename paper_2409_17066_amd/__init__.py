@@ -72,6 +72,8 @@ def load():
     L.vq_gemm_workspace_bytes.restype = ctypes.c_size_t
     L.vq_gemm_fast_workspace_bytes.argtypes = [P, ctypes.c_int32]
     L.vq_gemm_fast_workspace_bytes.restype = ctypes.c_size_t
+    L.vq_gemm_default_workspace_bytes.argtypes = [P, ctypes.c_int32]
+    L.vq_gemm_default_workspace_bytes.restype = ctypes.c_size_t
     L.vq_quantize_columns_workspace_bytes.argtypes = [ctypes.c_int32] * 4
     L.vq_quantize_columns_workspace_bytes.restype = ctypes.c_size_t
     L.vq_quantize_columns.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, ctypes.c_void_p, ctypes.c_int64,
@@ -89,7 +91,7 @@ def load():
 
 
 EXPORTED = ["vq_validate", "vq_dequant", "vq_gemv", "vq_gemv_workspace_bytes", "vq_gemv_with_workspace", "vq_gemv_static_workspace", "vq_gemv_multi", "vq_gemm", "vq_gemm_workspace_bytes", "vq_gemm_fast_workspace_bytes",
-            "vq_assign", "vq_assign_down", "vq_quantize_columns", "vq_quantize_columns_workspace_bytes", "vq_status_string", "vq_version"]
+            "vq_gemm_default_workspace_bytes", "vq_assign", "vq_assign_down", "vq_quantize_columns", "vq_quantize_columns_workspace_bytes", "vq_status_string", "vq_version"]
 
 
 # ---- the C entry points, same names, raw pointers (ints) and sizes ---------------------------------------
@@ -162,6 +164,10 @@ def vq_gemm_fast_workspace_bytes(desc, tokens):
     return load().vq_gemm_fast_workspace_bytes(ctypes.byref(desc), tokens)
 
 
+def vq_gemm_default_workspace_bytes(desc, tokens):
+    return load().vq_gemm_default_workspace_bytes(ctypes.byref(desc), tokens)
+
+
 def vq_status_string(status):
     return load().vq_status_string(status).decode()
 
@@ -182,8 +188,8 @@ def _native():
         L = load()
         from . import _binding as b
         b.bind({name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value
-                for name in ("vq_gemv", "vq_gemv_with_workspace", "vq_gemv_multi", "vq_gemm", "vq_gemm_workspace_bytes", "vq_gemm_fast_workspace_bytes", "vq_gemv_workspace_bytes", "vq_dequant", "vq_assign",
-                             "vq_assign_down")})
+                for name in ("vq_gemv", "vq_gemv_with_workspace", "vq_gemv_multi", "vq_gemm", "vq_gemm_workspace_bytes",
+                             "vq_gemm_default_workspace_bytes", "vq_gemv_workspace_bytes", "vq_dequant", "vq_assign", "vq_assign_down")})
         _bound = b
     return _bound
 
@@ -368,8 +374,9 @@ def quantize_columns(W, Hinv, codebook, codebook_res=None, block=128, want_T=Tru
 def gemm(dl: DeviceLayer, X, out=None, workspace=None):
     """X: fp16 [tokens][>=in] device tensor -> fp16 [tokens][out].  workspace: a uint8 device tensor, or "fast" to
     allocate the one vq_gemm_fast_workspace_bytes asks for (the restore-then-multiply route), or None, which from nine
-    tokens on does the same: torch's allocator hands the memory out and takes it back in stream order.  (An empty tensor
-    leaves the library without one.)"""
+    tokens on allocates the one of vq_gemm_default_workspace_bytes (as "fast" where the weights are rounded to binary16 in
+    any case): torch's allocator hands the memory out and takes it back in stream order.  (An empty tensor leaves the
+    library without one.)"""
     Y = (_bound or _native()).gemm(dl, X, out, workspace)
     if Y.__class__ is int:
         raise VQError(Y, "vq_gemm")
@@ -380,7 +387,7 @@ def gemm(dl: DeviceLayer, X, out=None, workspace=None):
     Y = out if out is not None else torch.empty((X.shape[0], dl.layer.out_features), dtype=torch.float16, device="cuda")
     if isinstance(workspace, str) or (workspace is None and X.shape[0] > 8):
         assert workspace in (None, "fast")
-        fast = vq_gemm_fast_workspace_bytes(dl.desc, X.shape[0])
+        fast = (vq_gemm_fast_workspace_bytes if workspace else vq_gemm_default_workspace_bytes)(dl.desc, X.shape[0])
         try:
             workspace = torch.empty(fast, dtype=torch.uint8, device="cuda") if fast else None
         except torch.OutOfMemoryError:

@@ -19,7 +19,7 @@ decltype(&vq_gemv_with_workspace) p_gemv_ws;
 decltype(&vq_gemv_workspace_bytes) p_gemv_workspace_bytes;
 decltype(&vq_gemv_multi) p_gemv_multi;
 decltype(&vq_gemm) p_gemm;
-decltype(&vq_gemm_workspace_bytes) p_gemm_workspace_bytes, p_gemm_fast_workspace_bytes;
+decltype(&vq_gemm_workspace_bytes) p_gemm_workspace_bytes, p_gemm_default_workspace_bytes;
 decltype(&vq_dequant) p_dequant;
 decltype(&vq_assign) p_assign, p_assign_down;
 
@@ -169,7 +169,7 @@ PyObject *gemm(PyObject *, PyObject *const *args, Py_ssize_t n) {
     const at::Tensor &ws = THPVariable_Unpack(args[3]);
     wp = ws.data_ptr();
     bytes = (size_t)ws.numel() * ws.element_size();
-  } else if (tokens > 8 && (bytes = p_gemm_fast_workspace_bytes(d, tokens)) != 0) {
+  } else if (tokens > 8 && (bytes = p_gemm_default_workspace_bytes(d, tokens)) != 0) {
     try {
       scratch = empty({(int64_t)bytes}, at::kByte);
       wp = scratch.data_ptr();
@@ -253,7 +253,7 @@ PyObject *bind(PyObject *, PyObject *addresses) {
     return f != nullptr;
   };
   if (!at("vq_gemv", p_gemv) || !at("vq_gemv_with_workspace", p_gemv_ws) || !at("vq_gemv_multi", p_gemv_multi) || !at("vq_gemm", p_gemm) ||
-      !at("vq_gemm_workspace_bytes", p_gemm_workspace_bytes) || !at("vq_gemv_workspace_bytes", p_gemv_workspace_bytes) || !at("vq_gemm_fast_workspace_bytes", p_gemm_fast_workspace_bytes) ||
+      !at("vq_gemm_workspace_bytes", p_gemm_workspace_bytes) || !at("vq_gemv_workspace_bytes", p_gemv_workspace_bytes) || !at("vq_gemm_default_workspace_bytes", p_gemm_default_workspace_bytes) ||
        !at("vq_dequant", p_dequant) || !at("vq_assign", p_assign) || !at("vq_assign_down", p_assign_down)) {
     if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "an entry point is missing");
     return nullptr;

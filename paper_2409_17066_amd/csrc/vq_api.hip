@@ -250,6 +250,13 @@ extern "C" size_t vq_gemm_fast_workspace_bytes(const vq_layer_desc *desc, int32_
   return vq::gemm_fast_workspace_bytes(p, tokens);
 }
 
+extern "C" size_t vq_gemm_default_workspace_bytes(const vq_layer_desc *desc, int32_t tokens) {
+  vq::read_switches();
+  vq::Params p;
+  if (vq::make_params(desc, &p) != VQ_OK || tokens < 1) return 0;
+  return vq::gemm_default_workspace_bytes(p, tokens);
+}
+
 extern "C" int vq_gemm(const vq_layer_desc *desc, const void *X, int64_t ldx, int32_t tokens,
                        void *Y, int64_t ldy, void *workspace, size_t workspace_bytes, void *hip_stream) {
   vq::read_switches();

@@ -85,6 +85,7 @@ int launch_quantize_columns(float *W, long long ldw, int rows, int cols, const f
                             long long idx_res_stride, float *T, long long ldt, void *workspace, hipStream_t st);
 size_t gemm_workspace_bytes(const Params &p, int tokens);
 size_t gemm_fast_workspace_bytes(const Params &p, int tokens);
+size_t gemm_default_workspace_bytes(const Params &p, int tokens);
 
 #ifdef __HIPCC__
 // Index p of a row's little-endian bitstream (bits <= 16).  `row` is 4-byte aligned and the row's

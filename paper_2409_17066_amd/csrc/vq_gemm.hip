@@ -196,6 +196,24 @@ static bool rows_beat_restoring(const Params &p, int tokens) {
   return (float)((tokens + 15) / 16) * launch < restore + gemm_dense_us(p, tokens);
 }
 
+static bool v6_tiles_fill(const Params &p, int tokens) { return tokens > 128 || (long long)((p.out_features + 127) / 128) * ((tokens + 127) / 128) >= 80; }
+
+// Whether the tile kernels would be a loss of precision: without a workspace these layers and token counts go through vq_gemv's kernels,
+// which keep centroids, scale and bias apart and in binary32 where the others multiply with weights rounded to binary16.
+static bool rows_hold_the_weights(const Params &p, int tokens) {
+  const long long ldx = (p.in_features + 7) & ~7;
+  if (p.perm || gemm_fused_applicable(p) || (gemm_v6_applicable(p) && tokens > 64 && v6_tiles_fill(p, tokens))) return false;
+  if (gemv_has_fast_kernel(p, nullptr, ldx)) return tokens <= 128 || (p.orientation == 0 && p.v == 6);
+  return tokens <= 32 && gemv_has_lds_kernel(p, nullptr, ldx);
+}
+
+// What a caller without a workspace of its own does well to allocate: room for W where it would be rounded in any case, else what
+// vq_gemv's kernels use.
+size_t gemm_default_workspace_bytes(const Params &p, int tokens) {
+  if (rows_hold_the_weights(p, tokens)) return gemv_workspace_bytes(p, nullptr, (p.in_features + 7) & ~7, tokens < 16 ? tokens : 16);
+  return gemm_fast_workspace_bytes(p, tokens);
+}
+
 // Routes, in this order:
 //  1. a workspace of gemm_fast_workspace_bytes() is there: vq_dequant into it, then the dense product (vq_gemm_dense.hip).  This
 //     is the paper's prompt-phase scheme; on gfx950 it beats restoring on the fly at every token count measured (17 to 2048),
@@ -239,8 +257,7 @@ int launch_gemm(const Params &p, const __half *X, long long ldx, int tokens, __h
   const char forced = switches().gemm;
   const size_t fast = gemm_fast_workspace_bytes(p, tokens);
   const bool have_ws = fast && workspace && workspace_bytes >= fast && (reinterpret_cast<uintptr_t>(workspace) & 15) == 0;
-  const bool v6_tiles_fill = tokens > 128 || (long long)((p.out_features + 127) / 128) * ((tokens + 127) / 128) >= 80;
-  if (gemm_v6_applicable(p) && (forced == '6' || (forced == '\0' && !have_ws && tokens > 64 && v6_tiles_fill))) {
+  if (gemm_v6_applicable(p) && (forced == '6' || (forced == '\0' && !have_ws && tokens > 64 && v6_tiles_fill(p, tokens)))) {
     const int rc = launch_gemm_v6(p, X, ldx, tokens, Y, ldy, s);
     if (rc != VQ_ERR_UNSUPPORTED) return rc;
   }
@@ -254,7 +271,7 @@ int launch_gemm(const Params &p, const __half *X, long long ldx, int tokens, __h
     else rows = (tokens <= 128 && fast_rows) || (tokens <= 32 && !gemm_v6_applicable(p) && lds_rows);
   }
   if (rows) {
-    const bool lend = have_ws && (reinterpret_cast<uintptr_t>(workspace) & 255) == 0;      // (vq_gemv cuts the columns into parts with it)
+    const bool lend = workspace && (reinterpret_cast<uintptr_t>(workspace) & 255) == 0;      // (vq_gemv cuts the columns into parts with it)
     for (int t0 = 0; t0 < tokens; t0 += 16) {
       const int rc = launch_gemv_ws(p, X + (long long)t0 * ldx, ldx, tokens - t0 < 16 ? tokens - t0 : 16, Y + (long long)t0 * ldy, ldy,
                                     lend ? workspace : nullptr, lend ? workspace_bytes : 0, s);

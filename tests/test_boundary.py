@@ -219,3 +219,23 @@ def test_assign_down_rejects_bad_arguments_before_any_launch():
 def test_binding_has_no_cpu_fallback():
     src = open(os.path.join(ROOT, "paper_2409_17066_amd", "__init__.py")).read()
     assert "oracle" not in src.replace("no CPU fallback", "")
+
+
+def test_default_workspace_of_gemm_has_room_for_W_only_where_it_is_rounded_anyway():
+    def default(tokens, **kw):
+        d = _desc(**kw)
+        assert vq.vq_validate(d) == vq.VQ_OK
+        return vq.vq_gemm_default_workspace_bytes(d, tokens), vq.vq_gemm_fast_workspace_bytes(d, tokens), vq.vq_gemv_workspace_bytes(d, min(tokens, 16))
+    v6 = dict(out_features=11008, in_features=4096, v=6, k=4096, idx_row_stride=1040)
+    for tokens, rounded in ((9, False), (64, False), (65, True), (509, True)):      # the kernel that restores on the fly from 65 tokens on
+        got, fast, rows = default(tokens, **v6)
+        assert fast == 11008 * 4096 * 2 and got == (fast if rounded else rows)
+    for tokens in (9, 100, 5000):                                                   # codebook groups: it takes none
+        got, fast, rows = default(tokens, **dict(v6, group_vectors=176))
+        assert fast and got == rows < fast
+    down = dict(out_features=11008, in_features=4096, v=6, k=4096, idx_row_stride=6144, orientation=1)
+    assert [default(t, **down)[0] == default(t, **down)[2] for t in (16, 128, 129)] == [True, True, False]
+    v12 = dict(out_features=11008, in_features=4096, v=12, k=4096, idx_row_stride=528)
+    assert [default(t, **v12)[0] == default(t, **v12)[2] for t in (16, 32, 33)] == [True, True, False]
+    assert default(9, **dict(v6, col_perm=0x1000))[0] == default(9, **dict(v6, col_perm=0x1000))[1]      # the generic tile kernel
+    assert vq.vq_gemm_default_workspace_bytes(_desc(v=0), 4) == 0

@@ -147,6 +147,58 @@ ROWS_LAYERS = {
 }
 
 
+def _unrounded_weights(gpu_lib, L):
+    """scale * (main + residual) + bias in binary64: what the products multiply with before anything is rounded.  (A layer without
+    residual, scale and bias restores to its centroids, exactly.)"""
+    import copy
+    parts = []
+    for codebook, idx, k in ((L.codebook, L.idx, L.k),) + (((L.codebook_res, L.idx_res, L.k_res),) if L.k_res else ()):
+        P = copy.copy(L)
+        P.codebook, P.idx, P.k, P.codebook_res, P.idx_res, P.k_res, P.scale, P.bias = codebook, idx, k, None, None, 0, None, None
+        D = gpu_lib.dequant(gpu_lib.DeviceLayer(P)).double()
+        if parts and L.n_outlier_cols:
+            D[:, : L.n_outlier_cols] = 0.0
+        parts.append(D)
+    scale, bias = (torch_double(a) for a in (L.scale, L.bias))
+    return scale[:, None] * sum(parts) + bias[:, None]
+
+
+def torch_double(a):
+    import torch
+    return torch.from_numpy(a.astype(np.float64)).cuda()
+
+
+HOLD_THE_WEIGHTS = {            # layers and token counts that vq_gemm without a workspace computes from unrounded weights
+    "v6, 64 tokens": (dict(out_features=512, in_features=1536, v=6, k=4096), 64),
+    "v6, no room for tiles": (dict(out_features=512, in_features=1536, v=6, k=4096, k_res=4096), 100),
+    "v6 groups": (dict(out_features=512, in_features=1536, v=6, k=4096, k_res=256, group_vectors=64), 300),
+    "orientation 1": (dict(out_features=384, in_features=1600, v=6, k=4096, orientation=1), 128),
+    "v4": (dict(out_features=512, in_features=1600, v=4, k=256), 32),
+    "v12": (dict(out_features=512, in_features=1536, v=12, k=4096, k_res=4096), 17),
+}
+
+
+@pytest.mark.parametrize("name", list(HOLD_THE_WEIGHTS))
+def test_gemm_by_default_rounds_no_weights_that_it_would_not_round_without_a_workspace(gpu_lib, name):
+    """The relative error (2-norm, against unrounded weights) of the default call against that of an empty workspace.  Rounding
+    every result to binary16 gives about 2^-12 / sqrt(3) * 1.4 = 2e-4; weights rounded as well add as much in quadrature, 1.4 times
+    the error, so 1.1 tells the two apart at 2^17 results."""
+    import torch
+    kw, tokens = HOLD_THE_WEIGHTS[name]
+    kw = dict(kw)
+    L = s.make_layer(61, "hold", kw.pop("out_features"), kw.pop("in_features"), kw.pop("v"), kw.pop("k"), kw.pop("k_res", 0), **kw)
+    dl = gpu_lib.DeviceLayer(L)
+    X = torch.from_numpy(s.make_activations(300, L, tokens)).cuda()
+    want = X.double() @ _unrounded_weights(gpu_lib, L).T.contiguous()
+
+    def error(workspace):
+        Y = gpu_lib.gemm(dl, X, workspace=workspace).double()
+        return float((Y - want).norm() / want.norm())
+    by_default, without, restored = error(None), error(torch.empty(0, dtype=torch.uint8, device="cuda")), error("fast")
+    print("%s: default %.3g, without %.3g, fast %.3g" % (name, by_default, without, restored))
+    assert by_default <= 1.1 * without
+
+
 @pytest.mark.parametrize("workspace", ["none", "fast"])
 @pytest.mark.parametrize("batch", [1, 3, 16])
 @pytest.mark.parametrize("orientation", [0, 1])
