@@ -259,7 +259,7 @@ size_t vq_gemm_fast_workspace_bytes(const vq_layer_desc *desc, int32_t tokens);
  * it to binary16, and so do the kernels that restore on the fly; vq_gemv's kernels keep centroids, scale and bias unrounded.  Where
  * vq_gemm without a workspace takes the latter (layers with v = 6 along the rows that the on-the-fly kernel does not take; up to 128
  * tokens of the other layers with a vq_gemv kernel of their own, up to 32 of those whose tables fit LDS) this is the size that they
- * use, as vq_gemv_workspace_bytes gives it, elsewhere vq_gemm_fast_workspace_bytes.                                           */
+ * use, as vq_gemv_workspace_bytes gives it, elsewhere vq_gemm_fast_workspace_bytes; 0 instead of more than 256 MiB.            */
 size_t vq_gemm_default_workspace_bytes(const vq_layer_desc *desc, int32_t tokens);
 
 /* Text for a status code (static storage).  */

@@ -225,6 +225,17 @@ class DeviceLayer:
         self.places_every_column = perm is None or bool((numpy.bincount(inside, minlength=layer.in_features) > 0).all())
 
 
+def _borrow(need):
+    """Workspace for one call from torch's allocator; None where neither it nor the device has that much to spare."""
+    import torch
+    if not need or (need > 1 << 20 and torch.cuda.mem_get_info()[0] + torch.cuda.memory_reserved() - torch.cuda.memory_allocated() < need):
+        return None
+    try:
+        return torch.empty(need, dtype=torch.uint8, device="cuda")
+    except torch.OutOfMemoryError:
+        return None
+
+
 def _stream():
     import torch
     return torch.cuda.current_stream().cuda_stream
@@ -271,11 +282,7 @@ def gemv(dl: DeviceLayer, x, out=None, workspace=None):
     if workspace is None:
         L = dl.layer
         plain = L.group_vectors or (L.v == 6 and L.k > 2048 and getattr(L, "col_perm", None) is None)
-        need = 0 if plain else vq_gemv_workspace_bytes(dl.desc, x.shape[0])
-        try:
-            workspace = torch.empty(need, dtype=torch.uint8, device="cuda") if need else None
-        except torch.OutOfMemoryError:
-            pass
+        workspace = None if plain else _borrow(vq_gemv_workspace_bytes(dl.desc, x.shape[0]))
     if workspace is None:
         rc = vq_gemv(dl.desc, x.data_ptr(), x.stride(0), x.shape[0], y.data_ptr(), y.stride(0), _stream())
     else:
@@ -375,8 +382,8 @@ def gemm(dl: DeviceLayer, X, out=None, workspace=None):
     """X: fp16 [tokens][>=in] device tensor -> fp16 [tokens][out].  workspace: a uint8 device tensor, or "fast" to
     allocate the one vq_gemm_fast_workspace_bytes asks for (the restore-then-multiply route), or None, which from nine
     tokens on allocates the one of vq_gemm_default_workspace_bytes (as "fast" where the weights are rounded to binary16 in
-    any case): torch's allocator hands the memory out and takes it back in stream order.  (An empty tensor leaves the
-    library without one.)"""
+    any case, and 256 MiB at most): torch's allocator hands the memory out and takes it back in stream order.  (An
+    empty tensor leaves the library without one, and so does a full card.)"""
     Y = (_bound or _native()).gemm(dl, X, out, workspace)
     if Y.__class__ is int:
         raise VQError(Y, "vq_gemm")
@@ -385,14 +392,12 @@ def gemm(dl: DeviceLayer, X, out=None, workspace=None):
     import torch
     assert X.is_cuda and X.dtype == torch.float16 and X.dim() == 2 and X.stride(1) == 1
     Y = out if out is not None else torch.empty((X.shape[0], dl.layer.out_features), dtype=torch.float16, device="cuda")
-    if isinstance(workspace, str) or (workspace is None and X.shape[0] > 8):
-        assert workspace in (None, "fast")
-        fast = (vq_gemm_fast_workspace_bytes if workspace else vq_gemm_default_workspace_bytes)(dl.desc, X.shape[0])
-        try:
-            workspace = torch.empty(fast, dtype=torch.uint8, device="cuda") if fast else None
-        except torch.OutOfMemoryError:
-            if workspace is not None:
-                raise
+    if workspace is None and X.shape[0] > 8:
+        workspace = _borrow(vq_gemm_default_workspace_bytes(dl.desc, X.shape[0]))
+    elif isinstance(workspace, str):
+        assert workspace == "fast"
+        fast = vq_gemm_fast_workspace_bytes(dl.desc, X.shape[0])
+        workspace = torch.empty(fast, dtype=torch.uint8, device="cuda") if fast else None
     need = vq_gemm_workspace_bytes(dl.desc, X.shape[0])
     if need and (workspace is None or workspace.numel() * workspace.element_size() < need):
         workspace = torch.empty(need, dtype=torch.uint8, device="cuda")

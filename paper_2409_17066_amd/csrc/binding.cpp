@@ -6,6 +6,7 @@
 #include <Python.h>
 #include <ATen/hip/EmptyTensor.h>
 #include <ATen/ops/zeros.h>
+#include <c10/hip/HIPCachingAllocator.h>
 #include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -68,6 +69,26 @@ PyObject *tensor_or_status(int rc, at::TensorBase &&fresh, PyObject *given) {
   return THPVariable_Wrap(std::move(fresh));
 }
 
+// Workspace for one call, from torch's allocator, or nullptr: there is a route without.  On a full card the allocator would first give
+// all its unused memory back and wait for the GPU, in every call: beyond the size of small results it is asked only for what it has
+// unused or the device has free.
+void *borrow(at::TensorBase &scratch, size_t bytes) {
+  try {
+    if (bytes > (1u << 20)) {
+      using c10::CachingAllocator::StatType;
+      const auto stats = c10::hip::HIPCachingAllocator::getDeviceStats(c10::hip::current_device());
+      const auto sum = static_cast<size_t>(StatType::AGGREGATE);
+      const size_t unused = (size_t)(stats.reserved_bytes[sum].current - stats.allocated_bytes[sum].current);
+      size_t free = 0, total = 0;
+      if (unused < bytes && hipMemGetInfo(&free, &total) == hipSuccess && free + unused < bytes) return nullptr;
+    }
+    scratch = empty({(int64_t)bytes}, at::kByte);
+    return scratch.data_ptr();
+  } catch (const c10::Error &) {
+    return nullptr;
+  }
+}
+
 #define VQ_TRY try {
 #define VQ_CATCH                                            \
   } catch (const std::exception &e) {                       \
@@ -109,12 +130,7 @@ PyObject *gemv(PyObject *, PyObject *const *args, Py_ssize_t n) {
     rc = released([&] { return p_gemv_ws(d, xp, ldx, batch, yp, ldy, wp, bytes, s); });
   } else if (const size_t bytes = lends_workspace(*d) ? p_gemv_workspace_bytes(d, batch) : 0) {
     at::TensorBase scratch;
-    void *wp = nullptr;
-    try {
-      scratch = empty({(int64_t)bytes}, at::kByte);
-      wp = scratch.data_ptr();
-    } catch (const c10::OutOfMemoryError &) {      // (there is a route without)
-    }
+    void *wp = borrow(scratch, bytes);
     rc = released([&] { return p_gemv_ws(d, xp, ldx, batch, yp, ldy, wp, wp ? bytes : 0, s); });
   } else {
     rc = released([&] { return p_gemv(d, xp, ldx, batch, yp, ldy, s); });
@@ -170,12 +186,8 @@ PyObject *gemm(PyObject *, PyObject *const *args, Py_ssize_t n) {
     wp = ws.data_ptr();
     bytes = (size_t)ws.numel() * ws.element_size();
   } else if (tokens > 8 && (bytes = p_gemm_default_workspace_bytes(d, tokens)) != 0) {
-    try {
-      scratch = empty({(int64_t)bytes}, at::kByte);
-      wp = scratch.data_ptr();
-    } catch (const c10::OutOfMemoryError &) {      // (there is a route without)
-      bytes = 0;
-    }
+    wp = borrow(scratch, bytes);
+    if (!wp) bytes = 0;
   }
   if (p_gemm_workspace_bytes(d, tokens) > bytes) Py_RETURN_NONE;
   at::TensorBase fresh;

@@ -239,3 +239,5 @@ def test_default_workspace_of_gemm_has_room_for_W_only_where_it_is_rounded_anywa
     assert [default(t, **v12)[0] == default(t, **v12)[2] for t in (16, 32, 33)] == [True, True, False]
     assert default(9, **dict(v6, col_perm=0x1000))[0] == default(9, **dict(v6, col_perm=0x1000))[1]      # the generic tile kernel
     assert vq.vq_gemm_default_workspace_bytes(_desc(v=0), 4) == 0
+    wide = dict(in_features=8192, v=8, k=65536, idx_row_stride=2048)                # 256 MiB, and more
+    assert default(100, **dict(wide, out_features=16384))[0] == 1 << 28 and default(100, **dict(wide, out_features=16385))[0] == 0

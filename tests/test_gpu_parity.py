@@ -199,6 +199,32 @@ def test_gemm_by_default_rounds_no_weights_that_it_would_not_round_without_a_wor
     assert by_default <= 1.1 * without
 
 
+@pytest.mark.parametrize("out_features,refused", [(16384, False), (8192, True)])
+def test_gemm_by_default_borrows_256_mib_at_most(gpu_lib, out_features, refused):
+    """W of 16384 x 8448 takes 264 MiB: the call goes without.  And one whose workspace (132 MiB) the allocator refuses does so too."""
+    import torch
+    L = s.make_layer(62, "large", out_features, 8448, 8, 65536)
+    dl = gpu_lib.DeviceLayer(L)
+    x = s.make_activations(300, L, 64)
+    X = torch.from_numpy(x).cuda()
+    Y = gpu_lib.gemm(dl, X, workspace=torch.empty(0, dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    torch.cuda.reset_peak_memory_stats()
+    before = torch.cuda.memory_allocated()
+    if refused:
+        torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + (8 << 20)) / torch.cuda.get_device_properties(0).total_memory)
+    try:
+        got = gpu_lib.gemm(dl, X)
+        torch.cuda.synchronize()
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert torch.cuda.max_memory_allocated() - before < 32 << 20
+    assert torch.equal(got, Y)
+    rows = np.arange(0, out_features, 64).astype(np.int32)
+    _check_matmul(got[:, torch.from_numpy(rows.astype(np.int64)).cuda()], oracle.gemm(L, x, rows=rows), "%d outputs" % out_features)
+
+
 @pytest.mark.parametrize("workspace", ["none", "fast"])
 @pytest.mark.parametrize("batch", [1, 3, 16])
 @pytest.mark.parametrize("orientation", [0, 1])
