@@ -4,20 +4,25 @@
 // nearest even to binary16; the results are the same bits.
 //
 // Vectors along the row: a lane restores sixteen bytes of it at a time, and looks up exactly what they hold: whole vectors (v = 2, 4, 8),
-// the four dwords of two neighbouring vectors (v = 6), two thirds of one or two (v = 12).  So a wave writes 1 KB in one piece, or, where
+// two thirds of one or two (v = 12); v = 6: one vector, twelve bytes, with one read and one store (as sixteen bytes it took four reads
+// of a dword from two vectors, 11008 x 4096 with v6 + 4096 31 -> 28 us).  So a wave writes 1 KB (768 bytes) in one piece, or, where
 // rows (or a codebook group's part of them) are shorter, the same of several rows.  Vectors down the outputs: a lane looks
-// eight columns up and writes eight weights of each of the v rows.  The next item's indices are in flight meanwhile.  Tables sit in LDS
+// eight columns up and writes eight weights of each of the v rows.  The next item's indices are in flight meanwhile; along the rows they
+// go to the other one of two sets of registers, so that nothing waits for the stores behind them (28 -> 26.5 us).  Tables sit in LDS
 // as they are in memory, copied without passing through registers; of a residual table of 12-element vectors that does not fit beside
 // the main one, the first two thirds (the others, and the 1 MiB table of 16-bit indices, are read through L2; W is then written past
 // the caches, so that it does not push the table out: 11008 x 4096 with v = 12 / 4096 + 4096 38 -> 31 us, v = 8 / 65536 31 -> 28).  With
 // codebook groups a workgroup serves one group.  Outlier columns (vectors of four) are extra workgroups of the same launch.
 //
+// W of more than 256 MiB, the memory-side cache, is written past the caches as well: 8192 x 28672 with v6 / 4096 145 -> 94 us, + 4096 162
+// -> 105, v4 / 256 134 -> 94, down the outputs 114 -> 92 and 114 -> 89.  Below, what follows finds it there, and lines shared by two
+// waves cost: 8192 x 8192 in four groups 29 us through the caches, 40 past them.
+//
 // What bounds it: writing W (6.8 TB/s on this card: 13 us for 11008 x 4096, and 3.5 of launch), with a table in memory the lookups.
-// Measured there, along the rows / down the outputs, against the kernels before (strips and transposes in LDS, dword stores, a
-// separate launch for outliers): v6 / 4096 20.0 / 17.2 us (19.8 / 18.9), + 4096 29 / 22 (36 / 26), + 256 and outliers 24 / 22
-// (31.5 / 30), v4 and v6 / 256 17.6 .. 18.7 / 17 (29 .. 33 / 58), v2 / 16 18 / 18 (45 / 72), v8 / 65536 28 / 30 (31 / 58),
-// v12 / 4096 + 4096 28 / 22 (58 / 61), with 4 groups and outliers 38 / 34 (81 / 70), v6 with 4 groups 24 / 17 (31 / 92).
-// Four runs per turn instead of two left fewer, longer turns to share out (+ 4096: 32 us; 640 x 576: 4.7 instead of 4.2).
+// Measured there, along the rows / down the outputs, against the first kernels (strips and transposes in LDS, dword stores, a
+// separate launch for outliers): v6 / 4096 20.3 / 17.2 us (20.4 / 18.9), + 4096 26.4 / 22 (36 / 26), + 256 and outliers 25.3 / 22
+// (32 / 30), v4 and v6 / 256 18.5 / 17 (30 .. 33 / 58), v2 / 16 18 / 18 (45 / 72), v8 / 65536 30 / 30 (32 / 58),
+// v12 / 4096 + 4096 30 / 22 (58 / 61), with 4 groups and outliers 38 / 34 (81 / 70), v6 with 4 groups 22 / 17 (32 / 92).
 #include "vq_lds_tables.hpp"
 #include <type_traits>
 #include <utility>
@@ -28,8 +33,16 @@ namespace {
 
 using namespace lds_tables;
 
-typedef unsigned uint4b __attribute__((ext_vector_type(4), aligned(2)));      // 16 and 8 bytes at any half
+typedef unsigned uint4b __attribute__((ext_vector_type(4), aligned(2)));      // 16, 12 and 8 bytes at any half
+typedef unsigned uint3b __attribute__((ext_vector_type(3), aligned(2)));
 typedef unsigned uint2b __attribute__((ext_vector_type(2), aligned(2)));
+
+constexpr int chunk_weights(int v) { return v == 6 ? 6 : 8; }      // of a row that a lane restores at a time
+
+// Runs along the row that a wave takes at a time: two, to have enough loads and stores on their way; four left fewer, longer turns to
+// share out (v6 + 4096, 11008 x 4096: 32 us at the time; 640 x 576: 4.7 instead of 4.2), and so do two of the quickest ones (v6 / 4096,
+// 4096 x 4096: 11.1 us instead of 10.2; with a residual table one is slower, 28.4 instead of 26.4).
+constexpr int runs_per_turn(int v, int bits, bool residual) { return v == 6 && bits == 12 && !residual ? 1 : 2; }
 
 enum Residual { NO_RES, RES_LDS, RES_MEM, RES_SPLIT };      // where the residual table is: RES_SPLIT, its first entries in LDS, the others in memory
 
@@ -50,9 +63,14 @@ __device__ __forceinline__ void copy16(const __amdgpu_buffer_rsrc_t &from, unsig
   __builtin_amdgcn_raw_ptr_buffer_load_lds(from, (__attribute__((address_space(3))) void *)to, 16, offset, 0, 0, 0);
 }
 __device__ __forceinline__ unsigned load4(const __amdgpu_buffer_rsrc_t &r, unsigned offset) { return __builtin_amdgcn_raw_buffer_load_b32(r, offset, 0, 0); }
+__device__ __forceinline__ unsigned short load2(const __amdgpu_buffer_rsrc_t &r, unsigned offset) { return (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(r, offset, 0, 0); }
 __device__ __forceinline__ uint2v load8(const __amdgpu_buffer_rsrc_t &r, unsigned offset) { return __builtin_bit_cast(uint2v, __builtin_amdgcn_raw_buffer_load_b64(r, offset, 0, 0)); }
 __device__ __forceinline__ uint4v load16(const __amdgpu_buffer_rsrc_t &r, unsigned offset) { return __builtin_bit_cast(uint4v, __builtin_amdgcn_raw_buffer_load_b128(r, offset, 0, 0)); }
 
+template <bool STREAM> __device__ __forceinline__ void store12(__half *to, const unsigned (&w)[3]) {
+  if constexpr (STREAM) __builtin_nontemporal_store((uint3b{w[0], w[1], w[2]}), reinterpret_cast<uint3b *>(to));
+  else *reinterpret_cast<uint3b *>(to) = uint3b{w[0], w[1], w[2]};
+}
 template <bool STREAM> __device__ __forceinline__ void store16(__half *to, const unsigned (&w)[4]) {
   if constexpr (STREAM) __builtin_nontemporal_store((uint4b{w[0], w[1], w[2], w[3]}), reinterpret_cast<uint4b *>(to));
   else *reinterpret_cast<uint4b *>(to) = uint4b{w[0], w[1], w[2], w[3]};
@@ -180,38 +198,44 @@ __global__ __launch_bounds__(NW * 64, 4) void dequant_tables_kernel(Params p, Dq
   // (segments > 1 only with whole waves to a row: rows * segments^2 < 2^32, which the launcher sees to)
   auto by_segments = [&](unsigned n) { return a.segments == 1 ? n : __umulhi(n, a.segments_inv); };
 
+  auto per_output = [&](const __half *values) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<__half *>(values ? values : p.cb), 0, values ? (unsigned)p.out_features * 2u : 0u, 0x00020000);
+  };
+
   if constexpr (!DOWN) {
-    constexpr int SUB = 2, N = V == 6 || V == 12 ? 2 : 8 / V, RB_ = RBITS ? RBITS : 8;
-    constexpr bool ONE = V == 8 && BITS != 12, RONE = V == 8 && RB_ != 12;      // (a group may begin at any vector)
+    // a lane's chunk: CW weights from N vectors
+    constexpr int SUB = runs_per_turn(V, BITS, ADD), CW = chunk_weights(V), CD = CW / 2, N = V == 6 ? 1 : V == 12 ? 2 : 8 / V, RB_ = RBITS ? RBITS : 8;
+    constexpr bool ONE = N == 1 && BITS != 12, RONE = N == 1 && RB_ != 12;      // (a group may begin at any vector)
     const unsigned lanes = 1u << a.log_lanes, rows_per_run = 64u >> a.log_lanes, row_lane = (unsigned)lane >> a.log_lanes, chunk_lane = (unsigned)lane & (lanes - 1u);
     const unsigned runs = (((unsigned)p.S + rows_per_run - 1u) >> (6 - a.log_lanes)) * (unsigned)a.segments;
     const unsigned items = (runs + SUB - 1) / SUB;
     const unsigned stride_items = (unsigned)a.wgs * NW;      // (neighbouring waves write neighbouring parts of W)
     const int weights = (int)min((long long)(p_hi - p_lo) * V, (long long)p.in_features - p.n_out - (long long)p_lo * V);      // of a row in this group
-    Run<N, BITS, ONE> idx[SUB], next[SUB];
-    Run<N, RB_, RONE> res[ADD ? SUB : 1], rnext[ADD ? SUB : 1];
-    unsigned short sc[SUB], bi[SUB], scn[SUB], bin[SUB];
-    auto place = [&](unsigned item, int u, unsigned &o, unsigned &c) {      // the lane's row and chunk of sixteen bytes
+    struct Turn { Run<N, BITS, ONE> idx[SUB]; Run<N, RB_, RONE> res[ADD ? SUB : 1]; unsigned short s[SUB], b[SUB]; } even, odd;
+    auto place = [&](unsigned item, int u, unsigned &o, unsigned &c) {      // the lane's row and chunk
       const unsigned run = min(item * SUB + u, runs - 1u), rb = by_segments(run);
       o = rb * rows_per_run + row_lane;
       c = (run - rb * (unsigned)a.segments) * lanes + chunk_lane;
     };
-    auto first_vector = [](unsigned c) -> unsigned { return V == 6 ? third(4u * c) : V == 12 ? third(2u * c) : c * (8 / V); };
-    auto load = [&](auto &i, auto &r, unsigned short (&s)[SUB], unsigned short (&b)[SUB], unsigned item) {
+    auto first_vector = [](unsigned c) -> unsigned { return V == 6 ? c : V == 12 ? third(2u * c) : c * (8 / V); };
+    // Waits go by count, and the compiler counts what every path issues: so the same loads always, also without scale or bias (zeros)
+    // and behind a wave's last item (the same again); and two sets of registers in turn, because a copy would be waited for.
+    const __amdgpu_buffer_rsrc_t r_s = per_output(p.scale), r_b = per_output(p.bias);
+    auto load = [&](Turn &t, unsigned item) {
 #pragma unroll
       for (int u = 0; u < SUB; ++u) {
         unsigned o, c;
         place(item, u, o, c);
         o = min(o, (unsigned)p.S - 1u);
         const unsigned v = (unsigned)p_lo + first_vector(c);
-        i[u].load(r_i, o * (unsigned)p.stride, v);       // (past a row's end: the next row's bits, or zeros; never stored)
-        if constexpr (ADD) r[u].load(r_r, o * (unsigned)p.stride_res, v);
-        s[u] = p.scale ? __half_as_ushort(p.scale[o]) : (unsigned short)0x3C00u;
-        b[u] = p.bias ? __half_as_ushort(p.bias[o]) : (unsigned short)0;
+        t.idx[u].load(r_i, o * (unsigned)p.stride, v);       // (past a row's end: the next row's bits, or zeros; never stored)
+        if constexpr (ADD) t.res[u].load(r_r, o * (unsigned)p.stride_res, v);
+        t.s[u] = load2(r_s, o * 2u);
+        t.b[u] = load2(r_b, o * 2u);
       }
     };
     const unsigned first = (unsigned)wave * (unsigned)a.wave_step + (unsigned)wg * (unsigned)a.wg_step;
-    if (first < items) load(next, rnext, scn, bin, first);
+    if (first < items) load(even, first);
     if constexpr (!MEM) {
       stage_table<V, NW>(lds, cb, p.k);
       if constexpr (RES == RES_LDS) stage_table<V, NW>(lds + a.off_res, cb_res, p.k_res);
@@ -223,16 +247,11 @@ __global__ __launch_bounds__(NW * 64, 4) void dequant_tables_kernel(Params p, Dq
         __syncthreads();
       }
     }
-    // the chunk's four dwords of a table: byte address of entry i, and what of it the chunk holds
-    auto chunk_of = [&](unsigned (&w)[4], const unsigned char *table, auto &run, unsigned last, unsigned c) {
+    // the chunk's dwords of a table
+    auto chunk_of = [&](unsigned (&w)[CD], const unsigned char *table, auto &run, unsigned last, unsigned c) {
       auto get1 = [&](unsigned at) { return *reinterpret_cast<const unsigned *>(table + at); };
       if constexpr (V == 6) {
-        const unsigned off = 4u * c - 3u * third(4u * c), e0 = min(run.template field<0>(), last) * 12u, e1 = min(run.template field<1>(), last) * 12u;
-        const unsigned a0 = e0 + 4u * off;
-        w[0] = get1(a0);
-        w[1] = get1(off < 2u ? a0 + 4u : e1);
-        w[2] = get1(off == 0u ? a0 + 8u : e1 + 4u * off - 4u);
-        w[3] = get1(e1 + 4u * off);
+        read_twelve(w, table + min(run.template field<0>(), last) * 12u);
       } else if constexpr (V == 12) {
         const unsigned part = 2u * c - 3u * third(2u * c), e0 = min(run.template field<0>(), last) * 24u, e1 = min(run.template field<1>(), last) * 24u;
         const uint2v x = *reinterpret_cast<const uint2v *>(table + e0 + 8u * part), y = *reinterpret_cast<const uint2v *>(table + (part < 2u ? e0 + 8u * part + 8u : e1));
@@ -247,39 +266,58 @@ __global__ __launch_bounds__(NW * 64, 4) void dequant_tables_kernel(Params p, Dq
         for_each<4>([&](auto q) { w[decltype(q)::value] = get1(min(run.template field<decltype(q)::value>(), last) * 4u); });
       }
     };
-    for (unsigned item = first; item < items; item += stride_items) {
-#pragma unroll
-      for (int u = 0; u < SUB; ++u) { idx[u] = next[u]; sc[u] = scn[u]; bi[u] = bin[u]; if constexpr (ADD) res[u] = rnext[u]; }
-      if (item + stride_items < items) load(next, rnext, scn, bin, item + stride_items);
+    auto restore_turn = [&](Turn &t, unsigned item) {
 #pragma unroll
       for (int u = 0; u < SUB; ++u) {
         unsigned o, c;
         place(item, u, o, c);
         const unsigned v = (unsigned)p_lo + first_vector(c);
-        const float s = __half2float(__ushort_as_half(sc[u])), b = __half2float(__ushort_as_half(bi[u]));
-        unsigned e[4], f[4], w[4];
-        idx[u].align(v);
-        if constexpr (MEM) chunk_of(e, reinterpret_cast<const unsigned char *>(cb), idx[u], k_max, c);
-        else chunk_of(e, lds, idx[u], k_max, c);
+        const float s = p.scale ? __half2float(__ushort_as_half(t.s[u])) : 1.0f, b = __half2float(__ushort_as_half(t.b[u]));
+        unsigned e[CD], f[CD], w[CD];
+        t.idx[u].align(v);
+        if constexpr (MEM) chunk_of(e, reinterpret_cast<const unsigned char *>(cb), t.idx[u], k_max, c);
+        else chunk_of(e, lds, t.idx[u], k_max, c);
         if constexpr (ADD) {
-          res[u].align(v);
+          t.res[u].align(v);
           if constexpr (RES == RES_SPLIT) {
-            const unsigned part = 2u * c - 3u * third(2u * c), i0 = min(res[u].template field<0>(), kr_max), i1 = min(res[u].template field<1>(), kr_max);
+            const unsigned part = 2u * c - 3u * third(2u * c), i0 = min(t.res[u].template field<0>(), kr_max), i1 = min(t.res[u].template field<1>(), kr_max);
             const uint2v x = split_read(i0, 8u * part), y = split_read(part < 2u ? i0 : i1, part < 2u ? 8u * part + 8u : 0u);
             f[0] = x.x; f[1] = x.y; f[2] = y.x; f[3] = y.y;
-          } else if constexpr (RES == RES_MEM) chunk_of(f, reinterpret_cast<const unsigned char *>(cb_res), res[u], kr_max, c);
-          else chunk_of(f, lds + a.off_res, res[u], kr_max, c);
+          } else if constexpr (RES == RES_MEM) chunk_of(f, reinterpret_cast<const unsigned char *>(cb_res), t.res[u], kr_max, c);
+          else chunk_of(f, lds + a.off_res, t.res[u], kr_max, c);
         }
 #pragma unroll
-        for (int d = 0; d < 4; ++d) w[d] = restore_pair<ADD>(e[d], ADD ? f[d] : 0u, s, b, s, b);
-        const int n = o < (unsigned)p.S && item * SUB + u < runs ? weights - 8 * (int)c : 0;      // weights of the chunk that exist
-        __half *to = a.W + (long long)o * a.ldw + p.n_out + (long long)p_lo * V + 8 * (int)c;
-        if (n >= 8) store16<STREAM>(to, w);
+        for (int d = 0; d < CD; ++d) w[d] = restore_pair<ADD>(e[d], ADD ? f[d] : 0u, s, b, s, b);
+        const int n = o < (unsigned)p.S && item * SUB + u < runs ? weights - CW * (int)c : 0;      // weights of the chunk that exist
+        __half *to = a.W + (long long)o * a.ldw + p.n_out + (long long)p_lo * V + CW * (int)c;
+        if (n >= CW) {
+          if constexpr (CW == 6) store12<STREAM>(to, w);
+          else store16<STREAM>(to, w);
+        }
         else if (n > 0) {
 #pragma unroll
-          for (int j = 0; j < 8; ++j)
+          for (int j = 0; j < CW; ++j)
             if (j < n) to[j] = __ushort_as_half((unsigned short)(w[j >> 1] >> (j & 1) * 16));
         }
+      }
+    };
+    if constexpr (V == 12) {                                 // (whose lookups are the bound: in turn, 3001 x 1501 took 9.4 us instead of 9.0)
+      for (unsigned item = first; item < items; item += stride_items) {
+        odd = even;
+        if (item + stride_items < items) load(even, item + stride_items);
+        restore_turn(odd, item);
+      }
+    } else if (items <= stride_items) {                      // no wave has two
+      if (first < items) restore_turn(even, first);
+    } else {
+      auto after = [&](unsigned item) { return item + stride_items < items ? item + stride_items : item; };
+      for (unsigned item = first; item < items;) {
+        load(odd, after(item));
+        restore_turn(even, item);
+        if ((item += stride_items) >= items) return;
+        load(even, after(item));
+        restore_turn(odd, item);
+        item += stride_items;
       }
     }
   } else {
@@ -404,7 +442,7 @@ template <auto KERNEL, int NW> int launch_kernel(dim3 grid, unsigned lds, hipStr
 
 template <int V, int BITS, int RBITS, int RES, bool DOWN>
 int launch_one(const Params &p, __half *W, long long ldw, hipStream_t s) {
-  constexpr bool STREAMS = BITS == 16 || RES == RES_MEM || RES == RES_SPLIT;      // (a lookup through L2: W must not push the table out of it)
+  constexpr bool L2_LOOKUPS = BITS == 16 || RES == RES_MEM || RES == RES_SPLIT;
   const unsigned main = BITS == 16 ? 0u : table_bytes(V, p.k), bytes = RES == RES_SPLIT ? 160u * 1024u : main + (RES == RES_LDS ? table_bytes(V, p.k_res) : 0u);
   DqArgs a = {W, ldw, main, 0, 0, 1, 0, 6, 1, 0, 0};
   if (RES == RES_SPLIT) a.split = min((bytes - main) / (V * 2u) - 1u, (unsigned)p.k_res);
@@ -413,10 +451,10 @@ int launch_one(const Params &p, __half *W, long long ldw, hipStream_t s) {
     a.segments = ((p.n_groups > 1 && p.Pg % 8 ? p.Pg + 7 : p.Pg) + 511) / 512;
     items = (long long)p.S * a.segments;
   } else {
-    const long long chunks = ((long long)p.Pg * V + 7) / 8;
+    const long long chunks = ((long long)p.Pg * V + chunk_weights(V) - 1) / chunk_weights(V);
     while (a.log_lanes > 3 && chunks <= 1LL << (a.log_lanes - 1)) --a.log_lanes;
     a.segments = (int)((chunks + (1LL << a.log_lanes) - 1) >> a.log_lanes);
-    items = (((long long)p.S + (64 >> a.log_lanes) - 1) / (64 >> a.log_lanes) * a.segments + 1) / 2;
+    items = (((long long)p.S + (64 >> a.log_lanes) - 1) / (64 >> a.log_lanes) * a.segments + runs_per_turn(V, BITS, RES != NO_RES) - 1) / runs_per_turn(V, BITS, RES != NO_RES);
   }
   a.segments_inv = (unsigned)(((1ULL << 32) + a.segments - 1) / a.segments);
   if (items > 0x1fffffffLL || (long long)p.S * a.segments * a.segments >= 1LL << 32) return VQ_ERR_UNSUPPORTED;
@@ -439,10 +477,13 @@ int launch_one(const Params &p, __half *W, long long ldw, hipStream_t s) {
   if (items <= wgs * nw) { a.wave_step = a.wgs; a.wg_step = 1; }      // no wave has two: every workgroup gets its share
   if (p.Q) a.out_wgs = (int)min((long long)(p.S_out + nw - 1) / nw, (long long)cu_count());
   const dim3 grid((unsigned)(wgs * p.n_groups + a.out_wgs));
-  const bool stream = STREAMS && ((reinterpret_cast<uintptr_t>(W) | (uintptr_t)ldw * 2 | (uintptr_t)p.n_out * 2) & 15) == 0;
-  const int rc = small ? (stream ? launch_kernel<dequant_tables_kernel<V, BITS, RBITS, RES, DOWN, 8, STREAMS>, 8>(grid, bytes, s, p, a)
+  // past the caches: where lookups go through L2, from which W must not push the table; and where W is larger than they are
+  // (down the outputs only if rows start on 64 bytes: with pieces of lines between them 8192 x 20480 took 103 us past the caches, 97 through)
+  const uintptr_t starts = reinterpret_cast<uintptr_t>(W) | (uintptr_t)ldw * 2 | (uintptr_t)p.n_out * 2;
+  const bool stream = (L2_LOOKUPS && (starts & 15) == 0) || ((long long)p.out_features * p.in_features * 2 > 256LL << 20 && (!DOWN || (starts & 63) == 0));
+  const int rc = small ? (stream ? launch_kernel<dequant_tables_kernel<V, BITS, RBITS, RES, DOWN, 8, true>, 8>(grid, bytes, s, p, a)
                                  : launch_kernel<dequant_tables_kernel<V, BITS, RBITS, RES, DOWN, 8, false>, 8>(grid, bytes, s, p, a))
-                       : (stream ? launch_kernel<dequant_tables_kernel<V, BITS, RBITS, RES, DOWN, 16, STREAMS>, 16>(grid, bytes, s, p, a)
+                       : (stream ? launch_kernel<dequant_tables_kernel<V, BITS, RBITS, RES, DOWN, 16, true>, 16>(grid, bytes, s, p, a)
                                  : launch_kernel<dequant_tables_kernel<V, BITS, RBITS, RES, DOWN, 16, false>, 16>(grid, bytes, s, p, a));
   if (rc != VQ_OK) return rc;
   return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;

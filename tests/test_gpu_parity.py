@@ -512,6 +512,27 @@ def test_dequant_tables_edges(gpu_lib, out_features, in_features, v, k, more, or
         assert (W[:, in_features:] == 3.0).all() and (got[:offset] == 3.0).all() and (got[offset + out_features * ldw:] == 3.0).all()
 
 
+@pytest.mark.parametrize("out_features,in_features,v,k,more", [
+    (6001, 1159, 6, 4096, {}), (9000, 772, 6, 4096, dict(k_res=256)), (12500, 770, 6, 4096, dict(k_res=4096, group_vectors=64)), (20000, 390, 6, 256, {}),
+    (7000, 1540, 4, 256, {}), (4100, 2050, 8, 65536, {}), (4000, 1540, 12, 4096, dict(k_res=4096)), (10000, 768, 2, 16, {}),
+    (8203, 16390, 6, 4096, dict(n_outlier_cols=8, v_out=4, k_out=4096)), (8203, 16390, 4, 256, {}), (8203, 16416, 6, 256, dict(orientation=1)),
+    (8203, 16390, 4, 256, dict(orientation=1)),
+])
+@pytest.mark.parametrize("scale", [True, False])
+def test_dequant_waves_with_several_turns(gpu_lib, out_features, in_features, v, k, more, scale):
+    """Layers of which a wave restores two runs and more, in turn from two sets of registers, and (the last four: W of more than
+    256 MiB) with stores past the caches; with and without scale and bias."""
+    import torch
+    if not scale and out_features * in_features > 1 << 27:
+        pytest.skip("once is enough for the largest")
+    L = s.make_layer(8300, "turns", out_features, in_features, v, k, **more)
+    if not scale:
+        L.scale = L.bias = None
+    W = gpu_lib.dequant(gpu_lib.DeviceLayer(L), in_features + 2)
+    torch.cuda.synchronize()
+    assert np.array_equal(W.cpu().numpy().view(np.uint16), oracle.dequant(L, in_features + 2).view(np.uint16))
+
+
 @pytest.mark.parametrize("name", ["lds_v12_two_tables", "lds_v12_groups_res_outlier", "down_lds_v12_two_tables", "down_lds_v12_odd_groups"])
 def test_dequant_two_tables_beyond_lds_in_two_passes(gpu_lib, monkeypatch, name):
     """Two tables that do not fit LDS together: by default the residual entries come from memory; dequant=s is the scheme
