@@ -126,9 +126,10 @@ __device__ __forceinline__ void wave_arg_min(float &d, unsigned &i) {
 //
 // Scores carry rounding errors, so the winning block is only trusted when it wins by more than they can be.  With T = |t|, the
 // nearest centroid and whichever centroid has the largest computed score have norms of at most R = T + sqrt(d), d their
-// squared distance; |c|^2 / 2 is kept to 2^-39, or 2^-30 of the largest; the products are exact in binary32 and the sum of one instruction was measured to be within 2^-23 of the
-// sum of its terms' magnitudes (2^-19 is allowed for; operands below the normal range count as 2^-14, which the hardware's
-// alignment of their products needs); the definition's own roundings move d by (v + 2) 2^-24.  Vectors that fail the test
+// squared distance; |c|^2 / 2 is kept to 2^-39, or 2^-30 of the largest; the products are exact in binary32, and an instruction cuts
+// each of its 16 terms and the accumulator where the largest one's binary32 ends: 17 2^-24 of the sum of the terms' magnitudes at most, for two scores
+// 34 2^-24 an instruction (probes/mfma_rounding_probe.hip finds up to 9 2^-24 where all terms lose their last bits to the same side, 6 2^-24
+// with operands like these; operands below the normal range count as 2^-14); the definition's own roundings move d by (v + 2) 2^-24.  Vectors that fail the test
 // -- about 0.3 % with 4096 Gaussian entries --, and all of them when a table has entries that are not finite or huge, are
 // compared with every centroid by the wave together.
 //
@@ -433,7 +434,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void assign_screen_kernel(Vectors fi
         const float T = __builtin_amdgcn_sqrtf(tt) * 1.001f, down = BASE ? ldexpf(1.0f, -e) : 1.0f, q = 0x1p-12f, qt = 0x1p-12f * down;
         const float dist = fmaxf(0.0f, tt - 2.0f * best_s * down) + 0x1p-13f * (tt + c_max * c_max);
         const float R = T + __builtin_amdgcn_sqrtf(dist) * 1.001f;
-        const float eps = 0x1p-20f * ((T + qt) * (R + q) + 0.5f * R * R + 0x1p-26f * (1.0f + down)) + (V + 3) * 0x1p-23f * dist +
+        const float eps = screen_instructions(V, BASE) * 0x1.2p-19f * ((T + qt) * (R + q) + 0.5f * R * R + 0x1p-26f * (1.0f + down)) + (V + 3) * 0x1p-23f * dist +
                           0x1p-28f * h_max + 0x1p-37f + 0x1p-21f * down * R;
         const float gap = (best_s - second) * down;
         sure = sure && gap > eps;                            // (false when anything is not a number)

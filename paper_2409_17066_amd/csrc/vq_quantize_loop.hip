@@ -109,12 +109,13 @@ __device__ __forceinline__ LoopTable loop_table(const float *h_max, const float 
   float m = 0.0f, b = 0.0f;
   for (int w = 0; w < waves; ++w) { m = fmaxf(m, h_max[w]); b += bad[w]; }
   t.f = m > 0.0f ? min(14, max(-14, 15 - __builtin_amdgcn_frexp_expf(m))) : 14;
-  // scores: 2^-19 of |t| |c| + |c|^2 / 2 (operands below 2^-14 counted as that), |c|^2 / 2 to 2^-21 of the largest, t to 2^-20 where its
+  // scores: two instructions whose v + 2 terms and accumulator are each cut at 2^-24 of the sum of the terms' magnitudes, |t| |c| + |c|^2 / 2
+  // (vq_assign.hip), for two scores (operands below 2^-14 counted as that); |c|^2 / 2 to 2^-21 of the largest, t to 2^-20 where its
   // low part runs out of bits; the definition's own roundings: (v + 2) 2^-24 of (|t| + |c|)^2, twice
   const float c = __builtin_amdgcn_sqrtf(2.0f * m) * 1.001f + 0x1p-12f, T = __builtin_amdgcn_sqrtf((float)VP) * 1.001f * 0x1p14f;
-  constexpr float D = (VP + 3) * 0x1p-23f;
-  t.eps0 = 0x1p-19f * T * c + D * 2.0f * T * c + 0x1p-20f * c;
-  t.eps_up = 0x1p-20f * c * c + D * c * c + 0x1p-21f * m + 0x1p-37f;
+  constexpr float D = (VP + 3) * 0x1p-23f, S = (VP + 3) * 0x1p-22f;
+  t.eps0 = S * T * c + D * 2.0f * T * c + 0x1p-20f * c;
+  t.eps_up = 0.5f * S * c * c + D * c * c + 0x1p-21f * m + 0x1p-37f;
   t.eps_down = D * T * T;
   if (b != 0.0f) t.eps0 = __builtin_inff();
   // (the same in every lane: kept in scalar registers)

@@ -153,6 +153,8 @@ SCREEN = {
     "equal_entries": (60, 600, 6, 512, False, "ties"),
     "equal_entries_base": (60, 600, 6, 512, True, "ties"),
     "nearly_equal_entries": (60, 600, 6, 512, False, "close"),
+    "nearly_equal_entries_base_v12": (60, 600, 12, 512, True, "close"),
+    "nearly_equal_entries_over_magnitudes": (60, 600, 12, 512, True, "spread close"),
     "subnormal_values": (40, 600, 6, 256, False, "tiny"),
     "subnormal_values_base": (40, 600, 8, 256, True, "tiny"),
     "values_near_the_top": (40, 600, 6, 256, False, "huge"),
@@ -168,12 +170,12 @@ def test_assign_screening_edges(gpu_lib, name):
     seed = 7300 + list(SCREEN).index(name)
     scale = {"tiny": 2e-6, "huge": 9000.0}.get(values, 0.02)
     W, C, B = (s.normal(seed + 100 * i, n, scale) for i, n in enumerate((rows * cols, k * v, rows * cols)))
-    if values == "spread":
+    if "spread" in values:
         W, C, B = (a * np.exp(2.0 * s.normal(seed + 100 * i + 50, a.size, 1.0)) for i, a in enumerate((W, C, B)))
     W, C = s.to_fp16(W).reshape(rows, cols), s.to_fp16(C).reshape(k, v)
     if values == "ties":
         C[k // 2:] = C[: k - k // 2][::-1]
-    if values == "close":              # the second half differs from the first by one unit in the last place of one element
+    if "close" in values:              # the second half differs from the first by one unit in the last place of one element
         C[k // 2:] = C[: k - k // 2]
         C[k // 2:, 0] = np.nextafter(C[k // 2:, 0], np.float16(1))
     B = s.to_fp16(B).reshape(rows, cols) if with_base else None
