@@ -146,6 +146,7 @@ template <int V, int BITS, int RBITS, int RES, bool DOWN, int NW, bool STREAM>
 __global__ __launch_bounds__(NW * 64, 4) void dequant_tables_kernel(Params p, DqArgs a) {
   constexpr bool MEM = BITS == 16, ADD = RES != NO_RES;
   constexpr int ED = DOWN && V == 6 ? 3 : entry_halfs(V) / 2;
+  static_assert(V != 12 || RES != RES_MEM, "of a table of 12-element vectors two thirds always fit");
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   auto scale_of = [&](int o) { return p.scale ? __half2float(p.scale[o]) : 1.0f; };
@@ -377,10 +378,7 @@ __global__ __launch_bounds__(NW * 64, 4) void dequant_tables_kernel(Params p, Dq
           if constexpr (V == 12) {
             const uint2v m = *reinterpret_cast<const uint2v *>(lds + ei[u] * 24u + d0 * 4u);
             e[u][0] = m.x; e[u][1] = m.y;
-            if constexpr (RES == RES_MEM) {
-              const uint2v r = *reinterpret_cast<const uint2v *>(reinterpret_cast<const unsigned char *>(cb_res) + fi[u] * 24u + d0 * 4u);
-              f[u][0] = r.x; f[u][1] = r.y;
-            } else if constexpr (RES == RES_SPLIT) {
+            if constexpr (RES == RES_SPLIT) {
               const uint2v r = split_read(fi[u], d0 * 4u);
               f[u][0] = r.x; f[u][1] = r.y;
             } else if constexpr (RES == RES_LDS) {

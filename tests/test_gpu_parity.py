@@ -535,12 +535,12 @@ def test_dequant_waves_with_several_turns(gpu_lib, out_features, in_features, v,
 
 @pytest.mark.parametrize("name", ["lds_v12_two_tables", "lds_v12_groups_res_outlier", "down_lds_v12_two_tables", "down_lds_v12_odd_groups"])
 def test_dequant_two_tables_beyond_lds_in_two_passes(gpu_lib, monkeypatch, name):
-    """Two tables that do not fit LDS together: by default the residual entries come from memory; dequant=s is the scheme
-    with two passes and a read-back of the main centroids.  Both bit for bit."""
+    """Two tables that do not fit LDS together: by default the last third of the residual entries comes from memory; dequant=g, the
+    generic kernels, read all tables there.  Both bit for bit."""
     import torch
     L = small_layer(name)
     want = oracle.dequant(L, L.in_features + 6).view(np.uint16)
-    for switch in (None, "dequant=s"):
+    for switch in (None, "dequant=g"):
         if switch:
             monkeypatch.setenv("VQ_SWITCHES", switch)
         W = gpu_lib.dequant(gpu_lib.DeviceLayer(L), L.in_features + 6)
