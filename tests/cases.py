@@ -1,6 +1,16 @@
 """Small layers for GPU parity: every shape spans several kernel tiles and ends in a ragged tail."""
 import vq_synth as s
 
+
+def lent(workspace):
+    """The workspace argument of gemv() and gemm() for a case "none": an empty tensor, because the calls may borrow one of their own
+    where they are given nothing."""
+    if workspace != "none":
+        return workspace
+    import torch
+    return torch.empty(0, dtype=torch.uint8, device="cuda")
+
+
 # name -> make_layer keyword arguments (config id 300+ keeps their seeds apart from the benchmark layers)
 SMALL = {
     "v6_k256": dict(out_features=70, in_features=391, v=6, k=256),

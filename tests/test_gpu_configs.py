@@ -4,6 +4,7 @@ import pytest
 
 import oracle
 import vq_synth as s
+from cases import lent
 
 pytestmark = pytest.mark.gpu
 TOL = 1e-2
@@ -62,13 +63,13 @@ def test_config_dequant_and_gemv(gpu_lib, layers, monkeypatch, cfg, name):
 
 
 @pytest.mark.parametrize("tokens", [512, 1024, 2048])
-@pytest.mark.parametrize("workspace", [None, "fast"])
+@pytest.mark.parametrize("workspace", [None, "none", "fast"])
 def test_config4_prefill_gemm(gpu_lib, layers, tokens, workspace):
     import torch
     _, L = layers(4, "prefill")
     dl = gpu_lib.DeviceLayer(L)
     x = s.make_activations(4, L, tokens)
-    Y = gpu_lib.gemm(dl, torch.from_numpy(x).cuda(), workspace=workspace)
+    Y = gpu_lib.gemm(dl, torch.from_numpy(x).cuda(), workspace=lent(workspace))
     torch.cuda.synchronize()
     if tokens == 512:
         _matmul_ok(Y, oracle.gemm(L, x), "cfg4 T=512 full")
@@ -79,14 +80,14 @@ def test_config4_prefill_gemm(gpu_lib, layers, tokens, workspace):
         _matmul_ok(Y[:, torch.from_numpy(rows.astype(np.int64)).cuda()], ref, "cfg4 T=%d sampled rows" % tokens)
 
 
-@pytest.mark.parametrize("workspace", [None, "fast"])
+@pytest.mark.parametrize("workspace", [None, "none", "fast"])
 def test_config3_small_gemm_with_outliers(gpu_lib, layers, workspace):
     import torch
     _, L = layers(3, "down70b")
     sub = s.make_layer(3, "slice", 256, L.in_features, 6, 4096, 256, 288, 4, 4096)
     dl = gpu_lib.DeviceLayer(sub)
     x = s.make_activations(3, sub, 64, outlier_gain=10.0)
-    Y = gpu_lib.gemm(dl, torch.from_numpy(x).cuda(), workspace=workspace)
+    Y = gpu_lib.gemm(dl, torch.from_numpy(x).cuda(), workspace=lent(workspace))
     torch.cuda.synchronize()
     _matmul_ok(Y, oracle.gemm(sub, x), "cfg3 slice gemm")
 
@@ -114,8 +115,8 @@ def test_headline_shape_with_codebook_groups(gpu_lib, group_vectors):
     for batch in (1, 16):
         x = s.make_activations(1, L, batch)
         ref = oracle.gemv(L, x)
-        for workspace in (None, "fast"):
-            y = gpu_lib.gemv(dl, torch.from_numpy(x).cuda(), workspace=workspace)
+        for workspace in ("none", "fast"):
+            y = gpu_lib.gemv(dl, torch.from_numpy(x).cuda(), workspace=lent(workspace))
             torch.cuda.synchronize()
             _matmul_ok(y, ref, "grouped headline shape, %d vectors a group, batch %d, workspace %s" % (group_vectors, batch, workspace))
 
@@ -130,8 +131,8 @@ def test_headline_shape_in_the_papers_orientation(gpu_lib, extra):
     for batch in (1, 4, 7, 16):
         x = s.make_activations(1, L, batch)
         ref = oracle.gemv(L, x)
-        for workspace in (None, "fast"):
-            y = gpu_lib.gemv(dl, torch.from_numpy(x).cuda(), workspace=workspace)
+        for workspace in ("none", "fast"):
+            y = gpu_lib.gemv(dl, torch.from_numpy(x).cuda(), workspace=lent(workspace))
             torch.cuda.synchronize()
             _matmul_ok(y, ref, "headline shape, orientation 1, batch %d, %s, workspace %s" % (batch, extra, workspace))
 
@@ -147,8 +148,8 @@ def test_config3_with_scattered_outlier_columns(gpu_lib):
     for batch in (1, 8):
         x = s.make_activations(3, L, batch, outlier_gain=c["outlier_gain"])
         ref = oracle.gemv(L, x)
-        for workspace in (None, "fast"):
-            y = gpu_lib.gemv(dl, torch.from_numpy(x).cuda(), workspace=workspace)
+        for workspace in ("none", "fast"):
+            y = gpu_lib.gemv(dl, torch.from_numpy(x).cuda(), workspace=lent(workspace))
             torch.cuda.synchronize()
             _matmul_ok(y, ref, "cfg3 with permuted columns, batch %d, workspace %s" % (batch, workspace))
 
@@ -163,7 +164,7 @@ def test_prefill_without_workspace_on_the_v6_layers(gpu_lib, layers, cfg, name, 
     dl = gpu_lib.DeviceLayer(L)
     assert gpu_lib.vq_gemm_workspace_bytes(dl.desc, tokens) == 0
     x = s.make_activations(cfg, L, tokens, layer_ordinal=ordinal)
-    Y = gpu_lib.gemm(dl, torch.from_numpy(x).cuda())
+    Y = gpu_lib.gemm(dl, torch.from_numpy(x).cuda(), workspace=lent("none"))
     torch.cuda.synchronize()
     rows = np.unique(np.concatenate([np.arange(0, L.out_features, 16), [L.out_features - 1, 127, 128, L.out_features - 128]])).astype(np.int32)
     _matmul_ok(Y[:, torch.from_numpy(rows.astype(np.int64)).cuda()], oracle.gemm(L, x, rows=rows), "cfg%d %s T=%d on the fly" % (cfg, name, tokens))
@@ -183,8 +184,8 @@ def test_the_2_26_bit_setting_at_full_size(gpu_lib, orientation):
     for batch in (1, 5):
         x = s.make_activations(1, L, batch)
         ref = oracle.gemv(L, x)
-        for workspace in (None, "fast"):
-            y = gpu_lib.gemv(dl, torch.from_numpy(x).cuda(), workspace=workspace)
+        for workspace in ("none", "fast"):
+            y = gpu_lib.gemv(dl, torch.from_numpy(x).cuda(), workspace=lent(workspace))
             torch.cuda.synchronize()
             _matmul_ok(y, ref, "2.26-bit setting, orientation %d, batch %d, workspace %s" % (orientation, batch, workspace))
     x = s.make_activations(1, L, 300)
@@ -204,7 +205,7 @@ def test_one_row_of_the_2_26_bit_setting_takes_no_longer_than_two(gpu_lib, out, 
     L = s.make_layer(1, "up", out, inp, 12, 4096, 4096, n_outlier_cols=n_out, v_out=4, k_out=8192, group_vectors=-(-P // 32) * 8)
     dl = gpu_lib.DeviceLayer(L)
     x = torch.from_numpy(s.make_activations(1, L, 2)).cuda()
-    none = torch.empty(0, dtype=torch.uint8, device="cuda")
+    none = lent("none")
 
     def microseconds(batch):
         y = torch.empty((batch, out), dtype=torch.float16, device="cuda")

@@ -4,7 +4,7 @@ import pytest
 
 import oracle
 import vq_synth as s
-from cases import SMALL, MULTI, small_layer, multi_layers
+from cases import SMALL, MULTI, small_layer, multi_layers, lent
 
 pytestmark = pytest.mark.gpu
 
@@ -68,19 +68,19 @@ def test_gemv_small(gpu_lib, monkeypatch, name, batch, kernel):
 
 
 # (the restore-then-multiply route exists for layers whose in_features is a multiple of 256: only those get its cases)
-GEMM_CASES = [(name, ws) for name in SMALL for ws in (None, "fast", "fast, 256 x 256 tiles")
-              if ws is None or SMALL[name]["in_features"] % 256 == 0]
+GEMM_CASES = [(name, ws) for name in SMALL for ws in (None, "none", "fast", "fast, 256 x 256 tiles")
+              if ws in (None, "none") or SMALL[name]["in_features"] % 256 == 0]
 
 
 @pytest.mark.parametrize("name,workspace", GEMM_CASES)
 @pytest.mark.parametrize("tokens", [1, 37, 130, 300])
 def test_gemm_small(gpu_lib, monkeypatch, name, tokens, workspace):
-    """Without a workspace (weights restored on the fly) and with the one that lets vq_gemm restore W once (that
-    route forced: by itself the library keeps small token counts on the on-the-fly kernel where it has one), the dense
-    product by the kernel with producer waves and by the four-wave kernel with 256 x 256 tiles."""
+    """By default, without a workspace (weights restored on the fly) and with the one that lets vq_gemm restore W once (that
+    route forced: by itself the library leaves small token counts to vq_gemv's kernels where those are faster), the dense product in
+    its smallest and its largest tiles."""
     import torch
-    if workspace is not None:
-        monkeypatch.setenv("VQ_SWITCHES", "gemm=w,dense=" + ("1" if "256" in workspace else "0"))      # the dense product's two kernels
+    if workspace not in (None, "none"):
+        monkeypatch.setenv("VQ_SWITCHES", "gemm=w,dense=" + ("1" if "256" in workspace else "0"))      # its smallest and its largest tiles
         workspace = "fast"
     L = small_layer(name)
     dl = gpu_lib.DeviceLayer(L)
@@ -92,7 +92,7 @@ def test_gemm_small(gpu_lib, monkeypatch, name, tokens, workspace):
     X[:, : L.in_features] = torch.from_numpy(x).cuda()
     if ldx > L.in_features:
         X[:, L.in_features:] = float("nan")           # padding of the caller's buffer must never be read into the sum
-    Y = gpu_lib.gemm(dl, X, workspace=workspace)
+    Y = gpu_lib.gemm(dl, X, workspace=lent(workspace))
     torch.cuda.synchronize()
     _check_matmul(Y, oracle.gemm(L, x), "%s tokens %d workspace %s" % (name, tokens, workspace))
 
@@ -128,7 +128,7 @@ def test_gemm_without_workspace(gpu_lib, name, tokens):
     x = s.make_activations(300, L, tokens)
     X = torch.full((tokens, (L.in_features + 7) // 8 * 8), float("nan"), dtype=torch.float16, device="cuda")
     X[:, : L.in_features] = torch.from_numpy(x).cuda()
-    Y = gpu_lib.gemm(gpu_lib.DeviceLayer(L), X, workspace=torch.empty(0, dtype=torch.uint8, device="cuda"))
+    Y = gpu_lib.gemm(gpu_lib.DeviceLayer(L), X, workspace=lent("none"))
     torch.cuda.synchronize()
     _check_matmul(Y, oracle.gemm(L, x), "%s tokens %d" % (name, tokens))
 
@@ -194,7 +194,7 @@ def test_gemm_by_default_rounds_no_weights_that_it_would_not_round_without_a_wor
     def error(workspace):
         Y = gpu_lib.gemm(dl, X, workspace=workspace).double()
         return float((Y - want).norm() / want.norm())
-    by_default, without, restored = error(None), error(torch.empty(0, dtype=torch.uint8, device="cuda")), error("fast")
+    by_default, without, restored = error(None), error(lent("none")), error("fast")
     print("%s: default %.3g, without %.3g, fast %.3g" % (name, by_default, without, restored))
     assert by_default <= 1.1 * without
 
@@ -207,7 +207,7 @@ def test_gemm_by_default_borrows_256_mib_at_most(gpu_lib, out_features, refused)
     dl = gpu_lib.DeviceLayer(L)
     x = s.make_activations(300, L, 64)
     X = torch.from_numpy(x).cuda()
-    Y = gpu_lib.gemm(dl, X, workspace=torch.empty(0, dtype=torch.uint8, device="cuda"))
+    Y = gpu_lib.gemm(dl, X, workspace=lent("none"))
     torch.cuda.synchronize()
     torch.cuda.empty_cache()
     torch.cuda.reset_peak_memory_stats()
@@ -242,7 +242,7 @@ def test_gemv_rows(gpu_lib, monkeypatch, name, orientation, batch, workspace):
     X = torch.full((batch, L.in_features + 4), float("nan"), dtype=torch.float16, device="cuda")
     X[:, : L.in_features] = torch.from_numpy(x).cuda()
     Y = torch.full((batch, L.out_features + 3), 7.0, dtype=torch.float16, device="cuda")
-    gpu_lib.gemv(gpu_lib.DeviceLayer(L), X, out=Y, workspace="fast" if workspace == "fast" else torch.empty(0, dtype=torch.uint8, device="cuda"))
+    gpu_lib.gemv(gpu_lib.DeviceLayer(L), X, out=Y, workspace=lent(workspace))
     torch.cuda.synchronize()
     _check_matmul(Y[:, : L.out_features], oracle.gemv(L, x), "%s orientation %d batch %d workspace %s" % (name, orientation, batch, workspace))
     assert (Y[:, L.out_features:] == 7.0).all()
@@ -265,7 +265,7 @@ def test_gemm_v6_on_the_fly(gpu_lib, monkeypatch, name, tokens):
     X = torch.full((tokens, L.in_features + 8), float("nan"), dtype=torch.float16, device="cuda")
     X[:, : L.in_features] = torch.from_numpy(x).cuda()
     Y = torch.full((tokens, L.out_features + 3), 7.0, dtype=torch.float16, device="cuda")
-    gpu_lib.gemm(dl, X, out=Y)
+    gpu_lib.gemm(dl, X, out=Y, workspace=lent("none"))
     torch.cuda.synchronize()
     _check_matmul(Y[:, : L.out_features], oracle.gemm(L, x), "%s tokens %d on the fly" % (name, tokens))
     assert (Y[:, L.out_features:] == 7.0).all()
@@ -424,8 +424,8 @@ LDS_SLOTS = ["lds_v12_groups_res_outlier", "lds_v12_groups_perm", "lds_v4_k256_g
 @pytest.mark.parametrize("batch", [1, 3, 4, 7, 16])
 def test_gemv_lds_table_slots_with_workspace(gpu_lib, name, batch):
     """The layers of the LDS-table pass kernel with two codebook groups or more when the caller lends a workspace: a group per
-    workgroup (the first group's also take the outlier columns), then the sum over the groups.  Workspace filled with NaN
-    patterns beforehand, guarded behind; too small a workspace is the plain route."""
+    workgroup and the outlier columns in workgroups of their own, from three rows on the kernel for any number of rows in parts, then
+    the sum over the groups.  Workspace filled with NaN patterns beforehand, guarded behind; too small a workspace is the plain route."""
     import torch
     L = small_layer(name)
     dl = gpu_lib.DeviceLayer(L)
@@ -473,7 +473,7 @@ def test_gemv_permuted_columns_with_workspace(gpu_lib, name, batch):
     assert rc == 0
     torch.cuda.synchronize()
     assert torch.equal(y, y2)
-    plain = gpu_lib.gemv(dl, x)                               # no workspace: gathered in the kernel, or the generic kernels
+    plain = gpu_lib.gemv(dl, x, workspace=lent("none"))       # no workspace: gathered in the kernel, or the generic kernels
     torch.cuda.synchronize()
     _check_matmul(plain, ref, "%s batch %d" % (name, batch))
 
@@ -528,9 +528,10 @@ def test_dequant_waves_with_several_turns(gpu_lib, out_features, in_features, v,
     L = s.make_layer(8300, "turns", out_features, in_features, v, k, **more)
     if not scale:
         L.scale = L.bias = None
-    W = gpu_lib.dequant(gpu_lib.DeviceLayer(L), in_features + 2)
+    ldw = in_features + (0 if in_features > 16000 else 2)         # (down the outputs past the caches only with rows on 64 bytes)
+    W = gpu_lib.dequant(gpu_lib.DeviceLayer(L), ldw)
     torch.cuda.synchronize()
-    assert np.array_equal(W.cpu().numpy().view(np.uint16), oracle.dequant(L, in_features + 2).view(np.uint16))
+    assert np.array_equal(W.cpu().numpy().view(np.uint16), oracle.dequant(L, ldw).view(np.uint16))
 
 
 @pytest.mark.parametrize("name", ["lds_v12_two_tables", "lds_v12_groups_res_outlier", "down_lds_v12_two_tables", "down_lds_v12_odd_groups"])
@@ -555,12 +556,12 @@ def test_permuted_unit_activation_reads_back_the_layers_column(gpu_lib):
     dl = gpu_lib.DeviceLayer(L)
     W = oracle.dequant(L).astype(np.float64)
     cols = [int(L.col_perm[0]), int(L.col_perm[23]), int(L.col_perm[24]), int(L.col_perm[1207]), 0, 1207]
-    for ws in (None, "fast"):
+    for ws in ("none", "fast"):
         for t in cols:
             x = np.zeros((2, L.in_features), dtype=np.float16)
             x[0, t] = 1.0
             x[1, t] = -2.0
-            y = gpu_lib.gemv(dl, torch.from_numpy(x).cuda(), workspace=ws).float().cpu().numpy()
+            y = gpu_lib.gemv(dl, torch.from_numpy(x).cuda(), workspace=lent(ws)).float().cpu().numpy()
             assert np.allclose(y[0], W[:, t], rtol=2e-3, atol=1e-7) and np.allclose(y[1], -2.0 * W[:, t], rtol=2e-3, atol=1e-7)
 
 
@@ -581,9 +582,9 @@ def test_permutation_entries_outside_the_row_are_ignored(gpu_lib):
     M.col_perm[bad] = [-1, L.in_features, 2 ** 31 - 1]
     dl = gpu_lib.DeviceLayer(M)
     x = torch.from_numpy(x_np).cuda()
-    for ws in (None, "fast"):
+    for ws in ("none", "fast"):
         for batch in (1, 3):
-            y = gpu_lib.gemv(dl, x[:batch], workspace=ws)
+            y = gpu_lib.gemv(dl, x[:batch], workspace=lent(ws))
             torch.cuda.synchronize()
             _check_matmul(y, ref[:batch], "out-of-range entries, batch %d, workspace %s" % (batch, ws))
     W = torch.full((M.out_features, M.in_features + 8), -3.5, dtype=torch.float16, device="cuda")
@@ -650,7 +651,7 @@ def test_gemv_native_orientation_column_parts_with_workspace(gpu_lib, name, batc
         _check_matmul(y1, oracle.gemv(L, x_np[:1]), "%s one row, workspace %s" % (name, workspace is not None))
 
 
-@pytest.mark.parametrize("workspace", [None, "fast"])
+@pytest.mark.parametrize("workspace", ["none", "fast"])
 @pytest.mark.parametrize("batch", [1, 3, 5, 16])
 @pytest.mark.parametrize("name,pad_x,pad_y", [("down_fast_res12", 8, 1), ("down_fast_outlier", 24, 6), ("down_fast_parts", 16, 3),
                                                ("down_fast_groups_outlier_tall", 8, 5),
@@ -665,7 +666,7 @@ def test_native_orientation_strided_buffers_and_untouched_padding(gpu_lib, name,
     xb = torch.full((batch, L.in_features + pad_x), float("nan"), dtype=torch.float16, device="cuda")
     xb[:, : L.in_features] = torch.from_numpy(x).cuda()
     yb = torch.full((batch, L.out_features + pad_y), 7.0, dtype=torch.float16, device="cuda")
-    gpu_lib.gemv(dl, xb, out=yb, workspace=workspace)
+    gpu_lib.gemv(dl, xb, out=yb, workspace=lent(workspace))
     torch.cuda.synchronize()
     _check_matmul(yb[:, : L.out_features], oracle.gemv(L, x), "strided %s batch %d workspace %s" % (name, batch, workspace))
     assert (yb[:, L.out_features:] == 7.0).all()
@@ -699,10 +700,12 @@ def test_eight_component_layers_random_shapes(gpu_lib, seed):
         xb = torch.full((batch, (in_features + 7) // 8 * 8 + 8), float("nan"), dtype=torch.float16, device="cuda")
         xb[:, :in_features] = torch.from_numpy(x).cuda()
         yb = torch.full((batch, out + 3), 7.0, dtype=torch.float16, device="cuda")
-        gpu_lib.gemv(dl, xb, out=yb)
-        torch.cuda.synchronize()
-        _check_matmul(yb[:, :out], oracle.gemv(L, x), "v = 8, orientation %d, %d x %d, k %d, %s, batch %d" % (orientation, out, in_features, k, kw, batch))
-        assert (yb[:, out:] == 7.0).all()
+        for workspace in ("none", None):
+            yb.fill_(7.0)
+            gpu_lib.gemv(dl, xb, out=yb, workspace=lent(workspace))
+            torch.cuda.synchronize()
+            _check_matmul(yb[:, :out], oracle.gemv(L, x), "v = 8, orientation %d, %d x %d, k %d, %s, batch %d" % (orientation, out, in_features, k, kw, batch))
+            assert (yb[:, out:] == 7.0).all()
 
 
 @pytest.mark.parametrize("seed", range(48))
@@ -746,9 +749,9 @@ def test_lds_table_kernels_random_shapes(gpu_lib, seed):
         xb[:, :in_features] = torch.from_numpy(x).cuda()
         yb = torch.full((batch, out + 3), 7.0, dtype=torch.float16, device="cuda")
         ref = oracle.gemv(L, x)
-        for workspace in (None, "fast"):     # (with a workspace: a codebook group or the outlier columns per workgroup, then a sum)
+        for workspace in ("none", "fast"):   # (with a workspace: a codebook group or the outlier columns per workgroup, then a sum)
             yb.fill_(7.0)
-            gpu_lib.gemv(dl, xb, out=yb, workspace=workspace)
+            gpu_lib.gemv(dl, xb, out=yb, workspace=lent(workspace))
             torch.cuda.synchronize()
             _check_matmul(yb[:, :out], ref, what + ", batch %d, workspace %s" % (batch, workspace))
             assert (yb[:, out:] == 7.0).all()
