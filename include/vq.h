@@ -255,12 +255,18 @@ int vq_gemm(const vq_layer_desc *desc, const void *X, int64_t ldx, int32_t token
             void *Y, int64_t ldy, void *workspace, size_t workspace_bytes, void *hip_stream);
 size_t vq_gemm_workspace_bytes(const vq_layer_desc *desc, int32_t tokens);
 size_t vq_gemm_fast_workspace_bytes(const vq_layer_desc *desc, int32_t tokens);
-/* What a caller that keeps no workspace may allocate for one call without a change in how the weights are held.  Restoring W rounds
- * it to binary16, and so do the kernels that restore on the fly; vq_gemv's kernels keep centroids, scale and bias unrounded.  Where
- * vq_gemm without a workspace takes the latter (layers with v = 6 along the rows that the on-the-fly kernel does not take; up to 128
- * tokens of the other layers with a vq_gemv kernel of their own, up to 32 of those whose tables fit LDS) this is the size that they
- * use, as vq_gemv_workspace_bytes gives it, elsewhere vq_gemm_fast_workspace_bytes; 0 instead of more than 256 MiB.            */
+/* vq_gemm for a caller that keeps no workspace and lends one for this call only, of vq_gemm_default_workspace_bytes: what
+ * that changes is the time, not how the weights are held.  Restoring W rounds it to binary16, and so do the kernels that
+ * restore on the fly; vq_gemv's kernels keep centroids, scale and bias unrounded.  Where vq_gemm without a workspace takes
+ * the latter (layers with v = 6 along the rows that the on-the-fly kernel does not take; up to 128 tokens of the other layers
+ * with a vq_gemv kernel of their own, up to 32 of those whose tables fit LDS) the call restores the centroids alone, which
+ * are binary16 numbers, main and residual ones apart, and applies scale and bias to the sums; or, where that is faster,
+ * runs those kernels with the workspace that they use.  Elsewhere it is vq_gemm with vq_gemm_fast_workspace_bytes.  The size
+ * is 0 instead of more than 256 MiB.  With less (or NULL) it is vq_gemm without a workspace.  Arguments, checks and errors
+ * are those of vq_gemm; a workspace that is aligned to 16 but not 256 bytes may be left unused.                          */
 size_t vq_gemm_default_workspace_bytes(const vq_layer_desc *desc, int32_t tokens);
+int vq_gemm_default(const vq_layer_desc *desc, const void *X, int64_t ldx, int32_t tokens,
+                    void *Y, int64_t ldy, void *workspace, size_t workspace_bytes, void *hip_stream);
 
 /* Text for a status code (static storage).  */
 const char *vq_status_string(int status);

@@ -68,6 +68,7 @@ def load():
     L.vq_assign_down.argtypes = L.vq_assign.argtypes
     L.vq_gemm.argtypes = [P, ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32, ctypes.c_void_p, ctypes.c_int64,
                           ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
+    L.vq_gemm_default.argtypes = L.vq_gemm.argtypes
     L.vq_gemm_workspace_bytes.argtypes = [P, ctypes.c_int32]
     L.vq_gemm_workspace_bytes.restype = ctypes.c_size_t
     L.vq_gemm_fast_workspace_bytes.argtypes = [P, ctypes.c_int32]
@@ -84,14 +85,14 @@ def load():
     L.vq_status_string.argtypes = [ctypes.c_int]
     L.vq_status_string.restype = ctypes.c_char_p
     L.vq_version.restype = ctypes.c_int
-    for f in (L.vq_validate, L.vq_dequant, L.vq_gemv, L.vq_gemv_with_workspace, L.vq_gemv_static_workspace, L.vq_gemv_multi, L.vq_gemm, L.vq_assign, L.vq_assign_down):
+    for f in (L.vq_validate, L.vq_dequant, L.vq_gemv, L.vq_gemv_with_workspace, L.vq_gemv_static_workspace, L.vq_gemv_multi, L.vq_gemm, L.vq_gemm_default, L.vq_assign, L.vq_assign_down):
         f.restype = ctypes.c_int
     _lib = L
     return L
 
 
-EXPORTED = ["vq_validate", "vq_dequant", "vq_gemv", "vq_gemv_workspace_bytes", "vq_gemv_with_workspace", "vq_gemv_static_workspace", "vq_gemv_multi", "vq_gemm", "vq_gemm_workspace_bytes", "vq_gemm_fast_workspace_bytes",
-            "vq_gemm_default_workspace_bytes", "vq_assign", "vq_assign_down", "vq_quantize_columns", "vq_quantize_columns_workspace_bytes", "vq_status_string", "vq_version"]
+EXPORTED = ["vq_validate", "vq_dequant", "vq_gemv", "vq_gemv_workspace_bytes", "vq_gemv_with_workspace", "vq_gemv_static_workspace", "vq_gemv_multi", "vq_gemm", "vq_gemm_default", "vq_gemm_workspace_bytes", "vq_gemm_fast_workspace_bytes",
+            "vq_gemm_default_workspace_bytes", "vq_gemm_default", "vq_assign", "vq_assign_down", "vq_quantize_columns", "vq_quantize_columns_workspace_bytes", "vq_status_string", "vq_version"]
 
 
 # ---- the C entry points, same names, raw pointers (ints) and sizes ---------------------------------------
@@ -135,6 +136,11 @@ def vq_gemv_multi(descs, x_ptr, ldx, batch, y_ptrs, ldys, stream=None):
 
 def vq_gemm(desc, X_ptr, ldx, tokens, Y_ptr, ldy, workspace_ptr=None, workspace_bytes=0, stream=None):
     return load().vq_gemm(ctypes.byref(desc) if desc is not None else None, X_ptr, ldx, tokens, Y_ptr, ldy,
+                          workspace_ptr, workspace_bytes, stream)
+
+
+def vq_gemm_default(desc, X_ptr, ldx, tokens, Y_ptr, ldy, workspace_ptr=None, workspace_bytes=0, stream=None):
+    return load().vq_gemm_default(ctypes.byref(desc) if desc is not None else None, X_ptr, ldx, tokens, Y_ptr, ldy,
                           workspace_ptr, workspace_bytes, stream)
 
 
@@ -188,7 +194,7 @@ def _native():
         L = load()
         from . import _binding as b
         b.bind({name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value
-                for name in ("vq_gemv", "vq_gemv_with_workspace", "vq_gemv_multi", "vq_gemm", "vq_gemm_workspace_bytes",
+                for name in ("vq_gemv", "vq_gemv_with_workspace", "vq_gemv_multi", "vq_gemm", "vq_gemm_default", "vq_gemm_workspace_bytes",
                              "vq_gemm_default_workspace_bytes", "vq_gemv_workspace_bytes", "vq_dequant", "vq_assign", "vq_assign_down")})
         _bound = b
     return _bound
@@ -381,9 +387,9 @@ def quantize_columns(W, Hinv, codebook, codebook_res=None, block=128, want_T=Tru
 def gemm(dl: DeviceLayer, X, out=None, workspace=None):
     """X: fp16 [tokens][>=in] device tensor -> fp16 [tokens][out].  workspace: a uint8 device tensor, or "fast" to
     allocate the one vq_gemm_fast_workspace_bytes asks for (the restore-then-multiply route), or None, which from nine
-    tokens on allocates the one of vq_gemm_default_workspace_bytes (as "fast" where the weights are rounded to binary16 in
-    any case, and 256 MiB at most): torch's allocator hands the memory out and takes it back in stream order.  (An
-    empty tensor leaves the library without one, and so does a full card.)"""
+    tokens on runs vq_gemm_default with what that asks for: no weights are rounded that would not be without a
+    workspace, and 256 MiB are borrowed at most (torch's allocator hands the memory out and takes it back in stream order;
+    a full card is left alone).  An empty tensor leaves the library without one."""
     Y = (_bound or _native()).gemm(dl, X, out, workspace)
     if Y.__class__ is int:
         raise VQError(Y, "vq_gemm")
@@ -392,8 +398,9 @@ def gemm(dl: DeviceLayer, X, out=None, workspace=None):
     import torch
     assert X.is_cuda and X.dtype == torch.float16 and X.dim() == 2 and X.stride(1) == 1
     Y = out if out is not None else torch.empty((X.shape[0], dl.layer.out_features), dtype=torch.float16, device="cuda")
+    call = vq_gemm
     if workspace is None and X.shape[0] > 8:
-        workspace = _borrow(vq_gemm_default_workspace_bytes(dl.desc, X.shape[0]))
+        call, workspace = vq_gemm_default, _borrow(vq_gemm_default_workspace_bytes(dl.desc, X.shape[0]))
     elif isinstance(workspace, str):
         assert workspace == "fast"
         fast = vq_gemm_fast_workspace_bytes(dl.desc, X.shape[0])
@@ -401,9 +408,9 @@ def gemm(dl: DeviceLayer, X, out=None, workspace=None):
     need = vq_gemm_workspace_bytes(dl.desc, X.shape[0])
     if need and (workspace is None or workspace.numel() * workspace.element_size() < need):
         workspace = torch.empty(need, dtype=torch.uint8, device="cuda")
-    rc = vq_gemm(dl.desc, X.data_ptr(), X.stride(0), X.shape[0], Y.data_ptr(), Y.stride(0),
-                 workspace.data_ptr() if workspace is not None else None,
-                 workspace.numel() * workspace.element_size() if workspace is not None else 0, _stream())
+    rc = call(dl.desc, X.data_ptr(), X.stride(0), X.shape[0], Y.data_ptr(), Y.stride(0),
+              workspace.data_ptr() if workspace is not None else None,
+              workspace.numel() * workspace.element_size() if workspace is not None else 0, _stream())
     if rc != VQ_OK:
         raise VQError(rc, "vq_gemm")
     return Y

@@ -19,7 +19,7 @@ decltype(&vq_gemv) p_gemv;
 decltype(&vq_gemv_with_workspace) p_gemv_ws;
 decltype(&vq_gemv_workspace_bytes) p_gemv_workspace_bytes;
 decltype(&vq_gemv_multi) p_gemv_multi;
-decltype(&vq_gemm) p_gemm;
+decltype(&vq_gemm) p_gemm, p_gemm_default;
 decltype(&vq_gemm_workspace_bytes) p_gemm_workspace_bytes, p_gemm_default_workspace_bytes;
 decltype(&vq_dequant) p_dequant;
 decltype(&vq_assign) p_assign, p_assign_down;
@@ -179,15 +179,16 @@ PyObject *gemm(PyObject *, PyObject *const *args, Py_ssize_t n) {
   void *wp = nullptr;
   size_t bytes = 0;
   at::TensorBase scratch;
+  auto call = p_gemm;
   const int32_t tokens = (int32_t)x->size(0);
   if (args[3] != Py_None) {
     if (!THPVariable_Check(args[3])) Py_RETURN_NONE;
     const at::Tensor &ws = THPVariable_Unpack(args[3]);
     wp = ws.data_ptr();
     bytes = (size_t)ws.numel() * ws.element_size();
-  } else if (tokens > 8 && (bytes = p_gemm_default_workspace_bytes(d, tokens)) != 0) {
-    wp = borrow(scratch, bytes);
-    if (!wp) bytes = 0;
+  } else if (tokens > 8) {
+    call = p_gemm_default;
+    if ((bytes = p_gemm_default_workspace_bytes(d, tokens)) != 0 && !(wp = borrow(scratch, bytes))) bytes = 0;
   }
   if (p_gemm_workspace_bytes(d, tokens) > bytes) Py_RETURN_NONE;
   at::TensorBase fresh;
@@ -202,7 +203,7 @@ PyObject *gemm(PyObject *, PyObject *const *args, Py_ssize_t n) {
   const void *xp = x->data_ptr();
   void *yp = y->data_ptr(), *s = stream();
   const int64_t ldx = x->stride(0), ldy = y->stride(0);
-  const int rc = released([&] { return p_gemm(d, xp, ldx, tokens, yp, ldy, wp, bytes, s); });
+  const int rc = released([&] { return call(d, xp, ldx, tokens, yp, ldy, wp, bytes, s); });
   return tensor_or_status(rc, std::move(fresh), args[2]);
   VQ_CATCH
 }
@@ -264,7 +265,7 @@ PyObject *bind(PyObject *, PyObject *addresses) {
     f = reinterpret_cast<std::remove_reference_t<decltype(f)>>(PyLong_AsVoidPtr(a));
     return f != nullptr;
   };
-  if (!at("vq_gemv", p_gemv) || !at("vq_gemv_with_workspace", p_gemv_ws) || !at("vq_gemv_multi", p_gemv_multi) || !at("vq_gemm", p_gemm) ||
+  if (!at("vq_gemv", p_gemv) || !at("vq_gemv_with_workspace", p_gemv_ws) || !at("vq_gemv_multi", p_gemv_multi) || !at("vq_gemm", p_gemm) || !at("vq_gemm_default", p_gemm_default) ||
       !at("vq_gemm_workspace_bytes", p_gemm_workspace_bytes) || !at("vq_gemv_workspace_bytes", p_gemv_workspace_bytes) || !at("vq_gemm_default_workspace_bytes", p_gemm_default_workspace_bytes) ||
        !at("vq_dequant", p_dequant) || !at("vq_assign", p_assign) || !at("vq_assign_down", p_assign_down)) {
     if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "an entry point is missing");

@@ -257,20 +257,35 @@ extern "C" size_t vq_gemm_default_workspace_bytes(const vq_layer_desc *desc, int
   return vq::gemm_default_workspace_bytes(p, tokens);
 }
 
-extern "C" int vq_gemm(const vq_layer_desc *desc, const void *X, int64_t ldx, int32_t tokens,
-                       void *Y, int64_t ldy, void *workspace, size_t workspace_bytes, void *hip_stream) {
-  vq::read_switches();
-  vq::Params p;
-  int rc = vq::make_params(desc, &p);
+namespace vq {
+namespace {
+// vq_gemm and vq_gemm_default: the same arguments, checks and errors
+template <typename Launch>
+int checked_gemm(const vq_layer_desc *desc, const void *X, int64_t ldx, int32_t tokens, void *Y, int64_t ldy, void *workspace, size_t workspace_bytes,
+                 void *hip_stream, Launch launch) {
+  read_switches();
+  Params p;
+  int rc = make_params(desc, &p);
   if (rc != VQ_OK) return rc;
   if (!X || !Y) return VQ_ERR_NULL;
   if (tokens < 1 || tokens > (1 << 24) || ldx < p.in_features || ldy < p.out_features) return VQ_ERR_SHAPE;
   if (!aligned(X, 16) || (ldx & 7) || !aligned(Y, 2)) return VQ_ERR_ALIGNMENT;
-  const size_t need = vq::gemm_workspace_bytes(p, tokens);
+  const size_t need = gemm_workspace_bytes(p, tokens);
   if (need && (!workspace || workspace_bytes < need)) return VQ_ERR_WORKSPACE;
   if (workspace && workspace_bytes && !aligned(workspace, 16)) return VQ_ERR_ALIGNMENT;
-  return vq::launch_gemm(p, static_cast<const __half *>(X), ldx, tokens, static_cast<__half *>(Y), ldy,
-                         workspace, workspace_bytes, static_cast<hipStream_t>(hip_stream));
+  return launch(p, static_cast<const __half *>(X), ldx, tokens, static_cast<__half *>(Y), ldy, workspace, workspace_bytes, static_cast<hipStream_t>(hip_stream));
+}
+}  // namespace
+}  // namespace vq
+
+extern "C" int vq_gemm(const vq_layer_desc *desc, const void *X, int64_t ldx, int32_t tokens,
+                       void *Y, int64_t ldy, void *workspace, size_t workspace_bytes, void *hip_stream) {
+  return vq::checked_gemm(desc, X, ldx, tokens, Y, ldy, workspace, workspace_bytes, hip_stream, vq::launch_gemm);
+}
+
+extern "C" int vq_gemm_default(const vq_layer_desc *desc, const void *X, int64_t ldx, int32_t tokens,
+                               void *Y, int64_t ldy, void *workspace, size_t workspace_bytes, void *hip_stream) {
+  return vq::checked_gemm(desc, X, ldx, tokens, Y, ldy, workspace, workspace_bytes, hip_stream, vq::launch_gemm_default);
 }
 
 extern "C" int vq_assign(const void *W, const void *B, int64_t ld, int32_t rows, int32_t cols, const void *codebook, int32_t v, int32_t k,

@@ -42,8 +42,9 @@ int cu_count();
 //   rows=0|1     the matrix-core kernel for layers looked up entry by entry: never / wherever it can
 //   groups=loop  layers with codebook groups: every workgroup walks all groups even when a workspace is there
 //   multi=0      vq_gemv_multi as one vq_gemv after the other
-//   gemm=g|f|w|r|6 vq_gemm: generic tile kernel / no restore-then-multiply / restore-then-multiply whenever a workspace is
-//                there / rows through vq_gemv / the on-the-fly kernel for v = 6 layers at every token count
+//   gemm=g|f|w|r|6|c vq_gemm: generic tile kernel / no restore-then-multiply / restore-then-multiply whenever a workspace is
+//                there / rows through vq_gemv / the on-the-fly kernel for v = 6 layers at every token count / vq_gemm_default: centroids restored
+//                and multiplied wherever that can be done
 //   dense=0|1    the dense product of the restore-then-multiply route: always the smallest / the largest tiles
 //   dequant=g    vq_dequant: generic kernels
 struct Switches {
@@ -86,6 +87,8 @@ int launch_quantize_columns(float *W, long long ldw, int rows, int cols, const f
 size_t gemm_workspace_bytes(const Params &p, int tokens);
 size_t gemm_fast_workspace_bytes(const Params &p, int tokens);
 size_t gemm_default_workspace_bytes(const Params &p, int tokens);
+int launch_gemm_default(const Params &p, const __half *X, long long ldx, int tokens, __half *Y, long long ldy, void *workspace, size_t workspace_bytes,
+                        hipStream_t s);
 
 #ifdef __HIPCC__
 // Index p of a row's little-endian bitstream (bits <= 16).  `row` is 4-byte aligned and the row's

@@ -183,7 +183,7 @@ bool gemm_v6_applicable(const Params &p);
 int launch_gemm_v6(const Params &p, const __half *X, long long ldx, int tokens, __half *Y, long long ldy, hipStream_t s);
 int launch_gemm_fused(const Params &p, const __half *X, long long ldx, int tokens, __half *Y, long long ldy, hipStream_t s);
 int launch_gemm_dense(const Params &p, const __half *X, long long ldx, int tokens, __half *Y, long long ldy, const __half *Wd,
-                      long long ldw, hipStream_t s);
+                      long long ldw, hipStream_t s, const float *xsum = nullptr, unsigned w2 = 0);
 
 // Row-wise v = 6 layers have the matrix-core GEMV, whose sixteen rows cost little more than one: it still beats restoring the
 // matrix for the first sixteens of tokens.  Estimates in microseconds from 130 random layers: a launch of it 5 + 1.2 per thousand
@@ -207,14 +207,110 @@ static bool rows_hold_the_weights(const Params &p, int tokens) {
   return tokens <= 32 && gemv_has_lds_kernel(p, nullptr, ldx);
 }
 
-// What a caller without a workspace of its own does well to allocate: room for W where it would be rounded in any case, else what
-// vq_gemv's kernels use; nothing beyond 256 MiB (W of 11008 x 11008), so that who leaves the workspace out to save memory still does
+// ---- the prompt-phase scheme with unrounded weights -------------------------------------------------------------------
+// Centroids are binary16 numbers: restored without scale and bias they are exact, and y = scale * (C x + C_res x) + bias * sum(x) is what
+// vq_gemv's kernels compute, with the dense product's rate.  The residual centroids are a second matrix, so that their sum with the main
+// ones is never rounded.  11008 x 4096, v = 6 in four groups, 509 tokens: 489 us sixteen rows at a time, 89 us like this (restored
+// and rounded: 85); vectors down the outputs, 128 tokens 146 -> 51 (43); 4096 x 4096 with a residual table and outlier columns, 509
+// tokens 354 -> 71 (38).  Relative error against unrounded weights 2.1e-4, as vq_gemv's kernels; rounded 2.9e-4.
+// sums[t] of X's rows (the first workgroups, a wave to a row), and zeros in the first `clear` columns of the matrix R (the others).
+__global__ __launch_bounds__(256) void row_sums_kernel(const __half *__restrict__ X, long long ldx, int tokens, int columns, float *__restrict__ sums,
+                                                       __half *__restrict__ R, long long ldr, int rows, int clear) {
+  const int sum_wgs = (tokens + 3) / 4;
+  if ((int)blockIdx.x >= sum_wgs) {
+    for (int r = blockIdx.x - sum_wgs; r < rows; r += gridDim.x - sum_wgs)
+      for (int c = threadIdx.x; c < clear; c += 256) R[(long long)r * ldr + c] = __float2half_rn(0.0f);
+    return;
+  }
+  const int lane = threadIdx.x & 63, t = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (t >= tokens) return;
+  const __half *row = X + (long long)t * ldx;
+  float sum = 0.0f;
+  for (int c = lane * 8; c < columns; c += 512) {            // (rows start on sixteen bytes; columns in multiples of eight)
+    const half8 x = *reinterpret_cast<const half8 *>(row + c);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sum += (float)x[i];
+  }
+  sum = wave_sum(sum);
+  if (lane == 0) sums[t] = sum;
+}
+
+static size_t matrix_bytes(const Params &p) { return ((size_t)p.out_features * (size_t)p.in_features * sizeof(__half) + 255) / 256 * 256; }
+static size_t centroids_workspace_bytes(const Params &p, int tokens) {
+  return matrix_bytes(p) * (p.k_res ? 2 : 1) + ((size_t)tokens * sizeof(float) + 255) / 256 * 256;
+}
+
+// Where this beats vq_gemv's kernels, sixteen rows at a time.  Estimates in microseconds: a launch of the row-wise v = 6 kernel 4 + 0.8 per
+// thousand columns and 0.07 per million weights, twice that and 1.5 with a residual table, 5 more with codebook groups (512 x 8200: 10.5;
+// 3000 x 2056: 6.4; 11008 x 4096: 10.5, four groups 15.5); of the others, above all those down the outputs, 5 and 0.32 per million
+// weights, 0.5 with a residual table (11008 x 4096: 19.6 and 28.8).
+static bool centroids_beat_rows(const Params &p, int tokens) {
+  const float weights = (float)((double)p.out_features * p.in_features * 1e-6), matrices = p.k_res ? 2.0f : 1.0f;
+  const float v6 = 4.0f + 0.8e-3f * (float)p.in_features + (p.k_res ? 1.5f + 0.14f * weights : 0.07f * weights) + (p.n_groups > 1 ? 5.0f : 0.0f);
+  const float launch = p.orientation == 0 && p.v == 6 ? v6 : 5.0f + (p.k_res ? 0.5f : 0.32f) * weights;
+  const float restore = matrices * (6.0f + 0.33f * weights) + (p.n_out ? 5.0f : 0.0f) + 4.0f;
+  return restore + matrices * gemm_dense_us(p, tokens) < (float)((tokens + 15) / 16) * launch;
+}
+
+constexpr size_t MOST_DEFAULT_WORKSPACE = (size_t)256 << 20;
+
+static bool centroids_wanted(const Params &p, int tokens) {
+  // (vq_dequant's kernel for few vectors of eight down the outputs takes no outlier columns, so it may not see such a layer without them)
+  if (!gemm_dense_applicable(p) || p.perm || (p.k_res && p.bits_res == 16) || centroids_workspace_bytes(p, tokens) > MOST_DEFAULT_WORKSPACE) return false;
+  if (switches().gemm != '\0') return switches().gemm == 'c';
+  return rows_hold_the_weights(p, tokens) && centroids_beat_rows(p, tokens);
+}
+
+static int launch_gemm_centroids(const Params &p, const __half *X, long long ldx, int tokens, __half *Y, long long ldy, void *workspace, hipStream_t s) {
+  __half *C = static_cast<__half *>(workspace), *R = C + matrix_bytes(p) / sizeof(__half);
+  float *xsum = reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + matrix_bytes(p) * (p.k_res ? 2 : 1));
+  // (the residual matrix has no outlier columns of its own)
+  const int clear = p.k_res ? p.n_out : 0, clear_wgs = !clear ? 0 : p.out_features < 4096 ? p.out_features : 4096;
+  hipLaunchKernelGGL(row_sums_kernel, dim3((unsigned)((tokens + 3) / 4 + clear_wgs)), dim3(256), 0, s, X, ldx, tokens, p.in_features, xsum, R,
+                     (long long)p.in_features, p.out_features, clear);
+  Params q = p;
+  q.scale = q.bias = nullptr;
+  q.cb_res = nullptr; q.idx_res = nullptr; q.k_res = 0; q.stride_res = 0;
+  int rc = launch_dequant(q, C, p.in_features, s);
+  if (rc == VQ_OK && p.k_res) {
+    // the residual table as a layer of its own, with room for outlier columns but none
+    q.cb = p.cb_res; q.k = p.k_res; q.idx = p.idx_res; q.bits = p.bits_res; q.stride = p.stride_res;
+    q.cb_out = nullptr; q.idx_out = nullptr; q.Q = q.S_out = 0;
+    rc = launch_dequant(q, R, p.in_features, s);
+  }
+  return rc == VQ_OK ? launch_gemm_dense(p, X, ldx, tokens, Y, ldy, C, p.in_features, s, xsum, p.k_res ? (unsigned)matrix_bytes(p) : 0u) : rc;
+}
+
+// Rows of X through vq_gemv, sixteen at a time, with the workspace if it is aligned for that (vq_gemv cuts the columns into parts with it).
+static int launch_gemm_rows(const Params &p, const __half *X, long long ldx, int tokens, __half *Y, long long ldy, void *workspace,
+                            size_t workspace_bytes, hipStream_t s) {
+  const bool lend = workspace && (reinterpret_cast<uintptr_t>(workspace) & 255) == 0;
+  for (int t0 = 0; t0 < tokens; t0 += 16) {
+    const int rc = launch_gemv_ws(p, X + (long long)t0 * ldx, ldx, tokens - t0 < 16 ? tokens - t0 : 16, Y + (long long)t0 * ldy, ldy,
+                                  lend ? workspace : nullptr, lend ? workspace_bytes : 0, s);
+    if (rc != VQ_OK) return rc;
+  }
+  return VQ_OK;
+}
+
+// What vq_gemm_default uses: room for W where it would be rounded in any case, else for the centroids, or what vq_gemv's kernels take;
+// nothing beyond 256 MiB (W of 11008 x 11008), so that who leaves the workspace out to save memory still does
 // where it counts (8192 x 28672, 448 MiB, 512 tokens: 532 us with it, 582 without).
 size_t gemm_default_workspace_bytes(const Params &p, int tokens) {
-  const size_t most = (size_t)256 << 20;
+  if (centroids_wanted(p, tokens)) return centroids_workspace_bytes(p, tokens);
   const size_t bytes = rows_hold_the_weights(p, tokens) ? gemv_workspace_bytes(p, nullptr, (p.in_features + 7) & ~7, tokens < 16 ? tokens : 16)
                                                         : gemm_fast_workspace_bytes(p, tokens);
-  return bytes <= most ? bytes : 0;
+  return bytes <= MOST_DEFAULT_WORKSPACE ? bytes : 0;
+}
+
+int launch_gemm_default(const Params &p, const __half *X, long long ldx, int tokens, __half *Y, long long ldy, void *workspace,
+                        size_t workspace_bytes, hipStream_t s) {
+  if (workspace && (reinterpret_cast<uintptr_t>(workspace) & 255) == 0 && centroids_wanted(p, tokens) && workspace_bytes >= centroids_workspace_bytes(p, tokens)) {
+    const int rc = launch_gemm_centroids(p, X, ldx, tokens, Y, ldy, workspace, s);
+    if (rc != VQ_ERR_UNSUPPORTED) return rc;
+  }
+  if (rows_hold_the_weights(p, tokens) && switches().gemm == '\0') return launch_gemm_rows(p, X, ldx, tokens, Y, ldy, workspace, workspace_bytes, s);
+  return launch_gemm(p, X, ldx, tokens, Y, ldy, workspace, workspace_bytes, s);
 }
 
 // Routes, in this order:
@@ -236,7 +332,7 @@ size_t gemm_default_workspace_bytes(const Params &p, int tokens) {
 //     (461 x 8448, 7 tokens: 25 against 146 us).
 //  5. the generic tile kernel.
 // Switch gemm=g forces 5, =f skips 1, =w takes 1 whenever a workspace is there, =6 takes 3 for every token count, =r takes
-// vq_gemv's kernels (measurement and tests).
+// vq_gemv's kernels, =c, for vq_gemm_default, the centroids' route wherever it can (measurement and tests).
 int launch_gemm(const Params &p, const __half *X, long long ldx, int tokens, __half *Y, long long ldy,
                 void *workspace, size_t workspace_bytes, hipStream_t s) {
   if (p.perm && tokens <= 65535 && workspace && workspace_bytes >= permuted_x_bytes(p, tokens) && (reinterpret_cast<uintptr_t>(workspace) & 15) == 0 &&
@@ -273,15 +369,7 @@ int launch_gemm(const Params &p, const __half *X, long long ldx, int tokens, __h
     else if (have_ws || gemm_fused_applicable(p)) rows = tokens <= (have_ws ? 8 : 16) && (fast_rows || lds_rows);
     else rows = (tokens <= 128 && fast_rows) || (tokens <= 32 && !gemm_v6_applicable(p) && lds_rows);
   }
-  if (rows) {
-    const bool lend = workspace && (reinterpret_cast<uintptr_t>(workspace) & 255) == 0;      // (vq_gemv cuts the columns into parts with it)
-    for (int t0 = 0; t0 < tokens; t0 += 16) {
-      const int rc = launch_gemv_ws(p, X + (long long)t0 * ldx, ldx, tokens - t0 < 16 ? tokens - t0 : 16, Y + (long long)t0 * ldy, ldy,
-                                    lend ? workspace : nullptr, lend ? workspace_bytes : 0, s);
-      if (rc != VQ_OK) return rc;
-    }
-    return VQ_OK;
-  }
+  if (rows) return launch_gemm_rows(p, X, ldx, tokens, Y, ldy, have_ws ? workspace : nullptr, have_ws ? workspace_bytes : 0, s);
   if (forced != 'g' && forced != 'f' && have_ws) {
     __half *Wd = static_cast<__half *>(workspace);
     int rc = launch_dequant(p, Wd, p.in_features, s);

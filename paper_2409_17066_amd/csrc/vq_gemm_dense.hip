@@ -31,6 +31,10 @@ struct DenseArgs {
   const __half *W; long long ldw; int out_features, in_features;
   __half *Y; long long ldy;
   int gx, gy;                  // tiles along the channels and the tokens
+  // CENTROIDS: W holds centroids, the residual ones in a second matrix w2 bytes behind (0: none), and y = scale * (W X) + bias * sum(X)
+  unsigned w2;
+  const __half *scale, *bias;
+  const float *xsum;
 };
 
 constexpr int DBK = 64;                                                  // columns per step: 128-byte rows in LDS
@@ -57,7 +61,7 @@ template <int N, class F> __device__ __forceinline__ void static_for(F &&f) { st
 
 __device__ __forceinline__ void keep_in_agprs(float4v &v) { asm volatile("" : "+a"(v)); }
 
-template <int MB, int NB, int NST>
+template <int MB, int NB, int NST, bool CENTROIDS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(dense_workgroups<MB, NB, NST>(), dense_workgroups<MB, NB, NST>())))
 void gemm_dense_kernel(DenseArgs a) {
   constexpr int TM = 64 * MB, TN = 64 * NB, PX = 2 * MB, PER = 2 * (MB + NB);      // copies of a wave and step: PX of the X tile, PER in all
@@ -71,12 +75,12 @@ void gemm_dense_kernel(DenseArgs a) {
   const int tiles = a.gx * a.gy, run = (tiles + 7) / 8, tile = (int)(blockIdx.x & 7) * run + (int)(blockIdx.x >> 3);
   if (tile >= tiles) return;
   const int n0 = tile / a.gy * TN, m0 = tile % a.gy * TM;
-  const int ksteps = (a.in_features + DBK - 1) / DBK;
+  const int wsteps = (a.in_features + DBK - 1) / DBK, ksteps = CENTROIDS && a.w2 ? 2 * wsteps : wsteps;
   // range-checked against the end of the last row: rows past the matrix read zeros
   const __amdgpu_buffer_rsrc_t r_x = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<__half *>(a.X), 0, (unsigned)(((long long)(a.tokens - 1) * a.ldx + a.in_features) * 2), 0x00020000);
   const __amdgpu_buffer_rsrc_t r_w = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<__half *>(a.W), 0, (unsigned)(((long long)(a.out_features - 1) * a.ldw + a.in_features) * 2), 0x00020000);
+      const_cast<__half *>(a.W), 0, (unsigned)(((long long)(a.out_features - 1) * a.ldw + a.in_features) * 2) + (CENTROIDS ? a.w2 : 0u), 0x00020000);
 
   // A step's copies, 8 rows x 128 bytes each: byte offsets of the lane's 16-byte chunk at step 0.  LDS slot (r, cs) holds chunk
   // cs ^ (r / 2 mod 8): then the 16-byte chunks that a group of 16 lanes reads from consecutive rows fall into all 64 banks.
@@ -91,9 +95,15 @@ void gemm_dense_kernel(DenseArgs a) {
   // byte offset of a step's columns; chunks past the last column, and the steps past the last one, go past the end of the
   // buffers (which end below 2 GiB: see the launcher), where copies read zeros and fetch nothing
   const int steps_even = (a.in_features - (int)even * 8 + DBK - 1) / DBK, steps_odd = (a.in_features - (int)(even ^ 4u) * 8 + DBK - 1) / DBK;
-  auto copy_piece = [&](int i, unsigned stage, unsigned step_even, unsigned step_odd) {
+  auto copy_piece = [&](int i, unsigned stage, unsigned step_even, unsigned step_odd, unsigned second) {
     unsigned char *to = smem + stage + (i < PX ? (unsigned)(wave * PX + i) * 1024u : XTILE + (unsigned)(wave * (PER - PX) + i - PX) * 1024u);
-    copy16(i < PX ? r_x : r_w, to, from[i] + (i & 1 ? step_odd : step_even));
+    copy16(i < PX ? r_x : r_w, to, from[i] + (i & 1 ? step_odd : step_even) + (CENTROIDS && i >= PX ? second : 0u));
+  };
+  // (the second matrix follows step by step, against the same columns of X; rows past the first read the second's: channels never stored)
+  auto second_of = [&](int &kt) -> unsigned {
+    if (!CENTROIDS || kt < wsteps) return 0u;
+    kt = kt < ksteps ? kt - wsteps : 0x7fffff00;
+    return a.w2;
   };
   // operand addresses: row (block base + lane & 15), whose swizzle depends on the lane only, chunk 4 h + (lane >> 4) of half h
   const unsigned lds0 = (unsigned)reinterpret_cast<size_t>((const __attribute__((address_space(3))) void *)smem);
@@ -117,11 +127,12 @@ void gemm_dense_kernel(DenseArgs a) {
   // between them: a wave that has its SIMD to itself issues nothing else meanwhile, and a block of products keeps the matrix
   // core busy for 16 clocks, in which it can issue three instructions.
   auto half_step = [&](auto copies, const half8 (&af)[AB], const half8 (&bf)[BB], unsigned at, half8 (&an)[AB], half8 (&bn)[BB],
-                       unsigned stage, int kt) {
+                       unsigned stage, int kt) {        // (kt: the step that is copied)
     constexpr bool COPY = decltype(copies)::value;
     constexpr int N = AB * BB, R = AB + BB;
     unsigned xa = at + x_base, wa = at + w_base;
     asm volatile("" : "+v"(xa), "+v"(wa));      // both addresses in registers of their own before the first read goes out
+    const unsigned second = COPY ? second_of(kt) : 0u;
     const unsigned step_even = COPY ? (kt < steps_even ? (unsigned)kt * ROW : 0x80000000u) : 0u;
     const unsigned step_odd = COPY ? (kt < steps_odd ? (unsigned)kt * ROW : 0x80000000u) : 0u;
     static_for<N>([&](auto index) {
@@ -137,7 +148,7 @@ void gemm_dense_kernel(DenseArgs a) {
       if constexpr (COPY) {
         static_for<PER>([&](auto piece) {
           constexpr int r = decltype(piece)::value;
-          if constexpr (r * N / (PER * 2) == n) copy_piece(r, stage, step_even, step_odd);
+          if constexpr (r * N / (PER * 2) == n) copy_piece(r, stage, step_even, step_odd, second);
         });
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -148,8 +159,10 @@ void gemm_dense_kernel(DenseArgs a) {
   // own by count (PER per step), the barrier covers the others'.
   static_for<NST>([&](auto index) {
     constexpr int j = decltype(index)::value;
-    const unsigned step_even = j < steps_even ? j * ROW : 0x80000000u, step_odd = j < steps_odd ? j * ROW : 0x80000000u;
-    static_for<PER>([&](auto piece) { copy_piece(decltype(piece)::value, j * STAGE, step_even, step_odd); });
+    int kt = j;
+    const unsigned second = second_of(kt);
+    const unsigned step_even = kt < steps_even ? (unsigned)kt * ROW : 0x80000000u, step_odd = kt < steps_odd ? (unsigned)kt * ROW : 0x80000000u;
+    static_for<PER>([&](auto piece) { copy_piece(decltype(piece)::value, j * STAGE, step_even, step_odd, second); });
   });
   wait_vmem_at_most<(NST - 1) * PER>();
   step_barrier();
@@ -192,10 +205,18 @@ void gemm_dense_kernel(DenseArgs a) {
   for (int i = 0; i < AB; ++i) {
 #pragma unroll
     for (int c = 0; c < BB; ++c) {
-      const bool o_on = n0 + wn + c * 16 + (lane & 15) < a.out_features;
+      const int o = n0 + wn + c * 16 + (lane & 15);
+      const bool o_on = o < a.out_features;
+      float scale = 1.0f, bias = 0.0f;
+      if constexpr (CENTROIDS) {
+        if (o_on && a.scale) scale = __half2float(a.scale[o]);
+        if (o_on && a.bias) bias = __half2float(a.bias[o]);
+      }
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const __half h = __float2half_rn(acc[i][c][r]);
+        float sum = acc[i][c][r];
+        if constexpr (CENTROIDS) sum = __fmaf_rn(scale, sum, bias * a.xsum[min(m0 + wm + i * 16 + 4 * (lane >> 4) + r, a.tokens - 1)]);
+        const __half h = __float2half_rn(sum);
         __builtin_amdgcn_raw_buffer_store_b16((short)__half_as_ushort(h), r_y, o_on ? y_lane + (unsigned)(i * 16 + r) * ldy2 + (unsigned)(c * 32) : 0xFFFFFFF0u, 0, 0);
       }
     }
@@ -203,9 +224,10 @@ void gemm_dense_kernel(DenseArgs a) {
   }
 }
 
-template <int MB, int NB, int NST>
+template <int MB, int NB, int NST, bool CENTROIDS>
 int launch_tiles(DenseArgs a, hipStream_t s) {
-  auto kernel = gemm_dense_kernel<MB, NB, NST>;
+  if constexpr (!CENTROIDS) if (a.xsum) return launch_tiles<MB, NB, NST, true>(a, s);
+  auto kernel = gemm_dense_kernel<MB, NB, NST, CENTROIDS>;
   VQ_ALLOW_FULL_LDS(kernel);
   a.gx = (a.out_features + 64 * NB - 1) / (64 * NB);
   a.gy = (a.tokens + 64 * MB - 1) / (64 * MB);
@@ -225,9 +247,9 @@ struct TileKind {
   int (*launch)(DenseArgs, hipStream_t);
 };
 const TileKind kTiles[] = {
-    {4, 4, 1, 9.9f, {1.12f, 0.0f}, launch_tiles<4, 4, 2>},  {4, 3, 1, 7.6f, {0.90f, 0.0f}, launch_tiles<4, 3, 2>},
-    {2, 2, 1, 4.2f, {0.383f, 0.0f}, launch_tiles<2, 2, 3>}, {1, 3, 2, 2.1f, {0.478f, 0.767f}, launch_tiles<1, 3, 2>},
-    {1, 2, 2, 2.3f, {0.273f, 0.558f}, launch_tiles<1, 2, 3>}, {1, 1, 2, 1.2f, {0.190f, 0.384f}, launch_tiles<1, 1, 4>},
+    {4, 4, 1, 9.9f, {1.12f, 0.0f}, launch_tiles<4, 4, 2, false>},  {4, 3, 1, 7.6f, {0.90f, 0.0f}, launch_tiles<4, 3, 2, false>},
+    {2, 2, 1, 4.2f, {0.383f, 0.0f}, launch_tiles<2, 2, 3, false>}, {1, 3, 2, 2.1f, {0.478f, 0.767f}, launch_tiles<1, 3, 2, false>},
+    {1, 2, 2, 2.3f, {0.273f, 0.558f}, launch_tiles<1, 2, 3, false>}, {1, 1, 2, 1.2f, {0.190f, 0.384f}, launch_tiles<1, 1, 4, false>},
 };
 
 float tile_cost(const TileKind &t, int tokens, int out_features, int in_features, int cus) {
@@ -241,13 +263,15 @@ float tile_cost(const TileKind &t, int tokens, int out_features, int in_features
 
 bool gemm_dense_applicable(const Params &p) { return p.in_features % 8 == 0; }       // (16-byte chunks of W's rows)
 
-// The tile shape with the least estimated time.  Switch dense=0 / =1: always the smallest / the largest one, for tests.
-int launch_gemm_dense(const Params &p, const __half *X, long long ldx, int tokens, __half *Y, long long ldy, const __half *Wd, long long ldw, hipStream_t s) {
+// The tile shape with the least estimated time.  Switch dense=0 / =1: always the smallest / the largest one, for tests.  With xsum, the
+// sums of X's rows: W holds the layer's centroids (w2 bytes behind it those of the residual table), see DenseArgs.
+int launch_gemm_dense(const Params &p, const __half *X, long long ldx, int tokens, __half *Y, long long ldy, const __half *Wd, long long ldw, hipStream_t s,
+                      const float *xsum, unsigned w2) {
   if (!gemm_dense_applicable(p)) return VQ_ERR_UNSUPPORTED;
   // Buffer offsets have 32 bits and the copies of missing chunks start 2 GiB up, so one launch covers at most 2 GiB of X and of W
   // and 4 GiB of Y (with room for a tile of rows past the end); more goes in several.
   const long long room = 1LL << 31, pad = 256;
-  const long long most_tokens = std::min(room / (ldx * 2), (room * 2 - 4096) / (ldy * 2)) - pad, most_out = room / (ldw * 2) - pad;
+  const long long most_tokens = std::min(room / (ldx * 2), (room * 2 - 4096) / (ldy * 2)) - pad, most_out = (room - w2) / (ldw * 2) - pad;
   if (most_tokens < 1 || most_out < 1) return VQ_ERR_UNSUPPORTED;
   const int force = switches().dense;
   for (long long o = 0; o < p.out_features; o += most_out)
@@ -257,7 +281,8 @@ int launch_gemm_dense(const Params &p, const __half *X, long long ldx, int token
       if (force != 0 && force != 1)
         for (const TileKind &k : kTiles)
           if (tile_cost(k, nt, no, p.in_features, cu_count()) < tile_cost(*best, nt, no, p.in_features, cu_count())) best = &k;
-      const int rc = best->launch({X + t * ldx, ldx, nt, Wd + o * ldw, ldw, no, p.in_features, Y + t * ldy + o, ldy, 0, 0}, s);
+      const int rc = best->launch({X + t * ldx, ldx, nt, Wd + o * ldw, ldw, no, p.in_features, Y + t * ldy + o, ldy, 0, 0, w2,
+                                   p.scale ? p.scale + o : nullptr, p.bias ? p.bias + o : nullptr, xsum ? xsum + t : nullptr}, s);
       if (rc != VQ_OK) return rc;
     }
   return VQ_OK;

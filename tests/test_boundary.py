@@ -227,17 +227,29 @@ def test_default_workspace_of_gemm_has_room_for_W_only_where_it_is_rounded_anywa
         assert vq.vq_validate(d) == vq.VQ_OK
         return vq.vq_gemm_default_workspace_bytes(d, tokens), vq.vq_gemm_fast_workspace_bytes(d, tokens), vq.vq_gemv_workspace_bytes(d, min(tokens, 16))
     v6 = dict(out_features=11008, in_features=4096, v=6, k=4096, idx_row_stride=1040)
-    for tokens, rounded in ((9, False), (64, False), (65, True), (509, True)):      # the kernel that restores on the fly from 65 tokens on
+    for tokens in (65, 509):                                    # the kernel that restores on the fly: rounded in any case
         got, fast, rows = default(tokens, **v6)
-        assert fast == 11008 * 4096 * 2 and got == (fast if rounded else rows)
-    for tokens in (9, 100, 5000):                                                   # codebook groups: it takes none
-        got, fast, rows = default(tokens, **dict(v6, group_vectors=176))
-        assert fast and got == rows < fast
+        assert got == fast == 11008 * 4096 * 2
+    for tokens in (9, 32, 48):                                  # vq_gemv's kernels
+        got, fast, rows = default(tokens, **v6)
+        assert got == rows == 0
+    res = dict(codebook_res=0x3000, idx_res=0x4000, idx_res_row_stride=1040, k_res=4096)
+    for kw, matrices in ((dict(v6, group_vectors=176), 1), (dict(v6, group_vectors=176, **res), 2)):      # codebook groups
+        assert default(9, **kw)[0] == default(9, **kw)[2]
+        for tokens in (100, 509):                               # ... centroids, and a sum a token
+            got, fast, rows = default(tokens, **kw)
+            assert got == matrices * fast + (tokens * 4 + 255) // 256 * 256
     down = dict(out_features=11008, in_features=4096, v=6, k=4096, idx_row_stride=6144, orientation=1)
-    assert [default(t, **down)[0] == default(t, **down)[2] for t in (16, 128, 129)] == [True, True, False]
+    got, fast, rows = default(16, **down)
+    assert got == rows
+    assert default(128, **down)[0] == fast + 512 and default(129, **down)[0] == fast
     v12 = dict(out_features=11008, in_features=4096, v=12, k=4096, idx_row_stride=528)
     assert [default(t, **v12)[0] == default(t, **v12)[2] for t in (16, 32, 33)] == [True, True, False]
     assert default(9, **dict(v6, col_perm=0x1000))[0] == default(9, **dict(v6, col_perm=0x1000))[1]      # the generic tile kernel
     assert vq.vq_gemm_default_workspace_bytes(_desc(v=0), 4) == 0
     wide = dict(in_features=8192, v=8, k=65536, idx_row_stride=2048)                # 256 MiB, and more
     assert default(100, **dict(wide, out_features=16384))[0] == 1 << 28 and default(100, **dict(wide, out_features=16385))[0] == 0
+    assert default(100, **dict(v6, out_features=20000, group_vectors=176, **res))[0] < 1 << 25      # (two matrices of 156 MiB)
+    assert vq.vq_gemm_default(_desc(), None, 32, 9, 0x9000, 8) == vq.VQ_ERR_NULL
+    assert vq.vq_gemm_default(_desc(), 0x8000, 32, 0, 0x9000, 8) == vq.VQ_ERR_SHAPE
+    assert vq.vq_gemm_default(_desc(), 0x8008, 32, 9, 0x9000, 8) == vq.VQ_ERR_ALIGNMENT

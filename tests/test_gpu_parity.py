@@ -171,8 +171,14 @@ def torch_double(a):
 HOLD_THE_WEIGHTS = {            # layers and token counts that vq_gemm without a workspace computes from unrounded weights
     "v6, 64 tokens": (dict(out_features=512, in_features=1536, v=6, k=4096), 64),
     "v6, no room for tiles": (dict(out_features=512, in_features=1536, v=6, k=4096, k_res=4096), 100),
-    "v6 groups": (dict(out_features=512, in_features=1536, v=6, k=4096, k_res=256, group_vectors=64), 300),
+    "v6 groups": (dict(out_features=512, in_features=1536, v=6, k=4096, group_vectors=64), 300),
+    "v6 groups, residual": (dict(out_features=513, in_features=1544, v=6, k=4096, k_res=256, group_vectors=64), 300),
+    "v6, odd outlier columns, residual": (dict(out_features=700, in_features=1600, v=6, k=4096, k_res=4096, n_outlier_cols=28, v_out=4, k_out=4096), 513),
+    "v6, ragged width": (dict(out_features=3000, in_features=2056, v=6, k=4096), 200),
+    "v6, odd width": (dict(out_features=512, in_features=1541, v=6, k=4096), 100),
     "orientation 1": (dict(out_features=384, in_features=1600, v=6, k=4096, orientation=1), 128),
+    "orientation 1, residual, outliers": (dict(out_features=3001, in_features=2056, v=6, k=4096, k_res=256, orientation=1, n_outlier_cols=7, v_out=4, k_out=300), 127),
+    "v8": (dict(out_features=3000, in_features=2048, v=8, k=256, k_res=256), 120),
     "v4": (dict(out_features=512, in_features=1600, v=4, k=256), 32),
     "v12": (dict(out_features=512, in_features=1536, v=12, k=4096, k_res=4096), 17),
 }
@@ -188,8 +194,10 @@ def test_gemm_by_default_rounds_no_weights_that_it_would_not_round_without_a_wor
     kw = dict(kw)
     L = s.make_layer(61, "hold", kw.pop("out_features"), kw.pop("in_features"), kw.pop("v"), kw.pop("k"), kw.pop("k_res", 0), **kw)
     dl = gpu_lib.DeviceLayer(L)
-    X = torch.from_numpy(s.make_activations(300, L, tokens)).cuda()
-    want = X.double() @ _unrounded_weights(gpu_lib, L).T.contiguous()
+    x = torch.from_numpy(s.make_activations(300, L, tokens)).cuda()
+    X = torch.full((tokens, (L.in_features + 7) // 8 * 8 + 8), float("nan"), dtype=torch.float16, device="cuda")
+    X[:, : L.in_features] = x
+    want = x.double() @ _unrounded_weights(gpu_lib, L).T.contiguous()
 
     def error(workspace):
         Y = gpu_lib.gemm(dl, X, workspace=workspace).double()
@@ -197,6 +205,31 @@ def test_gemm_by_default_rounds_no_weights_that_it_would_not_round_without_a_wor
     by_default, without, restored = error(None), error(lent("none")), error("fast")
     print("%s: default %.3g, without %.3g, fast %.3g" % (name, by_default, without, restored))
     assert by_default <= 1.1 * without
+
+
+@pytest.mark.parametrize("name", [n for n in SMALL if SMALL[n]["in_features"] % 8 == 0 and not SMALL[n].get("permute")])
+@pytest.mark.parametrize("tokens,tiles", [(9, "smallest"), (65, "auto"), (130, "largest"), (257, "largest"), (300, "smallest")])
+def test_gemm_from_restored_centroids(gpu_lib, monkeypatch, name, tokens, tiles):
+    """Centroids restored into one or two matrices, scale and bias applied to the sums, forced for every layer: around the edges of
+    the tiles and of the step from one matrix to the other, with NaN in the padding of X, a sentinel in that of Y, and a workspace
+    full of NaN."""
+    import torch
+    monkeypatch.setenv("VQ_SWITCHES", "gemm=c" + {"auto": "", "smallest": ",dense=0", "largest": ",dense=1"}[tiles])
+    L = small_layer(name)
+    dl = gpu_lib.DeviceLayer(L)
+    need = gpu_lib.vq_gemm_default_workspace_bytes(dl.desc, tokens)
+    matrices = 0 if L.k_res > 4096 else 2 if L.k_res else 1
+    assert need >= matrices * L.out_features * L.in_features * 2 + tokens * 4 or not matrices
+    x = s.make_activations(300, L, tokens)
+    X = torch.full((tokens, L.in_features + 8), float("nan"), dtype=torch.float16, device="cuda")
+    X[:, : L.in_features] = torch.from_numpy(x).cuda()
+    Y = torch.full((tokens, L.out_features + 3), 7.0, dtype=torch.float16, device="cuda")
+    ws = torch.full((need + 256,), 0xFF, dtype=torch.uint8, device="cuda")
+    rc = gpu_lib.vq_gemm_default(dl.desc, X.data_ptr(), X.stride(0), tokens, Y.data_ptr(), Y.stride(0), ws.data_ptr(), need, torch.cuda.current_stream().cuda_stream)
+    assert rc == gpu_lib.VQ_OK
+    torch.cuda.synchronize()
+    _check_matmul(Y[:, : L.out_features], oracle.gemm(L, x), "%s tokens %d" % (name, tokens))
+    assert (Y[:, L.out_features:] == 7.0).all() and (ws[need:] == 0xFF).all()
 
 
 @pytest.mark.parametrize("out_features,refused", [(16384, False), (8192, True)])
