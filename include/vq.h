@@ -41,8 +41,8 @@
  * the device address of vq_gemv_static_workspace's array), all of them guarded.
  * The environment variable VQ_SWITCHES ("name=value,..."; read once at the
  * start of every call) forces kernel choices for tests and measurements:
- * gemv=g|m|d (generic / matrix-core / dot-product kernels), groups=loop, multi=0,
- * gemm=g|f|w|r|6, dense=0|1, dequant=g; unset, every choice is the library's own.
+ * gemv=g|m|d (generic / matrix-core / dot-product kernels), rows=0|1, groups=loop, multi=0,
+ * gemm=g|f|w|r|6|c, dense=0|1, dequant=g; unset, every choice is the library's own.
  */
 #ifndef VQ_H
 #define VQ_H
@@ -93,8 +93,9 @@ typedef struct vq_layer_desc {
    * (n_outlier_cols need not be a multiple of v_out).  Codebook groups are ranges of group_vectors stream positions,
    * i.e. of main columns.  Scale and bias stay per output row.  This field occupies what used to be padding after
    * group_vectors: descriptors that were zeroed as a whole keep orientation 0.  Layers of orientation 1 with v = 6 /
-   * 12-bit indices or v = 8 / 8- or 16-bit indices have fast vq_gemv and vq_dequant kernels of their own; others, and
-   * vq_gemm without a workspace, run on the generic kernels.                                                        */
+   * 12-bit indices or v = 8 / 8- or 16-bit indices have vq_gemv kernels of their own, the paper's other settings the ones
+   * that they have in orientation 0, and vq_dequant treats both alike; vq_gemm without a workspace runs through vq_gemv's
+   * kernels, sixteen rows at a time, where those are faster than the generic one.                                   */
   int32_t orientation;
   /* Column order (Sec. 3.2.3: the columns that get the outlier codebook are the ones the Hessian's diagonal singles
    * out, wherever they lie; Algorithm 2's outlier step).  NULL: the stored order of the columns is the layer's.
@@ -132,8 +133,9 @@ int vq_dequant(const vq_layer_desc *desc, void *W, int64_t ldw, void *hip_stream
  * multiplications (the LDS lookups cost the same and the vector ALUs stop binding); VQ_SWITCHES gemv=d
  * keeps every batch on the vector ALUs.  That is the v = 6 / 12-bit layers; v = 8 with 8- or 16-bit indices gathers its
  * table from L2; the paper's other settings (v = 12 with two 4096-entry tables, v = 4 / k = 256, v = 2 / k = 16, ..., with
- * codebook groups and outlier columns of v = 4, in either orientation) run four rows a launch on the vector ALUs with
- * one table in LDS at a time; what is left runs on generic kernels.
+ * codebook groups and outlier columns of v = 4, in either orientation) run on the vector ALUs with one table in LDS at a
+ * time, and from three rows on (or where two tables do not fit LDS together) on the matrix cores, as v = 8 does, any number
+ * of rows in one launch; what is left runs on generic kernels.
  * x: fp16 [batch][ldx], ldx >= in_features; y: fp16 [batch][ldy],
  * ldy >= out_features; batch in [1,16]; x and y 2-byte aligned (a 16-byte aligned x with ldx % 8 == 0
  * lets the fastest kernels run).  y must not alias x.                                               */
@@ -141,7 +143,7 @@ int vq_gemv(const vq_layer_desc *desc, const void *x, int64_t ldx, int32_t batch
             void *y, int64_t ldy, void *hip_stream);
 
 /* vq_gemv with a workspace on loan (device memory, 256-byte aligned, owned by the caller, contents undefined
- * afterwards).  Only layers with codebook groups (Sec. 3.1) use it (v = 6 layers on the matrix-core kernel, the other
+ * afterwards).  Layers with codebook groups (Sec. 3.1) use it (v = 6 layers on the matrix-core kernel, the other
  * settings on the kernel that keeps one table in LDS at a time): with vq_gemv_workspace_bytes(desc, batch) bytes
  * every workgroup takes one group, whose tables it loads once, and a share of the rows, writes binary32 sums to the
  * workspace, and a second kernel adds the groups up in ascending order and applies scale and bias -- instead of every
@@ -149,7 +151,8 @@ int vq_gemv(const vq_layer_desc *desc, const void *x, int64_t ldx, int32_t batch
  * two rows on (from one row when a row of x does not fit the one-row kernel's LDS beside the tables: about 15000
  * columns with a 12-bit residual table): the matrix-core kernel of that orientation works in blocks of 16 index streams (96 output rows), too few
  * to fill the chip on most layers, so with a workspace it also cuts the columns into parts, one workgroup per (block,
- * part), and the same second kernel adds the parts up.  vq_gemv_workspace_bytes returns 0 when no kernel
+ * part), and the same second kernel adds the parts up; so does the matrix-core kernel of the paper's other settings.  Layers
+ * with a column permutation gather the activations into it first.  vq_gemv_workspace_bytes returns 0 when no kernel
  * would use a workspace for this layer.  With workspace NULL or smaller than that, and for every other layer, the
  * call is vq_gemv.  Same arguments, bar and errors as vq_gemv; a workspace that is not 256-byte aligned is
  * VQ_ERR_ALIGNMENT.  Calls that share a workspace must not overlap.                                          */
@@ -243,13 +246,14 @@ int vq_quantize_columns(void *W, int64_t ldw, int32_t rows, int32_t cols, const 
  *  - it must hold at least vq_gemm_workspace_bytes(desc, tokens) bytes (currently 0: NULL is fine),
  *    else VQ_ERR_WORKSPACE;
  *  - if it holds vq_gemm_fast_workspace_bytes(desc, tokens) bytes (non-zero when in_features is a
- *    multiple of 8), the call restores W into it once (as vq_dequant does) and multiplies from there,
+ *    multiple of 8), the call restores W into it once (as vq_dequant does, rounded to binary16) and multiplies from there,
  *    which is the faster route on this GPU; with less, the restored weights go straight from
  *    on-chip tiles into the matrix cores and W is never written to memory (kernels of their own for
  *    v = 8 / 16-bit indices, gathered from L2, and for v = 6 / 12-bit indices with one codebook group
  *    and outlier columns in multiples of 16, whose tables sit in LDS; other layers restore through the
  *    generic tile kernel).
- * Small token counts are computed as vq_gemv computes them, up to sixteen rows of X at a time, where
+ * Small token counts (and, without a workspace, any number for layers that no tile kernel but the generic one takes) are
+ * computed as vq_gemv computes them, from unrounded weights, up to sixteen rows of X at a time, where
  * that is the faster way on this GPU: same result bar, nothing for the caller to do.                */
 int vq_gemm(const vq_layer_desc *desc, const void *X, int64_t ldx, int32_t tokens,
             void *Y, int64_t ldy, void *workspace, size_t workspace_bytes, void *hip_stream);
