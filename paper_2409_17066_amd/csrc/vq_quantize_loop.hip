@@ -1,55 +1,73 @@
 // vq_quantize_columns in one launch: Algorithm 1 (Sec. 3.1) with its nearest-centroid searches on the matrix cores.
 #include "vq_quantize.hpp"
+#include <type_traits>
 
 namespace vq {
 namespace {
 
 // A workgroup owns up to four stack positions (P of them) and walks all columns of the matrix with them: nothing it needs comes
-// from another workgroup.  The tables stay where they are for the whole launch: as operands of v_mfma_f32_16x16x32_f16 in
-// registers, 64 centroids a wave and group (a wave of sixteen holds four such groups of a 4096-entry table), and as plain
-// entries in LDS.
+// from another workgroup.  Four of its eight waves search, one on each SIMD; the tables stay where they are for the whole launch: as
+// operands of v_mfma_f32_16x16x32_f16 in their registers, 64 centroids a wave and group (sixteen groups of a 4096-entry table), and as
+// plain entries in LDS.  The other four keep the positions' rows of the running block, a column to a thread.
 //
-// One column.  The owner wave of a position posts the vector t in LDS: as binary32, and scaled by a power of two and split into
-// two binary16 parts.  Every wave computes the scores t . c - |c|^2 / 2 of their centroids with all P vectors at once
-// (vq_assign.hip has the same scheme and its error bounds).  Entries of up to six elements take 8 of the instruction's 32 k
-// slots, |c|^2 / 2 in two parts behind them, so a row of operand A holds four centroids and each of the 16 columns of operand B
-// one of four vectors at one of the four places, zeros elsewhere: 64 centroids with four vectors in two instructions, for
-// the high and the low parts of t.  Entries of up to 14 elements take 16 slots, longer ones 32.  The largest score of each vector
-// meets in LDS (an atomic maximum); after a barrier the lanes whose scores are within the rounding bounds of it -- as a rule one --
-// compute the distances of those four centroids as defined, one each in a quad of lanes, and these meet in LDS too (an atomic
-// minimum of distance bits and index).  From the index the owner forms E and the next column's t and posts that;
-// while the others search it brings its tile of running weights up to date.  Three barriers a search.
+// One column.  Every search wave holds the P vectors t, up to four elements a lane (lane 16 q + 4 n + j: vector n, the j-th quarter
+// of its elements; the four rows of lanes alike), scales them by a power of two and rounds them to binary16: operand B.  Scores
+// t . c - |c|^2 / 2 come from the matrix cores.  Entries of up to six elements take 8 of its 32 k slots,
+// |c|^2 / 2 in two parts behind them, so a row of operand A holds four centroids and each of the 16 columns of operand B one of
+// four vectors at one of the four places, zeros elsewhere: 64 centroids with four vectors at once.  Entries of up to 14
+// elements take 16 slots, longer ones 32.  A lane gets the scores of four neighbouring centroids at a time and keeps the largest of these
+// groups' maxima, its group's number in the lowest bits, and the second largest.  A row of lanes computes the distances of its best
+// four centroids as defined, one in each lane of a quad; where anything else of the wave is within the rounding bounds of its largest
+// score (in a tenth of the columns) those distances are computed too.  What the rows of all waves find meets in LDS (an atomic
+// minimum of distance bits and index).  Behind the column's only barrier every search wave looks the winner up, forms the error and the
+// next column's t by itself: nothing else is exchanged on the way from one column to the next.
+//
+// The block's running weights lag two columns behind: t of column n + 1 is the value with the errors up to column n - 2, which the
+// keeping waves post while column n is searched, less the last two errors' shares, which the search waves hold.  The keeping
+// waves also file E, T and the indices.
 //
 // At the end of a block the workgroup writes its quantized columns and indices and applies E to its rows of the later columns:
-// v_mfma_f32_32x32x2_f32 on 32 rows (P v of them in use) and 32 columns, the rows of H^-1 straight from memory.
+// v_mfma_f32_4x4x1_16b_f32, four rows (broadcast from one of the sixteen blocks of operand A) by 64 columns, so that P v = 18 rows
+// cost 20 (of 32x32x2 they would use 18 of 32); the rows of H^-1 come straight from memory.
 //
-// What bounds it: the chain of a column.  A wave on its own issues an instruction every five clocks, so what counts is how many
-// stand on the path between one column's t and the next, the LDS round trips (130 clocks) and the barriers, not any rate: 3700
-// clocks a column, of which the owner's part between two searches is 1100 and the search 2600.  4096 x 4096, v = 6, k = 4096, blocks
-// of 128 columns: 20.9 -> 7.4 ms (of that the end of the blocks 1.5 ms); 475 x 1069: 2.5 -> 1.8 ms.
+// What bounds it: the chain of a column.  A wave on its own issues an instruction every five clocks or so, and what counts is how many
+// stand on the path between one column's t and the next (about 230 with a 4096-entry table), the LDS round trips (130 clocks, four of
+// them) and the barrier, not any rate: 1800 clocks a column, of which the comparisons of the scores are 500.  Eight search waves
+// of half the table each are slower (4.8 ms against 4.6): everything but the comparisons is then issued twice on every SIMD.
+// The end of a block waits for H^-1 (1 MB through every compute unit, which takes 64 bytes a clock) and for W, 94 of 340 thousand clocks at
+// 4096 columns.  Before, with the vector posted and its errors kept by one wave, three barriers and the low parts of t
+// multiplied as well, a column took 3700 clocks.  v = 6, k = 4096, 4096 x 4096: 7.2 -> 4.6 ms; 300 x 1000: 1.38 -> 0.87; with a
+// 256-entry residual table, 1500 x 1000: 2.23 -> 1.50; v = 12, k = 4096, 1500 x 1000: 2.28 -> 1.42; v = 4, k = 256: 1.26 -> 0.62.
 typedef _Float16 half8v __attribute__((ext_vector_type(8)));
+typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef float float4v __attribute__((ext_vector_type(4)));
 
 constexpr int PMAX = 4;
-constexpr int HB = 8;                    // rows of H^-1 that are fetched together
+constexpr int SEARCH = 4, KEEP = 4;      // waves
+constexpr int LOOP_THREADS = (SEARCH + KEEP) * 64;
 // k slots of an entry; entries side by side in an instruction's 32; registers of 8 slots a lane holds per 64 centroids.
 constexpr int entry_slots(int vp) { return vp <= 6 ? 8 : vp <= 14 ? 16 : 32; }
 constexpr int entries_wide(int vp) { return 32 / entry_slots(vp); }
 constexpr int group_tiles(int vp) { return 4 / entries_wide(vp); }
 constexpr int E_PITCH = QB + 1;
+constexpr int quarter(int vp) { return vp <= 8 ? 2 : vp <= 12 ? 3 : 4; }     // elements a lane holds of a vector
+constexpr unsigned TAG = 63u;            // group, tile and place: the lowest bits of a score
 
-struct LoopExchange {                  // LDS
-  _Float16 operand[PMAX][2][32];       // the vectors as k slots: high and low parts
-  _Float16 zeros[8];
-  float t[PMAX][20];
-  float eps[PMAX];                     // how far below the largest score a nearest centroid's may lie, in scaled scores
-  float most[2][PMAX];                 // largest score so far
-  unsigned long long nearest[2][PMAX]; // smallest (distance bits, index) so far
-  float h_max[2][16], c_bad[2][16];
-  float hinv[2 * HB][QB];              // rows of H^-1 inside the block, around the current column
+struct ColumnConstants { float diag, inverse, beside, beside2; };            // of H^-1: (n, n), its reciprocal or 0, (n, n + 1), (n - 1, n + 1)
+
+struct LoopExchange {                    // LDS
+  unsigned long long nearest[2][4][PMAX];  // [main, residual][column & 3]: smallest (distance bits, index) so far
+  // lane layout: [vector][quarter][element]
+  float next_w[2][PMAX * 16];            // the next column's weights without the last two errors
+  float e[2][PMAX * 16], t[2][PMAX * 16];
+  ColumnConstants column[QB];
+  float h_max[2][SEARCH + KEEP], c_bad[2][SEARCH + KEEP];
 };
 
+// An entry in LDS: its elements in order, but twelve elements in four quarters of four halfs (the last one zero).
 template <int VP> constexpr int loop_entry_halfs() { return VP <= 4 ? 4 : VP <= 8 ? 8 : 16; }
+template <int VP>
+__device__ __forceinline__ constexpr int entry_place(int el) { return VP == 12 ? el / 3 * 4 + el % 3 : el; }
 
 template <int VP>
 size_t loop_lds_bytes(int k, int k_res) {
@@ -57,14 +75,21 @@ size_t loop_lds_bytes(int k, int k_res) {
 }
 
 // Centroid whose slots a lane holds in tile `tile` of group `g`, and which eight of them: row m of operand A is lane m of every
-// sixteen, slots 8 q .. 8 q + 7 the q-th sixteen lanes.
+// sixteen, slots 8 q .. 8 q + 7 the q-th sixteen lanes.  Sixteen neighbours to a row's place, the waves side by side.
 template <int VP>
-__device__ __forceinline__ int operand_entry(int g, int tile, int lane, int wave, int waves) {
+__device__ __forceinline__ int operand_entry(int g, int tile, int lane, int wave) {
   constexpr int SW = entries_wide(VP);
-  return (g * waves + wave) * 64 + (tile * SW + (lane >> 4) * SW / 4) * 16 + (lane & 15);
+  return ((g * group_tiles(VP) + tile) * SW + (lane >> 4) * SW / 4) * (SEARCH * 16) + wave * 16 + (lane & 15);
 }
 template <int VP>
 __device__ __forceinline__ int operand_part(int lane) { return (lane >> 4) & (4 / entries_wide(VP) - 1); }
+
+// What a slot of an entry holds: an element, the first (-1) or second (-2) part of |c|^2 / 2, or nothing (-3).
+template <int VP>
+__device__ __forceinline__ constexpr int slot_content(int slot) {
+  if (VP == 12) return slot % 4 < 3 ? slot / 4 * 3 + slot % 4 : slot == 3 ? -1 : slot == 7 ? -2 : -3;
+  return slot < VP ? slot : slot == VP ? -1 : slot == VP + 1 ? -2 : -3;
+}
 
 // |c|^2 / 2 of an entry's first `len` elements.
 template <int VP>
@@ -80,205 +105,293 @@ __device__ __forceinline__ float half_norm(const __half *src, int len) {
 
 // A table as matrix-core operands (groups of 64 centroids, rows past the table repeating its last entry).
 template <int VP, int G>
-__device__ __forceinline__ void load_operands(const __half *cb, int k, int v, int len, int f, int lane, int wave, int waves,
-                                              half8v (&A)[G][group_tiles(VP)]) {
+__device__ __forceinline__ void load_operands(const __half *cb, int k, int v, int len, int f, int lane, int wave, half8v (&A)[G][group_tiles(VP)]) {
 #pragma unroll
   for (int g = 0; g < G; ++g)
 #pragma unroll
     for (int tile = 0; tile < group_tiles(VP); ++tile) {
-      const __half *src = cb + (long long)min(operand_entry<VP>(g, tile, lane, wave, waves), k - 1) * v;
+      const __half *src = cb + (long long)min(operand_entry<VP>(g, tile, lane, wave), k - 1) * v;
       const float x = ldexpf(half_norm<VP>(src, len), f);
       const _Float16 n1 = (_Float16)x, n2 = (_Float16)(x - (float)n1);
       const int part = operand_part<VP>(lane);
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const int slot = part * 8 + i;
-        const _Float16 c = __builtin_bit_cast(_Float16, src[slot < len ? slot : 0]);
-        A[g][tile][i] = slot < VP ? (slot < len ? c : (_Float16)0.0f) : slot == VP ? n1 : slot == VP + 1 ? n2 : (_Float16)0.0f;
+        _Float16 y = (_Float16)0.0f;
+#pragma unroll
+        for (int p = 0; p < 4 / entries_wide(VP); ++p) {
+          const int what = slot_content<VP>(p * 8 + i);
+          if (part == p) y = what >= 0 ? (what < len ? __builtin_bit_cast(_Float16, src[what < len ? what : 0]) : (_Float16)0.0f)
+                                       : what == -1 ? n1 : what == -2 ? n2 : (_Float16)0.0f;
+        }
+        A[g][tile][i] = y;
       }
+      asm volatile("" : "+v"(A[g][tile]) :: "memory");       // (one after the other: their loads would take all registers at once)
     }
 }
 
-// Scale of one table (|c|^2 / 2 times 2^f stays below 2^15), and the rounding bounds: with t scaled by 2^e to below 2^14, scaled
-// scores are within eps0 + eps_up 2^e + eps_down 2^-e of each other's order (infinity where the table's entries are not finite or huge).
-struct LoopTable { int f; float eps0, eps_up, eps_down; };
+// One table.  |c|^2 / 2 times 2^f stays below 2^15.  How far below the largest score of a wave (its lowest bits a tag) a nearest
+// centroid's may lie, in scaled scores, with t scaled by 2^e to below 2^14:
+// - what t lost to binary16, |low| |c| for each of two scores;
+// - an instruction's v + 2 terms, each cut at 2^-24 of the sum of the terms' magnitudes, |t| |c| + |c|^2 / 2 (vq_assign.hip);
+// - the definition's own roundings, (v + 2) 2^-24 of (|t| + |c|)^2, twice;
+// - |c|^2 / 2 itself: its sum, and two binary16 parts, 2^-21 of the largest;
+// - the tags: 2^-17 of either score.
+// Together low_c |low| + eps0 + eps_up 2^e + eps_down 2^-e; `bad` where entries are not finite or huge: every distance decides.
+struct LoopTable { int f, bad; float low_c, eps0, eps_up, eps_down; };
 
 template <int VP>
-__device__ __forceinline__ LoopTable loop_table(const float *h_max, const float *bad, int waves) {
+__device__ __forceinline__ LoopTable loop_table(const float *h_max, const float *bad) {
   LoopTable t;
   float m = 0.0f, b = 0.0f;
-  for (int w = 0; w < waves; ++w) { m = fmaxf(m, h_max[w]); b += bad[w]; }
+  for (int w = 0; w < SEARCH + KEEP; ++w) { m = fmaxf(m, h_max[w]); b += bad[w]; }
   t.f = m > 0.0f ? min(14, max(-14, 15 - __builtin_amdgcn_frexp_expf(m))) : 14;
-  // scores: two instructions whose v + 2 terms and accumulator are each cut at 2^-24 of the sum of the terms' magnitudes, |t| |c| + |c|^2 / 2
-  // (vq_assign.hip), for two scores (operands below 2^-14 counted as that); |c|^2 / 2 to 2^-21 of the largest, t to 2^-20 where its
-  // low part runs out of bits; the definition's own roundings: (v + 2) 2^-24 of (|t| + |c|)^2, twice
+  // (operands below 2^-14 count as that)
   const float c = __builtin_amdgcn_sqrtf(2.0f * m) * 1.001f + 0x1p-12f, T = __builtin_amdgcn_sqrtf((float)VP) * 1.001f * 0x1p14f;
-  constexpr float D = (VP + 3) * 0x1p-23f, S = (VP + 3) * 0x1p-22f;
-  t.eps0 = S * T * c + D * 2.0f * T * c + 0x1p-20f * c;
-  t.eps_up = 0.5f * S * c * c + D * c * c + 0x1p-21f * m + 0x1p-37f;
-  t.eps_down = D * T * T;
-  if (b != 0.0f) t.eps0 = __builtin_inff();
+  constexpr float K = (VP + 3) * 0x1p-23f, TAGS = 1.01f * 0x1p-16f;
+  t.low_c = 2.01f * c;
+  t.eps0 = T * c * (3.0f * K + TAGS);
+  t.eps_up = m * (4.0f * K + 0x1p-20f + TAGS) + K * c * c + 0x1p-37f;
+  t.eps_down = K * T * T;
   // (the same in every lane: kept in scalar registers)
   auto scalar = [](float y) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(y))); };
   t.f = __builtin_amdgcn_readfirstlane(t.f);
-  t.eps0 = scalar(t.eps0); t.eps_up = scalar(t.eps_up); t.eps_down = scalar(t.eps_down);
+  t.bad = __builtin_amdgcn_readfirstlane(b != 0.0f ? 1 : 0);
+  t.low_c = scalar(t.low_c); t.eps0 = scalar(t.eps0); t.eps_up = scalar(t.eps_up); t.eps_down = scalar(t.eps_down);
   return t;
 }
 
-template <int N>
-__device__ __forceinline__ float dpp_max(float x) {        // largest of the first N (8, 16) lanes' |x|, in those lanes
-#define VQ_DPP_FMAX(CTRL) x = __uint_as_float(max(__float_as_uint(x), (unsigned)__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, false)))
-  x = fabsf(x);
-  VQ_DPP_FMAX(0xB1);
-  VQ_DPP_FMAX(0x4E);
-  VQ_DPP_FMAX(0x141);
-  if constexpr (N > 8) VQ_DPP_FMAX(0x140);
-#undef VQ_DPP_FMAX
-  return x;
+#define VQ_QUAD(CTRL, X) __builtin_amdgcn_update_dpp(0, (int)(X), CTRL, 0xF, 0xF, true)
+template <int J>
+__device__ __forceinline__ unsigned quad_lane(unsigned x) { return (unsigned)VQ_QUAD(J * 0x55, x); }     // lane J of the quad
+// (maximum rather than fmaxf: no instruction to quiet its operands)
+__device__ __forceinline__ float maximum(float a, float b) { return __builtin_elementwise_maximum(a, b); }
+__device__ __forceinline__ float quad_max(float x) {
+  x = maximum(x, __int_as_float(VQ_QUAD(0xB1, __float_as_int(x))));
+  return maximum(x, __int_as_float(VQ_QUAD(0x4E, __float_as_int(x))));
+}
+__device__ __forceinline__ unsigned quad_max(unsigned x) {
+  x = max(x, (unsigned)VQ_QUAD(0xB1, x));
+  return max(x, (unsigned)VQ_QUAD(0x4E, x));
+}
+__device__ __forceinline__ float quad_sum(float x) {
+  x += __int_as_float(VQ_QUAD(0xB1, __float_as_int(x)));
+  return x + __int_as_float(VQ_QUAD(0x4E, __float_as_int(x)));
+}
+__device__ __forceinline__ unsigned quad_min(unsigned x) {
+  x = min(x, (unsigned)VQ_QUAD(0xB1, x));
+  return min(x, (unsigned)VQ_QUAD(0x4E, x));
+}
+#undef VQ_QUAD
+// Largest of the four rows of lanes, place by place, in all of them.
+__device__ __forceinline__ float rows_max(float x) {
+  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = maximum(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return maximum(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
-// Lane j of the owner wave holds t_j (0 from the vector's length on): puts the vector up for the search of table `tb`.
+// What a lane's place in operand B takes: masks of the part of its eight slots.
+struct LaneMasks { unsigned part[3]; };
 template <int VP>
-__device__ __forceinline__ void post_vector(LoopExchange &x, int p, float t, const LoopTable &tb, int lane) {
-  float most = dpp_max<VP + 2 <= 8 ? 8 : 16>(t);
-  if constexpr (VP + 2 > 16) most = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(most)));
-  const int e = most > 0.0f ? min(tb.f + 15, max(tb.f - 14, 14 - __builtin_amdgcn_frexp_expf(most))) : tb.f;
-  const float scaled = ldexpf(t, e);
-  const _Float16 hi = (_Float16)scaled, lo = (_Float16)(scaled - (float)hi);
-  // (the slots behind the elements: the |c|^2 slots' factor -2^(e - f) among the high parts, zeros among the low ones)
-  const _Float16 factor = __builtin_bit_cast(_Float16, (unsigned short)(0x8000u | (unsigned)(e - tb.f + 15) << 10));
-  const float eps = __fmaf_rn(tb.eps_up, ldexpf(1.0f, e), __fmaf_rn(tb.eps_down, ldexpf(1.0f, -e), tb.eps0));
-  if (lane < VP + 2) {
-    x.operand[p][0][lane] = lane < VP ? hi : factor;
-    x.operand[p][1][lane] = lo;
-    x.t[p][lane] = t;
-    x.eps[p] = eps;
+__device__ __forceinline__ LaneMasks lane_masks(int lane) {
+  constexpr int SW = entries_wide(VP);
+  const bool mine = (lane >> 4) * SW / 4 == (lane & (SW - 1));
+  LaneMasks m;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    m.part[i] = mine && operand_part<VP>(lane) == i ? ~0u : 0u;
+    asm volatile("" : "+v"(m.part[i]));                      // (an operand of an and, not a choice)
   }
+  return m;
 }
 
-// One padded table entry (EH halfs) from LDS, in whole 16-byte reads (8 bytes for the smallest entries; the compiler narrows and splits
-// a read whose tail is unused).  The wait stands in the same statement: this file's larger variants spill, and a register must not be
-// saved while a read into it is on its way.
-template <int EH>
-__device__ __forceinline__ void read_entry(unsigned (&dst)[EH / 2], unsigned lds_addr) {
-  if constexpr (EH == 4) {
-    uint2v a;
-    asm volatile("ds_read_b64 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(a) : "v"(lds_addr) : "memory");
-    dst[0] = a.x; dst[1] = a.y;
-  } else if constexpr (EH == 8) {
-    uint4v a;
-    asm volatile("ds_read_b128 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(a) : "v"(lds_addr) : "memory");
-    dst[0] = a.x; dst[1] = a.y; dst[2] = a.z; dst[3] = a.w;
+// The vectors as operand B, and what their search's bounds need.
+template <int VP>
+struct Posted {
+  half8v B;
+  float t[quarter(VP)], low[quarter(VP)];                    // (low: what the rounding to binary16 cut off)
+  int e;                                                     // scaled by 2^e
+  bool brute;                                                // not within binary16 so, or not a number
+};
+
+template <int VP>
+__device__ __forceinline__ Posted<VP> post_vectors(const float (&t)[quarter(VP)], const LoopTable &tb, const LaneMasks &in, int lane) {
+  constexpr int EPL = quarter(VP);
+  Posted<VP> p;
+  const int j = lane & 3;
+  unsigned most = 0u;
+#pragma unroll
+  for (int r = 0; r < EPL; ++r) { p.t[r] = t[r]; most = max(most, __float_as_uint(t[r]) & 0x7FFFFFFFu); }
+  const int e = 140 - (int)(quad_max(most) >> 23);
+  p.brute = e < tb.f - 14 || tb.bad != 0;
+  p.e = min(tb.f + 15, max(tb.f - 14, e));
+  _Float16 hi[4] = {(_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f};
+#pragma unroll
+  for (int r = 0; r < EPL; ++r) {
+    const float scaled = ldexpf(t[r], p.e);
+    hi[r] = (_Float16)scaled;
+    p.low[r] = scaled - (float)hi[r];
+  }
+  // (the |c|^2 slots' factor: -2^(e - f))
+  const unsigned one = ((unsigned)p.e << 10) + (0x8000u + (unsigned)(15 - tb.f) * 1024u);
+  auto pack = [](_Float16 a, _Float16 b) {
+    const half2v y = {a, b};
+    return __builtin_bit_cast(unsigned, y);
+  };
+  const unsigned ones = pack(__builtin_bit_cast(_Float16, (unsigned short)one), __builtin_bit_cast(_Float16, (unsigned short)one));
+  unsigned B[4];
+  if constexpr (EPL == 2) {
+    unsigned d = pack(hi[0], hi[1]);
+    if constexpr (VP < 8) d = j == VP / 2 ? ones : d;
+    B[0] = quad_lane<0>(d) & in.part[0]; B[1] = quad_lane<1>(d) & in.part[0];
+    B[2] = quad_lane<2>(d) & in.part[0]; B[3] = quad_lane<3>(d) & in.part[0];
+    if constexpr (VP == 8) B[0] |= ones & in.part[1];
   } else {
-    uint4v a, b;
-    asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %2 offset:16\n\ts_waitcnt lgkmcnt(0)" : "=&v"(a), "=v"(b) : "v"(lds_addr) : "memory");
-    dst[0] = a.x; dst[1] = a.y; dst[2] = a.z; dst[3] = a.w;
-    dst[4] = b.x; dst[5] = b.y; dst[6] = b.z; dst[7] = b.w;
+    const unsigned d0 = pack(hi[0], hi[1]);
+    unsigned d1 = pack(hi[2], hi[3]);
+    if constexpr (EPL == 3) d1 |= j < 2 ? ones & 0xFFFF0000u : 0u;
+    B[0] = (quad_lane<0>(d0) & in.part[0]) | (quad_lane<2>(d0) & in.part[1]);
+    B[1] = (quad_lane<0>(d1) & in.part[0]) | (quad_lane<2>(d1) & in.part[1]);
+    B[2] = (quad_lane<1>(d0) & in.part[0]) | (quad_lane<3>(d0) & in.part[1]);
+    B[3] = (quad_lane<1>(d1) & in.part[0]) | (quad_lane<3>(d1) & in.part[1]);
+    if constexpr (VP == 16) B[0] |= ones & in.part[2];
   }
+  const uint4v b = {B[0], B[1], B[2], B[3]};
+  p.B = __builtin_bit_cast(half8v, b);
+  return p;
 }
 
-// One search of all P posted vectors over a table of `count` entries; every wave of the workgroup takes part.
-template <int VP, int G>
-__device__ __forceinline__ void search_table(LoopExchange &x, const half8v (&A)[G][group_tiles(VP)], unsigned lds_entries, int count, int P, int par,
-                                             int lane, int wave, int waves) {
-  constexpr int EH = loop_entry_halfs<VP>(), SW = entries_wide(VP), TILES = group_tiles(VP);
-  // columns 4 n .. 4 n + 3 of operand B: vector n at the places 0 .. SW - 1 (and again)
-  const int n = (lane >> 2) & 3, place = lane & (SW - 1);
-  const bool mine = (lane >> 4) * SW / 4 == place;
-  half8v B[2];
+// One padded table entry (EH halfs) from LDS, in whole 16-byte reads (8 bytes for the smallest entries; the compiler would narrow
+// and split a read whose tail is unused).
+template <int EH>
+__device__ __forceinline__ void read_entry(unsigned (&dst)[EH / 2], const unsigned char *entry) {
+  if constexpr (EH == 4) {
+    const uint2v a = *reinterpret_cast<const uint2v *>(entry);
+    dst[0] = a.x; dst[1] = a.y;
+  } else {
 #pragma unroll
-  for (int part = 0; part < 2; ++part)
-    B[part] = *reinterpret_cast<const half8v *>(mine ? &x.operand[n][part][operand_part<VP>(lane) * 8] : &x.zeros[0]);
-  const float eps = x.eps[n];
-  float4v acc[G][TILES];
-#pragma unroll
-  for (int g = 0; g < G; ++g)
-#pragma unroll
-    for (int tile = 0; tile < TILES; ++tile)
-      acc[g][tile] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A[g][tile], B[0], float4v{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
-#pragma unroll
-  for (int g = 0; g < G; ++g)
-#pragma unroll
-    for (int tile = 0; tile < TILES; ++tile) acc[g][tile] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A[g][tile], B[1], acc[g][tile], 0, 0, 0);
-  float most = -__builtin_inff();
-#pragma unroll
-  for (int g = 0; g < G * TILES; ++g) {
-    const float4v &a = acc[g / TILES][g % TILES];
-    most = fmaxf(fmaxf(most, a[0]), a[1]);
-    most = fmaxf(fmaxf(most, a[2]), a[3]);
-  }
-  // of the four lanes that hold one vector, then of all of them that do
-  float quad = most;
-  asm("s_nop 1\n\tv_max_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\ts_nop 1\n\t"
-      "v_max_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf" : "+v"(quad));
-  if ((lane & 3) == 0) __hip_atomic_fetch_max(&x.most[par][n], quad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-  lds_barrier();                                             // (without it most waves would take their own largest for a candidate)
-  const float bar = __hip_atomic_load(&x.most[par][n], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) - eps;
-  if (!__any(n < P && !(quad < bar))) return;
-  // Tiles of which the four distances are wanted; the lanes of a quad compute one each, of the same four centroids.
-  unsigned ask = 0u;
-#pragma unroll
-  for (int g = 0; g < G * TILES; ++g) {
-    const float4v &a = acc[g / TILES][g % TILES];
-    ask |= n < P && (lane & 3) < SW && !(fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3])) < bar) ? 1u << g : 0u;
-  }
-  float t[VP];
-#pragma unroll
-  for (int j = 0; j < VP; ++j) t[j] = x.t[n][j];
-  while (__any(ask != 0u)) {
-    // the quad's first: place and tile
-    unsigned first = ask ? (unsigned)(lane & 3) << 8 | (unsigned)__builtin_ctz(ask) : 0xFFFFu;
-    first = min(first, (unsigned)__builtin_amdgcn_update_dpp(0, (int)first, 0xB1, 0xF, 0xF, false));
-    first = min(first, (unsigned)__builtin_amdgcn_update_dpp(0, (int)first, 0x4E, 0xF, 0xF, false));
-    if (first != 0xFFFFu) {
-      const int from = (int)(first >> 8), g = (int)(first & 0xFFu);
-      if (from == (lane & 3)) ask &= ask - 1u;
-      const int i = min((g / TILES * waves + wave) * 64 + (g % TILES * SW + from) * 16 + (lane >> 4) * 4 + (lane & 3), count - 1);
-      unsigned c[EH / 2];
-      read_entry<EH>(c, lds_entries + (unsigned)i * (EH * 2u));
-      float d = 0.0f;
-#pragma unroll
-      for (int j = 0; j < VP; ++j) {
-        // t - c in one operation: the product c * -1 is exact
-        const float diff = __fmaf_rn(half_of(c[j >> 1], j & 1), -1.0f, t[j]);
-        d = __fmaf_rn(diff, diff, d);
-      }
-      __hip_atomic_fetch_min(&x.nearest[par][n], (unsigned long long)__float_as_uint(d) << 32 | (unsigned)i, __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_WORKGROUP);
+    for (int q = 0; q < EH / 8; ++q) {
+      const uint4v a = *reinterpret_cast<const uint4v *>(entry + 16 * q);
+      asm volatile("" :: "v"(a.w));
+      dst[4 * q] = a.x; dst[4 * q + 1] = a.y; dst[4 * q + 2] = a.z; dst[4 * q + 3] = a.w;
     }
   }
 }
 
-template <int VP, int G, int GR, int LW>
-__global__ __launch_bounds__(LW * 64) void qcol_loop_kernel(LoopArgs a) {
+// Distance of a lane's vector to entry i, as defined; smallest first, then smallest index, of the four in a quad.
+template <int VP>
+__device__ __forceinline__ void quad_nearest(const unsigned char *entries, unsigned i, const float (&t)[VP], unsigned &d, unsigned &arg) {
   constexpr int EH = loop_entry_halfs<VP>();
+  unsigned c[EH / 2];
+  read_entry<EH>(c, entries + (size_t)i * (EH * 2u));
+  float s = 0.0f;
+#pragma unroll
+  for (int el = 0; el < VP; ++el) {
+    // t - c in one operation: the product c * -1 is exact
+    const float diff = __fmaf_rn(half_of(c[entry_place<VP>(el) >> 1], entry_place<VP>(el) & 1), -1.0f, t[el]);
+    s = __fmaf_rn(diff, diff, s);
+  }
+  const unsigned bits = __float_as_uint(s);
+  d = quad_min(bits);
+  arg = quad_min(bits == d ? i : 0xFFFFFFFFu);
+}
+
+// One search of all vectors over a wave's share of a table of `count` entries.
+template <int VP, int G>
+__device__ __forceinline__ void search_table(unsigned long long *nearest, const half8v (&A)[G][group_tiles(VP)], const unsigned char *entries, int count,
+                                             const Posted<VP> &p, const LoopTable &tb, int lane, int wave) {
+  constexpr int SW = entries_wide(VP), TILES = group_tiles(VP), EPL = quarter(VP), N = G * TILES, LEAD = N < 4 ? N : 4;
+  if (wave * 16 >= count) return;
+  const int place = lane & (SW - 1);
+  // the instructions run LEAD groups ahead of the comparisons
+  float4v acc[LEAD];
+  auto scores = [&](int g) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(A[g / TILES][g % TILES], p.B, float4v{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0); };
+  auto best_of = [&](const float4v &a) { return maximum(maximum(maximum(a[0], a[1]), a[2]), a[3]); };
+#pragma unroll
+  for (int g = 0; g < LEAD; ++g) acc[g] = scores(g);
+  __builtin_amdgcn_sched_barrier(0);
+  float t[VP], low = 0.0f;
+#pragma unroll
+  for (int el = 0; el < VP; ++el) {
+    const unsigned y = __float_as_uint(p.t[el % EPL]);
+    t[el] = __uint_as_float(el / EPL == 0 ? quad_lane<0>(y) : el / EPL == 1 ? quad_lane<1>(y) : el / EPL == 2 ? quad_lane<2>(y) : quad_lane<3>(y));
+  }
+#pragma unroll
+  for (int r = 0; r < EPL; ++r) low = __fmaf_rn(p.low[r], p.low[r], low);
+  const float eps = __fmaf_rn(tb.low_c, __builtin_amdgcn_sqrtf(quad_sum(low)),
+                              __fmaf_rn(tb.eps_up, ldexpf(1.0f, p.e), __fmaf_rn(tb.eps_down, ldexpf(1.0f, -p.e), tb.eps0)));
+  float m1 = 0.0f, m2 = -__builtin_inff();
+#pragma unroll
+  for (int g = 0; g < N; ++g) {
+    const float tagged = __uint_as_float((__float_as_uint(best_of(acc[g % LEAD])) & ~TAG) | (unsigned)(g * SW));
+    if (g + LEAD < N) acc[g % LEAD] = scores(g + LEAD);
+    if (g > 0) m2 = __builtin_amdgcn_fmed3f(m1, m2, tagged);
+    m1 = g > 0 ? maximum(m1, tagged) : tagged;
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  if constexpr (SW > 1) m1 = __uint_as_float(__float_as_uint(m1) | (unsigned)place);
+  const float best = quad_max(m1);
+  auto index = [&](unsigned at) {                            // of the quad's four, at group * SW + place
+    return min(at * (SEARCH * 16) + (wave * 16 + (lane >> 4) * 4 + (lane & 3)), (unsigned)count - 1u);
+  };
+  const unsigned tag = __float_as_uint(best);
+  unsigned d, i;
+  quad_nearest<VP>(entries, index(tag & TAG), t, d, i);
+  const float bar = rows_max(best) - eps;
+  const bool first = (lane & 3) == 0;
+  auto file = [&] {
+    __hip_atomic_fetch_min(nearest, (unsigned long long)d << 32 | i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  };
+  if (first & !(best < bar)) file();
+  bool more = p.brute | ((__float_as_uint(m1) != tag) & !(m1 < bar));
+  if constexpr (N > 1) more |= !(m2 < bar);
+  if (__builtin_expect(__builtin_amdgcn_ballot_w64(more) != 0ull, 0)) {
+    // Groups of which the four distances are wanted; the scores once more, since their registers are long in other use.
+    unsigned ask = 0u;
+#pragma unroll
+    for (int g = 0; g < N; ++g) {
+      ask |= ((lane & 3) < SW) & (p.brute | !(best_of(scores(g)) < bar)) ? 1u << g : 0u;
+      if (g % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+    }
+    while (__any(ask != 0u)) {
+      const unsigned next = quad_min(ask ? (unsigned)(lane & 3) << 8 | (unsigned)__builtin_ctz(ask) : 0xFFFFu);    // the quad's first: place and group
+      const unsigned from = next >> 8, g = next & 0xFFu;
+      const bool some = next != 0xFFFFu;
+      if (some && from == (unsigned)(lane & 3)) ask &= ask - 1u;
+      quad_nearest<VP>(entries, some ? index(g * SW + from) : 0u, t, d, i);
+      if (some && first) file();
+    }
+  }
+}
+
+template <int VP, int G, int GR>
+__global__ __launch_bounds__(LOOP_THREADS) void qcol_loop_kernel(LoopArgs a) {
+  constexpr int EH = loop_entry_halfs<VP>(), EPL = quarter(VP), POS = 32 / VP < PMAX ? 32 / VP : PMAX;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   __half *entries = reinterpret_cast<__half *>(smem);                                          // [k + k_res][EH]
   float *E = reinterpret_cast<float *>(smem + (((size_t)(a.k + a.k_res) * EH * 2 + 15) & ~(size_t)15));   // [32][E_PITCH]: row p * VP + j
   unsigned *codes = reinterpret_cast<unsigned *>(E + 32 * E_PITCH);                            // [2][PMAX][QB]
   LoopExchange &x = *reinterpret_cast<LoopExchange *>(codes + 2 * PMAX * QB);
-  constexpr int threads = LW * 64, waves = LW;
+  constexpr int threads = LOOP_THREADS;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool searching = wave < SEARCH;
   const int pos0 = blockIdx.x * a.P;
   const bool cut = pos0 >= a.whole;                                        // the workgroup of the cut-off position
   const int P = cut ? 1 : min(a.P, a.whole - pos0);
   const int first = cut ? a.whole : pos0;                                  // its first position
   const int len = cut ? a.rows - a.whole * a.v : a.v;                      // rows of a position: what its vectors are compared over
-  const int mine = wave;                                                   // an owner wave's position: the first waves also own one each
-  const bool owner = mine < P;
 
   // tables: entries in LDS (elements past `len` as zeros), operands in registers
   for (int e = tid; e < (a.k + a.k_res) * EH; e += threads) {
-    const int i = e / EH, j = e % EH;
+    const int i = e / EH, slot = e % EH;
+    const int j = VP == 12 ? (slot % 4 < 3 ? slot / 4 * 3 + slot % 4 : VP) : slot;
     const __half *src = i < a.k ? a.cb + (long long)i * a.v : a.cb_res + (long long)(i - a.k) * a.v;
     entries[e] = j < len ? src[j] : __float2half_rn(0.0f);
   }
   for (int e = tid; e < 32 * E_PITCH; e += threads) E[e] = 0.0f;
-  for (int e = tid; e < PMAX * 2 * 32 + 8; e += threads) (&x.operand[0][0][0])[e] = (_Float16)0.0f;          // (and the zeros behind them)
-  if (tid < PMAX * 20) (&x.t[0][0])[tid] = 0.0f;
-  if (tid < PMAX) x.eps[tid] = 0.0f;
-  if (tid < 2 * PMAX) { (&x.most[0][0])[tid] = -__builtin_inff(); (&x.nearest[0][0])[tid] = ~0ull; }
+  if (tid < 8 * PMAX) (&x.nearest[0][0][0])[tid] = ~0ull;
+  for (int e = tid; e < PMAX * 16 * 6; e += threads) (&x.next_w[0][0])[e] = 0.0f;              // (and e and t behind them)
   half8v A[G][group_tiles(VP)], AR[GR ? GR : 1][group_tiles(VP)];
   LoopTable main_table, res_table;
   {
@@ -297,141 +410,162 @@ __global__ __launch_bounds__(LW * 64) void qcol_loop_kernel(LoopArgs a) {
     post_norms(0, a.cb, a.k);
     if constexpr (GR) post_norms(1, a.cb_res, a.k_res);
     __syncthreads();
-    main_table = loop_table<VP>(x.h_max[0], x.c_bad[0], waves);
-    load_operands<VP, G>(a.cb, a.k, a.v, len, main_table.f, lane, wave, LW, A);
-    if constexpr (GR) {
-      res_table = loop_table<VP>(x.h_max[1], x.c_bad[1], waves);
-      load_operands<VP, GR>(a.cb_res, a.k_res, a.v, len, res_table.f, lane, wave, LW, AR);
+    main_table = loop_table<VP>(x.h_max[0], x.c_bad[0]);
+    if constexpr (GR) res_table = loop_table<VP>(x.h_max[1], x.c_bad[1]);
+    if (searching) {
+      load_operands<VP, G>(a.cb, a.k, a.v, len, main_table.f, lane, wave, A);
+      if constexpr (GR) load_operands<VP, GR>(a.cb_res, a.k_res, a.v, len, res_table.f, lane, wave, AR);
     }
   }
   const __half *entries_res = entries + (size_t)a.k * EH;
-  const unsigned lds_entries = (unsigned)reinterpret_cast<size_t>((const __attribute__((address_space(3))) void *)smem);
-  const int m0 = (first + mine) * a.v;                                     // the owner's first row
-  int par = 0;
 
   for (int s = 0; s < a.cols; s += a.block) {
     const int s_end = min(s + a.block, a.cols), nb = s_end - s;
-    {
-      // the owner's tile: lane l holds columns l and l + 64
-      float w[CPL][VP];
-      float t = 0.0f, e = 0.0f, next_w = 0.0f;                             // lane j: element j
-      // Rows of H^-1 inside the block pass through LDS, HB of them at a time: each wave holds RW of them on their way (the owners'
-      // waves come last), from one eighth column to the middle of the next
-      constexpr int RW = (HB + LW - 1) / LW;
-      const int loader = waves - 1 - wave;
-      float on_way[RW][CPL];
-      auto fetch = [&](int n0) {
+    if (searching) {
+      // (lanes of vectors past the last repeat the first)
+      const int n = ((lane >> 2) & 3) < P ? (lane >> 2) & 3 : 0, j = lane & 3;
+      const LaneMasks in = lane_masks<VP>(lane);
+      float t[EPL], e_last[EPL];
 #pragma unroll
-        for (int q = 0; q < RW; ++q)
-#pragma unroll
-          for (int i = 0; i < CPL; ++i) {
-            const int nn = n0 + loader + q * waves, c = s + lane + 64 * i;
-            on_way[q][i] = loader + q * waves < HB && nn < nb && c < s_end ? a.Hinv[(long long)(s + nn) * a.ldh + c] : 0.0f;
-          }
-      };
-      auto land = [&](int n0) {
-#pragma unroll
-        for (int q = 0; q < RW; ++q)
-          if (loader + q * waves < HB) {
-#pragma unroll
-            for (int i = 0; i < CPL; ++i) x.hinv[(n0 + loader + q * waves) & (2 * HB - 1)][lane + 64 * i] = on_way[q][i];
-          }
-      };
-      // element j of column nn of the tile, in lane j
-      auto column = [&](int nn) -> float {
-        const int src = nn & 63;
-        float r = 0.0f;
-#pragma unroll
-        for (int j = 0; j < VP; ++j) {
-          const float y = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(nn >> 6 ? w[1][j] : w[0][j]), src));
-          r = lane == j ? y : r;
-        }
-        return r;
-      };
-      auto take = [&](int count) -> unsigned { return min((unsigned)(x.nearest[par][mine] & 0xFFFFFFFFull), (unsigned)count - 1u); };
-      auto ready = [&] {                                    // the search's slots, for the one after next
-        if (lane == 0) { x.most[par][mine] = -__builtin_inff(); x.nearest[par][mine] = ~0ull; }
-      };
-      auto element = [&](const __half *table, unsigned i) -> float {      // of an entry, in the lane of that number
-        const float y = __half2float(table[(size_t)i * EH + (lane & (EH - 1))]);
-        return lane < EH ? y : 0.0f;
-      };
-      fetch(0);
-      if (owner) {
-        int lane_s = lane;
-        asm volatile("" : "+v"(lane_s));                    // (see the end of the block)
-#pragma unroll
-        for (int i = 0; i < CPL; ++i) {
-          const int c = s + lane_s + 64 * i;
-#pragma unroll
-          for (int j = 0; j < VP; ++j) w[i][j] = c < s_end && j < len ? a.W[(long long)(m0 + j) * a.ldw + c] : 0.0f;
-        }
-        t = column(0);
-        post_vector<VP>(x, mine, t, main_table, lane);
+      for (int r = 0; r < EPL; ++r) {
+        t[r] = EPL * j + r < len ? a.W[(long long)((first + n) * a.v + EPL * j + r) * a.ldw + s] : 0.0f;
+        e_last[r] = 0.0f;
       }
-      land(0);
+      // an entry's elements, in the lanes that hold them of the vector that took it
+      auto elements = [&](const __half *table, unsigned i, float (&q)[EPL]) {
+        unsigned at = i * EH + (EPL == 2 ? 2 * j : 4 * j);
+        if constexpr (VP == 4) at = i * EH + 2 * (j & 1);
+        const uint2v y = EPL == 2 ? uint2v{*reinterpret_cast<const unsigned *>(table + at), 0u} : *reinterpret_cast<const uint2v *>(table + at);
+#pragma unroll
+        for (int r = 0; r < EPL; ++r) {
+          q[r] = half_of(r < 2 ? y.x : y.y, r & 1);
+          if constexpr (VP == 4) q[r] = j < 2 ? q[r] : 0.0f;
+        }
+      };
+      const int own = n * 16 + j * 4;                        // lane layout
       for (int nn = 0; nn < nb; ++nn) {
-        float diag = 1.0f, beside = 0.0f;
+        Posted<VP> p = post_vectors<VP>(t, main_table, in, lane);
+        bool huge = p.brute;
+        search_table<VP, G>(&x.nearest[0][nn & 3][n], A, smem, a.k, p, main_table, lane, wave);
         lds_barrier();
-        if ((nn & (HB - 1)) == 0) fetch(nn + HB);
-        search_table<VP, G>(x, A, lds_entries, a.k, P, par, lane, wave, waves);
-        if ((nn & (HB - 1)) == HB / 2) land(nn + HB / 2);
-        if (owner) {
-          // the last column's error reaches the tile (columns that are done may hold anything), then the next column's elements
-          // are fetched from it: only this column's error is still missing from them
-          if (nn > 0) {
-            const float *before = x.hinv[(nn - 1) & (2 * HB - 1)];
-            float h[CPL];
+        const ColumnConstants at = x.column[nn];
+        float next[EPL], q[EPL], e[EPL];
+        elements(entries, (unsigned)x.nearest[0][nn & 3][n], q);
 #pragma unroll
-            for (int i = 0; i < CPL; ++i) h[i] = before[lane + 64 * i];
-#pragma unroll
-            for (int j = 0; j < VP; ++j) {
-              const float ej = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(e), j));
-#pragma unroll
-              for (int i = 0; i < CPL; ++i) w[i][j] = __fmaf_rn(-ej, h[i], w[i][j]);
-            }
-          }
-          next_w = column(min(nn + 1, QB - 1));
-          diag = x.hinv[nn & (2 * HB - 1)][nn];
-          beside = x.hinv[nn & (2 * HB - 1)][min(nn + 1, QB - 1)];
-        }
-        lds_barrier();
-        float q = 0.0f;
-        unsigned code = 0u, code_res = 0u;
-        if (owner) {
-          code = take(a.k);
-          q = element(entries, code);
-        }
+        for (int r = 0; r < EPL; ++r) next[r] = x.next_w[nn & 1][own + r];
         if constexpr (GR) {
-          if (owner) { post_vector<VP>(x, mine, __fsub_rn(t, q), res_table, lane); ready(); }
-          par ^= 1;
+          float rest[EPL], more[EPL];
+#pragma unroll
+          for (int r = 0; r < EPL; ++r) rest[r] = __fsub_rn(t[r], q[r]);
+          p = post_vectors<VP>(rest, res_table, in, lane);
+          huge |= p.brute;
+          search_table<VP, GR>(&x.nearest[1][nn & 3][n], AR, smem + (size_t)a.k * EH * 2, a.k_res, p, res_table, lane, wave);
           lds_barrier();
-          search_table<VP, GR>(x, AR, lds_entries + (unsigned)a.k * (EH * 2u), a.k_res, P, par, lane, wave, waves);
-          lds_barrier();
-          if (owner) {
-            code_res = take(a.k_res);
+          elements(entries_res, (unsigned)x.nearest[1][nn & 3][n], more);
+#pragma unroll
+          for (int r = 0; r < EPL; ++r) {
             // what inference restores: the binary32 sum of the two centroids, rounded to binary16 (Sec. 3.2.2)
-            float sum = __fadd_rn(q, element(entries_res, code_res));
+            float sum = __fadd_rn(q[r], more[r]);
             asm volatile("" : "+v"(sum));
-            q = __half2float(__float2half_rn(sum));
+            q[r] = __half2float(__float2half_rn(sum));
           }
         }
-        if (owner) {
-          const float done = t;
-          e = __fdiv_rn(__fsub_rn(t, q), diag);              // (0 in the lanes past the vector's elements)
-          t = __fmaf_rn(-e, beside, next_w);
-          if (nn + 1 < nb) post_vector<VP>(x, mine, t, main_table, lane);
-          ready();
-          if (lane < len) {
-            E[(mine * VP + lane) * E_PITCH + nn] = e;
-            if (a.T) a.T[(long long)(m0 + lane) * a.ldt + s + nn] = done;
-          }
-          if (lane == 0) { codes[mine * QB + nn] = code; codes[(PMAX + mine) * QB + nn] = code_res; }
+        // e = (t - q) / diag.  With the correctly rounded reciprocal, one correction of the rounded product gives the correctly rounded
+        // quotient (Markstein, IBM J. Res. Dev. 34, 1990), where nothing overflows: not for numbers out of the ordinary.
+#pragma unroll
+        for (int r = 0; r < EPL; ++r) {
+          const float diff = __fsub_rn(t[r], q[r]), about = __fmul_rn(diff, at.inverse);
+          e[r] = __fmaf_rn(__fmaf_rn(-about, at.diag, diff), at.inverse, about);
         }
-        par ^= 1;
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(huge | (at.inverse == 0.0f)) != 0ull, 0)) {
+#pragma unroll
+          for (int r = 0; r < EPL; ++r) e[r] = __fdiv_rn(__fsub_rn(t[r], q[r]), at.diag);
+        }
+        // (every wave writes the same)
+#pragma unroll
+        for (int r = 0; r < EPL; ++r) { x.e[nn & 1][own + r] = e[r]; x.t[nn & 1][own + r] = t[r]; }
+#pragma unroll
+        for (int r = 0; r < EPL; ++r) {
+          t[r] = __fmaf_rn(-e[r], at.beside, __fmaf_rn(-e_last[r], at.beside2, next[r]));
+          e_last[r] = e[r];
+        }
       }
+    } else {
+      // Keeping waves: thread c, and c + 128, hold column c of every other position's rows.
+      const int c = (tid - SEARCH * 64) & (QB - 1);
+      const int odd = __builtin_amdgcn_readfirstlane((tid - SEARCH * 64) / QB);
+      float w[(POS + 1) / 2][VP];
+#pragma unroll
+      for (int h = 0; h < (POS + 1) / 2; ++h)
+#pragma unroll
+        for (int el = 0; el < VP; ++el)
+          w[h][el] = c < nb && 2 * h + odd < P && el < len ? a.W[(long long)((first + 2 * h + odd) * a.v + el) * a.ldw + s + c] : 0.0f;
+      auto hinv = [&](int row, int col) -> float { return row >= 0 && row < nb && col < nb ? a.Hinv[(long long)(s + row) * a.ldh + s + col] : 0.0f; };
+      if (odd == 0 && c < nb) {
+        ColumnConstants at;
+        at.diag = hinv(c, c);
+        const float size = fabsf(at.diag);
+        at.inverse = size > 0x1p-40f && size < 0x1p40f ? __fdiv_rn(1.0f, at.diag) : 0.0f;
+        at.beside = hinv(c, c + 1);
+        at.beside2 = hinv(c - 1, c + 1);
+        x.column[c] = at;
+      }
+      // what a finished column leaves: E, T and the indices
+      const int i = tid - SEARCH * 64;                       // lane layout
+      const int ip = i >> 4, iel = EPL * (i >> 2 & 3) + (i & 3);
+      const bool files = i < PMAX * 16 && ip < P && (i & 3) < EPL && iel < len;
+      auto file = [&](int nn) {
+        if (files) {
+          E[(ip * VP + iel) * E_PITCH + nn] = x.e[nn & 1][i];
+          if (a.T) a.T[(long long)((first + ip) * a.v + iel) * a.ldt + s + nn] = x.t[nn & 1][i];
+        }
+        if (i < (GR ? 2 : 1) * PMAX) codes[i * QB + nn] = min((unsigned)x.nearest[i / PMAX][nn & 3][i % PMAX], (unsigned)(i / PMAX ? a.k_res : a.k) - 1u);
+      };
+      constexpr int RING = 8;
+      float row[RING], ahead[RING];
+#pragma unroll
+      for (int u = 0; u < RING; ++u) row[u] = hinv(u - 2, c);
+      for (int n0 = 0; n0 < nb; n0 += RING) {
+#pragma unroll
+        for (int u = 0; u < RING; ++u) ahead[u] = hinv(n0 + RING + u - 2, c);
+#pragma unroll
+        for (int u = 0; u < RING; ++u) {
+          const int nn = n0 + u;
+          if (nn >= nb) break;
+          if (nn >= 2) {
+#pragma unroll
+            for (int h = 0; h < (POS + 1) / 2; ++h)
+#pragma unroll
+              for (int el = 0; el < VP; ++el)
+                w[h][el] = __fmaf_rn(-x.e[nn & 1][(2 * h + odd) % PMAX * 16 + el / EPL * 4 + el % EPL], row[u], w[h][el]);
+            file(nn - 2);
+          }
+          if (c == nn + 1)
+#pragma unroll
+            for (int h = 0; h < (POS + 1) / 2; ++h)
+#pragma unroll
+              for (int el = 0; el < VP; ++el) x.next_w[nn & 1][(2 * h + odd) % PMAX * 16 + el / EPL * 4 + el % EPL] = w[h][el];
+          if (i < 2 * PMAX) x.nearest[i / PMAX][(nn + 1) & 3][i % PMAX] = ~0ull;
+          lds_barrier();
+          if constexpr (GR) lds_barrier();
+        }
+#pragma unroll
+        for (int u = 0; u < RING; ++u) row[u] = ahead[u];
+      }
+      if (nb > 1) file(nb - 2);
     }
     __syncthreads();
+    if (tid >= SEARCH * 64) {                                // (the last column)
+      const int i = tid - SEARCH * 64, nn = nb - 1;
+      const int ip = i >> 4, iel = EPL * (i >> 2 & 3) + (i & 3);
+      if (i < PMAX * 16 && ip < P && (i & 3) < EPL && iel < len) {
+        E[(ip * VP + iel) * E_PITCH + nn] = x.e[nn & 1][i];
+        if (a.T) a.T[(long long)((first + ip) * a.v + iel) * a.ldt + s + nn] = x.t[nn & 1][i];
+      }
+      if (i < (GR ? 2 : 1) * PMAX) codes[i * QB + nn] = min((unsigned)x.nearest[i / PMAX][nn & 3][i % PMAX], (unsigned)(i / PMAX ? a.k_res : a.k) - 1u);
+    }
+    __syncthreads();
+    if (tid < 8 * PMAX) (&x.nearest[0][0][0])[tid] = ~0ull;  // (the next block's columns count from 0 again)
 
     // (what follows computes its addresses from copies of the thread's numbers that the compiler cannot see through: hoisted out
     // of the block loop they would take the registers that the columns need)
@@ -442,9 +576,9 @@ __global__ __launch_bounds__(LW * 64) void qcol_loop_kernel(LoopArgs a) {
     for (int i = tid_e; i < P * VP * QB; i += threads) {
       const int c = i & (QB - 1), r = i / QB, p = r / VP, j = r - p * VP;
       if (c >= nb || j >= len) continue;
-      float q = __half2float(entries[(size_t)codes[p * QB + c] * EH + j]);
+      float q = __half2float(entries[(size_t)codes[p * QB + c] * EH + entry_place<VP>(j)]);
       if constexpr (GR) {
-        float sum = __fadd_rn(q, __half2float(entries_res[(size_t)codes[(PMAX + p) * QB + c] * EH + j]));
+        float sum = __fadd_rn(q, __half2float(entries_res[(size_t)codes[(PMAX + p) * QB + c] * EH + entry_place<VP>(j)]));
         asm volatile("" : "+v"(sum));
         q = __half2float(__float2half_rn(sum));
       }
@@ -462,60 +596,75 @@ __global__ __launch_bounds__(LW * 64) void qcol_loop_kernel(LoopArgs a) {
       atomicOr(row, code << sh);
       if (sh + bits > 32) atomicOr(row + 1, code >> (32u - sh));
     }
-    // W[:, later] -= E * Hinv[block, later], a tile of 32 columns per wave (lane l gives A[l & 31][l >> 5] and B[l >> 5][l & 31]; it
-    // gets back column l & 31 and, in register r, row 8 (r >> 2) + 4 (l >> 5) + (r & 3))
-    const int kmax = (nb + 1) & ~1, pitch = (int)a.ldh * 4;
-    const auto rows_of_block = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.Hinv + (long long)s * a.ldh), 0, (kmax * pitch), 0x00020000);
-    for (int c0 = s_end + wave * 32; c0 < a.cols; c0 += waves * 32) {
-      const int c = c0 + (lane_e & 31);
-      const bool in = c < a.cols;
-      const int off = (int)(((lane_e >> 5) * a.ldh + (in ? c : a.cols - 1)) * 4);
-      const float *row_e = E + (lane_e & 31) * E_PITCH + (lane_e >> 5);
-      float16v acc;
+    // W[:, later] -= E * Hinv[block, later], 64 columns a wave: row 4 b + i of E in lane 4 b + i of operand A, of which an instruction takes
+    // block b; row k of H^-1 in operand B, a column to a lane; the lane gets back rows 4 b .. 4 b + 3 of its column.
+    const int pitch = (int)a.ldh * 4;
+    const auto rows_of_block = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.Hinv + (long long)s * a.ldh), 0, nb * pitch, 0x00020000);
+    auto later = [&](auto positions) {
+      constexpr int NP = decltype(positions)::value, RG = (NP * VP + 3) / 4;
+      constexpr int UN = 16;                                 // rows on their way at once, and as many in use
+      const float *row_e = E + (lane_e & 31) * E_PITCH;
+      for (int c0 = s_end + wave * 64; c0 < a.cols; c0 += SEARCH * 64 + KEEP * 64) {
+        const int c = c0 + lane_e;
+        const bool in = c < a.cols;
+        const int off = (in ? c : a.cols - 1) * 4;
+        constexpr bool EARLY = G * group_tiles(VP) <= 16;    // (else the tables leave no registers for it)
+        float w[NP * VP];
+        auto weights = [&] {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-      constexpr int UN = LW == 4 ? 16 : 8;                   // pairs of rows on their way at once, and as many in use
-      float hv[UN];
-      // (past the block E has zeros, which add nothing to any row of the matrix)
-      auto rows = [&](int k0, float (&y)[UN]) {
+          for (int r = 0; r < NP * VP; ++r) w[r] = in && r % VP < len ? a.W[(long long)((first + r / VP) * a.v + r % VP) * a.ldw + c] : 0.0f;
+        };
+        if constexpr (EARLY) weights();
+        float4v acc[RG];
 #pragma unroll
-        for (int u = 0; u < UN; ++u)
-          y[u] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rows_of_block, off, min(k0 + 2 * u, kmax - 2) * pitch, 0));
-      };
-      rows(0, hv);
-      for (int k0 = 0; k0 < kmax; k0 += 2 * UN) {
-        float ahead[UN], ev[UN];
-        rows(k0 + 2 * UN, ahead);
+        for (int g = 0; g < RG; ++g) acc[g] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
+        float hv[UN];
+        // (past the block E has zeros, which add nothing)
+        auto rows = [&](int k0, float (&y)[UN]) {
 #pragma unroll
-        for (int u = 0; u < UN; ++u) ev[u] = row_e[k0 + 2 * u];
+          for (int u = 0; u < UN; ++u)
+            y[u] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rows_of_block, off, min(k0 + u, nb - 1) * pitch, 0));
+        };
+        rows(0, hv);
+        for (int k0 = 0; k0 < nb; k0 += UN) {
+          float ahead[UN], ev[UN];
+          rows(k0 + UN, ahead);
 #pragma unroll
-        for (int u = 0; u < UN; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(ev[u], hv[u], acc, 0, 0, 0);
+          for (int u = 0; u < UN; ++u) ev[u] = row_e[k0 + u];
 #pragma unroll
-        for (int u = 0; u < UN; ++u) hv[u] = ahead[u];
+          for (int u = 0; u < UN; ++u) {
+#define VQ_ROWS(B) if constexpr (B < RG) acc[B < RG ? B : 0] = __builtin_amdgcn_mfma_f32_4x4x1f32(ev[u], hv[u], acc[B < RG ? B : 0], 4, B, 0);
+            VQ_ROWS(0) VQ_ROWS(1) VQ_ROWS(2) VQ_ROWS(3) VQ_ROWS(4) VQ_ROWS(5) VQ_ROWS(6) VQ_ROWS(7)
+#undef VQ_ROWS
+          }
+#pragma unroll
+          for (int u = 0; u < UN; ++u) hv[u] = ahead[u];
+        }
+        if constexpr (!EARLY) weights();
+#pragma unroll
+        for (int r = 0; r < NP * VP; ++r)
+          if (in && r % VP < len) a.W[(long long)((first + r / VP) * a.v + r % VP) * a.ldw + c] = w[r] - acc[r / 4][r % 4];
       }
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        if (r % 4 == 0) __builtin_amdgcn_sched_barrier(0);   // (four rows' addresses and values in registers at a time)
-        const int row = 8 * (r >> 2) + 4 * (lane_e >> 5) + (r & 3), p = row / VP, j = row - p * VP;
-        if (in && p < P && j < len) a.W[(long long)((first + p) * a.v + j) * a.ldw + c] -= acc[r];
-      }
-    }
+    };
+    if (P == 1) later(std::integral_constant<int, 1>{});
+    if constexpr (POS >= 2) { if (P == 2) later(std::integral_constant<int, 2>{}); }
+    if constexpr (POS >= 3) { if (P == 3) later(std::integral_constant<int, 3>{}); }
+    if constexpr (POS >= 4) { if (P == 4) later(std::integral_constant<int, 4>{}); }
     __syncthreads();
   }
 }
 
-template <int VP, int G, int GR, int LW>
+template <int VP, int G, int GR>
 int launch_loop(LoopArgs a, hipStream_t st) {
-  auto kernel = qcol_loop_kernel<VP, G, GR, LW>;
+  auto kernel = qcol_loop_kernel<VP, G, GR>;
   VQ_ALLOW_FULL_LDS(kernel);
   const int cut = a.rows - a.whole * a.v > 0;
   const unsigned grid = (unsigned)((a.whole + a.P - 1) / a.P + cut);
-  hipLaunchKernelGGL(kernel, dim3(grid), dim3(LW * 64), loop_lds_bytes<VP>(a.k, a.k_res), st, a);
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(LOOP_THREADS), loop_lds_bytes<VP>(a.k, a.k_res), st, a);
   return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
 }
 
-// Groups of 64 centroids a wave holds: one of each table with up to 256 entries (four waves); with sixteen waves one up to 1024
-// entries and four up to 4096.
+// Groups of 64 centroids a search wave holds of each table: one up to 256 entries, four up to 1024, sixteen up to 4096.
 template <int VP>
 int launch_loop_vp(LoopArgs a, hipStream_t st) {
   if (loop_lds_bytes<VP>(a.k, a.k_res) > 160 * 1024 || a.ldh > (1 << 21)) return VQ_ERR_UNSUPPORTED;    // (a block of H^-1: 32-bit offsets)
@@ -524,15 +673,15 @@ int launch_loop_vp(LoopArgs a, hipStream_t st) {
   a.P = min(min(PMAX, 32 / VP), max(1, (a.whole + cu_count() - 2) / (cu_count() - 1)));
   const int big = max(a.k, a.k_res);
   if (a.k_res == 0) {
-    if (big <= 256) return launch_loop<VP, 1, 0, 4>(a, st);
-    if (big <= 1024) return launch_loop<VP, 1, 0, 16>(a, st);
-    if constexpr (VP <= 14) { if (big <= 4096) return launch_loop<VP, 4, 0, 16>(a, st); }
+    if (big <= 256) return launch_loop<VP, 1, 0>(a, st);
+    if (big <= 1024) return launch_loop<VP, 4, 0>(a, st);
+    if constexpr (VP <= 14) { if (big <= 4096) return launch_loop<VP, 16, 0>(a, st); }
   } else {
-    if (big <= 256) return launch_loop<VP, 1, 1, 4>(a, st);
-    if (big <= 1024) return launch_loop<VP, 1, 1, 16>(a, st);
+    if (big <= 256) return launch_loop<VP, 1, 1>(a, st);
+    if (big <= 1024) return launch_loop<VP, 4, 4>(a, st);
     // (longer vectors would not leave registers for the rest)
-    if constexpr (VP <= 14) { if (big <= 4096 && a.k_res <= 1024) return launch_loop<VP, 4, 1, 16>(a, st); }
-    if constexpr (VP <= 6) { if (big <= 4096) return launch_loop<VP, 4, 4, 16>(a, st); }
+    if constexpr (VP <= 14) { if (big <= 4096 && a.k_res <= 1024) return launch_loop<VP, 16, 4>(a, st); }
+    if constexpr (VP <= 6) { if (big <= 4096) return launch_loop<VP, 16, 16>(a, st); }
   }
   return VQ_ERR_UNSUPPORTED;
 }

@@ -113,6 +113,52 @@ def test_quantize_columns_is_valid_both_ways(gpu_lib, name):
           % (name, (idx == own["idx"]).mean(), np.abs(replay["T"] - Tg).max() / rms, ratio))
 
 
+# Sizes and numbers at which the one-launch loop takes other paths: three and four positions a workgroup, sixteen groups of wide entries beside a
+# residual table, weights so large that they do not scale into binary16 (every distance is computed), a diagonal whose
+# reciprocal is not used.  Bounds: as above; with weights 2^24 times larger than the centroids all distances agree to 2^-23 or so, and
+# EPS covers that.
+PATHS = {
+    "v6_three_positions": dict(M=3100, N=21, v=6, k=300, k_res=0, B=16),
+    "v7_k1500_res900": dict(M=45, N=50, v=7, k=1500, k_res=900, B=33),
+    "v12_k3000_two_positions": dict(M=3090, N=18, v=12, k=3000, k_res=0, B=16),
+    "weights_out_of_scale": dict(M=40, N=40, v=6, k=256, k_res=16, B=32, w_scale=2.0 ** 24),
+    "diagonal_out_of_range": dict(M=40, N=40, v=6, k=256, k_res=0, B=32, h_scale=2.0 ** -100),
+}
+
+
+@pytest.mark.parametrize("name", list(PATHS))
+def test_quantize_columns_paths(gpu_lib, name):
+    import torch
+    case = PATHS[name]
+    M, N, v, k, k_res, B = (case[n] for n in ("M", "N", "v", "k", "k_res", "B"))
+    seed = 80 + list(PATHS).index(name)
+    W0 = (s.make_weights(600 + seed, M, N).astype(np.float32) * case.get("w_scale", 1.0)).astype(np.float32)
+    H = s.make_hessian(600 + seed, N) * case.get("h_scale", 1.0)
+    U = np.ascontiguousarray(np.linalg.cholesky(np.linalg.inv(H)).T, dtype=np.float32)
+    C, R = _tables(seed, k, v, k_res)
+    Wd = torch.from_numpy(W0).cuda()
+    idx_b, idx_res_b, T = gpu_lib.quantize_columns(Wd, torch.from_numpy(U).cuda(), torch.from_numpy(C).cuda(),
+                                                   torch.from_numpy(R).cuda() if k_res else None, block=B)
+    torch.cuda.synchronize()
+    idx = _unpack(idx_b.cpu().numpy(), oracle.index_bits(k), N)
+    idx_res = _unpack(idx_res_b.cpu().numpy(), oracle.index_bits(k_res), N) if k_res else None
+    Tg = T.cpu().numpy().astype(np.float64)
+    Cd = C.astype(np.float64)
+    for p, rows in _vector_rows(M, v):
+        ln = rows.stop - rows.start
+        t = Tg[rows].T
+        d = ((t[:, None, :] - Cd[None, :, :ln]) ** 2).sum(2)
+        assert (d[np.arange(N), idx[p]] <= d.min(1) * (1 + EPS) + 1e-14).all(), (name, p)
+        if k_res:
+            r = (t.astype(np.float32) - Cd[idx[p], :ln].astype(np.float32)).astype(np.float64)
+            dr = ((r[:, None, :] - R.astype(np.float64)[None, :, :ln]) ** 2).sum(2)
+            assert (dr[np.arange(N), idx_res[p]] <= dr.min(1) * (1 + EPS) + 1e-14).all(), (name, p)
+    replay = oracle.quantize_columns(W0.astype(np.float64), U, C, R, block=B, given=(idx, idx_res))
+    rms = np.sqrt((W0.astype(np.float64) ** 2).mean())
+    assert np.abs(replay["T"] - Tg).max() <= TOL_T * rms, (name, np.abs(replay["T"] - Tg).max() / rms)
+    assert np.array_equal(replay["What"], Wd.cpu().numpy().astype(np.float64))
+
+
 def test_quantize_columns_restores_through_the_layer_path(gpu_lib):
     """The streams it writes are a layer of orientation 1: vq_dequant restores exactly the quantized weights it returned."""
     import torch
