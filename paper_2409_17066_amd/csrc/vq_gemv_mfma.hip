@@ -10,7 +10,7 @@
 // instead of 3 * batch dot-product operations, and the sum over a wave's lanes happens inside the MFMA:
 // the kernel runs at the LDS gather rate for every batch up to 16.
 //
-// Work split: a workgroup owns a block of rows (a multiple of 16) and walks them in chunks of up to four
+// Work split: a workgroup owns a block of rows (a multiple of 16) and walks them in chunks of up to six
 // 16-row blocks; within a chunk it makes passes over the columns: in pass p wave w covers vectors
 // [(p * MW + w) * 32, +32), eight per lane, whose 96 index bits are exactly three aligned dwords.  The
 // activations of a pass sit in registers (B operands) and are reused by every block of the chunk; index
@@ -30,13 +30,14 @@ namespace {
 
 using namespace v6;
 
-constexpr int NBMAX = 4;         // 16-row blocks per chunk
+constexpr int NBMAX = 6;         // 16-row blocks per chunk
 constexpr int VPL = 8;           // vectors per lane per pass: 8 x 12 bits = 3 dwords, 8 x 8 bits = 2 dwords
 
 struct MfmaPlan {
   int rows_per_wg;               // multiple of 16
   int nb;                        // blocks per chunk, 1 .. NBMAX
-  int part_bufs;                 // 1: barrier after the reduction as well; 2: chunks alternate buffers
+  int part_bufs;                 // 1: barrier after the reduction as well; 2: chunks alternate buffers; 0: there is one chunk, and its partials
+                                 // lie over the tables, which a barrier has found to be done with
   unsigned lds_out, lds_part, lds_xs;
   unsigned x_bytes;              // bytes from x[0][0] to the end of the last batch row
   int y_wide;                    // y rows allow 8-byte stores
@@ -73,14 +74,12 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
   typedef Layout<RES_BITS> LY;
   constexpr int RB = RES_BITS ? RES_BITS : 8;
   constexpr int PA = NB == 2 ? 4 : 2;                   // passes whose index words are in flight or in registers
-  constexpr int XD = 1, XS = XD + 1;                    // activations run XD passes ahead, in XS register sets
-  static_assert(PA % XS == 0, "the unrolled pass loop must map passes to activation sets statically");
+  constexpr int XL = 6;                                 // loads of a pass's activations, which run one pass ahead
   constexpr int R = PA * NB;                            // ring of index-word slots: slot (j, b) = j * NB + b
   constexpr int S = RES_BITS ? 2 : 1;                   // loads per slot
   // loads issued after a slot's own by the time the slot is used, while the ring is being refilled: the other
-  // R - 1 slots and PA groups of eight activation loads; after a pass's activation loads: XD passes of refills
-  // and the activation loads of the passes in between
-  constexpr int AFTER_SLOT = (R - 1) * S + 8 * PA, AFTER_X = XD * NB * S + (XD - 1) * 8;
+  // R - 1 slots and PA groups of activation loads; after a pass's activation loads: one pass of refills
+  constexpr int AFTER_SLOT = (R - 1) * S + XL * PA, AFTER_X = NB * S;
   static_assert(AFTER_SLOT < 64, "vmcnt holds 6 bits");
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   const int lane = threadIdx.x & 63;
@@ -110,7 +109,7 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
 
   uint3v win[R], wres[RES_BITS == 12 ? R : 1];   // index words, PA passes deep
   uint2v wres8[RES_BITS == 8 ? R : 1];
-  uint4v bxs[XS][VPL];                           // B operands (activations) of the current and of the next XD passes
+  uint4v xq[XL], bx[VPL];                        // activations of the next pass as loaded; B operands of the current one
 #pragma unroll
   for (int i = 0; i < R; ++i) {
     win[i] = uint3v{0u, 0u, 0u};
@@ -118,9 +117,9 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
     if (RES_BITS == 8) wres8[i] = uint2v{0u, 0u};
   }
 #pragma unroll
-  for (int i = 0; i < XS; ++i)
+  for (int i = 0; i < XL; ++i) xq[i] = uint4v{0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int u = 0; u < VPL; ++u) bxs[i][u] = uint4v{0u, 0u, 0u, 0u};
+  for (int u = 0; u < VPL; ++u) bx[u] = uint4v{0u, 0u, 0u, 0u};
 
   const uint4v ones = {0x3C003C00u, 0x3C003C00u, 0x3C003C00u, 0u};
   float4v acc[NB];
@@ -185,14 +184,15 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
     if (RES_BITS == 12) async_load_b96(wres[slot], r_res, o_res);
     if (RES_BITS == 8) async_load_b64(wres8[slot], r_res, o_res);
   };
-  // activations of one pass: eight overlapping 16-byte loads, one per vector; the fourth dword belongs to the
-  // next vector and meets the zero padding of the codebook entries
-  auto issue_x = [&](uint4v (&bx)[VPL], int pass) {
+  // Activations of one pass: a lane's 96 bytes in six loads, moved to the operands when they are there.  Every lane of such a load is an
+  // access of its own to L1 (sixteen rows), one a clock, and these are most of the kernel's time at 16 rows: with eight overlapping loads
+  // straight into the operands and at most three blocks a chunk, 16 rows of a 7B-shaped decoder layer took 90.3 us, now 78.7
+  // (the 18 moves a pass are nothing).
+  auto issue_x = [&](int pass) {
     const unsigned off = token_on ? xrow + ((unsigned)col_lo + (unsigned)((pass * MW + wl) * 4 + g) * (VPL * 6u)) * 2u : xrow;
-    async_load_b128_at<0>(bx[0], r_xa, off);  async_load_b128_at<12>(bx[1], r_xa, off);
-    async_load_b128_at<24>(bx[2], r_xa, off); async_load_b128_at<36>(bx[3], r_xa, off);
-    async_load_b128_at<48>(bx[4], r_xa, off); async_load_b128_at<60>(bx[5], r_xa, off);
-    async_load_b128_at<72>(bx[6], r_xa, off); async_load_b128_at<84>(bx[7], r_xa, off);
+    async_load_b128_at<0>(xq[0], r_xa, off);  async_load_b128_at<16>(xq[1], r_xa, off);
+    async_load_b128_at<32>(xq[2], r_xa, off); async_load_b128_at<48>(xq[3], r_xa, off);
+    async_load_b128_at<64>(xq[4], r_xa, off); async_load_b128_at<80>(xq[5], r_xa, off);
   };
 
   {
@@ -208,9 +208,8 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
       for (int b = 0; b < NB; ++b) load_slot(j * NB + b, b);
       advance_loader();
     }
-#pragma unroll
-    for (int d = 0; d < XD; ++d) issue_x(bxs[d], d % eff_passes);
-    wait_vmem_at_most<R * S + 8 * XD>();         // the tables are in; the index words may still be on their way
+    issue_x(0);
+    wait_vmem_at_most<R * S + XL>();             // the tables are in; the index words may still be on their way
     tables.store(p, lds, plan.lds_out, grp == 0 && !plan.out_global, tid);
   }
   // scale and bias of the workgroup's rows, one dword per row, for the reductions at the chunk ends
@@ -291,10 +290,18 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
           // ---- one pass over this wave's 32 vectors of every block of the chunk
           // Every pass issues the same number of loads, also past the end of the sequence (the loader then starts
           // over), so the counted waits hold throughout.
-          uint4v (&bx)[VPL] = bxs[j % XS];
           wait_vmem_at_most<AFTER_X>();
 #pragma unroll
-          for (int u = 0; u < VPL; ++u) settle(bx[u]);
+          for (int i = 0; i < XL; ++i) settle(xq[i]);
+          {
+            const unsigned xd[XL * 4] = {xq[0].x, xq[0].y, xq[0].z, xq[0].w, xq[1].x, xq[1].y, xq[1].z, xq[1].w, xq[2].x, xq[2].y, xq[2].z, xq[2].w,
+                                         xq[3].x, xq[3].y, xq[3].z, xq[3].w, xq[4].x, xq[4].y, xq[4].z, xq[4].w, xq[5].x, xq[5].y, xq[5].z, xq[5].w};
+#pragma unroll
+            for (int u = 0; u < VPL; ++u) {        // (the fourth dword meets the zero padding of the codebook entries)
+              bx[u] = uint4v{xd[3 * u], xd[3 * u + 1], xd[3 * u + 2], 0u};
+              settle(bx[u]);
+            }
+          }
           if (pass > last_clean_pass) {          // the group that holds the end of the row: zero what lies past it
             const int col = col_lo + ((pass * MW + wv) * 4 + g) * (VPL * 6);
 #pragma unroll
@@ -311,7 +318,7 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
             for (int u = 0; u < VPL; ++u) xs = mfma16(ones, bx[u], xs);
             if (g == 0) xs_part[wv * 16 + n] += xs.x;
           }
-          issue_x(bxs[(j + XD) % XS], (pass + XD) % my_passes);
+          issue_x((pass + 1) % my_passes);
 #pragma unroll
           for (int b = 0; b < NB; ++b) {
             const int slot = j * NB + b;
@@ -357,6 +364,7 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
 
         if (pass == eff_passes - 1) {
           // ---- chunk end: partial sums to LDS; wave b adds up block b, applies scale and bias, stores
+          if (plan.part_bufs == 0) lds_barrier();
           unsigned char *pbase = lds + plan.lds_part + (unsigned)(buf * NB) * (MW * 1024u);
 #pragma unroll
           for (int b = 0; b < NB; ++b)
@@ -412,7 +420,7 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
             }
             }
           }
-          if (plan.part_bufs == 1) lds_barrier(); else buf ^= 1;
+          if (plan.part_bufs == 1) lds_barrier(); else if (plan.part_bufs == 2) buf ^= 1;
           pass = 0; ++c;
         } else {
           ++pass;
@@ -564,15 +572,23 @@ int make_plan(const Params &p, int batch, long long ldx, const __half *y, long l
   plan.lds_part = off;
   if (off + (unsigned)waves * 1024u > lds_cap) return VQ_ERR_UNSUPPORTED;
   const int fit = (int)((lds_cap - off) / ((unsigned)waves * 1024u));    // 16-row partial blocks that fit
-  // Blocks per chunk: as many as the kernel's 256 registers allow -- four, or three with a residual index stream in the
-  // prefetch ring.  More would spill, which these kernels must not (see the build script).
-  // (with codebook groups one fewer: the group loop costs registers of its own)
-  const int nb_regs = grouped ? (rb == 12 ? 2 : 3) : (rb ? 3 : NBMAX);
-  plan.nb = min(min(nb_regs, blocks_per_wg), fit);
-  if (nb_force > 0) { if (nb_force > plan.nb) return VQ_ERR_UNSUPPORTED; plan.nb = nb_force; }
-  if (plan.nb < 1) return VQ_ERR_UNSUPPORTED;
-  plan.part_bufs = (fit >= 2 * plan.nb && blocks_per_wg > plan.nb) ? 2 : 1;
-  off += (unsigned)(plan.part_bufs * plan.nb) * ((unsigned)waves * 1024u);
+  // Blocks per chunk: as many as the kernel's 256 registers allow.  More would spill, which these kernels must not (see the build
+  // script).  (with codebook groups fewer: the group loop costs registers of its own)  Every chunk loads the activations again: a
+  // workgroup's blocks go in one chunk where they can, then in even ones.
+  const int nb_regs = grouped ? (rb == 12 ? 2 : 3) : NBMAX;
+  if (!grouped && blocks_per_wg <= nb_regs && blocks_per_wg > fit && (nb_force == 0 || nb_force >= blocks_per_wg)) {
+    plan.nb = nb_force > 0 ? nb_force : blocks_per_wg;
+    plan.part_bufs = 0;
+    plan.lds_part = 0;                                    // (at most 6 blocks of 8 KB; the tables have 64 KB and more)
+  } else {
+    plan.nb = min(min(nb_regs, blocks_per_wg), fit);
+    if (plan.nb < 1) return VQ_ERR_UNSUPPORTED;
+    const int chunks = (blocks_per_wg + plan.nb - 1) / plan.nb;
+    plan.nb = (blocks_per_wg + chunks - 1) / chunks;
+    if (nb_force > 0) { if (nb_force > min(min(nb_regs, blocks_per_wg), fit)) return VQ_ERR_UNSUPPORTED; plan.nb = nb_force; }
+    plan.part_bufs = (fit >= 2 * plan.nb && blocks_per_wg > plan.nb) ? 2 : 1;
+    off += (unsigned)(plan.part_bufs * plan.nb) * ((unsigned)waves * 1024u);
+  }
   const long long max_stride = max(p.stride, max(p.stride_res, p.stride_out));
   if ((long long)(plan.rows_per_wg + 16 * NBMAX * 8) * max_stride >= (1LL << 31)) return VQ_ERR_UNSUPPORTED;   // 32-bit buffer offsets
   const long long x_bytes = ((long long)(batch - 1) * ldx + p.in_features) * 2;
@@ -618,9 +634,9 @@ int launch_gemv_mfma(const Params &p, const __half *x, long long ldx, int batch,
   if (rb == RBITS && plan.nb == NBLK && !grouped) return launch_one<RBITS, MW, NBLK, false>(p, plan, off, grid, x, ldx, batch, y, ldy, s); \
   if (rb == RBITS && plan.nb == NBLK && grouped && NBLK <= (RBITS == 12 ? 2 : 3)) \
     return launch_one<RBITS, MW, (NBLK <= (RBITS == 12 ? 2 : 3) ? NBLK : 1), true>(p, plan, off, grid, x, ldx, batch, y, ldy, s);
-  VQ_CASE(0, 1) VQ_CASE(0, 2) VQ_CASE(0, 3) VQ_CASE(0, 4)
-  VQ_CASE(8, 1) VQ_CASE(8, 2) VQ_CASE(8, 3)
-  VQ_CASE(12, 1) VQ_CASE(12, 2) VQ_CASE(12, 3)
+  VQ_CASE(0, 1) VQ_CASE(0, 2) VQ_CASE(0, 3) VQ_CASE(0, 4) VQ_CASE(0, 5) VQ_CASE(0, 6)
+  VQ_CASE(8, 1) VQ_CASE(8, 2) VQ_CASE(8, 3) VQ_CASE(8, 4) VQ_CASE(8, 5) VQ_CASE(8, 6)
+  VQ_CASE(12, 1) VQ_CASE(12, 2) VQ_CASE(12, 3) VQ_CASE(12, 4) VQ_CASE(12, 5) VQ_CASE(12, 6)
 #undef VQ_CASE
   return VQ_ERR_UNSUPPORTED;
 }
@@ -722,9 +738,9 @@ int launch_gemv_mfma_multi(const Params *ps, int n, const __half *x, long long l
   const unsigned grid = (unsigned)a.first_wg[n];
   const int rb = pl[0].rb;
 #define VQ_CASE(RBITS, NBLK) if (rb == RBITS && nb == NBLK) return launch_multi<RBITS, NBLK>(a, lds_bytes, grid, x, ldx, batch, s);
-  VQ_CASE(0, 1) VQ_CASE(0, 2) VQ_CASE(0, 3) VQ_CASE(0, 4)
-  VQ_CASE(8, 1) VQ_CASE(8, 2) VQ_CASE(8, 3)
-  VQ_CASE(12, 1) VQ_CASE(12, 2) VQ_CASE(12, 3)
+  VQ_CASE(0, 1) VQ_CASE(0, 2) VQ_CASE(0, 3) VQ_CASE(0, 4) VQ_CASE(0, 5) VQ_CASE(0, 6)
+  VQ_CASE(8, 1) VQ_CASE(8, 2) VQ_CASE(8, 3) VQ_CASE(8, 4) VQ_CASE(8, 5) VQ_CASE(8, 6)
+  VQ_CASE(12, 1) VQ_CASE(12, 2) VQ_CASE(12, 3) VQ_CASE(12, 4) VQ_CASE(12, 5) VQ_CASE(12, 6)
 #undef VQ_CASE
   return VQ_ERR_UNSUPPORTED;
 }

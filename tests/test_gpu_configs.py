@@ -170,6 +170,27 @@ def test_prefill_without_workspace_on_the_v6_layers(gpu_lib, layers, cfg, name, 
     _matmul_ok(Y[:, torch.from_numpy(rows.astype(np.int64)).cuda()], oracle.gemm(L, x, rows=rows), "cfg%d %s T=%d on the fly" % (cfg, name, tokens))
 
 
+# Rows for which a workgroup of the matrix-core kernel has 4, 5, 6 and 7 blocks of sixteen (256 compute units): one chunk over the tables
+# where its partial sums do not fit beside them, one beside them, and two chunks of four and three blocks.
+@pytest.mark.parametrize("out,k_res,outliers", [(12300, 4096, 0), (16400, 0, 0), (20480, 256, 8), (24560, 4096, 8), (24561, 256, 0), (24592, 4096, 0)])
+def test_many_blocks_a_workgroup(gpu_lib, out, k_res, outliers):
+    import torch
+    L = s.make_layer(1, "up", out, 391, 6, 4096, k_res, **(dict(n_outlier_cols=outliers, v_out=4, k_out=4096) if outliers else {}))
+    dl = gpu_lib.DeviceLayer(L)
+    second = s.make_layer(2, "up", 70, 391, 6, 4096, k_res)
+    for batch in (3, 16):
+        x = s.make_activations(1, L, batch)
+        ref = oracle.gemv(L, x)
+        xd = torch.zeros((batch, 392), dtype=torch.float16, device="cuda")
+        xd[:, :391] = torch.from_numpy(x)
+        y = gpu_lib.gemv(dl, xd[:, :391], workspace=lent("none"))
+        ym, ys = gpu_lib.gemv_multi([dl, gpu_lib.DeviceLayer(second)], xd[:, :391])
+        torch.cuda.synchronize()
+        _matmul_ok(y, ref, "%d rows, k_res %d, batch %d" % (out, k_res, batch))
+        _matmul_ok(ym, ref, "%d rows, k_res %d, batch %d, one of two" % (out, k_res, batch))
+        _matmul_ok(ys, oracle.gemv(second, x), "70 rows beside %d, k_res %d, batch %d" % (out, k_res, batch))
+
+
 @pytest.mark.parametrize("orientation", [0, 1])
 def test_the_2_26_bit_setting_at_full_size(gpu_lib, orientation):
     """The 11008 x 4096 layer in the 2.26-bit setting of Table "Quantization parameters" (v = 12, two 4096-entry tables, four
