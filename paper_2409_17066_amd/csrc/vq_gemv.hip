@@ -435,6 +435,17 @@ int launch_gemv_ws(const Params &p, const __half *x, long long ldx, int batch, _
     q.perm = nullptr;
     __half *xp = static_cast<__half *>(workspace);
     const long long ldxp = (p.in_features + 7) & ~7;
+    // (in one launch of the LDS-table kernel the workgroups gather theirs by themselves: a group's columns, in the shade of its table)
+    if (p.perm && batch <= 4 && batch != 3 && p.orientation == 0 && !rows_wanted(q, batch, true) && !gemv_fast_applicable(q, xp, ldxp) && !switches().groups_loop) {
+      const size_t head = permuted_x_bytes(p, batch), slot_bytes = gemv_lds_slots_workspace_bytes(q, batch);
+      if (slot_bytes && workspace_bytes - head >= slot_bytes) {
+        const int slots = gemv_lds_slots(q, batch);
+        float *part = reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + head), *part_xs = part + (size_t)slots * (size_t)batch * (size_t)p.out_features;
+        const int rc = launch_gemv_lds_slots(p, x, ldx, batch, part, part_xs, s);
+        if (rc == VQ_OK) return launch_groups_finish(part, part_xs, slots, batch, p, y, ldy, s);
+        if (rc != VQ_ERR_UNSUPPORTED) return rc;
+      }
+    }
     const int rc = launch_gather_cols(x, ldx, batch, p.in_features, p.perm, xp, ldxp, s);
     if (rc != VQ_OK) return rc;
     const size_t head = permuted_x_bytes(p, batch);

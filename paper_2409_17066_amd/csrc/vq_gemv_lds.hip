@@ -349,9 +349,10 @@ struct PassPlan {
   unsigned off_x, off_xo, off_xsum, off_ypart, bytes;     // byte offsets in dynamic LDS (the pass's table at 0)
   unsigned x_pitch, xo_pitch;                             // bytes per staged row of main / outlier columns
   int rows_per_wg;
-  // With a workspace on loan a workgroup takes one "slot" -- a codebook group (its main and residual table) or the outlier
-  // columns -- and a block of rows, and leaves its sums in the workspace for the kernel that adds the slots up:
-  int n_slots, batch_total;                               // groups among the slots; 0: every workgroup walks all passes and writes y
+  // With a workspace on loan a workgroup takes one "slot" -- a codebook group (its main and residual table), or one table of it, or
+  // the outlier columns -- and a block of rows, and leaves its sums in the workspace for the kernel that adds the slots up:
+  int n_slots, batch_total;                               // groups or tables among the slots; 0: every workgroup walks all passes and writes y
+  int one_table;                                          // 1: a slot is one table
   int out_first, out_rows;                                // first of the workgroups for the outlier columns and the rows each takes; 0: the
                                                           // first group's workgroups take the outlier columns as well
   float *part, *part_xs;                                  // [n_slots][batch_total][out_features] sums, [n_slots][16] activation sums
@@ -372,7 +373,6 @@ __global__ __launch_bounds__(LW * 64) void gemv_lds_passes_kernel(Params p, Pass
   const int rows_per_wg = only_outliers ? plan.out_rows : plan.rows_per_wg;
   const int row0 = (only_outliers ? (int)blockIdx.x - plan.out_first : slots ? (int)blockIdx.x / plan.n_slots : (int)blockIdx.x) * rows_per_wg;
   const int row1 = min(p.out_features, row0 + rows_per_wg);
-  const int windows = (p.P + U - 1) / U;
   const __amdgpu_buffer_rsrc_t r_i = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(p.idx), 0, (unsigned)((long long)p.out_features * p.stride), 0x00020000);
   const __amdgpu_buffer_rsrc_t r_r = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(p.k_res ? p.idx_res : p.idx), 0,
                                                                        p.k_res ? (unsigned)((long long)p.out_features * p.stride_res) : 0u, 0x00020000);
@@ -403,8 +403,9 @@ __global__ __launch_bounds__(LW * 64) void gemv_lds_passes_kernel(Params p, Pass
 
   const int tables_per_group = p.k_res ? 2 : 1;
   const int table_passes = p.n_groups * tables_per_group;
-  const int pass_begin = slots ? slot * tables_per_group : 0;
-  const int my_table_passes = only_outliers ? 0 : slots ? tables_per_group : table_passes;
+  const int tables_per_slot = plan.one_table ? 1 : tables_per_group;
+  const int pass_begin = slots ? slot * tables_per_slot : 0;
+  const int my_table_passes = only_outliers ? 0 : slots ? tables_per_slot : table_passes;
   const int my_passes = my_table_passes + (p.Q && with_outliers ? 1 : 0);
   for (int ip = 0; ip < my_passes; ++ip) {
     const int pass = ip < my_table_passes ? pass_begin + ip : table_passes;
@@ -447,6 +448,22 @@ __global__ __launch_bounds__(LW * 64) void gemv_lds_passes_kernel(Params p, Pass
     int o = row0 + wv * (64 / SEG), it = 0;
     unsigned wm[ND < 2 ? 2 : ND];
     load_round(wm, o, 0);                                                 // the first round's words go out ahead of the staging
+    // the activations of the pass's windows: a new group's, with zeros outside the group (and past the row); the first AHEAD of a
+    // thread's go out ahead of the table, as they may be two lookups away
+    const bool stages_x = !outlier && (!second || plan.one_table);
+    constexpr int AHEAD = 2;
+    __half ahead[AHEAD][B];
+    auto x_of = [&](int t, int j) {
+      const int c = p.n_out + j, pv = j / V;
+      return pv >= p_lo && pv < p_hi && c < p.in_features ? x_at(t, c) : __float2half_rn(0.0f);
+    };
+    const int j0 = w_lo * (U * V) + (int)threadIdx.x, j1 = w_hi * (U * V);
+    if (stages_x) {
+#pragma unroll
+      for (int i = 0; i < AHEAD; ++i)
+#pragma unroll
+        for (int t = 0; t < B; ++t) ahead[i][t] = j0 + i * (LW * 64) < j1 ? x_of(t, j0 + i * (LW * 64)) : __float2half_rn(0.0f);
+    }
 
     __syncthreads();                                                      // every wave has left the table and rows of the pass before
     // ---- the pass's table into LDS: padded entries, an entry per thread and round (outlier entries: 8 bytes as they are)
@@ -457,20 +474,21 @@ __global__ __launch_bounds__(LW * 64) void gemv_lds_passes_kernel(Params p, Pass
 #pragma unroll 4
       for (int en = threadIdx.x; en < k_a; en += LW * 64) stage_entry<V>(lds, cb_a, en);
     }
-    // ---- the activations of the pass's windows: a new group's, with zeros outside the group (and past the row)
-    if (!outlier && !second) {
+    if (stages_x) {
 #pragma unroll
       for (int t = 0; t < B; ++t) {
         __half *xs = reinterpret_cast<__half *>(lds + plan.off_x + t * plan.x_pitch);
         float part = 0.0f;
-        for (int j = w_lo * (U * V) + (int)threadIdx.x; j < w_hi * (U * V); j += LW * 64) {
-          const int c = p.n_out + j, pv = j / V;
-          const __half v = pv >= p_lo && pv < p_hi && c < p.in_features ? x_at(t, c) : __float2half_rn(0.0f);
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i)
+          if (j0 + i * (LW * 64) < j1) { xs[j0 + i * (LW * 64)] = ahead[i][t]; part += __half2float(ahead[i][t]); }
+        for (int j = j0 + AHEAD * (LW * 64); j < j1; j += LW * 64) {
+          const __half v = x_of(t, j);
           xs[j] = v;
           part += __half2float(v);
         }
         part = wave_sum(part);                                            // the group's share of sum(x)
-        if (lane == 0) xpart[t * LW + wv] += part;
+        if (lane == 0 && !second) xpart[t * LW + wv] += part;
       }
     }
     __syncthreads();
@@ -569,6 +587,17 @@ bool outlier_slot(const Params &p, int batch) {
   return p.Q > 0 && p.n_groups <= 16 && cu_count() >= 64 && slots_bytes(p, p.n_groups + 1, batch) <= VQ_GEMV_STATIC_WORKSPACE_BYTES;
 }
 
+// Whether a slot is one table: then a workgroup stages one table instead of two and walks twice the rows with it (the 2.26-bit setting, one
+// row, 11008 x 4096: 27.2 -> 25.2 us, two rows 34.8 -> 32.0; 1024 x 2048 10.9 -> 10.0; two groups 27.5 -> 24.3, eight 26.8 -> 24.9; and
+// 29.5 -> 25.3 with permuted columns, which every workgroup now gathers for itself).  Up to 16 tables, and as long as the sums, with the
+// rows in stored order beside them, fit the library's own workspace.
+bool table_slots(const Params &p, int batch) {
+  const int slots = 2 * p.n_groups + (p.Q ? 1 : 0);
+  const size_t rows = ((size_t)batch * (size_t)((p.in_features + 7) & ~7) * sizeof(__half) + 255) / 256 * 256;
+  return p.k_res && p.n_groups <= 8 && cu_count() >= 64 && slots_bytes(p, slots, batch) + rows <= VQ_GEMV_STATIC_WORKSPACE_BYTES;
+}
+int group_slots(const Params &p, int batch) { return table_slots(p, batch) ? 2 * p.n_groups : p.n_groups; }
+
 bool make_pass_plan(const Params &p, int batch, int u, int eh, PassPlan *plan, int n_slots = 0, bool out_slot = false) {
   auto up16 = [](size_t v) { return (v + 15) / 16 * 16; };
   size_t table = up16((size_t)p.k * eh * 2);
@@ -587,6 +616,7 @@ bool make_pass_plan(const Params &p, int batch, int u, int eh, PassPlan *plan, i
     plan->out_rows = (p.out_features + out_wgs - 1) / out_wgs;
     if (plan->out_rows < LW) plan->out_rows = LW;
   }
+  plan->one_table = p.k_res && n_slots == 2 * p.n_groups;
   plan->n_slots = n_slots; plan->batch_total = 0; plan->part = nullptr; plan->part_xs = nullptr;
   const size_t sums = up16(4 * 4 * (1 + LW));
   const size_t total = table + (pitch + xo_pitch) * batch + sums + (size_t)std::max(plan->rows_per_wg, plan->out_rows) * batch * 4;
@@ -716,19 +746,19 @@ int launch_gemv_lds(const Params &p, const __half *x, long long ldx, int batch, 
 
 // Layers that the pass kernel takes and that have at least two codebook groups: with a workspace of
 // slots x (batch x out_features + 16) binary32 sums every workgroup takes one slot; 0 when that does not apply.
-int gemv_lds_slots(const Params &p, int batch) { return p.n_groups + (outlier_slot(p, batch) ? 1 : 0); }
+int gemv_lds_slots(const Params &p, int batch) { return group_slots(p, batch) + (outlier_slot(p, batch) ? 1 : 0); }
 
 size_t gemv_lds_slots_workspace_bytes(const Params &p, int batch) {
   PassPlan plan;
-  const int n_slots = p.n_groups;
-  if (p.orientation != 0 || n_slots < 2 || n_slots > 64 || !pass_pair(p)) return 0;
+  const int n_slots = group_slots(p, batch);
+  if (p.orientation != 0 || p.n_groups < 2 || n_slots > 64 || !pass_pair(p)) return 0;
   if (!make_pass_plan(p, 1, win_vectors(p.bits), entry_halfs(p.v), &plan, n_slots, outlier_slot(p, batch))) return 0;
   return slots_bytes(p, gemv_lds_slots(p, batch), batch);
 }
 
 // The slots' sums into part [slots][batch][out_features] and part_xs [slots][16]; the caller adds them up.
 int launch_gemv_lds_slots(const Params &p, const __half *x, long long ldx, int batch, float *part, float *part_xs, hipStream_t s) {
-  const int n_slots = p.n_groups;
+  const int n_slots = group_slots(p, batch);
   int done = 0, g_max = 4;
   while (done < batch) {
     int g = batch - done >= 4 ? 4 : batch - done >= 2 ? 2 : 1;

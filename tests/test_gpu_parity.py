@@ -484,6 +484,28 @@ def test_gemv_lds_table_slots_with_workspace(gpu_lib, name, batch):
     assert torch.equal(small, plain)
 
 
+@pytest.mark.parametrize("groups", [2, 8, 9])
+@pytest.mark.parametrize("permuted", [False, True])
+@pytest.mark.parametrize("v,k,k_res", [(12, 4096, 4000), (4, 256, 200)])
+def test_gemv_lds_table_slots_with_two_tables(gpu_lib, groups, permuted, v, k, k_res):
+    """Layers with a residual table: up to eight groups a slot is one table, more and it is a group; one launch gathers permuted
+    columns by itself.  Ragged ends: rows that fill no round, a last group of fewer vectors, columns cut off within a vector."""
+    import torch
+    per = 16 if groups < 9 else 8
+    cols = 40 + v * (per * groups - 3) - 1
+    L = s.make_layer(310, "slots", 611, cols + cols % 2, v, k, k_res, n_outlier_cols=40, v_out=4, k_out=5000, group_vectors=per, permute=permuted)
+    assert L.n_groups == groups
+    dl = gpu_lib.DeviceLayer(L)
+    for batch in (1, 2):
+        x_np = s.make_activations(310, L, batch)
+        need = gpu_lib.vq_gemv_workspace_bytes(dl.desc, batch)
+        ws = torch.full((need + 256,), 0xFF, dtype=torch.uint8, device="cuda")
+        y = gpu_lib.gemv(dl, torch.from_numpy(x_np).cuda(), workspace=ws[:need])
+        torch.cuda.synchronize()
+        _check_matmul(y, oracle.gemv(L, x_np), "v %d, %d groups, permuted %s, batch %d" % (v, groups, permuted, batch))
+        assert (ws[need:] == 0xFF).all()
+
+
 PERMUTED = [n for n in SMALL if n.startswith("perm_")]
 
 
