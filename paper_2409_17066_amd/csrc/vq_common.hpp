@@ -61,7 +61,8 @@ inline int index_bits(int k) { int b = 1; while ((1 << b) < k) ++b; return b; }
 int make_params(const vq_layer_desc *d, Params *p);
 
 // Kernel launchers (each returns a vq_status).
-int launch_dequant(const Params &p, __half *W, long long ldw, hipStream_t s);
+// (product_tokens: so many rows are multiplied by W next in the stream; 0: not known)
+int launch_dequant(const Params &p, __half *W, long long ldw, hipStream_t s, int product_tokens = 0);
 int launch_gemv(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, hipStream_t s);
 bool gemv_has_fast_kernel(const Params &p, const __half *x, long long ldx);
 size_t gemv_workspace_bytes(const Params &p, const __half *x, long long ldx, int batch);

@@ -82,20 +82,20 @@ __global__ __launch_bounds__(256) void dequant_down_kernel(Params p, __half *W, 
   }
 }
 
-int launch_dequant_tables(const Params &p, __half *W, long long ldw, hipStream_t s);
+int launch_dequant_tables(const Params &p, __half *W, long long ldw, hipStream_t s, int product_tokens);
 
-int launch_dequant(const Params &p, __half *W, long long ldw, hipStream_t s) {
+int launch_dequant(const Params &p, __half *W, long long ldw, hipStream_t s, int product_tokens) {
   if (p.perm && switches().dequant != 'g') {
     // Permuted column order: restore in stored order, then move every row's values to
     // their columns, in place, through LDS.  (Rows too long for LDS: the generic kernels below, which scatter their stores.)
     Params q = p;
     q.perm = nullptr;
     if ((long long)p.in_features * 2 <= 160 * 1024) {
-      const int rc = launch_dequant(q, W, ldw, s);
+      const int rc = launch_dequant(q, W, ldw, s, product_tokens);
       return rc == VQ_OK ? launch_place_cols(W, ldw, p.out_features, p.in_features, p.perm, s) : rc;
     }
   }
-  const int rc = launch_dequant_tables(p, W, ldw, s);
+  const int rc = launch_dequant_tables(p, W, ldw, s, product_tokens);
   if (rc != VQ_ERR_UNSUPPORTED) return rc;
   if (p.orientation == 1) {
     const int bps_main = (p.P + 255) / 256, bps_out = p.Q ? (p.Q + 255) / 256 : 1;

@@ -430,6 +430,94 @@ __global__ __launch_bounds__(256) void dequant_down_lookup_kernel(Params p, __ha
   }
 }
 
+// Vectors of eight along the rows and a table of up to 65536 of them (1 MiB), in front of a product of many tokens: the table passes
+// through LDS, a piece after the other, and every lane takes those of its sixteen vectors' entries that lie in the piece.  Two pieces of 5120
+// entries: one is filled while the other is read; the workgroups start at different pieces.  A workgroup takes 16384 neighbouring
+// vectors at a time, a wave 64 of them (1 KB of W).
+// What bounds it: filling 1 MB of LDS a compute unit and turn, at the 11 TB/s that L2 gives all of them together: 24 us.  Entries read
+// through L2 one by one bring lines of 128 bytes for sixteen: 48 us for two turns' vectors (8192 x 8192) by themselves, but behind and
+// ahead of a long product, which leaves L2 without the table and the chip at its power limit, a call is faster this way: 8192 x 8192
+// at 1024 / 2048 tokens 222 -> 207 and 300 -> 274 us, 14336 x 4096 177 -> 164 and 277 -> 261, 8192 x 28672 767 -> 691 and 964 -> 905.  At 300 tokens
+// it is not (4096 x 4096 35 us through L2, 46), nor with turns that are not full (4096 x 11008, 5.6 M vectors, 2048 tokens: 267, 271).
+constexpr long long PIECES_FROM = 7 << 20;
+constexpr int MANY_TOKENS = 1024;
+constexpr int PIECE = 5120, HELD = 16, PIECES_THREADS = 1024;
+
+// Entries at bytes [from, from + PIECE * 16) of the table, which lie at `piece` in LDS, to those lanes whose byte `at` is among them; all
+// lanes are active.  In one statement, the wait included: the compiler would wait for every read before the next.
+__device__ __forceinline__ void read_piece(uint4v *e, const unsigned *at, unsigned from, unsigned piece) {
+  unsigned t;
+#define VQ_READ(E, I) "v_subrev_u32 %8, %17, %" I "\n\tv_cmpx_gt_u32 vcc, %18, %8\n\tv_add_u32 %8, %19, %8\n\tds_read_b128 %" E ", %8\n\ts_mov_b64 exec, -1\n\t"
+  asm volatile(VQ_READ("0", "9") VQ_READ("1", "10") VQ_READ("2", "11") VQ_READ("3", "12") VQ_READ("4", "13") VQ_READ("5", "14") VQ_READ("6", "15") VQ_READ("7", "16")
+               "s_waitcnt lgkmcnt(0)"
+               : "+v"(e[0]), "+v"(e[1]), "+v"(e[2]), "+v"(e[3]), "+v"(e[4]), "+v"(e[5]), "+v"(e[6]), "+v"(e[7]), "=&v"(t)
+               : "v"(at[0]), "v"(at[1]), "v"(at[2]), "v"(at[3]), "v"(at[4]), "v"(at[5]), "v"(at[6]), "v"(at[7]), "s"(from), "s"(PIECE * 16u), "s"(piece)
+               : "vcc", "memory");
+#undef VQ_READ
+}
+
+template <bool STREAM>
+__global__ __launch_bounds__(PIECES_THREADS, 4) void dequant_pieces_kernel(Params p, __half *__restrict__ W, long long ldw, unsigned total, unsigned rows_inv) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  constexpr unsigned BYTES = PIECE * 16u;
+  const unsigned tid = threadIdx.x, lane = tid & 63u;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(tid >> 6));
+  const unsigned lds0 = (unsigned)reinterpret_cast<size_t>((const __attribute__((address_space(3))) void *)lds);
+  const unsigned P = (unsigned)p.P, n_pieces = ((unsigned)p.k + PIECE - 1) / PIECE, first_piece = blockIdx.x % n_pieces;
+  const __amdgpu_buffer_rsrc_t r_cb = __builtin_amdgcn_make_buffer_rsrc(const_cast<__half *>(p.cb), 0, (unsigned)p.k * 16u, 0x00020000);
+  const __amdgpu_buffer_rsrc_t r_i = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(p.idx), 0, (unsigned)((long long)p.S * p.stride), 0x00020000);
+  // row and position of a vector (rows_inv: 2^32 / P, rounded down; the quotient is short of one at most)
+  auto place = [&](unsigned n, unsigned &o, unsigned &at) {
+    o = __umulhi(n, rows_inv);
+    at = n - o * P;
+    if (at >= P) { ++o; at -= P; }
+  };
+  auto piece_of = [&](unsigned turn) { const unsigned c = first_piece + turn; return c < n_pieces ? c : c - n_pieces; };
+  auto fill = [&](unsigned turn) {
+    const unsigned from = piece_of(turn) * BYTES, to = (turn & 1u) * BYTES;
+#pragma unroll
+    for (unsigned at = 0; at < BYTES; at += PIECES_THREADS * 16u) copy16(r_cb, lds + to + at + wave * 1024u, from + at + (unsigned)wave * 1024u + lane * 16u);
+  };
+  static_assert(BYTES % (PIECES_THREADS * 16u) == 0, "whole rounds of all waves");
+  for (unsigned base = blockIdx.x * (PIECES_THREADS * HELD); base < total; base += gridDim.x * (PIECES_THREADS * HELD)) {
+    unsigned i[HELD];
+    uint4v e[HELD];
+#pragma unroll
+    for (int u = 0; u < HELD; ++u) {
+      unsigned o, at;
+      place(min(base + u * PIECES_THREADS + tid, total - 1u), o, at);
+      i[u] = load2(r_i, o * (unsigned)p.stride + at * 2u);
+    }
+    fill(0);
+#pragma unroll
+    for (int u = 0; u < HELD; ++u) {
+      i[u] = min(i[u], (unsigned)p.k - 1u) * 16u;            // (as bytes of the table)
+      e[u] = uint4v{0u, 0u, 0u, 0u};
+    }
+    for (unsigned turn = 0; turn < n_pieces; ++turn) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();                                     // (the piece is in, and every wave is through with the other one)
+      if (turn + 1 < n_pieces) fill(turn + 1);
+      const unsigned from = piece_of(turn) * BYTES, piece = lds0 + (turn & 1u) * BYTES;
+      read_piece(e, i, from, piece);
+      read_piece(e + HELD / 2, i + HELD / 2, from, piece);
+    }
+    __syncthreads();                                       // (the next vectors' first piece goes where the last one was, or beside it)
+#pragma unroll
+    for (int u = 0; u < HELD; ++u) {
+      const unsigned n = base + u * PIECES_THREADS + tid;
+      if (n < total) {
+        unsigned o, at;
+        place(n, o, at);
+        const float sc = p.scale ? __half2float(p.scale[o]) : 1.0f, bi = p.bias ? __half2float(p.bias[o]) : 0.0f;
+        const unsigned w[4] = {restore_pair<false>(e[u].x, 0u, sc, bi, sc, bi), restore_pair<false>(e[u].y, 0u, sc, bi, sc, bi),
+                               restore_pair<false>(e[u].z, 0u, sc, bi, sc, bi), restore_pair<false>(e[u].w, 0u, sc, bi, sc, bi)};
+        store16<STREAM>(W + (long long)o * ldw + at * 8u, w);
+      }
+    }
+  }
+}
+
 unsigned table_bytes(int v, int k) { return ((unsigned)k * (unsigned)v * 2u + 1023u) / 1024u * 1024u; }      // in LDS: whole pieces of 1 KB
 
 template <auto KERNEL, int NW> int launch_kernel(dim3 grid, unsigned lds, hipStream_t s, const Params &p, const DqArgs &a) {
@@ -439,7 +527,8 @@ template <auto KERNEL, int NW> int launch_kernel(dim3 grid, unsigned lds, hipStr
 }
 
 template <int V, int BITS, int RBITS, int RES, bool DOWN>
-int launch_one(const Params &p, __half *W, long long ldw, hipStream_t s) {
+int launch_one(const Params &p, __half *W, long long ldw, hipStream_t s, int product_tokens) {
+  const long long w_bytes = (long long)p.out_features * p.in_features * 2;
   constexpr bool L2_LOOKUPS = BITS == 16 || RES == RES_MEM || RES == RES_SPLIT;
   const unsigned main = BITS == 16 ? 0u : table_bytes(V, p.k), bytes = RES == RES_SPLIT ? 160u * 1024u : main + (RES == RES_LDS ? table_bytes(V, p.k_res) : 0u);
   DqArgs a = {W, ldw, main, 0, 0, 1, 0, 6, 1, 0, 0};
@@ -464,6 +553,20 @@ int launch_one(const Params &p, __half *W, long long ldw, hipStream_t s) {
       return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
     }
   }
+  if constexpr (!DOWN && V == 8 && BITS == 16 && RES == NO_RES) {
+    const long long vectors = (long long)p.S * p.P, turn = (long long)PIECES_THREADS * HELD * cu_count();
+    if (product_tokens >= MANY_TOKENS && p.n_groups == 1 && !p.Q && p.in_features == p.P * 8 && p.P > 1 && vectors >= PIECES_FROM && vectors < 1LL << 31 &&
+        vectors * 5 >= (vectors + turn - 1) / turn * turn * 4) {      // (turns that are full to four fifths)
+      const unsigned n = (unsigned)vectors, inv = (unsigned)((1ULL << 32) / (unsigned)p.P);
+      const unsigned rounds = (unsigned)((vectors + turn - 1) / turn), wg = (unsigned)((vectors + (long long)rounds * PIECES_THREADS * HELD - 1) / ((long long)rounds * PIECES_THREADS * HELD));
+      auto run = [&](auto kernel) {
+        VQ_ALLOW_FULL_LDS(kernel);
+        hipLaunchKernelGGL(kernel, dim3(wg), dim3(PIECES_THREADS), 2u * PIECE * 16u, s, p, W, ldw, n, inv);
+        return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
+      };
+      return w_bytes > 192LL << 20 ? run(dequant_pieces_kernel<true>) : run(dequant_pieces_kernel<false>);
+    }
+  }
   // four workgroups of eight waves on a CU where the tables are small; else two or one of sixteen, which share them (32 x 1 KB of
   // stores in flight either way; 3 x 8 waves with a 48 KB table each spent longer staging)
   const bool small = bytes <= 40 * 1024;
@@ -475,10 +578,13 @@ int launch_one(const Params &p, __half *W, long long ldw, hipStream_t s) {
   if (items <= wgs * nw) { a.wave_step = a.wgs; a.wg_step = 1; }      // no wave has two: every workgroup gets its share
   if (p.Q) a.out_wgs = (int)min((long long)(p.S_out + nw - 1) / nw, (long long)cu_count());
   const dim3 grid((unsigned)(wgs * p.n_groups + a.out_wgs));
+  // (in front of a product W goes through the caches as long as they hold it beside the rest: v8 / 65536 at 300 tokens 4096 x 4096 43.8 -> 34.9 us,
+  // 11008 x 4096 102 -> 91, v12 / 4096 + 4096 2048 x 4096 28.8 -> 25.7; 8192 x 8192 at 300 tokens 141 -> 146, but at 2048 300 -> 290)
   // past the caches: where lookups go through L2, from which W must not push the table; and where W is larger than they are
   // (down the outputs only if rows start on 64 bytes: with pieces of lines between them 8192 x 20480 took 103 us past the caches, 97 through)
+  const bool through = product_tokens > 0 && (w_bytes <= 96LL << 20 || (product_tokens >= MANY_TOKENS && w_bytes <= 192LL << 20));
   const uintptr_t starts = reinterpret_cast<uintptr_t>(W) | (uintptr_t)ldw * 2 | (uintptr_t)p.n_out * 2;
-  const bool stream = (L2_LOOKUPS && (starts & 15) == 0) || ((long long)p.out_features * p.in_features * 2 > 256LL << 20 && (!DOWN || (starts & 63) == 0));
+  const bool stream = (L2_LOOKUPS && !through && (starts & 15) == 0) || (w_bytes > 256LL << 20 && (!DOWN || (starts & 63) == 0));
   const int rc = small ? (stream ? launch_kernel<dequant_tables_kernel<V, BITS, RBITS, RES, DOWN, 8, true>, 8>(grid, bytes, s, p, a)
                                  : launch_kernel<dequant_tables_kernel<V, BITS, RBITS, RES, DOWN, 8, false>, 8>(grid, bytes, s, p, a))
                        : (stream ? launch_kernel<dequant_tables_kernel<V, BITS, RBITS, RES, DOWN, 16, true>, 16>(grid, bytes, s, p, a)
@@ -488,18 +594,18 @@ int launch_one(const Params &p, __half *W, long long ldw, hipStream_t s) {
 }
 
 template <int V, int BITS, int RBITS>
-int launch_pair(const Params &p, __half *W, long long ldw, hipStream_t s) {
+int launch_pair(const Params &p, __half *W, long long ldw, hipStream_t s, int product_tokens) {
   if (!p.k_res) {
-    if constexpr (RBITS == BITS) return p.orientation ? launch_one<V, BITS, 0, NO_RES, true>(p, W, ldw, s) : launch_one<V, BITS, 0, NO_RES, false>(p, W, ldw, s);
+    if constexpr (RBITS == BITS) return p.orientation ? launch_one<V, BITS, 0, NO_RES, true>(p, W, ldw, s, product_tokens) : launch_one<V, BITS, 0, NO_RES, false>(p, W, ldw, s, product_tokens);
     else return VQ_ERR_UNSUPPORTED;
   }
   if constexpr (BITS == 16) {
-    return p.orientation ? launch_one<V, BITS, RBITS, RES_MEM, true>(p, W, ldw, s) : launch_one<V, BITS, RBITS, RES_MEM, false>(p, W, ldw, s);
+    return p.orientation ? launch_one<V, BITS, RBITS, RES_MEM, true>(p, W, ldw, s, product_tokens) : launch_one<V, BITS, RBITS, RES_MEM, false>(p, W, ldw, s, product_tokens);
   } else {
     if (table_bytes(V, p.k) + table_bytes(V, p.k_res) <= 160 * 1024)
-      return p.orientation ? launch_one<V, BITS, RBITS, RES_LDS, true>(p, W, ldw, s) : launch_one<V, BITS, RBITS, RES_LDS, false>(p, W, ldw, s);
-    if constexpr (V == 12) return p.orientation ? launch_one<V, BITS, RBITS, RES_SPLIT, true>(p, W, ldw, s) : launch_one<V, BITS, RBITS, RES_SPLIT, false>(p, W, ldw, s);
-    if constexpr (V == 8) return p.orientation ? launch_one<V, BITS, RBITS, RES_MEM, true>(p, W, ldw, s) : launch_one<V, BITS, RBITS, RES_MEM, false>(p, W, ldw, s);
+      return p.orientation ? launch_one<V, BITS, RBITS, RES_LDS, true>(p, W, ldw, s, product_tokens) : launch_one<V, BITS, RBITS, RES_LDS, false>(p, W, ldw, s, product_tokens);
+    if constexpr (V == 12) return p.orientation ? launch_one<V, BITS, RBITS, RES_SPLIT, true>(p, W, ldw, s, product_tokens) : launch_one<V, BITS, RBITS, RES_SPLIT, false>(p, W, ldw, s, product_tokens);
+    if constexpr (V == 8) return p.orientation ? launch_one<V, BITS, RBITS, RES_MEM, true>(p, W, ldw, s, product_tokens) : launch_one<V, BITS, RBITS, RES_MEM, false>(p, W, ldw, s, product_tokens);
     return VQ_ERR_UNSUPPORTED;
   }
 }
@@ -507,12 +613,12 @@ int launch_pair(const Params &p, __half *W, long long ldw, hipStream_t s) {
 }  // namespace
 
 // The whole matrix in stored column order; VQ_ERR_UNSUPPORTED for (v, index width) pairs without a compiled kernel.
-int launch_dequant_tables(const Params &p, __half *W, long long ldw, hipStream_t s) {
+int launch_dequant_tables(const Params &p, __half *W, long long ldw, hipStream_t s, int product_tokens) {
   if (switches().dequant == 'g' || p.perm || (p.Q && p.v_out != 4)) return VQ_ERR_UNSUPPORTED;
   const long long limit = 1LL << 31;                       // 32-bit byte offsets, with room for what lies past the ends
   if (p.S * p.stride >= limit || (p.k_res && p.S * p.stride_res >= limit)) return VQ_ERR_UNSUPPORTED;
   const int rb = p.k_res ? p.bits_res : p.bits;
-#define VQ_PAIR(V, BITS, RBITS) if (p.v == V && p.bits == BITS && rb == RBITS) return launch_pair<V, BITS, RBITS>(p, W, ldw, s);
+#define VQ_PAIR(V, BITS, RBITS) if (p.v == V && p.bits == BITS && rb == RBITS) return launch_pair<V, BITS, RBITS>(p, W, ldw, s, product_tokens);
   VQ_PAIR(2, 4, 4) VQ_PAIR(4, 8, 8) VQ_PAIR(6, 8, 8) VQ_PAIR(8, 8, 8) VQ_PAIR(4, 12, 12) VQ_PAIR(6, 12, 12) VQ_PAIR(6, 12, 8) VQ_PAIR(8, 12, 12)
   VQ_PAIR(12, 12, 12) VQ_PAIR(8, 16, 16) VQ_PAIR(8, 16, 8) VQ_PAIR(8, 8, 16)
 #undef VQ_PAIR

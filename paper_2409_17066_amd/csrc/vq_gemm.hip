@@ -271,12 +271,12 @@ static int launch_gemm_centroids(const Params &p, const __half *X, long long ldx
   Params q = p;
   q.scale = q.bias = nullptr;
   q.cb_res = nullptr; q.idx_res = nullptr; q.k_res = 0; q.stride_res = 0;
-  int rc = launch_dequant(q, C, p.in_features, s);
+  int rc = launch_dequant(q, C, p.in_features, s, tokens);
   if (rc == VQ_OK && p.k_res) {
     // the residual table as a layer of its own, with room for outlier columns but none
     q.cb = p.cb_res; q.k = p.k_res; q.idx = p.idx_res; q.bits = p.bits_res; q.stride = p.stride_res;
     q.cb_out = nullptr; q.idx_out = nullptr; q.Q = q.S_out = 0;
-    rc = launch_dequant(q, R, p.in_features, s);
+    rc = launch_dequant(q, R, p.in_features, s, tokens);
   }
   return rc == VQ_OK ? launch_gemm_dense(p, X, ldx, tokens, Y, ldy, C, p.in_features, s, xsum, p.k_res ? (unsigned)matrix_bytes(p) : 0u) : rc;
 }
@@ -372,7 +372,7 @@ int launch_gemm(const Params &p, const __half *X, long long ldx, int tokens, __h
   if (rows) return launch_gemm_rows(p, X, ldx, tokens, Y, ldy, have_ws ? workspace : nullptr, have_ws ? workspace_bytes : 0, s);
   if (forced != 'g' && forced != 'f' && have_ws) {
     __half *Wd = static_cast<__half *>(workspace);
-    int rc = launch_dequant(p, Wd, p.in_features, s);
+    int rc = launch_dequant(p, Wd, p.in_features, s, tokens);
     if (rc == VQ_OK) rc = launch_gemm_dense(p, X, ldx, tokens, Y, ldy, Wd, p.in_features, s);
     if (rc != VQ_ERR_UNSUPPORTED) return rc;
   }

@@ -170,6 +170,24 @@ def test_prefill_without_workspace_on_the_v6_layers(gpu_lib, layers, cfg, name, 
     _matmul_ok(Y[:, torch.from_numpy(rows.astype(np.int64)).cuda()], oracle.gemm(L, x, rows=rows), "cfg%d %s T=%d on the fly" % (cfg, name, tokens))
 
 
+@pytest.mark.parametrize("out,inp,k", [(14341, 4104, 65536), (7371, 8200, 65530), (20480, 3072, 40000)])
+def test_long_prompts_of_the_v8_setting_restore_the_same_weights(gpu_lib, out, inp, k):
+    """In front of a product of many tokens a layer of v = 8 with a table beyond LDS is restored by a kernel of its own: the weights that it
+    leaves in the workspace are vq_dequant's, bit for bit (which the oracle checks elsewhere, and here on a few rows)."""
+    import torch
+    L = s.make_layer(4, "pieces", out, inp, 8, k)
+    dl = gpu_lib.DeviceLayer(L)
+    size = gpu_lib.vq_gemm_fast_workspace_bytes(dl.desc, 1024)
+    ws = torch.full((size,), 0xFF, dtype=torch.uint8, device="cuda")
+    x = torch.randn((1024, inp), device="cuda").half()
+    Y = gpu_lib.gemm(dl, x, workspace=ws)
+    W = gpu_lib.dequant(dl)
+    torch.cuda.synchronize()
+    assert torch.equal(ws[: out * inp * 2].view(torch.int16), W.view(torch.int16).reshape(-1))
+    rows = np.array([0, 1, out // 2, out - 1], dtype=np.int32)
+    _matmul_ok(Y[:, torch.from_numpy(rows.astype(np.int64)).cuda()][:64], oracle.gemm(L, x[:64].cpu().numpy(), rows=rows), "v8 %d x %d, 1024 tokens" % (out, inp))
+
+
 # Rows for which a workgroup of the matrix-core kernel has 4, 5, 6 and 7 blocks of sixteen (256 compute units): one chunk over the tables
 # where its partial sums do not fit beside them, one beside them, and two chunks of four and three blocks.
 @pytest.mark.parametrize("out,k_res,outliers", [(12300, 4096, 0), (16400, 0, 0), (20480, 256, 8), (24560, 4096, 8), (24561, 256, 0), (24592, 4096, 0)])
