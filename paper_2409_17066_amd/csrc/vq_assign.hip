@@ -6,7 +6,7 @@
 // subtraction, per element one subtraction and one fused multiply-add into a sum that starts at +0, elements in
 // ascending order, the first of equal distances wins.
 //
-// Three kernels.  assign_screen_kernel (v <= 13, tables of 64 entries and more) finds for every vector the 16 centroids among
+// Three kernels.  assign_screen_kernel (v <= 13, tables of 64 entries and more) finds for every vector the 16 or 32 centroids among
 // which the nearest one must be, on the matrix cores, and computes the distances as defined for those only.  The other two
 // compute every distance on the vector ALUs, 2 v + 3 instructions per (vector, centroid) pair: assign_short_kernel for
 // tables of fewer entries, assign_kernel for longer vectors.
@@ -76,22 +76,28 @@ struct Place {
   }
 };
 
-// The indices of `count` items (whole segments) from number x0 of a wave's place on, a lane per dword.
-__device__ __forceinline__ void pack_items(const Vectors &a, const Place &place, int x0, int count, int seg_len, int bits, const unsigned *codes, int lane) {
-  const int dwords = count * bits / 32, per_seg = seg_len * bits / 32;
-  for (int d = lane; d < dwords; d += 64) {
-    const int sg = d / per_seg;
-    int o, p;
-    place.item(x0 + sg * seg_len, o, p);
-    const long long at = (long long)(p / seg_len) * per_seg + (d - sg * per_seg);
-    if (o >= a.rows || 32 * at >= (long long)a.per_row * bits) continue;
-    unsigned w = 0;
-    for (int i = 32 * d / bits; i * bits < 32 * d + 32; ++i) {         // (past a row's end the codes are zero)
-      const int sh = i * bits - 32 * d;
-      w |= sh >= 0 ? codes[i] << sh : codes[i] >> -sh;
-    }
-    store_dword(a, reinterpret_cast<unsigned *>(a.idx + (long long)o * a.idx_stride) + at, at, w);
+// The dword of packed indices that a lane writes out of up to 64 items (whole segments; an index has 16 bits at most): the segment's
+// first item, the dword's number in the segment, the first code with bits in it and where that code starts.
+struct PackLane {
+  int item, word, code, shift, seg_shift;
+  __device__ PackLane(int lane, int seg_len, int bits) {
+    const int per_seg = seg_len * bits / 32, sg = lane / per_seg;
+    item = sg * seg_len; word = lane - sg * per_seg; code = 32 * lane / bits; shift = code * bits - 32 * lane;
+    seg_shift = __builtin_ctz(seg_len);                      // 8, 16 or 32
   }
+};
+
+// The indices of a wave's first `count` items, a lane per dword.
+__device__ __forceinline__ void pack_items(const Vectors &a, const Place &place, int count, const PackLane &lay, int bits, const unsigned *codes, int lane) {
+  if (lane >= count * bits / 32) return;
+  int o, p;
+  place.item(lay.item, o, p);
+  const long long at = (long long)(p >> lay.seg_shift) * (bits << lay.seg_shift >> 5) + lay.word;
+  if (o >= a.rows || 32 * at >= (long long)a.per_row * bits) return;
+  unsigned w = 0;
+  for (int i = lay.code, sh = lay.shift; sh < 32; ++i, sh += bits)          // (past a row's end the codes are zero)
+    w |= sh >= 0 ? codes[i] << sh : codes[i] >> -sh;
+  store_dword(a, reinterpret_cast<unsigned *>(a.idx + (long long)o * a.idx_stride) + at, at, w);
 }
 
 // The distance of the definition from t to one centroid.
@@ -105,6 +111,52 @@ __device__ __forceinline__ float distance(const float (&t)[V], Get element) {
     d = __fmaf_rn(diff, diff, d);
   }
   return d;
+}
+
+// The same to a centroid as the screening planes hold it, eight binary16 elements in 16 bytes (the second 16 bytes: elements 8 on).
+// (Inline assembly, as the compiler makes a conversion and a subtraction of the fused operation.)
+template <int V>
+__device__ __forceinline__ float distance(const float (&t)[V], const half8 &c0, const half8 &c1) {
+  const uint4v w0 = __builtin_bit_cast(uint4v, c0), w1 = __builtin_bit_cast(uint4v, c1);
+  float d = 0.0f;
+#pragma unroll
+  for (int j = 0; j < V; ++j) {
+    const unsigned w = j < 8 ? w0[j / 2 & 3] : w1[j / 2 & 3];
+    float diff;
+    if (j & 1) asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(diff) : "v"(w), "v"(t[j]));
+    else asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(diff) : "v"(w), "v"(t[j]));
+    d = __fmaf_rn(diff, diff, d);
+  }
+  return d;
+}
+
+// Entry i of a table in memory as the planes hold one: V elements, zeros from len on, in loads of as many bytes as divide a row where
+// those are aligned (`whole`).
+template <int V> constexpr int load_bytes() { return V % 8 == 0 ? 16 : V % 4 == 0 ? 8 : V % 2 == 0 ? 4 : 2; }
+
+template <int V>
+__device__ __forceinline__ void load_entry(const __half *codebook, int i, int stride, int len, bool whole, half8 &c0, half8 &c1) {
+  constexpr int N = load_bytes<V>() / 2;
+  typedef _Float16 part __attribute__((ext_vector_type(N)));
+  const __half *from = codebook + (long long)i * stride;
+  _Float16 c[16] = {};
+  if (whole) {
+#pragma unroll
+    for (int x = 0; x < V / N; ++x) {
+      const part y = reinterpret_cast<const part *>(from)[x];
+#pragma unroll
+      for (int j = 0; j < N; ++j) c[x * N + j] = y[j];
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < V; ++j) c[j] = __builtin_bit_cast(_Float16, from[j]);
+  }
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    if (j < V && len < V) c[j] = j < len ? c[j] : (_Float16)0.0f;
+    if (j < 8) c0[j] = c[j];
+    else c1[j & 7] = c[j];
+  }
 }
 
 // The lanes' candidates meet: the smaller distance, else the smaller index.  Distances are sums of squares, so their bits order
@@ -122,7 +174,8 @@ __device__ __forceinline__ void wave_arg_min(float &d, unsigned &i) {
 // split into three binary16 parts; the vector's column of operand B holds t and the matching negative power of two.  A t that is
 // a difference W - B is no binary16 number: it is scaled and split into two (v <= 6: both in one instruction's 16 k slots,
 // against the same elements twice; longer vectors: a second instruction with the same A).  A lane sees 16 rows of every result:
-// it keeps the largest score of any such block of 16, that block's number, and the largest score of every other block.
+// it keeps the largest score of any such block of 16 (of two results, 32, with tables of 4096 entries and more), that block's number,
+// and the largest score of every other block.
 //
 // Scores carry rounding errors, so the winning block is only trusted when it wins by more than they can be.  With T = |t|, the
 // nearest centroid and whichever centroid has the largest computed score have norms of at most R = T + sqrt(d), d their
@@ -133,10 +186,18 @@ __device__ __forceinline__ void wave_arg_min(float &d, unsigned &i) {
 // -- about 0.3 % with 4096 Gaussian entries --, and all of them when a table has entries that are not finite or huge, are
 // compared with every centroid by the wave together.
 //
-// What bounds it: two blocks of 16 scores (one result) cost 32 matrix-core clocks and 12 vector instructions of 4 clocks, 0.75
-// instructions per pair instead of 2 v + 3, and the two kinds of instruction hardly overlap on a SIMD (four waves of each, apart
-// 0.32 and 0.28 ms, together 0.55 ms).  Measured: 11008 x 4096, v = 6, k = 4096: 8.42 -> 1.15 ms, of which the distances of the
-// winning blocks, loads and packing are about a third; 1947 x 6656, v = 12: 0.23 ms; 107 x 7160, v = 8, k = 65536: 0.44 ms.
+// What bounds it: the vector ALUs, which are busy 86 % of the clocks (at 1.9 GHz: both units' power).  A result (two blocks of
+// 16 scores) costs 32 matrix-core clocks and 12 vector instructions of 4 clocks, 10 with blocks of 32; what a vector costs beside the search
+// -- operands, distances of the winning block, the test, packing -- is about a fifth of the time at k = 4096 and most of it at 256.  So:
+//  - the products of one result run while the largest score of the one before is found;
+//  - behind the search a lane has a vector to itself, its operands and results swapped between the two halves of the wave
+//    (one instruction a register) instead of both lanes of a vector doing the same;
+//  - a workgroup's waves draw their vectors by ticket: with equal shares the waves that a SIMD prefers were done early and on average
+//    2.6 of its four were left;
+//  - blocks of 32 from 4096 entries on: 8 instructions fewer for every 64 entries and 64 vectors, 16 distances of 15 instructions more
+//    (k = 4096: 995 -> 948 us; at 2048 the two are equal).
+// Measured, 11008 x 4096, v = 6: k = 4096 1161 -> 971 us, k = 256 263 -> 156 us; every distance on the vector ALUs 8.42 ms.
+// 4096 x 4096, v = 8, k = 65536, entries read whole where they are aligned instead of by element: 5.33 -> 4.74 ms.
 constexpr int WAVES = 16;
 constexpr int SCREEN_ROWS = 4096;                       // table rows in LDS at once: two planes of 16 bytes each
 constexpr int screen_instructions(int v, bool base) { return base && v > 6 ? 2 : 1; }
@@ -146,7 +207,7 @@ struct TableScale { int f; float h_max; bool fine; };
 
 // Centroids [c0, c0 + rows) into the two planes, rows past the table repeating its last entry; returns the scale.
 template <int V>
-__device__ TableScale stage_screen_table(const __half *__restrict__ codebook, int stride, int len, int k, int c0, int rows, half8 *plane, float *red) {
+__device__ TableScale stage_screen_table(const __half *__restrict__ codebook, int stride, int len, int k, int c0, int rows, bool whole, half8 *plane, float *red) {
   constexpr int PER = SCREEN_ROWS / (WAVES * 64);
   const int tid = threadIdx.x, wave = tid >> 6;
   float h[PER], most = 0.0f;
@@ -156,12 +217,11 @@ __device__ TableScale stage_screen_table(const __half *__restrict__ codebook, in
     const int e = tid + r * (WAVES * 64);
     h[r] = 0.0f;
     if (e < rows) {
-      const __half *src = codebook + (long long)min(c0 + e, k - 1) * stride;
+      half8 e0, e1;
+      load_entry<V>(codebook, min(c0 + e, k - 1), stride, len, whole, e0, e1);
       _Float16 c[V];
 #pragma unroll
-      for (int j = 0; j < V; ++j) c[j] = __builtin_bit_cast(_Float16, src[j]);
-#pragma unroll
-      for (int j = 0; j < V; ++j) c[j] = j < len ? c[j] : (_Float16)0.0f;
+      for (int j = 0; j < V; ++j) c[j] = j < 8 ? e0[j & 7] : e1[j & 7];
       float q = 0.0f;
 #pragma unroll
       for (int j = 0; j < V; ++j) q = __fmaf_rn((float)c[j], (float)c[j], q);
@@ -231,6 +291,40 @@ __device__ __forceinline__ void load_vector(const Vectors &a, int o, int u, bool
   }
 }
 
+template <int V>
+__device__ __forceinline__ void load_halves(const Vectors &a, int o, int u, bool on, _Float16 (&t)[V]) {
+  const long long at = on ? (long long)o * a.row_step + (long long)u * a.vec_step : 0;
+  const _Float16 *from = reinterpret_cast<const _Float16 *>(a.W) + at;
+  if (a.elem_step == 1 && a.len == V) {
+#pragma unroll
+    for (int j = 0; j < V; ++j) t[j] = from[j];
+  } else {
+#pragma unroll
+    for (int j = 0; j < V; ++j) t[j] = from[(j < a.len ? j : 0) * a.elem_step];
+#pragma unroll
+    for (int j = 0; j < V; ++j) t[j] = j < a.len ? t[j] : (_Float16)0.0f;
+  }
+#pragma unroll
+  for (int j = 0; j < V; ++j) t[j] = on ? t[j] : (_Float16)0.0f;
+}
+
+// The upper 32 lanes of x for the lower ones of y
+__device__ __forceinline__ void swap_halves(unsigned &x, unsigned &y) {
+  const auto z = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+  x = z[0]; y = z[1];
+}
+__device__ __forceinline__ void swap_halves(float &x, float &y) {
+  unsigned i = __float_as_uint(x), j = __float_as_uint(y);
+  swap_halves(i, j);
+  x = __uint_as_float(i); y = __uint_as_float(j);
+}
+__device__ __forceinline__ void swap_halves(half8 &x, half8 &y) {
+  uint4v i = __builtin_bit_cast(uint4v, x), j = __builtin_bit_cast(uint4v, y);
+#pragma unroll
+  for (int d = 0; d < 4; ++d) { unsigned p = i[d], q = j[d]; swap_halves(p, q); i[d] = p; j[d] = q; }
+  x = __builtin_bit_cast(half8, i); y = __builtin_bit_cast(half8, j);
+}
+
 // The power of two that scales a difference's elements to below 2^14 (as far as the |c|^2 slots' factor allows).
 template <int V>
 __device__ __forceinline__ int vector_scale(const float (&t)[V], int f) {
@@ -252,9 +346,9 @@ __device__ __forceinline__ void set_slots(half8 &b, int half, _Float16 factor) {
   else if (half) { b[5] = factor; b[6] = factor; b[7] = factor; }
 }
 
-// NT: tiles of 32 vectors a wave holds.  SPLIT: `split` waves (a power of two) share a tile of vectors, each taking its share
+// NT: tiles of 32 vectors a wave holds.  WIDE: blocks of 32 centroids.  SPLIT: `split` waves (a power of two) share a tile of vectors, each taking its share
 // of the table.  The first last_wgs workgroups take `last`, the others `first`.
-template <int V, bool BASE, int NT, bool SPLIT>
+template <int V, bool BASE, int NT, bool SPLIT, bool WIDE>
 __global__ __launch_bounds__(WAVES * 64, 4) void assign_screen_kernel(Vectors first, Vectors last, int last_wgs, const __half *__restrict__ codebook,
                                                                        int stride, int k, int bits, int seg_len, int split) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -266,26 +360,42 @@ __global__ __launch_bounds__(WAVES * 64, 4) void assign_screen_kernel(Vectors fi
   int *list = reinterpret_cast<int *>(meet + (SPLIT ? 3 * WAVES * 64 : 0));           // tables of several chunks: how many, then which
   constexpr bool TWO = screen_instructions(V, BASE) == 2;
   constexpr int TU = 2;                                         // tiles of the table taken at once
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 31, half = lane >> 5;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = lane & 31, half = lane >> 5;
   const bool is_last = (int)blockIdx.x < last_wgs;
   const Vectors a = is_last ? last : first;
   const int n_chunks = (k + SCREEN_ROWS - 1) / SCREEN_ROWS;
   const long long items = items_of(a, seg_len);
-  const int groups = SPLIT ? WAVES / split : WAVES, group = SPLIT ? wave / split : wave, part = SPLIT ? wave % split : 0;
+  const int groups = SPLIT ? WAVES / split : WAVES, part = SPLIT ? wave % split : 0;
   const int block_items = groups * NT * 32;
   const int n_blocks = (int)((items + block_items - 1) / block_items);
   unsigned *my_codes = codes + wave * (NT * 32);
+  const PackLane pack(lane, seg_len, bits);
+  const bool whole = stride == V && reinterpret_cast<size_t>(codebook) % load_bytes<V>() == 0;
   TableScale ts = {0, 0.0f, true};
-  if (n_chunks == 1) ts = stage_screen_table<V>(codebook, stride, a.len, k, 0, rows_lds, plane, red);
+  int *ticket = list;
+  const bool tickets = !SPLIT && n_chunks == 1;
+  if (tickets && threadIdx.x == 0) *ticket = 0;           // (seen by all behind the barriers of the next line)
+  if (n_chunks == 1) ts = stage_screen_table<V>(codebook, stride, a.len, k, 0, rows_lds, whole, plane, red);
 
   const int wg0 = is_last ? blockIdx.x : blockIdx.x - last_wgs, wgs = is_last ? last_wgs : gridDim.x - last_wgs;
-  for (int blk = wg0; blk < n_blocks; blk += wgs) {
+  for (int turn = 0;; ++turn) {
+    int blk = wg0 + turn * wgs, group = SPLIT ? wave / split : wave;
+    if (tickets) {
+      const int t = __builtin_amdgcn_readfirstlane(lane == 0 ? atomicAdd(ticket, 1) : 0);
+      blk = wg0 + t / WAVES * wgs; group = t % WAVES;
+    }
+    if (blk >= n_blocks) break;
     const long long g0 = (long long)blk * block_items + group * (NT * 32);
     const Place place(a, g0, items, seg_len);
     half8 b[NT], b_lo[TWO ? NT : 1];
+    // A lane looks after one vector: number `lane` of two tiles' 64, or n of one tile's 32, which both of its lanes then hold
+    const int x = NT == 2 ? lane : n;
+    int o, p;
+    place.item(x, o, p);
+    const bool on = o < a.rows && p < a.per_row, live = on && (NT == 2 || half == 0);
     constexpr bool KEEP = BASE && V <= 6;                    // (short enough to stay in registers across the search)
-    float kept[KEEP ? NT : 1][V];
-    int e_of[BASE ? NT : 1];
+    float kept[KEEP ? V : 1];
+    int e = 0;
     float b1[NT], b2[NT];
     int id[NT];
     bool trusted = true;                                     // (of this lane's vectors: every chunk's factor was in range)
@@ -293,99 +403,122 @@ __global__ __launch_bounds__(WAVES * 64, 4) void assign_screen_kernel(Vectors fi
     for (int ch = 0; ch < n_chunks; ++ch) {
       if (n_chunks > 1) {
         __syncthreads();
-        ts = stage_screen_table<V>(codebook, stride, a.len, k, ch * SCREEN_ROWS, rows_lds, plane, red);
+        ts = stage_screen_table<V>(codebook, stride, a.len, k, ch * SCREEN_ROWS, rows_lds, whole, plane, red);
       }
       h_max = fmaxf(h_max, ts.h_max);
       trusted = trusted && ts.fine;
       if (ch == 0) {
-#pragma unroll
-        for (int u = 0; u < NT; ++u) {
-          int o, p;
-          place.item(u * 32 + n, o, p);
+        // the vector's operands in the lower lanes (lo) and in the upper ones (up), of its first and second part
+        half8 lo = {}, up = {}, lo2 = {}, up2 = {};
+        if constexpr (BASE) {
           float t[V];
-          load_vector<V, BASE>(a, o, p, o < a.rows && p < a.per_row, t);
+          load_vector<V, BASE>(a, o, p, on, t);
           if constexpr (KEEP) {
 #pragma unroll
-            for (int j = 0; j < V; ++j) kept[u][j] = t[j];
+            for (int j = 0; j < V; ++j) kept[j] = t[j];
           }
-          int e = 0;
-          if constexpr (BASE) { e = vector_scale<V>(t, ts.f); e_of[u] = e; }
-          half8 hi = {}, lo = {};
+          e = vector_scale<V>(t, ts.f);
 #pragma unroll
           for (int j = 0; j < V; ++j) {
-            const float x = BASE ? ldexpf(t[j], e) : t[j];
-            const _Float16 xh = (_Float16)x, xl = BASE ? (_Float16)(x - (float)xh) : (_Float16)0.0f;     // (without a base: x is a binary16 number)
-            if constexpr (V <= 6) hi[j] = half ? xl : xh;
-            else if ((j >= 8) == (half != 0)) { hi[j & 7] = xh; lo[j & 7] = xl; }
+            const float y = ldexpf(t[j], e);
+            const _Float16 yh = (_Float16)y, yl = (_Float16)(y - (float)yh);
+            if constexpr (V <= 6) { lo[j] = yh; up[j] = yl; }
+            else if (j < 8) { lo[j & 7] = yh; lo2[j & 7] = yl; }
+            else { up[j & 7] = yh; up2[j & 7] = yl; }
           }
-          b[u] = hi;
-          if constexpr (TWO) b_lo[u] = lo;
-          b1[u] = -__builtin_inff(); b2[u] = -__builtin_inff(); id[u] = 0;
+        } else {
+          _Float16 t[V];
+          load_halves<V>(a, o, p, on, t);
+#pragma unroll
+          for (int j = 0; j < V; ++j) {
+            if (j < 8) lo[j & 7] = t[j];
+            else up[j & 7] = t[j];
+          }
         }
+        if constexpr (NT == 2) {
+          swap_halves(lo, up);
+          b[0] = lo; b[NT - 1] = up;
+          if constexpr (TWO) { swap_halves(lo2, up2); b_lo[0] = lo2; b_lo[NT - 1] = up2; }
+        } else {
+          b[0] = half ? up : lo;
+          if constexpr (TWO) b_lo[0] = half ? up2 : lo2;
+        }
+#pragma unroll
+        for (int u = 0; u < NT; ++u) { b1[u] = -__builtin_inff(); b2[u] = -__builtin_inff(); id[u] = 0; }
       }
       if (ch == 0 || n_chunks > 1) {
+        const _Float16 factor = slot_factor(e, ts.f);
+        trusted = trusted && factor != (_Float16)0.0f;
+        if constexpr (BASE && NT == 2) {
+          unsigned f0 = __builtin_bit_cast(unsigned short, factor), f1 = f0;
+          swap_halves(f0, f1);
+          set_slots<V>(b[0], half, __builtin_bit_cast(_Float16, (unsigned short)f0));
+          set_slots<V>(b[NT - 1], half, __builtin_bit_cast(_Float16, (unsigned short)f1));
+        } else {
 #pragma unroll
-        for (int u = 0; u < NT; ++u) {
-          const _Float16 factor = slot_factor(BASE ? e_of[u] : 0, ts.f);
-          trusted = trusted && factor != (_Float16)0.0f;
-          set_slots<V>(b[u], half, factor);
+          for (int u = 0; u < NT; ++u) set_slots<V>(b[u], half, factor);
         }
       }
       const int tiles = (min(k - ch * SCREEN_ROWS, SCREEN_ROWS) + 31) >> 5, rounds = (tiles + TU - 1) / TU;
-      const int step = SPLIT ? split : 1, tile0 = ch * (SCREEN_ROWS / 32);
+      const int step = SPLIT ? split : 1, round0 = ch * (SCREEN_ROWS / 32 / TU);
       const half8 *mine = plane + (half ? rows_lds : 0) + n;
-      half8 cur[TU];
+      // A round's two tiles: the products of one run while the largest score of the other is found
+      float16v s0[NT], s1[NT];
+      auto products = [&](half8 c, float16v (&s)[NT]) {
 #pragma unroll
-      for (int x = 0; x < TU; ++x) cur[x] = mine[(min(part, rounds - 1) * TU + x) * 32];
-      for (int round = part; round < rounds; round += step) {
-        half8 next[TU];
+        for (int u = 0; u < NT; ++u) {
+          float16v z;
 #pragma unroll
-        for (int x = 0; x < TU; ++x) next[x] = mine[(min(round + step, rounds - 1) * TU + x) * 32];
-        float16v s[TU][NT];
-#pragma unroll
-        for (int x = 0; x < TU; ++x)
-#pragma unroll
-          for (int u = 0; u < NT; ++u) {
-            float16v z;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) z[r] = 0.0f;
-            s[x][u] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cur[x], b[u], z, 0, 0, 0);
-            if constexpr (TWO) s[x][u] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cur[x], b_lo[u], s[x][u], 0, 0, 0);
-          }
-#pragma unroll
-        for (int x = 0; x < TU; ++x)
-#pragma unroll
-          for (int u = 0; u < NT; ++u) {
-            auto max3 = [](float p_, float q_, float r_) { return fmaxf(fmaxf(p_, q_), r_); };
-            const float16v &v = s[x][u];
-            const float m0 = max3(v[0], v[1], v[2]), m1 = max3(v[3], v[4], v[5]), m2 = max3(v[6], v[7], v[8]);
-            const float m3 = max3(v[9], v[10], v[11]), m4 = max3(v[12], v[13], v[14]);
-            const float m = max3(max3(m0, m1, m2), max3(m3, m4, v[15]), m0);
-            const bool up = m > b1[u];
-            b2[u] = __builtin_amdgcn_fmed3f(b1[u], b2[u], m);
-            id[u] = up ? tile0 + round * TU + x : id[u];
-            b1[u] = up ? m : b1[u];
-          }
-#pragma unroll
-        for (int x = 0; x < TU; ++x) {
-          asm volatile("" : "+v"(next[x]));                  // (keeps the reads up there: the compiler would turn them into reads of `cur`)
-          cur[x] = next[x];
+          for (int r = 0; r < 16; ++r) z[r] = 0.0f;
+          s[u] = __builtin_amdgcn_mfma_f32_32x32x16_f16(c, b[u], z, 0, 0, 0);
+          if constexpr (TWO) s[u] = __builtin_amdgcn_mfma_f32_32x32x16_f16(c, b_lo[u], s[u], 0, 0, 0);
         }
+      };
+      auto max3 = [](float p_, float q_, float r_) { return fmaxf(fmaxf(p_, q_), r_); };
+      auto largest = [&](const float16v &v, float m) {
+        const float m0 = max3(v[0], v[1], v[2]), m1 = max3(v[3], v[4], v[5]), m2 = max3(v[6], v[7], v[8]);
+        const float m3 = max3(v[9], v[10], v[11]), m4 = max3(v[12], v[13], v[14]);
+        return max3(max3(m0, m1, m2), max3(m3, m4, v[15]), m);
+      };
+      auto take = [&](int u, float m, int number) {
+        const bool up = m > b1[u];
+        b2[u] = __builtin_amdgcn_fmed3f(b1[u], b2[u], m);
+        id[u] = up ? number : id[u];
+        b1[u] = up ? m : b1[u];
+      };
+      auto tile_of = [&](int round, int x) { return mine[(min(round, rounds - 1) * TU + x) * 32]; };
+      half8 c1 = tile_of(part, 1), next = tile_of(part + step, 0);
+      products(tile_of(part, 0), s0);
+      for (int round = part; round < rounds; round += step) {
+        float m[NT];
+        products(c1, s1);
+        c1 = tile_of(round + step, 1);
+#pragma unroll
+        for (int u = 0; u < NT; ++u) {
+          m[u] = largest(s0[u], s0[u][0]);
+          if constexpr (!WIDE) take(u, m[u], (round0 + round) * TU);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        products(next, s0);
+        next = tile_of(round + 2 * step, 0);
+#pragma unroll
+        for (int u = 0; u < NT; ++u) {
+          if constexpr (WIDE) take(u, largest(s1[u], m[u]), round0 + round);
+          else take(u, largest(s1[u], s1[u][0]), (round0 + round) * TU + 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
-    int my_block[NT];
-#pragma unroll
-    for (int u = 0; u < NT; ++u) my_block[u] = 2 * id[u] + half;
     if constexpr (SPLIT) {                                   // the waves of a group meet in their first one
       float *m1 = meet, *m2 = meet + WAVES * 64, *mb = meet + 2 * WAVES * 64;
-      m1[wave * 64 + lane] = b1[0]; m2[wave * 64 + lane] = b2[0]; mb[wave * 64 + lane] = __int_as_float(my_block[0]);
+      m1[wave * 64 + lane] = b1[0]; m2[wave * 64 + lane] = b2[0]; mb[wave * 64 + lane] = __int_as_float(id[0]);
       __syncthreads();
       if (part == 0) {
         for (int w = 1; w < split; ++w) {
           const float o1 = m1[(wave + w) * 64 + lane], o2 = m2[(wave + w) * 64 + lane];
           const int ob = __float_as_int(mb[(wave + w) * 64 + lane]);
           b2[0] = fmaxf(fminf(b1[0], o1), fmaxf(b2[0], o2));
-          if (o1 > b1[0]) { b1[0] = o1; my_block[0] = ob; }
+          if (o1 > b1[0]) { b1[0] = o1; id[0] = ob; }
         }
       }
       __syncthreads();
@@ -395,42 +528,47 @@ __global__ __launch_bounds__(WAVES * 64, 4) void assign_screen_kernel(Vectors fi
       __syncthreads();
     }
 
-    // the distances as defined, for the 16 centroids of the winning block: eight per lane, the two lanes of a vector then meet
-    const float c_max = __builtin_amdgcn_sqrtf(2.0f * h_max) * 1.001f;
-#pragma unroll
-    for (int u = 0; u < NT; ++u) {
-      if (part != 0) break;
-      __builtin_amdgcn_sched_barrier(0);                     // (one tile's vectors in registers at a time)
-      int o, p;
-      place.item(u * 32 + n, o, p);
-      const bool live = o < a.rows && p < a.per_row;
+    // the distances as defined, for the centroids of the winning block: in the vector's lane, or half of them in each of its two lanes
+    if (part == 0) {
       float t[V];
       if constexpr (KEEP) {
 #pragma unroll
-        for (int j = 0; j < V; ++j) t[j] = kept[u][j];
+        for (int j = 0; j < V; ++j) t[j] = kept[j];
       } else if constexpr (BASE) {
-        load_vector<V, BASE>(a, o, p, live, t);
-      } else {                                               // the operand still holds the vector: elements 0 .. 7 in the lower lanes
-        const uint4v mine = __builtin_bit_cast(uint4v, b[u]);
+        load_vector<V, BASE>(a, o, p, on, t);
+      } else {                                               // the operands still hold the vectors: elements 0 .. 7 in the lower lanes
+        half8 lo = b[0], up = b[NT - 1];
+        if constexpr (NT == 2) {
+          swap_halves(lo, up);
+        } else {
+          const uint4v mine = __builtin_bit_cast(uint4v, b[0]);
+          uint4v l, h;
 #pragma unroll
-        for (int d = 0; d < (V + 1) / 2; ++d) {
-          const unsigned w = __shfl(d & 2 ? (d & 1 ? mine.w : mine.z) : (d & 1 ? mine.y : mine.x), d < 4 ? n : n + 32, 64);
-          t[2 * d] = __half2float(__ushort_as_half((unsigned short)(w & 0xFFFFu)));
-          if (2 * d + 1 < V) t[2 * d + 1 < V ? 2 * d + 1 : 0] = __half2float(__ushort_as_half((unsigned short)(w >> 16)));
+          for (int d = 0; d < 4; ++d) { l[d] = __shfl(mine[d], n, 64); h[d] = V > 8 ? __shfl(mine[d], n + 32, 64) : 0u; }
+          lo = __builtin_bit_cast(half8, l); up = __builtin_bit_cast(half8, h);
         }
+#pragma unroll
+        for (int j = 0; j < V; ++j) t[j] = (float)(j < 8 ? lo[j & 7] : up[j & 7]);
       }
-      const float other = __shfl_xor(b1[u], 32, 64);
-      const bool keep = b1[u] > other || (b1[u] == other && half == 0);
-      const float best_s = fmaxf(b1[u], other);
-      const float second = fmaxf(fminf(b1[u], other), fmaxf(b2[u], __shfl_xor(b2[u], 32, 64)));
-      const int other_block = __shfl_xor(my_block[u], 32, 64);
-      const int block = keep ? my_block[u] : other_block;
+      // what the lower and the upper lanes found for the vector
+      float s_lo = b1[0], s_up = b1[NT - 1], q_lo = b2[0], q_up = b2[NT - 1];
+      unsigned i_lo = (unsigned)id[0], i_up = (unsigned)id[NT - 1];
+      if constexpr (NT == 2) {
+        swap_halves(s_lo, s_up); swap_halves(q_lo, q_up); swap_halves(i_lo, i_up);
+      } else {
+        const float s = __shfl_xor(b1[0], 32, 64), q = __shfl_xor(b2[0], 32, 64);
+        const unsigned i = (unsigned)__shfl_xor(id[0], 32, 64);
+        if (half) { s_lo = s; q_lo = q; i_lo = i; }
+        else { s_up = s; q_up = q; i_up = i; }
+      }
+      const bool lower = s_lo >= s_up;
+      const float best_s = fmaxf(s_lo, s_up), second = fmaxf(fminf(s_lo, s_up), fmaxf(q_lo, q_up));
       bool sure = trusted;
       {
+        const float c_max = __builtin_amdgcn_sqrtf(2.0f * h_max) * 1.001f;
         float tt = 0.0f;
 #pragma unroll
         for (int j = 0; j < V; ++j) tt = __fmaf_rn(t[j], t[j], tt);
-        const int e = BASE ? e_of[u] : 0;
         const float T = __builtin_amdgcn_sqrtf(tt) * 1.001f, down = BASE ? ldexpf(1.0f, -e) : 1.0f, q = 0x1p-12f, qt = 0x1p-12f * down;
         const float dist = fmaxf(0.0f, tt - 2.0f * best_s * down) + 0x1p-13f * (tt + c_max * c_max);
         const float R = T + __builtin_amdgcn_sqrtf(dist) * 1.001f;
@@ -439,51 +577,65 @@ __global__ __launch_bounds__(WAVES * 64, 4) void assign_screen_kernel(Vectors fi
         const float gap = (best_s - second) * down;
         sure = sure && gap > eps;                            // (false when anything is not a number)
       }
+      // rows of a lane's results: registers r & 3 of quads of rows 8 apart, the upper lanes' quads 4 below
+      // (rows past the table repeat its last entry, which is never preferred to the entry itself)
+      constexpr int MINE = (WIDE ? 32 : 16) * NT / 2;
+      const int row0 = (int)(lower ? i_lo : i_up) * (WIDE ? 64 : 32) + (lower ? 0 : 4) + (NT == 2 ? 0 : half * 16);
       float best = __builtin_inff();
-      unsigned arg = 0u;
+      int nearest = 0;
+      auto consider = [&](float d, int at) {
+        const bool closer = d < best;
+        best = closer ? d : best;
+        nearest = closer ? at : nearest;
+      };
+      if (n_chunks == 1) {
+        const half8 *from = plane + row0, *from2 = from + (V > 8 ? rows_lds : 0);
 #pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        // rows of a lane's results: registers r & 3 of quads of rows 8 apart, the upper lanes' quads 4 below
-        // (rows past the table repeat its last entry, which is never preferred to the entry itself)
-        int row = (block >> 1) * 32 + (block & 1) * 4 + half * 16 + (r & 3) + 8 * (r >> 2);
-        float d;
-        if (n_chunks == 1) {
-          const half8 c0 = plane[row], c1 = plane[V > 8 ? rows_lds + row : row];
-          d = distance<V>(t, [&](int j) -> float { return j < 8 ? (float)c0[j & 7] : (float)c1[j & 7]; });
-        } else {
-          row = min(row, k - 1);
-          const __half *c = codebook + (long long)row * stride;
-          d = distance<V>(t, [&](int j) -> float { const float x = __half2float(c[j < a.len ? j : 0]); return j < a.len ? x : 0.0f; });
+        for (int r = 0; r < MINE; ++r) {
+          const int at = (r & 3) + 8 * (r >> 2);
+          consider(distance<V>(t, from[at], from2[at]), at);
         }
-        if (d < best) { best = d; arg = (unsigned)row; }
+      } else {
+#pragma unroll 1
+        for (int quad = 0; quad < MINE / 4; ++quad) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            half8 c0, c1;
+            load_entry<V>(codebook, min(row0 + r + 8 * quad, k - 1), stride, a.len, whole, c0, c1);
+            consider(distance<V>(t, c0, c1), r + 8 * quad);
+          }
+        }
       }
-      {
+      unsigned arg = best < __builtin_inff() ? (unsigned)min(row0 + nearest, k - 1) : 0u;
+      if constexpr (NT == 1) {
         const float od = __shfl_xor(best, 32, 64);
         const unsigned oa = __shfl_xor(arg, 32, 64);
         if (od < best || (od == best && oa < arg)) { best = od; arg = oa; }
       }
       // vectors whose block is not sure: the wave takes them one at a time, its lanes the centroids in turn
       if (n_chunks > 1) {
-        if (live && !sure && half == 0) list[1 + atomicAdd(&list[0], 1)] = group * (NT * 32) + u * 32 + n;
+        if (live && !sure) list[1 + atomicAdd(&list[0], 1)] = group * (NT * 32) + x;
       } else {
-        for (unsigned long long todo = __ballot(live && !sure && half == 0); todo; todo &= todo - 1) {
+        for (unsigned long long todo = __ballot(live && !sure); todo; todo &= todo - 1) {
           const int w = __builtin_ctzll(todo);
           float tv[V];
 #pragma unroll
           for (int j = 0; j < V; ++j) tv[j] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t[j]), w));
           float bd = __builtin_inff();
           unsigned bi = 0xFFFFFFFFu;
-#pragma unroll 4
-          for (int i = lane; i < rows_lds; i += 64) {
-            const half8 c0 = plane[i], c1 = plane[V > 8 ? rows_lds + i : i];
-            const float d = distance<V>(tv, [&](int j) -> float { return j < 8 ? (float)c0[j & 7] : (float)c1[j & 7]; });
-            if (d < bd) { bd = d; bi = (unsigned)i; }
+          for (int i0 = lane; i0 < rows_lds; i0 += 128) {      // (rows_lds is a multiple of 128)
+#pragma unroll
+            for (int y = 0; y < 2; ++y) {
+              const int i = i0 + 64 * y;
+              const float d = distance<V>(tv, plane[i], plane[V > 8 ? rows_lds + i : i]);
+              if (d < bd) { bd = d; bi = (unsigned)i; }
+            }
           }
           wave_arg_min(bd, bi);
-          if (n == w) arg = bi == 0xFFFFFFFFu ? 0u : bi;       // (no distance below infinity: the first centroid)
+          if (lane == w) arg = bi == 0xFFFFFFFFu ? 0u : bi;    // (no distance below infinity: the first centroid)
         }
       }
-      if (half == 0) my_codes[u * 32 + n] = live ? arg : 0u;
+      if (NT == 2 || half == 0) my_codes[x] = live ? arg : 0u;
     }
     if (n_chunks > 1) {
       // the vectors that are not sure, against the whole table: every wave takes a share of it
@@ -500,12 +652,15 @@ __global__ __launch_bounds__(WAVES * 64, 4) void assign_screen_kernel(Vectors fi
         load_vector<V, BASE>(a, o, p, true, t);
         float bd = __builtin_inff();
         unsigned bi = 0xFFFFFFFFu;
-#pragma unroll 4
-        for (int i0 = from; i0 < to; i0 += 64) {
-          const int i = min(i0 + lane, k - 1);
-          const __half *c = codebook + (long long)i * stride;
-          const float d = distance<V>(t, [&](int j) -> float { const float y = __half2float(c[j]); return j < a.len ? y : 0.0f; });
-          if (d < bd) { bd = d; bi = (unsigned)i; }
+        for (int i0 = from; i0 < to; i0 += 256) {
+          half8 c0[4], c1[4];
+#pragma unroll
+          for (int y = 0; y < 4; ++y) load_entry<V>(codebook, min(i0 + 64 * y + lane, k - 1), stride, a.len, whole, c0[y], c1[y]);
+#pragma unroll
+          for (int y = 0; y < 4; ++y) {
+            const float d = distance<V>(t, c0[y], c1[y]);
+            if (d < bd) { bd = d; bi = (unsigned)min(i0 + 64 * y + lane, k - 1); }
+          }
         }
         wave_arg_min(bd, bi);
         if (lane == 0) { found_d[x * WAVES + wave] = bd; found_i[x * WAVES + wave] = bi; }
@@ -532,7 +687,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void assign_screen_kernel(Vectors fi
         if (o < a.rows && p < a.per_row) scatter_index(a, p, my_codes[x], bits);
       }
     } else {
-      pack_items(a, place, 0, NT * 32, seg_len, bits, my_codes, lane);
+      pack_items(a, place, NT * 32, pack, bits, my_codes, lane);
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
@@ -577,7 +732,7 @@ __global__ __launch_bounds__(SHORT_THREADS) void assign_short_kernel(Vectors fir
   }
   codes[threadIdx.x] = live ? arg : 0u;
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  pack_items(a, place, 0, 64, seg_len, bits, codes + wave0, lane);
+  pack_items(a, place, 64, PackLane(lane, seg_len, bits), bits, codes + wave0, lane);
 }
 
 // Long vectors.  A lane owns `seg` consecutive vectors of a row, seg = 8, 16 or 32 chosen so that they fill whole dwords of
@@ -681,13 +836,13 @@ int launch_short(const Vectors &first, const Vectors &last, const __half *codebo
   return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
 }
 
-template <int V, bool BASE, int NT, bool SPLIT>
+template <int V, bool BASE, int NT, bool SPLIT, bool WIDE>
 int launch_screen_nt(const Vectors &first, const Vectors &last, const __half *codebook, int k, int bits, int split, hipStream_t s) {
-  auto kernel = assign_screen_kernel<V, BASE, NT, SPLIT>;
+  auto kernel = assign_screen_kernel<V, BASE, NT, SPLIT, WIDE>;
   VQ_ALLOW_FULL_LDS(kernel);
   const int seg_len = segment(bits), block_items = WAVES / split * NT * 32;
   const size_t lds = (size_t)screen_rows(k) * 32 + 2 * WAVES * sizeof(float) + WAVES * NT * 32 * sizeof(unsigned) + (SPLIT ? 3 * WAVES * 64 * sizeof(float) : 0) +
-                     (k > SCREEN_ROWS ? (WAVES / split * NT * 32 + 1) * sizeof(int) : 0);
+                     (k > SCREEN_ROWS ? WAVES / split * NT * 32 + 1 : 1) * sizeof(int);
   const long long blocks = (items_of(first, seg_len) + block_items - 1) / block_items;
   long long last_wgs = (items_of(last, seg_len) + block_items - 1) / block_items, wgs = blocks;
   if (blocks > 0x7fffffffLL || last_wgs > 0x7fffffffLL) return VQ_ERR_UNSUPPORTED;
@@ -709,10 +864,12 @@ int launch_screen(const Vectors &first, const Vectors &last, const __half *codeb
   // smaller blocks takes about 0.6 of the time), and with less than one round of those the waves of a workgroup
   // share the table's rows until there is about one
   const long long waves = (long long)cu_count() * WAVES, rounds2 = (tiles + 2 * waves - 1) / (2 * waves), rounds1 = (tiles + waves - 1) / waves;
-  if (10 * rounds2 <= 6 * rounds1) return launch_screen_nt<V, BASE, 2, false>(first, last, codebook, k, bits, 1, s);
+  if (10 * rounds2 <= 6 * rounds1)
+    return k >= SCREEN_ROWS ? launch_screen_nt<V, BASE, 2, false, true>(first, last, codebook, k, bits, 1, s)
+                            : launch_screen_nt<V, BASE, 2, false, false>(first, last, codebook, k, bits, 1, s);
   int split = 1;
   while (split < WAVES && tiles * split * 2 <= waves && split * 128 < min(k, SCREEN_ROWS)) split *= 2;
-  return launch_screen_nt<V, BASE, 1, true>(first, last, codebook, k, bits, split, s);
+  return launch_screen_nt<V, BASE, 1, true, false>(first, last, codebook, k, bits, split, s);
 }
 
 template <int V>

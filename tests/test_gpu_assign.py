@@ -185,3 +185,50 @@ def test_assign_screening_edges(gpu_lib, name):
         torch.cuda.synchronize()
         want = oracle.assign(W, C, base=B, orientation=orientation)
         assert np.array_equal(idx.cpu().numpy(), s.pack_indices(want, oracle.index_bits(k), idx.shape[1])), (name, orientation)
+
+
+# v, k, base, values, table starts at an odd address: waves that hold two tiles of vectors (more than 131072 vectors), whose lanes look
+# after one vector each, in blocks of 16 and (k >= 4096) 32 centroids, with tables of one chunk and of several, in both operand layouts
+TWO_TILES = {
+    "v6_k4096": (6, 4096, False, "normal", False),
+    "v6_k4095_blocks_of_16": (6, 4095, False, "normal", False),
+    "v6_k4097_second_chunk_of_one": (6, 4097, False, "normal", False),
+    "v8_k8200_odd_table": (8, 8200, False, "normal", True),
+    "v12_k4160_base": (12, 4160, True, "normal", False),
+    "v1_k64": (1, 64, False, "normal", False),
+    "v6_k64_base_odd_table": (6, 64, True, "normal", True),
+    "v7_k100_base": (7, 100, True, "normal", False),
+    "v9_k300": (9, 300, False, "normal", False),
+    "v13_k4096_base": (13, 4096, True, "normal", False),
+    "v6_k4096_ties": (6, 4096, True, "ties", False),
+    "v12_k256_subnormal": (12, 256, False, "tiny", False),
+    "v6_k256_not_finite": (6, 256, False, "not finite", False),
+}
+
+
+@pytest.mark.parametrize("name", list(TWO_TILES))
+def test_assign_two_tiles_a_wave(gpu_lib, name):
+    """Sampled rows (blocks of rows) of a large matrix, bit for bit: an index has no tolerance."""
+    import torch
+    v, k, with_base, values, odd = TWO_TILES[name]
+    rows, cols, seed = 905, 150 * v + (1 if v > 1 else 0), 7500 + list(TWO_TILES).index(name)
+    scale = 2e-6 if values == "tiny" else 0.02
+    W, C, B = (s.to_fp16(s.normal(seed + 100 * i, n, scale)) for i, n in enumerate((rows * cols, k * v, rows * cols)))
+    W, C, B = W.reshape(rows, cols), C.reshape(k, v), B.reshape(rows, cols) if with_base else None
+    if values == "ties":
+        C[k // 2:] = C[: k - k // 2][::-1]
+    if values == "not finite":                                 # (a vector without a distance below infinity takes the first entry)
+        C[5, 2], W[0, 7], W[450, 100], W[904, 200] = np.inf, np.inf, np.nan, -np.inf
+    room = torch.zeros(k * v + 1, dtype=torch.float16, device="cuda")
+    Cd = room[1:] if odd else room[:-1]
+    Cd = Cd.view(k, v).copy_(torch.from_numpy(C))
+    Wd, Bd = torch.from_numpy(W).cuda(), torch.from_numpy(B).cuda() if with_base else None
+    for orientation in (0, 1):
+        idx = gpu_lib.assign(Wd, Cd, base=Bd, orientation=orientation)
+        torch.cuda.synchronize()
+        got = idx.cpu().numpy()
+        for at in (0, 450, 904) if orientation == 0 else (0, 450 // v, 904 // v):
+            part = slice(at, at + 1) if orientation == 0 else slice(at * v, min(rows, at * v + v))
+            with np.errstate(all="ignore"):
+                want = oracle.assign(W[part], C, base=B[part] if with_base else None, orientation=orientation)
+            assert np.array_equal(got[at:at + 1], s.pack_indices(want, oracle.index_bits(k), idx.shape[1])), (name, orientation, at)
