@@ -45,7 +45,7 @@ int cu_count();
 //   gemm=g|f|w|r|6|c vq_gemm: generic tile kernel / no restore-then-multiply / restore-then-multiply whenever a workspace is
 //                there / rows through vq_gemv / the on-the-fly kernel for v = 6 layers at every token count / vq_gemm_default: centroids restored
 //                and multiplied wherever that can be done
-//   dense=0|1    the dense product of the restore-then-multiply route: always the smallest / the largest tiles
+//   dense=0|1..9 the dense product of the restore-then-multiply route: always the smallest tiles / the kind of that number (1: the largest)
 //   dequant=g    vq_dequant: generic kernels
 struct Switches {
   char gemv = 0, gemm = 0, dequant = 0;

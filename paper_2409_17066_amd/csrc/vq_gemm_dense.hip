@@ -240,14 +240,22 @@ int launch_tiles(DenseArgs a, hipStream_t s) {
 
 // Tile shapes and what they cost, in microseconds at the clocks that full load leaves: a fixed part per round of workgroups, and per
 // 64-column step with one or two workgroups on a compute unit.  Fitted to 60 random shapes (17 to 2048 tokens, 256 to 11008 channels,
-// 512 to 11008 columns), whose times the sums below meet within 4% on average.
+// 512 to 11008 columns), whose times the sums below meet within 4% on average; the shapes of 64 x 192 in three stages to 192 x 192 to
+// 130 others (45 to 2048 tokens, up to 28672 channels and 13824 columns).  Most products are one or two rounds of workgroups, and what a
+// kind costs is how much of the last round it leaves empty: with the kinds 256 x 256, 256 x 192, 128 x 128, 64 x 192 in two
+// stages, 64 x 128 and 64 x 64 alone the 130 took 2.9 % longer on average, 24 of them 3 to 37 % (1500 x 4096 x 4096: 63.6 -> 49.9 us
+// in 256 tiles of 192 x 128; 900 x 8192 x 8192: 134 -> 116 in 256 of 128 x 256; 700 x 11008 x 4096: 75 -> 63 in 232 of 192 x 192;
+// 200 x 11008 x 4096: 31.3 -> 29.4 in 232 of 64 x 192), and none more than 1.4 % less.  128 x 192 in two stages is not among
+// them: 509 x 11008 x 4096 54.7 -> 50.9 us with W in the caches, but 3 % slower together with the restoring of W where W's memory is not.
 struct TileKind {
   int mb, nb, per_cu;
   float round, step[2];
   int (*launch)(DenseArgs, hipStream_t);
 };
 const TileKind kTiles[] = {
-    {4, 4, 1, 9.9f, {1.12f, 0.0f}, launch_tiles<4, 4, 2, false>},  {4, 3, 1, 7.6f, {0.90f, 0.0f}, launch_tiles<4, 3, 2, false>},
+    {4, 4, 1, 9.9f, {1.12f, 0.0f}, launch_tiles<4, 4, 2, false>},  {2, 4, 1, 5.3f, {0.755f, 0.0f}, launch_tiles<2, 4, 3, false>},
+    {3, 3, 1, 6.2f, {0.752f, 0.0f}, launch_tiles<3, 3, 3, false>}, {3, 2, 1, 5.3f, {0.545f, 0.0f}, launch_tiles<3, 2, 3, false>},
+    {1, 3, 1, 4.0f, {0.375f, 0.0f}, launch_tiles<1, 3, 3, false>}, {4, 3, 1, 7.6f, {0.90f, 0.0f}, launch_tiles<4, 3, 2, false>},
     {2, 2, 1, 4.2f, {0.383f, 0.0f}, launch_tiles<2, 2, 3, false>}, {1, 3, 2, 2.1f, {0.478f, 0.767f}, launch_tiles<1, 3, 2, false>},
     {1, 2, 2, 2.3f, {0.273f, 0.558f}, launch_tiles<1, 2, 3, false>}, {1, 1, 2, 1.2f, {0.190f, 0.384f}, launch_tiles<1, 1, 4, false>},
 };
@@ -263,7 +271,7 @@ float tile_cost(const TileKind &t, int tokens, int out_features, int in_features
 
 bool gemm_dense_applicable(const Params &p) { return p.in_features % 8 == 0; }       // (16-byte chunks of W's rows)
 
-// The tile shape with the least estimated time.  Switch dense=0 / =1: always the smallest / the largest one, for tests.  With xsum, the
+// The tile shape with the least estimated time.  Switch dense=0 / =n: always the last one / number n of the list, for tests.  With xsum, the
 // sums of X's rows: W holds the layer's centroids (w2 bytes behind it those of the residual table), see DenseArgs.
 int launch_gemm_dense(const Params &p, const __half *X, long long ldx, int tokens, __half *Y, long long ldy, const __half *Wd, long long ldw, hipStream_t s,
                       const float *xsum, unsigned w2) {
@@ -277,8 +285,9 @@ int launch_gemm_dense(const Params &p, const __half *X, long long ldx, int token
   for (long long o = 0; o < p.out_features; o += most_out)
     for (long long t = 0; t < tokens; t += most_tokens) {
       const int nt = (int)std::min<long long>(most_tokens, tokens - t), no = (int)std::min<long long>(most_out, p.out_features - o);
-      const TileKind *best = force == 1 ? &kTiles[0] : &kTiles[sizeof(kTiles) / sizeof(kTiles[0]) - 1];
-      if (force != 0 && force != 1)
+      constexpr int kinds = sizeof(kTiles) / sizeof(kTiles[0]);
+      const TileKind *best = &kTiles[force > 0 && force <= kinds ? force - 1 : kinds - 1];
+      if (force < 0)
         for (const TileKind &k : kTiles)
           if (tile_cost(k, nt, no, p.in_features, cu_count()) < tile_cost(*best, nt, no, p.in_features, cu_count())) best = &k;
       const int rc = best->launch({X + t * ldx, ldx, nt, Wd + o * ldw, ldw, no, p.in_features, Y + t * ldy + o, ldy, 0, 0, w2,

@@ -119,6 +119,25 @@ def test_gemm_dense_tile_edges(gpu_lib, monkeypatch, tokens, out_features, in_fe
     assert (Y[:, out_features:] == 7.0).all()
 
 
+@pytest.mark.parametrize("kind", range(2, 6))
+@pytest.mark.parametrize("tokens,out_features,in_features", [(1, 1, 8), (193, 257, 200), (192, 256, 128), (400, 600, 1032)])
+def test_gemm_dense_tile_kinds(gpu_lib, monkeypatch, tokens, out_features, in_features, kind):
+    """The tiles between the largest and the smallest, each forced: less than a tile, one row, channel and chunk of columns past a tile,
+    exactly one tile, several; with fewer steps than stages, and as centroids as well (scale and bias after the sum)."""
+    import torch
+    for route, setting in (("w", dict(v=4, k=16)), ("c", dict(v=6, k=256, k_res=256))):
+        monkeypatch.setenv("VQ_SWITCHES", "gemm=%s,dense=%d" % (route, kind))
+        L = s.make_layer(8, "kinds", out_features, in_features, **setting)
+        x = s.make_activations(301, L, tokens)
+        X = torch.full((tokens, in_features + 8), float("nan"), dtype=torch.float16, device="cuda")
+        X[:, :in_features] = torch.from_numpy(x).cuda()
+        Y = torch.full((tokens, out_features + 3), 7.0, dtype=torch.float16, device="cuda")
+        gpu_lib.gemm(gpu_lib.DeviceLayer(L), X, out=Y, workspace="fast" if route == "w" else None)
+        torch.cuda.synchronize()
+        _check_matmul(Y[:, :out_features], oracle.gemm(L, x), "%s %s %s" % ((tokens, out_features, in_features), route, kind))
+        assert (Y[:, out_features:] == 7.0).all()
+
+
 @pytest.mark.parametrize("name", list(SMALL))
 @pytest.mark.parametrize("tokens", [9, 37, 300])
 def test_gemm_without_workspace(gpu_lib, name, tokens):
