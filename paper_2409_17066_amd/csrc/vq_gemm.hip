@@ -162,7 +162,7 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(Params p, const __half *
 
 size_t gemm_workspace_bytes(const Params &, int) { return 0; }
 bool gemm_dense_applicable(const Params &p);
-float gemm_dense_us(const Params &p, int tokens);
+float gemm_dense_us(const Params &p, int tokens, bool against_rows = false);
 
 // Bytes of the FP16 weight matrix [out][in] that the two-step route below writes; 0 when that route does not apply.
 // For a layer with a permuted column order (Sec. 3.2.3) the activations, gathered into stored order, come first: tokens
@@ -193,7 +193,7 @@ static bool rows_beat_restoring(const Params &p, int tokens) {
   const float weights = (float)((double)p.out_features * p.in_features * 1e-6);
   const float launch = 5.0f + 1.2e-3f * (float)p.in_features + (p.k_res ? 1.5f + 0.06f * weights : 0.03f * weights) + (p.n_groups > 1 ? 8.0f : 0.0f);
   const float restore = 5.0f + (p.k_res ? 0.8f : 0.4f) * weights + (p.n_out ? 5.0f : 0.0f);
-  return (float)((tokens + 15) / 16) * launch < restore + gemm_dense_us(p, tokens);
+  return (float)((tokens + 15) / 16) * launch < restore + gemm_dense_us(p, tokens, true);
 }
 
 static bool v6_tiles_fill(const Params &p, int tokens) { return tokens > 128 || (long long)((p.out_features + 127) / 128) * ((tokens + 127) / 128) >= 80; }

@@ -251,11 +251,12 @@ struct TileKind {
   int mb, nb, per_cu;
   float round, step[2];
   int (*launch)(DenseArgs, hipStream_t);
+  bool later = false;
 };
 const TileKind kTiles[] = {
-    {4, 4, 1, 9.9f, {1.12f, 0.0f}, launch_tiles<4, 4, 2, false>},  {2, 4, 1, 5.3f, {0.755f, 0.0f}, launch_tiles<2, 4, 3, false>},
-    {3, 3, 1, 6.2f, {0.752f, 0.0f}, launch_tiles<3, 3, 3, false>}, {3, 2, 1, 5.3f, {0.545f, 0.0f}, launch_tiles<3, 2, 3, false>},
-    {1, 3, 1, 4.0f, {0.375f, 0.0f}, launch_tiles<1, 3, 3, false>}, {4, 3, 1, 7.6f, {0.90f, 0.0f}, launch_tiles<4, 3, 2, false>},
+    {4, 4, 1, 9.9f, {1.12f, 0.0f}, launch_tiles<4, 4, 2, false>},  {2, 4, 1, 5.3f, {0.755f, 0.0f}, launch_tiles<2, 4, 3, false>, true},
+    {3, 3, 1, 6.2f, {0.752f, 0.0f}, launch_tiles<3, 3, 3, false>, true}, {3, 2, 1, 5.3f, {0.545f, 0.0f}, launch_tiles<3, 2, 3, false>, true},
+    {1, 3, 1, 4.0f, {0.375f, 0.0f}, launch_tiles<1, 3, 3, false>, true}, {4, 3, 1, 7.6f, {0.90f, 0.0f}, launch_tiles<4, 3, 2, false>},
     {2, 2, 1, 4.2f, {0.383f, 0.0f}, launch_tiles<2, 2, 3, false>}, {1, 3, 2, 2.1f, {0.478f, 0.767f}, launch_tiles<1, 3, 2, false>},
     {1, 2, 2, 2.3f, {0.273f, 0.558f}, launch_tiles<1, 2, 3, false>}, {1, 1, 2, 1.2f, {0.190f, 0.384f}, launch_tiles<1, 1, 4, false>},
 };
@@ -298,10 +299,12 @@ int launch_gemm_dense(const Params &p, const __half *X, long long ldx, int token
 }
 
 // Estimated time of launch_gemm_dense in microseconds, at least that of reading W at 4.5 TB/s (the route rules of vq_gemm compare
-// it with other kernels').
-float gemm_dense_us(const Params &p, int tokens) {
+// it with other kernels').  For vq_gemv's kernels, which do not round W, against restoring (`against_rows`) the four later tile shapes do
+// not count: that line stays where it was drawn, and with it the precision of a call (of 20000 random ones it would move one).
+float gemm_dense_us(const Params &p, int tokens, bool against_rows) {
   float best = 1e30f;
-  for (const TileKind &k : kTiles) best = std::min(best, tile_cost(k, tokens, p.out_features, p.in_features, cu_count()));
+  for (const TileKind &k : kTiles)
+    if (!against_rows || !k.later) best = std::min(best, tile_cost(k, tokens, p.out_features, p.in_features, cu_count()));
   return std::max(best, 3.0f + (float)((double)p.out_features * p.in_features * 2 / 4.5e6));
 }
 
