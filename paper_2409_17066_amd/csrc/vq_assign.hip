@@ -130,33 +130,39 @@ __device__ __forceinline__ float distance(const float (&t)[V], const half8 &c0, 
   return d;
 }
 
-// Entry i of a table in memory as the planes hold one: V elements, zeros from len on, in loads of as many bytes as divide a row where
+// Entries of a table in memory as the planes hold one: V elements, zeros from len on, in loads of as many bytes as divide a row where
 // those are aligned (`whole`).
 template <int V> constexpr int load_bytes() { return V % 8 == 0 ? 16 : V % 4 == 0 ? 8 : V % 2 == 0 ? 4 : 2; }
 
-template <int V>
-__device__ __forceinline__ void load_entry(const __half *codebook, int i, int stride, int len, bool whole, half8 &c0, half8 &c1) {
-  constexpr int N = load_bytes<V>() / 2;
-  typedef _Float16 part __attribute__((ext_vector_type(N)));
-  const __half *from = codebook + (long long)i * stride;
-  _Float16 c[16] = {};
+// N entries under one branch: with a branch for each the compiler would wait for each before the next.
+template <int V, int N>
+__device__ __forceinline__ void load_entries(const __half *codebook, const int (&i)[N], int stride, int len, bool whole, half8 (&c0)[N], half8 (&c1)[N]) {
+  constexpr int B = load_bytes<V>() / 2;
+  typedef _Float16 part __attribute__((ext_vector_type(B)));
+  _Float16 c[N][16] = {};
   if (whole) {
 #pragma unroll
-    for (int x = 0; x < V / N; ++x) {
-      const part y = reinterpret_cast<const part *>(from)[x];
+    for (int n = 0; n < N; ++n)
 #pragma unroll
-      for (int j = 0; j < N; ++j) c[x * N + j] = y[j];
-    }
+      for (int x = 0; x < V / B; ++x) {
+        const part y = reinterpret_cast<const part *>(codebook + (long long)i[n] * stride)[x];
+#pragma unroll
+        for (int j = 0; j < B; ++j) c[n][x * B + j] = y[j];
+      }
   } else {
 #pragma unroll
-    for (int j = 0; j < V; ++j) c[j] = __builtin_bit_cast(_Float16, from[j]);
+    for (int n = 0; n < N; ++n)
+#pragma unroll
+      for (int j = 0; j < V; ++j) c[n][j] = __builtin_bit_cast(_Float16, codebook[(long long)i[n] * stride + j]);
   }
 #pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    if (j < V && len < V) c[j] = j < len ? c[j] : (_Float16)0.0f;
-    if (j < 8) c0[j] = c[j];
-    else c1[j & 7] = c[j];
-  }
+  for (int n = 0; n < N; ++n)
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      if (j < V && len < V) c[n][j] = j < len ? c[n][j] : (_Float16)0.0f;
+      if (j < 8) c0[n][j] = c[n][j];
+      else c1[n][j & 7] = c[n][j];
+    }
 }
 
 // The lanes' candidates meet: the smaller distance, else the smaller index.  Distances are sums of squares, so their bits order
@@ -196,7 +202,9 @@ __device__ __forceinline__ void wave_arg_min(float &d, unsigned &i) {
 //    2.6 of its four were left;
 //  - blocks of 32 from 4096 entries on: 8 instructions fewer for every 64 entries and 64 vectors, 16 distances of 15 instructions more
 //    (k = 4096: 995 -> 948 us; at 2048 the two are equal).
-// Measured, 11008 x 4096, v = 6: k = 4096 1161 -> 971 us, k = 256 263 -> 156 us; every distance on the vector ALUs 8.42 ms.
+//  - tables of more than 4096 entries are kernels of their own, which keep their registers out of the others (11008 x 4096, k = 256:
+//    156 -> 144 us, v = 12 with a base 835 -> 775).
+// Measured, 11008 x 4096, v = 6: k = 4096 1152 -> 952 us, k = 256 261 -> 144 us; every distance on the vector ALUs 8.42 ms.
 // 4096 x 4096, v = 8, k = 65536, entries read whole where they are aligned instead of by element: 5.33 -> 4.74 ms.
 constexpr int WAVES = 16;
 constexpr int SCREEN_ROWS = 4096;                       // table rows in LDS at once: two planes of 16 bytes each
@@ -210,6 +218,11 @@ template <int V>
 __device__ TableScale stage_screen_table(const __half *__restrict__ codebook, int stride, int len, int k, int c0, int rows, bool whole, half8 *plane, float *red) {
   constexpr int PER = SCREEN_ROWS / (WAVES * 64);
   const int tid = threadIdx.x, wave = tid >> 6;
+  half8 first_half[PER], second_half[PER];
+  int which[PER];
+#pragma unroll
+  for (int r = 0; r < PER; ++r) which[r] = min(c0 + tid + r * (WAVES * 64), k - 1);
+  load_entries<V, PER>(codebook, which, stride, len, whole, first_half, second_half);
   float h[PER], most = 0.0f;
   bool fine = true;
 #pragma unroll
@@ -217,8 +230,7 @@ __device__ TableScale stage_screen_table(const __half *__restrict__ codebook, in
     const int e = tid + r * (WAVES * 64);
     h[r] = 0.0f;
     if (e < rows) {
-      half8 e0, e1;
-      load_entry<V>(codebook, min(c0 + e, k - 1), stride, len, whole, e0, e1);
+      const half8 e0 = first_half[r], e1 = second_half[r];
       _Float16 c[V];
 #pragma unroll
       for (int j = 0; j < V; ++j) c[j] = j < 8 ? e0[j & 7] : e1[j & 7];
@@ -346,9 +358,9 @@ __device__ __forceinline__ void set_slots(half8 &b, int half, _Float16 factor) {
   else if (half) { b[5] = factor; b[6] = factor; b[7] = factor; }
 }
 
-// NT: tiles of 32 vectors a wave holds.  WIDE: blocks of 32 centroids.  SPLIT: `split` waves (a power of two) share a tile of vectors, each taking its share
+// NT: tiles of 32 vectors a wave holds.  WIDE: blocks of 32 centroids.  CHUNKED: more than SCREEN_ROWS entries, a chunk of them after the other.  SPLIT: `split` waves (a power of two) share a tile of vectors, each taking its share
 // of the table.  The first last_wgs workgroups take `last`, the others `first`.
-template <int V, bool BASE, int NT, bool SPLIT, bool WIDE>
+template <int V, bool BASE, int NT, bool SPLIT, bool WIDE, bool CHUNKED>
 __global__ __launch_bounds__(WAVES * 64, 4) void assign_screen_kernel(Vectors first, Vectors last, int last_wgs, const __half *__restrict__ codebook,
                                                                        int stride, int k, int bits, int seg_len, int split) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -363,7 +375,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void assign_screen_kernel(Vectors fi
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = lane & 31, half = lane >> 5;
   const bool is_last = (int)blockIdx.x < last_wgs;
   const Vectors a = is_last ? last : first;
-  const int n_chunks = (k + SCREEN_ROWS - 1) / SCREEN_ROWS;
+  const int n_chunks = CHUNKED ? (k + SCREEN_ROWS - 1) / SCREEN_ROWS : 1;
   const long long items = items_of(a, seg_len);
   const int groups = SPLIT ? WAVES / split : WAVES, part = SPLIT ? wave % split : 0;
   const int block_items = groups * NT * 32;
@@ -373,9 +385,9 @@ __global__ __launch_bounds__(WAVES * 64, 4) void assign_screen_kernel(Vectors fi
   const bool whole = stride == V && reinterpret_cast<size_t>(codebook) % load_bytes<V>() == 0;
   TableScale ts = {0, 0.0f, true};
   int *ticket = list;
-  const bool tickets = !SPLIT && n_chunks == 1;
+  constexpr bool tickets = !SPLIT && !CHUNKED;
   if (tickets && threadIdx.x == 0) *ticket = 0;           // (seen by all behind the barriers of the next line)
-  if (n_chunks == 1) ts = stage_screen_table<V>(codebook, stride, a.len, k, 0, rows_lds, whole, plane, red);
+  if constexpr (!CHUNKED) ts = stage_screen_table<V>(codebook, stride, a.len, k, 0, rows_lds, whole, plane, red);
 
   const int wg0 = is_last ? blockIdx.x : blockIdx.x - last_wgs, wgs = is_last ? last_wgs : gridDim.x - last_wgs;
   for (int turn = 0;; ++turn) {
@@ -401,7 +413,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void assign_screen_kernel(Vectors fi
     bool trusted = true;                                     // (of this lane's vectors: every chunk's factor was in range)
     float h_max = 0.0f;
     for (int ch = 0; ch < n_chunks; ++ch) {
-      if (n_chunks > 1) {
+      if constexpr (CHUNKED) {
         __syncthreads();
         ts = stage_screen_table<V>(codebook, stride, a.len, k, ch * SCREEN_ROWS, rows_lds, whole, plane, red);
       }
@@ -446,7 +458,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void assign_screen_kernel(Vectors fi
 #pragma unroll
         for (int u = 0; u < NT; ++u) { b1[u] = -__builtin_inff(); b2[u] = -__builtin_inff(); id[u] = 0; }
       }
-      if (ch == 0 || n_chunks > 1) {
+      if (ch == 0 || CHUNKED) {
         const _Float16 factor = slot_factor(e, ts.f);
         trusted = trusted && factor != (_Float16)0.0f;
         if constexpr (BASE && NT == 2) {
@@ -487,6 +499,21 @@ __global__ __launch_bounds__(WAVES * 64, 4) void assign_screen_kernel(Vectors fi
         b1[u] = up ? m : b1[u];
       };
       auto tile_of = [&](int round, int x) { return mine[(min(round, rounds - 1) * TU + x) * 32]; };
+      if constexpr (SPLIT) {                                 // (few rounds a chunk: nothing to run ahead of)
+        half8 c0 = tile_of(part, 0), c1 = tile_of(part, 1);
+        for (int round = part; round < rounds; round += step) {
+          products(c0, s0);
+          products(c1, s1);
+          c0 = tile_of(round + step, 0);
+          c1 = tile_of(round + step, 1);
+#pragma unroll
+          for (int u = 0; u < NT; ++u) {
+            take(u, largest(s0[u], s0[u][0]), (round0 + round) * TU);
+            take(u, largest(s1[u], s1[u][0]), (round0 + round) * TU + 1);
+          }
+        }
+        continue;
+      }
       half8 c1 = tile_of(part, 1), next = tile_of(part + step, 0);
       products(tile_of(part, 0), s0);
       for (int round = part; round < rounds; round += step) {
@@ -523,7 +550,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void assign_screen_kernel(Vectors fi
       }
       __syncthreads();
     }
-    if (n_chunks > 1) {
+    if constexpr (CHUNKED) {
       if (threadIdx.x == 0) list[0] = 0;
       __syncthreads();
     }
@@ -588,7 +615,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void assign_screen_kernel(Vectors fi
         best = closer ? d : best;
         nearest = closer ? at : nearest;
       };
-      if (n_chunks == 1) {
+      if constexpr (!CHUNKED) {
         const half8 *from = plane + row0, *from2 = from + (V > 8 ? rows_lds : 0);
 #pragma unroll
         for (int r = 0; r < MINE; ++r) {
@@ -596,14 +623,16 @@ __global__ __launch_bounds__(WAVES * 64, 4) void assign_screen_kernel(Vectors fi
           consider(distance<V>(t, from[at], from2[at]), at);
         }
       } else {
-#pragma unroll 1
+        constexpr int QUADS = NT == 1 ? 2 : 1;
+#pragma unroll QUADS
         for (int quad = 0; quad < MINE / 4; ++quad) {
+          half8 c0[4], c1[4];
+          int which[4];
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            half8 c0, c1;
-            load_entry<V>(codebook, min(row0 + r + 8 * quad, k - 1), stride, a.len, whole, c0, c1);
-            consider(distance<V>(t, c0, c1), r + 8 * quad);
-          }
+          for (int r = 0; r < 4; ++r) which[r] = min(row0 + r + 8 * quad, k - 1);
+          load_entries<V, 4>(codebook, which, stride, a.len, whole, c0, c1);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) consider(distance<V>(t, c0[r], c1[r]), r + 8 * quad);
         }
       }
       unsigned arg = best < __builtin_inff() ? (unsigned)min(row0 + nearest, k - 1) : 0u;
@@ -613,7 +642,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void assign_screen_kernel(Vectors fi
         if (od < best || (od == best && oa < arg)) { best = od; arg = oa; }
       }
       // vectors whose block is not sure: the wave takes them one at a time, its lanes the centroids in turn
-      if (n_chunks > 1) {
+      if constexpr (CHUNKED) {
         if (live && !sure) list[1 + atomicAdd(&list[0], 1)] = group * (NT * 32) + x;
       } else {
         for (unsigned long long todo = __ballot(live && !sure); todo; todo &= todo - 1) {
@@ -637,7 +666,7 @@ __global__ __launch_bounds__(WAVES * 64, 4) void assign_screen_kernel(Vectors fi
       }
       if (NT == 2 || half == 0) my_codes[x] = live ? arg : 0u;
     }
-    if (n_chunks > 1) {
+    if constexpr (CHUNKED) {
       // the vectors that are not sure, against the whole table: every wave takes a share of it
       __syncthreads();
       const int n_list = list[0], share = (k + WAVES * 64 - 1) / (WAVES * 64) * 64, from = wave * share, to = min(k, from + share);
@@ -654,12 +683,14 @@ __global__ __launch_bounds__(WAVES * 64, 4) void assign_screen_kernel(Vectors fi
         unsigned bi = 0xFFFFFFFFu;
         for (int i0 = from; i0 < to; i0 += 256) {
           half8 c0[4], c1[4];
+          int which[4];
 #pragma unroll
-          for (int y = 0; y < 4; ++y) load_entry<V>(codebook, min(i0 + 64 * y + lane, k - 1), stride, a.len, whole, c0[y], c1[y]);
+          for (int y = 0; y < 4; ++y) which[y] = min(i0 + 64 * y + lane, k - 1);
+          load_entries<V, 4>(codebook, which, stride, a.len, whole, c0, c1);
 #pragma unroll
           for (int y = 0; y < 4; ++y) {
             const float d = distance<V>(t, c0[y], c1[y]);
-            if (d < bd) { bd = d; bi = (unsigned)min(i0 + 64 * y + lane, k - 1); }
+            if (d < bd) { bd = d; bi = (unsigned)which[y]; }
           }
         }
         wave_arg_min(bd, bi);
@@ -836,9 +867,9 @@ int launch_short(const Vectors &first, const Vectors &last, const __half *codebo
   return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
 }
 
-template <int V, bool BASE, int NT, bool SPLIT, bool WIDE>
+template <int V, bool BASE, int NT, bool SPLIT, bool WIDE, bool CHUNKED>
 int launch_screen_nt(const Vectors &first, const Vectors &last, const __half *codebook, int k, int bits, int split, hipStream_t s) {
-  auto kernel = assign_screen_kernel<V, BASE, NT, SPLIT, WIDE>;
+  auto kernel = assign_screen_kernel<V, BASE, NT, SPLIT, WIDE, CHUNKED>;
   VQ_ALLOW_FULL_LDS(kernel);
   const int seg_len = segment(bits), block_items = WAVES / split * NT * 32;
   const size_t lds = (size_t)screen_rows(k) * 32 + 2 * WAVES * sizeof(float) + WAVES * NT * 32 * sizeof(unsigned) + (SPLIT ? 3 * WAVES * 64 * sizeof(float) : 0) +
@@ -865,11 +896,13 @@ int launch_screen(const Vectors &first, const Vectors &last, const __half *codeb
   // share the table's rows until there is about one
   const long long waves = (long long)cu_count() * WAVES, rounds2 = (tiles + 2 * waves - 1) / (2 * waves), rounds1 = (tiles + waves - 1) / waves;
   if (10 * rounds2 <= 6 * rounds1)
-    return k >= SCREEN_ROWS ? launch_screen_nt<V, BASE, 2, false, true>(first, last, codebook, k, bits, 1, s)
-                            : launch_screen_nt<V, BASE, 2, false, false>(first, last, codebook, k, bits, 1, s);
+    return k > SCREEN_ROWS    ? launch_screen_nt<V, BASE, 2, false, true, true>(first, last, codebook, k, bits, 1, s)
+           : k == SCREEN_ROWS ? launch_screen_nt<V, BASE, 2, false, true, false>(first, last, codebook, k, bits, 1, s)
+                              : launch_screen_nt<V, BASE, 2, false, false, false>(first, last, codebook, k, bits, 1, s);
   int split = 1;
   while (split < WAVES && tiles * split * 2 <= waves && split * 128 < min(k, SCREEN_ROWS)) split *= 2;
-  return launch_screen_nt<V, BASE, 1, true, false>(first, last, codebook, k, bits, split, s);
+  return k > SCREEN_ROWS ? launch_screen_nt<V, BASE, 1, true, false, true>(first, last, codebook, k, bits, split, s)
+                         : launch_screen_nt<V, BASE, 1, true, false, false>(first, last, codebook, k, bits, split, s);
 }
 
 template <int V>
