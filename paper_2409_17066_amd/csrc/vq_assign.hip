@@ -205,7 +205,7 @@ __device__ __forceinline__ void wave_arg_min(float &d, unsigned &i) {
 //  - tables of more than 4096 entries are kernels of their own, which keep their registers out of the others (11008 x 4096, k = 256:
 //    156 -> 144 us, v = 12 with a base 835 -> 775).
 // Measured, 11008 x 4096, v = 6: k = 4096 1152 -> 952 us, k = 256 261 -> 144 us; every distance on the vector ALUs 8.42 ms.
-// 4096 x 4096, v = 8, k = 65536, entries read whole where they are aligned instead of by element: 5.33 -> 4.74 ms.
+// 4096 x 4096, v = 8, k = 65536, entries loaded together, and whole where they are aligned: 5.13 -> 4.40 ms.
 constexpr int WAVES = 16;
 constexpr int SCREEN_ROWS = 4096;                       // table rows in LDS at once: two planes of 16 bytes each
 constexpr int screen_instructions(int v, bool base) { return base && v > 6 ? 2 : 1; }
