@@ -587,17 +587,6 @@ bool outlier_slot(const Params &p, int batch) {
   return p.Q > 0 && p.n_groups <= 16 && cu_count() >= 64 && slots_bytes(p, p.n_groups + 1, batch) <= VQ_GEMV_STATIC_WORKSPACE_BYTES;
 }
 
-// Whether a slot is one table: then a workgroup stages one table instead of two and walks twice the rows with it (the 2.26-bit setting, one
-// row, 11008 x 4096: 27.2 -> 25.2 us, two rows 34.8 -> 32.0; 1024 x 2048 10.9 -> 10.0; two groups 27.5 -> 24.3, eight 26.8 -> 24.9; and
-// 29.5 -> 25.3 with permuted columns, which every workgroup now gathers for itself).  Up to 16 tables, and as long as the sums, with the
-// rows in stored order beside them, fit the library's own workspace.
-bool table_slots(const Params &p, int batch) {
-  const int slots = 2 * p.n_groups + (p.Q ? 1 : 0);
-  const size_t rows = ((size_t)batch * (size_t)((p.in_features + 7) & ~7) * sizeof(__half) + 255) / 256 * 256;
-  return p.k_res && p.n_groups <= 8 && cu_count() >= 64 && slots_bytes(p, slots, batch) + rows <= VQ_GEMV_STATIC_WORKSPACE_BYTES;
-}
-int group_slots(const Params &p, int batch) { return table_slots(p, batch) ? 2 * p.n_groups : p.n_groups; }
-
 bool make_pass_plan(const Params &p, int batch, int u, int eh, PassPlan *plan, int n_slots = 0, bool out_slot = false) {
   auto up16 = [](size_t v) { return (v + 15) / 16 * 16; };
   size_t table = up16((size_t)p.k * eh * 2);
@@ -628,6 +617,27 @@ bool make_pass_plan(const Params &p, int batch, int u, int eh, PassPlan *plan, i
   plan->bytes = (unsigned)total; plan->x_pitch = (unsigned)pitch; plan->xo_pitch = (unsigned)xo_pitch;
   return true;
 }
+
+// Rows that one launch of the pass kernel takes of `batch` with that many slots; 0: not even one fits LDS.
+int rows_at_once(const Params &p, int batch, int n_slots) {
+  PassPlan plan;
+  for (int rows = batch >= 4 ? 4 : batch >= 2 ? 2 : 1; rows >= 1; rows /= 2)
+    if (make_pass_plan(p, rows, win_vectors(p.bits), entry_halfs(p.v), &plan, n_slots, outlier_slot(p, batch))) return rows;
+  return 0;
+}
+
+// Whether a slot is one table: then a workgroup stages one table instead of two and walks twice the rows with it (the 2.26-bit setting, one
+// row, 11008 x 4096: 27.2 -> 25.2 us, two rows 34.8 -> 32.0; 1024 x 2048 10.9 -> 10.0; two groups 27.5 -> 24.3, eight 26.8 -> 24.9; and
+// 29.5 -> 25.3 with permuted columns, which every workgroup now gathers for itself).  Up to 16 tables, as long as the sums, with the
+// rows in stored order beside them, fit the library's own workspace, and where the sums of twice the rows leave room in LDS for as many
+// activation rows a launch as a group a slot does (53248 x 28672, eight groups: they leave none).
+bool table_slots(const Params &p, int batch) {
+  const int slots = 2 * p.n_groups + (p.Q ? 1 : 0);
+  const size_t rows = ((size_t)batch * (size_t)((p.in_features + 7) & ~7) * sizeof(__half) + 255) / 256 * 256;
+  return p.k_res && p.n_groups <= 8 && cu_count() >= 64 && slots_bytes(p, slots, batch) + rows <= VQ_GEMV_STATIC_WORKSPACE_BYTES &&
+         rows_at_once(p, batch, 2 * p.n_groups) > 0 && rows_at_once(p, batch, 2 * p.n_groups) >= rows_at_once(p, batch, p.n_groups);
+}
+int group_slots(const Params &p, int batch) { return table_slots(p, batch) ? 2 * p.n_groups : p.n_groups; }
 
 // layers the pass kernel takes: a compiled (V, BITS) pair, a residual stream of the same width, outlier vectors of four
 bool pass_pair(const Params &p) {
@@ -750,8 +760,8 @@ int gemv_lds_slots(const Params &p, int batch) { return group_slots(p, batch) + 
 
 size_t gemv_lds_slots_workspace_bytes(const Params &p, int batch) {
   PassPlan plan;
+  if (p.orientation != 0 || p.n_groups < 2 || p.n_groups > 64 || !pass_pair(p)) return 0;
   const int n_slots = group_slots(p, batch);
-  if (p.orientation != 0 || p.n_groups < 2 || n_slots > 64 || !pass_pair(p)) return 0;
   if (!make_pass_plan(p, 1, win_vectors(p.bits), entry_halfs(p.v), &plan, n_slots, outlier_slot(p, batch))) return 0;
   return slots_bytes(p, gemv_lds_slots(p, batch), batch);
 }

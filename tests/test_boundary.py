@@ -253,3 +253,16 @@ def test_default_workspace_of_gemm_has_room_for_W_only_where_it_is_rounded_anywa
     assert vq.vq_gemm_default(_desc(), None, 32, 9, 0x9000, 8) == vq.VQ_ERR_NULL
     assert vq.vq_gemm_default(_desc(), 0x8000, 32, 0, 0x9000, 8) == vq.VQ_ERR_SHAPE
     assert vq.vq_gemm_default(_desc(), 0x8008, 32, 9, 0x9000, 8) == vq.VQ_ERR_ALIGNMENT
+
+
+@pytest.mark.parametrize("out_features", [32000, 53248])
+def test_gemv_workspace_of_layers_whose_rows_leave_no_room_for_a_table_a_slot(out_features):
+    """v = 12 with two tables of 4096 in eight codebook groups, one and two rows: a slot is a group where LDS has no room for the row
+    sums of twice the rows, and the workspace is that of the eight groups."""
+    columns = 28672
+    vectors = -(-columns // 12)
+    stride = (vectors * 12 + 127) // 128 * 16
+    d = _desc(out_features=out_features, in_features=columns, v=12, k=4096, k_res=4096, codebook_res=0x3000, idx_row_stride=stride,
+              idx_res=0x4000, idx_res_row_stride=stride, group_vectors=-(-vectors // 64) * 8)
+    for batch in (1, 2):
+        assert vq.vq_gemv_workspace_bytes(d, batch) == (8 * (batch * out_features + 16) * 4 + 255) // 256 * 256
