@@ -212,8 +212,8 @@ extern "C" int vq_gemv_static_workspace(const vq_layer_desc *desc, const void *x
     rc = vq::static_workspace(&ws);
     if (rc != VQ_OK) return rc;
   }
-  return vq::launch_gemv_ws(p, static_cast<const __half *>(x), ldx, batch, static_cast<__half *>(y), ldy, ws, need,
-                            static_cast<hipStream_t>(hip_stream));
+  return vq::launch_gemv_ws(p, static_cast<const __half *>(x), ldx, batch, static_cast<__half *>(y), ldy, ws,
+                            ws ? (size_t)VQ_GEMV_STATIC_WORKSPACE_BYTES : 0, static_cast<hipStream_t>(hip_stream));
 }
 
 extern "C" int vq_gemv_multi(const vq_layer_desc *const *descs, int32_t n_layers, const void *x, int64_t ldx, int32_t batch,

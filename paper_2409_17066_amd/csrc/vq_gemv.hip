@@ -118,13 +118,12 @@ bool gemv_fast_applicable(const Params &p, const __half *x, long long ldx);
 bool gemv_res8_applicable(const Params &p, const __half *x);
 bool gemv_lds_applicable(const Params &p, int batch);
 int launch_gemv_lds(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, hipStream_t s);
-size_t gemv_lds_slots_workspace_bytes(const Params &p, int batch);
-int gemv_lds_slots(const Params &p, int batch);
+size_t gemv_lds_slots_workspace_bytes(const Params &p, int batch, bool least);
 bool gemv_down_lds_applicable(const Params &p, int batch);
 size_t gemv_down_lds_slots_workspace_bytes(const Params &p, int batch);
 int launch_gemv_down_lds_slots(const Params &p, const __half *x, long long ldx, int batch, float *part, float *part_xs, hipStream_t s);
 int launch_gemv_down_lds(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, hipStream_t s);
-int launch_gemv_lds_slots(const Params &p, const __half *x, long long ldx, int batch, float *part, float *part_xs, hipStream_t s);
+int launch_gemv_lds_slots(const Params &p, const __half *x, long long ldx, int batch, float *part, size_t bytes, int *n_part, hipStream_t s);
 int launch_gemv_res8(const Params &p, const __half *x, __half *y, hipStream_t s);
 int launch_gemv_fast(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, hipStream_t s);
 
@@ -389,7 +388,7 @@ static bool permuted_in_kernel(const Params &p, const __half *x, long long ldx, 
 // for more than vq_gemv_static_workspace has, which would refuse a layer that needs none.)
 static bool rows_gathered(const Params &p, int batch) { return batch >= 5 && (p.in_features & 1) && p.in_features < (1 << 18) && rows_wanted(p, batch, true); }
 
-static size_t stored_order_workspace_bytes(const Params &p, const __half *x, long long ldx, int batch) {
+static size_t stored_order_workspace_bytes(const Params &p, const __half *x, long long ldx, int batch, bool least) {
   if (rows_wanted(p, batch, true) && (batch == 1 || !(ldx & 1))) {
     // (0 with codebook groups that the kernel walks by itself: the slots of the kernels below are asked for instead, which run where
     // this one does not take x)
@@ -407,27 +406,40 @@ static size_t stored_order_workspace_bytes(const Params &p, const __half *x, lon
     return gemv_down_applicable(p, x, ldx) || gemv_v8_down_applicable(p) ? 0 : gemv_down_lds_slots_workspace_bytes(p, batch);
   }
   if (!gemv_fast_applicable(p, x, ldx))       // the LDS-table kernels, when the layer gets that far: a slot per workgroup
-    return gemv_v8_applicable(p, x, ldx) ? 0 : gemv_lds_slots_workspace_bytes(p, batch);
+    return gemv_v8_applicable(p, x, ldx) ? 0 : gemv_lds_slots_workspace_bytes(p, batch, least);
   if (forced_kernel() == 'd') return 0;
   return gemv_mfma_groups_workspace_bytes(p, batch);
 }
 
-size_t gemv_workspace_bytes(const Params &p, const __half *x, long long ldx, int batch) {
+// Of a call with exactly these rows.  least: the fewest bytes that it makes use of.
+static size_t workspace_bytes_of(const Params &p, const __half *x, long long ldx, int batch, bool least) {
   if (force_generic()) return 0;
   if (p.perm || rows_gathered(p, batch)) {
     if (p.perm && permuted_in_kernel(p, x, ldx, batch)) return 0;
     Params q = p;
     q.perm = nullptr;
-    const size_t head = permuted_x_bytes(p, batch), rest = stored_order_workspace_bytes(q, nullptr, (p.in_features + 7) & ~7, batch);
+    const size_t head = permuted_x_bytes(p, batch), rest = stored_order_workspace_bytes(q, nullptr, (p.in_features + 7) & ~7, batch, least);
     // (the column parts of vq_gemv_rows.hip are done without where the two together are more than vq_gemv_static_workspace has)
     return rows_wanted(q, batch, true) && head + rest > VQ_GEMV_STATIC_WORKSPACE_BYTES ? head : head + rest;
   }
-  return stored_order_workspace_bytes(p, x, ldx, batch);
+  return stored_order_workspace_bytes(p, x, ldx, batch, least);
 }
 
-int launch_gemv_ws(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, void *workspace,
-                   size_t workspace_bytes, hipStream_t s) {
-  const size_t need = gemv_workspace_bytes(p, x, ldx, batch);
+// (One and two rows of a layer with two tables a group take a slot a table, whose workspace may be larger than that of three rows, which
+// another kernel takes.  What holds a slot a group of fewer rows is made to hold that, so that a loop can lend its calls the workspace of the
+// largest batch.)
+size_t gemv_workspace_bytes(const Params &p, const __half *x, long long ldx, int batch) {
+  const size_t own = workspace_bytes_of(p, x, ldx, batch, false);
+  size_t bytes = own;
+  if (p.orientation == 0 && p.k_res && p.n_groups > 1)
+    for (int rows = 1; rows < batch; ++rows)
+      if (own >= workspace_bytes_of(p, x, ldx, rows, true)) bytes = std::max(bytes, workspace_bytes_of(p, x, ldx, rows, false));
+  return bytes;
+}
+
+static int launch_with_workspace(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, void *workspace,
+                                 size_t workspace_bytes, bool least, hipStream_t s) {
+  const size_t need = workspace_bytes_of(p, x, ldx, batch, least);
   if (p.perm || (rows_gathered(p, batch) && !gemv_rows_takes(p, x, ldx, batch))) {
     if (!need || !workspace || workspace_bytes < need) return launch_gemv(p, x, ldx, batch, y, ldy, s);
     // gather the activations into stored order, then the layer is an unpermuted one
@@ -437,19 +449,19 @@ int launch_gemv_ws(const Params &p, const __half *x, long long ldx, int batch, _
     const long long ldxp = (p.in_features + 7) & ~7;
     // (in one launch of the LDS-table kernel the workgroups gather theirs by themselves: a group's columns, in the shade of its table)
     if (p.perm && batch <= 4 && batch != 3 && p.orientation == 0 && !rows_wanted(q, batch, true) && !gemv_fast_applicable(q, xp, ldxp) && !switches().groups_loop) {
-      const size_t head = permuted_x_bytes(p, batch), slot_bytes = gemv_lds_slots_workspace_bytes(q, batch);
+      const size_t head = permuted_x_bytes(p, batch), slot_bytes = gemv_lds_slots_workspace_bytes(q, batch, true);
       if (slot_bytes && workspace_bytes - head >= slot_bytes) {
-        const int slots = gemv_lds_slots(q, batch);
-        float *part = reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + head), *part_xs = part + (size_t)slots * (size_t)batch * (size_t)p.out_features;
-        const int rc = launch_gemv_lds_slots(p, x, ldx, batch, part, part_xs, s);
-        if (rc == VQ_OK) return launch_groups_finish(part, part_xs, slots, batch, p, y, ldy, s);
+        float *part = reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + head);
+        int slots;
+        const int rc = launch_gemv_lds_slots(p, x, ldx, batch, part, workspace_bytes - head, &slots, s);
+        if (rc == VQ_OK) return launch_groups_finish(part, part + (size_t)slots * (size_t)batch * (size_t)p.out_features, slots, batch, p, y, ldy, s);
         if (rc != VQ_ERR_UNSUPPORTED) return rc;
       }
     }
     const int rc = launch_gather_cols(x, ldx, batch, p.in_features, p.perm, xp, ldxp, s);
     if (rc != VQ_OK) return rc;
     const size_t head = permuted_x_bytes(p, batch);
-    return launch_gemv_ws(q, xp, ldxp, batch, y, ldy, static_cast<unsigned char *>(workspace) + head, workspace_bytes - head, s);
+    return launch_with_workspace(q, xp, ldxp, batch, y, ldy, static_cast<unsigned char *>(workspace) + head, workspace_bytes - head, false, s);
   }
   if (rows_wanted(p, batch, workspace != nullptr) && gemv_rows_takes(p, x, ldx, batch)) {
     const int per_group = workspace && workspace_bytes >= gemv_rows_workspace_bytes(p, batch) ? gemv_rows_parts(p) : 0, parts = per_group * p.n_groups;
@@ -486,12 +498,12 @@ int launch_gemv_ws(const Params &p, const __half *x, long long ldx, int batch, _
     if (rc == VQ_OK) return launch_groups_finish(part, part_xs, slots, batch, p, y, ldy, s);
     if (rc != VQ_ERR_UNSUPPORTED || done != 0) return rc;
   } else if (need && workspace && workspace_bytes >= need && !gemv_fast_applicable(p, x, ldx)) {
-    const size_t slot_bytes = gemv_lds_slots_workspace_bytes(p, batch);
+    const size_t slot_bytes = gemv_lds_slots_workspace_bytes(p, batch, true);
     if (!switches().groups_loop && slot_bytes && workspace_bytes >= slot_bytes) {
-      const int slots = gemv_lds_slots(p, batch);                  // (the outlier columns as a rule are one more)
-      float *part = static_cast<float *>(workspace), *part_xs = part + (size_t)slots * (size_t)batch * (size_t)p.out_features;
-      const int rc = launch_gemv_lds_slots(p, x, ldx, batch, part, part_xs, s);
-      if (rc == VQ_OK) return launch_groups_finish(part, part_xs, slots, batch, p, y, ldy, s);
+      float *part = static_cast<float *>(workspace);
+      int slots;                                                   // (the outlier columns as a rule are one more)
+      const int rc = launch_gemv_lds_slots(p, x, ldx, batch, part, workspace_bytes, &slots, s);
+      if (rc == VQ_OK) return launch_groups_finish(part, part + (size_t)slots * (size_t)batch * (size_t)p.out_features, slots, batch, p, y, ldy, s);
       if (rc != VQ_ERR_UNSUPPORTED) return rc;
     }
   } else if (need && workspace && workspace_bytes >= need && !switches().groups_loop) {
@@ -499,6 +511,16 @@ int launch_gemv_ws(const Params &p, const __half *x, long long ldx, int batch, _
     if (rc != VQ_ERR_UNSUPPORTED) return rc;
   }
   return launch_gemv(p, x, ldx, batch, y, ldy, s);
+}
+
+int launch_gemv_ws(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, void *workspace,
+                   size_t workspace_bytes, hipStream_t s) {
+  const long long even = p.in_features + (p.in_features & 1);
+  const bool enough = workspace && workspace_bytes >= gemv_workspace_bytes(p, nullptr, even, batch);
+  // less than vq_gemv_workspace_bytes asks for, though not for these rows alone: vq_gemv
+  if (workspace && !enough && workspace_bytes >= workspace_bytes_of(p, nullptr, even, batch, false)) return launch_gemv(p, x, ldx, batch, y, ldy, s);
+  // (rows of an odd width may go to other kernels than the size was asked for, which make do with what it is)
+  return launch_with_workspace(p, x, ldx, batch, y, ldy, workspace, workspace_bytes, enough && !p.perm && (ldx & 1), s);
 }
 
 int launch_gemv_mfma_multi(const Params *ps, int n, const __half *x, long long ldx, int batch, __half *const *ys,

@@ -637,7 +637,6 @@ bool table_slots(const Params &p, int batch) {
   return p.k_res && p.n_groups <= 8 && cu_count() >= 64 && slots_bytes(p, slots, batch) + rows <= VQ_GEMV_STATIC_WORKSPACE_BYTES &&
          rows_at_once(p, batch, 2 * p.n_groups) > 0 && rows_at_once(p, batch, 2 * p.n_groups) >= rows_at_once(p, batch, p.n_groups);
 }
-int group_slots(const Params &p, int batch) { return table_slots(p, batch) ? 2 * p.n_groups : p.n_groups; }
 
 // layers the pass kernel takes: a compiled (V, BITS) pair, a residual stream of the same width, outlier vectors of four
 bool pass_pair(const Params &p) {
@@ -755,20 +754,19 @@ int launch_gemv_lds(const Params &p, const __half *x, long long ldx, int batch, 
 }
 
 // Layers that the pass kernel takes and that have at least two codebook groups: with a workspace of
-// slots x (batch x out_features + 16) binary32 sums every workgroup takes one slot; 0 when that does not apply.
-int gemv_lds_slots(const Params &p, int batch) { return group_slots(p, batch) + (outlier_slot(p, batch) ? 1 : 0); }
-
-size_t gemv_lds_slots_workspace_bytes(const Params &p, int batch) {
-  PassPlan plan;
-  if (p.orientation != 0 || p.n_groups < 2 || p.n_groups > 64 || !pass_pair(p)) return 0;
-  const int n_slots = group_slots(p, batch);
-  if (!make_pass_plan(p, 1, win_vectors(p.bits), entry_halfs(p.v), &plan, n_slots, outlier_slot(p, batch))) return 0;
-  return slots_bytes(p, gemv_lds_slots(p, batch), batch);
+// slots x (batch x out_features + 16) binary32 sums every workgroup takes one slot; 0 when that does not apply.  least: the fewest bytes that
+// are made use of, a group a slot, where a table each would be the better choice (a caller's workspace may be that of another batch).
+size_t gemv_lds_slots_workspace_bytes(const Params &p, int batch, bool least) {
+  if (p.orientation != 0 || p.n_groups < 2 || p.n_groups > 64 || !pass_pair(p) || rows_at_once(p, 1, p.n_groups) == 0) return 0;
+  return slots_bytes(p, (!least && table_slots(p, batch) ? 2 * p.n_groups : p.n_groups) + (outlier_slot(p, batch) ? 1 : 0), batch);
 }
 
-// The slots' sums into part [slots][batch][out_features] and part_xs [slots][16]; the caller adds them up.
-int launch_gemv_lds_slots(const Params &p, const __half *x, long long ldx, int batch, float *part, float *part_xs, hipStream_t s) {
-  const int n_slots = group_slots(p, batch);
+// The slots' sums into part [slots][batch][out_features] and behind them [slots][16], in a workspace of at least the least bytes;
+// the caller adds them up, *n_part slots.
+int launch_gemv_lds_slots(const Params &p, const __half *x, long long ldx, int batch, float *part, size_t bytes, int *n_part, hipStream_t s) {
+  const int n_slots = table_slots(p, batch) && bytes >= gemv_lds_slots_workspace_bytes(p, batch, false) ? 2 * p.n_groups : p.n_groups;
+  *n_part = n_slots + (outlier_slot(p, batch) ? 1 : 0);
+  float *part_xs = part + (size_t)*n_part * (size_t)batch * (size_t)p.out_features;
   int done = 0, g_max = 4;
   while (done < batch) {
     int g = batch - done >= 4 ? 4 : batch - done >= 2 ? 2 : 1;

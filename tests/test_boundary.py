@@ -266,3 +266,22 @@ def test_gemv_workspace_of_layers_whose_rows_leave_no_room_for_a_table_a_slot(ou
               idx_res=0x4000, idx_res_row_stride=stride, group_vectors=-(-vectors // 64) * 8)
     for batch in (1, 2):
         assert vq.vq_gemv_workspace_bytes(d, batch) == (8 * (batch * out_features + 16) * 4 + 255) // 256 * 256
+
+
+@pytest.mark.parametrize("perm", [None, 0x5000])
+@pytest.mark.parametrize("v,k,columns", [(12, 4096, 1024), (4, 256, 4096), (2, 16, 771)])
+@pytest.mark.parametrize("groups", [2, 5, 8])
+def test_gemv_workspace_of_more_rows_holds_that_of_fewer(perm, v, k, columns, groups):
+    """A loop lends the workspace of its largest batch to every call.  One and two rows of a layer with two tables a group take a slot a
+    table: where the workspace of more rows holds a slot a group for them, it holds those too."""
+    vectors = -(-columns // v)
+    stride = (vectors * (k - 1).bit_length() + 127) // 128 * 16
+    d = _desc(out_features=512, in_features=columns, v=v, k=k, k_res=k, codebook_res=0x3000, idx_row_stride=stride, idx_res=0x4000,
+              idx_res_row_stride=stride, group_vectors=-(-vectors // (8 * groups)) * 8, col_perm=perm)
+    sizes = [vq.vq_gemv_workspace_bytes(d, batch) for batch in range(1, 17)]
+    assert sizes[0] > 0
+    for rows in (1, 2):
+        head = (rows * ((columns + 7) // 8 * 8) * 2 + 255) // 256 * 256 if perm else 0
+        a_slot_a_group = head + (groups * (rows * 512 + 16) * 4 + 255) // 256 * 256
+        assert all(size >= sizes[rows - 1] for size in sizes[rows:] if size >= a_slot_a_group)
+    assert sizes[2] >= sizes[1]

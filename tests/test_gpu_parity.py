@@ -525,6 +525,28 @@ def test_gemv_lds_table_slots_with_two_tables(gpu_lib, groups, permuted, v, k, k
         assert (ws[need:] == 0xFF).all()
 
 
+@pytest.mark.parametrize("permuted", [False, True])
+@pytest.mark.parametrize("batch,lent_for", [(1, 3), (2, 3), (1, 4), (4, 4)])
+def test_gemv_lds_table_slots_with_the_workspace_of_other_rows(gpu_lib, permuted, batch, lent_for):
+    """Two tables a group: one and two rows take a table a slot, more another kernel, whose workspace has to do for fewer rows as well, and
+    for four rows of an odd width, which go to a group a slot.  That the workspace is made use of: its first sums are written."""
+    import torch
+    groups, v = 4, 12
+    L = s.make_layer(312, "slots", 611, v * (16 * groups - 3) - 1, v, 4096, 4000, group_vectors=16, permute=permuted)
+    assert L.n_groups == groups and L.in_features % 2 == 1
+    dl = gpu_lib.DeviceLayer(L)
+    x_np = s.make_activations(312, L, batch)
+    need = gpu_lib.vq_gemv_workspace_bytes(dl.desc, lent_for)
+    head = (batch * ((L.in_features + 7) // 8 * 8) * 2 + 255) // 256 * 256 if permuted else 0
+    ws = torch.full((need + 256,), 0xFF, dtype=torch.uint8, device="cuda")
+    y = gpu_lib.gemv(dl, torch.from_numpy(x_np).cuda(), workspace=ws[:need])
+    torch.cuda.synchronize()
+    _check_matmul(y, oracle.gemv(L, x_np), "permuted %s, batch %d, lent for %d" % (permuted, batch, lent_for))
+    assert (ws[need:] == 0xFF).all()
+    if not permuted or batch < 4:                     # (four gathered rows have an even width again)
+        assert torch.isfinite(ws[head : head + groups * batch * L.out_features * 4].view(torch.float32)).all()
+
+
 PERMUTED = [n for n in SMALL if n.startswith("perm_")]
 
 
