@@ -445,7 +445,7 @@ __global__ __launch_bounds__(LOOP_THREADS) void qcol_loop_kernel(LoopArgs a) {
       const int own = n * 16 + j * 4;                        // lane layout
       for (int nn = 0; nn < nb; ++nn) {
         Posted<VP> p = post_vectors<VP>(t, main_table, in, lane);
-        bool huge = p.brute;
+        bool odd = p.brute;
         search_table<VP, G>(&x.nearest[0][nn & 3][n], A, smem, a.k, p, main_table, lane, wave);
         lds_barrier();
         const ColumnConstants at = x.column[nn];
@@ -458,7 +458,7 @@ __global__ __launch_bounds__(LOOP_THREADS) void qcol_loop_kernel(LoopArgs a) {
 #pragma unroll
           for (int r = 0; r < EPL; ++r) rest[r] = __fsub_rn(t[r], q[r]);
           p = post_vectors<VP>(rest, res_table, in, lane);
-          huge |= p.brute;
+          odd |= p.brute;
           search_table<VP, GR>(&x.nearest[1][nn & 3][n], AR, smem + (size_t)a.k * EH * 2, a.k_res, p, res_table, lane, wave);
           lds_barrier();
           elements(entries_res, (unsigned)x.nearest[1][nn & 3][n], more);
@@ -471,13 +471,19 @@ __global__ __launch_bounds__(LOOP_THREADS) void qcol_loop_kernel(LoopArgs a) {
           }
         }
         // e = (t - q) / diag.  With the correctly rounded reciprocal, one correction of the rounded product gives the correctly rounded
-        // quotient (Markstein, IBM J. Res. Dev. 34, 1990), where nothing overflows: not for numbers out of the ordinary.
+        // quotient (Markstein, IBM J. Res. Dev. 34, 1990), where nothing overflows and the remainder, some 2^-47 of t - q, is a
+        // binary32 number: not for numbers out of the ordinary.
+        // (a t - q below 2^-80 is t, as entries are multiples of 2^-24; from there on the quotient is no subnormal number either)
+        unsigned least = ~0u;
+#pragma unroll
+        for (int r = 0; r < EPL; ++r) least = min(least, 2u * __float_as_uint(t[r]) - 1u);     // (but zero)
+        odd |= least < 2u * __float_as_uint(0x1p-80f) - 1u;
 #pragma unroll
         for (int r = 0; r < EPL; ++r) {
           const float diff = __fsub_rn(t[r], q[r]), about = __fmul_rn(diff, at.inverse);
-          e[r] = __fmaf_rn(__fmaf_rn(-about, at.diag, diff), at.inverse, about);
+          e[r] = __fmaf_rn(-__fmaf_rn(about, at.diag, -diff), at.inverse, about);
         }
-        if (__builtin_expect(__builtin_amdgcn_ballot_w64(huge | (at.inverse == 0.0f)) != 0ull, 0)) {
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(odd | (at.inverse == 0.0f)) != 0ull, 0)) {
 #pragma unroll
           for (int r = 0; r < EPL; ++r) e[r] = __fdiv_rn(__fsub_rn(t[r], q[r]), at.diag);
         }

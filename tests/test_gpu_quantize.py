@@ -159,6 +159,40 @@ def test_quantize_columns_paths(gpu_lib, name):
     assert np.array_equal(replay["What"], Wd.cpu().numpy().astype(np.float64))
 
 
+def test_quantize_columns_divides(gpu_lib):
+    """E is a division, rounded once, down to the subnormal numbers and for diagonals far from one.  The factor couples columns 2 i and
+    2 i + 1 alone, with 1, and the odd columns are zeros: T there is 0 - E of the column before."""
+    import torch
+    M, N = 72, 512
+    rng = np.random.default_rng(5)
+    W = np.zeros((M, N), dtype=np.float32)
+    exponent = rng.integers(-148, -60, (M, N // 2))
+    exponent[:, ::4] = rng.integers(-30, -4, (M, N // 8))
+    W[:, ::2] = (rng.uniform(1, 2, (M, N // 2)) * 2.0 ** exponent * rng.choice([-1.0, 1.0], (M, N // 2))).astype(np.float32)
+    W[::7, ::2] = -0.0
+    U = np.zeros((N, N), dtype=np.float32)
+    diagonal = rng.uniform(1, 2, N).astype(np.float32)
+    diagonal[64:128] *= np.float32(2.0) ** rng.integers(-39, 39, 64).astype(np.float32)
+    diagonal[128:160] *= -1.0
+    U[np.arange(N), np.arange(N)] = diagonal
+    U[np.arange(0, N, 2), np.arange(1, N, 2)] = 1.0
+    C = np.zeros((16, 6), dtype=np.float16)
+    C[1:] = s.to_fp16(s.normal(77, 15 * 6, 0.02)).reshape(15, 6)
+    Wd = torch.from_numpy(W).cuda()
+    idx_b, _, T = gpu_lib.quantize_columns(Wd, torch.from_numpy(U).cuda(), torch.from_numpy(C).cuda(), None, block=128)
+    torch.cuda.synchronize()
+    idx = _unpack(idx_b.cpu().numpy(), 4, N)
+    q = C[idx].transpose(0, 2, 1).reshape(-1, N)[:M].astype(np.float32)
+    T = T.cpu().numpy()
+    assert np.array_equal(T[:, ::2], W[:, ::2])
+    with np.errstate(under="ignore", over="ignore"):
+        E = (W - q)[:, ::2] / diagonal[::2]                          # (numpy divides binary32 numbers with one rounding)
+    got = T[:, 1::2]
+    wrong = got != -E
+    assert not wrong.any(), (int(wrong.sum()), W[:, ::2][wrong][:4], got[wrong][:4], -E[wrong][:4])
+    assert (E != 0).mean() > 0.5 and (np.abs(E[E != 0]) < 2.0 ** -126).any()
+
+
 def test_quantize_columns_restores_through_the_layer_path(gpu_lib):
     """The streams it writes are a layer of orientation 1: vq_dequant restores exactly the quantized weights it returned."""
     import torch
