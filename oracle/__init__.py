@@ -55,6 +55,8 @@ def lib():
         L.vq_oracle_assign.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32,
                                        ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32, ctypes.c_void_p, ctypes.c_int]
         L.vq_oracle_assign_down.argtypes = L.vq_oracle_assign.argtypes
+        L.vq_oracle_nearest_down.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, ctypes.c_void_p, ctypes.c_int32,
+                                             ctypes.c_int32, ctypes.c_void_p, ctypes.c_int]
         L.vq_oracle_matmul.argtypes = [ctypes.POINTER(_Layer), ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32,
                                        ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p, ctypes.c_int64, ctypes.c_int]
         L.vq_oracle_quantize_columns.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32, ctypes.c_void_p, ctypes.c_int32,
@@ -172,6 +174,18 @@ def assign(W: np.ndarray, codebook: np.ndarray, base: np.ndarray | None = None, 
     rc = fn(_ptr(W), _ptr(base), W.shape[1], W.shape[0], cols, _ptr(codebook), v, k, _ptr(out), n_threads or default_threads())
     if rc:
         raise OracleError("assign failed: %d" % rc)
+    return out
+
+
+def nearest_down(T: np.ndarray, codebook: np.ndarray, n_threads: int | None = None) -> np.ndarray:
+    """Index of the nearest centroid (fp16 [k][v]) of every vector down the columns of binary32 T [rows][cols], by the binary32 distance of
+    assign(): int32 [ceil(rows / v)][cols]."""
+    T, codebook = _c(T, np.float32), _c(codebook, np.float16)
+    k, v = codebook.shape
+    out = np.empty((-(-T.shape[0] // v), T.shape[1]), dtype=np.int32)
+    rc = lib().vq_oracle_nearest_down(_ptr(T), T.shape[1], T.shape[0], T.shape[1], _ptr(codebook), v, k, _ptr(out), n_threads or default_threads())
+    if rc:
+        raise OracleError("nearest_down failed: %d" % rc)
     return out
 
 

@@ -277,6 +277,33 @@ extern "C" int vq_oracle_assign_down(const uint16_t *W, const uint16_t *B, int64
   });
 }
 
+// The same choice for binary32 vectors.
+extern "C" int vq_oracle_nearest_down(const float *T, int64_t ld, int32_t rows, int32_t cols, const uint16_t *codebook, int32_t v, int32_t k,
+                                      int32_t *out, int n_threads) {
+  if (!T || !codebook || !out || rows < 1 || cols < 1 || ld < cols || v < 1 || k < 1) return VQO_ERR_ARG;
+  const int64_t S = ((int64_t)rows + v - 1) / v;
+  std::vector<float> C((size_t)k * v);
+  for (int64_t e = 0; e < (int64_t)k * v; ++e) C[e] = vq_oracle_half_to_float(codebook[e]);
+  return parallel_rows(S * cols, n_threads, [&](int64_t lo, int64_t hi) {
+    for (int64_t at = lo; at < hi; ++at) {
+      const int64_t p = at / cols, n = at % cols;
+      const int len = (int)std::min<int64_t>(v, rows - p * v);
+      int32_t best = 0;
+      float best_d = 0.0f;
+      for (int32_t i = 0; i < k; ++i) {
+        volatile float d = 0.0f;
+        for (int j = 0; j < len; ++j) {
+          volatile float diff = T[(p * v + j) * ld + n] - C[(size_t)i * v + j];
+          d = std::fmaf(diff, diff, d);
+        }
+        if (i == 0 || d < best_d) { best = i; best_d = d; }
+      }
+      out[at] = best;
+    }
+    return (int)VQO_OK;
+  });
+}
+
 // Algorithm 1 (Sec. 3.1): the quantizer's column loop, in the algorithm's order and notation.  See the header.
 extern "C" int vq_oracle_quantize_columns(const double *W0, const double *Hinv, int32_t M, int32_t N, const uint16_t *codebook, int32_t v,
                                           int32_t k, const uint16_t *codebook_res, int32_t k_res, int32_t B, const int32_t *given_idx,

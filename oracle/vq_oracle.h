@@ -106,6 +106,11 @@ int vq_oracle_assign(const uint16_t *W, const uint16_t *B, int64_t ld, int32_t r
 int vq_oracle_assign_down(const uint16_t *W, const uint16_t *B, int64_t ld, int32_t rows, int32_t cols,
                           const uint16_t *codebook, int32_t v, int32_t k, int32_t *out, int n_threads);
 
+/* vq_oracle_assign_down for vectors that are binary32 already (the columns as a column loop leaves them): T [rows][ld], out
+ * [ceil(rows / v)][cols]; t_j is T's element as it is, the rest of the arithmetic the same.                          */
+int vq_oracle_nearest_down(const float *T, int64_t ld, int32_t rows, int32_t cols, const uint16_t *codebook, int32_t v, int32_t k,
+                           int32_t *out, int n_threads);
+
 /* The column loop of the quantizer (Algorithm 1, Sec. 3.1 "VPTQ Algorithm"; the error update is the Delta W equation of
  * that section): columns are quantized one at a time, every column as a stack of length-v vectors that each take their
  * nearest centroid (Eq. 2; with a residual codebook, a second nearest centroid for what the first leaves, Sec. 3.2.2), the

@@ -159,6 +159,52 @@ def test_quantize_columns_paths(gpu_lib, name):
     assert np.array_equal(replay["What"], Wd.cpu().numpy().astype(np.float64))
 
 
+# Where the search has to tell more from less: every entry twice, entries that differ in their last bits.
+TIGHT = {
+    "every_entry_twice": dict(M=36, N=40, v=6, k=512, k_res=128, B=32, table="twice"),
+    "every_entry_twice_4096": dict(M=30, N=24, v=6, k=4096, k_res=0, B=32, table="twice"),
+    "last_bits": dict(M=48, N=40, v=8, k=1024, k_res=0, B=32, table="near"),
+    "last_bits_4096_res": dict(M=30, N=24, v=6, k=4096, k_res=4096, B=16, table="near"),
+}
+
+
+def _tight_tables(seed, case):
+    C, R = _tables(seed, case["k"], case["v"], case["k_res"])
+    for T in (C, R):
+        if T is None or "table" not in case:
+            continue
+        half = len(T) // 2
+        T[half:] = T[:half] if case["table"] == "twice" else np.nextafter(T[:half], np.float16(np.inf))
+    return C, R
+
+
+@pytest.mark.parametrize("name", list(CASES) + list(PATHS) + list(TIGHT))
+def test_quantize_columns_takes_the_first_of_the_nearest(gpu_lib, name):
+    """The distance of include/vq.h is binary32 arithmetic fixed to the last bit, and T is returned in binary32: every index is the first
+    one of the smallest distance from T's vector, and every residual index that of T less the main centroid (one subtraction)."""
+    import torch
+    case = {**CASES, **PATHS, **TIGHT}[name]
+    M, N, v, k, k_res, B = (case[n] for n in ("M", "N", "v", "k", "k_res", "B"))
+    seed = 120 + (list(CASES) + list(PATHS) + list(TIGHT)).index(name)
+    W0 = (s.make_weights(600 + seed, M, N).astype(np.float32) * case.get("w_scale", 1.0)).astype(np.float32)
+    H = s.make_hessian(600 + seed, N) * case.get("h_scale", 1.0)
+    U = np.ascontiguousarray(np.linalg.cholesky(np.linalg.inv(H)).T, dtype=np.float32)
+    C, R = _tight_tables(seed, case)
+    Wd = torch.from_numpy(W0).cuda()
+    idx_b, idx_res_b, T = gpu_lib.quantize_columns(Wd, torch.from_numpy(U).cuda(), torch.from_numpy(C).cuda(),
+                                                   torch.from_numpy(R).cuda() if k_res else None, block=B)
+    torch.cuda.synchronize()
+    idx = _unpack(idx_b.cpu().numpy(), oracle.index_bits(k), N)
+    T = T.cpu().numpy()
+    want = oracle.nearest_down(T, C)
+    assert np.array_equal(idx, want), (name, int((idx != want).sum()), np.argwhere(idx != want)[:4].tolist())
+    if k_res:
+        q = C[idx].transpose(0, 2, 1).reshape(-1, N)[:M].astype(np.float32)             # [positions][N][v] -> rows
+        want = oracle.nearest_down(T - q, R)
+        idx_res = _unpack(idx_res_b.cpu().numpy(), oracle.index_bits(k_res), N)
+        assert np.array_equal(idx_res, want), (name, int((idx_res != want).sum()), np.argwhere(idx_res != want)[:4].tolist())
+
+
 def test_quantize_columns_divides(gpu_lib):
     """E is a division, rounded once, down to the subnormal numbers and for diagonals far from one.  The factor couples columns 2 i and
     2 i + 1 alone, with 1, and the odd columns are zeros: T there is 0 - E of the column before."""

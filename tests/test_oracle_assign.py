@@ -138,3 +138,15 @@ def test_encoding_a_decoded_layer_of_the_papers_orientation_returns_its_indices(
     assert len(np.unique(L.codebook, axis=0)) == 256
     idx = oracle.assign(oracle.dequant(L), L.codebook, orientation=1)
     assert np.array_equal(idx, L.raw_idx)
+
+
+def test_nearest_of_binary32_vectors_is_assign_where_they_are_binary16_numbers():
+    """nearest_down on vectors down the columns, a cut-off block of rows among them, against assign(); and one vector off the binary16 grid
+    between two centroids."""
+    rng = np.random.default_rng(17)
+    C = rng.normal(0, 0.02, (100, 6)).astype(np.float16)
+    W = rng.normal(0, 0.02, (20, 31)).astype(np.float16)
+    assert np.array_equal(oracle.nearest_down(W.astype(np.float32), C), oracle.assign(W, C, orientation=1))
+    two = np.array([[1.0], [1.5]], dtype=np.float16)
+    T = np.array([[1.25, np.nextafter(np.float32(1.25), np.float32(2))]], dtype=np.float32)
+    assert oracle.nearest_down(T, two).tolist() == [[0, 1]]
