@@ -364,7 +364,37 @@ __device__ __forceinline__ void search_table(unsigned long long *nearest, const 
   }
 }
 
-template <int VP, int G, int GR>
+// The same for vectors of one or two elements: every distance, the first elements of an entry being the first slots of the operand that a
+// lane holds.  In so few dimensions many entries lie within the bounds of the largest score, and the search above takes them one after
+// the other.  600 columns, a last position of one row: v = 6, k = 4096 1727 -> 533 us, k = 1024 832 -> 399; v = 12, k = 4096 3080 -> 884; of two rows:
+// 825 -> 533, 438 -> 400, 1497 -> 885 (whole positions alone: 502, 388, 847).  Whole positions of v = 1, k = 4096, four a workgroup 2002 ->
+// 1133; of v = 2, two 933 -> 691, but four 1013 -> 1116: a vector after the other, where the search above takes four at once.
+template <int VP, int G>
+__device__ __forceinline__ void search_narrow(unsigned long long *nearest, const half8v (&A)[G][group_tiles(VP)], int count, const float (&t)[quarter(VP)], int P,
+                                              int lane, int wave) {
+  constexpr int SW = entries_wide(VP), TILES = group_tiles(VP);
+  if (wave * 16 >= count) return;
+  const bool holds = operand_part<VP>(lane) == 0;
+  for (int n = 0; n < P; ++n) {
+    const float t0 = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(t[0]), 4 * n));
+    const float t1 = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(t[1]), 4 * n));
+    unsigned d = ~0u, at = 0u;
+#pragma unroll
+    for (int i = 0; i < G * TILES; ++i) {
+      const half8v &c = A[i / TILES][i % TILES];
+      const float d0 = __fmaf_rn((float)c[0], -1.0f, t0), d1 = __fmaf_rn((float)c[1], -1.0f, t1);
+      const unsigned bits = __float_as_uint(__fmaf_rn(d1, d1, __fmaf_rn(d0, d0, 0.0f)));
+      at = bits < d ? (unsigned)i : at;
+      d = min(d, bits);
+    }
+    const unsigned i = min((at * SW + (lane >> 4) * SW / 4) * (SEARCH * 16) + wave * 16 + (lane & 15), (unsigned)count - 1u);
+    const unsigned least = wave_min_u32(holds ? d : ~0u), first = wave_min_u32(holds && d == least ? i : ~0u);
+    if (lane == 0) __hip_atomic_fetch_min(nearest + n, (unsigned long long)least << 32 | first, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+}
+
+// SHORT: with positions of one or two rows among them (a kernel of its own, as the second search costs the first one 4 %).
+template <int VP, int G, int GR, bool SHORT>
 __global__ __launch_bounds__(LOOP_THREADS) void qcol_loop_kernel(LoopArgs a) {
   constexpr int EH = loop_entry_halfs<VP>(), EPL = quarter(VP), POS = 32 / VP < PMAX ? 32 / VP : PMAX;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -381,6 +411,7 @@ __global__ __launch_bounds__(LOOP_THREADS) void qcol_loop_kernel(LoopArgs a) {
   const int P = cut ? 1 : min(a.P, a.whole - pos0);
   const int first = cut ? a.whole : pos0;                                  // its first position
   const int len = cut ? a.rows - a.whole * a.v : a.v;                      // rows of a position: what its vectors are compared over
+  const bool narrow = len == 1 || (len == 2 && P <= 2);                    // (see search_narrow)
 
   // tables: entries in LDS (elements past `len` as zeros), operands in registers
   for (int e = tid; e < (a.k + a.k_res) * EH; e += threads) {
@@ -446,7 +477,8 @@ __global__ __launch_bounds__(LOOP_THREADS) void qcol_loop_kernel(LoopArgs a) {
       for (int nn = 0; nn < nb; ++nn) {
         Posted<VP> p = post_vectors<VP>(t, main_table, in, lane);
         bool odd = p.brute;
-        search_table<VP, G>(&x.nearest[0][nn & 3][n], A, smem, a.k, p, main_table, lane, wave);
+        if (SHORT && narrow) search_narrow<VP, G>(x.nearest[0][nn & 3], A, a.k, t, P, lane, wave);
+        else search_table<VP, G>(&x.nearest[0][nn & 3][n], A, smem, a.k, p, main_table, lane, wave);
         lds_barrier();
         const ColumnConstants at = x.column[nn];
         float next[EPL], q[EPL], e[EPL];
@@ -459,7 +491,8 @@ __global__ __launch_bounds__(LOOP_THREADS) void qcol_loop_kernel(LoopArgs a) {
           for (int r = 0; r < EPL; ++r) rest[r] = __fsub_rn(t[r], q[r]);
           p = post_vectors<VP>(rest, res_table, in, lane);
           odd |= p.brute;
-          search_table<VP, GR>(&x.nearest[1][nn & 3][n], AR, smem + (size_t)a.k * EH * 2, a.k_res, p, res_table, lane, wave);
+          if (SHORT && narrow) search_narrow<VP, GR>(x.nearest[1][nn & 3], AR, a.k_res, rest, P, lane, wave);
+          else search_table<VP, GR>(&x.nearest[1][nn & 3][n], AR, smem + (size_t)a.k * EH * 2, a.k_res, p, res_table, lane, wave);
           lds_barrier();
           elements(entries_res, (unsigned)x.nearest[1][nn & 3][n], more);
 #pragma unroll
@@ -660,11 +693,14 @@ __global__ __launch_bounds__(LOOP_THREADS) void qcol_loop_kernel(LoopArgs a) {
   }
 }
 
-template <int VP, int G, int GR>
+template <int VP, int G, int GR, bool SHORT = false>
 int launch_loop(LoopArgs a, hipStream_t st) {
-  auto kernel = qcol_loop_kernel<VP, G, GR>;
+  const int cut_rows = a.rows - a.whole * a.v, cut = cut_rows > 0;
+  // (tables of up to 256 entries hold too few within the bounds: v = 6, a last position of one row 454 us, of more 351)
+  if constexpr (!SHORT && (G > 1 || GR > 1))
+    if ((cut && cut_rows <= 2) || a.v <= 2) return launch_loop<VP, G, GR, true>(a, st);
+  auto kernel = qcol_loop_kernel<VP, G, GR, SHORT>;
   VQ_ALLOW_FULL_LDS(kernel);
-  const int cut = a.rows - a.whole * a.v > 0;
   const unsigned grid = (unsigned)((a.whole + a.P - 1) / a.P + cut);
   hipLaunchKernelGGL(kernel, dim3(grid), dim3(LOOP_THREADS), loop_lds_bytes<VP>(a.k, a.k_res), st, a);
   return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;

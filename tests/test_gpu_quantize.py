@@ -159,12 +159,24 @@ def test_quantize_columns_paths(gpu_lib, name):
     assert np.array_equal(replay["What"], Wd.cpu().numpy().astype(np.float64))
 
 
-# Where the search has to tell more from less: every entry twice, entries that differ in their last bits.
+# Where the search has to tell more from less: every entry twice, entries that differ in their last bits, a last position of one or two
+# rows (in one or two dimensions many entries are about as near), vectors of one to three elements, weights beyond binary16's range.
 TIGHT = {
     "every_entry_twice": dict(M=36, N=40, v=6, k=512, k_res=128, B=32, table="twice"),
     "every_entry_twice_4096": dict(M=30, N=24, v=6, k=4096, k_res=0, B=32, table="twice"),
     "last_bits": dict(M=48, N=40, v=8, k=1024, k_res=0, B=32, table="near"),
     "last_bits_4096_res": dict(M=30, N=24, v=6, k=4096, k_res=4096, B=16, table="near"),
+    "one_row_left": dict(M=25, N=71, v=6, k=4096, k_res=256, B=64),
+    "one_row_left_wide": dict(M=33, N=40, v=16, k=1024, k_res=0, B=40),
+    "one_row_left_v12": dict(M=25, N=40, v=12, k=4096, k_res=0, B=40),
+    "one_row_left_v8": dict(M=9, N=60, v=8, k=3000, k_res=200, B=64),
+    "two_rows_left": dict(M=20, N=60, v=6, k=4096, k_res=4096, B=64),
+    "two_rows_left_v12": dict(M=26, N=40, v=12, k=4096, k_res=0, B=40),
+    "three_rows_left": dict(M=21, N=60, v=6, k=4096, k_res=0, B=64),
+    "v1": dict(M=40, N=40, v=1, k=1024, k_res=60, B=32),
+    "v2": dict(M=41, N=40, v=2, k=4096, k_res=0, B=32),
+    "v3": dict(M=3100, N=20, v=3, k=2000, k_res=0, B=32),
+    "one_row_left_out_of_scale": dict(M=25, N=40, v=6, k=4096, k_res=16, B=32, w_scale=2.0 ** 20),
 }
 
 
