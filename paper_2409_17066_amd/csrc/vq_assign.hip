@@ -11,6 +11,7 @@
 // compute every distance on the vector ALUs, 2 v + 3 instructions per (vector, centroid) pair: assign_short_kernel for
 // tables of fewer entries, assign_kernel for longer vectors.
 #include "vq_common.hpp"
+#include <type_traits>
 
 namespace vq {
 namespace {
@@ -155,14 +156,47 @@ __device__ __forceinline__ void load_entries(const __half *codebook, const int (
 #pragma unroll
       for (int j = 0; j < V; ++j) c[n][j] = __builtin_bit_cast(_Float16, codebook[(long long)i[n] * stride + j]);
   }
+  // (whole dwords masked: a choice for every element takes several instructions)
+  unsigned mask[8];
 #pragma unroll
-  for (int n = 0; n < N; ++n)
+  for (int d = 0; d < 8; ++d) mask[d] = len > 2 * d + 1 ? 0xFFFFFFFFu : len > 2 * d ? 0xFFFFu : 0u;
+#pragma unroll
+  for (int n = 0; n < N; ++n) {
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
-      if (j < V && len < V) c[n][j] = j < len ? c[n][j] : (_Float16)0.0f;
       if (j < 8) c0[n][j] = c[n][j];
       else c1[n][j & 7] = c[n][j];
     }
+    uint4v w0 = __builtin_bit_cast(uint4v, c0[n]), w1 = __builtin_bit_cast(uint4v, c1[n]);
+#pragma unroll
+    for (int d = 0; d < (V + 1) / 2; ++d) {
+      if (d < 4) w0[d & 3] &= mask[d];
+      else w1[d & 3] &= mask[d];
+    }
+    c0[n] = __builtin_bit_cast(half8, w0); c1[n] = __builtin_bit_cast(half8, w1);
+  }
+}
+
+// Distances from t to N entries in memory.
+template <int V, int N>
+__device__ __forceinline__ void distances_to(const __half *codebook, const int (&i)[N], int stride, int len, bool whole, const float (&t)[V], float (&d)[N]) {
+  if constexpr (V % 2 == 0) {
+    half8 c0[N], c1[N];
+    load_entries<V, N>(codebook, i, stride, len, whole, c0, c1);
+#pragma unroll
+    for (int n = 0; n < N; ++n) d[n] = distance<V>(t, c0[n], c1[n]);
+  } else {                                                   // (loaded one by one, and not packed to be taken apart again)
+    float c[N][V];
+#pragma unroll
+    for (int n = 0; n < N; ++n)
+#pragma unroll
+      for (int j = 0; j < V; ++j) {
+        const float y = __half2float(codebook[(long long)i[n] * stride + j]);
+        c[n][j] = j < len ? y : 0.0f;
+      }
+#pragma unroll
+    for (int n = 0; n < N; ++n) d[n] = distance<V>(t, [&](int j) -> float { return c[n][j]; });
+  }
 }
 
 // The lanes' candidates meet: the smaller distance, else the smaller index.  Distances are sums of squares, so their bits order
@@ -626,13 +660,13 @@ __global__ __launch_bounds__(WAVES * 64, 4) void assign_screen_kernel(Vectors fi
         constexpr int QUADS = NT == 1 ? 2 : 1;
 #pragma unroll QUADS
         for (int quad = 0; quad < MINE / 4; ++quad) {
-          half8 c0[4], c1[4];
           int which[4];
+          float d[4];
 #pragma unroll
           for (int r = 0; r < 4; ++r) which[r] = min(row0 + r + 8 * quad, k - 1);
-          load_entries<V, 4>(codebook, which, stride, a.len, whole, c0, c1);
+          distances_to<V, 4>(codebook, which, stride, a.len, whole, t, d);
 #pragma unroll
-          for (int r = 0; r < 4; ++r) consider(distance<V>(t, c0[r], c1[r]), r + 8 * quad);
+          for (int r = 0; r < 4; ++r) consider(d[r], r + 8 * quad);
         }
       }
       unsigned arg = best < __builtin_inff() ? (unsigned)min(row0 + nearest, k - 1) : 0u;
@@ -652,14 +686,17 @@ __global__ __launch_bounds__(WAVES * 64, 4) void assign_screen_kernel(Vectors fi
           for (int j = 0; j < V; ++j) tv[j] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t[j]), w));
           float bd = __builtin_inff();
           unsigned bi = 0xFFFFFFFFu;
-          for (int i0 = lane; i0 < rows_lds; i0 += 128) {      // (rows_lds is a multiple of 128)
+          auto compare = [&](int i0, auto entries) {
 #pragma unroll
-            for (int y = 0; y < 2; ++y) {
+            for (int y = 0; y < decltype(entries)::value; ++y) {
               const int i = i0 + 64 * y;
               const float d = distance<V>(tv, plane[i], plane[V > 8 ? rows_lds + i : i]);
               if (d < bd) { bd = d; bi = (unsigned)i; }
             }
-          }
+          };
+          int i0 = lane;                                       // (rows_lds is a multiple of 128; two at a time 297 x 4231 took 332 us, 298)
+          for (; i0 + 192 < rows_lds; i0 += 256) compare(i0, std::integral_constant<int, 4>{});
+          if (i0 < rows_lds) compare(i0, std::integral_constant<int, 2>{});
           wave_arg_min(bd, bi);
           if (lane == w) arg = bi == 0xFFFFFFFFu ? 0u : bi;    // (no distance below infinity: the first centroid)
         }
@@ -681,18 +718,20 @@ __global__ __launch_bounds__(WAVES * 64, 4) void assign_screen_kernel(Vectors fi
         load_vector<V, BASE>(a, o, p, true, t);
         float bd = __builtin_inff();
         unsigned bi = 0xFFFFFFFFu;
-        for (int i0 = from; i0 < to; i0 += 256) {
-          half8 c0[4], c1[4];
-          int which[4];
+        auto compare = [&](int i0, auto entries) {
+          constexpr int N = decltype(entries)::value;
+          int which[N];
+          float d[N];
 #pragma unroll
-          for (int y = 0; y < 4; ++y) which[y] = min(i0 + 64 * y + lane, k - 1);
-          load_entries<V, 4>(codebook, which, stride, a.len, whole, c0, c1);
+          for (int y = 0; y < N; ++y) which[y] = min(i0 + 64 * y + lane, k - 1);
+          distances_to<V, N>(codebook, which, stride, a.len, whole, t, d);
 #pragma unroll
-          for (int y = 0; y < 4; ++y) {
-            const float d = distance<V>(t, c0[y], c1[y]);
-            if (d < bd) { bd = d; bi = (unsigned)which[y]; }
-          }
-        }
+          for (int y = 0; y < N; ++y)
+            if (d[y] < bd) { bd = d[y]; bi = (unsigned)which[y]; }
+        };
+        int i0 = from;
+        for (; i0 + 256 <= to; i0 += 256) compare(i0, std::integral_constant<int, 4>{});
+        for (; i0 < to; i0 += 64) compare(i0, std::integral_constant<int, 1>{});        // (a share need not fill fours: k = 5000, 320)
         wave_arg_min(bd, bi);
         if (lane == 0) { found_d[x * WAVES + wave] = bd; found_i[x * WAVES + wave] = bi; }
       }

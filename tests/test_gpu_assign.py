@@ -232,3 +232,21 @@ def test_assign_two_tiles_a_wave(gpu_lib, name):
             with np.errstate(all="ignore"):
                 want = oracle.assign(W[part], C, base=B[part] if with_base else None, orientation=orientation)
             assert np.array_equal(got[at:at + 1], s.pack_indices(want, oracle.index_bits(k), idx.shape[1])), (name, orientation, at)
+
+
+@pytest.mark.parametrize("v,k", [(3, 5000), (5, 4097), (6, 4300), (8, 8192), (12, 4700), (13, 5000), (6, 4096), (6, 130), (8, 384)])
+@pytest.mark.parametrize("with_base", [False, True])
+def test_assign_of_cut_off_vectors_of_one_element(gpu_lib, v, k, with_base):
+    """Among scalars many entries are about as near, so that every distance is computed: tables whose shares do not fill the steps of that
+    loop, elements loaded one by one and in whole entries, entries twice in the table."""
+    import torch
+    rows, cols = 3 * v + 1, 40 * v + 1
+    W, C, B = (s.to_fp16(s.normal(7700 + 10 * v + i, n, 0.02)) for i, n in enumerate((rows * cols, k * v, rows * cols)))
+    W, C, B = W.reshape(rows, cols), C.reshape(k, v), B.reshape(rows, cols) if with_base else None
+    C[k - 20:] = C[:20]
+    for orientation in (0, 1):
+        idx = gpu_lib.assign(torch.from_numpy(W).cuda(), torch.from_numpy(C).cuda(), base=torch.from_numpy(B).cuda() if with_base else None,
+                             orientation=orientation)
+        torch.cuda.synchronize()
+        want = oracle.assign(W, C, base=B, orientation=orientation)
+        assert np.array_equal(idx.cpu().numpy(), s.pack_indices(want, oracle.index_bits(k), idx.shape[1])), (v, k, orientation)
