@@ -520,6 +520,16 @@ __global__ __launch_bounds__(PIECES_THREADS, 4) void dequant_pieces_kernel(Param
 
 unsigned table_bytes(int v, int k) { return ((unsigned)k * (unsigned)v * 2u + 1023u) / 1024u * 1024u; }      // in LDS: whole pieces of 1 KB
 
+// In front of a product W goes through the caches as long as they hold it beside the rest: v8 / 65536 at 300 tokens 4096 x 4096 43.8 -> 34.9 us,
+// 11008 x 4096 102 -> 91, v12 / 4096 + 4096 2048 x 4096 28.8 -> 25.7; 8192 x 8192 at 300 tokens 141 -> 146, but at 2048 300 -> 290.  Not in front of
+// a short product of short rows: of 36 shapes of less than 1216 columns, 6 to 14 MB and up to 191 tokens 34 were slower through the caches, by
+// 4 % on average (10520 x 576, 36 tokens 15.3 -> 17.2; smaller ones, longer rows and more tokens gain: 700 shapes 6 % on average).
+bool through_caches(long long w_bytes, int in_features, int product_tokens) {
+  if (product_tokens <= 0 || w_bytes > 192LL << 20) return false;
+  if (in_features < 1216 && product_tokens < 192 && w_bytes >= 6LL << 20 && w_bytes < 14LL << 20) return false;
+  return w_bytes <= 96LL << 20 || product_tokens >= MANY_TOKENS;
+}
+
 template <auto KERNEL, int NW> int launch_kernel(dim3 grid, unsigned lds, hipStream_t s, const Params &p, const DqArgs &a) {
   VQ_ALLOW_FULL_LDS(KERNEL);
   hipLaunchKernelGGL(KERNEL, grid, dim3(NW * 64), lds, s, p, a);
@@ -578,11 +588,9 @@ int launch_one(const Params &p, __half *W, long long ldw, hipStream_t s, int pro
   if (items <= wgs * nw) { a.wave_step = a.wgs; a.wg_step = 1; }      // no wave has two: every workgroup gets its share
   if (p.Q) a.out_wgs = (int)min((long long)(p.S_out + nw - 1) / nw, (long long)cu_count());
   const dim3 grid((unsigned)(wgs * p.n_groups + a.out_wgs));
-  // (in front of a product W goes through the caches as long as they hold it beside the rest: v8 / 65536 at 300 tokens 4096 x 4096 43.8 -> 34.9 us,
-  // 11008 x 4096 102 -> 91, v12 / 4096 + 4096 2048 x 4096 28.8 -> 25.7; 8192 x 8192 at 300 tokens 141 -> 146, but at 2048 300 -> 290)
   // past the caches: where lookups go through L2, from which W must not push the table; and where W is larger than they are
   // (down the outputs only if rows start on 64 bytes: with pieces of lines between them 8192 x 20480 took 103 us past the caches, 97 through)
-  const bool through = product_tokens > 0 && (w_bytes <= 96LL << 20 || (product_tokens >= MANY_TOKENS && w_bytes <= 192LL << 20));
+  const bool through = through_caches(w_bytes, p.in_features, product_tokens);
   const uintptr_t starts = reinterpret_cast<uintptr_t>(W) | (uintptr_t)ldw * 2 | (uintptr_t)p.n_out * 2;
   const bool stream = (L2_LOOKUPS && !through && (starts & 15) == 0) || (w_bytes > 256LL << 20 && (!DOWN || (starts & 63) == 0));
   const int rc = small ? (stream ? launch_kernel<dequant_tables_kernel<V, BITS, RBITS, RES, DOWN, 8, true>, 8>(grid, bytes, s, p, a)
