@@ -187,6 +187,20 @@ def torch_double(a):
     return torch.from_numpy(a.astype(np.float64)).cuda()
 
 
+@pytest.mark.parametrize("scaled", [(True, False), (False, True), (False, False)])
+@pytest.mark.parametrize("tiles", [0, 1, 5])
+def test_gemm_centroids_without_scale_or_bias(gpu_lib, monkeypatch, scaled, tiles):
+    """The centroids' product, whose last step applies scale and bias to the sums, of layers that lack one or both of them."""
+    import torch
+    monkeypatch.setenv("VQ_SWITCHES", "gemm=c,dense=%d" % tiles)
+    L = s.make_layer(9, "unscaled", 333, 520, v=6, k=256, k_res=256)
+    L.scale, L.bias = L.scale if scaled[0] else None, L.bias if scaled[1] else None
+    x = s.make_activations(302, L, 131)
+    Y = gpu_lib.gemm(gpu_lib.DeviceLayer(L), torch.from_numpy(x).cuda())
+    torch.cuda.synchronize()
+    _check_matmul(Y, oracle.gemm(L, x), "scale %s, bias %s" % scaled)
+
+
 HOLD_THE_WEIGHTS = {            # layers and token counts that vq_gemm without a workspace computes from unrounded weights
     "v6, 64 tokens": (dict(out_features=512, in_features=1536, v=6, k=4096), 64),
     "v6, no room for tiles": (dict(out_features=512, in_features=1536, v=6, k=4096, k_res=4096), 100),
