@@ -522,11 +522,13 @@ unsigned table_bytes(int v, int k) { return ((unsigned)k * (unsigned)v * 2u + 10
 
 // In front of a product W goes through the caches as long as they hold it beside the rest: v8 / 65536 at 300 tokens 4096 x 4096 43.8 -> 34.9 us,
 // 11008 x 4096 102 -> 91, v12 / 4096 + 4096 2048 x 4096 28.8 -> 25.7; 8192 x 8192 at 300 tokens 141 -> 146, but at 2048 300 -> 290.  Not in front of
-// a short product of short rows: of 36 shapes of less than 1216 columns, 6 to 14 MB and up to 191 tokens 34 were slower through the caches, by
-// 4 % on average (10520 x 576, 36 tokens 15.3 -> 17.2; smaller ones, longer rows and more tokens gain: 700 shapes 6 % on average).
-bool through_caches(long long w_bytes, int in_features, int product_tokens) {
+// a short product of short rows: of 38 shapes of less than 1216 columns, 0.4 to 0.9 million vectors and up to 191 tokens 36 were slower through the
+// caches, by 4 % on average (v8 10520 x 576, 36 tokens 15.3 -> 17.2, v12 12312 x 576, 67 tokens 19.5 -> 21.4; smaller ones, longer rows and more tokens
+// gain: 700 shapes 6 % on average).
+bool through_caches(const Params &p, int product_tokens) {
+  const long long w_bytes = (long long)p.out_features * p.in_features * 2, vectors = (long long)p.S * p.P;
   if (product_tokens <= 0 || w_bytes > 192LL << 20) return false;
-  if (in_features < 1216 && product_tokens < 192 && w_bytes >= 6LL << 20 && w_bytes < 14LL << 20) return false;
+  if (p.in_features < 1216 && product_tokens < 192 && vectors >= 3 << 17 && vectors < 7 << 17) return false;
   return w_bytes <= 96LL << 20 || product_tokens >= MANY_TOKENS;
 }
 
@@ -590,7 +592,7 @@ int launch_one(const Params &p, __half *W, long long ldw, hipStream_t s, int pro
   const dim3 grid((unsigned)(wgs * p.n_groups + a.out_wgs));
   // past the caches: where lookups go through L2, from which W must not push the table; and where W is larger than they are
   // (down the outputs only if rows start on 64 bytes: with pieces of lines between them 8192 x 20480 took 103 us past the caches, 97 through)
-  const bool through = through_caches(w_bytes, p.in_features, product_tokens);
+  const bool through = through_caches(p, product_tokens);
   const uintptr_t starts = reinterpret_cast<uintptr_t>(W) | (uintptr_t)ldw * 2 | (uintptr_t)p.n_out * 2;
   const bool stream = (L2_LOOKUPS && !through && (starts & 15) == 0) || (w_bytes > 256LL << 20 && (!DOWN || (starts & 63) == 0));
   const int rc = small ? (stream ? launch_kernel<dequant_tables_kernel<V, BITS, RBITS, RES, DOWN, 8, true>, 8>(grid, bytes, s, p, a)
@@ -619,6 +621,13 @@ int launch_pair(const Params &p, __half *W, long long ldw, hipStream_t s, int pr
 }
 
 }  // namespace
+
+// Whether launch_dequant leaves W, or so many matrices of its size, in the caches for a product of so many tokens.
+bool dequant_leaves_cached(const Params &p, int product_tokens, int matrices) {
+  const long long w_bytes = (long long)p.out_features * p.in_features * 2 * matrices;
+  const bool l2_lookups = p.bits == 16 || (p.k_res && table_bytes(p.v, p.k) + table_bytes(p.v, p.k_res) > 160 * 1024);
+  return l2_lookups ? through_caches(p, product_tokens) : w_bytes <= 224LL << 20;      // (beside X, Y and the streams)
+}
 
 // The whole matrix in stored column order; VQ_ERR_UNSUPPORTED for (v, index width) pairs without a compiled kernel.
 int launch_dequant_tables(const Params &p, __half *W, long long ldw, hipStream_t s, int product_tokens) {

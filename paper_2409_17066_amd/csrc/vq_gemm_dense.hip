@@ -257,16 +257,19 @@ int launch_tiles(DenseArgs a, hipStream_t s) {
 // in 256 tiles of 192 x 128; 900 x 8192 x 8192: 134 -> 116 in 256 of 128 x 256; 700 x 11008 x 4096: 75 -> 63 in 232 of 192 x 192;
 // 200 x 11008 x 4096: 31.3 -> 29.4 in 232 of 64 x 192), and none more than 1.4 % less.  128 x 192 in two stages is not among
 // them: 509 x 11008 x 4096 54.7 -> 50.9 us with W in the caches, but 3 % slower together with the restoring of W where W's memory is not.
+// For the same reason 64 x 192 in three stages is not for a W past the caches, where 128 x 128, 2 % more by the sums below, is the faster one
+// (v = 8 / 65536: 13016 x 7808, 169 tokens 145 -> 132 us, 7088 x 11712, 291 tokens 158 -> 141, 6768 x 10432, 395 tokens 137 -> 125; W in the caches, 40
+// shapes: 4 % slower).
 struct TileKind {
   int mb, nb, per_cu;
   float round, step[2];
   int (*launch)(DenseArgs, hipStream_t);
-  bool later = false;
+  bool later = false, cached = false;              // cached: only where W is in the caches
 };
 const TileKind kTiles[] = {
     {4, 4, 1, 9.9f, {1.12f, 0.0f}, launch_tiles<4, 4, 2, false>},  {2, 4, 1, 5.3f, {0.755f, 0.0f}, launch_tiles<2, 4, 3, false>, true},
     {3, 3, 1, 6.2f, {0.752f, 0.0f}, launch_tiles<3, 3, 3, false>, true}, {3, 2, 1, 5.3f, {0.545f, 0.0f}, launch_tiles<3, 2, 3, false>, true},
-    {1, 3, 1, 4.0f, {0.375f, 0.0f}, launch_tiles<1, 3, 3, false>, true}, {4, 3, 1, 7.6f, {0.90f, 0.0f}, launch_tiles<4, 3, 2, false>},
+    {1, 3, 1, 4.0f, {0.375f, 0.0f}, launch_tiles<1, 3, 3, false>, true, true}, {4, 3, 1, 7.6f, {0.90f, 0.0f}, launch_tiles<4, 3, 2, false>},
     {2, 2, 1, 4.2f, {0.383f, 0.0f}, launch_tiles<2, 2, 3, false>}, {1, 3, 2, 2.1f, {0.478f, 0.767f}, launch_tiles<1, 3, 2, false>},
     {1, 2, 2, 2.3f, {0.273f, 0.558f}, launch_tiles<1, 2, 3, false>}, {1, 1, 2, 1.2f, {0.190f, 0.384f}, launch_tiles<1, 1, 4, false>},
 };
@@ -280,6 +283,7 @@ float tile_cost(const TileKind &t, int tokens, int out_features, int in_features
 
 }  // namespace
 
+bool dequant_leaves_cached(const Params &p, int product_tokens, int matrices);
 bool gemm_dense_applicable(const Params &p) { return p.in_features % 8 == 0; }       // (16-byte chunks of W's rows)
 
 // The tile shape with the least estimated time.  Switch dense=0 / =n: always the last one / number n of the list, for tests.  With xsum, the
@@ -293,6 +297,7 @@ int launch_gemm_dense(const Params &p, const __half *X, long long ldx, int token
   const long long most_tokens = std::min(room / (ldx * 2), (room * 2 - 4096) / (ldy * 2)) - pad, most_out = (room - w2) / (ldw * 2) - pad;
   if (most_tokens < 1 || most_out < 1) return VQ_ERR_UNSUPPORTED;
   const int force = switches().dense;
+  const bool cached = dequant_leaves_cached(p, tokens, w2 ? 2 : 1);
   for (long long o = 0; o < p.out_features; o += most_out)
     for (long long t = 0; t < tokens; t += most_tokens) {
       const int nt = (int)std::min<long long>(most_tokens, tokens - t), no = (int)std::min<long long>(most_out, p.out_features - o);
@@ -300,7 +305,7 @@ int launch_gemm_dense(const Params &p, const __half *X, long long ldx, int token
       const TileKind *best = &kTiles[force > 0 && force <= kinds ? force - 1 : kinds - 1];
       if (force < 0)
         for (const TileKind &k : kTiles)
-          if (tile_cost(k, nt, no, p.in_features, cu_count()) < tile_cost(*best, nt, no, p.in_features, cu_count())) best = &k;
+          if ((cached || !k.cached) && tile_cost(k, nt, no, p.in_features, cu_count()) < tile_cost(*best, nt, no, p.in_features, cu_count())) best = &k;
       const int rc = best->launch({X + t * ldx, ldx, nt, Wd + o * ldw, ldw, no, p.in_features, Y + t * ldy + o, ldy, 0, 0, w2,
                                    p.scale ? p.scale + o : nullptr, p.bias ? p.bias + o : nullptr, xsum ? xsum + t : nullptr}, s);
       if (rc != VQ_OK) return rc;

@@ -188,6 +188,34 @@ def test_long_prompts_of_the_v8_setting_restore_the_same_weights(gpu_lib, out, i
     _matmul_ok(Y[:, torch.from_numpy(rows.astype(np.int64)).cuda()][:64], oracle.gemm(L, x[:64].cpu().numpy(), rows=rows), "v8 %d x %d, 1024 tokens" % (out, inp))
 
 
+@pytest.mark.parametrize("out,inp,tokens,permute,setting", [
+    (8191, 16000, 1024, False, dict(v=8, k=65536)),              # W of 262 MB: past the caches, from the pieces of the table
+    (7371, 8200, 1024, True, dict(v=8, k=65536)),                # permuted columns: the gathered activations lie in front of W
+    (6003, 1000, 40, False, dict(v=8, k=65536)),                 # a short product of short rows: past the caches
+    (9001, 600, 130, False, dict(v=12, k=4096, k_res=4096)),
+    (6003, 1000, 200, True, dict(v=8, k=65536, k_res=256)),      # more tokens: through them
+])
+def test_restoring_in_front_of_a_product_leaves_the_same_weights(gpu_lib, out, inp, tokens, permute, setting):
+    """What vq_gemm restores into its workspace is what vq_dequant restores from the layer in stored order, bit for bit, whichever way the
+    stores go; and the product is that of a few rows."""
+    import torch
+    L = s.make_layer(5, "front", out, inp, permute=permute, **setting)
+    dl = gpu_lib.DeviceLayer(L)
+    size = gpu_lib.vq_gemm_fast_workspace_bytes(dl.desc, tokens)
+    head = (tokens * inp * 2 + 255) // 256 * 256 if permute else 0
+    assert size >= head + out * inp * 2
+    ws = torch.full((size,), 0xFF, dtype=torch.uint8, device="cuda")
+    x = torch.randn((tokens, inp), device="cuda").half()
+    Y = gpu_lib.gemm(dl, x, workspace=ws)
+    rows = np.array([0, 1, out // 2, out - 1], dtype=np.int32)
+    ref = oracle.gemm(L, x[:16].cpu().numpy(), rows=rows)
+    L.col_perm = None
+    W = gpu_lib.dequant(gpu_lib.DeviceLayer(L))
+    torch.cuda.synchronize()
+    assert torch.equal(ws[head : head + out * inp * 2].view(torch.int16), W.view(torch.int16).reshape(-1))
+    _matmul_ok(Y[:, torch.from_numpy(rows.astype(np.int64)).cuda()][:16], ref, "%d x %d, %d tokens" % (out, inp, tokens))
+
+
 # Rows for which a workgroup of the matrix-core kernel has 4, 5, 6 and 7 blocks of sixteen (256 compute units): one chunk over the tables
 # where its partial sums do not fit beside them, one beside them, and two chunks of four and three blocks.
 @pytest.mark.parametrize("out,k_res,outliers", [(12300, 4096, 0), (16400, 0, 0), (20480, 256, 8), (24560, 4096, 8), (24561, 256, 0), (24592, 4096, 0)])
