@@ -67,14 +67,21 @@ __device__ __forceinline__ float4v mfma16(uint4v a, uint4v b, float4v c) {
 // LDS address, activations loaded straight into MFMA operand registers, load addresses advanced by
 // additions, end-of-row masking only in the one column group that needs it.
 // `wg` is the workgroup's number within its layer (a launch may hold the workgroups of several layers).
-template <int RES_BITS, int MW, int NB, bool GROUPED>
+// ONE_GROUP: of a codebook group per workgroup (with a workspace).
+template <int RES_BITS, int MW, int NB, bool GROUPED, bool ONE_GROUP = false>
 __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPlan &plan, const __half *__restrict__ x, long long ldx,
                                                   int batch, __half *__restrict__ y, long long ldy, int wg,
                                                   const GroupRange gr = GroupRange{0, 1, nullptr, nullptr}) {
   typedef Layout<RES_BITS> LY;
   constexpr int RB = RES_BITS ? RES_BITS : 8;
   constexpr int PA = NB == 2 ? 4 : 2;                   // passes whose index words are in flight or in registers
-  constexpr int XL = 6;                                 // loads of a pass's activations, which run one pass ahead
+  // Activations straight into the operands, eight loads a pass, where a chunk has two blocks and a group a pass or two: six loads and
+  // their moves are 4 to 16 % slower there at any number of rows (v = 6 with a 12-bit residual table, eight groups, 9536 x 4352, one row 24.2
+  // against 26.3 us, sixteen 26.8 against 29.4; 16 groups, 11008 x 4096 41 against 48; but a workgroup that walks four groups, 16 rows: 38.6
+  // against 36.3)
+  constexpr bool DIRECT = ONE_GROUP && RES_BITS == 12;
+  constexpr int XL = DIRECT ? 8 : 6;                    // loads of a pass's activations, which run one pass ahead
+  static_assert(PA % 2 == 0, "the unrolled pass loop must map passes to activation sets statically");
   constexpr int R = PA * NB;                            // ring of index-word slots: slot (j, b) = j * NB + b
   constexpr int S = RES_BITS ? 2 : 1;                   // loads per slot
   // loads issued after a slot's own by the time the slot is used, while the ring is being refilled: the other
@@ -109,7 +116,7 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
 
   uint3v win[R], wres[RES_BITS == 12 ? R : 1];   // index words, PA passes deep
   uint2v wres8[RES_BITS == 8 ? R : 1];
-  uint4v xq[XL], bx[VPL];                        // activations of the next pass as loaded; B operands of the current one
+  uint4v xq[DIRECT ? 1 : XL], bxs[DIRECT ? 2 : 1][VPL];    // activations of the next pass as loaded; B operands of the current one (and the next)
 #pragma unroll
   for (int i = 0; i < R; ++i) {
     win[i] = uint3v{0u, 0u, 0u};
@@ -117,9 +124,11 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
     if (RES_BITS == 8) wres8[i] = uint2v{0u, 0u};
   }
 #pragma unroll
-  for (int i = 0; i < XL; ++i) xq[i] = uint4v{0u, 0u, 0u, 0u};
+  for (int i = 0; i < (DIRECT ? 1 : XL); ++i) xq[i] = uint4v{0u, 0u, 0u, 0u};
 #pragma unroll
-  for (int u = 0; u < VPL; ++u) bx[u] = uint4v{0u, 0u, 0u, 0u};
+  for (int i = 0; i < (DIRECT ? 2 : 1); ++i)
+#pragma unroll
+    for (int u = 0; u < VPL; ++u) bxs[i][u] = uint4v{0u, 0u, 0u, 0u};
 
   const uint4v ones = {0x3C003C00u, 0x3C003C00u, 0x3C003C00u, 0u};
   float4v acc[NB];
@@ -186,13 +195,20 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
   };
   // Activations of one pass: a lane's 96 bytes in six loads, moved to the operands when they are there.  Every lane of such a load is an
   // access of its own to L1 (sixteen rows), one a clock, and these are most of the kernel's time at 16 rows: with eight overlapping loads
-  // straight into the operands and at most three blocks a chunk, 16 rows of a 7B-shaped decoder layer took 90.3 us, now 78.7
-  // (the 18 moves a pass are nothing).
-  auto issue_x = [&](int pass) {
+  // straight into the operands and at most three blocks a chunk, 16 rows of a 7B-shaped decoder layer took 90.3 us, now 77.6.  (At two to
+  // four rows, long ones without a residual table, the 18 moves a pass are 3 to 6 %: 9664 x 13952, three rows 16.5 -> 17.5 us, eight 19.3 -> 18.1.)
+  auto issue_x = [&](int pass, uint4v (&to)[VPL]) {
     const unsigned off = token_on ? xrow + ((unsigned)col_lo + (unsigned)((pass * MW + wl) * 4 + g) * (VPL * 6u)) * 2u : xrow;
-    async_load_b128_at<0>(xq[0], r_xa, off);  async_load_b128_at<16>(xq[1], r_xa, off);
-    async_load_b128_at<32>(xq[2], r_xa, off); async_load_b128_at<48>(xq[3], r_xa, off);
-    async_load_b128_at<64>(xq[4], r_xa, off); async_load_b128_at<80>(xq[5], r_xa, off);
+    if constexpr (DIRECT) {      // (they overlap: the fourth dword belongs to the next vector)
+      async_load_b128_at<0>(to[0], r_xa, off);  async_load_b128_at<12>(to[1], r_xa, off);
+      async_load_b128_at<24>(to[2], r_xa, off); async_load_b128_at<36>(to[3], r_xa, off);
+      async_load_b128_at<48>(to[4], r_xa, off); async_load_b128_at<60>(to[5], r_xa, off);
+      async_load_b128_at<72>(to[6], r_xa, off); async_load_b128_at<84>(to[7], r_xa, off);
+    } else {
+      async_load_b128_at<0>(xq[0], r_xa, off);  async_load_b128_at<16>(xq[1], r_xa, off);
+      async_load_b128_at<32>(xq[2], r_xa, off); async_load_b128_at<48>(xq[3], r_xa, off);
+      async_load_b128_at<64>(xq[4], r_xa, off); async_load_b128_at<80>(xq[5], r_xa, off);
+    }
   };
 
   {
@@ -208,7 +224,7 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
       for (int b = 0; b < NB; ++b) load_slot(j * NB + b, b);
       advance_loader();
     }
-    issue_x(0);
+    issue_x(0, bxs[0]);
     wait_vmem_at_most<R * S + XL>();             // the tables are in; the index words may still be on their way
     tables.store(p, lds, plan.lds_out, grp == 0 && !plan.out_global, tid);
   }
@@ -290,10 +306,14 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
           // ---- one pass over this wave's 32 vectors of every block of the chunk
           // Every pass issues the same number of loads, also past the end of the sequence (the loader then starts
           // over), so the counted waits hold throughout.
+          uint4v (&bx)[VPL] = bxs[DIRECT ? j % 2 : 0];
           wait_vmem_at_most<AFTER_X>();
+          if constexpr (DIRECT) {
 #pragma unroll
-          for (int i = 0; i < XL; ++i) settle(xq[i]);
-          {
+            for (int u = 0; u < VPL; ++u) settle(bx[u]);
+          } else {
+#pragma unroll
+            for (int i = 0; i < XL; ++i) settle(xq[i]);
             const unsigned xd[XL * 4] = {xq[0].x, xq[0].y, xq[0].z, xq[0].w, xq[1].x, xq[1].y, xq[1].z, xq[1].w, xq[2].x, xq[2].y, xq[2].z, xq[2].w,
                                          xq[3].x, xq[3].y, xq[3].z, xq[3].w, xq[4].x, xq[4].y, xq[4].z, xq[4].w, xq[5].x, xq[5].y, xq[5].z, xq[5].w};
 #pragma unroll
@@ -318,7 +338,7 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
             for (int u = 0; u < VPL; ++u) xs = mfma16(ones, bx[u], xs);
             if (g == 0) xs_part[wv * 16 + n] += xs.x;
           }
-          issue_x((pass + 1) % my_passes);
+          issue_x((pass + 1) % my_passes, bxs[DIRECT ? (j + 1) % 2 : 0]);
 #pragma unroll
           for (int b = 0; b < NB; ++b) {
             const int slot = j * NB + b;
@@ -451,8 +471,8 @@ __global__ __launch_bounds__(MW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
                                                                        int wgs_per_group) {
   warm_kernel_arguments();
   const int grp = (int)blockIdx.x / wgs_per_group, wg = (int)blockIdx.x - grp * wgs_per_group;
-  gemv_v6_mfma_body<RES_BITS, MW, NB, true>(p, plan, x, ldx, batch, nullptr, 0, wg,
-                                            GroupRange{grp, grp + 1, part + (long long)grp * batch * p.out_features, part_xs});
+  gemv_v6_mfma_body<RES_BITS, MW, NB, true, true>(p, plan, x, ldx, batch, nullptr, 0, wg,
+                                                  GroupRange{grp, grp + 1, part + (long long)grp * batch * p.out_features, part_xs});
 }
 
 // y[t][o] = fp16(scale[o] * sum_g part[g][t][o] + bias[o] * sum_g part_xs[g][t]), groups in ascending order.
