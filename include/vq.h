@@ -107,7 +107,8 @@ typedef struct vq_layer_desc {
    * by vq_dequant, repeated entries give unspecified values in the columns involved; neither leaves the buffers.
    * Kernels: vq_gemv gathers the activations itself in its one- and two-row kernels for v = 6 layers, in the kernels
    * that keep other layers' tables in LDS, and in the generic kernels; with a workspace (vq_gemv_with_workspace,
-   * vq_gemv_static_workspace, vq_gemm) the activations are first gathered into it (vq_gemv_workspace_bytes / vq_gemm_fast_workspace_bytes count that copy) and every kernel of
+   * vq_gemv_static_workspace, vq_gemm) the activations are first gathered into it (vq_gemv_workspace_bytes /
+   * vq_gemm_fast_workspace_bytes count that copy, also where one or two rows do without it) and every kernel of
    * the library then runs as for an unpermuted layer; vq_dequant restores in stored order and then reorders each
    * row in place through LDS.  A caller that sets struct_size to VQ_LAYER_DESC_SIZE_V2 (the layout up to
    * `orientation`) gets the identity.                                                                             */
@@ -152,8 +153,9 @@ int vq_gemv(const vq_layer_desc *desc, const void *x, int64_t ldx, int32_t batch
  * columns with a 12-bit residual table): the matrix-core kernel of that orientation works in blocks of 16 index streams (96 output rows), too few
  * to fill the chip on most layers, so with a workspace it also cuts the columns into parts, one workgroup per (block,
  * part), and the same second kernel adds the parts up; so does the matrix-core kernel of the paper's other settings.  Layers
- * with a column permutation gather the activations into it first.  vq_gemv_workspace_bytes returns 0 when no kernel
- * would use a workspace for this layer.  With workspace NULL or smaller than that, and for every other layer, the
+ * with a column permutation gather the activations into it first, but for one and two rows of layers with codebook groups on the
+ * kernel that keeps one table in LDS at a time, whose workgroups gather theirs by themselves.  vq_gemv_workspace_bytes returns 0 when
+ * no kernel would use a workspace for this layer.  With workspace NULL or smaller than that, and for every other layer, the
  * call is vq_gemv.  Same arguments, bar and errors as vq_gemv; a workspace that is not 256-byte aligned is
  * VQ_ERR_ALIGNMENT.  Calls that share a workspace must not overlap.                                          */
 size_t vq_gemv_workspace_bytes(const vq_layer_desc *desc, int32_t batch);
