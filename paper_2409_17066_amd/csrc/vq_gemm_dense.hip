@@ -201,23 +201,32 @@ void gemm_dense_kernel(DenseArgs a) {
   const __amdgpu_buffer_rsrc_t r_y = __builtin_amdgcn_make_buffer_rsrc(a.Y, 0, (unsigned)(((long long)(a.tokens - 1) * a.ldy + a.out_features) * 2), 0x00020000);
   const unsigned ldy2 = (unsigned)a.ldy * 2u;
   const unsigned y_lane = (unsigned)(m0 + wm + 4 * (lane >> 4)) * ldy2 + (unsigned)(n0 + wn + (lane & 15)) * 2u;
-  // (what a tile's channels and tokens need, all of it on its way before the first is waited for: one block after the other they took 25 us
-  // of a 256 x 256 tile; v = 6 with outlier columns, 13168 x 1216, 1382 tokens 128 -> 83 us)
-  float scale[BB], bias[BB], xsum[AB][4];
+  // (read ahead of the blocks: what the tile's channels need at once, what its tokens need one row of blocks early; one block
+  // after the other took 25 us of a 256 x 256 tile (v = 6 with outlier columns, 13168 x 1216, 1382 tokens 176 -> 127 us), and all
+  // sums at once crowd the accumulators out of their registers inside the steps (7760 x 8640, 1615 tokens 561 against 507))
+  float scale[BB], bias[BB], xsum[4], xnext[4];
+  int at = lane;                       // (addresses formed here: hoisted out of the loop over the steps they crowd the accumulators)
+  asm volatile("" : "+v"(at));
+  auto sums_of = [&](int i, float (&to)[4]) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) to[r] = a.xsum[min(m0 + wm + i * 16 + 4 * (at >> 4) + r, a.tokens - 1)];
+  };
   if constexpr (CENTROIDS) {
 #pragma unroll
     for (int c = 0; c < BB; ++c) {
-      const int o = min(n0 + wn + c * 16 + (lane & 15), a.out_features - 1);
+      const int o = min(n0 + wn + c * 16 + (at & 15), a.out_features - 1);
       scale[c] = a.scale ? __half2float(a.scale[o]) : 1.0f;
       bias[c] = a.bias ? __half2float(a.bias[o]) : 0.0f;
     }
-#pragma unroll
-    for (int i = 0; i < AB; ++i)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) xsum[i][r] = a.xsum[min(m0 + wm + i * 16 + 4 * (lane >> 4) + r, a.tokens - 1)];
+    sums_of(0, xnext);
   }
 #pragma unroll
   for (int i = 0; i < AB; ++i) {
+    if constexpr (CENTROIDS) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) xsum[r] = xnext[r];
+      if (i + 1 < AB) sums_of(i + 1, xnext);
+    }
 #pragma unroll
     for (int c = 0; c < BB; ++c) {
       const int o = n0 + wn + c * 16 + (lane & 15);
@@ -225,7 +234,7 @@ void gemm_dense_kernel(DenseArgs a) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         float sum = acc[i][c][r];
-        if constexpr (CENTROIDS) sum = __fmaf_rn(scale[c], sum, bias[c] * xsum[i][r]);
+        if constexpr (CENTROIDS) sum = __fmaf_rn(scale[c], sum, bias[c] * xsum[r]);
         const __half h = __float2half_rn(sum);
         __builtin_amdgcn_raw_buffer_store_b16((short)__half_as_ushort(h), r_y, o_on ? y_lane + (unsigned)(i * 16 + r) * ldy2 + (unsigned)(c * 32) : 0xFFFFFFF0u, 0, 0);
       }
