@@ -214,8 +214,8 @@ __device__ __forceinline__ void wave_arg_min(float &d, unsigned &i) {
 // split into three binary16 parts; the vector's column of operand B holds t and the matching negative power of two.  A t that is
 // a difference W - B is no binary16 number: it is scaled and split into two (v <= 6: both in one instruction's 16 k slots,
 // against the same elements twice; longer vectors: a second instruction with the same A).  A lane sees 16 rows of every result:
-// it keeps the largest score of any such block of 16 (of two results, 32, with tables of 4096 entries and more), that block's number,
-// and the largest score of every other block.
+// it keeps the largest score of any such block of 16 (of two results, 32, where a wave holds two tiles of vectors and the table has 4096
+// entries or more), that block's number, and the largest score of every other block.
 //
 // Scores carry rounding errors, so the winning block is only trusted when it wins by more than they can be.  With T = |t|, the
 // nearest centroid and whichever centroid has the largest computed score have norms of at most R = T + sqrt(d), d their
@@ -226,7 +226,7 @@ __device__ __forceinline__ void wave_arg_min(float &d, unsigned &i) {
 // -- about 0.3 % with 4096 Gaussian entries --, and all of them when a table has entries that are not finite or huge, are
 // compared with every centroid by the wave together.
 //
-// What bounds it: the vector ALUs, which are busy 86 % of the clocks (at 1.9 GHz: both units' power).  A result (two blocks of
+// What bounds it: the vector ALUs, which are busy 89 % of the clocks (profiles/case_counters.txt; at 1.9 GHz: both units' power).  A result (two blocks of
 // 16 scores) costs 32 matrix-core clocks and 12 vector instructions of 4 clocks, 10 with blocks of 32; what a vector costs beside the search
 // -- operands, distances of the winning block, the test, packing -- is about a fifth of the time at k = 4096 and most of it at 256.  So:
 //  - the products of one result run while the largest score of the one before is found;
@@ -234,12 +234,13 @@ __device__ __forceinline__ void wave_arg_min(float &d, unsigned &i) {
 //    (one instruction a register) instead of both lanes of a vector doing the same;
 //  - a workgroup's waves draw their vectors by ticket: with equal shares the waves that a SIMD prefers were done early and on average
 //    2.6 of its four were left;
-//  - blocks of 32 from 4096 entries on: 8 instructions fewer for every 64 entries and 64 vectors, 16 distances of 15 instructions more
-//    (k = 4096: 995 -> 948 us; at 2048 the two are equal).
+//  - blocks of 32 from 4096 entries on, for waves of two tiles: 8 instructions fewer for every 64 entries and 64 vectors, 16 distances of
+//    15 instructions more (k = 4096: 995 -> 950 us; at 2048 the two are equal).
 //  - tables of more than 4096 entries are kernels of their own, which keep their registers out of the others (11008 x 4096, k = 256:
 //    156 -> 144 us, v = 12 with a base 835 -> 775).
-// Measured, 11008 x 4096, v = 6: k = 4096 1152 -> 952 us, k = 256 261 -> 144 us; every distance on the vector ALUs 8.42 ms.
-// 4096 x 4096, v = 8, k = 65536, entries loaded together, and whole where they are aligned: 5.13 -> 4.40 ms.
+// Measured, 11008 x 4096, v = 6: k = 4096 1152 -> 950 us, k = 256 261 -> 144 us; every distance on the vector ALUs 8.4 ms.
+// 4096 x 4096, v = 8, k = 65536, entries loaded together, and whole where they are aligned: 5.1 -> 4.2 ms;
+// 2048 x 2048 with a base 1.74 -> 1.42.
 constexpr int WAVES = 16;
 constexpr int SCREEN_ROWS = 4096;                       // table rows in LDS at once: two planes of 16 bytes each
 constexpr int screen_instructions(int v, bool base) { return base && v > 6 ? 2 : 1; }

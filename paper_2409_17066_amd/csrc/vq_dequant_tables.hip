@@ -4,8 +4,8 @@
 // nearest even to binary16; the results are the same bits.
 //
 // Vectors along the row: a lane restores sixteen bytes of it at a time, and looks up exactly what they hold: whole vectors (v = 2, 4, 8),
-// two thirds of one or two (v = 12); v = 6: one vector, twelve bytes, with one read and one store (as sixteen bytes it took four reads
-// of a dword from two vectors, 11008 x 4096 with v6 + 4096 31 -> 28 us).  So a wave writes 1 KB (768 bytes) in one piece, or, where
+// two thirds of one or two (v = 12); v = 6: one vector, twelve bytes, looked up as two dwords and one, with one store (as sixteen bytes it
+// took four reads of a dword from two vectors, 11008 x 4096 with v6 + 4096 31 -> 28 us).  So a wave writes 1 KB (768 bytes) in one piece, or, where
 // rows (or a codebook group's part of them) are shorter, the same of several rows.  Vectors down the outputs: a lane looks
 // eight columns up and writes eight weights of each of the v rows.  The next item's indices are in flight meanwhile; along the rows they
 // go to the other one of two sets of registers, so that nothing waits for the stores behind them (28 -> 26.5 us).  Tables sit in LDS
@@ -18,7 +18,9 @@
 // -> 105, v4 / 256 134 -> 94, down the outputs 114 -> 92 and 114 -> 89.  Below, what follows finds it there, and lines shared by two
 // waves cost: 8192 x 8192 in four groups 29 us through the caches, 40 past them.
 //
-// What bounds it: writing W (6.8 TB/s on this card: 13 us for 11008 x 4096, and 3.5 of launch), with a table in memory the lookups.
+// What bounds it: writing W (6.8 TB/s on this card: 13 us for 11008 x 4096, and 3.5 of launch), with a table in memory the lookups.  v = 6
+// along the rows: L1's address unit, to which a store of twelve bytes a lane is an access a lane: with two tables it is busy 34 of a compute
+// unit's 47 thousand clocks, LDS with the lookups 20 (profiles/case_counters.txt).
 // Measured there, along the rows / down the outputs, against the first kernels (strips and transposes in LDS, dword stores, a
 // separate launch for outliers): v6 / 4096 20.3 / 17.2 us (20.4 / 18.9), + 4096 26.4 / 22 (36 / 26), + 256 and outliers 25.3 / 22
 // (32 / 30), v4 and v6 / 256 18.5 / 17 (30 .. 33 / 58), v2 / 16 18 / 18 (45 / 72), v8 / 65536 30 / 30 (32 / 58),
@@ -122,7 +124,7 @@ template <int V, int ED> __device__ __forceinline__ void memory_entry(unsigned (
   }
 }
 
-// twelve bytes of LDS at any dword
+// twelve bytes of LDS at any dword (two instructions, 22 clocks for 64 lookups; an aligned read of sixteen takes 13)
 __device__ __forceinline__ void read_twelve(unsigned (&e)[3], const unsigned char *at) {
   typedef unsigned uint3d __attribute__((ext_vector_type(3), aligned(4)));
   const uint3d v = *reinterpret_cast<const uint3d *>(at);

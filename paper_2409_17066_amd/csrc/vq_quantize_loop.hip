@@ -18,7 +18,8 @@ namespace {
 // elements take 16 slots, longer ones 32.  A lane gets the scores of four neighbouring centroids at a time and keeps the largest of these
 // groups' maxima, its group's number in the lowest bits, and the second largest.  A row of lanes computes the distances of its best
 // four centroids as defined, one in each lane of a quad; where anything else of the wave is within the rounding bounds of its largest
-// score (in a tenth of the columns) those distances are computed too.  What the rows of all waves find meets in LDS (an atomic
+// score (in a tenth of the columns) those distances are computed too.  Scores see eleven bits of t, and their lowest six bits are the
+// group's number: both are part of the bounds (loop_table), and every index is decided by distances as defined.  What the rows of all waves find meets in LDS (an atomic
 // minimum of distance bits and index).  Behind the column's only barrier every search wave looks the winner up, forms the error and the
 // next column's t by itself: nothing else is exchanged on the way from one column to the next.
 //
@@ -32,7 +33,7 @@ namespace {
 //
 // What bounds it: the chain of a column.  A wave on its own issues an instruction every five clocks or so, and what counts is how many
 // stand on the path between one column's t and the next (about 230 with a 4096-entry table), the LDS round trips (130 clocks, four of
-// them) and the barrier, not any rate: 1800 clocks a column, of which the comparisons of the scores are 500.  Eight search waves
+// them) and the barrier, not any rate: 1900 clocks a column, of which the comparisons of the scores are 500.  Eight search waves
 // of half the table each are slower (4.8 ms against 4.6): everything but the comparisons is then issued twice on every SIMD.
 // The end of a block waits for H^-1 (1 MB through every compute unit, which takes 64 bytes a clock) and for W, 94 of 340 thousand clocks at
 // 4096 columns.  Before, with the vector posted and its errors kept by one wave, three barriers and the low parts of t
