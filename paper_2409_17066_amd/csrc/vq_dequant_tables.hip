@@ -440,9 +440,10 @@ __global__ __launch_bounds__(256) void dequant_down_lookup_kernel(Params p, __ha
 // through L2 one by one bring lines of 128 bytes for sixteen: 48 us for two turns' vectors (8192 x 8192) by themselves, but behind and
 // ahead of a long product, which leaves L2 without the table and the chip at its power limit, a call with new inputs is faster this way: 8192 x 8192
 // at 1024 / 2048 tokens 189 -> 178 and 285 -> 276 us, 14336 x 4096 171 -> 162 and 264 -> 256, 8192 x 28672 654 -> 596 at 1024; one full turn is as good as
-// two (8192 x 4096 99 -> 92 and 149 -> 142, 4096 x 8192 106 -> 103 and 155 -> 151).  (The same call over and over, its streams in the caches, is 3 %
-// slower.)  At 300 tokens it is not faster (4096 x 4096 35 us through L2, 46), nor with turns that are not full (4096 x 11008, 5.6 M vectors, 2048
-// tokens: 267, 271).
+// two (8192 x 4096 99 -> 92 and 149 -> 142, 4096 x 8192 106 -> 103 and 155 -> 151).  At 300 tokens it is not faster (4096 x 4096 35 us through
+// L2, 46), nor with turns that are not full (4096 x 11008, 5.6 M vectors, 2048 tokens: 267, 271): two of them have to be full to four fifths
+// (13500 x 4096, 1024 tokens 167 -> 161), a single one to 15 / 16 (0.83 of one, 6800 x 4096 79 -> 82, 0.93, 7600 x 4096 equal, 0.96, 7900 x 4096
+// 95 -> 91).  (The same call over and over, its streams in the caches, is 3 to 7 % slower.)
 constexpr int MANY_TOKENS = 1024;
 constexpr int PIECE = 5120, HELD = 16, PIECES_THREADS = 1024;
 
@@ -571,7 +572,7 @@ int launch_one(const Params &p, __half *W, long long ldw, hipStream_t s, int pro
   if constexpr (!DOWN && V == 8 && BITS == 16 && RES == NO_RES) {
     const long long vectors = (long long)p.S * p.P, turn = (long long)PIECES_THREADS * HELD * cu_count();
     if (product_tokens >= MANY_TOKENS && p.n_groups == 1 && !p.Q && p.in_features == p.P * 8 && p.P > 1 && vectors < 1LL << 31 &&
-        vectors * 5 >= (vectors + turn - 1) / turn * turn * 4) {      // (turns that are full to four fifths)
+        (vectors > turn ? vectors * 5 >= (vectors + turn - 1) / turn * turn * 4 : vectors * 16 >= turn * 15)) {      // (turns full to four fifths, a single one to 15 / 16)
       const unsigned n = (unsigned)vectors, inv = (unsigned)((1ULL << 32) / (unsigned)p.P);
       const unsigned rounds = (unsigned)((vectors + turn - 1) / turn), wg = (unsigned)((vectors + (long long)rounds * PIECES_THREADS * HELD - 1) / ((long long)rounds * PIECES_THREADS * HELD));
       auto run = [&](auto kernel) {
