@@ -310,7 +310,7 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
           wait_vmem_at_most<AFTER_X>();
           if constexpr (DIRECT) {
 #pragma unroll
-            for (int u = 0; u < VPL; ++u) settle(bx[u]);
+            for (int u = 0; u < VPL; ++u) { settle(bx[u]); bx[u].w = 0u; }      // (the next vector's: infinite ones would meet the padding's zeros)
           } else {
 #pragma unroll
             for (int i = 0; i < XL; ++i) settle(xq[i]);

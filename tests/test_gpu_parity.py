@@ -561,6 +561,31 @@ def test_gemv_lds_table_slots_with_the_workspace_of_other_rows(gpu_lib, permuted
         assert torch.isfinite(ws[head : head + groups * batch * L.out_features * 4].view(torch.float32)).all()
 
 
+@pytest.mark.parametrize("out,inp,setting,batch", [
+    (300, 1918, dict(k_res=4096, group_vectors=40), 1),             # a group a workgroup: activations straight into the operands
+    (300, 1918, dict(k_res=4096, group_vectors=40), 4),
+    (300, 1918, dict(k_res=256, group_vectors=40), 4),             # moved there
+    (300, 766, dict(), 5),
+])
+def test_gemv_of_infinite_activations(gpu_lib, out, inp, setting, batch):
+    """An infinite activation at either end of a vector makes every output infinite, where no table and no bias has a negative or zero value:
+    what is loaded beside a vector never meets the zeros that its entries are padded with."""
+    import torch
+    L = s.make_layer(313, "infinite", out, inp, 6, 4096, **setting)
+    L.codebook, L.bias = np.maximum(np.abs(L.codebook), np.float16(1e-3)), np.maximum(np.abs(L.bias), np.float16(1e-3))
+    if L.codebook_res is not None:
+        L.codebook_res = np.maximum(np.abs(L.codebook_res), np.float16(1e-3))
+    dl = gpu_lib.DeviceLayer(L)
+    x = torch.from_numpy(s.make_activations(313, L, batch)).cuda()
+    ws = torch.empty((gpu_lib.vq_gemv_workspace_bytes(dl.desc, batch),), dtype=torch.uint8, device="cuda")
+    for column in (6, 7, 11, inp // 2 // 6 * 6, inp - 1):
+        z = x.clone()
+        z[batch - 1, column] = float("inf")
+        y = gpu_lib.gemv(dl, z, workspace=ws)
+        assert (y[batch - 1] == float("inf")).all(), column
+        assert torch.isfinite(y[: batch - 1]).all(), column
+
+
 PERMUTED = [n for n in SMALL if n.startswith("perm_")]
 
 
