@@ -67,19 +67,17 @@ __device__ __forceinline__ float4v mfma16(uint4v a, uint4v b, float4v c) {
 // LDS address, activations loaded straight into MFMA operand registers, load addresses advanced by
 // additions, end-of-row masking only in the one column group that needs it.
 // `wg` is the workgroup's number within its layer (a launch may hold the workgroups of several layers).
-// ONE_GROUP: of a codebook group per workgroup (with a workspace).
-template <int RES_BITS, int MW, int NB, bool GROUPED, bool ONE_GROUP = false>
+// DIRECT: a pass's activations by eight loads straight into the operands, not by six and moves.  For few rows (see few_rows), and for a group
+// a workgroup with a 12-bit residual table, where a chunk has two blocks and a group a pass or two: six loads are 4 to 16 % slower there at any
+// number of rows (eight groups, 9536 x 4352, one row 24.2 against 26.3 us, sixteen 26.8 against 29.4; 16 groups, 11008 x 4096 41 against 48; but a
+// workgroup that walks four groups, 16 rows: 38.6 against 36.3).
+template <int RES_BITS, int MW, int NB, bool GROUPED, bool DIRECT = false>
 __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPlan &plan, const __half *__restrict__ x, long long ldx,
                                                   int batch, __half *__restrict__ y, long long ldy, int wg,
                                                   const GroupRange gr = GroupRange{0, 1, nullptr, nullptr}) {
   typedef Layout<RES_BITS> LY;
   constexpr int RB = RES_BITS ? RES_BITS : 8;
   constexpr int PA = NB == 2 ? 4 : 2;                   // passes whose index words are in flight or in registers
-  // Activations straight into the operands, eight loads a pass, where a chunk has two blocks and a group a pass or two: six loads and
-  // their moves are 4 to 16 % slower there at any number of rows (v = 6 with a 12-bit residual table, eight groups, 9536 x 4352, one row 24.2
-  // against 26.3 us, sixteen 26.8 against 29.4; 16 groups, 11008 x 4096 41 against 48; but a workgroup that walks four groups, 16 rows: 38.6
-  // against 36.3)
-  constexpr bool DIRECT = ONE_GROUP && RES_BITS == 12;
   constexpr int XL = DIRECT ? 8 : 6;                    // loads of a pass's activations, which run one pass ahead
   static_assert(PA % 2 == 0, "the unrolled pass loop must map passes to activation sets statically");
   constexpr int R = PA * NB;                            // ring of index-word slots: slot (j, b) = j * NB + b
@@ -195,8 +193,8 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
   };
   // Activations of one pass: a lane's 96 bytes in six loads, moved to the operands when they are there.  Every lane of such a load is an
   // access of its own to L1 (sixteen rows), one a clock, and these are most of the kernel's time at 16 rows: with eight overlapping loads
-  // straight into the operands and at most three blocks a chunk, 16 rows of a 7B-shaped decoder layer took 90.3 us, now 77.6.  (At two to
-  // four rows, long ones without a residual table, the 18 moves a pass are 3 to 6 %: 9664 x 13952, three rows 16.5 -> 17.5 us, eight 19.3 -> 18.1.)
+  // straight into the operands and at most three blocks a chunk, 16 rows of a 7B-shaped decoder layer took 90.3 us, now 77.6.  (The 18 moves
+  // a pass cost more than that at few rows: DIRECT.)
   auto issue_x = [&](int pass, uint4v (&to)[VPL]) {
     const unsigned off = token_on ? xrow + ((unsigned)col_lo + (unsigned)((pass * MW + wl) * 4 + g) * (VPL * 6u)) * 2u : xrow;
     if constexpr (DIRECT) {      // (they overlap: the fourth dword belongs to the next vector)
@@ -454,11 +452,11 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
   }
 }
 
-template <int RES_BITS, int MW, int NB, bool GROUPED>
+template <int RES_BITS, int MW, int NB, bool GROUPED, bool DIRECT>
 __global__ __launch_bounds__(MW * 64) void gemv_v6_mfma_kernel(Params p, MfmaPlan plan, const __half *__restrict__ x, long long ldx,
                                                                 int batch, __half *__restrict__ y, long long ldy) {
   warm_kernel_arguments();
-  gemv_v6_mfma_body<RES_BITS, MW, NB, GROUPED>(p, plan, x, ldx, batch, y, ldy, (int)blockIdx.x, GroupRange{0, p.n_groups, nullptr, nullptr});
+  gemv_v6_mfma_body<RES_BITS, MW, NB, GROUPED, DIRECT>(p, plan, x, ldx, batch, y, ldy, (int)blockIdx.x, GroupRange{0, p.n_groups, nullptr, nullptr});
 }
 
 // A layer with codebook groups when the caller lends a workspace: every workgroup takes one group (its tables go into
@@ -471,7 +469,7 @@ __global__ __launch_bounds__(MW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
                                                                        int wgs_per_group) {
   warm_kernel_arguments();
   const int grp = (int)blockIdx.x / wgs_per_group, wg = (int)blockIdx.x - grp * wgs_per_group;
-  gemv_v6_mfma_body<RES_BITS, MW, NB, true, true>(p, plan, x, ldx, batch, nullptr, 0, wg,
+  gemv_v6_mfma_body<RES_BITS, MW, NB, true, RES_BITS == 12>(p, plan, x, ldx, batch, nullptr, 0, wg,
                                                   GroupRange{grp, grp + 1, part + (long long)grp * batch * p.out_features, part_xs});
 }
 
@@ -531,20 +529,20 @@ struct MultiArgs {
   MultiLayer layer[MULTI_MAX];
 };
 
-template <int RES_BITS, int MW, int NB>
+template <int RES_BITS, int MW, int NB, bool DIRECT>
 __global__ __launch_bounds__(MW * 64) void gemv_v6_mfma_multi_kernel(MultiArgs a, const __half *__restrict__ x, long long ldx, int batch) {
   warm_kernel_arguments();
   int i = 0;
   while (i + 1 < a.n && (int)blockIdx.x >= a.first_wg[i + 1]) ++i;
   const MultiLayer &l = a.layer[i];
-  gemv_v6_mfma_body<RES_BITS, MW, NB, false>(l.p, l.plan, x, ldx, batch, l.y, l.ldy, (int)blockIdx.x - a.first_wg[i]);
+  gemv_v6_mfma_body<RES_BITS, MW, NB, false, DIRECT>(l.p, l.plan, x, ldx, batch, l.y, l.ldy, (int)blockIdx.x - a.first_wg[i]);
 }
 
 
-template <int RES_BITS, int MW, int NB, bool GROUPED>
+template <int RES_BITS, int MW, int NB, bool GROUPED, bool DIRECT = false>
 int launch_one(const Params &p, const MfmaPlan &plan, unsigned lds_bytes, unsigned grid, const __half *x, long long ldx, int batch,
                __half *y, long long ldy, hipStream_t s) {
-  auto kernel = gemv_v6_mfma_kernel<RES_BITS, MW, NB, GROUPED>;
+  auto kernel = gemv_v6_mfma_kernel<RES_BITS, MW, NB, GROUPED, DIRECT>;
   VQ_ALLOW_FULL_LDS(kernel);
   hipLaunchKernelGGL(kernel, dim3(grid), dim3(MW * 64), lds_bytes, s, p, plan, x, ldx, batch, y, ldy);
   return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
@@ -631,13 +629,20 @@ bool narrow_groups(const Params &p) {
   return p.n_groups > 1 && (p.Pg + 31) / 32 <= NARROW_WAVES && !(p.k_res && p.bits_res == 12) && p.Q == 0;
 }
 
-template <int RES_BITS, int NB>
+template <int RES_BITS, int NB, bool DIRECT = false>
 int launch_multi(const MultiArgs &a, unsigned lds_bytes, unsigned grid, const __half *x, long long ldx, int batch, hipStream_t s) {
-  auto kernel = gemv_v6_mfma_multi_kernel<RES_BITS, MW, NB>;
+  auto kernel = gemv_v6_mfma_multi_kernel<RES_BITS, MW, NB, DIRECT>;
   VQ_ALLOW_FULL_LDS(kernel);
   hipLaunchKernelGGL(kernel, dim3(grid), dim3(MW * 64), lds_bytes, s, a, x, ldx, batch);
   return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
 }
+
+// Without a residual table: the activations of long rows straight into the operands (see DIRECT), which fewer accesses to L1 do not pay for
+// at few rows.  With six loads in place of eight, 8192 x 28672, two blocks a chunk: two rows 22.6 -> 25.2 us, three 24.3 -> 25.5, four 25.8 ->
+// 25.7, six 27.2 -> 26.0; 9664 x 13952, three blocks: two rows 16.9 -> 17.7, five 16.7 -> 17.5, six 17.4 -> 17.7, eight 19.3 -> 18.1.  With one block
+// six are the faster ones (rows of 8000 columns and more by 6 to 20 %), and of rows of less than 8000 columns neither is by more
+// than 2 % (140 sets of layers; against the line, 5120 x 13824, three rows 15.8 -> 15.2).
+bool few_rows(const Params &p, int batch, int nb) { return nb >= 2 && p.in_features >= 8000 && batch <= (nb >= 3 ? 5 : 3); }
 
 }  // namespace
 
@@ -652,6 +657,9 @@ int launch_gemv_mfma(const Params &p, const __half *x, long long ldx, int batch,
   const int rb = pl.rb;
   const bool grouped = pl.grouped;
   const unsigned off = pl.lds_bytes, grid = pl.grid;
+#define VQ_CASE(NBLK) if (plan.nb == NBLK) return launch_one<0, MW, NBLK, false, true>(p, plan, off, grid, x, ldx, batch, y, ldy, s);
+  if (rb == 0 && !grouped && few_rows(p, batch, plan.nb)) { VQ_CASE(2) VQ_CASE(3) VQ_CASE(4) }
+#undef VQ_CASE
 #define VQ_CASE(RBITS, NBLK) \
   if (rb == RBITS && plan.nb == NBLK && !grouped) return launch_one<RBITS, MW, NBLK, false>(p, plan, off, grid, x, ldx, batch, y, ldy, s); \
   if (rb == RBITS && plan.nb == NBLK && grouped && NBLK <= (RBITS == 12 ? 2 : 3)) \
@@ -759,6 +767,9 @@ int launch_gemv_mfma_multi(const Params *ps, int n, const __half *x, long long l
   }
   const unsigned grid = (unsigned)a.first_wg[n];
   const int rb = pl[0].rb;
+#define VQ_CASE(NBLK) if (nb == NBLK) return launch_multi<0, NBLK, true>(a, lds_bytes, grid, x, ldx, batch, s);
+  if (rb == 0 && few_rows(ps[0], batch, nb)) { VQ_CASE(2) VQ_CASE(3) VQ_CASE(4) }
+#undef VQ_CASE
 #define VQ_CASE(RBITS, NBLK) if (rb == RBITS && nb == NBLK) return launch_multi<RBITS, NBLK>(a, lds_bytes, grid, x, ldx, batch, s);
   VQ_CASE(0, 1) VQ_CASE(0, 2) VQ_CASE(0, 3) VQ_CASE(0, 4) VQ_CASE(0, 5) VQ_CASE(0, 6)
   VQ_CASE(8, 1) VQ_CASE(8, 2) VQ_CASE(8, 3) VQ_CASE(8, 4) VQ_CASE(8, 5)

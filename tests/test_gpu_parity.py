@@ -566,6 +566,8 @@ def test_gemv_lds_table_slots_with_the_workspace_of_other_rows(gpu_lib, permuted
     (300, 1918, dict(k_res=4096, group_vectors=40), 4),
     (300, 1918, dict(k_res=256, group_vectors=40), 4),             # moved there
     (300, 766, dict(), 5),
+    (4100, 8004, dict(), 3),                                       # long rows, few of them: straight into the operands again
+    (8200, 8010, dict(), 5),
 ])
 def test_gemv_of_infinite_activations(gpu_lib, out, inp, setting, batch):
     """An infinite activation at either end of a vector makes every output infinite, where no table and no bias has a negative or zero value:
@@ -584,6 +586,31 @@ def test_gemv_of_infinite_activations(gpu_lib, out, inp, setting, batch):
         y = gpu_lib.gemv(dl, z, workspace=ws)
         assert (y[batch - 1] == float("inf")).all(), column
         assert torch.isfinite(y[: batch - 1]).all(), column
+
+
+@pytest.mark.parametrize("outs,inp,outliers", [
+    ((4100,), 8004, 0),                    # two blocks of rows a chunk: up to three activation rows straight into the operands
+    ((8200,), 8010, 0),                    # three: up to five
+    ((12290,), 8002, 8),                   # four, and outlier columns
+    ((3000, 1500, 700), 8006, 0),
+    ((9000, 3300), 9998, 4),
+])
+def test_gemv_of_few_long_rows(gpu_lib, outs, inp, outliers):
+    """The matrix-core kernel's operands hold the same values whichever way they are loaded: a row's outputs are the same bits beside any number
+    of other rows, and a few of them those of the oracle."""
+    import torch
+    layers = [s.make_layer(314 + i, "long", out, inp, 6, 4096, 0, outliers, 4 if outliers else 0, 4096 if outliers else 0) for i, out in enumerate(outs)]
+    dls = [gpu_lib.DeviceLayer(L) for L in layers]
+    x_np = s.make_activations(314, layers[0], 7)
+    x = torch.from_numpy(x_np).cuda()
+    run = (lambda z: gpu_lib.gemv_multi(dls, z)) if len(dls) > 1 else (lambda z: [gpu_lib.gemv(dls[0], z)])
+    seven = run(x)
+    for L, y in zip(layers, seven):
+        rows = np.array([0, 17, L.out_features // 2, L.out_features - 1], dtype=np.int32)
+        _check_matmul(y[:, torch.from_numpy(rows.astype(np.int64)).cuda()], oracle.gemm(L, x_np, rows=rows), "%d x %d" % (L.out_features, inp))
+    for batch in (2, 3, 4, 5, 6):
+        for y, few in zip(seven, run(x[:batch].contiguous())):
+            assert torch.equal(few.view(torch.int16), y[:batch].view(torch.int16)), batch
 
 
 PERMUTED = [n for n in SMALL if n.startswith("perm_")]
