@@ -526,13 +526,14 @@ unsigned table_bytes(int v, int k) { return ((unsigned)k * (unsigned)v * 2u + 10
 
 // In front of a product W goes through the caches as long as they hold it beside the rest: v8 / 65536 at 300 tokens 4096 x 4096 43.8 -> 34.9 us,
 // 11008 x 4096 102 -> 91, v12 / 4096 + 4096 2048 x 4096 28.8 -> 25.7; 8192 x 8192 at 300 tokens 141 -> 146, but at 2048 300 -> 290.  Not in front of
-// a short product of short rows: of 38 shapes of less than 1216 columns, 0.4 to 0.9 million vectors and up to 191 tokens 36 were slower through the
-// caches, by 4 % on average (v8 10520 x 576, 36 tokens 15.3 -> 17.2, v12 12312 x 576, 67 tokens 19.5 -> 21.4; smaller ones, longer rows and more tokens
-// gain: 700 shapes 6 % on average).
+// a short product of very short rows: of less than 600 columns, 0.4 to 0.9 million vectors and up to 191 tokens most are slower through the
+// caches, in a loop over eight layers by 4 % on average (v8 10520 x 576, 36 tokens 16.4 -> 17.7 us, v12 12312 x 576, 67 tokens 20.6 -> 23.2).  From
+// there to 1216 columns such a loop takes the same either way, and a call with new inputs is faster through them by 9 % (v8 5022 x 720, 189
+// tokens 14.1 -> 12.4, 6102 x 952, 44 tokens 16.0 -> 13.9, v12 5447 x 1072, 138 tokens 20.8 -> 19.0).
 bool through_caches(const Params &p, int product_tokens) {
   const long long w_bytes = (long long)p.out_features * p.in_features * 2, vectors = (long long)p.S * p.P;
   if (product_tokens <= 0 || w_bytes > 192LL << 20) return false;
-  if (p.in_features < 1216 && product_tokens < 192 && vectors >= 3 << 17 && vectors < 7 << 17) return false;
+  if (p.in_features < 600 && product_tokens < 192 && vectors >= 3 << 17 && vectors < 7 << 17) return false;
   return w_bytes <= 96LL << 20 || product_tokens >= MANY_TOKENS;
 }
 

@@ -192,9 +192,9 @@ def test_long_prompts_of_the_v8_setting_restore_the_same_weights(gpu_lib, out, i
     (8191, 16000, 1024, False, dict(v=8, k=65536)),              # W of 262 MB: past the caches, from the pieces of the table
     (7903, 4104, 1024, False, dict(v=8, k=40000)),               # a single turn of all workgroups, just full enough
     (7371, 8200, 1024, True, dict(v=8, k=65536)),                # permuted columns: the gathered activations lie in front of W
-    (6003, 1000, 40, False, dict(v=8, k=65536)),                 # a short product of short rows: past the caches
-    (9001, 600, 130, False, dict(v=12, k=4096, k_res=4096)),
-    (6003, 1000, 200, True, dict(v=8, k=65536, k_res=256)),      # more tokens: through them
+    (9003, 584, 40, False, dict(v=8, k=65536)),                  # a short product of short rows: past the caches
+    (9001, 592, 130, False, dict(v=12, k=4096, k_res=4096)),
+    (9003, 584, 200, True, dict(v=8, k=65536, k_res=256)),       # more tokens: through them
 ])
 def test_restoring_in_front_of_a_product_leaves_the_same_weights(gpu_lib, out, inp, tokens, permute, setting):
     """What vq_gemm restores into its workspace is what vq_dequant restores from the layer in stored order, bit for bit, whichever way the
