@@ -13,7 +13,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libvq.so")
 BINDING = os.path.join(HERE, "_binding.so")
-SOURCES = ["vq_api.hip", "vq_dequant.hip", "vq_gemv.hip", "vq_gemv_fast.hip", "vq_gemv_res8.hip", "vq_gemv_mfma.hip", "vq_gemm.hip", "vq_gemm_fused.hip", "vq_gemm_dense.hip", "vq_assign.hip", "vq_gemv_down.hip", "vq_gemv_down_mfma.hip", "vq_gemv_v8.hip", "vq_colperm.hip", "vq_quantize.hip", "vq_quantize_loop.hip", "vq_gemm_v6.hip", "vq_gemv_lds.hip", "vq_gemv_rows.hip", "vq_dequant_tables.hip", "vq_gemv_down_lds.hip"]
+SOURCES = ["vq_api.hip", "vq_dequant.hip", "vq_gemv.hip", "vq_gemv_fast.hip", "vq_gemv_res8.hip", "vq_gemv_mfma.hip", "vq_gemm.hip", "vq_gemm_fused.hip", "vq_gemm_dense.hip", "vq_assign.hip", "vq_gemv_down.hip", "vq_gemv_down_mfma.hip", "vq_gemv_v8.hip", "vq_colperm.hip", "vq_quantize.hip", "vq_quantize_loop.hip", "vq_gemm_v6.hip", "vq_gemv_lds.hip", "vq_gemv_rows.hip", "vq_dequant_tables.hip", "vq_gemv_down_lds.hip", "vq_gemv_products.hip"]
 # packed-FP32 VALU forms are switched off for every device compile (they are not trusted on the test machines)
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-command-line-argument"]

@@ -36,6 +36,7 @@ void read_switches() {
       else if (n == 6 && !strncmp(e, "groups", 6)) sw.groups_loop = v == 'l';
       else if (n == 5 && !strncmp(e, "multi", 5)) sw.multi_off = v == '0';
       else if (n == 4 && !strncmp(e, "rows", 4)) sw.rows = v == '0' ? 0 : v == '1' ? 1 : -1;
+      else if (n == 8 && !strncmp(e, "products", 8)) sw.products = v == '0' ? 0 : v == '1' ? 1 : -1;
       else if (n == 5 && !strncmp(e, "dense", 5)) sw.dense = v >= '0' && v <= '9' ? v - '0' : -1;
     }
     e = *end ? end + 1 : end;

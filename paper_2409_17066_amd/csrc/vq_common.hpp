@@ -40,6 +40,7 @@ int cu_count();
 // once at the start of every entry-point call (one getenv), so that one process can walk through all of them:
 //   gemv=g|m|d   generic kernels only / the matrix-core kernels wherever they take the layer / the dot-product kernels
 //   rows=0|1     the matrix-core kernel for layers looked up entry by entry: never / wherever it can
+//   products=0|1 vq_gemv with a workspace, from tables of products: never / wherever it can
 //   groups=loop  layers with codebook groups: every workgroup walks all groups even when a workspace is there
 //   multi=0      vq_gemv_multi as one vq_gemv after the other
 //   gemm=g|f|w|r|6|c vq_gemm: generic tile kernel / no restore-then-multiply / restore-then-multiply whenever a workspace is
@@ -50,7 +51,7 @@ int cu_count();
 struct Switches {
   char gemv = 0, gemm = 0, dequant = 0;
   bool groups_loop = false, multi_off = false;
-  int dense = -1, rows = -1;
+  int dense = -1, rows = -1, products = -1;
 };
 const Switches &switches();
 void read_switches();

@@ -388,6 +388,10 @@ static bool permuted_in_kernel(const Params &p, const __half *x, long long ldx, 
 // for more than vq_gemv_static_workspace has, which would refuse a layer that needs none.)
 static bool rows_gathered(const Params &p, int batch) { return batch >= 5 && (p.in_features & 1) && p.in_features < (1 << 18) && rows_wanted(p, batch, true); }
 
+size_t gemv_products_workspace_bytes(const Params &p, int batch);
+int launch_gemv_products(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, void *workspace, size_t workspace_bytes,
+                         hipStream_t s);
+
 static size_t stored_order_workspace_bytes(const Params &p, const __half *x, long long ldx, int batch, bool least) {
   if (rows_wanted(p, batch, true) && (batch == 1 || !(ldx & 1))) {
     // (0 with codebook groups that the kernel walks by itself: the slots of the kernels below are asked for instead, which run where
@@ -428,12 +432,19 @@ static size_t workspace_bytes_of(const Params &p, const __half *x, long long ldx
 // (One and two rows of a layer with two tables a group take a slot a table, whose workspace may be larger than that of three rows, which
 // another kernel takes.  What holds a slot a group of fewer rows is made to hold that, so that a loop can lend its calls the workspace of the
 // largest batch.)
-size_t gemv_workspace_bytes(const Params &p, const __half *x, long long ldx, int batch) {
+static size_t other_workspace_bytes(const Params &p, const __half *x, long long ldx, int batch) {
   const size_t own = workspace_bytes_of(p, x, ldx, batch, false);
   size_t bytes = own;
   if (p.orientation == 0 && p.k_res && p.n_groups > 1)
     for (int rows = 1; rows < batch; ++rows)
       if (own >= workspace_bytes_of(p, x, ldx, rows, true)) bytes = std::max(bytes, workspace_bytes_of(p, x, ldx, rows, false));
+  return bytes;
+}
+// (one and two rows from tables of products, vq_gemv_products.hip, may take more than the other kernels do of more rows; for the same loop that is
+// part of what more rows ask for)
+size_t gemv_workspace_bytes(const Params &p, const __half *x, long long ldx, int batch) {
+  size_t bytes = other_workspace_bytes(p, x, ldx, batch);
+  for (int rows = 1; rows <= std::min(batch, 2); ++rows) bytes = std::max(bytes, gemv_products_workspace_bytes(p, rows));
   return bytes;
 }
 
@@ -515,6 +526,10 @@ static int launch_with_workspace(const Params &p, const __half *x, long long ldx
 
 int launch_gemv_ws(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, void *workspace,
                    size_t workspace_bytes, hipStream_t s) {
+  if (workspace) {
+    const int rc = launch_gemv_products(p, x, ldx, batch, y, ldy, workspace, workspace_bytes, s);
+    if (rc != VQ_ERR_UNSUPPORTED) return rc;
+  }
   const long long even = p.in_features + (p.in_features & 1);
   const bool enough = workspace && workspace_bytes >= gemv_workspace_bytes(p, nullptr, even, batch);
   // less than vq_gemv_workspace_bytes asks for, though not for these rows alone: vq_gemv

@@ -929,3 +929,50 @@ def test_lds_table_kernels_random_shapes(gpu_lib, seed):
         Y = gpu_lib.gemm(dl, torch.from_numpy(x).cuda(), workspace="fast")
         torch.cuda.synchronize()
         _check_matmul(Y, oracle.gemm(L, x), what + ", 70 tokens")
+
+
+@pytest.mark.parametrize("out_features,in_features,more", [
+    (1, 13, {}), (65, 100, dict(k_res=4096)), (611, 2003, dict(k_res=4000)), (1030, 96 * 3, dict(k_res=2722, group_vectors=8)),
+    (4099, 205, {}), (333, 28675, dict(k_res=4096)), (1025, 40 + 12 * 181 - 1, dict(k_res=4096, group_vectors=48, n_outlier_cols=40, v_out=4, k_out=5000)),
+    (9001, 772, dict(n_outlier_cols=4, v_out=4, k_out=8192)), (61, 1600, dict(n_outlier_cols=404, v_out=4, k_out=4097)), (130, 1301, dict(k_res=4096, group_vectors=40, n_outlier_cols=12, v_out=4, k_out=9)),
+])
+@pytest.mark.parametrize("k", [4096, 2050])
+@pytest.mark.parametrize("permuted", [False, True])
+def test_gemv_from_tables_of_products(gpu_lib, monkeypatch, out_features, in_features, more, k, permuted):
+    """One and two rows of layers of twelve-element vectors with a workspace: rows and runs of positions that fill no workgroup, octets cut off by a
+    group's or the row's end, tables that are not full, outlier columns, activation rows of any pitch."""
+    import torch
+    monkeypatch.setenv("VQ_SWITCHES", "products=1")
+    L = s.make_layer(313, "products", out_features, in_features, 12, k, permute=permuted, **more)
+    dl = gpu_lib.DeviceLayer(L)
+    for batch, pitch in ((1, in_features), (2, in_features), (2, in_features + 3)):
+        x_np = s.make_activations(313, L, batch)
+        x = torch.full((batch, pitch), float("nan"), dtype=torch.float16, device="cuda")
+        x[:, :in_features] = torch.from_numpy(x_np)
+        need = gpu_lib.vq_gemv_workspace_bytes(dl.desc, batch)
+        ws = torch.full((need + 256,), 0xFF, dtype=torch.uint8, device="cuda")
+        y = gpu_lib.gemv(dl, x[:, :in_features], workspace=ws[:need])
+        torch.cuda.synchronize()
+        _check_matmul(y, oracle.gemv(L, x_np), "batch %d" % batch)
+        assert (ws[need:] == 0xFF).all() and (ws[:4] != 0xFF).any()
+
+
+def test_tables_of_products_keep_what_is_no_number_where_it_belongs(gpu_lib, monkeypatch):
+    """An infinite activation reaches every output, an infinite entry those that name it, and neither a neighbour in the same instruction."""
+    import torch
+    monkeypatch.setenv("VQ_SWITCHES", "products=1")
+    L = s.make_layer(314, "products", 200, 24 * 12, 12, 4096, 4096)
+    x_np = s.make_activations(314, L, 1)
+    L.codebook[1::2, 3] = np.inf                       # the odd entries; then no index but even ones, save in the first row
+    bits = np.unpackbits(L.idx, axis=1, bitorder="little")
+    bits[1:, 0:24 * 12:12] = 0
+    bits[0, 0:24 * 12:12] = 1
+    L.idx = np.packbits(bits, axis=1, bitorder="little")
+    dl = gpu_lib.DeviceLayer(L)
+    x = torch.from_numpy(x_np).cuda()
+    ws = torch.empty(gpu_lib.vq_gemv_workspace_bytes(dl.desc, 1), dtype=torch.uint8, device="cuda")
+    y = gpu_lib.gemv(dl, x, workspace=ws).float().cpu()[0]
+    assert not torch.isfinite(y[0]) and torch.isfinite(y[1:]).all()
+    x[0, 30] = float("inf")
+    y = gpu_lib.gemv(dl, x, workspace=ws).float().cpu()[0]
+    assert not torch.isfinite(y).any()
