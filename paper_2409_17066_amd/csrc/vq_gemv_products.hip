@@ -11,13 +11,14 @@
 // streams -- neighbouring runs, the same rows -- are on one XCD, behind one L2.  Outlier columns are workgroups of their own.
 // Two activation rows share a lookup of eight bytes; a table of products then holds four positions.
 //
-// What bounds it, in clocks of a compute unit (11008 x 4096, four groups, one row: 17 thousand of them, 13.4 us with the second launch's three
-// and both launches' own time): 6.9 thousand until activations and the operands' 96 KB are there; 2.1 for storing a table of products (64 bytes
-// a clock), twice; one a row and octet for the lookups (64 of four bytes take 64 clocks for a wave's eight), twice 2.2, the first time 3.5 as
-// the index loads, a line a lane, keep L1's address unit busy for 4.5.
-// Measured against a slot a table (vq_gemv_lds.hip), the 2.26-bit setting, one / two rows: 11008 x 4096 24.0 -> 13.4 us, 30.5 -> 16.4;
-// 4096 x 11008 22.6 -> 12.5, 29.1 -> 15.7; 8192 x 28672 89 -> 44, 173 -> 51; 1024 x 4096 11.0 -> 9.4, 12.0 -> 11.5.  With one group, one row,
-// against vq_gemv_rows.hip: 11008 x 4096 16.1 -> 12.7, 4096 x 11008 16.6 -> 12.3, 8192 x 28672 equal.
+// What bounds it, in clocks of a compute unit (11008 x 4096, four groups, one row, with indices and tables out of the caches: 21 thousand of
+// them, 15.3 us with the second launch's and both launches' own time): 7.9 thousand until activations and the operands' 96 KB are there, 10.8 in
+// the workgroups that wait for lines of the indices as well; 2.1 for storing a table of products (64 bytes a clock), twice; one a row and octet
+// for the lookups (64 of four bytes take 64 clocks for a wave's eight), twice 2.2, the first time 3.6 as the index loads, a line a lane, keep
+// L1's address unit busy for 4.5.
+// Measured against a slot a table (vq_gemv_lds.hip), the 2.26-bit setting, the same call over and over, one / two rows: 11008 x 4096 24.0 ->
+// 13.5 us, 30.5 -> 16.4; 4096 x 11008 22.6 -> 12.5, 29.1 -> 15.7; 8192 x 28672 89 -> 44, 173 -> 51; 1024 x 4096 11.0 -> 9.4, 12.0 -> 11.5.  With one
+// group, one row, against vq_gemv_rows.hip: 11008 x 4096 16.1 -> 12.7, 4096 x 11008 16.6 -> 12.3, 8192 x 28672 equal.
 #include <algorithm>
 
 #include "vq_lds_tables.hpp"
@@ -140,8 +141,9 @@ __global__ __launch_bounds__(THREADS) void gemv_products_kernel(Params p, Produc
   auto load = [&](int pair, int c) {                                       // (past a row's end: the next row's bits, or zeros)
     const int row = row0 + c * THREADS + lane;
     const unsigned at = row < row1 ? (unsigned)row * (unsigned)stride + (unsigned)((p_first >> 3) + 2 * pair) * 12u : 0xFFFFFF00u;
+    const bool more = p_first + pair * 16 + 10 < p_hi;                    // (else the last indices are in the first load; the second would be the next row's line: 19.1 us)
     const uint4v a = __builtin_bit_cast(uint4v, __builtin_amdgcn_raw_buffer_load_b128(r_i, at, 0, 0));
-    const uint2v b = __builtin_bit_cast(uint2v, __builtin_amdgcn_raw_buffer_load_b64(r_i, at + 16u, 0, 0));
+    const uint2v b = __builtin_bit_cast(uint2v, __builtin_amdgcn_raw_buffer_load_b64(r_i, more ? at + 16u : 0xFFFFFF00u, 0, 0));
     win[c][0] = a.x; win[c][1] = a.y; win[c][2] = a.z; win[c][3] = a.w; win[c][4] = b.x; win[c][5] = b.y;
   };
   // (in the order in which they are waited for: the column of a thread's first activation, the table, the activation, the indices)
@@ -166,6 +168,16 @@ __global__ __launch_bounds__(THREADS) void gemv_products_kernel(Params p, Produc
     entries[i] = __builtin_bit_cast(half8v, uint4v{both[0], both[1], both[2], both[3]});
 #pragma unroll
     for (int d = 0; d < 4; ++d) top = max(top, max(both[d] & 0x7C00u, (both[d] >> 16) & 0x7C00u));
+  }
+
+  // The lines of the indices start on their way from memory to L2 here: neighbouring runs share them, so each touches a share of the
+  // rows, with waves that have no activations to wait for (forty layers in turn, 11008 x 4096: 16.4 -> 15.3 us; one layer 13.5 -> 13.9).
+  const int share = max(1, 5 / plan.run_pairs);
+  unsigned touched[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int row = split * plan.split_rows + (tid - THREADS / 2 + u * (THREADS / 2)) * share + run % share;
+    touched[u] = tid >= THREADS / 2 && row < row1 ? __builtin_amdgcn_raw_buffer_load_b32(r_i, (unsigned)row * (unsigned)stride + (unsigned)(p_first >> 3) * 12u, 0, 0) : 0u;
   }
 
   // activations of the run, a vector to sixteen places, zeros past it, past the group and past the row
@@ -271,6 +283,7 @@ __global__ __launch_bounds__(THREADS) void gemv_products_kernel(Params p, Produc
       }
     }
   }
+  asm volatile("" :: "v"(touched[0]), "v"(touched[1]));
   const int plane = rest;
 #pragma unroll
   for (int c = 0; c < CHUNKS; ++c) {
