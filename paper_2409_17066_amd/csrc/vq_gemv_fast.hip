@@ -121,10 +121,13 @@ __device__ __forceinline__ void gemv_v6_body(const Params &p, const GemvPlan &pl
   const int first_vec = (slice * 64 + lane) * U;
 
   // ---- index stream geometry of this lane
+  // (a lane past the row's last vector reads past the end of the streams, i.e. zeros: index 0 in all such lanes is one address, the next row's
+  // bits would be as many lookups as anyone's)
+  const bool past = is_main && first_vec >= p.P;
   const unsigned bit0 = (unsigned)first_vec * 12u;
-  const unsigned dw_main = bit0 >> 5, sh_main = bit0 & 31u;
+  const unsigned dw_main = past ? 0x20000000u : bit0 >> 5, sh_main = bit0 & 31u;
   const unsigned bitr = (unsigned)first_vec * (unsigned)RB;
-  const unsigned dw_res = bitr >> 5, sh_res = bitr & 31u;
+  const unsigned dw_res = past ? 0x20000000u : bitr >> 5, sh_res = bitr & 31u;
   const unsigned st_main = (unsigned)(is_out ? p.stride_out : p.stride), st_res = (unsigned)p.stride_res;
   const __amdgpu_buffer_rsrc_t r_main =
       is_out ? make_rsrc(p.idx_out + (long long)row0 * p.stride_out, (unsigned)rows_here * st_main)
@@ -214,8 +217,21 @@ __device__ __forceinline__ void gemv_v6_body(const Params &p, const GemvPlan &pl
     }
     const int b = b0;
     const unsigned char *xl = lds + plan.lds_x + region * plan.x_bytes;
+    // (in pieces of sixteen bytes where the lanes' vectors begin on them: in dwords, sixteen banks' worth of which lie under 64 lanes, the
+    // reads of all waves took a thousand clocks of the start-up)
+    const bool wide = U % 4 == 0 && is_main && p.n_out % 8 == 0;
+    if (wide) {
+#pragma unroll
+      for (int i = 0; i < U * 3 / 4; ++i) {
+        const uint4v v = *reinterpret_cast<const uint4v *>(xl + c0 * 2 + i * 16);
+        const unsigned d[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) xr[b][(i * 4 + j) / 3][(i * 4 + j) % 3] = d[j];
+      }
+    }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
+      if (wide) break;
       if (is_main) {
 #pragma unroll
         for (int h = 0; h < 3; ++h) xr[b][u][h] = *reinterpret_cast<const unsigned *>(xl + (c0 + u * 6 + h * 2) * 2);
@@ -232,7 +248,7 @@ __device__ __forceinline__ void gemv_v6_body(const Params &p, const GemvPlan &pl
     float s0 = 0.0f;
     for (unsigned o = threadIdx.x * 16u; o < plan.x_bytes; o += NW * 64 * 16u) {
       const uint4v v = *reinterpret_cast<const uint4v *>(xl + o);
-      s0 += half_pair_sum(v.x) + half_pair_sum(v.y) + half_pair_sum(v.z) + half_pair_sum(v.w);
+      s0 = dot2(v.w, 0x3C003C00u, dot2(v.z, 0x3C003C00u, dot2(v.y, 0x3C003C00u, dot2(v.x, 0x3C003C00u, s0))));      // (times one)
     }
     const float s = wave_reduce_to_lane63(s0);
     if (lane == 63) xsum[b * NW + wv] = s;
