@@ -152,20 +152,42 @@ static bool down_mfma_wanted(const Params &p, const __half *x, long long ldx, in
   const char fk = forced_kernel();
   return fk != 'g' && fk != 'd' && gemv_down_applicable(p, x, ldx) && gemv_down_mfma_applicable(p, x, ldx, batch);
 }
-// With a workspace (column parts, one workgroup per block of 16 streams and part): from two rows on, and for any batch
-// when there are codebook groups (measured, 4096 x 4096: one row 12.8 against 10.5 us, two rows 13.0 against 12.7 us and
-// level from there; 16 groups, one row: 15.5 against 17.4 us).
+// Estimates in microseconds, beyond the five of either kernel's start, of 150 layers (300 to 14336 outputs, 1000 to 20000 columns, without
+// and with a residual table).  The matrix-core kernel: a workgroup walks a part of the columns of 16 streams, at the same price for any number of
+// rows; parts are added up by a second launch.  The other one deals single streams out to the whole chip, up to four rows a launch (three
+// are two).  One to four rows without parts, 11008 x 4096: 10.9 against 8.8, 11.4, 20.0, 17.5 us; 4096 x 4096: 10.7 against 6.7, 8.5, 15.0, 12.3;
+// 14336 x 2048: 8.2 against 9.9, 12.3, 22.1, 18.4; 2000 x 20000, three and four rows: 33 against 25 and 29.  With two 4096-entry tables, 4096 x 4096:
+// 18.5 against 10.1, 12.5, 22.4, 24.4.
+static float down_mfma_us(const Params &p, int parts) {
+  const int blocks = (p.S + 15) / 16;
+  return (p.k_res ? 3.0e-3f : 1.4e-3f) * (float)p.P / (float)parts * (float)((blocks * parts + cu_count() - 1) / cu_count()) + (parts > 1 ? 2.1f : 0.0f);
+}
+static float down_streams_us(const Params &p, int batch) {
+  const float vectors = (float)p.S * (float)p.P * 1e-6f;
+  const bool many_columns = p.P >= 8192;                  // (of which fewer rows, or slower ones, fit LDS)
+  if (!p.k_res) return batch == 1 ? (many_columns ? 0.8f : 0.6f) * vectors : batch == 2 ? 0.6f + 1.05f * vectors : batch == 3 ? 6.0f + 2.35f * vectors : 2.4f + 1.9f * vectors;
+  if (many_columns && p.bits_res == 12) return 1.5f * (float)batch * vectors;
+  return batch == 1 ? (many_columns ? 1.5f : 1.05f) * vectors : batch == 2 ? 2.2f + 1.3f * vectors : batch == 3 ? 8.5f + 2.3f * vectors : 4.0f + 3.4f * vectors;
+}
+// With a workspace (column parts, one workgroup per block of 16 streams and part): from two rows on, for any batch when there are codebook
+// groups (16 groups, one row: 15.5 against 17.4 us), and for one row by the estimates (4096 x 4096 8.3 against 6.7 us; 4096 x 11008 10.4
+// against 11.4; not with outlier columns, a set of sums more: 2000 x 20000 20.7 against 18.8).
 // (and for one row of a layer whose activations do not fit the other kernel's LDS beside the tables)
 static bool down_mfma_parts_wanted(const Params &p, const __half *x, long long ldx, int batch) {
-  return down_mfma_wanted(p, x, ldx, batch) && (batch >= 2 || p.n_groups > 1 || forced_kernel() == 'm' || !gemv_down_fits(p));
+  return down_mfma_wanted(p, x, ldx, batch) && (batch >= 2 || p.n_groups > 1 || forced_kernel() == 'm' || !gemv_down_fits(p) ||
+                                                (!p.Q && down_mfma_us(p, gemv_down_mfma_parts(p)) < down_streams_us(p, 1)));
 }
-// Without a workspace a block of 16 streams is one workgroup over all the columns: with few blocks and three or four rows the
-// other kernel, which spreads single streams over the chip, is still ahead (4096 x 11008, 43 blocks: 26 against 34 us).
 static bool down_mfma_alone_wanted(const Params &p, const __half *x, long long ldx, int batch) {
   if (!down_mfma_wanted(p, x, ldx, batch)) return false;
   if (p.n_groups > 1) return true;                        // the only fast kernel of this orientation that walks codebook groups by itself
-  // (with a 12-bit residual stream the other kernel pays twice per row, and three rows are enough: 4096 x 11008, 54 against 46 us)
-  return batch >= 5 || (batch >= 3 && (p.S >= 64 * 16 || (p.k_res && p.bits_res == 12))) || forced_kernel() == 'm';
+  return batch >= 5 || forced_kernel() == 'm' || down_mfma_us(p, 1) < down_streams_us(p, batch);      // (of five rows and more a launch of four is one of two)
+}
+// Whether parts of the columns, which a workspace is there for, are worth the second launch (300 x 1000, two rows 8.5 -> 6.1 us, four 8.1 -> 6.2;
+// 4096 x 4096, two rows, parts 8.4, without 8.6).
+static bool down_mfma_parts_pay(const Params &p, int batch) {
+  if (p.n_groups > 1 || forced_kernel() == 'm' || !gemv_down_fits(p)) return true;
+  const float alone = down_mfma_us(p, 1);
+  return down_mfma_us(p, gemv_down_mfma_parts(p)) < (batch <= 4 ? std::min(alone, down_streams_us(p, batch)) : alone);
 }
 
 bool gemv_rows_applicable(const Params &p);
@@ -482,6 +504,7 @@ static int launch_with_workspace(const Params &p, const __half *x, long long ldx
     return rc == VQ_OK ? launch_groups_finish(part, part_xs, parts, batch, p, y, ldy, s) : rc;
   }
   if (need && workspace && workspace_bytes >= need && p.orientation == 1 && down_mfma_parts_wanted(p, x, ldx, batch)) {
+    if (!down_mfma_parts_pay(p, batch)) return launch_gemv(p, x, ldx, batch, y, ldy, s);
     const int parts = gemv_down_mfma_parts(p), slots = parts + (p.Q ? 1 : 0);
     float *part = static_cast<float *>(workspace), *part_xs = part + (size_t)slots * (size_t)batch * (size_t)p.out_features;
     int rc = launch_gemv_down_mfma(p, x, ldx, batch, nullptr, 0, s, part, part_xs, parts);

@@ -2,23 +2,23 @@
 // layout, Sec. 3.1 and Algorithm 1), v = 6, 12-bit indices, optional 12- or 8-bit residual codebook, outlier columns,
 // any batch up to 16 in one launch (App. "Our Dequantization Implementation", second phase), one or more codebook groups.
 //
-// In this layout a gathered centroid meets ONE activation and feeds six output rows, y[6p + j] += C[I[p][n]][j] * x[n]:
-// on the vector ALUs that is six multiply-adds per gather and token, and from four tokens on the kernel of
-// vq_gemv_down.hip is bound by them.  One v_mfma_f32_16x16x32_f16 takes their place.  Its 32 "k" slots are four groups
-// of eight; a group is one column n of the layer, and the eight slots are the six elements j' of the centroid of that
-// column plus two zeros -- exactly the 16-byte table entry in LDS, as operand A of the stream (l & 15).  Operand B is
-// built to match: its 16 columns are (token, j) pairs -- the 6 x batch pairs of a launch are dealt out 16 to an
-// instruction, ceil(6 batch / 16) instructions per step -- and the value in slot (n, j') of column (t, j) is x[t][n] where
-// j' = j and zero elsewhere.  The product then is D[stream][(t, j)] = sum over the four columns of
-// C[I[stream][n]][j] * x[t][n]: 16 streams x 4 columns x 2 2/3 tokens per instruction, an eighth of its multiply-adds put
-// to use, and still several times the rate of the vector ALUs.  A lane builds one B operand with three byte permutes
-// (v_perm_b32 with per-lane selectors that place one half of an activation dword and zero the rest).
+// In this layout a gathered centroid meets ONE activation and feeds six output rows, y[6p + j] += C[I[p][n]][j] * x[n]: on the vector ALUs
+// six multiply-adds per gather and token.  A lane looks up eight neighbouring columns of stream (l & 15); element j of those eight
+// entries, put together with four byte permutes, is operand A of v_mfma_f32_16x16x32_f16 for output row j of sixteen streams and 32
+// columns, and operand B are the token's eight activations as they lie in memory.  So a window takes six instructions (twelve with a
+// residual table) and 24 (48) permutes at any number of tokens up to 16, and a lane gets row j of four streams for its token.
+// (Before, operand A was the entry and operand B the activations in six places among zeros, ceil(6 batch / 16) instructions a column of entries
+// and three permutes each: sixteen rows, 11008 x 4096 with column parts 18.4 -> 12.5 us, four 11.3 -> 9.9; two 4096-entry tables, without
+// parts, 4096 x 11008, 93 -> 38 and 40 -> 37; a whole decoder layer, sixteen rows 89 -> 52 us, with residual tables 125 -> 70.)
+//
+// What bounds it: eleven of the 17 thousand clocks of 11008 x 4096 in two parts are the windows', 160 of a compute unit each, of which LDS
+// takes 106 for the lookups.  Sixteen waves instead of eight (9.9 -> 10.8 us) and lookups a window ahead of the products (10.3) are slower.
 //
 // Work split: a workgroup of eight waves owns one block of 16 index streams (96 output rows) and one part of the
 // columns; wave w takes the part's windows w, w + 8, ... of 32 columns (eight per lane: 96 index bits, three aligned
-// dwords; its eight activations per token are one 16-byte load, read straight from memory -- they are hits in L2 --
+// dwords; its eight activations of its token are one 16-byte load, read straight from memory -- they are hits in L2 --
 // with range-checked buffer loads).  Index words and activations run a few windows ahead in a register ring.  At the
-// end the waves' 16 x 16 sums per token pair meet in LDS, in the space of the tables, which are no longer needed.
+// end the waves' 16 x 16 sums per output row of the streams meet in LDS, in the space of the tables, which are no longer needed.
 // With one part the workgroup applies y = scale * sum + bias * sum(x) itself; a block of 16 streams is a coarse unit,
 // though (a 4096 x 4096 layer has 43 of them for 256 compute units), so when the caller lends a workspace the columns
 // are cut into parts, every (block, part) is a workgroup, the binary32 sums go to the workspace [part][token][row] and
@@ -63,22 +63,19 @@ __device__ __forceinline__ float4v mfma16(uint4v a, uint4v b, float4v c) {
 // take one group (or the only one) and have no loop around the start-up (with the loop in every instantiation the
 // single-group ones lost up to 4 us on a 4096 x 4096 layer in 16 groups: registers held across the loop edge).
 // `wg` is the workgroup's number within its layer (a launch may hold the workgroups of several layers).
-// NTP: instructions per step, each with 16 of the 6 x batch (token, row) pairs as operand columns.
-template <int RES_BITS, int NTP, bool WALK>
+template <int RES_BITS, bool WALK>
 __device__ __forceinline__ void gemv_down_mfma_body(const Params &p, const DownMfmaPlan &plan, const __half *__restrict__ x, long long ldx,
                                                     __half *__restrict__ y, long long ldy, int wg) {
   typedef Layout<RES_BITS> LY;
   constexpr int RB = RES_BITS ? RES_BITS : 8;
   constexpr int NR = RES_BITS == 12 ? 3 : 2;             // dwords of a lane's residual indices
   // (measured: a ring deeper than this only adds start-up loads -- a wave of a column part has few windows -- and the
-  // refill of a slot already runs a window ahead of its use; 4 deep -> 1 deep: 4096 x 4096 with residual and workspace,
-  // batch 4, 14.1 -> 12.9 us; q+k+v fused, batch 4, 24.4 -> 22.1 us)
-  constexpr int DEPTH = (NTP == 1 && RES_BITS == 0) ? 2 : 1;
-  constexpr bool LATE_X = NTP >= 6;                      // registers: refill a slot's activations only after the window's last product
+  // refill of a slot already runs a window ahead of its use)
+  constexpr int DEPTH = 1;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int n = lane & 15, g = lane >> 4;                // A: stream n of the block, column group g.  B and D: column n = (token, j)
+  const int n = lane & 15, g = lane >> 4;                // A: stream n of the block, column group g.  B: token n.  D: token n, streams 4g..4g+3
   const int blk = wg / plan.ksplit, part_i = wg - blk * plan.ksplit;
   // A part belongs to one codebook group; without a workspace the workgroup walks all groups, one set of tables after the
   // other in LDS, and its sums simply keep running (the tables change with the column, the output rows do not).
@@ -97,33 +94,14 @@ __device__ __forceinline__ void gemv_down_mfma_body(const Params &p, const DownM
   unsigned short *o_tile = reinterpret_cast<unsigned short *>(lds + plan.lds_o);
   unsigned short *o_x = o_tile + OROWS * Q2;
   float *o_sum = reinterpret_cast<float *>(o_x + 16 * Q2), *o_xs = o_sum + 16 * OROWS;
-  // ---- this lane's side of operand B
-  // (operand column n of instruction m is pair 16 m + n of the 6 x batch (token, row j) pairs: token (16 m + n) / 6, row
-  // (16 m + n) % 6 = (n + 4 (m % 3)) % 6 -- three patterns of rows; pairs past the batch read zero activations)
-  auto token_of = [&](int m) { return (16 * m + n) / 6; };
-  auto row_of = [&](int m) { return (16 * m + n) % 6; };
-  // byte selectors that move the low (even column) or high (odd column) half of an activation dword into half (j & 1) of
-  // dword (j >> 1) of the operand, zeros (selector byte 0x0c) everywhere else
-  constexpr int NPAT = NTP < 3 ? NTP : 3;
-  unsigned sel[NPAT][3][2];
-#pragma unroll
-  for (int pm = 0; pm < NPAT; ++pm) {
-    const int j = row_of(pm);
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      const bool mine = d == (j >> 1);
-      sel[pm][d][0] = !mine ? 0x0c0c0c0cu : (j & 1) ? 0x01000c0cu : 0x0c0c0100u;
-      sel[pm][d][1] = !mine ? 0x0c0c0c0cu : (j & 1) ? 0x03020c0cu : 0x0c0c0302u;
-    }
-  }
   const unsigned st_main = (unsigned)p.stride, st_res = (unsigned)p.stride_res;
   const __amdgpu_buffer_rsrc_t r_main = make_rsrc(p.idx, (unsigned)p.S * st_main);
   const __amdgpu_buffer_rsrc_t r_res = make_rsrc(RES_BITS ? p.idx_res : p.idx, RES_BITS ? (unsigned)p.S * st_res : 0u);
   const __amdgpu_buffer_rsrc_t r_x = make_rsrc(x, plan.x_bytes);
-  float4v acc[NTP];
-  float xs[NTP];
+  float4v acc[6];                                        // output row j of every stream
+  float xs = 0.0f;
 #pragma unroll
-  for (int tp = 0; tp < NTP; ++tp) { acc[tp] = float4v{0.0f, 0.0f, 0.0f, 0.0f}; xs[tp] = 0.0f; }
+  for (int j = 0; j < 6; ++j) acc[j] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
 
   for (int grp = g_lo; grp < g_hi; ++grp) {
     // the group's stream positions [pos_lo, pos_hi) -- pos_lo a multiple of 8, a dword boundary of the streams -- and the
@@ -179,23 +157,16 @@ __device__ __forceinline__ void gemv_down_mfma_body(const Params &p, const DownM
 
     }
 
-    // byte offset of this lane's first activation of window 0, per token pair; a token past the batch (and the idle columns)
-    // reads out of range, i.e. zeros
+    // byte offset of this lane's first activation of window 0; a token past the batch reads out of range, i.e. zeros
     const int col0 = p.n_out + pos_lo;                     // column of x that meets the part's window 0
-    unsigned xoff[NTP];
-#pragma unroll
-    for (int tp = 0; tp < NTP; ++tp) {
-      const int t = token_of(tp);
-      xoff[tp] = t < plan.batch ? (unsigned)(((long long)t * ldx + col0 + 8 * g) * 2) : 0x80000000u;
-    }
+    const unsigned xoff = n < plan.batch ? (unsigned)(((long long)n * ldx + col0 + 8 * g) * 2) : 0x80000000u;
 
     // a stream past the last one reads out of range: index 0, whose products land in rows that are never stored
     const unsigned srow_main = (unsigned)(blk * 16 + n) * st_main + (unsigned)(pos_lo >> 3) * 12u;
     const unsigned srow_res = (unsigned)(blk * 16 + n) * st_res + (unsigned)(pos_lo >> 3) * (unsigned)RB;
 
     // The loaders run DEPTH windows ahead of the consumer.  A slot's index words are refilled as soon as the gather
-    // addresses have been formed from them; so are its activations, from a copy, except with 16 tokens, where the copy
-    // would not fit the registers and the refill waits for the window's last product.
+    // addresses have been formed from them; so are its activations, from a copy.
     int lw = w_lo + wv, lwx = w_lo + wv;
     auto load_idx = [&](Window<3> &wm, Window<NR> &wr) {
       const unsigned wq = (unsigned)(lw < w_hi ? lw : w_lo);                   // past the end: any window in range, never used
@@ -204,20 +175,19 @@ __device__ __forceinline__ void gemv_down_mfma_body(const Params &p, const DownM
       if (RES_BITS == 12) load_window(wr, r_res, srow_res + (wq * 4u + (unsigned)g) * 12u, 0u);
       if (RES_BITS == 8) load_window(wr, r_res, srow_res + (wq * 4u + (unsigned)g) * 8u, 0u);
     };
-    auto load_x = [&](uint4v (&xx)[NTP]) {
+    auto load_x = [&](uint4v &xx) {
       const unsigned wq = (unsigned)(lwx < w_hi ? lwx : w_lo);
       lwx += MW;
-#pragma unroll
-      for (int tp = 0; tp < NTP; ++tp) xx[tp] = __builtin_amdgcn_raw_buffer_load_b128(r_x, xoff[tp] + wq * 64u, 0, 0);
+      xx = __builtin_amdgcn_raw_buffer_load_b128(r_x, xoff + wq * 64u, 0, 0);
     };
 
     Window<3> win[DEPTH];
     Window<NR> wres[DEPTH];
-    uint4v xr[DEPTH][NTP];
+    uint4v xr[DEPTH];
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d) { load_idx(win[d], wres[d]); load_x(xr[d]); }
     // the table loads are older than the ring's (loads return in order): at most the ring's may still be on their way
-    wait_vmem_at_most<DEPTH * (1 + (RES_BITS ? 1 : 0) + NTP)>();
+    wait_vmem_at_most<DEPTH * (2 + (RES_BITS ? 1 : 0))>();
     tables.store(p, lds, 0u, false, tid);
     lds_barrier();                                       // the tables are in (a full barrier would also wait for the ring's loads from HBM)
 
@@ -260,11 +230,9 @@ __device__ __forceinline__ void gemv_down_mfma_body(const Params &p, const DownM
           const int w = w_lo + wv + k * MW;
           const Window<3> cm = win[d];
           const Window<NR> cr = wres[d];
-          uint4v xv[NTP];
-#pragma unroll
-          for (int tp = 0; tp < NTP; ++tp) xv[tp] = xr[d][tp];
+          uint4v xv = xr[d];
           load_idx(win[d], wres[d]);                     // refill the slot; the copies above are what this window uses
-          if (!LATE_X) load_x(xr[d]);
+          load_x(xr[d]);
           uint4v e[VPL], f[RES_BITS ? VPL : 1];
 #pragma unroll
           for (int u = 0; u < VPL; ++u) lds_gather16<LY::MAIN_OFF>(e[u], field_addr<12, LY::MAIN_SH>(cm, u));
@@ -274,58 +242,46 @@ __device__ __forceinline__ void gemv_down_mfma_body(const Params &p, const DownM
           }
           if (w == windows - 1) {                          // the window that holds the end of the stream or of the group: zero what lies past it
             const int left = pos_hi - pos_lo - (w * 32 + g * 8);               // of this lane's eight positions
+            unsigned xd[4] = {xv.x, xv.y, xv.z, xv.w};
 #pragma unroll
-            for (int tp = 0; tp < NTP; ++tp) {
-              unsigned xd[4] = {xv[tp].x, xv[tp].y, xv[tp].z, xv[tp].w};
-#pragma unroll
-              for (int q = 0; q < 4; ++q) xd[q] = left >= 2 * q + 2 ? xd[q] : left == 2 * q + 1 ? xd[q] & 0xFFFFu : 0u;
-              xv[tp].x = xd[0]; xv[tp].y = xd[1]; xv[tp].z = xd[2]; xv[tp].w = xd[3];
-            }
+            for (int q = 0; q < 4; ++q) xd[q] = left >= 2 * q + 2 ? xd[q] : left == 2 * q + 1 ? xd[q] & 0xFFFFu : 0u;
+            xv = uint4v{xd[0], xd[1], xd[2], xd[3]};
           }
-          if (need_xs) {
-#pragma unroll
-            for (int tp = 0; tp < NTP; ++tp)
-              xs[tp] = dot2(xv[tp].x, 0x3C003C00u, dot2(xv[tp].y, 0x3C003C00u, dot2(xv[tp].z, 0x3C003C00u, dot2(xv[tp].w, 0x3C003C00u, xs[tp]))));
-          }
+          if (need_xs) xs = dot2(xv.x, 0x3C003C00u, dot2(xv.y, 0x3C003C00u, dot2(xv.z, 0x3C003C00u, dot2(xv.w, 0x3C003C00u, xs))));
           lds_gather_wait();
 #pragma unroll
           for (int u = 0; u < VPL; ++u) { settle(e[u]); if (RES_BITS) settle(f[u]); }
+          // row j of the eight columns' entries, in the order of the columns: operand A against the token's activations as they are
 #pragma unroll
-          for (int u = 0; u < VPL; ++u) {
+          for (int j = 0; j < 6; ++j) {
+            auto row_of = [&](const uint4v (&v)[VPL]) {
+              unsigned a[4];
 #pragma unroll
-            for (int tp = 0; tp < NTP; ++tp) {
-              const unsigned xd = (u >> 1) == 0 ? xv[tp].x : (u >> 1) == 1 ? xv[tp].y : (u >> 1) == 2 ? xv[tp].z : xv[tp].w;
-              uint4v b;
-              b.x = __builtin_amdgcn_perm(xd, xd, sel[tp % 3][0][u & 1]);
-              b.y = __builtin_amdgcn_perm(xd, xd, sel[tp % 3][1][u & 1]);
-              b.z = __builtin_amdgcn_perm(xd, xd, sel[tp % 3][2][u & 1]);
-              b.w = 0u;
-              acc[tp] = mfma16(e[u], b, acc[tp]);
-              if (RES_BITS) acc[tp] = mfma16(f[u], b, acc[tp]);
-            }
+              for (int q = 0; q < 4; ++q) a[q] = __builtin_amdgcn_perm(v[2 * q + 1][j >> 1], v[2 * q][j >> 1], j & 1 ? 0x07060302u : 0x05040100u);
+              return uint4v{a[0], a[1], a[2], a[3]};
+            };
+            acc[j] = mfma16(row_of(e), xv, acc[j]);
+            if constexpr (RES_BITS != 0) acc[j] = mfma16(row_of(f), xv, acc[j]);
           }
-          if (LATE_X) load_x(xr[d]);
         }
       }
     }
 
   }
 
-  // ---- the waves meet: sums per token pair, 1 KB per wave and pair, in the space of the tables
+  // ---- the waves meet: sums per output row of the streams, 1 KB per wave and row, in the space of the tables
   __syncthreads();
-  float4v *pbuf = reinterpret_cast<float4v *>(lds);                           // [NTP][MW][64]
-  float *xsb = reinterpret_cast<float *>(lds + NTP * MW * 1024);              // [MW][16 tokens][4]
+  float4v *pbuf = reinterpret_cast<float4v *>(lds);                           // [6][MW][64]
+  float *xsb = reinterpret_cast<float *>(lds + 6 * MW * 1024);                // [MW][16 tokens][4]
 #pragma unroll
-  for (int tp = 0; tp < NTP; ++tp) {
-    pbuf[(tp * MW + wv) * 64 + lane] = acc[tp];
-    if (row_of(tp) == 0 && token_of(tp) < plan.batch) xsb[(wv * 16 + token_of(tp)) * 4 + g] = xs[tp];
-  }
+  for (int j = 0; j < 6; ++j) pbuf[(j * MW + wv) * 64 + lane] = acc[j];
+  xsb[(wv * 16 + n) * 4 + g] = xs;
   __syncthreads();
-  if (wv < NTP) {                                        // wave tp finishes token pair tp
-    const int tp = wv, t = token_of(tp), j = row_of(tp);
+  if (wv < 6) {                                          // wave j finishes row j
+    const int t = n, j = wv;
     float4v s = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int w = 0; w < MW; ++w) s += pbuf[(tp * MW + w) * 64 + lane];
+    for (int w = 0; w < MW; ++w) s += pbuf[(j * MW + w) * 64 + lane];
     if (t < plan.batch) {
       float xsum = 0.0f;
       if (need_xs) {
@@ -357,10 +313,10 @@ __device__ __forceinline__ void gemv_down_mfma_body(const Params &p, const DownM
   }
 }
 
-template <int RES_BITS, int NTP, bool WALK>
+template <int RES_BITS, bool WALK>
 __global__ __launch_bounds__(MW * 64) void gemv_down_mfma_kernel(Params p, DownMfmaPlan plan, const __half *__restrict__ x, long long ldx,
                                                                  __half *__restrict__ y, long long ldy) {
-  gemv_down_mfma_body<RES_BITS, NTP, WALK>(p, plan, x, ldx, y, ldy, (int)blockIdx.x);
+  gemv_down_mfma_body<RES_BITS, WALK>(p, plan, x, ldx, y, ldy, (int)blockIdx.x);
 }
 
 // Several layers that read the same activations (the query, key and value projections of a decoder layer; its gate and up
@@ -380,32 +336,32 @@ struct DownMultiArgs {
   DownMultiLayer layer[DMULTI_MAX];
 };
 
-template <int RES_BITS, int NTP>
+template <int RES_BITS>
 __global__ __launch_bounds__(MW * 64) void gemv_down_mfma_multi_kernel(DownMultiArgs a, const __half *__restrict__ x, long long ldx) {
   int i = 0;
   while (i + 1 < a.n && (int)blockIdx.x >= a.first_wg[i + 1]) ++i;
-  gemv_down_mfma_body<RES_BITS, NTP, false>(a.layer[i].p, a.layer[i].plan, x, ldx, a.layer[i].y, a.layer[i].ldy, (int)blockIdx.x - a.first_wg[i]);
+  gemv_down_mfma_body<RES_BITS, false>(a.layer[i].p, a.layer[i].plan, x, ldx, a.layer[i].y, a.layer[i].ldy, (int)blockIdx.x - a.first_wg[i]);
 }
 
 
 // LDS of one layer: tables (or the meeting place of the waves, which takes their space at the end), then the outlier tile
-template <int RES_BITS, int NTP>
+template <int RES_BITS>
 unsigned place_lds(const Params &p, DownMfmaPlan &plan) {
   unsigned lds_bytes = Layout<RES_BITS>::BYTES;
-  const unsigned meet = (unsigned)(NTP * MW) * 1024u + (unsigned)(MW * 16 * 4) * 4u;
+  const unsigned meet = (unsigned)(6 * MW) * 1024u + (unsigned)(MW * 16 * 4) * 4u;
   if (lds_bytes < meet) lds_bytes = meet;
   plan.lds_o = lds_bytes;
   if (p.Q) lds_bytes += (unsigned)((OROWS + 16) * plan.o_pitch + 16 * OROWS + 16) * 4u;
   return lds_bytes;
 }
 
-template <int RES_BITS, int NTP>
+template <int RES_BITS>
 int launch_multi(DownMultiArgs &a, const __half *x, long long ldx, hipStream_t s) {
-  auto kernel = gemv_down_mfma_multi_kernel<RES_BITS, NTP>;
+  auto kernel = gemv_down_mfma_multi_kernel<RES_BITS>;
   VQ_ALLOW_FULL_LDS(kernel);
   unsigned lds_bytes = 0;
   for (int i = 0; i < a.n; ++i) {
-    const unsigned b = place_lds<RES_BITS, NTP>(a.layer[i].p, a.layer[i].plan);
+    const unsigned b = place_lds<RES_BITS>(a.layer[i].p, a.layer[i].plan);
     if (b > lds_bytes) lds_bytes = b;
   }
   if (lds_bytes > 160u * 1024u) return VQ_ERR_UNSUPPORTED;
@@ -413,12 +369,12 @@ int launch_multi(DownMultiArgs &a, const __half *x, long long ldx, hipStream_t s
   return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
 }
 
-template <int RES_BITS, int NTP, bool WALK>
+template <int RES_BITS, bool WALK>
 int launch_one(const Params &p, DownMfmaPlan &plan, unsigned grid, const __half *x, long long ldx, __half *y, long long ldy,
                hipStream_t s) {
-  auto kernel = gemv_down_mfma_kernel<RES_BITS, NTP, WALK>;
+  auto kernel = gemv_down_mfma_kernel<RES_BITS, WALK>;
   VQ_ALLOW_FULL_LDS(kernel);
-  const unsigned lds_bytes = place_lds<RES_BITS, NTP>(p, plan);
+  const unsigned lds_bytes = place_lds<RES_BITS>(p, plan);
   if (lds_bytes > 160u * 1024u) return VQ_ERR_UNSUPPORTED;                  // too many outlier columns to hold beside the tables
   hipLaunchKernelGGL(kernel, dim3(grid), dim3(MW * 64), lds_bytes, s, p, plan, x, ldx, y, ldy);
   return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
@@ -484,13 +440,10 @@ int launch_gemv_down_mfma(const Params &p, const __half *x, long long ldx, int b
   const int rc_plan = make_plan(p, ldx, batch, part, part_xs, parts, plan, &grid);
   if (rc_plan != VQ_OK) return rc_plan;
   const int rb = p.k_res ? p.bits_res : 0;
-  const int ntp = (6 * batch + 15) / 16;                // instructions whose 16 operand columns hold the 6 x batch (token, row) pairs
   const bool walk = !part && p.n_groups > 1;
-#define VQ_CASE(R, N, LO) if (rb == R && ntp > LO && ntp <= N) \
-    return walk ? launch_one<R, N, true>(p, plan, (unsigned)grid, x, ldx, y, ldy, s) : launch_one<R, N, false>(p, plan, (unsigned)grid, x, ldx, y, ldy, s);
-  VQ_CASE(0, 1, 0) VQ_CASE(0, 2, 1) VQ_CASE(0, 3, 2) VQ_CASE(0, 4, 3) VQ_CASE(0, 6, 4)
-  VQ_CASE(8, 1, 0) VQ_CASE(8, 2, 1) VQ_CASE(8, 3, 2) VQ_CASE(8, 4, 3) VQ_CASE(8, 6, 4)
-  VQ_CASE(12, 1, 0) VQ_CASE(12, 2, 1) VQ_CASE(12, 3, 2) VQ_CASE(12, 4, 3) VQ_CASE(12, 6, 4)
+#define VQ_CASE(R) if (rb == R) \
+    return walk ? launch_one<R, true>(p, plan, (unsigned)grid, x, ldx, y, ldy, s) : launch_one<R, false>(p, plan, (unsigned)grid, x, ldx, y, ldy, s);
+  VQ_CASE(0) VQ_CASE(8) VQ_CASE(12)
 #undef VQ_CASE
   return VQ_ERR_UNSUPPORTED;
 }
@@ -516,11 +469,8 @@ int launch_gemv_down_mfma_multi(const Params *ps, int n, const __half *x, long l
     if (total > 0x7FFFFFFFLL) return VQ_ERR_UNSUPPORTED;
   }
   a.first_wg[n] = (int)total;
-  const int ntp = (6 * batch + 15) / 16;
-#define VQ_CASE(R, N, LO) if (rb == R && ntp > LO && ntp <= N) return launch_multi<R, N>(a, x, ldx, s);
-  VQ_CASE(0, 1, 0) VQ_CASE(0, 2, 1) VQ_CASE(0, 3, 2) VQ_CASE(0, 4, 3) VQ_CASE(0, 6, 4)
-  VQ_CASE(8, 1, 0) VQ_CASE(8, 2, 1) VQ_CASE(8, 3, 2) VQ_CASE(8, 4, 3) VQ_CASE(8, 6, 4)
-  VQ_CASE(12, 1, 0) VQ_CASE(12, 2, 1) VQ_CASE(12, 3, 2) VQ_CASE(12, 4, 3) VQ_CASE(12, 6, 4)
+#define VQ_CASE(R) if (rb == R) return launch_multi<R>(a, x, ldx, s);
+  VQ_CASE(0) VQ_CASE(8) VQ_CASE(12)
 #undef VQ_CASE
   return VQ_ERR_UNSUPPORTED;
 }

@@ -976,3 +976,24 @@ def test_tables_of_products_keep_what_is_no_number_where_it_belongs(gpu_lib, mon
     x[0, 30] = float("inf")
     y = gpu_lib.gemv(dl, x, workspace=ws).float().cpu()[0]
     assert not torch.isfinite(y).any()
+
+
+@pytest.mark.parametrize("out_features,in_features,k_res", [(3000, 16390, 0), (1000, 9001, 4096), (100, 300, 256), (97, 1000, 0)])
+@pytest.mark.parametrize("batch", [1, 2, 3, 4, 16])
+def test_gemv_down_routes(gpu_lib, out_features, in_features, k_res, batch):
+    """Vectors down the outputs: one row in column parts, few rows on either kernel, parts left out where they do not pay; streams and columns
+    that fill no block, part or window."""
+    import torch
+    L = s.make_layer(315, "down", out_features, in_features, 6, 4096, k_res, orientation=1)
+    dl = gpu_lib.DeviceLayer(L)
+    pitch = (in_features + 7) // 8 * 8
+    x_np = s.make_activations(315, L, batch)
+    x = torch.full((batch, pitch), float("nan"), dtype=torch.float16, device="cuda")
+    x[:, :in_features] = torch.from_numpy(x_np)
+    ref = oracle.gemv(L, x_np)
+    need = gpu_lib.vq_gemv_workspace_bytes(dl.desc, batch)
+    ws = torch.full((need + 256,), 0xFF, dtype=torch.uint8, device="cuda")
+    for y in (gpu_lib.gemv(dl, x[:, :in_features], workspace=ws[:need] if need else None), gpu_lib.gemv(dl, x[:, :in_features])):
+        torch.cuda.synchronize()
+        _check_matmul(y, ref, "batch %d" % batch)
+    assert (ws[need:] == 0xFF).all()
