@@ -196,6 +196,15 @@ static bool rows_beat_restoring(const Params &p, int tokens) {
   return (float)((tokens + 15) / 16) * launch < restore + gemm_dense_us(p, tokens, true);
 }
 
+// The same for vectors down the outputs, whose matrix-core kernel takes sixteen rows at the price of one; restoring 4 and 0.3 per million weights (0.4
+// with a residual table).  11008 x 4096 with a workspace, 9 / 17 / 33 tokens: 34 -> 11, 34 -> 21, 35 -> 34 us; 4096 x 11008 with residual tables 59 -> 17,
+// 59 -> 33, 59 -> 51; at 65 tokens they are level or behind.
+float gemv_down_rows_us(const Params &p, const __half *x, long long ldx);
+static bool down_rows_beat_restoring(const Params &p, const __half *X, long long ldx, int tokens) {
+  const float launch = gemv_down_rows_us(p, X, ldx), weights = (float)((double)p.out_features * p.in_features * 1e-6);
+  return launch > 0.0f && (float)((tokens + 15) / 16) * launch < 4.0f + (p.k_res ? 0.4f : 0.3f) * weights + gemm_dense_us(p, tokens, true);
+}
+
 static bool v6_tiles_fill(const Params &p, int tokens) { return tokens > 128 || (long long)((p.out_features + 127) / 128) * ((tokens + 127) / 128) >= 80; }
 
 // Whether the tile kernels would be a loss of precision: without a workspace these layers and token counts go through vq_gemv's kernels,
@@ -242,12 +251,13 @@ static size_t centroids_workspace_bytes(const Params &p, int tokens) {
 
 // Where this beats vq_gemv's kernels, sixteen rows at a time.  Estimates in microseconds: a launch of the row-wise v = 6 kernel 4 + 0.8 per
 // thousand columns and 0.07 per million weights, twice that and 1.5 with a residual table, 5 more with codebook groups (512 x 8200: 10.5;
-// 3000 x 2056: 6.4; 11008 x 4096: 10.5, four groups 15.5); of the others, above all those down the outputs, 5 and 0.32 per million
-// weights, 0.5 with a residual table (11008 x 4096: 19.6 and 28.8).
+// 3000 x 2056: 6.4; 11008 x 4096: 10.5, four groups 15.5); of the matrix-core kernel down the outputs that kernel's own; of the others 5 and
+// 0.32 per million weights, 0.5 with a residual table.
 static bool centroids_beat_rows(const Params &p, int tokens) {
   const float weights = (float)((double)p.out_features * p.in_features * 1e-6), matrices = p.k_res ? 2.0f : 1.0f;
   const float v6 = 4.0f + 0.8e-3f * (float)p.in_features + (p.k_res ? 1.5f + 0.14f * weights : 0.07f * weights) + (p.n_groups > 1 ? 5.0f : 0.0f);
-  const float launch = p.orientation == 0 && p.v == 6 ? v6 : 5.0f + (p.k_res ? 0.5f : 0.32f) * weights;
+  const float down = gemv_down_rows_us(p, nullptr, (p.in_features + 7) & ~7);
+  const float launch = p.orientation == 0 && p.v == 6 ? v6 : down > 0.0f ? down : 5.0f + (p.k_res ? 0.5f : 0.32f) * weights;
   const float restore = matrices * (6.0f + 0.33f * weights) + (p.n_out ? 5.0f : 0.0f) + 4.0f;
   return restore + matrices * gemm_dense_us(p, tokens) < (float)((tokens + 15) / 16) * launch;
 }
@@ -318,7 +328,7 @@ int launch_gemm_default(const Params &p, const __half *X, long long ldx, int tok
 //     is the paper's prompt-phase scheme; on gfx950 it beats restoring on the fly at every token count measured (17 to 2048),
 //     because tables are looked up once and not once for every token tile, and the restored matrix is read in full lines.
 //     Any layer the library can dequantize qualifies (in_features a multiple of 8).  It leaves to vq_gemv's kernels, sixteen rows
-//     at a time, what they do faster: row-wise v = 6 layers by the estimates above; layers of vq_gemv_rows.hip up to 32 tokens
+//     at a time, what they do faster: v = 6 layers by the estimates above; layers of vq_gemv_rows.hip up to 32 tokens
 //     (v = 12 with two tables, 8960 x 8192, 10 tokens: 22 against 121 us; v = 4, 8064 x 8448, 17 tokens: 34 against 73 us; level from
 //     33 on), 16 with codebook groups; others up to eight.
 //  2. no workspace, and a layer whose only tile kernel is the generic one: vq_gemv's kernels where that was measured faster.
@@ -364,6 +374,7 @@ int launch_gemm(const Params &p, const __half *X, long long ldx, int tokens, __h
   if (forced == '\0') {
     const bool fast_rows = gemv_has_fast_kernel(p, X, ldx), lds_rows = gemv_has_lds_kernel(p, X, ldx);
     if (p.orientation == 0 && p.v == 6 && fast_rows) rows = !have_ws || rows_beat_restoring(p, tokens);
+    else if (have_ws && p.orientation == 1 && tokens > 8 && down_rows_beat_restoring(p, X, ldx, tokens)) rows = true;
     else if (gemv_rows_applicable(p) && gemv_rows_takes(p, X, ldx, 16))
       rows = have_ws ? tokens <= (p.n_groups > 1 ? 16 : 32) : tokens <= 32 || !gemm_fused_applicable(p);
     else if (have_ws || gemm_fused_applicable(p)) rows = tokens <= (have_ws ? 8 : 16) && (fast_rows || lds_rows);

@@ -190,6 +190,14 @@ static bool down_mfma_parts_pay(const Params &p, int batch) {
   return down_mfma_us(p, gemv_down_mfma_parts(p)) < (batch <= 4 ? std::min(alone, down_streams_us(p, batch)) : alone);
 }
 
+// Estimated time in microseconds of up to sixteen rows on the matrix cores of that orientation with a workspace (the route rules of vq_gemm); 0 for
+// layers that do not go there.
+float gemv_down_rows_us(const Params &p, const __half *x, long long ldx) {
+  if (p.orientation != 1 || !down_mfma_wanted(p, x, ldx, 16)) return 0.0f;
+  const int parts = gemv_down_mfma_parts(p);
+  return 6.0f + std::min(down_mfma_us(p, 1), down_mfma_us(p, parts)) + (p.k_res ? 1.0f : 0.0f) + (p.Q ? 2.0f : 0.0f) + (p.n_groups > 1 ? 3.0f : 0.0f);
+}
+
 bool gemv_rows_applicable(const Params &p);
 bool gemv_rows_takes(const Params &p, const __half *x, long long ldx, int batch);
 int gemv_rows_parts(const Params &p);
