@@ -63,7 +63,10 @@ __device__ __forceinline__ float4v mfma16(uint4v a, uint4v b, float4v c) {
 // take one group (or the only one) and have no loop around the start-up (with the loop in every instantiation the
 // single-group ones lost up to 4 us on a 4096 x 4096 layer in 16 groups: registers held across the loop edge).
 // `wg` is the workgroup's number within its layer (a launch may hold the workgroups of several layers).
-template <int RES_BITS, bool WALK>
+// FEW: up to two tokens of a layer with a residual table: 48 permutes a window are more than those tokens are worth.  Operand A is the entry as it
+// is, operand B has (token, row) pairs for columns, the activation in place j of eight for row j and zeros elsewhere, and serves both tables: 16
+// instructions and 24 permutes a window (two rows, 384 x 18752 13.1 -> 12.6 us; a decoder layer's one row, 832 and 2752 wide, 33.9 -> 33.1).
+template <int RES_BITS, bool WALK, bool FEW>
 __device__ __forceinline__ void gemv_down_mfma_body(const Params &p, const DownMfmaPlan &plan, const __half *__restrict__ x, long long ldx,
                                                     __half *__restrict__ y, long long ldy, int wg) {
   typedef Layout<RES_BITS> LY;
@@ -76,6 +79,8 @@ __device__ __forceinline__ void gemv_down_mfma_body(const Params &p, const DownM
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 15, g = lane >> 4;                // A: stream n of the block, column group g.  B: token n.  D: token n, streams 4g..4g+3
+  constexpr int PLANES = FEW ? 1 : 6;                    // sums a lane holds of its four streams
+  const int token = FEW ? n / 6 : n;
   const int blk = wg / plan.ksplit, part_i = wg - blk * plan.ksplit;
   // A part belongs to one codebook group; without a workspace the workgroup walks all groups, one set of tables after the
   // other in LDS, and its sums simply keep running (the tables change with the column, the output rows do not).
@@ -98,10 +103,22 @@ __device__ __forceinline__ void gemv_down_mfma_body(const Params &p, const DownM
   const __amdgpu_buffer_rsrc_t r_main = make_rsrc(p.idx, (unsigned)p.S * st_main);
   const __amdgpu_buffer_rsrc_t r_res = make_rsrc(RES_BITS ? p.idx_res : p.idx, RES_BITS ? (unsigned)p.S * st_res : 0u);
   const __amdgpu_buffer_rsrc_t r_x = make_rsrc(x, plan.x_bytes);
-  float4v acc[6];                                        // output row j of every stream
+  float4v acc[PLANES];                                   // output row j of every stream (FEW: row n % 6)
   float xs = 0.0f;
 #pragma unroll
-  for (int j = 0; j < 6; ++j) acc[j] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
+  for (int j = 0; j < PLANES; ++j) acc[j] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
+  // FEW: byte selectors that move the low (even column) or high (odd column) half of an activation dword into half (j & 1) of dword (j >> 1) of
+  // the operand, zeros (selector byte 0x0c) everywhere else
+  unsigned sel[3][2];
+  if constexpr (FEW) {
+    const int j = n % 6;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const bool mine = d == (j >> 1);
+      sel[d][0] = !mine ? 0x0c0c0c0cu : (j & 1) ? 0x01000c0cu : 0x0c0c0100u;
+      sel[d][1] = !mine ? 0x0c0c0c0cu : (j & 1) ? 0x03020c0cu : 0x0c0c0302u;
+    }
+  }
 
   for (int grp = g_lo; grp < g_hi; ++grp) {
     // the group's stream positions [pos_lo, pos_hi) -- pos_lo a multiple of 8, a dword boundary of the streams -- and the
@@ -159,7 +176,7 @@ __device__ __forceinline__ void gemv_down_mfma_body(const Params &p, const DownM
 
     // byte offset of this lane's first activation of window 0; a token past the batch reads out of range, i.e. zeros
     const int col0 = p.n_out + pos_lo;                     // column of x that meets the part's window 0
-    const unsigned xoff = n < plan.batch ? (unsigned)(((long long)n * ldx + col0 + 8 * g) * 2) : 0x80000000u;
+    const unsigned xoff = token < plan.batch ? (unsigned)(((long long)token * ldx + col0 + 8 * g) * 2) : 0x80000000u;
 
     // a stream past the last one reads out of range: index 0, whose products land in rows that are never stored
     const unsigned srow_main = (unsigned)(blk * 16 + n) * st_main + (unsigned)(pos_lo >> 3) * 12u;
@@ -251,6 +268,16 @@ __device__ __forceinline__ void gemv_down_mfma_body(const Params &p, const DownM
           lds_gather_wait();
 #pragma unroll
           for (int u = 0; u < VPL; ++u) { settle(e[u]); if (RES_BITS) settle(f[u]); }
+          if constexpr (FEW) {
+#pragma unroll
+            for (int u = 0; u < VPL; ++u) {
+              const unsigned xd = xv[u >> 1];
+              const uint4v b = {__builtin_amdgcn_perm(xd, xd, sel[0][u & 1]), __builtin_amdgcn_perm(xd, xd, sel[1][u & 1]),
+                                __builtin_amdgcn_perm(xd, xd, sel[2][u & 1]), 0u};
+              acc[0] = mfma16(e[u], b, acc[0]);
+              if constexpr (RES_BITS != 0) acc[0] = mfma16(f[u], b, acc[0]);
+            }
+          } else
           // row j of the eight columns' entries, in the order of the columns: operand A against the token's activations as they are
 #pragma unroll
           for (int j = 0; j < 6; ++j) {
@@ -274,14 +301,14 @@ __device__ __forceinline__ void gemv_down_mfma_body(const Params &p, const DownM
   float4v *pbuf = reinterpret_cast<float4v *>(lds);                           // [6][MW][64]
   float *xsb = reinterpret_cast<float *>(lds + 6 * MW * 1024);                // [MW][16 tokens][4]
 #pragma unroll
-  for (int j = 0; j < 6; ++j) pbuf[(j * MW + wv) * 64 + lane] = acc[j];
-  xsb[(wv * 16 + n) * 4 + g] = xs;
+  for (int j = 0; j < PLANES; ++j) pbuf[(j * MW + wv) * 64 + lane] = acc[j];
+  if (!FEW || n % 6 == 0) xsb[(wv * 16 + token) * 4 + g] = xs;
   __syncthreads();
-  if (wv < 6) {                                          // wave j finishes row j
-    const int t = n, j = wv;
+  if (wv < PLANES) {                                     // wave j finishes row j
+    const int t = token, plane = wv, j = FEW ? n % 6 : wv;
     float4v s = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int w = 0; w < MW; ++w) s += pbuf[(j * MW + w) * 64 + lane];
+    for (int w = 0; w < MW; ++w) s += pbuf[(plane * MW + w) * 64 + lane];
     if (t < plan.batch) {
       float xsum = 0.0f;
       if (need_xs) {
@@ -313,10 +340,10 @@ __device__ __forceinline__ void gemv_down_mfma_body(const Params &p, const DownM
   }
 }
 
-template <int RES_BITS, bool WALK>
+template <int RES_BITS, bool WALK, bool FEW>
 __global__ __launch_bounds__(MW * 64) void gemv_down_mfma_kernel(Params p, DownMfmaPlan plan, const __half *__restrict__ x, long long ldx,
                                                                  __half *__restrict__ y, long long ldy) {
-  gemv_down_mfma_body<RES_BITS, WALK>(p, plan, x, ldx, y, ldy, (int)blockIdx.x);
+  gemv_down_mfma_body<RES_BITS, WALK, FEW>(p, plan, x, ldx, y, ldy, (int)blockIdx.x);
 }
 
 // Several layers that read the same activations (the query, key and value projections of a decoder layer; its gate and up
@@ -336,11 +363,11 @@ struct DownMultiArgs {
   DownMultiLayer layer[DMULTI_MAX];
 };
 
-template <int RES_BITS>
+template <int RES_BITS, bool FEW>
 __global__ __launch_bounds__(MW * 64) void gemv_down_mfma_multi_kernel(DownMultiArgs a, const __half *__restrict__ x, long long ldx) {
   int i = 0;
   while (i + 1 < a.n && (int)blockIdx.x >= a.first_wg[i + 1]) ++i;
-  gemv_down_mfma_body<RES_BITS, false>(a.layer[i].p, a.layer[i].plan, x, ldx, a.layer[i].y, a.layer[i].ldy, (int)blockIdx.x - a.first_wg[i]);
+  gemv_down_mfma_body<RES_BITS, false, FEW>(a.layer[i].p, a.layer[i].plan, x, ldx, a.layer[i].y, a.layer[i].ldy, (int)blockIdx.x - a.first_wg[i]);
 }
 
 
@@ -355,9 +382,9 @@ unsigned place_lds(const Params &p, DownMfmaPlan &plan) {
   return lds_bytes;
 }
 
-template <int RES_BITS>
+template <int RES_BITS, bool FEW>
 int launch_multi(DownMultiArgs &a, const __half *x, long long ldx, hipStream_t s) {
-  auto kernel = gemv_down_mfma_multi_kernel<RES_BITS>;
+  auto kernel = gemv_down_mfma_multi_kernel<RES_BITS, FEW>;
   VQ_ALLOW_FULL_LDS(kernel);
   unsigned lds_bytes = 0;
   for (int i = 0; i < a.n; ++i) {
@@ -369,10 +396,10 @@ int launch_multi(DownMultiArgs &a, const __half *x, long long ldx, hipStream_t s
   return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
 }
 
-template <int RES_BITS, bool WALK>
+template <int RES_BITS, bool WALK, bool FEW>
 int launch_one(const Params &p, DownMfmaPlan &plan, unsigned grid, const __half *x, long long ldx, __half *y, long long ldy,
                hipStream_t s) {
-  auto kernel = gemv_down_mfma_kernel<RES_BITS, WALK>;
+  auto kernel = gemv_down_mfma_kernel<RES_BITS, WALK, FEW>;
   VQ_ALLOW_FULL_LDS(kernel);
   const unsigned lds_bytes = place_lds<RES_BITS>(p, plan);
   if (lds_bytes > 160u * 1024u) return VQ_ERR_UNSUPPORTED;                  // too many outlier columns to hold beside the tables
@@ -442,7 +469,8 @@ int launch_gemv_down_mfma(const Params &p, const __half *x, long long ldx, int b
   const int rb = p.k_res ? p.bits_res : 0;
   const bool walk = !part && p.n_groups > 1;
 #define VQ_CASE(R) if (rb == R) \
-    return walk ? launch_one<R, true>(p, plan, (unsigned)grid, x, ldx, y, ldy, s) : launch_one<R, false>(p, plan, (unsigned)grid, x, ldx, y, ldy, s);
+    return batch <= 2 && R ? (walk ? launch_one<R, true, R != 0>(p, plan, (unsigned)grid, x, ldx, y, ldy, s) : launch_one<R, false, R != 0>(p, plan, (unsigned)grid, x, ldx, y, ldy, s)) \
+                           : (walk ? launch_one<R, true, false>(p, plan, (unsigned)grid, x, ldx, y, ldy, s) : launch_one<R, false, false>(p, plan, (unsigned)grid, x, ldx, y, ldy, s));
   VQ_CASE(0) VQ_CASE(8) VQ_CASE(12)
 #undef VQ_CASE
   return VQ_ERR_UNSUPPORTED;
@@ -469,7 +497,7 @@ int launch_gemv_down_mfma_multi(const Params *ps, int n, const __half *x, long l
     if (total > 0x7FFFFFFFLL) return VQ_ERR_UNSUPPORTED;
   }
   a.first_wg[n] = (int)total;
-#define VQ_CASE(R) if (rb == R) return launch_multi<R>(a, x, ldx, s);
+#define VQ_CASE(R) if (rb == R) return batch <= 2 && R ? launch_multi<R, R != 0>(a, x, ldx, s) : launch_multi<R, false>(a, x, ldx, s);
   VQ_CASE(0) VQ_CASE(8) VQ_CASE(12)
 #undef VQ_CASE
   return VQ_ERR_UNSUPPORTED;
