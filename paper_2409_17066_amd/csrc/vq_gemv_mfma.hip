@@ -30,6 +30,7 @@ namespace {
 
 using namespace v6;
 
+constexpr int MW = 8;            // waves per workgroup
 constexpr int NBMAX = 6;         // 16-row blocks per chunk
 constexpr int VPL = 8;           // vectors per lane per pass: 8 x 12 bits = 3 dwords, 8 x 8 bits = 2 dwords
 
@@ -71,7 +72,7 @@ __device__ __forceinline__ float4v mfma16(uint4v a, uint4v b, float4v c) {
 // a workgroup with a 12-bit residual table, where a chunk has two blocks and a group a pass or two: six loads are 4 to 16 % slower there at any
 // number of rows (eight groups, 9536 x 4352, one row 24.2 against 26.3 us, sixteen 26.8 against 29.4; 16 groups, 11008 x 4096 41 against 48; but a
 // workgroup that walks four groups, 16 rows: 38.6 against 36.3).
-template <int RES_BITS, int MW, int NB, bool GROUPED, bool DIRECT = false>
+template <int RES_BITS, int MW, int NB, bool GROUPED, bool DIRECT = false, bool PART = false>
 __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPlan &plan, const __half *__restrict__ x, long long ldx,
                                                   int batch, __half *__restrict__ y, long long ldy, int wg,
                                                   const GroupRange gr = GroupRange{0, 1, nullptr, nullptr}) {
@@ -136,14 +137,15 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
   if (g == 0) xs_part[wv * 16 + n] = 0.0f;
   int buf = 0;
 
-  const int grp_end = GROUPED ? gr.end : 1;
-  const bool partial = GROUPED && gr.part != nullptr;
-  for (int grp = GROUPED ? gr.begin : 0; grp < grp_end; ++grp) {
+  constexpr bool RANGE = GROUPED || PART;
+  const int grp_end = GROUPED ? gr.end : PART ? gr.begin + 1 : 1;
+  const bool partial = PART || (GROUPED && gr.part != nullptr);
+  for (int grp = RANGE ? gr.begin : 0; grp < grp_end; ++grp) {
   // ---- this codebook group's vectors [v_lo, v_lo + v_n) and columns [col_lo, col_hi) of every row
-  const int v_lo = GROUPED ? grp * p.Pg : 0;                                  // a multiple of 8: a dword boundary in the streams
-  const int v_n = GROUPED ? min(p.Pg, p.P - v_lo) : p.P;
+  const int v_lo = RANGE ? grp * p.Pg : 0;                                  // a multiple of 8: a dword boundary in the streams
+  const int v_n = RANGE ? min(p.Pg, p.P - v_lo) : p.P;
   const int col_lo = p.n_out + v_lo * 6;
-  const int col_hi = GROUPED ? min(p.in_features, col_lo + v_n * 6) : p.in_features;
+  const int col_hi = RANGE ? min(p.in_features, col_lo + v_n * 6) : p.in_features;
   const unsigned gb_main = (unsigned)(v_lo >> 3) * 12u, gb_res = (unsigned)(v_lo >> 3) * (RES_BITS == 8 ? 8u : 12u);
   // passes in which this wave has vectors: a prefix 0 .. my_passes-1 (pass p: group p * MW + wv of 32 vectors)
   const int wave_groups = (v_n + 31) >> 5;
@@ -215,7 +217,7 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
     // in registers through the main loop for the next group)
     unsigned tid = threadIdx.x;
     if (GROUPED) asm volatile("" : "+v"(tid));
-    tables.issue(p, grp, grp == 0 && !plan.out_global, tid);
+    tables.issue(p, PART ? 0 : grp, grp == 0 && !plan.out_global, tid);
 #pragma unroll
     for (int j = 0; j < PA; ++j) {
 #pragma unroll
@@ -227,7 +229,7 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
     tables.store(p, lds, plan.lds_out, grp == 0 && !plan.out_global, tid);
   }
   // scale and bias of the workgroup's rows, one dword per row, for the reductions at the chunk ends
-  for (int r = (int)threadIdx.x; r < (grp == (GROUPED ? gr.begin : 0) && !partial ? plan.rows_per_wg : 0); r += MW * 64) {
+  for (int r = (int)threadIdx.x; r < (grp == (RANGE ? gr.begin : 0) && !partial ? plan.rows_per_wg : 0); r += MW * 64) {
     const unsigned short sc = (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(r_scale, (unsigned)(row0 + r) * 2u, 0, 0);
     const unsigned short bi = (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(r_bias, (unsigned)(row0 + r) * 2u, 0, 0);
     *reinterpret_cast<unsigned *>(lds + plan.lds_sb + (unsigned)r * 4u) = (unsigned)sc | ((unsigned)bi << 16);
@@ -473,6 +475,15 @@ __global__ __launch_bounds__(MW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
                                                   GroupRange{grp, grp + 1, part + (long long)grp * batch * p.out_features, part_xs});
 }
 
+// A layer of one table and few blocks of rows, the caller's workspace lent: every workgroup takes a part of the columns and so many more blocks.
+template <int RES_BITS, int NB>
+__global__ __launch_bounds__(MW * 64) void gemv_v6_mfma_parts_kernel(Params p, MfmaPlan plan, const __half *__restrict__ x, long long ldx, int batch,
+                                                                     float *__restrict__ part, float *__restrict__ part_xs, int wgs_per_part) {
+  warm_kernel_arguments();
+  const int i = (int)blockIdx.x / wgs_per_part, wg = (int)blockIdx.x - i * wgs_per_part;
+  gemv_v6_mfma_body<RES_BITS, MW, NB, false, false, true>(p, plan, x, ldx, batch, nullptr, 0, wg, GroupRange{i, i + 1, part + (long long)i * batch * p.out_features, part_xs});
+}
+
 // y[t][o] = fp16(scale[o] * sum_g part[g][t][o] + bias[o] * sum_g part_xs[g][t]), groups in ascending order.
 // The sums were written by other compute units a moment ago and come from beyond this one's caches: the loads of
 // FINISH_AHEAD groups are issued together (a group past the last repeats the last and is not added), the additions
@@ -548,10 +559,6 @@ int launch_one(const Params &p, const MfmaPlan &plan, unsigned lds_bytes, unsign
   return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
 }
 
-#ifndef VQ_MFMA_WAVES
-#define VQ_MFMA_WAVES 8
-#endif
-constexpr int MW = VQ_MFMA_WAVES;
 constexpr int NARROW_WAVES = 4;            // workgroup size for layers whose codebook groups are narrow (see narrow_groups)
 
 }  // namespace
@@ -571,7 +578,7 @@ struct Planned {
 // `waves` and `lds_cap`: the workgroup's size and its share of the compute unit's LDS (the defaults: one workgroup of
 // MW waves per compute unit).
 int make_plan(const Params &p, int batch, long long ldx, const __half *y, long long ldy, int blocks_per_wg, int nb_force, Planned *out,
-              bool partial = false, int waves = MW, unsigned lds_cap = 160u * 1024u) {
+              bool partial = false, int waves = MW, unsigned lds_cap = 160u * 1024u, bool column_parts = false) {
   MfmaPlan plan{};
   if (p.in_features < 64) return VQ_ERR_UNSUPPORTED;      // idle lanes load the first 100 bytes of the first activation row
   const int rb = p.k_res ? p.bits_res : 0;
@@ -584,7 +591,7 @@ int make_plan(const Params &p, int batch, long long ldx, const __half *y, long l
   plan.rows_per_wg = blocks_per_wg * 16;
   out->grid = (unsigned)((blocks_total + blocks_per_wg - 1) / blocks_per_wg);
   plan.lds_sb = off; off += partial ? 0u : (unsigned)plan.rows_per_wg * 4u;
-  const bool grouped = p.n_groups > 1;
+  const bool grouped = p.n_groups > 1 && !column_parts;
   if (grouped && (p.Pg & 7)) return VQ_ERR_UNSUPPORTED;   // a group must start on a dword of the 12- and 8-bit streams
   plan.lds_yacc = off; off += grouped && !partial ? (unsigned)blocks_per_wg * 1024u : 0u;
   plan.lds_part = off;
@@ -671,16 +678,64 @@ int launch_gemv_mfma(const Params &p, const __half *x, long long ldx, int batch,
   return VQ_ERR_UNSUPPORTED;
 }
 
-// Bytes of the workspace with which a layer with codebook groups runs as "one group per workgroup, then add up"; 0 when
-// that route does not apply (one group, group size not a multiple of 8 vectors, more groups than compute units).
+// Parts that the columns of a layer of one table are cut into with a workspace; 1: none.  A workgroup of a part has as many times the
+// blocks of rows, which share its activations, and the last of them leave fewer compute units idle; the second launch costs 2 to 3 us.  In vectors of a
+// row, with / without parts:
+//  * up to half more blocks than compute units, from 1500 on (5120 x 13824, 3 / 16 rows 13.5 / 15.8 us, 18.1 / 22.5; with residual tables 21.0 /
+//    23.4, 24.1 / 30.2; 5120 x 8192: 11.3 / 10.2), and up to twice as many from 3500 on (8192 x 28672 24.6 / 25.9, 28.6 / 36.4; with a residual table
+//    only for more than eight rows: 44.6 / 47.9, three rows level);
+//  * a quarter as many blocks, from 2000 on (512 x 16384, three rows 9.3 / 10.5, sixteen 11.4 / 18.9, with residual tables 11.2 / 14.9, 12.7 /
+//    21.1), for more than eight rows from 1300 on (1024 x 8192, sixteen 9.5 / 11.3; eight 9.0 / 8.5);
+//  * without a residual table, twelve rows or more, from 1700 on (4096 x 11008, sixteen 13.3 / 15.2; 4096 x 14336, twelve 13.7 / 15.6, eight level;
+//    with residual tables 18.4 / 17.7).
+static int column_parts(const Params &p, int batch) {
+  const int blocks = (p.out_features + 15) / 16, cus = cu_count();
+  if (p.n_groups > 1 || batch < 3) return 1;
+  if (blocks > cus) return (2 * blocks <= 3 * cus && p.P >= 1500) || (blocks <= 2 * cus && p.P >= 3500 && batch >= (p.k_res ? 9 : 3)) ? 2 : 1;
+  if (4 * blocks <= cus && p.P >= (batch > 8 ? 1300 : 2000)) return 4;
+  return !p.k_res && batch >= 12 && p.P >= 1700 ? 4 : 1;
+}
+// vectors of a part: whole steps of the workgroup's waves, as far as that leaves every part some
+static int part_vectors(const Params &p, int parts) { return ((p.P + parts - 1) / parts + 31) / 32 * 32; }
+
+// Bytes of the workspace with which a layer with codebook groups runs as "one group per workgroup, then add up", or one of a single group in
+// parts of the columns; 0 when neither applies (group size not a multiple of 8 vectors, more groups than compute units).
 size_t gemv_mfma_groups_workspace_bytes(const Params &p, int batch) {
-  if (p.n_groups < 2 || (p.Pg & 7) || p.n_groups > cu_count()) return 0;
-  return ((size_t)p.n_groups * ((size_t)batch * (size_t)p.out_features + 16) * sizeof(float) + 255) / 256 * 256;
+  const int parts = p.n_groups > 1 ? p.n_groups : column_parts(p, batch);
+  if (parts < 2 || (p.n_groups > 1 && (p.Pg & 7)) || parts > cu_count()) return 0;
+  return ((size_t)parts * ((size_t)batch * (size_t)p.out_features + 16) * sizeof(float) + 255) / 256 * 256;
+}
+
+// One table, parts of the columns: a workgroup takes a part of them and so many more blocks of rows.
+static int launch_column_parts(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, void *workspace, hipStream_t s) {
+  const int parts = column_parts(p, batch), blocks_total = (p.out_features + 15) / 16, wgs_per_part = cu_count() / parts;
+  if (parts < 2 || wgs_per_part < 1) return VQ_ERR_UNSUPPORTED;
+  Params q = p;
+  q.Pg = part_vectors(p, parts);
+  q.n_groups = (p.P + q.Pg - 1) / q.Pg;
+  Planned pl;
+  const int rc = make_plan(q, batch, ldx, y, ldy, (blocks_total + wgs_per_part - 1) / wgs_per_part, 0, &pl, true, MW, 160u * 1024u, true);
+  if (rc != VQ_OK) return rc;
+  float *part = static_cast<float *>(workspace), *part_xs = part + (size_t)q.n_groups * (size_t)batch * (size_t)p.out_features;
+#define VQ_CASE(RBITS, NBLK)                                                                                                              \
+  if (pl.rb == RBITS && pl.plan.nb == NBLK) {                                                                                             \
+    auto kernel = gemv_v6_mfma_parts_kernel<RBITS, NBLK>;                                                                                 \
+    VQ_ALLOW_FULL_LDS(kernel);                                                                                                            \
+    hipLaunchKernelGGL(kernel, dim3(pl.grid * (unsigned)q.n_groups), dim3(MW * 64), pl.lds_bytes, s, q, pl.plan, x, ldx, batch, part, part_xs, (int)pl.grid); \
+    launch_finish(part, part_xs, q.n_groups, batch, p, y, ldy, s);                                                                        \
+    return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;                                                                          \
+  }
+  VQ_CASE(0, 1) VQ_CASE(0, 2) VQ_CASE(0, 3) VQ_CASE(0, 4) VQ_CASE(0, 5) VQ_CASE(0, 6)
+  VQ_CASE(8, 1) VQ_CASE(8, 2) VQ_CASE(8, 3) VQ_CASE(8, 4) VQ_CASE(8, 5)
+  VQ_CASE(12, 1) VQ_CASE(12, 2) VQ_CASE(12, 3) VQ_CASE(12, 4) VQ_CASE(12, 5)
+#undef VQ_CASE
+  return VQ_ERR_UNSUPPORTED;
 }
 
 // The caller has checked gemv_fast_applicable() and that the workspace holds gemv_mfma_groups_workspace_bytes().
 int launch_gemv_mfma_groups(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, void *workspace,
                             hipStream_t s) {
+  if (p.n_groups == 1) return launch_column_parts(p, x, ldx, batch, y, ldy, workspace, s);
   const int blocks_total = (p.out_features + 15) / 16;
   bool narrow = narrow_groups(p) && 2 * cu_count() / p.n_groups >= 1;
   Planned pl;

@@ -997,3 +997,24 @@ def test_gemv_down_routes(gpu_lib, out_features, in_features, k_res, batch):
         torch.cuda.synchronize()
         _check_matmul(y, ref, "batch %d" % batch)
     assert (ws[need:] == 0xFF).all()
+
+
+@pytest.mark.parametrize("out_features,in_features,more,batch", [
+    (4115, 9008, {}, 3), (4115, 9402, dict(k_res=4096), 16), (500, 12140, dict(k_res=256, n_outlier_cols=120, v_out=4, k_out=4096), 5),
+    (1001, 7900, dict(k_res=4096, n_outlier_cols=8, v_out=4, k_out=4096), 9), (1100, 10300, {}, 13), (17, 12011 * 2, dict(permute=True), 3),
+])
+def test_gemv_column_parts(gpu_lib, out_features, in_features, more, batch):
+    """Rows of v = 6 vectors in parts of the columns, added up by a second kernel: parts that end within a step of the waves, a last block of few
+    rows, outlier columns with the first part, columns gathered first."""
+    import torch
+    L = s.make_layer(316, "parts", out_features, in_features, 6, 4096, **more)
+    dl = gpu_lib.DeviceLayer(L)
+    need = gpu_lib.vq_gemv_workspace_bytes(dl.desc, batch)
+    assert need >= 2 * (batch * out_features + 16) * 4
+    x_np = s.make_activations(316, L, batch)
+    x = torch.from_numpy(x_np).cuda()
+    ws = torch.full((need + 256,), 0xFF, dtype=torch.uint8, device="cuda")
+    y = gpu_lib.gemv(dl, x, workspace=ws[:need])
+    torch.cuda.synchronize()
+    _check_matmul(y, oracle.gemv(L, x_np), "batch %d" % batch)
+    assert (ws[need:] == 0xFF).all() and (ws[:need] != 0xFF).any()
