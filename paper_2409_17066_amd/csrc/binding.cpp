@@ -98,7 +98,8 @@ void *borrow(at::TensorBase &scratch, size_t bytes) {
 
 // Whether gemv() without a workspace borrows one: not for layers with codebook groups, nor for v = 6 / 12-bit layers in stored order:
 // their kernels without one are good, and sum in the same order with gemv_multi() or a workspace that is too small.
-bool lends_workspace(const vq_layer_desc &d) { return !d.group_vectors && (d.v != 6 || d.k <= 2048 || d.col_perm); }
+// But for rows of an odd width, which those kernels take from a copy.
+bool lends_workspace(const vq_layer_desc &d) { return (!d.group_vectors && (d.v != 6 || d.k <= 2048 || d.col_perm)) || (d.v == 6 && (d.in_features & 1)); }
 
 // gemv(layer, x, out or None, workspace or None)
 PyObject *gemv(PyObject *, PyObject *const *args, Py_ssize_t n) {

@@ -128,6 +128,7 @@ int launch_gemv_res8(const Params &p, const __half *x, __half *y, hipStream_t s)
 int launch_gemv_fast(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, hipStream_t s);
 
 int launch_gemv_mfma(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, hipStream_t s);
+bool gemv_fast_applicable_even(const Params &p);
 bool gemv_down_applicable(const Params &p, const __half *x, long long ldx);
 bool gemv_down_fits(const Params &p);
 bool gemv_v8_applicable(const Params &p, const __half *x, long long ldx);
@@ -179,7 +180,14 @@ static bool down_mfma_parts_wanted(const Params &p, const __half *x, long long l
 }
 static bool down_mfma_alone_wanted(const Params &p, const __half *x, long long ldx, int batch) {
   if (!down_mfma_wanted(p, x, ldx, batch)) return false;
-  if (p.n_groups > 1) return true;                        // the only fast kernel of this orientation that walks codebook groups by itself
+  if (p.n_groups > 1) {
+    // groups that a workgroup walks: for one row the kernel that keeps one table in LDS at a time is the other one, which pays more for a
+    // group and spreads its streams (four groups, 11008 x 4096 16.7 against 19.1 us, 4096 x 4096 16.7 / 16.0, 4096 x 11008 25.7 / 21.7; sixteen
+    // 45.3 / 50.7)
+    const float groups = (float)p.n_groups * (p.k_res ? 2.0f : 1.0f), vectors = (float)p.S * (float)p.P * 1e-6f;
+    return batch >= 2 || forced_kernel() == 'm' || !gemv_down_lds_applicable(p, 1) ||
+           1.55f * groups + down_mfma_us(p, 1) < 2.5f * groups + (p.k_res ? 1.3f : 0.65f) * vectors;
+  }
   return batch >= 5 || forced_kernel() == 'm' || down_mfma_us(p, 1) < down_streams_us(p, batch);      // (of five rows and more a launch of four is one of two)
 }
 // Whether parts of the columns, which a workspace is there for, are worth the second launch (300 x 1000, two rows 8.5 -> 6.1 us, four 8.1 -> 6.2;
@@ -416,7 +424,29 @@ static bool permuted_in_kernel(const Params &p, const __half *x, long long ldx, 
 // Rows of an odd width start between dwords for all but the first: the kernel that wants dwords has them copied, which costs 2 us
 // (v = 12, 305 x 1281, 2 rows: 10.4 us, 11.1 with the copy).  (The copy counts as workspace, and of rows beyond 2^18 columns it could ask
 // for more than vq_gemv_static_workspace has, which would refuse a layer that needs none.)
-static bool rows_gathered(const Params &p, int batch) { return batch >= 5 && (p.in_features & 1) && p.in_features < (1 << 18) && rows_wanted(p, batch, true); }
+// The v = 6 / 12-bit kernels want dwords at any number of rows, those along the rows an even width as well: there the copy's next column, zeros,
+// counts as the layer's last (P is the same: an odd width is short of whole vectors).  3520 x 6587, 1 / 4 / 16 rows: 9.7 -> 7.9, 18.3 -> 9.2, 71 -> 11.2 us;
+// down the outputs, 4 / 16 rows 21.5 -> 12.0, 82 -> 14.2.
+static bool even_width_wanted(const Params &p) { return p.orientation == 0 && (p.in_features & 1) && gemv_fast_applicable_even(p); }
+static size_t stored_order_workspace_bytes(const Params &p, const __half *x, long long ldx, int batch, bool least);
+static Params gathered(const Params &p) {
+  Params q = p;
+  q.perm = nullptr;
+  if (even_width_wanted(p)) ++q.in_features;
+  return q;
+}
+// (of 2^17 vectors and more, which take longer than the copy; and not where the copy and the sums are more than vq_gemv_static_workspace has)
+static bool rows_gathered(const Params &p, int batch) {
+  if (!(p.in_features & 1) || p.in_features >= (1 << 18) || forced_kernel() != '\0') return false;
+  if (batch >= 5 && rows_wanted(p, batch, true)) return true;
+  if ((long long)p.S * p.P < 1 << 17 || !((even_width_wanted(p) && (batch >= 2 || p.n_groups == 1)) || (batch >= 2 && down_mfma_wanted(p, nullptr, p.in_features + 1, batch)))) return false;
+  return permuted_x_bytes(p, batch) + stored_order_workspace_bytes(gathered(p), nullptr, (p.in_features + 7) & ~7, batch, false) <= VQ_GEMV_STATIC_WORKSPACE_BYTES;
+}
+// ... unless the rows can be taken as they are
+static bool taken_as_they_are(const Params &p, const __half *x, long long ldx, int batch) {
+  if (even_width_wanted(p)) return false;
+  return down_mfma_wanted(p, nullptr, p.in_features + 1, batch) ? down_mfma_wanted(p, x, ldx, batch) : gemv_rows_takes(p, x, ldx, batch);
+}
 
 size_t gemv_products_workspace_bytes(const Params &p, int batch);
 int launch_gemv_products(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, void *workspace, size_t workspace_bytes,
@@ -450,8 +480,7 @@ static size_t workspace_bytes_of(const Params &p, const __half *x, long long ldx
   if (force_generic()) return 0;
   if (p.perm || rows_gathered(p, batch)) {
     if (p.perm && permuted_in_kernel(p, x, ldx, batch)) return 0;
-    Params q = p;
-    q.perm = nullptr;
+    const Params q = gathered(p);
     const size_t head = permuted_x_bytes(p, batch), rest = stored_order_workspace_bytes(q, nullptr, (p.in_features + 7) & ~7, batch, least);
     // (the column parts of vq_gemv_rows.hip are done without where the two together are more than vq_gemv_static_workspace has)
     return rows_wanted(q, batch, true) && head + rest > VQ_GEMV_STATIC_WORKSPACE_BYTES ? head : head + rest;
@@ -481,11 +510,10 @@ size_t gemv_workspace_bytes(const Params &p, const __half *x, long long ldx, int
 static int launch_with_workspace(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, void *workspace,
                                  size_t workspace_bytes, bool least, hipStream_t s) {
   const size_t need = workspace_bytes_of(p, x, ldx, batch, least);
-  if (p.perm || (rows_gathered(p, batch) && !gemv_rows_takes(p, x, ldx, batch))) {
+  if (p.perm || (rows_gathered(p, batch) && !taken_as_they_are(p, x, ldx, batch))) {
     if (!need || !workspace || workspace_bytes < need) return launch_gemv(p, x, ldx, batch, y, ldy, s);
     // gather the activations into stored order, then the layer is an unpermuted one
-    Params q = p;
-    q.perm = nullptr;
+    const Params q = gathered(p);
     __half *xp = static_cast<__half *>(workspace);
     const long long ldxp = (p.in_features + 7) & ~7;
     // (in one launch of the LDS-table kernel the workgroups gather theirs by themselves: a group's columns, in the shade of its table)

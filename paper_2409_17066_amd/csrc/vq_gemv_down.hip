@@ -159,12 +159,14 @@ __global__ __launch_bounds__(DW * 64) void gemv_down_v6_kernel(Params p, DownPla
 #pragma unroll
     for (int t = 0; t < B; ++t) {
       const __half *xt = x + (long long)t * ldx + col0;                      // stream position n is column col0 + n
-      const bool wide = (col0 & 7) == 0;                                     // then the 16-byte pieces are aligned (x is, on the host's word)
+      // (rows that begin anywhere: pieces of sixteen bytes at any half)
+      typedef unsigned uint4h __attribute__((ext_vector_type(4), aligned(2)));
       float sum = 0.0f;
       for (int c = (int)threadIdx.x * 8; c < plan.passes * 512; c += DW * 64 * 8) {
         uint4v val = {0u, 0u, 0u, 0u};
-        if (wide && c + 8 <= p.P) {
-          val = *reinterpret_cast<const uint4v *>(xt + c);
+        if (c + 8 <= p.P) {
+          const uint4h piece = *reinterpret_cast<const uint4h *>(xt + c);
+          val = uint4v{piece.x, piece.y, piece.z, piece.w};
         } else if (c < p.P) {
           unsigned short h[8];
 #pragma unroll
@@ -367,7 +369,6 @@ bool gemv_down_applicable(const Params &p, const __half *x, long long ldx) {
   if (p.orientation != 1 || p.v != 6 || p.bits != 12) return false;
   if (p.n_groups > 1 && (p.Pg & 7)) return false;        // a group starts on a dword of the index streams (and needs a workspace)
   if (p.k_res && p.bits_res != 12 && p.bits_res != 8) return false;
-  if ((reinterpret_cast<uintptr_t>(x) & 15) || (ldx & 7)) return false;
   const long long max_stride = p.stride > p.stride_res ? p.stride : p.stride_res;
   return (long long)p.S * max_stride < (1LL << 31);                          // 32-bit buffer offsets
 }

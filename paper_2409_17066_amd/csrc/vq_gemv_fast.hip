@@ -427,6 +427,13 @@ bool gemv_fast_applicable(const Params &p, const __half *x, long long ldx) {
   return true;
 }
 
+// The same of a layer whose odd width is made even by a column of zeros.
+bool gemv_fast_applicable_even(const Params &p) {
+  Params q = p;
+  ++q.in_features;
+  return gemv_fast_applicable(q, nullptr, q.in_features);
+}
+
 // Vectors per lane the kernels are built for, by batch group and residual use (register budget of 128).
 static bool u_allowed(int U, int batch, bool res) {
   if (batch == 1) return res ? (U == 4 || U == 5 || U == 6) : (U == 4 || U == 5 || U == 6 || U == 8);

@@ -1018,3 +1018,29 @@ def test_gemv_column_parts(gpu_lib, out_features, in_features, more, batch):
     torch.cuda.synchronize()
     _check_matmul(y, oracle.gemv(L, x_np), "batch %d" % batch)
     assert (ws[need:] == 0xFF).all() and (ws[:need] != 0xFF).any()
+
+
+@pytest.mark.parametrize("out_features,in_features,more", [
+    (1030, 1203, {}), (700, 1801, dict(k_res=4096)), (640, 1403, dict(k_res=256, n_outlier_cols=16, v_out=4, k_out=4096)), (1300, 1211, dict(group_vectors=48)),
+    (770, 1201, dict(permute=True)), (1030, 1206, dict(orientation=1)), (6000, 901, dict(orientation=1, k_res=4096)),
+    (4000, 1202, dict(orientation=1, k_res=256, n_outlier_cols=10, v_out=4, k_out=4096)), (4000, 1203, dict(orientation=1, n_outlier_cols=9, v_out=4, k_out=4096)),
+    (4004, 1205, dict(orientation=1, group_vectors=304)),
+])
+@pytest.mark.parametrize("batch", [1, 2, 5, 16])
+def test_gemv_rows_of_any_width(gpu_lib, out_features, in_features, more, batch):
+    """v = 6 / 12-bit layers of widths that are no multiples of eight, rows that begin at any half: taken as they are or from a copy."""
+    import torch
+    L = s.make_layer(317, "width", out_features, in_features, 6, 4096, **more)
+    dl = gpu_lib.DeviceLayer(L)
+    x_np = s.make_activations(317, L, batch)
+    ref = oracle.gemv(L, x_np)
+    need = gpu_lib.vq_gemv_workspace_bytes(dl.desc, batch)
+    ws = torch.full((need + 256,), 0xFF, dtype=torch.uint8, device="cuda")
+    for pitch, offset in ((in_features, 0), (in_features + 3, 1)):
+        x = torch.full((batch * pitch + 8,), float("nan"), dtype=torch.float16, device="cuda")
+        rows = x[offset: offset + batch * pitch].view(batch, pitch)[:, :in_features]
+        rows.copy_(torch.from_numpy(x_np))
+        for y in (gpu_lib.gemv(dl, rows, workspace=ws[:need] if need else None), gpu_lib.gemv(dl, rows)):
+            torch.cuda.synchronize()
+            _check_matmul(y, ref, "batch %d, pitch %d" % (batch, pitch))
+    assert (ws[need:] == 0xFF).all()
