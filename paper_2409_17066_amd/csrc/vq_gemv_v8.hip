@@ -34,10 +34,33 @@ template <int BYTES> __device__ __forceinline__ unsigned load_idx(const uint8_t 
 
 constexpr int WAVES = 4, CHAINS = 4;
 
+// Eight activations from column c on, of a row that begins at any half; zeros past the row's end.
+__device__ __forceinline__ half8v activations(const __half *row, int c, int columns) {
+  typedef _Float16 half8h __attribute__((ext_vector_type(8), aligned(2)));
+  half8v v = {0, 0, 0, 0, 0, 0, 0, 0};
+  if (c + 8 <= columns) {
+    const half8h w = *reinterpret_cast<const half8h *>(row + c);
+    v = half8v{w[0], w[1], w[2], w[3], w[4], w[5], w[6], w[7]};
+  } else {
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (c + j < columns) v[j] = __builtin_bit_cast(_Float16, row[c + j]);
+  }
+  return v;
+}
+// The first `n` elements of an entry: what the row's cut-off last vector drops may be no number.
+__device__ __forceinline__ half8v first_of(const half8v &e, int n) {
+  half8v v;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) v[j] = j < n ? e[j] : (_Float16)0;
+  return v;
+}
+
 // B rows of x; IB / RB: bytes per main / residual index (RB = 0: no residual table); R output rows per wave.  With
 // R = 2 a wave walks two rows at once, CHAINS / 2 chains each: as many gathers in flight, but every activation it
 // loads serves both rows -- x is otherwise re-read once per output row, which is what four and more tokens pay for.
-template <int B, int IB, int RB, int R>
+// ANY: x at any half, and a last vector that the row cuts off (in every instantiation they cost 2 to 12 %: 1024 x 4096, two rows 5.6 -> 6.3 us).
+template <int B, int IB, int RB, int R, bool ANY>
 __global__ __launch_bounds__(WAVES * 64) void gemv_v8_kernel(Params p, const __half *__restrict__ x, long long ldx, __half *__restrict__ y,
                                                              long long ldy) {
   constexpr int NC = CHAINS / R;
@@ -53,6 +76,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_v8_kernel(Params p, const __h
   }
   const half8v ones = {1, 1, 1, 1, 1, 1, 1, 1}, zeros = {0, 0, 0, 0, 0, 0, 0, 0};
   const bool with_bias = p.bias != nullptr;
+  const int cut = p.in_features & 7;              // elements of a cut-off last vector
   float acc[R][B], xs[B];
 #pragma unroll
   for (int t = 0; t < B; ++t) {
@@ -83,13 +107,17 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_v8_kernel(Params p, const __h
       for (int q = 0; q < R; ++q) {
         e[u][q] = *reinterpret_cast<const half8v *>(p.cb + (group * p.k + min(i[u][q], (unsigned)p.k - 1u)) * 8);
         if (RB) f[u][q] = *reinterpret_cast<const half8v *>(p.cb_res + (group * p.k_res + min(r[u][q], (unsigned)p.k_res - 1u)) * 8);
+        if (ANY && cut && pvc[u] == p.P - 1) {
+          e[u][q] = first_of(e[u][q], cut);
+          if (RB) f[u][q] = first_of(f[u][q], cut);
+        }
       }
     }
 #pragma unroll
     for (int u = 0; u < NC; ++u) {
 #pragma unroll
       for (int t = 0; t < B; ++t) {
-        half8v xv = *reinterpret_cast<const half8v *>(x + (long long)t * ldx + (long long)pvc[u] * 8);
+        half8v xv = ANY ? activations(x + (long long)t * ldx, pvc[u] * 8, p.in_features) : *reinterpret_cast<const half8v *>(x + (long long)t * ldx + (long long)pvc[u] * 8);
         if (!on[u]) xv = zeros;
 #pragma unroll
         for (int q = 0; q < R; ++q) {
@@ -115,9 +143,9 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_v8_kernel(Params p, const __h
   }
 }
 
-template <int B, int IB, int RB, int R>
+template <int B, int IB, int RB, int R, bool ANY>
 int launch_rows(const Params &p, const __half *x, long long ldx, __half *y, long long ldy, hipStream_t s) {
-  hipLaunchKernelGGL((gemv_v8_kernel<B, IB, RB, R>), dim3((unsigned)((p.out_features + WAVES * R - 1) / (WAVES * R))), dim3(WAVES * 64), 0, s, p, x, ldx,
+  hipLaunchKernelGGL((gemv_v8_kernel<B, IB, RB, R, ANY>), dim3((unsigned)((p.out_features + WAVES * R - 1) / (WAVES * R))), dim3(WAVES * 64), 0, s, p, x, ldx,
                      y, ldy);
   return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
 }
@@ -126,8 +154,9 @@ int launch_rows(const Params &p, const __half *x, long long ldx, __half *y, long
 // waves (batch 8: 8192 x 8192 74 -> 66 us, 8192 x 28672 242 -> 203 us; 4096 x 4096 would go from 22.3 to 23.5 us).
 template <int B, int IB, int RB>
 int launch_one(const Params &p, const __half *x, long long ldx, __half *y, long long ldy, hipStream_t s) {
-  if (B >= 4 && p.in_features >= 8192) return launch_rows<B, IB, RB, (B >= 4 ? 2 : 1)>(p, x, ldx, y, ldy, s);
-  return launch_rows<B, IB, RB, 1>(p, x, ldx, y, ldy, s);
+  if ((p.in_features & 7) || (reinterpret_cast<uintptr_t>(x) & 15) || (ldx & 7)) return launch_rows<B, IB, RB, 1, true>(p, x, ldx, y, ldy, s);
+  if (B >= 4 && p.in_features >= 8192) return launch_rows<B, IB, RB, (B >= 4 ? 2 : 1), false>(p, x, ldx, y, ldy, s);
+  return launch_rows<B, IB, RB, 1, false>(p, x, ldx, y, ldy, s);
 }
 
 // The same for layers stored with vectors down the output dimension (Sec. 3.1, Algorithm 1: W[8s + j][c] =
@@ -220,12 +249,11 @@ int index_bytes(int bits) { return bits == 8 ? 1 : bits == 16 ? 2 : 0; }
 
 }  // namespace
 
-// Row-wise layers of 8-component vectors with byte-aligned indices, no outlier columns, whole vectors only; x rows
-// 16-byte aligned.  (The tables are 16-byte aligned by the descriptor's rules; an index row by its 16-byte stride.)
+// Row-wise layers of 8-component vectors with byte-aligned indices, no outlier columns.  (Of any width, x at any half: 3520 x 6586, one row 107
+// us on the generic kernel, 22.  The tables are 16-byte aligned by the descriptor's rules; an index row by its 16-byte stride.)
 bool gemv_v8_applicable(const Params &p, const __half *x, long long ldx) {
-  if (p.orientation != 0 || p.v != 8 || p.Q != 0 || p.n_out != 0 || (p.in_features & 7)) return false;
+  if (p.orientation != 0 || p.v != 8 || p.Q != 0 || p.n_out != 0) return false;
   if (!index_bytes(p.bits) || (p.k_res && !index_bytes(p.bits_res))) return false;
-  if ((reinterpret_cast<uintptr_t>(x) & 15) || (ldx & 7)) return false;
   if ((reinterpret_cast<uintptr_t>(p.cb) & 15) || (p.k_res && (reinterpret_cast<uintptr_t>(p.cb_res) & 15))) return false;
   return (p.stride & 1) == 0 && (!p.k_res || (p.stride_res & 1) == 0);
 }

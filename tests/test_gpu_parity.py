@@ -1044,3 +1044,20 @@ def test_gemv_rows_of_any_width(gpu_lib, out_features, in_features, more, batch)
             torch.cuda.synchronize()
             _check_matmul(y, ref, "batch %d, pitch %d" % (batch, pitch))
     assert (ws[need:] == 0xFF).all()
+
+
+@pytest.mark.parametrize("in_features,k,k_res,group_vectors", [(9, 65536, 0, 0), (1203, 65536, 300, 0), (1030, 200, 65536, 31), (2051, 256, 256, 0)])
+@pytest.mark.parametrize("batch", [1, 2, 5])
+def test_gemv_v8_rows_of_any_width(gpu_lib, in_features, k, k_res, group_vectors, batch):
+    """Vectors of eight along rows of any width that begin at any half."""
+    import torch
+    L = s.make_layer(318, "v8", 70, in_features, 8, k, k_res, group_vectors=group_vectors)
+    dl = gpu_lib.DeviceLayer(L)
+    x_np = s.make_activations(318, L, batch)
+    for pitch, offset in ((in_features, 0), (in_features + 3, 1)):
+        x = torch.full((batch * pitch + 8,), float("nan"), dtype=torch.float16, device="cuda")
+        rows = x[offset: offset + batch * pitch].view(batch, pitch)[:, :in_features]
+        rows.copy_(torch.from_numpy(x_np))
+        y = gpu_lib.gemv(dl, rows)
+        torch.cuda.synchronize()
+        _check_matmul(y, oracle.gemv(L, x_np), "batch %d, pitch %d" % (batch, pitch))
