@@ -647,6 +647,26 @@ def test_gemv_permuted_columns_with_workspace(gpu_lib, name, batch):
     _check_matmul(plain, ref, "%s batch %d" % (name, batch))
 
 
+@pytest.mark.parametrize("orientation", [0, 1])
+@pytest.mark.parametrize("pitch", [0, 3])
+@pytest.mark.parametrize("out_features,in_features", [(1023, 1030), (1024, 6), (1025, 1031), (1026, 8), (1027, 4096), (1030, 10240), (1030, 10241), (2048, 33)])
+def test_dequant_moves_columns_of_several_rows(gpu_lib, out_features, in_features, pitch, orientation):
+    """Permuted columns of one row to a workgroup and of four, a last one of fewer, rows at any half, columns past the last eight: bit for bit
+    what the layer restores in stored order, at its columns; nothing beyond them."""
+    import copy
+    import torch
+    L = s.make_layer(8300, "moved", out_features, in_features, 6, 300, orientation=orientation, permute=True)
+    stored = copy.copy(L)
+    stored.col_perm = None
+    want = gpu_lib.dequant(gpu_lib.DeviceLayer(stored))
+    dl = gpu_lib.DeviceLayer(L)
+    W = torch.full((out_features, in_features + pitch), -3.5, dtype=torch.float16, device="cuda")
+    assert gpu_lib.vq_dequant(dl.desc, W.data_ptr(), W.stride(0), torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(W[:, torch.from_numpy(np.asarray(L.col_perm)).long().cuda()].view(torch.int16), want.view(torch.int16))
+    assert (W[:, in_features:] == -3.5).all()
+
+
 @pytest.mark.parametrize("name", PERMUTED)
 def test_dequant_permuted_columns_by_the_scattering_kernels(gpu_lib, monkeypatch, name):
     """The generic kernels, which store every value at its column themselves (rows too long for LDS take them)."""
