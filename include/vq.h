@@ -249,7 +249,8 @@ int vq_quantize_columns(void *W, int64_t ldw, int32_t rows, int32_t cols, const 
  *    else VQ_ERR_WORKSPACE;
  *  - if it holds vq_gemm_fast_workspace_bytes(desc, tokens) bytes (non-zero when in_features is a
  *    multiple of 8), the call restores W into it once (as vq_dequant does, rounded to binary16) and multiplies from there,
- *    which is the faster route on this GPU; with less, the restored weights go straight from
+ *    which is the faster route on this GPU (up to 8 MiB of it, behind W, take the partial sums of products with few
+ *    outputs and tokens; with W's out_features * in_features * 2 bytes alone they are not cut); with less, the restored weights go straight from
  *    on-chip tiles into the matrix cores and W is never written to memory (kernels of their own for
  *    v = 8 / 16-bit indices, gathered from L2, and for v = 6 / 12-bit indices with one codebook group
  *    and outlier columns in multiples of 16, whose tables sit in LDS; other layers restore through the

@@ -169,10 +169,17 @@ float gemm_dense_us(const Params &p, int tokens, bool against_rows = false);
 // rows of in_features rounded up to 8 halfs, the whole rounded up to 256 bytes; every kernel then works in stored order.
 static size_t permuted_x_bytes(const Params &p, int tokens) { return ((size_t)tokens * (size_t)((p.in_features + 7) & ~7) * sizeof(__half) + 255) / 256 * 256; }
 
+// Behind the restored matrix: the partial sums of a product whose columns are cut into parts (vq_gemm_dense.hip), the same for any number of
+// tokens, so that a workspace for many serves few.  Without this part a product is not cut; 8 MiB hold what 512 tiles of 64 x 64 leave, two for
+// every compute unit.  Up to 512 columns there is nothing to gain (eight steps), nor above 8192 outputs, whose tiles of 64 tokens keep half the compute
+// units busy already (43 tokens, 8461 x 6912: 52.9 us whole, 53.8 in parts; 88 tokens, 5696 x 9472: 55.4 and 55.8).
+static size_t restored_bytes(const Params &p) { return ((size_t)p.out_features * (size_t)p.in_features * sizeof(__half) + 255) / 256 * 256; }
+static size_t dense_scratch_bytes(const Params &p) { return p.in_features > 512 && p.out_features <= 8192 ? (size_t)8 << 20 : 0; }
+
 size_t gemm_fast_workspace_bytes(const Params &p, int tokens) {
   const size_t head = p.perm ? permuted_x_bytes(p, tokens) : 0;
   if (!gemm_dense_applicable(p)) return head;
-  return head + (size_t)p.out_features * (size_t)p.in_features * sizeof(__half);
+  return head + restored_bytes(p) + dense_scratch_bytes(p);
 }
 
 bool gemm_fused_applicable(const Params &p);
@@ -183,7 +190,7 @@ bool gemm_v6_applicable(const Params &p);
 int launch_gemm_v6(const Params &p, const __half *X, long long ldx, int tokens, __half *Y, long long ldy, hipStream_t s);
 int launch_gemm_fused(const Params &p, const __half *X, long long ldx, int tokens, __half *Y, long long ldy, hipStream_t s);
 int launch_gemm_dense(const Params &p, const __half *X, long long ldx, int tokens, __half *Y, long long ldy, const __half *Wd,
-                      long long ldw, hipStream_t s, const float *xsum = nullptr, unsigned w2 = 0);
+                      long long ldw, hipStream_t s, const float *xsum = nullptr, unsigned w2 = 0, void *scratch = nullptr, size_t scratch_bytes = 0);
 
 // Row-wise v = 6 layers have the matrix-core GEMV, whose sixteen rows cost little more than one: it still beats restoring the
 // matrix for the first sixteens of tokens.  Estimates in microseconds from 130 random layers: a launch of it 5 + 1.2 per thousand
@@ -244,9 +251,8 @@ __global__ __launch_bounds__(256) void row_sums_kernel(const __half *__restrict_
   if (lane == 0) sums[t] = sum;
 }
 
-static size_t matrix_bytes(const Params &p) { return ((size_t)p.out_features * (size_t)p.in_features * sizeof(__half) + 255) / 256 * 256; }
 static size_t centroids_workspace_bytes(const Params &p, int tokens) {
-  return matrix_bytes(p) * (p.k_res ? 2 : 1) + ((size_t)tokens * sizeof(float) + 255) / 256 * 256;
+  return restored_bytes(p) * (p.k_res ? 2 : 1) + ((size_t)tokens * sizeof(float) + 255) / 256 * 256;
 }
 
 // Where this beats vq_gemv's kernels, sixteen rows at a time.  Estimates in microseconds: a launch of the row-wise v = 6 kernel 4 + 0.8 per
@@ -272,8 +278,8 @@ static bool centroids_wanted(const Params &p, int tokens) {
 }
 
 static int launch_gemm_centroids(const Params &p, const __half *X, long long ldx, int tokens, __half *Y, long long ldy, void *workspace, hipStream_t s) {
-  __half *C = static_cast<__half *>(workspace), *R = C + matrix_bytes(p) / sizeof(__half);
-  float *xsum = reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + matrix_bytes(p) * (p.k_res ? 2 : 1));
+  __half *C = static_cast<__half *>(workspace), *R = C + restored_bytes(p) / sizeof(__half);
+  float *xsum = reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + restored_bytes(p) * (p.k_res ? 2 : 1));
   // (the residual matrix has no outlier columns of its own)
   const int clear = p.k_res ? p.n_out : 0, clear_wgs = !clear ? 0 : p.out_features < 4096 ? p.out_features : 4096;
   hipLaunchKernelGGL(row_sums_kernel, dim3((unsigned)((tokens + 3) / 4 + clear_wgs)), dim3(256), 0, s, X, ldx, tokens, p.in_features, xsum, R,
@@ -288,7 +294,7 @@ static int launch_gemm_centroids(const Params &p, const __half *X, long long ldx
     q.cb_out = nullptr; q.idx_out = nullptr; q.Q = q.S_out = 0;
     rc = launch_dequant(q, R, p.in_features, s, tokens);
   }
-  return rc == VQ_OK ? launch_gemm_dense(p, X, ldx, tokens, Y, ldy, C, p.in_features, s, xsum, p.k_res ? (unsigned)matrix_bytes(p) : 0u) : rc;
+  return rc == VQ_OK ? launch_gemm_dense(p, X, ldx, tokens, Y, ldy, C, p.in_features, s, xsum, p.k_res ? (unsigned)restored_bytes(p) : 0u) : rc;
 }
 
 // Rows of X through vq_gemv, sixteen at a time, with the workspace if it is aligned for that (vq_gemv cuts the columns into parts with it).
@@ -310,6 +316,8 @@ size_t gemm_default_workspace_bytes(const Params &p, int tokens) {
   if (centroids_wanted(p, tokens)) return centroids_workspace_bytes(p, tokens);
   const size_t bytes = rows_hold_the_weights(p, tokens) ? gemv_workspace_bytes(p, nullptr, (p.in_features + 7) & ~7, tokens < 16 ? tokens : 16)
                                                         : gemm_fast_workspace_bytes(p, tokens);
+  if (bytes > MOST_DEFAULT_WORKSPACE && !rows_hold_the_weights(p, tokens) && gemm_dense_applicable(p) && bytes - dense_scratch_bytes(p) <= MOST_DEFAULT_WORKSPACE)
+    return bytes - dense_scratch_bytes(p);
   return bytes <= MOST_DEFAULT_WORKSPACE ? bytes : 0;
 }
 
@@ -364,7 +372,8 @@ int launch_gemm(const Params &p, const __half *X, long long ldx, int tokens, __h
     return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
   }
   const char forced = switches().gemm;
-  const size_t fast = gemm_fast_workspace_bytes(p, tokens);
+  // (a workspace of the restored matrix alone is enough for this route)
+  const size_t fast = gemm_dense_applicable(p) ? (size_t)p.out_features * (size_t)p.in_features * sizeof(__half) : 0;
   const bool have_ws = fast && workspace && workspace_bytes >= fast && (reinterpret_cast<uintptr_t>(workspace) & 15) == 0;
   if (gemm_v6_applicable(p) && (forced == '6' || (forced == '\0' && !have_ws && tokens > 64 && v6_tiles_fill(p, tokens)))) {
     const int rc = launch_gemm_v6(p, X, ldx, tokens, Y, ldy, s);
@@ -383,8 +392,9 @@ int launch_gemm(const Params &p, const __half *X, long long ldx, int tokens, __h
   if (rows) return launch_gemm_rows(p, X, ldx, tokens, Y, ldy, have_ws ? workspace : nullptr, have_ws ? workspace_bytes : 0, s);
   if (forced != 'g' && forced != 'f' && have_ws) {
     __half *Wd = static_cast<__half *>(workspace);
+    const size_t matrix = restored_bytes(p), room = workspace_bytes > matrix ? std::min(workspace_bytes - matrix, dense_scratch_bytes(p)) : 0;
     int rc = launch_dequant(p, Wd, p.in_features, s, tokens);
-    if (rc == VQ_OK) rc = launch_gemm_dense(p, X, ldx, tokens, Y, ldy, Wd, p.in_features, s);
+    if (rc == VQ_OK) rc = launch_gemm_dense(p, X, ldx, tokens, Y, ldy, Wd, p.in_features, s, nullptr, 0u, room ? Wd + matrix / sizeof(__half) : nullptr, room);
     if (rc != VQ_ERR_UNSUPPORTED) return rc;
   }
   if (forced != 'g' && gemm_fused_applicable(p)) {

@@ -12,7 +12,9 @@
 // matrix cores busy about 90% of the clocks, so energy counts: the 16x16x32 instruction in place of 32x32x16 took 219 -> 197 us at
 // the same traffic (1395 TFLOP/s); before, issuing reads and copies between the products instead of ahead of them 250 -> 221 us
 // (a wave that has its SIMD to itself issues nothing else meanwhile).  Deeper stages or other placements of the reads changed
-// nothing.  The smaller tiles are bound by LDS traffic per product and, with few workgroups, by the latency of a step.
+// nothing.  The smaller tiles are bound by LDS traffic per product and, with few workgroups, by the latency of a step: 0.19 us for 64 x 64,
+// so 16 such tiles of 8448 columns took 32 us on 16 compute units.  Then the columns are cut into parts (SPLIT), a workgroup to a tile and part,
+// whose binary32 sums a second kernel adds up in their order: 704 x 8448, 64 tokens, with the restoring 38.8 -> 19.6 us.
 #include "vq_gemm_tiles.hpp"
 #include <algorithm>
 #include <type_traits>
@@ -35,6 +37,9 @@ struct DenseArgs {
   unsigned w2;
   const __half *scale, *bias;
   const float *xsum;
+  // SPLIT: a workgroup takes `per` steps of the columns, of which there are `parts`, and leaves its sums in partial[part][token][channel]
+  float *partial;
+  int parts, per;
 };
 
 constexpr int DBK = 64;                                                  // columns per step: 128-byte rows in LDS
@@ -61,7 +66,7 @@ template <int N, class F> __device__ __forceinline__ void static_for(F &&f) { st
 
 __device__ __forceinline__ void keep_in_agprs(float4v &v) { asm volatile("" : "+a"(v)); }
 
-template <int MB, int NB, int NST, bool CENTROIDS>
+template <int MB, int NB, int NST, bool CENTROIDS, bool SPLIT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(dense_workgroups<MB, NB, NST>(), dense_workgroups<MB, NB, NST>())))
 void gemm_dense_kernel(DenseArgs a) {
   constexpr int TM = 64 * MB, TN = 64 * NB, PX = 2 * MB, PER = 2 * (MB + NB);      // copies of a wave and step: PX of the X tile, PER in all
@@ -72,10 +77,11 @@ void gemm_dense_kernel(DenseArgs a) {
   const int wm = (wave >> 1) * (32 * MB), wn = (wave & 1) * (32 * NB);
   // Workgroups go round robin over the eight XCDs, each with an L2 of its own: an XCD takes a run of tiles, token tiles first,
   // whose W rows it then fetches once
-  const int tiles = a.gx * a.gy, run = (tiles + 7) / 8, tile = (int)(blockIdx.x & 7) * run + (int)(blockIdx.x >> 3);
-  if (tile >= tiles) return;
+  const int tiles = a.gx * a.gy * (SPLIT ? a.parts : 1), run = (tiles + 7) / 8, item = (int)(blockIdx.x & 7) * run + (int)(blockIdx.x >> 3);
+  if (item >= tiles) return;
+  const int part = SPLIT ? item / (a.gx * a.gy) : 0, tile = SPLIT ? item - part * (a.gx * a.gy) : item;
   const int n0 = tile / a.gy * TN, m0 = tile % a.gy * TM;
-  const int wsteps = (a.in_features + DBK - 1) / DBK, ksteps = CENTROIDS && a.w2 ? 2 * wsteps : wsteps;
+  const int wsteps = (a.in_features + DBK - 1) / DBK, first = SPLIT ? part * a.per : 0, ksteps = SPLIT ? min(first + a.per, wsteps) : CENTROIDS && a.w2 ? 2 * wsteps : wsteps;
   // range-checked against the end of the last row: rows past the matrix read zeros
   const __amdgpu_buffer_rsrc_t r_x = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<__half *>(a.X), 0, (unsigned)(((long long)(a.tokens - 1) * a.ldx + a.in_features) * 2), 0x00020000);
@@ -94,7 +100,8 @@ void gemm_dense_kernel(DenseArgs a) {
   }
   // byte offset of a step's columns; chunks past the last column, and the steps past the last one, go past the end of the
   // buffers (which end below 2 GiB: see the launcher), where copies read zeros and fetch nothing
-  const int steps_even = (a.in_features - (int)even * 8 + DBK - 1) / DBK, steps_odd = (a.in_features - (int)(even ^ 4u) * 8 + DBK - 1) / DBK;
+  int steps_even = (a.in_features - (int)even * 8 + DBK - 1) / DBK, steps_odd = (a.in_features - (int)(even ^ 4u) * 8 + DBK - 1) / DBK;
+  if constexpr (SPLIT) { steps_even = min(steps_even, ksteps); steps_odd = min(steps_odd, ksteps); }
   auto copy_piece = [&](int i, unsigned stage, unsigned step_even, unsigned step_odd, unsigned second) {
     unsigned char *to = smem + stage + (i < PX ? (unsigned)(wave * PX + i) * 1024u : XTILE + (unsigned)(wave * (PER - PX) + i - PX) * 1024u);
     copy16(i < PX ? r_x : r_w, to, from[i] + (i & 1 ? step_odd : step_even) + (CENTROIDS && i >= PX ? second : 0u));
@@ -159,7 +166,7 @@ void gemm_dense_kernel(DenseArgs a) {
   // own by count (PER per step), the barrier covers the others'.
   static_for<NST>([&](auto index) {
     constexpr int j = decltype(index)::value;
-    int kt = j;
+    int kt = first + j;
     const unsigned second = second_of(kt);
     const unsigned step_even = kt < steps_even ? (unsigned)kt * ROW : 0x80000000u, step_odd = kt < steps_odd ? (unsigned)kt * ROW : 0x80000000u;
     static_for<PER>([&](auto piece) { copy_piece(decltype(piece)::value, j * STAGE, step_even, step_odd, second); });
@@ -174,7 +181,7 @@ void gemm_dense_kernel(DenseArgs a) {
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   operands_in(a0, b0);
   unsigned stage = 0;
-  for (int kt = 0; kt < ksteps; ++kt) {
+  for (int kt = first; kt < ksteps; ++kt) {
     const unsigned next = stage + STAGE == NST * STAGE ? 0u : stage + STAGE;
     half_step(std::false_type{}, a0, b0, half1 + stage, a1, b1, 0u, 0);
     // this wave's copies of step kt + 1 are in when no more are out than those of the steps after it
@@ -198,6 +205,21 @@ void gemm_dense_kernel(DenseArgs a) {
   // ---- store: a lane holds channel (lane & 15) of four tokens of block (i, c).  Range-checked 2-byte buffer stores with 32-bit
   // offsets: rows past the last token fall off the end of the buffer, channels past the last one are sent there on purpose.
   // (8-byte stores of four channels of a token, from the transposed product, were slower: 16 rows a store instead of 4.)
+  if constexpr (SPLIT) {
+    const __amdgpu_buffer_rsrc_t r_p = __builtin_amdgcn_make_buffer_rsrc(a.partial + (long long)part * a.tokens * a.out_features, 0,
+                                                                        (unsigned)a.tokens * (unsigned)a.out_features * 4u, 0x00020000);
+    const unsigned ldp4 = (unsigned)a.out_features * 4u, p_lane = (unsigned)(m0 + wm + 4 * (lane >> 4)) * ldp4 + (unsigned)(n0 + wn + (lane & 15)) * 4u;
+#pragma unroll
+    for (int i = 0; i < AB; ++i)
+#pragma unroll
+      for (int c = 0; c < BB; ++c) {
+        const bool on = n0 + wn + c * 16 + (lane & 15) < a.out_features;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[i][c][r]), r_p, on ? p_lane + (unsigned)(i * 16 + r) * ldp4 + (unsigned)(c * 64) : 0xFFFFFFF0u, 0, 0);
+      }
+    return;
+  }
   const __amdgpu_buffer_rsrc_t r_y = __builtin_amdgcn_make_buffer_rsrc(a.Y, 0, (unsigned)(((long long)(a.tokens - 1) * a.ldy + a.out_features) * 2), 0x00020000);
   const unsigned ldy2 = (unsigned)a.ldy * 2u;
   const unsigned y_lane = (unsigned)(m0 + wm + 4 * (lane >> 4)) * ldy2 + (unsigned)(n0 + wn + (lane & 15)) * 2u;
@@ -243,17 +265,29 @@ void gemm_dense_kernel(DenseArgs a) {
   }
 }
 
-template <int MB, int NB, int NST, bool CENTROIDS>
+// The parts' sums, in the order of the columns, a thread to a channel of a token.
+__global__ __launch_bounds__(256) void gemm_dense_finish_kernel(DenseArgs a) {
+  const int n = a.tokens * a.out_features, at = (int)blockIdx.x * 256 + (int)threadIdx.x;
+  if (at >= n) return;
+  float sum = 0.0f;
+#pragma unroll 8
+  for (int i = 0; i < a.parts; ++i) sum += a.partial[(long long)i * n + at];
+  const int t = at / a.out_features;
+  a.Y[t * a.ldy + (at - t * a.out_features)] = __float2half_rn(sum);
+}
+
+template <int MB, int NB, int NST, bool CENTROIDS, bool SPLIT = false>
 int launch_tiles(DenseArgs a, hipStream_t s) {
-  if constexpr (!CENTROIDS) if (a.xsum) return launch_tiles<MB, NB, NST, true>(a, s);
-  auto kernel = gemm_dense_kernel<MB, NB, NST, CENTROIDS>;
+  if constexpr (!CENTROIDS && !SPLIT) if (a.xsum) return launch_tiles<MB, NB, NST, true>(a, s);
+  auto kernel = gemm_dense_kernel<MB, NB, NST, CENTROIDS, SPLIT>;
   VQ_ALLOW_FULL_LDS(kernel);
   a.gx = (a.out_features + 64 * NB - 1) / (64 * NB);
   a.gy = (a.tokens + 64 * MB - 1) / (64 * MB);
-  const long long tiles = (long long)a.gx * a.gy;
+  const long long tiles = (long long)a.gx * a.gy * (SPLIT ? a.parts : 1);
   if (tiles > (1 << 24)) return VQ_ERR_UNSUPPORTED;
   constexpr unsigned lds = dense_lds<MB, NB, NST>();
   hipLaunchKernelGGL(kernel, dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(256), lds, s, a);
+  if constexpr (SPLIT) hipLaunchKernelGGL(gemm_dense_finish_kernel, dim3((unsigned)((a.tokens * a.out_features + 255) / 256)), dim3(256), 0, s, a);
   return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
 }
 
@@ -274,19 +308,21 @@ struct TileKind {
   float round, step[2];
   int (*launch)(DenseArgs, hipStream_t);
   bool later = false, cached = false;              // cached: only where W is in the caches
+  int (*split)(DenseArgs, hipStream_t) = nullptr;  // the columns in parts
 };
 const TileKind kTiles[] = {
     {4, 4, 1, 9.9f, {1.12f, 0.0f}, launch_tiles<4, 4, 2, false>},  {2, 4, 1, 5.3f, {0.755f, 0.0f}, launch_tiles<2, 4, 3, false>, true},
     {3, 3, 1, 6.2f, {0.752f, 0.0f}, launch_tiles<3, 3, 3, false>, true}, {3, 2, 1, 5.3f, {0.545f, 0.0f}, launch_tiles<3, 2, 3, false>, true},
     {1, 3, 1, 4.0f, {0.375f, 0.0f}, launch_tiles<1, 3, 3, false>, true, true}, {4, 3, 1, 7.6f, {0.90f, 0.0f}, launch_tiles<4, 3, 2, false>},
-    {2, 2, 1, 4.2f, {0.383f, 0.0f}, launch_tiles<2, 2, 3, false>}, {1, 3, 2, 2.1f, {0.478f, 0.767f}, launch_tiles<1, 3, 2, false>},
-    {1, 2, 2, 2.3f, {0.273f, 0.558f}, launch_tiles<1, 2, 3, false>}, {1, 1, 2, 1.2f, {0.190f, 0.384f}, launch_tiles<1, 1, 4, false>},
+    {2, 2, 1, 4.2f, {0.383f, 0.0f}, launch_tiles<2, 2, 3, false>, false, false, launch_tiles<2, 2, 3, false, true>}, {1, 3, 2, 2.1f, {0.478f, 0.767f}, launch_tiles<1, 3, 2, false>},
+    {1, 2, 2, 2.3f, {0.273f, 0.558f}, launch_tiles<1, 2, 3, false>, false, false, launch_tiles<1, 2, 3, false, true>},
+    {1, 1, 2, 1.2f, {0.190f, 0.384f}, launch_tiles<1, 1, 4, false>, false, false, launch_tiles<1, 1, 4, false, true>},
 };
 
-float tile_cost(const TileKind &t, int tokens, int out_features, int in_features, int cus) {
-  const long long tiles = (long long)((tokens + 64 * t.mb - 1) / (64 * t.mb)) * ((out_features + 64 * t.nb - 1) / (64 * t.nb));
+float tile_cost(const TileKind &t, int tokens, int out_features, int in_features, int cus, int parts = 1) {
+  const long long tiles = (long long)((tokens + 64 * t.mb - 1) / (64 * t.mb)) * ((out_features + 64 * t.nb - 1) / (64 * t.nb)) * parts;
   const long long most = (tiles + cus - 1) / cus, rounds = most / t.per_cu, rest = most % t.per_cu;
-  const float steps = (float)((in_features + DBK - 1) / DBK);
+  const float steps = (float)(((in_features + DBK - 1) / DBK + parts - 1) / parts);
   return (float)rounds * (t.round + steps * t.step[t.per_cu - 1]) + (rest ? t.round + steps * t.step[rest - 1] : 0.0f);
 }
 
@@ -295,10 +331,11 @@ float tile_cost(const TileKind &t, int tokens, int out_features, int in_features
 bool dequant_leaves_cached(const Params &p, int product_tokens, int matrices);
 bool gemm_dense_applicable(const Params &p) { return p.in_features % 8 == 0; }       // (16-byte chunks of W's rows)
 
-// The tile shape with the least estimated time.  Switch dense=0 / =n: always the last one / number n of the list, for tests.  With xsum, the
+// The tile shape with the least estimated time, and with `scratch` (16-byte aligned, for the sums) the parts of the columns.  Switch
+// dense=0 / =n: always the last one / number n of the list and whole columns, for tests.  With xsum, the
 // sums of X's rows: W holds the layer's centroids (w2 bytes behind it those of the residual table), see DenseArgs.
 int launch_gemm_dense(const Params &p, const __half *X, long long ldx, int tokens, __half *Y, long long ldy, const __half *Wd, long long ldw, hipStream_t s,
-                      const float *xsum, unsigned w2) {
+                      const float *xsum, unsigned w2, void *scratch, size_t scratch_bytes) {
   if (!gemm_dense_applicable(p)) return VQ_ERR_UNSUPPORTED;
   // Buffer offsets have 32 bits and the copies of missing chunks start 2 GiB up, so one launch covers at most 2 GiB of X and of W
   // and 4 GiB of Y (with room for a tile of rows past the end); more goes in several.
@@ -307,6 +344,7 @@ int launch_gemm_dense(const Params &p, const __half *X, long long ldx, int token
   if (most_tokens < 1 || most_out < 1) return VQ_ERR_UNSUPPORTED;
   const int force = switches().dense;
   const bool cached = dequant_leaves_cached(p, tokens, w2 ? 2 : 1);
+  const int wsteps = (p.in_features + DBK - 1) / DBK;
   for (long long o = 0; o < p.out_features; o += most_out)
     for (long long t = 0; t < tokens; t += most_tokens) {
       const int nt = (int)std::min<long long>(most_tokens, tokens - t), no = (int)std::min<long long>(most_out, p.out_features - o);
@@ -315,8 +353,27 @@ int launch_gemm_dense(const Params &p, const __half *X, long long ldx, int token
       if (force < 0)
         for (const TileKind &k : kTiles)
           if ((cached || !k.cached) && tile_cost(k, nt, no, p.in_features, cu_count()) < tile_cost(*best, nt, no, p.in_features, cu_count())) best = &k;
-      const int rc = best->launch({X + t * ldx, ldx, nt, Wd + o * ldw, ldw, no, p.in_features, Y + t * ldy + o, ldy, 0, 0, w2,
-                                   p.scale ? p.scale + o : nullptr, p.bias ? p.bias + o : nullptr, xsum ? xsum + t : nullptr}, s);
+      DenseArgs a = {X + t * ldx, ldx, nt, Wd + o * ldw, ldw, no, p.in_features, Y + t * ldy + o, ldy, 0, 0, w2,
+                     p.scale ? p.scale + o : nullptr, p.bias ? p.bias + o : nullptr, xsum ? xsum + t : nullptr, static_cast<float *>(scratch), 1, wsteps};
+      // The columns in parts, by the same estimates, where that saves 1 us and more: 3 us for the second launch, and the parts' way through
+      // the caches at 5 TB/s.  (Of 150 random calls of 17 to 1555 tokens 49 are cut, which takes 25 % off the whole vq_gemm in the geometric mean
+      // and makes none slower by more than 2 %: v = 6, 78 tokens, 624 x 10752 45.9 -> 21.8 us, 64 of 1024 x 4096 22.4 -> 15.5, of 4096 x 4096
+      // 32.1 -> 20.9; v = 12, 145 of 3200 x 6632 56.0 -> 43.3; 88 of 5696 x 9472 55.4 -> 55.8.)
+      const TileKind *split = nullptr;
+      const size_t part_bytes = (size_t)nt * (size_t)no * sizeof(float);
+      if (scratch && !xsum && force < 0 && part_bytes * 2 <= scratch_bytes) {
+        float least = tile_cost(*best, nt, no, p.in_features, cu_count()) - 1.0f;
+        for (const TileKind &k : kTiles) {
+          if (!k.split) continue;
+          for (int n : {2, 3, 4, 6, 8, 12, 16, 24, 32}) {
+            if (n > wsteps / 2 || part_bytes * (size_t)n > scratch_bytes) break;
+            const int per = (wsteps + n - 1) / n, parts = (wsteps + per - 1) / per;
+            const float us = tile_cost(k, nt, no, p.in_features, cu_count(), parts) + 3.0f + (float)((double)part_bytes * 2 * parts / 5e6);
+            if (us < least) { least = us; split = &k; a.parts = parts; a.per = per; }
+          }
+        }
+      }
+      const int rc = split ? split->split(a, s) : best->launch(a, s);
       if (rc != VQ_OK) return rc;
     }
   return VQ_OK;

@@ -97,6 +97,35 @@ def test_gemm_small(gpu_lib, monkeypatch, name, tokens, workspace):
     _check_matmul(Y, oracle.gemm(L, x), "%s tokens %d workspace %s" % (name, tokens, workspace))
 
 
+@pytest.mark.parametrize("tokens,out_features,in_features,more", [
+    (33, 64, 1544, {}), (65, 130, 2056, dict(permute=True)), (17, 67, 3400, dict(k_res=200)), (129, 1000, 4104, dict(orientation=1)),
+    (326, 977, 5296, {}), (385, 2482, 7192, {}), (40, 300, 520, {}), (64, 512, 512, {}),
+])
+def test_gemm_columns_in_parts(gpu_lib, tokens, out_features, in_features, more):
+    """Products of few tiles and many columns, the columns cut into parts of whole steps, the last one ragged (64 x 64, 64 x 128 and 128 x 128 tiles; the
+    last two shapes are not cut); with room for the restored matrix alone they are not.  Workspace filled with NaN patterns, guarded behind."""
+    import torch
+    L = s.make_layer(8400, "parts", out_features, in_features, 8, 300, **more)
+    dl = gpu_lib.DeviceLayer(L)
+    x = s.make_activations(8400, L, tokens)
+    X = torch.full((tokens, in_features + 8), float("nan"), dtype=torch.float16, device="cuda")
+    X[:, :in_features] = torch.from_numpy(x).cuda()
+    need = gpu_lib.vq_gemm_fast_workspace_bytes(dl.desc, tokens)
+    assert need <= gpu_lib.vq_gemm_fast_workspace_bytes(dl.desc, 4 * tokens)      # (the workspace of more tokens does for fewer)
+    matrix = (tokens * in_features * 2 + 255) // 256 * 256 * bool(more.get("permute")) + out_features * in_features * 2
+    rows = np.unique(np.linspace(0, out_features - 1, 130).astype(np.int32))
+    ref = oracle.gemm(L, x, rows=rows)
+    ws = torch.full((need + 256,), 0xFF, dtype=torch.uint8, device="cuda")
+    stream = torch.cuda.current_stream().cuda_stream
+    for size in (need, matrix):
+        ws[:] = 0xFF
+        Y = torch.full((tokens, out_features + 3), 7.0, dtype=torch.float16, device="cuda")
+        assert gpu_lib.vq_gemm(dl.desc, X.data_ptr(), X.stride(0), tokens, Y.data_ptr(), Y.stride(0), ws.data_ptr(), size, stream) == 0
+        torch.cuda.synchronize()
+        _check_matmul(Y[:, torch.from_numpy(rows.astype(np.int64)).cuda()], ref, "%d tokens, workspace of %d bytes" % (tokens, size))
+        assert torch.isfinite(Y).all() and (Y[:, out_features:] == 7.0).all() and (ws[size:] == 0xFF).all()
+
+
 DENSE_SHAPES = [(1, 1, 8), (17, 300, 520), (64, 64, 64), (65, 129, 120), (128, 192, 192), (191, 257, 1032), (256, 256, 128), (300, 513, 136), (513, 768, 320)]
 
 
