@@ -270,6 +270,11 @@ static bool centroids_beat_rows(const Params &p, int tokens) {
 
 constexpr size_t MOST_DEFAULT_WORKSPACE = (size_t)256 << 20;
 
+// `bytes` and the sums of a product in parts behind them, or without these `bytes`, or nothing.
+static size_t default_bytes(const Params &p, size_t bytes) {
+  return bytes > MOST_DEFAULT_WORKSPACE ? 0 : bytes + dense_scratch_bytes(p) <= MOST_DEFAULT_WORKSPACE ? bytes + dense_scratch_bytes(p) : bytes;
+}
+
 static bool centroids_wanted(const Params &p, int tokens) {
   // (vq_dequant's kernel for few vectors of eight down the outputs takes no outlier columns, so it may not see such a layer without them)
   if (!gemm_dense_applicable(p) || p.perm || (p.k_res && p.bits_res == 16) || centroids_workspace_bytes(p, tokens) > MOST_DEFAULT_WORKSPACE) return false;
@@ -277,7 +282,8 @@ static bool centroids_wanted(const Params &p, int tokens) {
   return rows_hold_the_weights(p, tokens) && centroids_beat_rows(p, tokens);
 }
 
-static int launch_gemm_centroids(const Params &p, const __half *X, long long ldx, int tokens, __half *Y, long long ldy, void *workspace, hipStream_t s) {
+static int launch_gemm_centroids(const Params &p, const __half *X, long long ldx, int tokens, __half *Y, long long ldy, void *workspace,
+                                 size_t workspace_bytes, hipStream_t s) {
   __half *C = static_cast<__half *>(workspace), *R = C + restored_bytes(p) / sizeof(__half);
   float *xsum = reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + restored_bytes(p) * (p.k_res ? 2 : 1));
   // (the residual matrix has no outlier columns of its own)
@@ -294,7 +300,10 @@ static int launch_gemm_centroids(const Params &p, const __half *X, long long ldx
     q.cb_out = nullptr; q.idx_out = nullptr; q.Q = q.S_out = 0;
     rc = launch_dequant(q, R, p.in_features, s, tokens);
   }
-  return rc == VQ_OK ? launch_gemm_dense(p, X, ldx, tokens, Y, ldy, C, p.in_features, s, xsum, p.k_res ? (unsigned)restored_bytes(p) : 0u) : rc;
+  if (rc != VQ_OK) return rc;
+  const size_t used = centroids_workspace_bytes(p, tokens), room = std::min(workspace_bytes - used, dense_scratch_bytes(p));
+  return launch_gemm_dense(p, X, ldx, tokens, Y, ldy, C, p.in_features, s, xsum, p.k_res ? (unsigned)restored_bytes(p) : 0u,
+                           room ? static_cast<unsigned char *>(workspace) + used : nullptr, room);
 }
 
 // Rows of X through vq_gemv, sixteen at a time, with the workspace if it is aligned for that (vq_gemv cuts the columns into parts with it).
@@ -313,18 +322,17 @@ static int launch_gemm_rows(const Params &p, const __half *X, long long ldx, int
 // nothing beyond 256 MiB (W of 11008 x 11008), so that who leaves the workspace out to save memory still does
 // where it counts (8192 x 28672, 448 MiB, 512 tokens: 532 us with it, 582 without).
 size_t gemm_default_workspace_bytes(const Params &p, int tokens) {
-  if (centroids_wanted(p, tokens)) return centroids_workspace_bytes(p, tokens);
+  if (centroids_wanted(p, tokens)) return default_bytes(p, centroids_workspace_bytes(p, tokens));
+  if (!rows_hold_the_weights(p, tokens) && gemm_dense_applicable(p)) return default_bytes(p, gemm_fast_workspace_bytes(p, tokens) - dense_scratch_bytes(p));
   const size_t bytes = rows_hold_the_weights(p, tokens) ? gemv_workspace_bytes(p, nullptr, (p.in_features + 7) & ~7, tokens < 16 ? tokens : 16)
                                                         : gemm_fast_workspace_bytes(p, tokens);
-  if (bytes > MOST_DEFAULT_WORKSPACE && !rows_hold_the_weights(p, tokens) && gemm_dense_applicable(p) && bytes - dense_scratch_bytes(p) <= MOST_DEFAULT_WORKSPACE)
-    return bytes - dense_scratch_bytes(p);
   return bytes <= MOST_DEFAULT_WORKSPACE ? bytes : 0;
 }
 
 int launch_gemm_default(const Params &p, const __half *X, long long ldx, int tokens, __half *Y, long long ldy, void *workspace,
                         size_t workspace_bytes, hipStream_t s) {
   if (workspace && (reinterpret_cast<uintptr_t>(workspace) & 255) == 0 && centroids_wanted(p, tokens) && workspace_bytes >= centroids_workspace_bytes(p, tokens)) {
-    const int rc = launch_gemm_centroids(p, X, ldx, tokens, Y, ldy, workspace, s);
+    const int rc = launch_gemm_centroids(p, X, ldx, tokens, Y, ldy, workspace, workspace_bytes, s);
     if (rc != VQ_ERR_UNSUPPORTED) return rc;
   }
   if (rows_hold_the_weights(p, tokens) && switches().gemm == '\0') return launch_gemm_rows(p, X, ldx, tokens, Y, ldy, workspace, workspace_bytes, s);

@@ -81,7 +81,7 @@ void gemm_dense_kernel(DenseArgs a) {
   if (item >= tiles) return;
   const int part = SPLIT ? item / (a.gx * a.gy) : 0, tile = SPLIT ? item - part * (a.gx * a.gy) : item;
   const int n0 = tile / a.gy * TN, m0 = tile % a.gy * TM;
-  const int wsteps = (a.in_features + DBK - 1) / DBK, first = SPLIT ? part * a.per : 0, ksteps = SPLIT ? min(first + a.per, wsteps) : CENTROIDS && a.w2 ? 2 * wsteps : wsteps;
+  const int wsteps = (a.in_features + DBK - 1) / DBK, first = SPLIT ? part * a.per : 0, all = CENTROIDS && a.w2 ? 2 * wsteps : wsteps, ksteps = SPLIT ? min(first + a.per, all) : all;
   // range-checked against the end of the last row: rows past the matrix read zeros
   const __amdgpu_buffer_rsrc_t r_x = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<__half *>(a.X), 0, (unsigned)(((long long)(a.tokens - 1) * a.ldx + a.in_features) * 2), 0x00020000);
@@ -273,12 +273,14 @@ __global__ __launch_bounds__(256) void gemm_dense_finish_kernel(DenseArgs a) {
 #pragma unroll 8
   for (int i = 0; i < a.parts; ++i) sum += a.partial[(long long)i * n + at];
   const int t = at / a.out_features;
-  a.Y[t * a.ldy + (at - t * a.out_features)] = __float2half_rn(sum);
+  const int o = at - t * a.out_features;
+  if (a.xsum) sum = __fmaf_rn(a.scale ? __half2float(a.scale[o]) : 1.0f, sum, (a.bias ? __half2float(a.bias[o]) : 0.0f) * a.xsum[t]);
+  a.Y[t * a.ldy + o] = __float2half_rn(sum);
 }
 
 template <int MB, int NB, int NST, bool CENTROIDS, bool SPLIT = false>
 int launch_tiles(DenseArgs a, hipStream_t s) {
-  if constexpr (!CENTROIDS && !SPLIT) if (a.xsum) return launch_tiles<MB, NB, NST, true>(a, s);
+  if constexpr (!CENTROIDS) if (a.xsum) return launch_tiles<MB, NB, NST, true, SPLIT>(a, s);
   auto kernel = gemm_dense_kernel<MB, NB, NST, CENTROIDS, SPLIT>;
   VQ_ALLOW_FULL_LDS(kernel);
   a.gx = (a.out_features + 64 * NB - 1) / (64 * NB);
@@ -319,11 +321,38 @@ const TileKind kTiles[] = {
     {1, 1, 2, 1.2f, {0.190f, 0.384f}, launch_tiles<1, 1, 4, false>, false, false, launch_tiles<1, 1, 4, false, true>},
 };
 
-float tile_cost(const TileKind &t, int tokens, int out_features, int in_features, int cus, int parts = 1) {
+float tile_cost(const TileKind &t, int tokens, int out_features, int steps_of_64, int cus, int parts = 1) {
   const long long tiles = (long long)((tokens + 64 * t.mb - 1) / (64 * t.mb)) * ((out_features + 64 * t.nb - 1) / (64 * t.nb)) * parts;
   const long long most = (tiles + cus - 1) / cus, rounds = most / t.per_cu, rest = most % t.per_cu;
-  const float steps = (float)(((in_features + DBK - 1) / DBK + parts - 1) / parts);
+  const float steps = (float)((steps_of_64 + parts - 1) / parts);
   return (float)rounds * (t.round + steps * t.step[t.per_cu - 1]) + (rest ? t.round + steps * t.step[rest - 1] : 0.0f);
+}
+
+// The kind and the parts of the columns with which a product takes less than `least` us: by the same estimates, 3 us for the second launch, and the
+// parts' way through the caches at 5 TB/s.  (With 1 us and more to gain: of 150 random calls of 17 to 1555 tokens 49 are cut, which takes 25 % off
+// the whole vq_gemm in the geometric mean and makes none slower by more than 2 %: v = 6, 78 tokens, 624 x 10752 45.9 -> 21.8 us, 64 of
+// 1024 x 4096 22.4 -> 15.5, of 4096 x 4096 32.1 -> 20.9; v = 12, 145 of 3200 x 6632 56.0 -> 43.3; 88 of 5696 x 9472 55.4 -> 55.8.  Of
+// 110 with the centroids in W 44, 28 %: v = 4, 44 tokens, 632 x 7936 35.9 -> 14.2, v = 6 + 4096, 95 of 1216 x 7680 73.8 -> 47.2.  With two
+// matrices 4 us and more: at 3.2 by the estimate, 81 of 2905 x 2304 took 41.5 -> 45.0.)
+struct Cut {
+  const TileKind *kind;
+  int parts, per;
+  float us;
+};
+Cut cut_columns(int tokens, int out_features, int steps, size_t scratch_bytes, float least) {
+  Cut best = {nullptr, 1, steps, least};
+  const size_t part_bytes = (size_t)tokens * (size_t)out_features * sizeof(float);
+  if (part_bytes * 2 <= scratch_bytes)
+    for (const TileKind &k : kTiles) {
+      if (!k.split) continue;
+      for (int n : {2, 3, 4, 6, 8, 12, 16, 24, 32}) {
+        if (n > steps / 2 || part_bytes * (size_t)n > scratch_bytes) break;
+        const int per = (steps + n - 1) / n, parts = (steps + per - 1) / per;
+        const float us = tile_cost(k, tokens, out_features, steps, cu_count(), parts) + 3.0f + (float)((double)part_bytes * 2 * parts / 5e6);
+        if (us < best.us) best = {&k, parts, per, us};
+      }
+    }
+  return best;
 }
 
 }  // namespace
@@ -344,7 +373,7 @@ int launch_gemm_dense(const Params &p, const __half *X, long long ldx, int token
   if (most_tokens < 1 || most_out < 1) return VQ_ERR_UNSUPPORTED;
   const int force = switches().dense;
   const bool cached = dequant_leaves_cached(p, tokens, w2 ? 2 : 1);
-  const int wsteps = (p.in_features + DBK - 1) / DBK;
+  const int steps = (p.in_features + DBK - 1) / DBK * (w2 ? 2 : 1);
   for (long long o = 0; o < p.out_features; o += most_out)
     for (long long t = 0; t < tokens; t += most_tokens) {
       const int nt = (int)std::min<long long>(most_tokens, tokens - t), no = (int)std::min<long long>(most_out, p.out_features - o);
@@ -352,28 +381,12 @@ int launch_gemm_dense(const Params &p, const __half *X, long long ldx, int token
       const TileKind *best = &kTiles[force > 0 && force <= kinds ? force - 1 : kinds - 1];
       if (force < 0)
         for (const TileKind &k : kTiles)
-          if ((cached || !k.cached) && tile_cost(k, nt, no, p.in_features, cu_count()) < tile_cost(*best, nt, no, p.in_features, cu_count())) best = &k;
+          if ((cached || !k.cached) && tile_cost(k, nt, no, steps, cu_count()) < tile_cost(*best, nt, no, steps, cu_count())) best = &k;
       DenseArgs a = {X + t * ldx, ldx, nt, Wd + o * ldw, ldw, no, p.in_features, Y + t * ldy + o, ldy, 0, 0, w2,
-                     p.scale ? p.scale + o : nullptr, p.bias ? p.bias + o : nullptr, xsum ? xsum + t : nullptr, static_cast<float *>(scratch), 1, wsteps};
-      // The columns in parts, by the same estimates, where that saves 1 us and more: 3 us for the second launch, and the parts' way through
-      // the caches at 5 TB/s.  (Of 150 random calls of 17 to 1555 tokens 49 are cut, which takes 25 % off the whole vq_gemm in the geometric mean
-      // and makes none slower by more than 2 %: v = 6, 78 tokens, 624 x 10752 45.9 -> 21.8 us, 64 of 1024 x 4096 22.4 -> 15.5, of 4096 x 4096
-      // 32.1 -> 20.9; v = 12, 145 of 3200 x 6632 56.0 -> 43.3; 88 of 5696 x 9472 55.4 -> 55.8.)
-      const TileKind *split = nullptr;
-      const size_t part_bytes = (size_t)nt * (size_t)no * sizeof(float);
-      if (scratch && !xsum && force < 0 && part_bytes * 2 <= scratch_bytes) {
-        float least = tile_cost(*best, nt, no, p.in_features, cu_count()) - 1.0f;
-        for (const TileKind &k : kTiles) {
-          if (!k.split) continue;
-          for (int n : {2, 3, 4, 6, 8, 12, 16, 24, 32}) {
-            if (n > wsteps / 2 || part_bytes * (size_t)n > scratch_bytes) break;
-            const int per = (wsteps + n - 1) / n, parts = (wsteps + per - 1) / per;
-            const float us = tile_cost(k, nt, no, p.in_features, cu_count(), parts) + 3.0f + (float)((double)part_bytes * 2 * parts / 5e6);
-            if (us < least) { least = us; split = &k; a.parts = parts; a.per = per; }
-          }
-        }
-      }
-      const int rc = split ? split->split(a, s) : best->launch(a, s);
+                     p.scale ? p.scale + o : nullptr, p.bias ? p.bias + o : nullptr, xsum ? xsum + t : nullptr, static_cast<float *>(scratch), 1, steps};
+      const Cut cut = scratch && force < 0 ? cut_columns(nt, no, steps, scratch_bytes, tile_cost(*best, nt, no, steps, cu_count()) - (w2 ? 4.0f : 1.0f)) : Cut{};
+      if (cut.kind) { a.parts = cut.parts; a.per = cut.per; }
+      const int rc = cut.kind ? cut.kind->split(a, s) : best->launch(a, s);
       if (rc != VQ_OK) return rc;
     }
   return VQ_OK;
@@ -385,7 +398,7 @@ int launch_gemm_dense(const Params &p, const __half *X, long long ldx, int token
 float gemm_dense_us(const Params &p, int tokens, bool against_rows) {
   float best = 1e30f;
   for (const TileKind &k : kTiles)
-    if (!against_rows || !k.later) best = std::min(best, tile_cost(k, tokens, p.out_features, p.in_features, cu_count()));
+    if (!against_rows || !k.later) best = std::min(best, tile_cost(k, tokens, p.out_features, (p.in_features + DBK - 1) / DBK, cu_count()));
   return std::max(best, 3.0f + (float)((double)p.out_features * p.in_features * 2 / 4.5e6));
 }
 

@@ -126,6 +126,33 @@ def test_gemm_columns_in_parts(gpu_lib, tokens, out_features, in_features, more)
         assert torch.isfinite(Y).all() and (Y[:, out_features:] == 7.0).all() and (ws[size:] == 0xFF).all()
 
 
+@pytest.mark.parametrize("tokens,out_features,in_features,v,k,more", [
+    (44, 333, 4104, 4, 256, {}), (79, 130, 5000, 6, 300, dict(group_vectors=400)), (95, 650, 5128, 6, 300, dict(k_res=256, group_vectors=100)),
+    (64, 257, 5000, 12, 300, dict(k_res=300, orientation=1, group_vectors=999, n_outlier_cols=40, v_out=4, k_out=300)),
+    (326, 977, 5296, 4, 256, {}),
+])
+def test_gemm_by_default_with_columns_in_parts(gpu_lib, tokens, out_features, in_features, v, k, more):
+    """The same with the centroids in W, and those of a residual table in a second matrix behind it: scale, bias and the rows' sums come in with
+    the parts.  With less room the columns stay whole."""
+    import torch
+    L = s.make_layer(8500, "parts", out_features, in_features, v, k, **more)
+    dl = gpu_lib.DeviceLayer(L)
+    x = s.make_activations(8500, L, tokens)
+    X = torch.from_numpy(x).cuda()
+    need = gpu_lib.vq_gemm_default_workspace_bytes(dl.desc, tokens)
+    rows = np.unique(np.linspace(0, out_features - 1, 130).astype(np.int32))
+    ref = oracle.gemm(L, x, rows=rows)
+    ws = torch.empty(need + 256, dtype=torch.uint8, device="cuda")
+    for size in (need, need - 256, max(need - (8 << 20), 0)):
+        ws[:] = 0xFF
+        Y = torch.full((tokens, out_features + 3), 7.0, dtype=torch.float16, device="cuda")
+        rc = gpu_lib.vq_gemm_default(dl.desc, X.data_ptr(), X.stride(0), tokens, Y.data_ptr(), Y.stride(0), ws.data_ptr(), size, torch.cuda.current_stream().cuda_stream)
+        assert rc == 0
+        torch.cuda.synchronize()
+        _check_matmul(Y[:, torch.from_numpy(rows.astype(np.int64)).cuda()], ref, "%d tokens, workspace of %d bytes" % (tokens, size))
+        assert torch.isfinite(Y).all() and (Y[:, out_features:] == 7.0).all() and (ws[size:] == 0xFF).all()
+
+
 DENSE_SHAPES = [(1, 1, 8), (17, 300, 520), (64, 64, 64), (65, 129, 120), (128, 192, 192), (191, 257, 1032), (256, 256, 128), (300, 513, 136), (513, 768, 320)]
 
 
