@@ -507,6 +507,10 @@ size_t gemv_workspace_bytes(const Params &p, const __half *x, long long ldx, int
   return bytes;
 }
 
+// Sums of `slots` parts, groups or tables, and those of the activations, in front of a second launch that adds them up.
+static size_t sums_bytes(const Params &p, size_t slots, int batch) { return slots * ((size_t)batch * (size_t)p.out_features + 16) * sizeof(float); }
+
+// (Every branch compares the workspace with what its kernels write: `need` may count a copy of the activations that is not made here.)
 static int launch_with_workspace(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, void *workspace,
                                  size_t workspace_bytes, bool least, hipStream_t s) {
   const size_t need = workspace_bytes_of(p, x, ldx, batch, least);
@@ -540,14 +544,14 @@ static int launch_with_workspace(const Params &p, const __half *x, long long ldx
     return rc == VQ_OK ? launch_groups_finish(part, part_xs, parts, batch, p, y, ldy, s) : rc;
   }
   if (need && workspace && workspace_bytes >= need && p.orientation == 1 && down_mfma_parts_wanted(p, x, ldx, batch)) {
-    if (!down_mfma_parts_pay(p, batch)) return launch_gemv(p, x, ldx, batch, y, ldy, s);
     const int parts = gemv_down_mfma_parts(p), slots = parts + (p.Q ? 1 : 0);
+    if (parts < 2 || workspace_bytes < sums_bytes(p, slots, batch) || !down_mfma_parts_pay(p, batch)) return launch_gemv(p, x, ldx, batch, y, ldy, s);
     float *part = static_cast<float *>(workspace), *part_xs = part + (size_t)slots * (size_t)batch * (size_t)p.out_features;
     int rc = launch_gemv_down_mfma(p, x, ldx, batch, nullptr, 0, s, part, part_xs, parts);
     if (rc == VQ_OK) return launch_groups_finish(part, part_xs, slots, batch, p, y, ldy, s);
     if (rc != VQ_ERR_UNSUPPORTED) return rc;
   } else if (need && workspace && workspace_bytes >= need && p.orientation == 1 && !gemv_down_applicable(p, x, ldx)) {
-    if (!switches().groups_loop) {                            // the LDS-table kernel of this orientation: a group per workgroup
+    if (!switches().groups_loop && workspace_bytes >= sums_bytes(p, p.n_groups, batch)) {      // the LDS-table kernel of this orientation: a group per workgroup
       float *part = static_cast<float *>(workspace), *part_xs = part + (size_t)p.n_groups * (size_t)batch * (size_t)p.out_features;
       const int rc = launch_gemv_down_lds_slots(p, x, ldx, batch, part, part_xs, s);
       if (rc == VQ_OK) return launch_groups_finish(part, part_xs, p.n_groups, batch, p, y, ldy, s);
@@ -555,6 +559,7 @@ static int launch_with_workspace(const Params &p, const __half *x, long long ldx
     }
   } else if (need && workspace && workspace_bytes >= need && p.orientation == 1) {
     const int slots = p.n_groups + (p.Q ? 1 : 0);             // the outlier columns are one more set of sums to add up
+    if (workspace_bytes < sums_bytes(p, slots, batch)) return launch_gemv(p, x, ldx, batch, y, ldy, s);
     float *part = static_cast<float *>(workspace), *part_xs = part + (size_t)slots * (size_t)batch * (size_t)p.out_features;
     int done = 0, g_max = 4, rc = VQ_OK;
     while (done < batch) {                                // batch rows in launches of 4, 2 or 1, as without groups
@@ -576,7 +581,7 @@ static int launch_with_workspace(const Params &p, const __half *x, long long ldx
       if (rc == VQ_OK) return launch_groups_finish(part, part + (size_t)slots * (size_t)batch * (size_t)p.out_features, slots, batch, p, y, ldy, s);
       if (rc != VQ_ERR_UNSUPPORTED) return rc;
     }
-  } else if (need && workspace && workspace_bytes >= need && !switches().groups_loop) {
+  } else if (need && workspace && workspace_bytes >= std::max(need, gemv_mfma_groups_workspace_bytes(p, batch)) && !switches().groups_loop) {
     const int rc = launch_gemv_mfma_groups(p, x, ldx, batch, y, ldy, workspace, s);
     if (rc != VQ_ERR_UNSUPPORTED) return rc;
   }

@@ -1122,6 +1122,24 @@ def test_gemv_rows_of_any_width(gpu_lib, out_features, in_features, more, batch)
     assert (ws[need:] == 0xFF).all()
 
 
+@pytest.mark.parametrize("rows,lent_for", [(4, 4), (5, 16)])
+def test_gemv_of_odd_rows_without_parts_leaves_the_workspace_alone(gpu_lib, rows, lent_for):
+    """As many blocks of streams as compute units, and a row that does not fit LDS beside two tables: the activations are taken as they are, there are
+    no parts, and the workspace, which has the size of a copy, is not written."""
+    import torch
+    L = s.make_layer(319, "blocks", 12391, 15873, 6, 4096, 4096, orientation=1)
+    dl = gpu_lib.DeviceLayer(L)
+    x_np = s.make_activations(319, L, rows)
+    x = torch.full((rows, 15880), float("nan"), dtype=torch.float16, device="cuda")
+    x[:, :15873] = torch.from_numpy(x_np)
+    need = gpu_lib.vq_gemv_workspace_bytes(dl.desc, lent_for)
+    ws = torch.full((need + (4 << 20),), 0xFF, dtype=torch.uint8, device="cuda")
+    y = gpu_lib.gemv(dl, x[:, :15873], workspace=ws[:need])
+    torch.cuda.synchronize()
+    _check_matmul(y, oracle.gemv(L, x_np), "%d rows" % rows)
+    assert (ws == 0xFF).all()
+
+
 @pytest.mark.parametrize("in_features,k,k_res,group_vectors", [(9, 65536, 0, 0), (1203, 65536, 300, 0), (1030, 200, 65536, 31), (2051, 256, 256, 0)])
 @pytest.mark.parametrize("batch", [1, 2, 5])
 def test_gemv_v8_rows_of_any_width(gpu_lib, in_features, k, k_res, group_vectors, batch):

@@ -1,0 +1,56 @@
+"""Routes and workspaces of the library's calls, from the launches that they make on a machine without a GPU (launches.py)."""
+import random
+
+import launches
+import pytest
+
+
+def _layer(rng, odd):
+    """A layer of any of the settings that vq_gemv knows; odd: of an odd width."""
+    v, k = rng.choice([(6, 4096), (6, 4096), (6, 3000), (12, 4096), (8, 256), (8, 65536), (4, 256), (2, 16), (5, 37)])
+    out = round(2 ** rng.uniform(4, 14))
+    inp = round(2 ** rng.uniform(6, 14.2)) // 2 * 2 + odd
+    outliers = 4 * rng.randint(1, 10) if rng.random() < 0.3 else 0
+    orientation = rng.randint(0, 1)
+    vectors = (inp - outliers) // (1 if orientation else v)
+    return dict(out_features=out, in_features=inp, v=v, k=k, k_res=rng.choice([0, 0, k, min(k, 256)]), n_outlier_cols=outliers, orientation=orientation,
+                group_vectors=rng.choice([0, 0, 0, max(8, vectors // rng.randint(2, 16) // 8 * 8)]), col_perm=rng.random() < 0.3)
+
+
+def _inside(call, answer):
+    """The sums and the copy of the activations that an answer's kernels write lie in the workspace."""
+    for launch in answer["launches"]:
+        words, end = launch["words"], launches.WORKSPACE + answer["lent"]
+        if "finish" in launch["name"]:
+            part, part_xs, slots, batch, out = words[:5]
+            assert launches.WORKSPACE <= part and part + slots * batch * out * 4 <= part_xs and part_xs + slots * 64 <= end, (call, launch)
+        if "gather_cols" in launch["name"]:
+            to, pitch = words[4:6]
+            assert launches.WORKSPACE <= to and to + call["rows"] * pitch * 2 <= end, (call, launch)
+
+
+@pytest.mark.parametrize("odd", [1, 0])
+def test_gemv_stays_inside_its_workspace(odd):
+    """A workspace of the size asked for, one byte less, one asked for more rows: with activations that can be taken as they are and others."""
+    rng = random.Random(odd)
+    calls = []
+    for _ in range(700):
+        layer, rows = _layer(rng, odd), rng.choice([1, 2, 3, 4, 5, 8, 16])
+        inp = layer["in_features"]
+        for pitch, x in ((inp + odd, 0), ((inp + 7) // 8 * 8, 0), (inp + 3, 2)):
+            one = dict(entry="gemv_with_workspace", layer=layer, rows=rows, pitch=pitch, x=launches.X + x, workspace="asked")
+            calls += [one, dict(one, asked_for_rows=rng.randint(rows, 16))]
+    # two tables of vectors down the outputs and more activations than fit LDS beside them, in as many blocks as compute units: no parts, and once
+    # the size of a copy that was not made passed for that of the sums
+    for rows, out in ((4, 14336), (8, 14336), (16, 14336), (2, 30000)):
+        layer = dict(out_features=out, in_features=15873, k_res=4096, orientation=1)
+        calls += [dict(entry="gemv_with_workspace", layer=layer, rows=rows, pitch=pitch, workspace="asked", asked_for_rows=asked)
+                  for pitch in (15880, 15873) for asked in (rows, 16)]
+    answers = launches.run(calls)
+    smaller = [dict(call, workspace=answer["asked"] - 256) for call, answer in zip(calls, answers) if answer["asked"] > 256]
+    with_sums = 0
+    for call, answer in list(zip(calls, answers)) + list(zip(smaller, launches.run(smaller))):
+        assert answer["status"] == 0 and answer["launches"]
+        _inside(call, answer)
+        with_sums += any("finish" in launch["name"] for launch in answer["launches"])
+    assert with_sums > 300
