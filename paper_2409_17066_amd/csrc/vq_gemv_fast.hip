@@ -122,7 +122,7 @@ __device__ __forceinline__ void gemv_v6_body(const Params &p, const GemvPlan &pl
 
   // ---- index stream geometry of this lane
   // (a lane past the row's last vector reads past the end of the streams, i.e. zeros: index 0 in all such lanes is one address, the next row's
-  // bits would be as many lookups as anyone's)
+  // bits would be as many lookups as anyone's.  What it makes of the entry is left out of the sum: zero times an entry that is no number is none.)
   const bool past = is_main && first_vec >= p.P;
   const unsigned bit0 = (unsigned)first_vec * 12u;
   const unsigned dw_main = past ? 0x20000000u : bit0 >> 5, sh_main = bit0 & 31u;
@@ -336,7 +336,7 @@ __device__ __forceinline__ void gemv_v6_body(const Params &p, const GemvPlan &pl
           const int col = is_main ? slice : plan.W + slice;
 #pragma unroll
           for (int b = 0; b < B; ++b) {
-            const float s = wave_reduce_to_lane63(acc[b]);
+            const float s = wave_reduce_to_lane63(past ? 0.0f : acc[b]);
             if (lane == 63) part[(rl * Wt + col) * B + b] = s;
           }
         }

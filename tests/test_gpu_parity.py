@@ -644,6 +644,22 @@ def test_gemv_of_infinite_activations(gpu_lib, out, inp, setting, batch):
         assert torch.isfinite(y[: batch - 1]).all(), column
 
 
+@pytest.mark.parametrize("out,k_res", [(300, 0), (4000, 4096), (300, 256)])
+@pytest.mark.parametrize("batch", [1, 2])
+def test_gemv_of_an_infinite_entry_that_no_index_names(gpu_lib, out, k_res, batch):
+    """480 vectors a row, whole lanes of four, five, six or eight: the lanes behind them add nothing to a row, whatever entry they look up."""
+    import torch
+    L = s.make_layer(320, "entry", out, 2880, 6, 4096, k_res)
+    L.codebook[0] = np.inf
+    bits = np.unpackbits(L.idx, axis=1, bitorder="little")
+    bits[:, 0:480 * 12:12] = 1                           # odd indices
+    L.idx = np.packbits(bits, axis=1, bitorder="little")
+    x_np = s.make_activations(320, L, batch)
+    y = gpu_lib.gemv(gpu_lib.DeviceLayer(L), torch.from_numpy(x_np).cuda())
+    torch.cuda.synchronize()
+    _check_matmul(y, oracle.gemv(L, x_np), "batch %d" % batch)
+
+
 @pytest.mark.parametrize("outs,inp,outliers", [
     ((4100,), 8004, 0),                    # two blocks of rows a chunk: up to three activation rows straight into the operands
     ((8200,), 8010, 0),                    # three: up to five
