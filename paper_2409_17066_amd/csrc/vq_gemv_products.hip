@@ -201,6 +201,7 @@ __global__ __launch_bounds__(THREADS) void gemv_products_kernel(Params p, Produc
   }
   // entries that are no numbers: products of the two entries of a tile are then kept apart, as 0 times such an element is not 0
   const bool odd = __any(top == 0x7C00u);
+  const int elements = p.in_features - p.n_out - (p.P - 1) * ENTRY;       // of the row's last vector
 
   float sum[CHUNKS][B];
 #pragma unroll
@@ -254,6 +255,33 @@ __global__ __launch_bounds__(THREADS) void gemv_products_kernel(Params p, Produc
           for (int r = 0; r < 4; ++r)                                      // (whatever bits stand behind the last index: nothing)
             if (first + (B == 1 ? a_plane : ((lane >> 4 & 1) * 4 + r) / B) >= p_hi) d[r] = 0.0f;
           keep(i, d);
+        }
+        // of the row's last vector, what lies past the row is dropped: its products once more
+        if (elements < ENTRY && first <= p.P - 1 && first + AT_ONCE >= p.P) {
+#pragma unroll 1
+          for (int turn = 0; turn < TILES; ++turn) {
+            half8v mine;                                                   // (entry `turn` of the array, which stays in registers)
+#pragma unroll
+            for (int i = 0; i < TILES; ++i)
+              if (i == turn) mine = entries[i];
+            uint4v e = __builtin_bit_cast(uint4v, mine);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const int left = elements - (lane >> 4 & 1) * 8 - 2 * q;     // elements of this dword that are the row's
+              e[q] = left >= 2 ? e[q] : left == 1 ? e[q] & 0xFFFFu : 0u;
+            }
+            const unsigned low = lane < 32 ? ~0u : 0u;
+            const float4v d1 = multiply(A, __builtin_bit_cast(half8v, e & low)), d2 = multiply(A, __builtin_bit_cast(half8v, e & ~low));
+            const float4v d = first_entry ? d1 : d2;
+            unsigned char *to = lds + entry_at + (unsigned)(wave * TILES + turn) * (32u * 4u * B);
+            const int position = first + (B == 1 ? a_plane : (lane >> 4 & 1) * 2);
+            if constexpr (B == 1) {
+              if (position == p.P - 1) *reinterpret_cast<float4v *>(to) = d;
+            } else {
+              if (position == p.P - 1) *reinterpret_cast<float2v *>(to) = float2v{d[0], d[1]};
+              if (position + 1 == p.P - 1) *reinterpret_cast<float2v *>(to + 32768) = float2v{d[2], d[3]};
+            }
+          }
         }
       } else {
 #pragma unroll

@@ -1070,6 +1070,29 @@ def test_tables_of_products_keep_what_is_no_number_where_it_belongs(gpu_lib, mon
     assert not torch.isfinite(y).any()
 
 
+@pytest.mark.parametrize("batch", [1, 2])
+@pytest.mark.parametrize("last", [1, 7, 8, 11, 12])
+def test_tables_of_products_drop_what_lies_past_the_row(gpu_lib, monkeypatch, last, batch):
+    """Entries that are infinite past the elements of a row that its last vector has, named by that vector alone; in both tables, in a group of its own."""
+    import torch
+    monkeypatch.setenv("VQ_SWITCHES", "products=1")
+    inp = 12 * 57 + last
+    L = s.make_layer(321, "products", 200, inp, 12, 4096, 4096, group_vectors=40)
+    L.codebook[1::2, last:] = np.inf
+    L.codebook_res[1::2, last:] = -np.inf
+    for stream in ("idx", "idx_res"):
+        bits = np.unpackbits(getattr(L, stream), axis=1, bitorder="little")
+        bits[:, 0:58 * 12:12] = 0
+        bits[::2, 57 * 12] = 1                           # every second row's last vector
+        setattr(L, stream, np.packbits(bits, axis=1, bitorder="little"))
+    x_np = s.make_activations(321, L, batch)
+    dl = gpu_lib.DeviceLayer(L)
+    ws = torch.empty(gpu_lib.vq_gemv_workspace_bytes(dl.desc, batch), dtype=torch.uint8, device="cuda")
+    y = gpu_lib.gemv(dl, torch.from_numpy(x_np).cuda(), workspace=ws)
+    torch.cuda.synchronize()
+    _check_matmul(y, oracle.gemv(L, x_np), "%d of twelve" % last)
+
+
 @pytest.mark.parametrize("out_features,in_features,k_res", [(3000, 16390, 0), (1000, 9001, 4096), (100, 300, 256), (97, 1000, 0)])
 @pytest.mark.parametrize("batch", [1, 2, 3, 4, 16])
 def test_gemv_down_routes(gpu_lib, out_features, in_features, k_res, batch):
