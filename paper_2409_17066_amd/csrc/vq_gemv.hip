@@ -426,7 +426,7 @@ static bool permuted_in_kernel(const Params &p, const __half *x, long long ldx, 
 // for more than vq_gemv_static_workspace has, which would refuse a layer that needs none.)
 // The v = 6 / 12-bit kernels want dwords at any number of rows, those along the rows an even width as well: there the copy's next column, zeros,
 // counts as the layer's last (P is the same: an odd width is short of whole vectors).  3520 x 6587, 1 / 4 / 16 rows: 9.7 -> 7.9, 18.3 -> 9.2, 71 -> 11.2 us;
-// down the outputs, 4 / 16 rows 21.5 -> 12.0, 82 -> 14.2.
+// down the outputs, in column parts, 4 / 16 rows 20.7 -> 10.5, 80.6 -> 12.4 (without parts 16.0, 17.5).
 static bool even_width_wanted(const Params &p) { return p.orientation == 0 && (p.in_features & 1) && gemv_fast_applicable_even(p); }
 static size_t stored_order_workspace_bytes(const Params &p, const __half *x, long long ldx, int batch, bool least);
 static Params gathered(const Params &p) {
@@ -510,11 +510,12 @@ size_t gemv_workspace_bytes(const Params &p, const __half *x, long long ldx, int
 // Sums of `slots` parts, groups or tables, and those of the activations, in front of a second launch that adds them up.
 static size_t sums_bytes(const Params &p, size_t slots, int batch) { return slots * ((size_t)batch * (size_t)p.out_features + 16) * sizeof(float); }
 
-// (Every branch compares the workspace with what its kernels write: `need` may count a copy of the activations that is not made here.)
+static int launch_stored_order(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, void *workspace,
+                               size_t workspace_bytes, bool least, hipStream_t s);
 static int launch_with_workspace(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, void *workspace,
                                  size_t workspace_bytes, bool least, hipStream_t s) {
-  const size_t need = workspace_bytes_of(p, x, ldx, batch, least);
   if (p.perm || (rows_gathered(p, batch) && !taken_as_they_are(p, x, ldx, batch))) {
+    const size_t need = workspace_bytes_of(p, x, ldx, batch, least);
     if (!need || !workspace || workspace_bytes < need) return launch_gemv(p, x, ldx, batch, y, ldy, s);
     // gather the activations into stored order, then the layer is an unpermuted one
     const Params q = gathered(p);
@@ -534,8 +535,16 @@ static int launch_with_workspace(const Params &p, const __half *x, long long ldx
     const int rc = launch_gather_cols(x, ldx, batch, p.in_features, p.perm, xp, ldxp, s);
     if (rc != VQ_OK) return rc;
     const size_t head = permuted_x_bytes(p, batch);
-    return launch_with_workspace(q, xp, ldxp, batch, y, ldy, static_cast<unsigned char *>(workspace) + head, workspace_bytes - head, false, s);
+    return launch_stored_order(q, xp, ldxp, batch, y, ldy, static_cast<unsigned char *>(workspace) + head, workspace_bytes - head, false, s);
   }
+  return launch_stored_order(p, x, ldx, batch, y, ldy, workspace, workspace_bytes, least, s);
+}
+
+// Activations that are taken as they are, in stored order (the caller's, or the copy of them in front of this workspace).  Every branch compares
+// the workspace with what its kernels write.
+static int launch_stored_order(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, void *workspace,
+                               size_t workspace_bytes, bool least, hipStream_t s) {
+  const size_t need = force_generic() ? 0 : stored_order_workspace_bytes(p, x, ldx, batch, least);
   if (rows_wanted(p, batch, workspace != nullptr) && gemv_rows_takes(p, x, ldx, batch)) {
     const int per_group = workspace && workspace_bytes >= gemv_rows_workspace_bytes(p, batch) ? gemv_rows_parts(p) : 0, parts = per_group * p.n_groups;
     if (parts == 0) return launch_gemv_rows(p, x, ldx, batch, y, ldy, nullptr, nullptr, 0, s);

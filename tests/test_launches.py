@@ -54,3 +54,24 @@ def test_gemv_stays_inside_its_workspace(odd):
         _inside(call, answer)
         with_sums += any("finish" in launch["name"] for launch in answer["launches"])
     assert with_sums > 300
+
+
+@pytest.mark.parametrize("permuted", [False, True])
+@pytest.mark.parametrize("out,inp,more", [
+    (3520, 6587, {}), (4096, 4097, {}), (2048, 8193, dict(k_res=4096)), (2048, 8193, dict(k_res=256, n_outlier_cols=40)), (4096, 4097, dict(group_vectors=256)),
+])
+def test_gemv_of_odd_rows_down_the_outputs_in_parts(out, inp, more, permuted):
+    """The workspace of an odd width takes the copy of the activations, where there is one, and the same parts as the next even width."""
+    calls = []
+    for rows in (2, 4, 16):
+        for width, pitch in ((inp, inp), (inp, inp + 1), (inp + 1, inp + 1)):
+            layer = dict(out_features=out, in_features=width, orientation=1, col_perm=permuted, **more)
+            calls.append(dict(entry="gemv_with_workspace", layer=layer, rows=rows, pitch=pitch, workspace="asked"))
+    answers = launches.run(calls)
+    for call, answer in zip(calls, answers):
+        _inside(call, answer)
+    for i in range(0, len(answers), 3):
+        copied, even_pitch, even = [[(launch["name"], launch["grid"]) for launch in answer["launches"] if "gather" not in launch["name"]] for answer in answers[i:i + 3]]
+        assert copied == even and even_pitch == even
+        assert any("finish" in name for name, _ in even)
+        assert answers[i]["launches"][0]["name"] == "gather_cols_kernel" and (answers[i + 1]["launches"][0]["name"] == "gather_cols_kernel") == permuted
