@@ -131,7 +131,7 @@ int launch_gemv_mfma(const Params &p, const __half *x, long long ldx, int batch,
 bool gemv_fast_applicable_even(const Params &p);
 bool gemv_down_applicable(const Params &p, const __half *x, long long ldx);
 bool gemv_down_fits(const Params &p);
-bool gemv_v8_applicable(const Params &p, const __half *x, long long ldx);
+bool gemv_v8_wanted(const Params &p, const __half *x, long long ldx, int batch, bool workspace);
 int launch_gemv_v8(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, hipStream_t s);
 bool gemv_v8_down_applicable(const Params &p);
 int launch_gemv_v8_down(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, hipStream_t s);
@@ -241,7 +241,7 @@ static bool rows_wanted(const Params &p, int batch, bool workspace) {
 bool gemv_has_lds_kernel(const Params &p, const __half *x, long long ldx) {
   if (forced_kernel() != '\0') return false;
   if (p.orientation == 1) return !gemv_down_applicable(p, x, ldx) && !gemv_v8_down_applicable(p) && gemv_down_lds_applicable(p, 1);
-  return !gemv_fast_applicable(p, x, ldx) && !gemv_v8_applicable(p, x, ldx) && gemv_lds_applicable(p, 1);
+  return !gemv_fast_applicable(p, x, ldx) && !gemv_v8_wanted(p, x, ldx, 16, false) && gemv_lds_applicable(p, 1);
 }
 
 // Whether vq_gemv has one of its specialised kernels for this layer and these activations (vq_gemm sends small token
@@ -249,7 +249,7 @@ bool gemv_has_lds_kernel(const Params &p, const __half *x, long long ldx) {
 bool gemv_has_fast_kernel(const Params &p, const __half *x, long long ldx) {
   if (forced_kernel() != '\0') return false;
   if (p.orientation == 1) return down_mfma_wanted(p, x, ldx, 16) || gemv_v8_down_applicable(p);
-  return gemv_fast_applicable(p, x, ldx) || gemv_v8_applicable(p, x, ldx);
+  return gemv_fast_applicable(p, x, ldx) || gemv_v8_wanted(p, x, ldx, 16, false);
 }
 
 // Layers without a kernel of their own whose tables fit LDS (vq_gemv_lds.hip): batch rows in launches of 4, 2 or 1, fewer
@@ -386,7 +386,7 @@ int launch_gemv(const Params &p, const __half *x, long long ldx, int batch, __ha
       if (rc != VQ_ERR_UNSUPPORTED) return rc;
     }
   }
-  if (!force_generic() && gemv_v8_applicable(p, x, ldx)) {
+  if (!force_generic() && gemv_v8_wanted(p, x, ldx, batch, false)) {
     // 8-component vectors, tables read through L2: batch rows in launches of 8, 4, 2 or 1
     int done = 0, rc = VQ_OK;
     while (done < batch && rc == VQ_OK) {
@@ -470,7 +470,7 @@ static size_t stored_order_workspace_bytes(const Params &p, const __half *x, lon
     return gemv_down_applicable(p, x, ldx) || gemv_v8_down_applicable(p) ? 0 : gemv_down_lds_slots_workspace_bytes(p, batch);
   }
   if (!gemv_fast_applicable(p, x, ldx))       // the LDS-table kernels, when the layer gets that far: a slot per workgroup
-    return gemv_v8_applicable(p, x, ldx) ? 0 : gemv_lds_slots_workspace_bytes(p, batch, least);
+    return gemv_v8_wanted(p, x, ldx, batch, true) ? 0 : gemv_lds_slots_workspace_bytes(p, batch, least);
   if (forced_kernel() == 'd') return 0;
   return gemv_mfma_groups_workspace_bytes(p, batch);
 }

@@ -17,6 +17,7 @@ namespace {
 
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef _Float16 half8v __attribute__((ext_vector_type(8)));
+typedef unsigned uint4v __attribute__((ext_vector_type(4)));
 
 // (The operands stay vectors of halves from the load to the instruction: this compiler turned bit casts of the dwords of
 // a four-dword load into four uses of the first dword.)
@@ -34,32 +35,26 @@ template <int BYTES> __device__ __forceinline__ unsigned load_idx(const uint8_t 
 
 constexpr int WAVES = 4, CHAINS = 4;
 
-// Eight activations from column c on, of a row that begins at any half; zeros past the row's end.
-__device__ __forceinline__ half8v activations(const __half *row, int c, int columns) {
+// Eight activations that begin at any half.
+__device__ __forceinline__ half8v activations(const __half *from) {
   typedef _Float16 half8h __attribute__((ext_vector_type(8), aligned(2)));
-  half8v v = {0, 0, 0, 0, 0, 0, 0, 0};
-  if (c + 8 <= columns) {
-    const half8h w = *reinterpret_cast<const half8h *>(row + c);
-    v = half8v{w[0], w[1], w[2], w[3], w[4], w[5], w[6], w[7]};
-  } else {
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-      if (c + j < columns) v[j] = __builtin_bit_cast(_Float16, row[c + j]);
-  }
-  return v;
+  const half8h w = *reinterpret_cast<const half8h *>(from);
+  return half8v{w[0], w[1], w[2], w[3], w[4], w[5], w[6], w[7]};
 }
-// The first `n` elements of an entry: what the row's cut-off last vector drops may be no number.
-__device__ __forceinline__ half8v first_of(const half8v &e, int n) {
-  half8v v;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) v[j] = j < n ? e[j] : (_Float16)0;
-  return v;
+// The first 8 - n elements of an entry, n places up, zeros before them: what the row's cut-off last vector drops may be no number.
+__device__ __forceinline__ half8v moved_up(const half8v &e, int n) {
+  uint4v d = __builtin_bit_cast(uint4v, e);
+  if (n & 4) d = uint4v{0u, 0u, d.x, d.y};
+  if (n & 2) d = uint4v{0u, d.x, d.y, d.z};
+  if (n & 1) d = uint4v{d.x << 16, __builtin_amdgcn_alignbit(d.y, d.x, 16), __builtin_amdgcn_alignbit(d.z, d.y, 16), __builtin_amdgcn_alignbit(d.w, d.z, 16)};
+  return __builtin_bit_cast(half8v, d);
 }
 
 // B rows of x; IB / RB: bytes per main / residual index (RB = 0: no residual table); R output rows per wave.  With
 // R = 2 a wave walks two rows at once, CHAINS / 2 chains each: as many gathers in flight, but every activation it
 // loads serves both rows -- x is otherwise re-read once per output row, which is what four and more tokens pay for.
 // ANY: x at any half, and a last vector that the row cuts off (in every instantiation they cost 2 to 12 %: 1024 x 4096, two rows 5.6 -> 6.3 us).
+// That vector meets the row's last eight activations, its entry moved up to them and those of the vector before cleared.
 template <int B, int IB, int RB, int R, bool ANY>
 __global__ __launch_bounds__(WAVES * 64) void gemv_v8_kernel(Params p, const __half *__restrict__ x, long long ldx, __half *__restrict__ y,
                                                              long long ldy) {
@@ -76,7 +71,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_v8_kernel(Params p, const __h
   }
   const half8v ones = {1, 1, 1, 1, 1, 1, 1, 1}, zeros = {0, 0, 0, 0, 0, 0, 0, 0};
   const bool with_bias = p.bias != nullptr;
-  const int cut = p.in_features & 7;              // elements of a cut-off last vector
+  const int missing = -p.in_features & 7;         // elements that the row's last vector is short of
   float acc[R][B], xs[B];
 #pragma unroll
   for (int t = 0; t < B; ++t) {
@@ -107,18 +102,27 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_v8_kernel(Params p, const __h
       for (int q = 0; q < R; ++q) {
         e[u][q] = *reinterpret_cast<const half8v *>(p.cb + (group * p.k + min(i[u][q], (unsigned)p.k - 1u)) * 8);
         if (RB) f[u][q] = *reinterpret_cast<const half8v *>(p.cb_res + (group * p.k_res + min(r[u][q], (unsigned)p.k_res - 1u)) * 8);
-        if (ANY && cut && pvc[u] == p.P - 1) {
-          e[u][q] = first_of(e[u][q], cut);
-          if (RB) f[u][q] = first_of(f[u][q], cut);
+        if (ANY && missing && on[u] && pvc[u] == p.P - 1) {
+          e[u][q] = moved_up(e[u][q], missing);
+          if (RB) f[u][q] = moved_up(f[u][q], missing);
         }
+        if (ANY && !on[u]) e[u][q] = f[u][q] = zeros;      // (zero times an entry that is no number is none)
       }
     }
 #pragma unroll
     for (int u = 0; u < NC; ++u) {
+      uint4v mine;                                // of the activations: none of a lane past the row
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        const int others = !on[u] ? 8 : pvc[u] == p.P - 1 ? missing : 0;
+        mine[d] = others <= 2 * d ? ~0u : others == 2 * d + 1 ? 0xFFFF0000u : 0u;
+      }
 #pragma unroll
       for (int t = 0; t < B; ++t) {
-        half8v xv = ANY ? activations(x + (long long)t * ldx, pvc[u] * 8, p.in_features) : *reinterpret_cast<const half8v *>(x + (long long)t * ldx + (long long)pvc[u] * 8);
-        if (!on[u]) xv = zeros;
+        const __half *xt = x + (long long)t * ldx;
+        half8v xv = ANY ? activations(xt + min(pvc[u] * 8, p.in_features - 8)) : *reinterpret_cast<const half8v *>(xt + (long long)pvc[u] * 8);
+        if (ANY) xv = __builtin_bit_cast(half8v, __builtin_bit_cast(uint4v, xv) & mine);
+        else if (!on[u]) xv = zeros;
 #pragma unroll
         for (int q = 0; q < R; ++q) {
           acc[q][t] = dot8(e[u][q], xv, acc[q][t]);
@@ -152,9 +156,10 @@ int launch_rows(const Params &p, const __half *x, long long ldx, __half *y, long
 
 // Two rows per wave from four tokens and 8192 columns on, where the re-reading of x weighs more than the halved number of
 // waves (batch 8: 8192 x 8192 74 -> 66 us, 8192 x 28672 242 -> 203 us; 4096 x 4096 would go from 22.3 to 23.5 us).
+bool in_pieces_of_sixteen_bytes(const Params &p, const __half *x, long long ldx) { return !((p.in_features & 7) || (reinterpret_cast<uintptr_t>(x) & 15) || (ldx & 7)); }
 template <int B, int IB, int RB>
 int launch_one(const Params &p, const __half *x, long long ldx, __half *y, long long ldy, hipStream_t s) {
-  if ((p.in_features & 7) || (reinterpret_cast<uintptr_t>(x) & 15) || (ldx & 7)) return launch_rows<B, IB, RB, 1, true>(p, x, ldx, y, ldy, s);
+  if (!in_pieces_of_sixteen_bytes(p, x, ldx)) return launch_rows<B, IB, RB, 1, true>(p, x, ldx, y, ldy, s);
   if (B >= 4 && p.in_features >= 8192) return launch_rows<B, IB, RB, (B >= 4 ? 2 : 1), false>(p, x, ldx, y, ldy, s);
   return launch_rows<B, IB, RB, 1, false>(p, x, ldx, y, ldy, s);
 }
@@ -249,16 +254,34 @@ int index_bytes(int bits) { return bits == 8 ? 1 : bits == 16 ? 2 : 0; }
 
 }  // namespace
 
-// Row-wise layers of 8-component vectors with byte-aligned indices, no outlier columns.  (Of any width, x at any half: 3520 x 6586, one row 107
-// us on the generic kernel, 22.  The tables are 16-byte aligned by the descriptor's rules; an index row by its 16-byte stride.)
-bool gemv_v8_applicable(const Params &p, const __half *x, long long ldx) {
-  if (p.orientation != 0 || p.v != 8 || p.Q != 0 || p.n_out != 0) return false;
+// Row-wise layers of 8-component vectors with byte-aligned indices, no outlier columns, of any width from one vector on, x at any half.  (The
+// tables are 16-byte aligned by the descriptor's rules; an index row by its 16-byte stride.)
+static bool rows_applicable(const Params &p) {
+  if (p.orientation != 0 || p.v != 8 || p.Q != 0 || p.n_out != 0 || p.in_features < 8) return false;
   if (!index_bytes(p.bits) || (p.k_res && !index_bytes(p.bits_res))) return false;
   if ((reinterpret_cast<uintptr_t>(p.cb) & 15) || (p.k_res && (reinterpret_cast<uintptr_t>(p.cb_res) & 15))) return false;
   return (p.stride & 1) == 0 && (!p.k_res || (p.stride_res & 1) == 0);
 }
 
-// batch = 1, 2, 4 or 8 rows of x.  The caller has checked gemv_v8_applicable().
+// Whether it is the kernel for them.  Rows that neither end nor begin on sixteen bytes cost it more, and it is only taken where that was faster (570
+// layers of 32 to 16384 outputs and 64 to 16384 columns, 1 to 16 rows):
+//  * both tables in LDS, one group: few outputs, of which the other kernel's workgroups of sixteen rows leave most compute units idle (550 x 3666,
+//    sixteen rows 38 -> 19 us, 959 x 9407, one row 9.5 -> 7.0; but 7214 x 14999, four rows 43 -> 120, 16160 x 330, five 18 -> 48);
+//  * with groups, which that kernel walks with a table at a time or, with a workspace, side by side (without 454 x 7033, four rows 85 -> 11 us,
+//    10676 x 1248, five 87 -> 36, 16166 x 97, four 10 -> 26; with 2346 x 5352, one row 42 -> 11, 3089 x 3560,
+//    three rows 69 -> 22, 10740 x 689, four 13 -> 18, 1532 x 11787, four 19 -> 27);
+//  * a table past LDS, against the generic kernel: all but several rows of a few vectors (3520 x 6586, one row 107 -> 19 us, 1972 x 16081 208 -> 24;
+//    5198 x 113, sixteen rows 27 -> 44).
+bool gemv_lds_applicable(const Params &p, int batch);
+bool gemv_v8_wanted(const Params &p, const __half *x, long long ldx, int batch, bool workspace) {
+  if (!rows_applicable(p)) return false;
+  if (in_pieces_of_sixteen_bytes(p, x, ldx)) return true;
+  if (!gemv_lds_applicable(p, 1)) return p.in_features >= 320 || batch < 3 || p.out_features <= 1024;
+  if (p.n_groups > 1) return p.out_features <= (p.in_features >= 9984 ? 1024 : workspace ? 6144 : 14336);
+  return p.out_features <= 1024 && (p.in_features >= 6144 || (p.in_features >= 1024 && batch >= 2));
+}
+
+// batch = 1, 2, 4 or 8 rows of x.  The caller has checked gemv_v8_wanted().
 int launch_gemv_v8(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, hipStream_t s) {
   const int ib = index_bytes(p.bits), rb = p.k_res ? index_bytes(p.bits_res) : 0;
 #define VQ_CASE(BB, IB, RB) if (batch == BB && ib == IB && rb == RB) return launch_one<BB, IB, RB>(p, x, ldx, y, ldy, s);

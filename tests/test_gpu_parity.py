@@ -1194,3 +1194,31 @@ def test_gemv_v8_rows_of_any_width(gpu_lib, in_features, k, k_res, group_vectors
         y = gpu_lib.gemv(dl, rows)
         torch.cuda.synchronize()
         _check_matmul(y, oracle.gemv(L, x_np), "batch %d, pitch %d" % (batch, pitch))
+
+
+@pytest.mark.parametrize("last", [1, 2, 3, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("batch", [1, 2, 8])
+def test_gemv_v8_last_vector_of_any_length(gpu_lib, last, batch):
+    """Rows that begin at any half, their last vector short of any number of elements: it meets the row's last eight activations.  Neither entries that
+    are infinite past the row nor an infinite activation of the vector before, which one row of the batch has, reach what they are not part of."""
+    import torch
+    inp = 8 * 70 + last
+    L = s.make_layer(322, "v8", 70, inp, 8, 65536, 256)
+    L.codebook[: 65535, last:] = np.inf
+    L.idx.view(np.uint16)[:, :70] = 65535                # the last vector alone names them
+    L.idx.view(np.uint16)[:, 70] %= 65535
+    L.codebook[65535] = np.abs(L.codebook[65535]) + np.float16(0.01)
+    L.codebook_res = np.abs(L.codebook_res)
+    x_np = s.make_activations(322, L, batch)
+    want = oracle.gemv(L, x_np)
+    pitch = inp + 3
+    x = torch.full((batch * pitch + 8,), float("nan"), dtype=torch.float16, device="cuda")
+    rows = x[1: 1 + batch * pitch].view(batch, pitch)[:, :inp]
+    rows.copy_(torch.from_numpy(x_np))
+    dl = gpu_lib.DeviceLayer(L)
+    _check_matmul(gpu_lib.gemv(dl, rows), want, "%d of eight" % last)
+    L.bias = None
+    rows[batch - 1, 8 * 70 - 1] = float("inf")
+    y = gpu_lib.gemv(gpu_lib.DeviceLayer(L), rows).float()
+    torch.cuda.synchronize()
+    assert torch.isinf(y[batch - 1]).all() and torch.isfinite(y[: batch - 1]).all()

@@ -75,3 +75,17 @@ def test_gemv_of_odd_rows_down_the_outputs_in_parts(out, inp, more, permuted):
         assert copied == even and even_pitch == even
         assert any("finish" in name for name, _ in even)
         assert answers[i]["launches"][0]["name"] == "gather_cols_kernel" and (answers[i + 1]["launches"][0]["name"] == "gather_cols_kernel") == permuted
+
+
+@pytest.mark.parametrize("entry,out,inp,rows,more,kernel", [
+    ("gemv", 7214, 14999, 4, {}, "gemv_lds"), ("gemv", 550, 3667, 16, {}, "gemv_v8"), ("gemv", 550, 367, 16, {}, "gemv_lds"),
+    ("gemv", 16166, 97, 4, dict(group_vectors=8), "gemv_lds"), ("gemv", 10676, 1249, 5, dict(group_vectors=16), "gemv_v8"),
+    ("gemv_with_workspace", 10740, 689, 4, dict(group_vectors=40), "gemv_lds"), ("gemv_with_workspace", 2346, 5353, 1, dict(group_vectors=48), "gemv_v8"),
+    ("gemv", 5198, 113, 16, dict(k=65536), "gemv_generic"), ("gemv", 5198, 113, 1, dict(k=65536), "gemv_v8"), ("gemv", 50, 7, 1, dict(k=65536), "gemv_generic"),
+])
+def test_gemv_v8_rows_that_begin_anywhere(entry, out, inp, rows, more, kernel):
+    """Each side of the lines between the lookups through L2 and the kernels that take such rows otherwise."""
+    layer = dict(dict(out_features=out, in_features=inp, v=8, k=256, k_res=256), **more)
+    answer, = launches.run([dict(entry=entry, rows=rows, workspace="asked" if entry != "gemv" else None, layer=layer, pitch=inp)])
+    assert answer["status"] == 0
+    assert all(launch["name"].startswith((kernel, "gemv_groups_finish")) for launch in answer["launches"]), answer
