@@ -141,6 +141,8 @@ int launch_groups_finish(const float *part, const float *part_xs, int n_groups, 
                          hipStream_t s);
 bool gemv_down_mfma_applicable(const Params &p, const __half *x, long long ldx, int batch);
 int gemv_down_mfma_parts(const Params &p);
+float gemv_down_mfma_us(const Params &p, int parts);
+float gemv_down_streams_us(const Params &p, int batch);
 int launch_gemv_down_mfma(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, hipStream_t s,
                           float *part, float *part_xs, int parts);
 
@@ -153,49 +155,42 @@ static bool down_mfma_wanted(const Params &p, const __half *x, long long ldx, in
   const char fk = forced_kernel();
   return fk != 'g' && fk != 'd' && gemv_down_applicable(p, x, ldx) && gemv_down_mfma_applicable(p, x, ldx, batch);
 }
-// Estimates in microseconds, beyond the five of either kernel's start, of 150 layers (300 to 14336 outputs, 1000 to 20000 columns, without
-// and with a residual table).  The matrix-core kernel: a workgroup walks a part of the columns of 16 streams, at the same price for any number of
-// rows; parts are added up by a second launch.  The other one deals single streams out to the whole chip, up to four rows a launch (three
-// are two).  One to four rows without parts, 11008 x 4096: 10.9 against 8.8, 11.4, 20.0, 17.5 us; 4096 x 4096: 10.7 against 6.7, 8.5, 15.0, 12.3;
-// 14336 x 2048: 8.2 against 9.9, 12.3, 22.1, 18.4; 2000 x 20000, three and four rows: 33 against 25 and 29.  With two 4096-entry tables, 4096 x 4096:
-// 18.5 against 10.1, 12.5, 22.4, 24.4.
-static float down_mfma_us(const Params &p, int parts) {
-  const int blocks = (p.S + 15) / 16;
-  return (p.k_res ? 3.0e-3f : 1.4e-3f) * (float)p.P / (float)parts * (float)((blocks * parts + cu_count() - 1) / cu_count()) + (parts > 1 ? 2.1f : 0.0f);
-}
-static float down_streams_us(const Params &p, int batch) {
-  const float vectors = (float)p.S * (float)p.P * 1e-6f;
-  const bool many_columns = p.P >= 8192;                  // (of which fewer rows, or slower ones, fit LDS)
-  if (!p.k_res) return batch == 1 ? (many_columns ? 0.8f : 0.6f) * vectors : batch == 2 ? 0.6f + 1.05f * vectors : batch == 3 ? 6.0f + 2.35f * vectors : 2.4f + 1.9f * vectors;
-  if (many_columns && p.bits_res == 12) return 1.5f * (float)batch * vectors;
-  return batch == 1 ? (many_columns ? 1.5f : 1.05f) * vectors : batch == 2 ? 2.2f + 1.3f * vectors : batch == 3 ? 8.5f + 2.3f * vectors : 4.0f + 3.4f * vectors;
-}
 // With a workspace (column parts, one workgroup per block of 16 streams and part): from two rows on, for any batch when there are codebook
 // groups (16 groups, one row: 15.5 against 17.4 us), and for one row by the estimates (4096 x 4096 8.3 against 6.7 us; 4096 x 11008 10.4
-// against 11.4; not with outlier columns, a set of sums more: 2000 x 20000 20.7 against 18.8).
+// against 11.4).
 // (and for one row of a layer whose activations do not fit the other kernel's LDS beside the tables)
 static bool down_mfma_parts_wanted(const Params &p, const __half *x, long long ldx, int batch) {
   return down_mfma_wanted(p, x, ldx, batch) && (batch >= 2 || p.n_groups > 1 || forced_kernel() == 'm' || !gemv_down_fits(p) ||
-                                                (!p.Q && down_mfma_us(p, gemv_down_mfma_parts(p)) < down_streams_us(p, 1)));
+                                                gemv_down_mfma_us(p, gemv_down_mfma_parts(p)) < gemv_down_streams_us(p, 1));
 }
 static bool down_mfma_alone_wanted(const Params &p, const __half *x, long long ldx, int batch) {
   if (!down_mfma_wanted(p, x, ldx, batch)) return false;
   if (p.n_groups > 1) {
     // groups that a workgroup walks: for one row the kernel that keeps one table in LDS at a time is the other one, which pays more for a
     // group and spreads its streams (four groups, 11008 x 4096 16.7 against 19.1 us, 4096 x 4096 16.7 / 16.0, 4096 x 11008 25.7 / 21.7; sixteen
-    // 45.3 / 50.7)
-    const float groups = (float)p.n_groups * (p.k_res ? 2.0f : 1.0f), vectors = (float)p.S * (float)p.P * 1e-6f;
-    return batch >= 2 || forced_kernel() == 'm' || !gemv_down_lds_applicable(p, 1) ||
-           1.55f * groups + down_mfma_us(p, 1) < 2.5f * groups + (p.k_res ? 1.3f : 0.65f) * vectors;
+    // 45.3 / 50.7); with an 8-bit residual table it is the generic one, which pays nothing for a group (876 x 138, 18 groups 39 / 11, 8 groups 17 / 11)
+    if (batch >= 2 || forced_kernel() == 'm') return true;
+    const float groups = (float)p.n_groups, vectors = (float)p.S * (float)p.P * 1e-6f, walk = gemv_down_mfma_us(p, 1) - 5.0f;
+    if (!gemv_down_lds_applicable(p, 1)) return 1.9f * groups + walk < 1.0f + 0.03f * (float)p.P * std::max(1.0f, 1e-3f * (float)p.S);
+    return (p.k_res ? 3.1f : 1.55f) * groups + walk < (p.k_res ? 5.0f : 2.5f) * groups + (p.k_res ? 1.3f : 0.65f) * vectors;
   }
-  return batch >= 5 || forced_kernel() == 'm' || down_mfma_us(p, 1) < down_streams_us(p, batch);      // (of five rows and more a launch of four is one of two)
+  return batch >= 5 || forced_kernel() == 'm' || gemv_down_mfma_us(p, 1) < gemv_down_streams_us(p, batch);      // (of five rows and more a launch of four is one of two)
 }
 // Whether parts of the columns, which a workspace is there for, are worth the second launch (300 x 1000, two rows 8.5 -> 6.1 us, four 8.1 -> 6.2;
 // 4096 x 4096, two rows, parts 8.4, without 8.6).
 static bool down_mfma_parts_pay(const Params &p, int batch) {
   if (p.n_groups > 1 || forced_kernel() == 'm' || !gemv_down_fits(p)) return true;
-  const float alone = down_mfma_us(p, 1);
-  return down_mfma_us(p, gemv_down_mfma_parts(p)) < (batch <= 4 ? std::min(alone, down_streams_us(p, batch)) : alone);
+  const float alone = gemv_down_mfma_us(p, 1);
+  return gemv_down_mfma_us(p, gemv_down_mfma_parts(p)) < (batch <= 4 ? std::min(alone, gemv_down_streams_us(p, batch)) : alone);
+}
+
+// Rows that begin off sixteen bytes, which only that kernel and the one with a table in LDS at a time take as a rule: the latter where residual tables
+// of 4096 entries leave the other no room for two rows (61 x 10331, eight rows 53 against 70 us, 5602 x 11375, two 36 / 39), and several rows of a
+// few hundred columns with outlier columns (13521 x 366, two 10.9 / 14.9, 4439 x 463, four 12.4 / 13.7).  Of 187 other such calls the time here is
+// 0.79 of that there, one row 0.73.
+static bool down_table_at_a_time(const Params &p, const __half *x, long long ldx, int batch) {
+  if (!((reinterpret_cast<uintptr_t>(x) & 15) || (ldx & 7)) || batch < 2 || forced_kernel() != '\0' || !gemv_down_lds_applicable(p, 1)) return false;
+  return p.k_res ? p.bits_res == 12 && p.P >= 8192 && p.P < 12288 : p.Q && p.P < 1024;
 }
 
 // Estimated time in microseconds of up to sixteen rows on the matrix cores of that orientation with a workspace (the route rules of vq_gemm); 0 for
@@ -203,7 +198,7 @@ static bool down_mfma_parts_pay(const Params &p, int batch) {
 float gemv_down_rows_us(const Params &p, const __half *x, long long ldx) {
   if (p.orientation != 1 || !down_mfma_wanted(p, x, ldx, 16)) return 0.0f;
   const int parts = gemv_down_mfma_parts(p);
-  return 6.0f + std::min(down_mfma_us(p, 1), down_mfma_us(p, parts)) + (p.k_res ? 1.0f : 0.0f) + (p.Q ? 2.0f : 0.0f) + (p.n_groups > 1 ? 3.0f : 0.0f);
+  return 1.0f + std::min(gemv_down_mfma_us(p, 1), gemv_down_mfma_us(p, parts)) + (p.k_res ? 1.0f : 0.0f) + (p.n_groups > 1 ? 3.0f : 0.0f);
 }
 
 bool gemv_rows_applicable(const Params &p);
@@ -315,7 +310,7 @@ int launch_gemv(const Params &p, const __half *x, long long ldx, int batch, __ha
       const int rc = launch_gemv_down_mfma(p, x, ldx, batch, y, ldy, s, nullptr, nullptr, 1);
       if (rc != VQ_ERR_UNSUPPORTED) return rc;
     }
-    if (!force_generic() && p.n_groups == 1 && gemv_down_applicable(p, x, ldx)) {
+    if (!force_generic() && p.n_groups == 1 && gemv_down_applicable(p, x, ldx) && !down_table_at_a_time(p, x, ldx, batch)) {
       // batch rows go in groups of 4, 2 or 1 (fewer when the rows do not fit LDS beside the tables)
       int done = 0, g_max = 4, rc = VQ_OK;
       while (done < batch) {

@@ -436,6 +436,14 @@ static int parts_per_group(const Params &p) {
 }
 int gemv_down_mfma_parts(const Params &p) { return p.n_groups * parts_per_group(p); }
 
+// Estimated time in microseconds of any rows of a layer without codebook groups in `parts` parts, from the same 900 layers as that of the other
+// kernel (vq_gemv_down.hip), 8 % off in the mean: a workgroup's start and its waves' windows, as often as compute units take one; the second launch.
+float gemv_down_mfma_us(const Params &p, int parts) {
+  const int blocks = (p.S + 15) / 16, windows = (p.P + 31) / 32, rounds = (blocks * parts + cu_count() - 1) / cu_count();
+  const int steps = ((windows + parts - 1) / parts + MW - 1) / MW;
+  return 2.5f + (float)rounds * (2.5f + (p.k_res ? 0.68f : 0.33f) * (float)steps) + (parts > 1 ? 2.1f : 0.0f) + (p.Q ? 2.2f : 0.0f);
+}
+
 static int make_plan(const Params &p, long long ldx, int batch, float *part, float *part_xs, int parts, DownMfmaPlan &plan, long long *grid_out) {
   const int blocks = (p.S + 15) / 16, windows = (min(p.P, p.Pg) + 31) / 32;                // windows of the widest group
   if (blocks < 1 || windows < 1) return VQ_ERR_UNSUPPORTED;

@@ -89,3 +89,18 @@ def test_gemv_v8_rows_that_begin_anywhere(entry, out, inp, rows, more, kernel):
     answer, = launches.run([dict(entry=entry, rows=rows, workspace="asked" if entry != "gemv" else None, layer=layer, pitch=inp)])
     assert answer["status"] == 0
     assert all(launch["name"].startswith((kernel, "gemv_groups_finish")) for launch in answer["launches"]), answer
+
+
+@pytest.mark.parametrize("entry,out,inp,rows,pitch,more,kernel", [
+    ("gemv_with_workspace", 76, 15648, 4, 15648, {}, "gemv_groups_finish"), ("gemv_with_workspace", 44, 11397, 4, 11400, dict(n_outlier_cols=32), "gemv_groups_finish"),
+    ("gemv_with_workspace", 184, 13424, 3, 13424, dict(k_res=4096), "gemv_groups_finish"), ("gemv_with_workspace", 2213, 5096, 1, 5096, {}, "gemv_down_v6"),
+    ("gemv", 12798, 816, 1, 816, dict(k_res=256), "gemv_down_mfma"), ("gemv", 2670, 1144, 1, 1144, dict(k_res=256), "gemv_down_v6"),
+    ("gemv", 61, 10331, 8, 10331, dict(k_res=4096), "gemv_down_lds"), ("gemv", 61, 10331, 1, 10331, dict(k_res=4096), "gemv_down_v6"),
+    ("gemv", 13521, 366, 2, 369, dict(n_outlier_cols=20), "gemv_down_lds"), ("gemv", 13521, 366, 2, 369, {}, "gemv_down_v6"),
+    ("gemv", 876, 138, 1, 138, dict(k_res=256, group_vectors=8), "gemv_down_kernel"), ("gemv", 876, 1380, 1, 1384, dict(k_res=256, group_vectors=200), "gemv_down_mfma"),
+])
+def test_gemv_down_takes_the_faster_kernel(entry, out, inp, rows, pitch, more, kernel):
+    """Each side of the lines between the kernels for vectors down the outputs, v = 6."""
+    layer = dict(dict(out_features=out, in_features=inp, orientation=1), **more)
+    answer, = launches.run([dict(entry=entry, rows=rows, pitch=pitch, x=launches.X + (2 if pitch % 8 else 0), workspace="asked" if entry != "gemv" else None, layer=layer)])
+    assert answer["status"] == 0 and answer["launches"][-1]["name"].startswith(kernel), answer
