@@ -406,10 +406,14 @@ bool products_plan(const Params &p, int batch, ProductsPlan *plan) {
   if (switches().gemv || switches().groups_loop || switches().rows >= 0 || switches().products == 0) return false;
   // Two launches, each with a start of its own, want enough vectors to look up.  With codebook groups, where a table a workgroup is the
   // alternative: one row from 2^15 on (512 x 512, 22 thousand: 8.8 us without, 9.0; 256 x 2048, 43 thousand: 9.4, 9.0), two rows from 2^18 (2048 x
-  // 1024, 2^17.4: 11.2, 11.3; 1024 x 4096, 2^18.4: 12.0, 11.5); with one group, where the matrix cores take several rows at the price of
-  // one: one row from 3 x 2^17 on (2048 x 2048, 350 thousand: 9.4, 9.5; 4096 x 4096: 11.1, 10.2), two rows never (11008 x 4096: 16.2, 16.3).
+  // 1024, 2^17.4: 11.2, 11.3; 1024 x 4096, 2^18.4: 12.0, 11.5), with few groups of one table from 2^19 and 2^20 (four, one row, 637 x 3640: 9.0, 9.6;
+  // seven, two rows, 2164 x 3903: 10.5, 12.0); with one group, where the matrix cores take several rows at the price of one, two rows never
+  // (11008 x 4096: 16.2, 16.3), one row with two tables, which those look up one after the other, from 3 x 2^17 on (2048 x 2048, 350 thousand: 9.4, 9.5;
+  // 4096 x 4096: 11.1, 10.2), with one from 9 x 2^19 (6399 x 1052: 6.9, 9.9; 12213 x 4395, 2^22.1: 10.0, 11.4; 5859 x 10344, 2^22.3: 14.8, 11.8).
   const long long vectors = (long long)p.out_features * p.P;
-  if (switches().products < 0 && (p.n_groups > 1 ? vectors < (batch == 1 ? 1 << 15 : 1 << 18) : batch > 1 || vectors < 3 << 17)) return false;
+  const bool few_tables = !p.k_res && p.n_groups <= 8;
+  const long long least = p.n_groups > 1 ? (batch == 1 ? few_tables ? 1 << 19 : 1 << 15 : few_tables ? 1 << 20 : 1 << 18) : p.k_res ? 3 << 17 : 9 << 19;
+  if (switches().products < 0 && (vectors < least || (p.n_groups == 1 && batch > 1))) return false;
   if (p.orientation != 0 || p.v != ENTRY || p.bits != 12 || (p.k_res && p.bits_res != 12) || batch > 2 || cu_count() < 64) return false;
   if (p.n_groups > 1 && p.Pg % 8) return false;                            // (octets begin at a dword of the stream)
   if (p.Q && (p.v_out != 4 || p.k_out > 8192)) return false;

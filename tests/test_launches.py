@@ -104,3 +104,16 @@ def test_gemv_down_takes_the_faster_kernel(entry, out, inp, rows, pitch, more, k
     layer = dict(dict(out_features=out, in_features=inp, orientation=1), **more)
     answer, = launches.run([dict(entry=entry, rows=rows, pitch=pitch, x=launches.X + (2 if pitch % 8 else 0), workspace="asked" if entry != "gemv" else None, layer=layer)])
     assert answer["status"] == 0 and answer["launches"][-1]["name"].startswith(kernel), answer
+
+
+@pytest.mark.parametrize("out,inp,rows,more,products", [
+    (6399, 1052, 1, {}, False), (12213, 4395, 1, {}, False), (5859, 10344, 1, {}, True), (5859, 10344, 2, {}, False), (4096, 4096, 1, dict(k_res=4096), True),
+    (637, 3640, 1, dict(group_vectors=80), False), (1700, 4096, 1, dict(group_vectors=88), True), (637, 3640, 1, dict(group_vectors=32), True),
+    (637, 3640, 1, dict(group_vectors=80, k_res=4096), True), (2164, 3903, 2, dict(group_vectors=48), False), (2164, 3903, 2, dict(group_vectors=16), True),
+    (4096, 4096, 2, dict(group_vectors=48), True),
+])
+def test_gemv_from_tables_of_products_where_they_pay(out, inp, rows, more, products):
+    """Each side of the lines between tables of products and the kernels that look entries up, v = 12."""
+    layer = dict(dict(out_features=out, in_features=inp, v=12), **more)
+    answer, = launches.run([dict(entry="gemv_with_workspace", layer=layer, rows=rows, pitch=(inp + 7) // 8 * 8, workspace="asked")])
+    assert answer["status"] == 0 and answer["launches"][0]["name"].startswith("gemv_products") == products, answer
