@@ -422,24 +422,35 @@ static bool permuted_in_kernel(const Params &p, const __half *x, long long ldx, 
 // The v = 6 / 12-bit kernels want dwords at any number of rows, those along the rows an even width as well: there the copy's next column, zeros,
 // counts as the layer's last (P is the same: an odd width is short of whole vectors).  3520 x 6587, 1 / 4 / 16 rows: 9.7 -> 7.9, 18.3 -> 9.2, 71 -> 11.2 us;
 // down the outputs, in column parts, 4 / 16 rows 20.7 -> 10.5, 80.6 -> 12.4 (without parts 16.0, 17.5).
-static bool even_width_wanted(const Params &p) { return p.orientation == 0 && (p.in_features & 1) && gemv_fast_applicable_even(p); }
+// Not along the rows where the kernels that keep one table in LDS at a time are as fast without the copy (540 layers of 32 to 16384 outputs): short
+// rows, one of which takes them no longer than the copy (12461 x 193 7.4 us, 9.3 with it, 3589 x 557 5.7 / 6.2, 735 x 1089 9.0 / 6.7); and up to two
+// rows with codebook groups, side by side there, four, which they take in one launch, with a residual table, five with outlier columns (two of 12996 x
+// 2263 in 16 groups 21 / 55, of 9283 x 1081 with two tables in 23 37 / 86, four of 2843 x 2455 with two in 18 20 / 23.5, five of 10973 x 1533 in 16 with
+// 16 outlier columns 34 / 51), unless the residual table has 8-bit indices, for which there is only the generic kernel (two of 8181 x 3129 in groups, 0.31 of
+// its time).
+static bool even_width_wanted(const Params &p, int batch) {
+  if (p.orientation != 0 || !(p.in_features & 1) || !gemv_fast_applicable_even(p)) return false;
+  if (p.k_res && p.bits_res == 8) return true;
+  if (p.n_groups > 1) return batch >= (p.Q ? 6 : 3) && !(p.k_res && batch == 4);
+  return p.in_features >= (batch >= 2 ? 300 : p.k_res ? 512 : 1024);
+}
 static size_t stored_order_workspace_bytes(const Params &p, const __half *x, long long ldx, int batch, bool least);
-static Params gathered(const Params &p) {
+static Params gathered(const Params &p, int batch) {
   Params q = p;
   q.perm = nullptr;
-  if (even_width_wanted(p)) ++q.in_features;
+  if (even_width_wanted(p, batch)) ++q.in_features;
   return q;
 }
 // (of 2^17 vectors and more, which take longer than the copy; and not where the copy and the sums are more than vq_gemv_static_workspace has)
 static bool rows_gathered(const Params &p, int batch) {
   if (!(p.in_features & 1) || p.in_features >= (1 << 18) || forced_kernel() != '\0') return false;
   if (batch >= 5 && rows_wanted(p, batch, true)) return true;
-  if ((long long)p.S * p.P < 1 << 17 || !((even_width_wanted(p) && (batch >= 2 || p.n_groups == 1)) || (batch >= 2 && down_mfma_wanted(p, nullptr, p.in_features + 1, batch)))) return false;
-  return permuted_x_bytes(p, batch) + stored_order_workspace_bytes(gathered(p), nullptr, (p.in_features + 7) & ~7, batch, false) <= VQ_GEMV_STATIC_WORKSPACE_BYTES;
+  if ((long long)p.S * p.P < 1 << 17 || !((even_width_wanted(p, batch) && (batch >= 2 || p.n_groups == 1)) || (batch >= 2 && down_mfma_wanted(p, nullptr, p.in_features + 1, batch)))) return false;
+  return permuted_x_bytes(p, batch) + stored_order_workspace_bytes(gathered(p, batch), nullptr, (p.in_features + 7) & ~7, batch, false) <= VQ_GEMV_STATIC_WORKSPACE_BYTES;
 }
 // ... unless the rows can be taken as they are
 static bool taken_as_they_are(const Params &p, const __half *x, long long ldx, int batch) {
-  if (even_width_wanted(p)) return false;
+  if (even_width_wanted(p, batch)) return false;
   return down_mfma_wanted(p, nullptr, p.in_features + 1, batch) ? down_mfma_wanted(p, x, ldx, batch) : gemv_rows_takes(p, x, ldx, batch);
 }
 
@@ -475,7 +486,7 @@ static size_t workspace_bytes_of(const Params &p, const __half *x, long long ldx
   if (force_generic()) return 0;
   if (p.perm || rows_gathered(p, batch)) {
     if (p.perm && permuted_in_kernel(p, x, ldx, batch)) return 0;
-    const Params q = gathered(p);
+    const Params q = gathered(p, batch);
     const size_t head = permuted_x_bytes(p, batch), rest = stored_order_workspace_bytes(q, nullptr, (p.in_features + 7) & ~7, batch, least);
     // (the column parts of vq_gemv_rows.hip are done without where the two together are more than vq_gemv_static_workspace has)
     return rows_wanted(q, batch, true) && head + rest > VQ_GEMV_STATIC_WORKSPACE_BYTES ? head : head + rest;
@@ -513,7 +524,7 @@ static int launch_with_workspace(const Params &p, const __half *x, long long ldx
     const size_t need = workspace_bytes_of(p, x, ldx, batch, least);
     if (!need || !workspace || workspace_bytes < need) return launch_gemv(p, x, ldx, batch, y, ldy, s);
     // gather the activations into stored order, then the layer is an unpermuted one
-    const Params q = gathered(p);
+    const Params q = gathered(p, batch);
     __half *xp = static_cast<__half *>(workspace);
     const long long ldxp = (p.in_features + 7) & ~7;
     // (in one launch of the LDS-table kernel the workgroups gather theirs by themselves: a group's columns, in the shade of its table)

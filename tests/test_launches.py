@@ -106,6 +106,22 @@ def test_gemv_down_takes_the_faster_kernel(entry, out, inp, rows, pitch, more, k
     assert answer["status"] == 0 and answer["launches"][-1]["name"].startswith(kernel), answer
 
 
+@pytest.mark.parametrize("out,inp,rows,more,copied", [
+    (12461, 193, 1, {}, False), (3589, 557, 1, {}, False), (1735, 1089, 1, {}, True), (2759, 513, 1, dict(k_res=4096), True), (2759, 335, 2, {}, True),
+    (9609, 173, 2, {}, False), (12996, 2263, 2, dict(group_vectors=24), False), (12996, 2263, 3, dict(group_vectors=24), True),
+    (12996, 2263, 4, dict(group_vectors=24, n_outlier_cols=4), False), (12996, 2263, 6, dict(group_vectors=24, n_outlier_cols=4), True),
+    (2843, 2455, 4, dict(group_vectors=24, k_res=4096), False), (2843, 2455, 5, dict(group_vectors=24, k_res=4096), True),
+    (8181, 3129, 2, dict(group_vectors=104, k_res=256), True),
+])
+@pytest.mark.parametrize("permuted", [False, True])
+def test_gemv_of_an_odd_width_made_even(out, inp, rows, more, copied, permuted):
+    """Each side of the lines between the kernels of even widths, on a copy, and those that keep a table in LDS at a time."""
+    layer = dict(dict(out_features=out, in_features=inp, col_perm=permuted), **more)
+    answer, = launches.run([dict(entry="gemv_with_workspace", layer=layer, rows=rows, pitch=inp, workspace="asked")])
+    names = [launch["name"] for launch in answer["launches"]]
+    assert answer["status"] == 0 and any(name.startswith("gemv_v6") for name in names) == copied and (not copied or names[0] == "gather_cols_kernel"), names
+
+
 @pytest.mark.parametrize("out,inp,rows,more,products", [
     (6399, 1052, 1, {}, False), (12213, 4395, 1, {}, False), (5859, 10344, 1, {}, True), (5859, 10344, 2, {}, False), (4096, 4096, 1, dict(k_res=4096), True),
     (637, 3640, 1, dict(group_vectors=80), False), (1700, 4096, 1, dict(group_vectors=88), True), (637, 3640, 1, dict(group_vectors=32), True),
