@@ -268,8 +268,8 @@ size_t vq_gemm_fast_workspace_bytes(const vq_layer_desc *desc, int32_t tokens);
  * the latter (layers with v = 6 along the rows that the on-the-fly kernel does not take; up to 128 tokens of the other layers
  * with a vq_gemv kernel of their own, up to 32 of those whose tables fit LDS) the call restores the centroids alone, which
  * are binary16 numbers, main and residual ones apart, and applies scale and bias to the sums; or, where that is faster,
- * runs those kernels with the workspace that they use.  Elsewhere it is vq_gemm with vq_gemm_fast_workspace_bytes.  The size
- * is 0 instead of more than 256 MiB.  With less (or NULL) it is vq_gemm without a workspace.  Arguments, checks and errors
+ * runs those kernels with the workspace that they use.  Elsewhere it is vq_gemm with vq_gemm_fast_workspace_bytes, of
+ * which the size counts what these tokens use.  The size is 0 instead of more than 256 MiB.  With less (or NULL) it is vq_gemm without a workspace.  Arguments, checks and errors
  * are those of vq_gemm; a workspace that is aligned to 16 but not 256 bytes may be left unused.                          */
 size_t vq_gemm_default_workspace_bytes(const vq_layer_desc *desc, int32_t tokens);
 int vq_gemm_default(const vq_layer_desc *desc, const void *X, int64_t ldx, int32_t tokens,

@@ -163,6 +163,7 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(Params p, const __half *
 size_t gemm_workspace_bytes(const Params &, int) { return 0; }
 bool gemm_dense_applicable(const Params &p);
 float gemm_dense_us(const Params &p, int tokens, bool against_rows = false);
+size_t gemm_dense_scratch_bytes(const Params &p, int tokens, int matrices, size_t most);
 
 // Bytes of the FP16 weight matrix [out][in] that the two-step route below writes; 0 when that route does not apply.
 // For a layer with a permuted column order (Sec. 3.2.3) the activations, gathered into stored order, come first: tokens
@@ -270,9 +271,13 @@ static bool centroids_beat_rows(const Params &p, int tokens) {
 
 constexpr size_t MOST_DEFAULT_WORKSPACE = (size_t)256 << 20;
 
-// `bytes` and the sums of a product in parts behind them, or without these `bytes`, or nothing.
-static size_t default_bytes(const Params &p, size_t bytes) {
-  return bytes > MOST_DEFAULT_WORKSPACE ? 0 : bytes + dense_scratch_bytes(p) <= MOST_DEFAULT_WORKSPACE ? bytes + dense_scratch_bytes(p) : bytes;
+// `bytes` and the sums of this product in parts behind them (vq_gemm_fast_workspace_bytes has room for any number of tokens', this one is for one
+// call: 700 x 640, 200 tokens, whose product is not cut, 0.9 MB and not 9.3), or without these `bytes`, or nothing.
+static size_t default_bytes(const Params &p, int tokens, int matrices, size_t bytes) {
+  Params q = p;
+  q.perm = nullptr;                                        // (the product runs on gathered activations)
+  const size_t most = dense_scratch_bytes(p), sums = most ? gemm_dense_scratch_bytes(q, tokens, matrices, most) : 0;
+  return bytes > MOST_DEFAULT_WORKSPACE ? 0 : bytes + sums <= MOST_DEFAULT_WORKSPACE ? bytes + sums : bytes;
 }
 
 static bool centroids_wanted(const Params &p, int tokens) {
@@ -322,8 +327,8 @@ static int launch_gemm_rows(const Params &p, const __half *X, long long ldx, int
 // nothing beyond 256 MiB (W of 11008 x 11008), so that who leaves the workspace out to save memory still does
 // where it counts (8192 x 28672, 448 MiB, 512 tokens: 532 us with it, 582 without).
 size_t gemm_default_workspace_bytes(const Params &p, int tokens) {
-  if (centroids_wanted(p, tokens)) return default_bytes(p, centroids_workspace_bytes(p, tokens));
-  if (!rows_hold_the_weights(p, tokens) && gemm_dense_applicable(p)) return default_bytes(p, gemm_fast_workspace_bytes(p, tokens) - dense_scratch_bytes(p));
+  if (centroids_wanted(p, tokens)) return default_bytes(p, tokens, p.k_res ? 2 : 1, centroids_workspace_bytes(p, tokens));
+  if (!rows_hold_the_weights(p, tokens) && gemm_dense_applicable(p)) return default_bytes(p, tokens, 1, gemm_fast_workspace_bytes(p, tokens) - dense_scratch_bytes(p));
   const size_t bytes = rows_hold_the_weights(p, tokens) ? gemv_workspace_bytes(p, nullptr, (p.in_features + 7) & ~7, tokens < 16 ? tokens : 16)
                                                         : gemm_fast_workspace_bytes(p, tokens);
   return bytes <= MOST_DEFAULT_WORKSPACE ? bytes : 0;

@@ -338,9 +338,10 @@ struct Cut {
   const TileKind *kind;
   int parts, per;
   float us;
+  size_t bytes;                                    // of scratch with which the choice is this one
 };
 Cut cut_columns(int tokens, int out_features, int steps, size_t scratch_bytes, float least) {
-  Cut best = {nullptr, 1, steps, least};
+  Cut best = {nullptr, 1, steps, least, 0};
   const size_t part_bytes = (size_t)tokens * (size_t)out_features * sizeof(float);
   if (part_bytes * 2 <= scratch_bytes)
     for (const TileKind &k : kTiles) {
@@ -349,16 +350,36 @@ Cut cut_columns(int tokens, int out_features, int steps, size_t scratch_bytes, f
         if (n > steps / 2 || part_bytes * (size_t)n > scratch_bytes) break;
         const int per = (steps + n - 1) / n, parts = (steps + per - 1) / per;
         const float us = tile_cost(k, tokens, out_features, steps, cu_count(), parts) + 3.0f + (float)((double)part_bytes * 2 * parts / 5e6);
-        if (us < best.us) best = {&k, parts, per, us};
+        if (us < best.us) best = {&k, parts, per, us, part_bytes * (size_t)n};
       }
     }
   return best;
+}
+
+const TileKind *least_kind(int tokens, int out_features, int steps, bool cached) {
+  const TileKind *best = &kTiles[sizeof(kTiles) / sizeof(kTiles[0]) - 1];
+  for (const TileKind &k : kTiles)
+    if ((cached || !k.cached) && tile_cost(k, tokens, out_features, steps, cu_count()) < tile_cost(*best, tokens, out_features, steps, cu_count())) best = &k;
+  return best;
+}
+int steps_of(const Params &p, int matrices) { return (p.in_features + DBK - 1) / DBK * matrices; }
+Cut cut_of(const TileKind &whole, int tokens, int out_features, int steps, int matrices, size_t scratch_bytes) {
+  return cut_columns(tokens, out_features, steps, scratch_bytes, tile_cost(whole, tokens, out_features, steps, cu_count()) - (matrices > 1 ? 4.0f : 1.0f));
 }
 
 }  // namespace
 
 bool dequant_leaves_cached(const Params &p, int product_tokens, int matrices);
 bool gemm_dense_applicable(const Params &p) { return p.in_features % 8 == 0; }       // (16-byte chunks of W's rows)
+
+// What launch_gemm_dense uses of `most` bytes of scratch for these tokens (0: the columns stay whole); with that much it makes the same choice.
+// (A product that goes in several launches, of 2 GiB of X or W, has more tiles than any that is cut.)
+size_t gemm_dense_scratch_bytes(const Params &p, int tokens, int matrices, size_t most) {
+  if (!gemm_dense_applicable(p) || switches().dense >= 0) return 0;
+  const int steps = steps_of(p, matrices);
+  const Cut cut = cut_of(*least_kind(tokens, p.out_features, steps, dequant_leaves_cached(p, tokens, matrices)), tokens, p.out_features, steps, matrices, most);
+  return cut.kind ? (cut.bytes + 255) / 256 * 256 : 0;
+}
 
 // The tile shape with the least estimated time, and with `scratch` (16-byte aligned, for the sums) the parts of the columns.  Switch
 // dense=0 / =n: always the last one / number n of the list and whole columns, for tests.  With xsum, the
@@ -371,20 +392,16 @@ int launch_gemm_dense(const Params &p, const __half *X, long long ldx, int token
   const long long room = 1LL << 31, pad = 256;
   const long long most_tokens = std::min(room / (ldx * 2), (room * 2 - 4096) / (ldy * 2)) - pad, most_out = (room - w2) / (ldw * 2) - pad;
   if (most_tokens < 1 || most_out < 1) return VQ_ERR_UNSUPPORTED;
-  const int force = switches().dense;
-  const bool cached = dequant_leaves_cached(p, tokens, w2 ? 2 : 1);
-  const int steps = (p.in_features + DBK - 1) / DBK * (w2 ? 2 : 1);
+  const int force = switches().dense, matrices = w2 ? 2 : 1, steps = steps_of(p, matrices);
+  const bool cached = dequant_leaves_cached(p, tokens, matrices);
   for (long long o = 0; o < p.out_features; o += most_out)
     for (long long t = 0; t < tokens; t += most_tokens) {
       const int nt = (int)std::min<long long>(most_tokens, tokens - t), no = (int)std::min<long long>(most_out, p.out_features - o);
       constexpr int kinds = sizeof(kTiles) / sizeof(kTiles[0]);
-      const TileKind *best = &kTiles[force > 0 && force <= kinds ? force - 1 : kinds - 1];
-      if (force < 0)
-        for (const TileKind &k : kTiles)
-          if ((cached || !k.cached) && tile_cost(k, nt, no, steps, cu_count()) < tile_cost(*best, nt, no, steps, cu_count())) best = &k;
+      const TileKind *best = force < 0 ? least_kind(nt, no, steps, cached) : &kTiles[force > 0 && force <= kinds ? force - 1 : kinds - 1];
       DenseArgs a = {X + t * ldx, ldx, nt, Wd + o * ldw, ldw, no, p.in_features, Y + t * ldy + o, ldy, 0, 0, w2,
                      p.scale ? p.scale + o : nullptr, p.bias ? p.bias + o : nullptr, xsum ? xsum + t : nullptr, static_cast<float *>(scratch), 1, steps};
-      const Cut cut = scratch && force < 0 ? cut_columns(nt, no, steps, scratch_bytes, tile_cost(*best, nt, no, steps, cu_count()) - (w2 ? 4.0f : 1.0f)) : Cut{};
+      const Cut cut = scratch && force < 0 ? cut_of(*best, nt, no, steps, matrices, scratch_bytes) : Cut{};
       if (cut.kind) { a.parts = cut.parts; a.per = cut.per; }
       const int rc = cut.kind ? cut.kind->split(a, s) : best->launch(a, s);
       if (rc != VQ_OK) return rc;

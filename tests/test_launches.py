@@ -133,3 +133,28 @@ def test_gemv_from_tables_of_products_where_they_pay(out, inp, rows, more, produ
     layer = dict(dict(out_features=out, in_features=inp, v=12), **more)
     answer, = launches.run([dict(entry="gemv_with_workspace", layer=layer, rows=rows, pitch=(inp + 7) // 8 * 8, workspace="asked")])
     assert answer["status"] == 0 and answer["launches"][0]["name"].startswith("gemv_products") == products, answer
+
+
+def test_gemm_default_asks_for_the_sums_that_it_writes():
+    """Beside the restored matrix only the sums of a product that is cut: 8 MiB more once stood there whatever the tokens."""
+    rng = random.Random(5)
+    calls = [dict(entry="gemm_default", rows=200, workspace="asked", layer=dict(out_features=700, in_features=640))]
+    for _ in range(400):
+        v, k = rng.choice([(6, 4096), (12, 4096), (8, 65536), (4, 256)])
+        layer = dict(out_features=round(2 ** rng.uniform(6, 13.2)), in_features=round(2 ** rng.uniform(3, 10)) * 8 + 256, v=v, k=k, k_res=rng.choice([0, 0, 256]),
+                     orientation=rng.randint(0, 1), col_perm=rng.random() < 0.3)
+        calls.append(dict(entry="gemm_default", rows=round(2 ** rng.uniform(4.1, 11)), workspace="asked", layer=layer))
+    answers = launches.run(calls)
+    more = launches.run([dict(call, workspace=answer["asked"] + (8 << 20)) for call, answer in zip(calls, answers)])
+    whole = cut = 0
+    for call, answer, with_more in zip(calls, answers, more):
+        names = [launch["name"] for launch in answer["launches"]]
+        assert answer["status"] == 0 and (answer["launches"] == with_more["launches"] or not any("gemm_dense" in launch["name"] for launch in with_more["launches"])), call
+        if "gemm_dense_finish_kernel" in names:
+            cut += 1
+        elif any(name.startswith("gemm_dense_kernel") for name in names):
+            whole += 1
+            d, tokens = call["layer"], call["rows"]
+            matrices = 2 if d.get("k_res") else 1
+            assert answer["asked"] <= matrices * (d["out_features"] * d["in_features"] * 2 + 256) + tokens * (4 + d["in_features"] * 2 * d.get("col_perm", 0)) + 512, call
+    assert whole > 100 and cut > 30
