@@ -605,12 +605,12 @@ static int launch_stored_order(const Params &p, const __half *x, long long ldx, 
 
 int launch_gemv_ws(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, void *workspace,
                    size_t workspace_bytes, hipStream_t s) {
-  if (workspace) {
+  const long long even = p.in_features + (p.in_features & 1);
+  const bool enough = workspace && workspace_bytes >= gemv_workspace_bytes(p, nullptr, even, batch);
+  if (enough) {
     const int rc = launch_gemv_products(p, x, ldx, batch, y, ldy, workspace, workspace_bytes, s);
     if (rc != VQ_ERR_UNSUPPORTED) return rc;
   }
-  const long long even = p.in_features + (p.in_features & 1);
-  const bool enough = workspace && workspace_bytes >= gemv_workspace_bytes(p, nullptr, even, batch);
   // less than vq_gemv_workspace_bytes asks for, though not for these rows alone: vq_gemv
   if (workspace && !enough && workspace_bytes >= workspace_bytes_of(p, nullptr, even, batch, false)) return launch_gemv(p, x, ldx, batch, y, ldy, s);
   // (rows of an odd width may go to other kernels than the size was asked for, which make do with what it is)

@@ -158,3 +158,18 @@ def test_gemm_default_asks_for_the_sums_that_it_writes():
             matrices = 2 if d.get("k_res") else 1
             assert answer["asked"] <= matrices * (d["out_features"] * d["in_features"] * 2 + 256) + tokens * (4 + d["in_features"] * 2 * d.get("col_perm", 0)) + 512, call
     assert whole > 100 and cut > 30
+
+
+@pytest.mark.parametrize("out,inp,rows,more", [
+    (2872, 3616, 1, dict(group_vectors=16, col_perm=True)), (5315, 936, 2, dict(group_vectors=8, col_perm=True)),
+    (7812, 592, 2, dict(group_vectors=8, k_res=4096, n_outlier_cols=16, col_perm=True)), (1024, 4096, 1, dict(group_vectors=88, k_res=4096)),
+    (5859, 10344, 1, {}),
+])
+def test_gemv_with_less_than_it_asks_for_is_gemv(out, inp, rows, more):
+    """Tables of products take a part of a workspace that other kernels ask more of; with no more than that part the call is vq_gemv."""
+    layer = dict(dict(out_features=out, in_features=inp, v=12), **more)
+    call = dict(entry="gemv_with_workspace", layer=layer, rows=rows, pitch=inp)
+    enough, plain = launches.run([dict(call, workspace="asked"), dict(call, entry="gemv")])
+    assert enough["launches"][0]["name"].startswith("gemv_products")
+    less, = launches.run([dict(call, workspace=enough["asked"] - 256)])
+    assert [launch["name"] for launch in less["launches"]] == [launch["name"] for launch in plain["launches"]]
