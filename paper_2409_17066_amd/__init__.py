@@ -58,6 +58,8 @@ def load():
     L.vq_gemv.argtypes = [P, ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32, ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p]
     L.vq_gemv_workspace_bytes.argtypes = [P, ctypes.c_int32]
     L.vq_gemv_workspace_bytes.restype = ctypes.c_size_t
+    L.vq_lend_gemv_bytes.argtypes = [P, ctypes.c_int32]              # (csrc/vq_lend.h)
+    L.vq_lend_gemv_bytes.restype = ctypes.c_size_t
     L.vq_gemv_with_workspace.argtypes = [P, ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32, ctypes.c_void_p, ctypes.c_int64,
                                          ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
     L.vq_gemv_static_workspace.argtypes = L.vq_gemv.argtypes
@@ -195,7 +197,7 @@ def _native():
         from . import _binding as b
         b.bind({name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value
                 for name in ("vq_gemv", "vq_gemv_with_workspace", "vq_gemv_multi", "vq_gemm", "vq_gemm_default", "vq_gemm_workspace_bytes",
-                             "vq_gemm_default_workspace_bytes", "vq_gemv_workspace_bytes", "vq_dequant", "vq_assign", "vq_assign_down")})
+                             "vq_gemm_default_workspace_bytes", "vq_lend_gemv_bytes", "vq_dequant", "vq_assign", "vq_assign_down")})
         _bound = b
     return _bound
 
@@ -275,8 +277,8 @@ def dequant(dl: DeviceLayer, ldw=None):
 def gemv(dl: DeviceLayer, x, out=None, workspace=None):
     """x: fp16 [batch][>=in] device tensor -> fp16 [batch][out].  workspace: a uint8 device tensor; "fast" allocates the one
     vq_gemv_workspace_bytes asks for, if any (torch's allocator hands it out and takes it back in stream order), and so does
-    None except for layers with codebook groups and v = 6 / 12-bit ones in stored order, whose kernels without one sum in the order of gemv_multi; an empty tensor leaves
-    the library without."""
+    None except for layers with codebook groups and v = 6 / 12-bit ones in stored order, whose kernels without one sum in the order of gemv_multi
+    (v = 6 rows of an odd width: in that of a workspace); an empty tensor leaves the library without."""
     y = (_bound or _native()).gemv(dl, x, out, workspace)
     if y.__class__ is int:
         raise VQError(y, "vq_gemv")
@@ -286,9 +288,7 @@ def gemv(dl: DeviceLayer, x, out=None, workspace=None):
     assert x.is_cuda and x.dtype == torch.float16 and x.dim() == 2 and x.stride(1) == 1
     y = out if out is not None else torch.empty((x.shape[0], dl.layer.out_features), dtype=torch.float16, device="cuda")
     if workspace is None:
-        L = dl.layer
-        plain = L.group_vectors or (L.v == 6 and L.k > 2048 and getattr(L, "col_perm", None) is None)
-        workspace = None if plain else _borrow(vq_gemv_workspace_bytes(dl.desc, x.shape[0]))
+        workspace = _borrow(load().vq_lend_gemv_bytes(ctypes.byref(dl.desc), x.shape[0]))
     if workspace is None:
         rc = vq_gemv(dl.desc, x.data_ptr(), x.stride(0), x.shape[0], y.data_ptr(), y.stride(0), _stream())
     else:

@@ -12,12 +12,13 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "../../include/vq.h"
+#include "vq_lend.h"
 
 namespace {
 
 decltype(&vq_gemv) p_gemv;
 decltype(&vq_gemv_with_workspace) p_gemv_ws;
-decltype(&vq_gemv_workspace_bytes) p_gemv_workspace_bytes;
+decltype(&vq_lend_gemv_bytes) p_lend_gemv_bytes;
 decltype(&vq_gemv_multi) p_gemv_multi;
 decltype(&vq_gemm) p_gemm, p_gemm_default;
 decltype(&vq_gemm_workspace_bytes) p_gemm_workspace_bytes, p_gemm_default_workspace_bytes;
@@ -96,10 +97,8 @@ void *borrow(at::TensorBase &scratch, size_t bytes) {
     return nullptr;                                         \
   }
 
-// Whether gemv() without a workspace borrows one: not for layers with codebook groups, nor for v = 6 / 12-bit layers in stored order:
-// their kernels without one are good, and sum in the same order with gemv_multi() or a workspace that is too small.
-// But for rows of an odd width, which those kernels take from a copy.
-bool lends_workspace(const vq_layer_desc &d) { return (!d.group_vectors && (d.v != 6 || d.k <= 2048 || d.col_perm)) || (d.v == 6 && (d.in_features & 1)); }
+// Whether gemv() without a workspace may borrow one (vq_lend.h says how much): the layers that never do are spared the question.
+bool may_borrow(const vq_layer_desc &d) { return (!d.group_vectors && (d.v != 6 || d.k <= 2048 || d.col_perm)) || (d.v == 6 && (d.in_features & 1)); }
 
 // gemv(layer, x, out or None, workspace or None)
 PyObject *gemv(PyObject *, PyObject *const *args, Py_ssize_t n) {
@@ -129,7 +128,7 @@ PyObject *gemv(PyObject *, PyObject *const *args, Py_ssize_t n) {
     void *wp = ws.data_ptr();
     const size_t bytes = (size_t)ws.numel();
     rc = released([&] { return p_gemv_ws(d, xp, ldx, batch, yp, ldy, wp, bytes, s); });
-  } else if (const size_t bytes = lends_workspace(*d) ? p_gemv_workspace_bytes(d, batch) : 0) {
+  } else if (const size_t bytes = may_borrow(*d) ? p_lend_gemv_bytes(d, batch) : 0) {
     at::TensorBase scratch;
     void *wp = borrow(scratch, bytes);
     rc = released([&] { return p_gemv_ws(d, xp, ldx, batch, yp, ldy, wp, wp ? bytes : 0, s); });
@@ -267,7 +266,7 @@ PyObject *bind(PyObject *, PyObject *addresses) {
     return f != nullptr;
   };
   if (!at("vq_gemv", p_gemv) || !at("vq_gemv_with_workspace", p_gemv_ws) || !at("vq_gemv_multi", p_gemv_multi) || !at("vq_gemm", p_gemm) || !at("vq_gemm_default", p_gemm_default) ||
-      !at("vq_gemm_workspace_bytes", p_gemm_workspace_bytes) || !at("vq_gemv_workspace_bytes", p_gemv_workspace_bytes) || !at("vq_gemm_default_workspace_bytes", p_gemm_default_workspace_bytes) ||
+      !at("vq_gemm_workspace_bytes", p_gemm_workspace_bytes) || !at("vq_lend_gemv_bytes", p_lend_gemv_bytes) || !at("vq_gemm_default_workspace_bytes", p_gemm_default_workspace_bytes) ||
        !at("vq_dequant", p_dequant) || !at("vq_assign", p_assign) || !at("vq_assign_down", p_assign_down)) {
     if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "an entry point is missing");
     return nullptr;

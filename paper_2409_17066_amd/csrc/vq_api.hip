@@ -1,5 +1,6 @@
 // C-ABI entry points: descriptor validation and dispatch.  All device work is in the kernel files.
 #include "vq_common.hpp"
+#include "vq_lend.h"
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
@@ -156,6 +157,14 @@ extern "C" size_t vq_gemv_workspace_bytes(const vq_layer_desc *desc, int32_t bat
   if (vq::make_params(desc, &p) != VQ_OK || batch < 1 || batch > 16) return 0;
   // the size does not depend on x; the fast kernels' conditions on x are checked again at the call
   return vq::gemv_workspace_bytes(p, nullptr, p.in_features + (p.in_features & 1), batch);
+}
+
+extern "C" size_t vq_lend_gemv_bytes(const vq_layer_desc *desc, int32_t batch) {
+  vq::read_switches();
+  vq::Params p;
+  if (vq::make_params(desc, &p) != VQ_OK || batch < 1 || batch > 16) return 0;
+  const bool plain = desc->group_vectors || (p.v == 6 && p.k > 2048 && !p.perm), odd = p.v == 6 && (p.in_features & 1);
+  return plain && !odd ? 0 : vq::gemv_lent_bytes(p, batch);
 }
 
 extern "C" int vq_gemv_with_workspace(const vq_layer_desc *desc, const void *x, int64_t ldx, int32_t batch, void *y, int64_t ldy,

@@ -67,6 +67,7 @@ int launch_dequant(const Params &p, __half *W, long long ldw, hipStream_t s, int
 int launch_gemv(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, hipStream_t s);
 bool gemv_has_fast_kernel(const Params &p, const __half *x, long long ldx);
 size_t gemv_workspace_bytes(const Params &p, const __half *x, long long ldx, int batch);
+size_t gemv_lent_bytes(const Params &p, int batch);
 int launch_gemv_ws(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, void *workspace,
                    size_t workspace_bytes, hipStream_t s);
 int launch_gemv_multi(const Params *ps, int n, const __half *x, long long ldx, int batch, __half *const *ys, const long long *ldys,

@@ -513,6 +513,13 @@ size_t gemv_workspace_bytes(const Params &p, const __half *x, long long ldx, int
   return bytes;
 }
 
+// The same for one call of exactly these rows, to which nothing is lent that its kernels leave alone (v = 12, two tables, two rows and more: tables
+// of products are one row's; 11008 x 4096, 16 rows: 1.9 MB).
+size_t gemv_lent_bytes(const Params &p, int batch) {
+  const long long ldx = p.in_features + (p.in_features & 1);
+  return gemv_products_workspace_bytes(p, batch) || workspace_bytes_of(p, nullptr, ldx, batch, false) ? gemv_workspace_bytes(p, nullptr, ldx, batch) : 0;
+}
+
 // Sums of `slots` parts, groups or tables, and those of the activations, in front of a second launch that adds them up.
 static size_t sums_bytes(const Params &p, size_t slots, int batch) { return slots * ((size_t)batch * (size_t)p.out_features + 16) * sizeof(float); }
 

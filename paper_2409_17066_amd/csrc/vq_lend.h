@@ -1,0 +1,19 @@
+/* What the torch conveniences (binding.cpp, __init__.py) lend a call that was given no workspace, for that call alone.  Exported for them by libvq.so;
+ * no part of the library's interface. */
+#ifndef VQ_LEND_H
+#define VQ_LEND_H
+#include "../../include/vq.h"
+
+#ifdef __cplusplus
+extern "C" {
+#endif
+
+/* Of vq_gemv_with_workspace.  0 where no kernel of exactly these rows would use it, and for layers with codebook groups and v = 6 / 12-bit layers in
+ * stored order: their kernels without one are good, and sum in the same order with vq_gemv_multi or a workspace that is too small.  Of v = 6 rows of an
+ * odd width, which those kernels take far more slowly than a copy of them, or than group by group, that order is given up. */
+size_t vq_lend_gemv_bytes(const vq_layer_desc *desc, int32_t batch);
+
+#ifdef __cplusplus
+}
+#endif
+#endif

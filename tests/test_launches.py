@@ -173,3 +173,22 @@ def test_gemv_with_less_than_it_asks_for_is_gemv(out, inp, rows, more):
     assert enough["launches"][0]["name"].startswith("gemv_products")
     less, = launches.run([dict(call, workspace=enough["asked"] - 256)])
     assert [launch["name"] for launch in less["launches"]] == [launch["name"] for launch in plain["launches"]]
+
+
+def test_gemv_borrows_only_what_its_rows_use():
+    """gemv() without a workspace: none for tables of products that only fewer rows take; with v = 6 and an odd width what a workspace is good for."""
+    wide = dict(out_features=11008, in_features=4096, v=12, k_res=4096)
+    calls = [dict(entry="gemv_with_workspace", layer=wide, rows=rows, pitch=4096, workspace="lent") for rows in (1, 2, 16)]
+    calls += [dict(entry="gemv_with_workspace", layer=dict(out_features=128, in_features=28672, v=12), rows=16, pitch=28672, workspace="lent")]
+    rng = random.Random(9)
+    for _ in range(300):
+        layer = dict(_layer(rng, 1), v=6, k=rng.choice([4096, 256]), k_res=rng.choice([0, 256, 4096]), col_perm=False)
+        calls.append(dict(entry="gemv_with_workspace", layer=layer, rows=rng.randint(1, 16), workspace="lent", pitch=layer["in_features"]))
+    one, two, sixteen, narrow, *odd = launches.run(calls)
+    assert one["lent"] and one["launches"][0]["name"].startswith("gemv_products") and not two["lent"] and not sixteen["lent"] and narrow["lent"]
+    plain = launches.run([dict(call, entry="gemv", workspace=None) for call in calls[4:]])
+    asked = launches.run([dict(call, workspace="asked") for call in calls[4:]])
+    assert [answer["launches"] for answer in odd] == [answer["launches"] for answer in asked]
+    unused = [call for call, answer, without in zip(calls[4:], odd, plain) if answer["lent"] and answer["launches"] == without["launches"]]
+    # (of some layers of few vectors the size is asked for, for activations that begin elsewhere)
+    assert sum(answer["lent"] > 0 for answer in odd) > 100 and len(unused) < 20
