@@ -77,6 +77,8 @@ def load():
     L.vq_gemm_fast_workspace_bytes.restype = ctypes.c_size_t
     L.vq_gemm_default_workspace_bytes.argtypes = [P, ctypes.c_int32]
     L.vq_gemm_default_workspace_bytes.restype = ctypes.c_size_t
+    L.vq_lend_gemm_least_bytes.argtypes = [P, ctypes.c_int32]
+    L.vq_lend_gemm_least_bytes.restype = ctypes.c_size_t
     L.vq_quantize_columns_workspace_bytes.argtypes = [ctypes.c_int32] * 4
     L.vq_quantize_columns_workspace_bytes.restype = ctypes.c_size_t
     L.vq_quantize_columns.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, ctypes.c_void_p, ctypes.c_int64,
@@ -197,7 +199,7 @@ def _native():
         from . import _binding as b
         b.bind({name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value
                 for name in ("vq_gemv", "vq_gemv_with_workspace", "vq_gemv_multi", "vq_gemm", "vq_gemm_default", "vq_gemm_workspace_bytes",
-                             "vq_gemm_default_workspace_bytes", "vq_lend_gemv_bytes", "vq_dequant", "vq_assign", "vq_assign_down")})
+                             "vq_gemm_default_workspace_bytes", "vq_lend_gemv_bytes", "vq_lend_gemm_least_bytes", "vq_dequant", "vq_assign", "vq_assign_down")})
         _bound = b
     return _bound
 
@@ -400,7 +402,11 @@ def gemm(dl: DeviceLayer, X, out=None, workspace=None):
     Y = out if out is not None else torch.empty((X.shape[0], dl.layer.out_features), dtype=torch.float16, device="cuda")
     call = vq_gemm
     if workspace is None and X.shape[0] > 8:
-        call, workspace = vq_gemm_default, _borrow(vq_gemm_default_workspace_bytes(dl.desc, X.shape[0]))
+        call, bytes_ = vq_gemm_default, vq_gemm_default_workspace_bytes(dl.desc, X.shape[0])
+        workspace = _borrow(bytes_)
+        least = load().vq_lend_gemm_least_bytes(ctypes.byref(dl.desc), X.shape[0]) if bytes_ and workspace is None else bytes_
+        if least < bytes_:
+            workspace = _borrow(least)
     elif isinstance(workspace, str):
         assert workspace == "fast"
         fast = vq_gemm_fast_workspace_bytes(dl.desc, X.shape[0])

@@ -21,7 +21,7 @@ decltype(&vq_gemv_with_workspace) p_gemv_ws;
 decltype(&vq_lend_gemv_bytes) p_lend_gemv_bytes;
 decltype(&vq_gemv_multi) p_gemv_multi;
 decltype(&vq_gemm) p_gemm, p_gemm_default;
-decltype(&vq_gemm_workspace_bytes) p_gemm_workspace_bytes, p_gemm_default_workspace_bytes;
+decltype(&vq_gemm_workspace_bytes) p_gemm_workspace_bytes, p_gemm_default_workspace_bytes, p_lend_gemm_least_bytes;
 decltype(&vq_dequant) p_dequant;
 decltype(&vq_assign) p_assign, p_assign_down;
 
@@ -188,7 +188,10 @@ PyObject *gemm(PyObject *, PyObject *const *args, Py_ssize_t n) {
     bytes = (size_t)ws.numel() * ws.element_size();
   } else if (tokens > 8) {
     call = p_gemm_default;
-    if ((bytes = p_gemm_default_workspace_bytes(d, tokens)) != 0 && !(wp = borrow(scratch, bytes))) bytes = 0;
+    if ((bytes = p_gemm_default_workspace_bytes(d, tokens)) != 0 && !(wp = borrow(scratch, bytes))) {
+      const size_t least = p_lend_gemm_least_bytes(d, tokens);
+      bytes = least < bytes && (wp = borrow(scratch, least)) ? least : 0;
+    }
   }
   if (p_gemm_workspace_bytes(d, tokens) > bytes) Py_RETURN_NONE;
   at::TensorBase fresh;
@@ -267,6 +270,7 @@ PyObject *bind(PyObject *, PyObject *addresses) {
   };
   if (!at("vq_gemv", p_gemv) || !at("vq_gemv_with_workspace", p_gemv_ws) || !at("vq_gemv_multi", p_gemv_multi) || !at("vq_gemm", p_gemm) || !at("vq_gemm_default", p_gemm_default) ||
       !at("vq_gemm_workspace_bytes", p_gemm_workspace_bytes) || !at("vq_lend_gemv_bytes", p_lend_gemv_bytes) || !at("vq_gemm_default_workspace_bytes", p_gemm_default_workspace_bytes) ||
+      !at("vq_lend_gemm_least_bytes", p_lend_gemm_least_bytes) ||
        !at("vq_dequant", p_dequant) || !at("vq_assign", p_assign) || !at("vq_assign_down", p_assign_down)) {
     if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "an entry point is missing");
     return nullptr;

@@ -264,7 +264,14 @@ extern "C" size_t vq_gemm_default_workspace_bytes(const vq_layer_desc *desc, int
   vq::read_switches();
   vq::Params p;
   if (vq::make_params(desc, &p) != VQ_OK || tokens < 1) return 0;
-  return vq::gemm_default_workspace_bytes(p, tokens);
+  return vq::gemm_default_workspace_bytes(p, tokens, true);
+}
+
+extern "C" size_t vq_lend_gemm_least_bytes(const vq_layer_desc *desc, int32_t tokens) {
+  vq::read_switches();
+  vq::Params p;
+  if (vq::make_params(desc, &p) != VQ_OK || tokens < 1) return 0;
+  return vq::gemm_default_workspace_bytes(p, tokens, false);
 }
 
 namespace vq {

@@ -89,7 +89,7 @@ int launch_quantize_columns(float *W, long long ldw, int rows, int cols, const f
                             long long idx_res_stride, float *T, long long ldt, void *workspace, hipStream_t st);
 size_t gemm_workspace_bytes(const Params &p, int tokens);
 size_t gemm_fast_workspace_bytes(const Params &p, int tokens);
-size_t gemm_default_workspace_bytes(const Params &p, int tokens);
+size_t gemm_default_workspace_bytes(const Params &p, int tokens, bool sums);
 int launch_gemm_default(const Params &p, const __half *X, long long ldx, int tokens, __half *Y, long long ldy, void *workspace, size_t workspace_bytes,
                         hipStream_t s);
 

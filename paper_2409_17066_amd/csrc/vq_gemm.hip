@@ -272,11 +272,11 @@ static bool centroids_beat_rows(const Params &p, int tokens) {
 constexpr size_t MOST_DEFAULT_WORKSPACE = (size_t)256 << 20;
 
 // `bytes` and the sums of this product in parts behind them (vq_gemm_fast_workspace_bytes has room for any number of tokens', this one is for one
-// call: 700 x 640, 200 tokens, whose product is not cut, 0.9 MB and not 9.3), or without these `bytes`, or nothing.
+// call: 700 x 640, 200 tokens, whose product is not cut, 0.9 MB and not 9.3), or without these `bytes`, or nothing.  tokens = 0: no sums.
 static size_t default_bytes(const Params &p, int tokens, int matrices, size_t bytes) {
   Params q = p;
   q.perm = nullptr;                                        // (the product runs on gathered activations)
-  const size_t most = dense_scratch_bytes(p), sums = most ? gemm_dense_scratch_bytes(q, tokens, matrices, most) : 0;
+  const size_t most = dense_scratch_bytes(p), sums = most && tokens ? gemm_dense_scratch_bytes(q, tokens, matrices, most) : 0;
   return bytes > MOST_DEFAULT_WORKSPACE ? 0 : bytes + sums <= MOST_DEFAULT_WORKSPACE ? bytes + sums : bytes;
 }
 
@@ -326,9 +326,12 @@ static int launch_gemm_rows(const Params &p, const __half *X, long long ldx, int
 // What vq_gemm_default uses: room for W where it would be rounded in any case, else for the centroids, or what vq_gemv's kernels take;
 // nothing beyond 256 MiB (W of 11008 x 11008), so that who leaves the workspace out to save memory still does
 // where it counts (8192 x 28672, 448 MiB, 512 tokens: 532 us with it, 582 without).
-size_t gemm_default_workspace_bytes(const Params &p, int tokens) {
-  if (centroids_wanted(p, tokens)) return default_bytes(p, tokens, p.k_res ? 2 : 1, centroids_workspace_bytes(p, tokens));
-  if (!rows_hold_the_weights(p, tokens) && gemm_dense_applicable(p)) return default_bytes(p, tokens, 1, gemm_fast_workspace_bytes(p, tokens) - dense_scratch_bytes(p));
+// sums: with the room for those of a product in parts.
+size_t gemm_default_workspace_bytes(const Params &p, int tokens, bool sums) {
+  const int matrices = p.k_res ? 2 : 1;
+  if (centroids_wanted(p, tokens)) return default_bytes(p, sums ? tokens : 0, matrices, centroids_workspace_bytes(p, tokens));
+  if (!rows_hold_the_weights(p, tokens) && gemm_dense_applicable(p))
+    return default_bytes(p, sums ? tokens : 0, 1, gemm_fast_workspace_bytes(p, tokens) - dense_scratch_bytes(p));
   const size_t bytes = rows_hold_the_weights(p, tokens) ? gemv_workspace_bytes(p, nullptr, (p.in_features + 7) & ~7, tokens < 16 ? tokens : 16)
                                                         : gemm_fast_workspace_bytes(p, tokens);
   return bytes <= MOST_DEFAULT_WORKSPACE ? bytes : 0;

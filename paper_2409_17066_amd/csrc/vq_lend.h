@@ -12,6 +12,8 @@ extern "C" {
  * stored order: their kernels without one are good, and sum in the same order with vq_gemv_multi or a workspace that is too small.  Of v = 6 rows of an
  * odd width, which those kernels take far more slowly than a copy of them, or than group by group, that order is given up. */
 size_t vq_lend_gemv_bytes(const vq_layer_desc *desc, int32_t batch);
+/* Of vq_gemm_default, on a card without room for what it asks for: the same route without the sums of a product in parts. */
+size_t vq_lend_gemm_least_bytes(const vq_layer_desc *desc, int32_t tokens);
 
 #ifdef __cplusplus
 }

@@ -4,7 +4,7 @@ run(calls) starts a process of its own in which libvq.so finds launch_log.cpp in
 each its status, the workspace that was asked for and the launches.  A call is a dict: "entry" (an entry point's name without vq_), "layer" (sizes of
 a descriptor; pointers and strides are made up), "rows", "pitch" and "x" (columns from one row of activations to the next, address of the
 first; both have defaults), "workspace" (bytes; None: none; "asked": what the library asks for; "lent": what
-the package lends gemv() of its own accord), "asked_for_rows" (whose size that is; default: "rows").
+the package lends gemv() of its own accord; "least": gemm() on a card without room for what the library asks for), "asked_for_rows" (whose size that is; default: "rows").
 """
 import ctypes
 import json
@@ -68,6 +68,7 @@ def _main(shim, lib):
         pitch = call.get("pitch", n + (n & 1) if gemv else (n + 7) // 8 * 8)
         bytes_ = call.get("workspace")
         bytes_ = asked if bytes_ == "asked" else vq.load().vq_lend_gemv_bytes(ctypes.byref(d), rows) if bytes_ == "lent" else bytes_
+        bytes_ = vq.load().vq_lend_gemm_least_bytes(ctypes.byref(d), rows) if bytes_ == "least" else bytes_
         x = call.get("x", X)
         log.launch_log_clear()
         if entry in ("gemv", "gemv_static_workspace"):

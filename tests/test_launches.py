@@ -146,14 +146,18 @@ def test_gemm_default_asks_for_the_sums_that_it_writes():
         calls.append(dict(entry="gemm_default", rows=round(2 ** rng.uniform(4.1, 11)), workspace="asked", layer=layer))
     answers = launches.run(calls)
     more = launches.run([dict(call, workspace=answer["asked"] + (8 << 20)) for call, answer in zip(calls, answers)])
+    least = launches.run([dict(call, workspace="least") for call in calls])
     whole = cut = 0
-    for call, answer, with_more in zip(calls, answers, more):
+    for call, answer, with_more, with_less in zip(calls, answers, more, least):
         names = [launch["name"] for launch in answer["launches"]]
         assert answer["status"] == 0 and (answer["launches"] == with_more["launches"] or not any("gemm_dense" in launch["name"] for launch in with_more["launches"])), call
         if "gemm_dense_finish_kernel" in names:
             cut += 1
+            # without that room the same route, not cut
+            assert with_less["lent"] < answer["lent"] and [name.split("<")[0] for name in names[:-1]] == [launch["name"].split("<")[0] for launch in with_less["launches"]]
         elif any(name.startswith("gemm_dense_kernel") for name in names):
             whole += 1
+            assert with_less == answer
             d, tokens = call["layer"], call["rows"]
             matrices = 2 if d.get("k_res") else 1
             assert answer["asked"] <= matrices * (d["out_features"] * d["in_features"] * 2 + 256) + tokens * (4 + d["in_features"] * 2 * d.get("col_perm", 0)) + 512, call
