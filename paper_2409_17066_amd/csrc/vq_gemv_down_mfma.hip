@@ -453,8 +453,8 @@ static int make_plan(const Params &p, long long ldx, int batch, float *part, flo
   plan.wpp = (windows + plan.sub - 1) / plan.sub;
   plan.batch = batch;
   // (a whole number of dwords: the buffer's range check drops a dword that straddles the end, and with it the last
-  // column of the last row when in_features is odd; ldx is a multiple of 8 here, so the half after it is the caller's
-  // padding, and the kernel masks it like every position past the stream's end)
+  // column of the last row when in_features is odd; x begins at a dword and ldx is even, so that column and the half after it,
+  // which need not be the caller's, are one dword and lie on one page, and the kernel masks the half like every position past the stream's end)
   plan.x_bytes = (unsigned)((((long long)(batch - 1) * ldx + p.in_features) * 2 + 3) & ~3LL);
   plan.part = part; plan.part_xs = part_xs;
   plan.o_pitch = ((p.Q + 1) / 2) | 1;
