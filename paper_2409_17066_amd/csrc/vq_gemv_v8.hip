@@ -271,12 +271,13 @@ static bool rows_applicable(const Params &p) {
 //    10676 x 1248, five 87 -> 36, 16166 x 97, four 10 -> 26; with 2346 x 5352, one row 42 -> 11, 3089 x 3560,
 //    three rows 69 -> 22, 10740 x 689, four 13 -> 18, 1532 x 11787, four 19 -> 27);
 //  * a table past LDS, against the generic kernel: all but several rows of a few vectors (3520 x 6586, one row 107 -> 19 us, 1972 x 16081 208 -> 24;
-//    5198 x 113, sixteen rows 27 -> 44).
+//    5198 x 113, sixteen rows 27 -> 44).  Of 240 such layers of 24 to 500 columns four rows, one launch, take 0.65 to 0.99 of the time there, three, which are
+//    two, 0.9 to 1.2.
 bool gemv_lds_applicable(const Params &p, int batch);
 bool gemv_v8_wanted(const Params &p, const __half *x, long long ldx, int batch, bool workspace) {
   if (!rows_applicable(p)) return false;
   if (in_pieces_of_sixteen_bytes(p, x, ldx)) return true;
-  if (!gemv_lds_applicable(p, 1)) return p.in_features >= 320 || batch < 3 || p.out_features <= 1024;
+  if (!gemv_lds_applicable(p, 1)) return p.in_features >= 320 || batch < 3 || batch == 4 || p.out_features <= 1024 || (batch == 3 && p.out_features <= 3000);
   if (p.n_groups > 1) return p.out_features <= (p.in_features >= 9984 ? 1024 : workspace ? 6144 : 14336);
   return p.out_features <= 1024 && (p.in_features >= 6144 || (p.in_features >= 1024 && batch >= 2));
 }

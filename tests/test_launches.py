@@ -81,7 +81,7 @@ def test_gemv_of_odd_rows_down_the_outputs_in_parts(out, inp, more, permuted):
     ("gemv", 7214, 14999, 4, {}, "gemv_lds"), ("gemv", 550, 3667, 16, {}, "gemv_v8"), ("gemv", 550, 367, 16, {}, "gemv_lds"),
     ("gemv", 16166, 97, 4, dict(group_vectors=8), "gemv_lds"), ("gemv", 10676, 1249, 5, dict(group_vectors=16), "gemv_v8"),
     ("gemv_with_workspace", 10740, 689, 4, dict(group_vectors=40), "gemv_lds"), ("gemv_with_workspace", 2346, 5353, 1, dict(group_vectors=48), "gemv_v8"),
-    ("gemv", 5198, 113, 16, dict(k=65536), "gemv_generic"), ("gemv", 5198, 113, 1, dict(k=65536), "gemv_v8"), ("gemv", 50, 7, 1, dict(k=65536), "gemv_generic"),
+    ("gemv", 5198, 113, 16, dict(k=65536), "gemv_generic"), ("gemv", 5198, 113, 1, dict(k=65536), "gemv_v8"), ("gemv", 1472, 297, 4, dict(k=65536, k_res=0), "gemv_v8"), ("gemv", 50, 7, 1, dict(k=65536), "gemv_generic"),
 ])
 def test_gemv_v8_rows_that_begin_anywhere(entry, out, inp, rows, more, kernel):
     """Each side of the lines between the lookups through L2 and the kernels that take such rows otherwise."""
