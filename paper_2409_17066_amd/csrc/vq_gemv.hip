@@ -422,17 +422,31 @@ static bool permuted_in_kernel(const Params &p, const __half *x, long long ldx, 
 // The v = 6 / 12-bit kernels want dwords at any number of rows, those along the rows an even width as well: there the copy's next column, zeros,
 // counts as the layer's last (P is the same: an odd width is short of whole vectors).  3520 x 6587, 1 / 4 / 16 rows: 9.7 -> 7.9, 18.3 -> 9.2, 71 -> 11.2 us;
 // down the outputs, in column parts, 4 / 16 rows 20.7 -> 10.5, 80.6 -> 12.4 (without parts 16.0, 17.5).
-// Not along the rows where the kernels that keep one table in LDS at a time are as fast without the copy (540 layers of 32 to 16384 outputs): short
-// rows, one of which takes them no longer than the copy (12461 x 193 7.4 us, 9.3 with it, 3589 x 557 5.7 / 6.2, 735 x 1089 9.0 / 6.7); and up to two
-// rows with codebook groups, side by side there, four, which they take in one launch, with a residual table, five with outlier columns (two of 12996 x
-// 2263 in 16 groups 21 / 55, of 9283 x 1081 with two tables in 23 37 / 86, four of 2843 x 2455 with two in 18 20 / 23.5, five of 10973 x 1533 in 16 with
-// 16 outlier columns 34 / 51), unless the residual table has 8-bit indices, for which there is only the generic kernel (two of 8181 x 3129 in groups, 0.31 of
-// its time).
+// Not along the rows where the kernels that keep one table in LDS at a time are as fast without the copy.  With one group (450 layers of 1024
+// to 14336 outputs, 65 to 1400 columns): one and two short rows, which take them no longer than the copy (one of 12461 x 193 7.4 us, 9.3 with it, of 3589 x
+// 557 5.7 / 6.2, of 735 x 1089 9.0 / 6.7; three rows and more, of any width, are two launches there: 0.2 to 0.6 of the time with the copy).  With
+// codebook groups (430 layers of 256 to 14336 outputs, 300 to 28672 columns, 2 to 24 groups; there the groups are side by side either way): two rows and
+// four, which they take in one launch, by the estimates below, which cost 0.7 % over the better choice where the copy always costs 12 and never 25 (two
+// rows of 12996 x 2263 in 16 groups 21 / 55, of 2836 x 27149 in four 36 / 15.5, four of 2068 x 26017 in four with two tables 82 / 28); other
+// numbers of rows only where outlier columns stand beside groups of few vectors (three of 9098 x 1467 in 16 groups 25 / 43, of 12378 x 437 in four
+// 18.4 / 21.7).  For residual tables of 8-bit indices there is only the generic kernel without it (two of 8181 x 3129 in groups, 0.31 of its time).
+static bool groups_taken_odd(const Params &p, int batch) {
+  if (batch != 2 && batch != 4) return batch < 6 && p.Q && p.Pg <= 32;
+  const float vectors = (float)p.out_features * (float)p.P * 1e-6f, sums = (float)p.out_features * (float)p.n_groups * 1e-4f, columns = (float)p.in_features * 1e-4f;
+  const float groups = (float)p.n_groups, outliers = p.Q ? 1.0f : 0.0f;
+  const float copied = p.k_res ? 10.1f + 0.95f * vectors + 1.8f * sums + 0.65f * columns + 1.5f * outliers + 0.18f * groups
+                               : 9.2f + 0.5f * vectors + 0.7f * sums + 0.35f * columns + 1.5f * outliers + 0.13f * groups;
+  if (batch == 2)
+    return (p.k_res ? 7.7f + 2.0f * vectors + 0.4f * sums + 1.3f * columns + 0.8f * outliers + 0.25f * groups
+                    : 8.3f + 0.93f * vectors + 0.2f * sums + 1.6f * columns + 0.3f * outliers + 0.06f * groups) < copied;
+  return (p.k_res ? 7.6f + 3.0f * vectors + 0.5f * sums + 5.4f * columns + 1.1f * outliers + 0.26f * groups
+                  : 8.6f + 1.2f * vectors + 0.4f * sums + 5.8f * columns + 0.4f * outliers) < copied;
+}
 static bool even_width_wanted(const Params &p, int batch) {
   if (p.orientation != 0 || !(p.in_features & 1) || !gemv_fast_applicable_even(p)) return false;
   if (p.k_res && p.bits_res == 8) return true;
-  if (p.n_groups > 1) return batch >= (p.Q ? 6 : 3) && !(p.k_res && batch == 4);
-  return p.in_features >= (batch >= 2 ? 300 : p.k_res ? 512 : 1024);
+  if (p.n_groups > 1) return batch >= 2 && !groups_taken_odd(p, batch);
+  return batch >= 3 || p.in_features >= (batch == 2 && p.Q ? 400 : p.k_res ? 512 : batch == 2 ? 700 : 1024);
 }
 static size_t stored_order_workspace_bytes(const Params &p, const __half *x, long long ldx, int batch, bool least);
 static Params gathered(const Params &p, int batch) {

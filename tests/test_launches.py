@@ -107,11 +107,13 @@ def test_gemv_down_takes_the_faster_kernel(entry, out, inp, rows, pitch, more, k
 
 
 @pytest.mark.parametrize("out,inp,rows,more,copied", [
-    (12461, 193, 1, {}, False), (3589, 557, 1, {}, False), (1735, 1089, 1, {}, True), (2759, 513, 1, dict(k_res=4096), True), (2759, 335, 2, {}, True),
+    (12461, 193, 1, {}, False), (3589, 557, 1, {}, False), (1735, 1089, 1, {}, True), (2759, 513, 1, dict(k_res=4096), True), (2759, 735, 2, {}, True), (2759, 335, 2, {}, False), (12201, 289, 10, dict(k_res=4096), True),
     (9609, 173, 2, {}, False), (12996, 2263, 2, dict(group_vectors=24), False), (12996, 2263, 3, dict(group_vectors=24), True),
     (12996, 2263, 4, dict(group_vectors=24, n_outlier_cols=4), False), (12996, 2263, 6, dict(group_vectors=24, n_outlier_cols=4), True),
     (2843, 2455, 4, dict(group_vectors=24, k_res=4096), False), (2843, 2455, 5, dict(group_vectors=24, k_res=4096), True),
-    (8181, 3129, 2, dict(group_vectors=104, k_res=256), True),
+    (8181, 3129, 2, dict(group_vectors=104, k_res=256), True), (2836, 27149, 2, dict(group_vectors=1136), True), (2068, 26017, 4, dict(group_vectors=1088, k_res=4096), True),
+    (3200, 26733, 4, dict(group_vectors=1104, n_outlier_cols=268), True), (9098, 1467, 3, dict(group_vectors=16, n_outlier_cols=16), False),
+    (4526, 25701, 3, dict(group_vectors=1432, n_outlier_cols=256), True),
 ])
 @pytest.mark.parametrize("permuted", [False, True])
 def test_gemv_of_an_odd_width_made_even(out, inp, rows, more, copied, permuted):
