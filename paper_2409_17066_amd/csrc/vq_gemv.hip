@@ -141,7 +141,7 @@ int launch_groups_finish(const float *part, const float *part_xs, int n_groups, 
                          hipStream_t s);
 bool gemv_down_mfma_applicable(const Params &p, const __half *x, long long ldx, int batch);
 int gemv_down_mfma_parts(const Params &p);
-float gemv_down_mfma_us(const Params &p, int parts);
+float gemv_down_mfma_us(const Params &p, int parts, int batch);
 float gemv_down_streams_us(const Params &p, int batch);
 int launch_gemv_down_mfma(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, hipStream_t s,
                           float *part, float *part_xs, int parts);
@@ -155,13 +155,16 @@ static bool down_mfma_wanted(const Params &p, const __half *x, long long ldx, in
   const char fk = forced_kernel();
   return fk != 'g' && fk != 'd' && gemv_down_applicable(p, x, ldx) && gemv_down_mfma_applicable(p, x, ldx, batch);
 }
+// What `launches` launches take at least, one after another from a host's program: 4.8, 8.4, 12 us through the torch binding.  (Not in a graph, where
+// a second launch is 1.6 us: layers whose parts take less than that floor would be up to 1 us faster there with them.)
+static float launched(float us, int launches) { return std::max(us, 1.3f + 3.55f * (float)launches); }
 // With a workspace (column parts, one workgroup per block of 16 streams and part): from two rows on, for any batch when there are codebook
 // groups (16 groups, one row: 15.5 against 17.4 us), and for one row by the estimates (4096 x 4096 8.3 against 6.7 us; 4096 x 11008 10.4
 // against 11.4).
 // (and for one row of a layer whose activations do not fit the other kernel's LDS beside the tables)
 static bool down_mfma_parts_wanted(const Params &p, const __half *x, long long ldx, int batch) {
   return down_mfma_wanted(p, x, ldx, batch) && (batch >= 2 || p.n_groups > 1 || forced_kernel() == 'm' || !gemv_down_fits(p) ||
-                                                gemv_down_mfma_us(p, gemv_down_mfma_parts(p)) < gemv_down_streams_us(p, 1));
+                                                1.06f * launched(gemv_down_mfma_us(p, gemv_down_mfma_parts(p), 1), 2) < gemv_down_streams_us(p, 1));
 }
 static bool down_mfma_alone_wanted(const Params &p, const __half *x, long long ldx, int batch) {
   if (!down_mfma_wanted(p, x, ldx, batch)) return false;
@@ -170,35 +173,39 @@ static bool down_mfma_alone_wanted(const Params &p, const __half *x, long long l
     // group and spreads its streams (four groups, 11008 x 4096 16.7 against 19.1 us, 4096 x 4096 16.7 / 16.0, 4096 x 11008 25.7 / 21.7; sixteen
     // 45.3 / 50.7); with an 8-bit residual table it is the generic one, which pays nothing for a group (876 x 138, 18 groups 39 / 11, 8 groups 17 / 11)
     if (batch >= 2 || forced_kernel() == 'm') return true;
-    const float groups = (float)p.n_groups, vectors = (float)p.S * (float)p.P * 1e-6f, walk = gemv_down_mfma_us(p, 1) - 5.0f;
+    const float groups = (float)p.n_groups, vectors = (float)p.S * (float)p.P * 1e-6f, walk = gemv_down_mfma_us(p, 1, 1) - 5.0f;
     if (!gemv_down_lds_applicable(p, 1)) return 1.9f * groups + walk < 1.0f + 0.03f * (float)p.P * std::max(1.0f, 1e-3f * (float)p.S);
     return (p.k_res ? 3.1f : 1.55f) * groups + walk < (p.k_res ? 5.0f : 2.5f) * groups + (p.k_res ? 1.3f : 0.65f) * vectors;
   }
-  return batch >= 5 || forced_kernel() == 'm' || gemv_down_mfma_us(p, 1) < gemv_down_streams_us(p, batch);      // (of five rows and more a launch of four is one of two)
+  return batch >= 5 || forced_kernel() == 'm' || 1.02f * gemv_down_mfma_us(p, 1, batch) < gemv_down_streams_us(p, batch);      // (of five rows and more a launch of four is one of two)
 }
-// Whether parts of the columns, which a workspace is there for, are worth the second launch (300 x 1000, two rows 8.5 -> 6.1 us, four 8.1 -> 6.2;
-// 4096 x 4096, two rows, parts 8.4, without 8.6).
-static bool down_mfma_parts_pay(const Params &p, int batch) {
+// Whether parts of the columns, which a workspace is there for, are worth the second launch, or with the activations copied in front a third one
+// (4096 x 4096, two rows, parts 8.4, without 8.6; 6513 x 2176, three rows 8.7 and 8.0; 539 x 3101, sixteen copied rows 13.4 and 12.0).
+static bool down_mfma_parts_pay(const Params &p, int batch, bool copied) {
   if (p.n_groups > 1 || forced_kernel() == 'm' || !gemv_down_fits(p)) return true;
-  const float alone = gemv_down_mfma_us(p, 1);
-  return gemv_down_mfma_us(p, gemv_down_mfma_parts(p)) < (batch <= 4 ? std::min(alone, gemv_down_streams_us(p, batch)) : alone);
+  const float copy = copied ? 1.8f : 0.0f;
+  const int launches = copied ? 2 : 1;
+  const float alone = launched(gemv_down_mfma_us(p, 1, batch) + copy, launches);
+  const float parts = launched(gemv_down_mfma_us(p, gemv_down_mfma_parts(p), batch) + copy, launches + 1);
+  return parts < alone && (batch > 4 || 1.06f * parts < gemv_down_streams_us(p, batch) + copy);
 }
 
 // Rows that begin off sixteen bytes, which only that kernel and the one with a table in LDS at a time take as a rule: the latter where residual tables
-// of 4096 entries leave the other no room for two rows (61 x 10331, eight rows 53 against 70 us, 5602 x 11375, two 36 / 39), and several rows of a
+// of 4096 entries leave the other no room for two rows (61 x 10331, eight rows 53 against 70 us, 5602 x 11375, two 36 / 39; not 1874 x 11674, two 26.5 / 24), and several rows of a
 // few hundred columns with outlier columns (13521 x 366, two 10.9 / 14.9, 4439 x 463, four 12.4 / 13.7).  Of 187 other such calls the time here is
 // 0.79 of that there, one row 0.73.
 static bool down_table_at_a_time(const Params &p, const __half *x, long long ldx, int batch) {
   if (!((reinterpret_cast<uintptr_t>(x) & 15) || (ldx & 7)) || batch < 2 || forced_kernel() != '\0' || !gemv_down_lds_applicable(p, 1)) return false;
-  return p.k_res ? p.bits_res == 12 && p.P >= 8192 && p.P < 12288 : p.Q && p.P < 1024;
+  return p.k_res ? p.bits_res == 12 && p.P >= 8192 && p.P < 12288 && (batch >= 3 || p.out_features >= 4096) : p.Q && p.P < 1024;
 }
 
 // Estimated time in microseconds of up to sixteen rows on the matrix cores of that orientation with a workspace (the route rules of vq_gemm); 0 for
-// layers that do not go there.
+// layers that do not go there.  (Of 150 layers, and not the finer estimates above: that line decides how a product's weights are held, and stays.)
 float gemv_down_rows_us(const Params &p, const __half *x, long long ldx) {
   if (p.orientation != 1 || !down_mfma_wanted(p, x, ldx, 16)) return 0.0f;
-  const int parts = gemv_down_mfma_parts(p);
-  return 1.0f + std::min(gemv_down_mfma_us(p, 1), gemv_down_mfma_us(p, parts)) + (p.k_res ? 1.0f : 0.0f) + (p.n_groups > 1 ? 3.0f : 0.0f);
+  const int blocks = (p.S + 15) / 16, parts = gemv_down_mfma_parts(p);
+  auto us = [&](int n) { return (p.k_res ? 3.0e-3f : 1.4e-3f) * (float)p.P / (float)n * (float)((blocks * n + cu_count() - 1) / cu_count()) + (n > 1 ? 2.1f : 0.0f); };
+  return 6.0f + std::min(us(1), us(parts)) + (p.k_res ? 1.0f : 0.0f) + (p.Q ? 2.0f : 0.0f) + (p.n_groups > 1 ? 3.0f : 0.0f);
 }
 
 bool gemv_rows_applicable(const Params &p);
@@ -538,7 +545,7 @@ size_t gemv_lent_bytes(const Params &p, int batch) {
 static size_t sums_bytes(const Params &p, size_t slots, int batch) { return slots * ((size_t)batch * (size_t)p.out_features + 16) * sizeof(float); }
 
 static int launch_stored_order(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, void *workspace,
-                               size_t workspace_bytes, bool least, hipStream_t s);
+                               size_t workspace_bytes, bool least, bool copied, hipStream_t s);
 static int launch_with_workspace(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, void *workspace,
                                  size_t workspace_bytes, bool least, hipStream_t s) {
   if (p.perm || (rows_gathered(p, batch) && !taken_as_they_are(p, x, ldx, batch))) {
@@ -562,15 +569,15 @@ static int launch_with_workspace(const Params &p, const __half *x, long long ldx
     const int rc = launch_gather_cols(x, ldx, batch, p.in_features, p.perm, xp, ldxp, s);
     if (rc != VQ_OK) return rc;
     const size_t head = permuted_x_bytes(p, batch);
-    return launch_stored_order(q, xp, ldxp, batch, y, ldy, static_cast<unsigned char *>(workspace) + head, workspace_bytes - head, false, s);
+    return launch_stored_order(q, xp, ldxp, batch, y, ldy, static_cast<unsigned char *>(workspace) + head, workspace_bytes - head, false, true, s);
   }
-  return launch_stored_order(p, x, ldx, batch, y, ldy, workspace, workspace_bytes, least, s);
+  return launch_stored_order(p, x, ldx, batch, y, ldy, workspace, workspace_bytes, least, false, s);
 }
 
 // Activations that are taken as they are, in stored order (the caller's, or the copy of them in front of this workspace).  Every branch compares
 // the workspace with what its kernels write.
 static int launch_stored_order(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, void *workspace,
-                               size_t workspace_bytes, bool least, hipStream_t s) {
+                               size_t workspace_bytes, bool least, bool copied, hipStream_t s) {
   const size_t need = force_generic() ? 0 : stored_order_workspace_bytes(p, x, ldx, batch, least);
   if (rows_wanted(p, batch, workspace != nullptr) && gemv_rows_takes(p, x, ldx, batch)) {
     const int per_group = workspace && workspace_bytes >= gemv_rows_workspace_bytes(p, batch) ? gemv_rows_parts(p) : 0, parts = per_group * p.n_groups;
@@ -581,7 +588,7 @@ static int launch_stored_order(const Params &p, const __half *x, long long ldx, 
   }
   if (need && workspace && workspace_bytes >= need && p.orientation == 1 && down_mfma_parts_wanted(p, x, ldx, batch)) {
     const int parts = gemv_down_mfma_parts(p), slots = parts + (p.Q ? 1 : 0);
-    if (parts < 2 || workspace_bytes < sums_bytes(p, slots, batch) || !down_mfma_parts_pay(p, batch)) return launch_gemv(p, x, ldx, batch, y, ldy, s);
+    if (parts < 2 || workspace_bytes < sums_bytes(p, slots, batch) || !down_mfma_parts_pay(p, batch, copied)) return launch_gemv(p, x, ldx, batch, y, ldy, s);
     float *part = static_cast<float *>(workspace), *part_xs = part + (size_t)slots * (size_t)batch * (size_t)p.out_features;
     int rc = launch_gemv_down_mfma(p, x, ldx, batch, nullptr, 0, s, part, part_xs, parts);
     if (rc == VQ_OK) return launch_groups_finish(part, part_xs, slots, batch, p, y, ldy, s);

@@ -415,19 +415,21 @@ bool gemv_down_fits(const Params &p) {
 }
 
 // Estimated time in microseconds of `batch` rows in launches of 4, 2 or 1, as many as fit LDS beside the tables, of a layer without codebook groups: a
-// launch's start and the passes of its busiest wave, from 900 layers (32 to 16384 outputs, 90 to 23000 columns), 6 % off in the mean.
+// launch's start and the passes of its busiest wave, and the outlier columns of a workgroup's rows, from 1560 layers (256 to 14336 outputs, 256 to 28672
+// columns), 6 % off in the mean; a launch after another one 0.7 more outside a graph.
 float gemv_down_streams_us(const Params &p, int batch) {
-  static const float start[3][3] = {{3.9f, 4.8f, 5.6f}, {4.3f, 4.9f, 6.1f}, {4.9f, 5.6f, 6.1f}}, pass[3][3] = {{0.61f, 0.85f, 1.7f}, {0.92f, 1.33f, 2.6f}, {1.04f, 1.45f, 2.9f}};
+  static const float start[3][3] = {{3.8f, 4.7f, 6.1f}, {4.0f, 5.0f, 7.5f}, {4.9f, 5.55f, 6.95f}}, pass[3][3] = {{0.63f, 0.84f, 1.43f}, {0.955f, 1.29f, 2.09f}, {1.02f, 1.37f, 2.31f}};
   const int tables = !p.k_res ? 0 : p.bits_res == 8 ? 1 : 2;
   float us = 0.0f;
-  for (int g = 2; batch > 0;) {                          // of 4 >> (2 - g) rows
+  for (int g = 2; batch > 0;) {                          // of 1 << g rows
     DownPlan plan;
     unsigned off, grid;
     if (batch < 1 << g || make_plan(p, 1 << g, nullptr, nullptr, 0, &plan, &off, &grid) != VQ_OK) {
       if (--g < 0) return 1e30f;
       continue;
     }
-    us += start[tables][g] + pass[tables][g] * (float)plan.iters * ((float)plan.ppw + (plan.ws_log2 ? 0.5f : 0.33f)) + (p.Q ? 3.1f : 0.0f);
+    us += start[tables][g] + (us > 0.0f ? 0.7f : 0.0f) + pass[tables][g] * (float)plan.iters * ((float)plan.ppw + (plan.ws_log2 ? 0.5f : 0.33f));
+    if (p.Q) us += 3.0f + (float)p.Q * (0.0055f + 5.3e-4f * (float)(plan.iters * (DW >> plan.ws_log2) * 6 * ((1 << g) - 1)));
     batch -= 1 << g;
   }
   return us;

@@ -436,12 +436,21 @@ static int parts_per_group(const Params &p) {
 }
 int gemv_down_mfma_parts(const Params &p) { return p.n_groups * parts_per_group(p); }
 
-// Estimated time in microseconds of any rows of a layer without codebook groups in `parts` parts, from the same 900 layers as that of the other
-// kernel (vq_gemv_down.hip), 8 % off in the mean: a workgroup's start and its waves' windows, as often as compute units take one; the second launch.
-float gemv_down_mfma_us(const Params &p, int parts) {
+// Estimated time in microseconds of `batch` rows of a layer without codebook groups in `parts` parts, from 1560 layers (256 to 14336 outputs, 256 to
+// 28672 columns, one to sixteen rows; 4 % off in the mean, sixteen rows 7): a workgroup's start and its waves' windows, as often as compute units take
+// one; the second launch and its sums; the outlier columns, which a block's rows have one workgroup for, or one a part.
+float gemv_down_mfma_us(const Params &p, int parts, int batch) {
   const int blocks = (p.S + 15) / 16, windows = (p.P + 31) / 32, rounds = (blocks * parts + cu_count() - 1) / cu_count();
   const int steps = ((windows + parts - 1) / parts + MW - 1) / MW;
-  return 2.5f + (float)rounds * (2.5f + (p.k_res ? 0.68f : 0.33f) * (float)steps) + (parts > 1 ? 2.1f : 0.0f) + (p.Q ? 2.2f : 0.0f);
+  const bool few = p.k_res && batch <= 2, long_table = p.bits_res == 12;
+  const float start = (!p.k_res ? 2.5f : long_table ? (few ? 2.7f : 3.03f) : few ? 2.25f : 2.55f) + (batch > 8 ? 0.2f : 0.0f);
+  const float step = !p.k_res ? 0.335f : !long_table ? 0.7f : few ? 0.715f : 0.73f, outputs = (float)p.out_features;
+  // (sixteen rows that begin on one of few lines of L1 each get in one another's way; a part of them less so)
+  const float pitch = parts == 1 && batch > 8 && !p.k_res && p.in_features % 256 == 0 ? 1.18f : 1.0f;
+  float us = start * (float)(1 + rounds) + pitch * step * (float)(rounds * steps);
+  if (parts > 1) us += 0.85f + (float)parts * (0.12f + outputs * (1.7e-5f + 5.2e-6f * (float)batch));
+  if (p.Q) us += 1.2f + (float)p.Q * (parts > 1 ? 0.03f + 2.2e-6f * outputs : p.k_res ? 0.06f : 0.08f);
+  return us;
 }
 
 static int make_plan(const Params &p, long long ldx, int batch, float *part, float *part_xs, int parts, DownMfmaPlan &plan, long long *grid_out) {

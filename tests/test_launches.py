@@ -57,13 +57,14 @@ def test_gemv_stays_inside_its_workspace(odd):
 
 
 @pytest.mark.parametrize("permuted", [False, True])
-@pytest.mark.parametrize("out,inp,more", [
-    (3520, 6587, {}), (4096, 4097, {}), (2048, 8193, dict(k_res=4096)), (2048, 8193, dict(k_res=256, n_outlier_cols=40)), (4096, 4097, dict(group_vectors=256)),
+@pytest.mark.parametrize("out,inp,numbers,more", [
+    (3520, 6587, (2, 4, 16), {}), (4096, 4097, (16,), {}), (2048, 8193, (2, 4, 16), dict(k_res=4096)), (2048, 8193, (2, 4, 16), dict(k_res=256, n_outlier_cols=40)),
+    (4096, 4097, (2, 4, 16), dict(group_vectors=256)),
 ])
-def test_gemv_of_odd_rows_down_the_outputs_in_parts(out, inp, more, permuted):
+def test_gemv_of_odd_rows_down_the_outputs_in_parts(out, inp, numbers, more, permuted):
     """The workspace of an odd width takes the copy of the activations, where there is one, and the same parts as the next even width."""
     calls = []
-    for rows in (2, 4, 16):
+    for rows in numbers:
         for width, pitch in ((inp, inp), (inp, inp + 1), (inp + 1, inp + 1)):
             layer = dict(out_features=out, in_features=width, orientation=1, col_perm=permuted, **more)
             calls.append(dict(entry="gemv_with_workspace", layer=layer, rows=rows, pitch=pitch, workspace="asked"))
