@@ -686,14 +686,14 @@ int launch_gemv_mfma(const Params &p, const __half *x, long long ldx, int batch,
 //    only for more than eight rows: 44.6 / 47.9, three rows level);
 //  * a quarter as many blocks, from 2000 on (512 x 16384, three rows 9.3 / 10.5, sixteen 11.4 / 18.9, with residual tables 11.2 / 14.9, 12.7 /
 //    21.1), for more than eight rows from 1300 on (1024 x 8192, sixteen 9.5 / 11.3; eight 9.0 / 8.5);
-//  * without a residual table, twelve rows or more, from 1700 on (4096 x 11008, sixteen 13.3 / 15.2; 4096 x 14336, twelve 13.7 / 15.6, eight level;
-//    with residual tables 18.4 / 17.7).
+//  * without a residual table, twelve rows or more, from 1700 on, of more blocks than seven tenths of the compute units from 1800 (4096 x 11008, sixteen
+//    13.3 / 15.2; 4096 x 14336, twelve 13.7 / 15.6, eight level; with residual tables 18.4 / 17.7; 2688 x 10208, twelve 10.9 / 11.6, but 3200 x 10208 12.1 / 11.5).
 static int column_parts(const Params &p, int batch) {
   const int blocks = (p.out_features + 15) / 16, cus = cu_count();
   if (p.n_groups > 1 || batch < 3) return 1;
   if (blocks > cus) return (2 * blocks <= 3 * cus && p.P >= 1500) || (blocks <= 2 * cus && p.P >= 3500 && batch >= (p.k_res ? 9 : 3)) ? 2 : 1;
   if (4 * blocks <= cus && p.P >= (batch > 8 ? 1300 : 2000)) return 4;
-  return !p.k_res && batch >= 12 && p.P >= 1700 ? 4 : 1;
+  return !p.k_res && batch >= 12 && p.P >= (10 * blocks > 7 * cus ? 1800 : 1700) ? 4 : 1;
 }
 // vectors of a part: whole steps of the workgroup's waves, as far as that leaves every part some
 static int part_vectors(const Params &p, int parts) { return ((p.P + parts - 1) / parts + 31) / 32 * 32; }
