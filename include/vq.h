@@ -41,8 +41,8 @@
  * the device address of vq_gemv_static_workspace's array), all of them guarded.
  * The environment variable VQ_SWITCHES ("name=value,..."; read once at the
  * start of every call) forces kernel choices for tests and measurements:
- * gemv=g|m|d (generic / matrix-core / dot-product kernels), rows=0|1, groups=loop, multi=0,
- * gemm=g|f|w|r|6|c, dense=0|1, dequant=g; unset, every choice is the library's own.
+ * gemv=g|m|d (generic / matrix-core / dot-product kernels), rows=0|1, products=0|1, groups=loop,
+ * multi=0, gemm=g|f|w|r|6|c, dense=0..9, dequant=g; unset, every choice is the library's own.
  */
 #ifndef VQ_H
 #define VQ_H
@@ -152,9 +152,12 @@ int vq_gemv(const vq_layer_desc *desc, const void *x, int64_t ldx, int32_t batch
  * two rows on (from one row when a row of x does not fit the one-row kernel's LDS beside the tables: about 15000
  * columns with a 12-bit residual table): the matrix-core kernel of that orientation works in blocks of 16 index streams (96 output rows), too few
  * to fill the chip on most layers, so with a workspace it also cuts the columns into parts, one workgroup per (block,
- * part), and the same second kernel adds the parts up; so does the matrix-core kernel of the paper's other settings.  Layers
- * with a column permutation gather the activations into it first, but for one and two rows of layers with codebook groups on the
- * kernel that keeps one table in LDS at a time, whose workgroups gather theirs by themselves.  vq_gemv_workspace_bytes returns 0 when
+ * part), and the same second kernel adds the parts up; so do the matrix-core kernel of the paper's other settings and, from three
+ * rows on, that of v = 6 / 12-bit layers along the rows with one group and few blocks of rows.  v = 12 layers with 12-bit indices take
+ * one and two rows from tables of products of their entries and the activations, whose sums over runs of columns a second kernel adds up in
+ * ascending order.  Layers with a column permutation gather the activations into it first, but for one and two rows of layers with codebook
+ * groups on the kernel that keeps one table in LDS at a time, whose workgroups gather theirs by themselves; rows of an odd width that a kernel of
+ * dwords is the faster one for are copied into it.  vq_gemv_workspace_bytes returns 0 when
  * no kernel would use a workspace for this layer.  With workspace NULL or smaller than that, and for every other layer, the
  * call is vq_gemv.  Same arguments, bar and errors as vq_gemv; a workspace that is not 256-byte aligned is
  * VQ_ERR_ALIGNMENT.  Calls that share a workspace must not overlap.                                          */
