@@ -8,7 +8,9 @@ namespace {
 // A workgroup owns up to four stack positions (P of them) and walks all columns of the matrix with them: nothing it needs comes
 // from another workgroup.  Four of its eight waves search, one on each SIMD; the tables stay where they are for the whole launch: as
 // operands of v_mfma_f32_16x16x32_f16 in their registers, 64 centroids a wave and group (sixteen groups of a 4096-entry table), and as
-// plain entries in LDS.  The other four keep the positions' rows of the running block, a column to a thread.
+// plain entries in LDS.  The other four keep the positions' rows of the running block and of the next one, 64 columns a wave, as results of
+// v_mfma_f32_4x4x1_16b_f32: four rows (broadcast from one of the sixteen blocks of operand A) by 64 columns, so that P v = 18 rows
+// cost 20 (of 32x32x2 they would use 18 of 32).
 //
 // One column.  Every search wave holds the P vectors t, up to four elements a lane (lane 16 q + 4 n + j: vector n, the j-th quarter
 // of its elements; the four rows of lanes alike), scales them by a power of two and rounds them to binary16: operand B.  Scores
@@ -25,23 +27,28 @@ namespace {
 //
 // The block's running weights lag two columns behind: t of column n + 1 is the value with the errors up to column n - 2, which the
 // keeping waves post while column n is searched, less the last two errors' shares, which the search waves hold.  The keeping
-// waves also file E, T and the indices.
+// waves also file E; the search waves store T, the quantized weights and the indices, one kind a wave, as they never wait for memory.
 //
-// At the end of a block the workgroup writes its quantized columns and indices and applies E to its rows of the later columns:
-// v_mfma_f32_4x4x1_16b_f32, four rows (broadcast from one of the sixteen blocks of operand A) by 64 columns, so that P v = 18 rows
-// cost 20 (of 32x32x2 they would use 18 of 32); the rows of H^-1 come straight from memory.
+// Between two blocks there is little to do: the next one's columns have their errors already.  The columns beyond it take a block's errors beside the
+// next block's columns: a step of eight rows of H^-1 by 128 columns a keeping wave and column, its loads a column ahead, until all columns
+// have them (what is left at the end of a block, beyond 4096 columns or so, follows without a pause).
 //
 // What bounds it: the chain of a column.  A wave on its own issues an instruction every five clocks or so, and what counts is how many
-// stand on the path between one column's t and the next (about 230 with a 4096-entry table), the LDS round trips (130 clocks, four of
-// them) and the barrier, not any rate: 1900 clocks a column, of which the comparisons of the scores are 500.  Eight search waves
-// of half the table each are slower (4.8 ms against 4.6): everything but the comparisons is then issued twice on every SIMD.
-// The end of a block waits for H^-1 (1 MB through every compute unit, which takes 64 bytes a clock) and for W, 94 of 340 thousand clocks at
-// 4096 columns.  Before, with the vector posted and its errors kept by one wave, three barriers and the low parts of t
-// multiplied as well, a column took 3700 clocks.  v = 6, k = 4096, 4096 x 4096: 7.2 -> 4.6 ms; 300 x 1000: 1.38 -> 0.87; with a
-// 256-entry residual table, 1500 x 1000: 2.23 -> 1.50; v = 12, k = 4096, 1500 x 1000: 2.28 -> 1.42; v = 4, k = 256: 1.26 -> 0.62.
+// stand on the path between one column's t and the next (about 200 with a 4096-entry table), the LDS round trips (130 clocks, four of
+// them) and the barrier, not any rate: 2000 clocks a column (of 2.4 GHz), of which the comparisons of the scores are 500.  Whatever else a SIMD
+// executes adds to that, binary32 products above all: they keep the search wave from issuing for as long as they take, wherever in a column
+// they stand and whatever the waves' priorities (80 instructions of 8 clocks a column: search 1910 -> 2460 clocks; without any later columns
+// 4096 x 4096 would take 3.5 ms, 0.5 of the 0.6 between are the products).  Eight search waves of half the table each are slower (4.8 ms against 4.6
+// then): everything but the comparisons is issued twice on every SIMD.
+// With the later columns' update at the end of each block, by all waves and waiting for H^-1 and W, 94 of a block's 340 thousand clocks:
+// v = 6, k = 4096, 4096 x 4096 4.57 -> 4.10 ms; 3000 x 2000 1833 -> 1737 us; v = 8, k = 4096 2670 -> 2267; v = 12, k = 4096 2799 -> 2440; v = 4, k = 256
+// 1347 -> 1191.  The same update as 16 x 16 x 1 products in place of 4 x 4 x 1 took as long, and so did one ahead of the kept columns' update
+// in place of behind it; sums in the vector ALUs for the kept columns 2 % longer; stores of T, weights and indices by the keeping waves,
+// whose loads then wait for them, 2 % longer.
 typedef _Float16 half8v __attribute__((ext_vector_type(8)));
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef float float4v __attribute__((ext_vector_type(4)));
+typedef float float2v __attribute__((ext_vector_type(2)));
 
 constexpr int PMAX = 4;
 constexpr int SEARCH = 4, KEEP = 4;      // waves
@@ -50,17 +57,19 @@ constexpr int LOOP_THREADS = (SEARCH + KEEP) * 64;
 constexpr int entry_slots(int vp) { return vp <= 6 ? 8 : vp <= 14 ? 16 : 32; }
 constexpr int entries_wide(int vp) { return 32 / entry_slots(vp); }
 constexpr int group_tiles(int vp) { return 4 / entries_wide(vp); }
-constexpr int E_PITCH = QB + 1;
 constexpr int quarter(int vp) { return vp <= 8 ? 2 : vp <= 12 ? 3 : 4; }     // elements a lane holds of a vector
 constexpr unsigned TAG = 63u;            // group, tile and place: the lowest bits of a score
 
 struct ColumnConstants { float diag, inverse, beside, beside2; };            // of H^-1: (n, n), its reciprocal or 0, (n, n + 1), (n - 1, n + 1)
 
+constexpr int ROWS = 36;                 // of four positions of eight or two of sixteen, and four more that whole sixteen-byte pieces take
+
 struct LoopExchange {                    // LDS
   unsigned long long nearest[2][4][PMAX];  // [main, residual][column & 3]: smallest (distance bits, index) so far
-  // lane layout: [vector][quarter][element]
-  float next_w[2][PMAX * 16];            // the next column's weights without the last two errors
-  float e[2][PMAX * 16], t[2][PMAX * 16];
+  // by rows (vector * VP + element), in whole quarters of the last vector
+  float next_w[2][ROWS];                 // the next column's weights without the last two errors
+  float e[2][ROWS];
+  float first_t[ROWS];                   // the weights of a block's first column
   ColumnConstants column[QB];
   float h_max[2][SEARCH + KEEP], c_bad[2][SEARCH + KEEP];
 };
@@ -70,9 +79,16 @@ template <int VP> constexpr int loop_entry_halfs() { return VP <= 4 ? 4 : VP <= 
 template <int VP>
 __device__ __forceinline__ constexpr int entry_place(int el) { return VP == 12 ? el / 3 * 4 + el % 3 : el; }
 
+// E of a block and of the one before: [row p * VP + j][column], rows in whole operands, columns in whole steps of the update (FAR) and four more
+// (sixteen-byte reads of neighbouring rows then take neighbouring banks).
+constexpr int FAR = 8;
+constexpr int positions_most(int vp) { return 32 / vp < PMAX ? 32 / vp : PMAX; }
+constexpr int e_rows(int vp) { return (positions_most(vp) * vp + 3) / 4 * 4; }
+__host__ __device__ constexpr int e_pitch(int block) { return (block + FAR - 1) / FAR * FAR + 4; }
+
 template <int VP>
-size_t loop_lds_bytes(int k, int k_res) {
-  return (size_t)(k + k_res) * loop_entry_halfs<VP>() * 2 + 32 * E_PITCH * 4 + 2 * PMAX * QB * 4 + sizeof(LoopExchange) + 64;
+size_t loop_lds_bytes(int k, int k_res, int block) {
+  return (size_t)(k + k_res) * loop_entry_halfs<VP>() * 2 + (size_t)2 * e_rows(VP) * e_pitch(block) * 4 + sizeof(LoopExchange) + 64;
 }
 
 // Centroid whose slots a lane holds in tile `tile` of group `g`, and which eight of them: row m of operand A is lane m of every
@@ -397,12 +413,12 @@ __device__ __forceinline__ void search_narrow(unsigned long long *nearest, const
 // SHORT: with positions of one or two rows among them (a kernel of its own, as the second search costs the first one 4 %).
 template <int VP, int G, int GR, bool SHORT>
 __global__ __launch_bounds__(LOOP_THREADS) void qcol_loop_kernel(LoopArgs a) {
-  constexpr int EH = loop_entry_halfs<VP>(), EPL = quarter(VP), POS = 32 / VP < PMAX ? 32 / VP : PMAX;
+  constexpr int EH = loop_entry_halfs<VP>(), EPL = quarter(VP), POS = positions_most(VP), E_ROWS = e_rows(VP);
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   __half *entries = reinterpret_cast<__half *>(smem);                                          // [k + k_res][EH]
-  float *E = reinterpret_cast<float *>(smem + (((size_t)(a.k + a.k_res) * EH * 2 + 15) & ~(size_t)15));   // [32][E_PITCH]: row p * VP + j
-  unsigned *codes = reinterpret_cast<unsigned *>(E + 32 * E_PITCH);                            // [2][PMAX][QB]
-  LoopExchange &x = *reinterpret_cast<LoopExchange *>(codes + 2 * PMAX * QB);
+  const int pitch_e = e_pitch(a.block);
+  float *E = reinterpret_cast<float *>(smem + (((size_t)(a.k + a.k_res) * EH * 2 + 15) & ~(size_t)15));   // [2][E_ROWS][pitch_e]: row p * VP + j
+  LoopExchange &x = *reinterpret_cast<LoopExchange *>(E + 2 * E_ROWS * pitch_e);
   constexpr int threads = LOOP_THREADS;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -421,10 +437,9 @@ __global__ __launch_bounds__(LOOP_THREADS) void qcol_loop_kernel(LoopArgs a) {
     const __half *src = i < a.k ? a.cb + (long long)i * a.v : a.cb_res + (long long)(i - a.k) * a.v;
     entries[e] = j < len ? src[j] : __float2half_rn(0.0f);
   }
-  for (int e = tid; e < 32 * E_PITCH; e += threads) E[e] = 0.0f;
+  for (int e = tid; e < 2 * E_ROWS * pitch_e; e += threads) E[e] = 0.0f;
   if (tid < 8 * PMAX) (&x.nearest[0][0][0])[tid] = ~0ull;
-  for (int e = tid; e < PMAX * 16 * 6; e += threads) (&x.next_w[0][0])[e] = 0.0f;              // (and e and t behind them)
-  half8v A[G][group_tiles(VP)], AR[GR ? GR : 1][group_tiles(VP)];
+  for (int e = tid; e < ROWS * 5; e += threads) (&x.next_w[0][0])[e] = 0.0f;                   // (and e and first_t behind them)
   LoopTable main_table, res_table;
   {
     auto post_norms = [&](int which, const __half *cb, int k) {
@@ -442,50 +457,85 @@ __global__ __launch_bounds__(LOOP_THREADS) void qcol_loop_kernel(LoopArgs a) {
     post_norms(0, a.cb, a.k);
     if constexpr (GR) post_norms(1, a.cb_res, a.k_res);
     __syncthreads();
-    main_table = loop_table<VP>(x.h_max[0], x.c_bad[0]);
-    if constexpr (GR) res_table = loop_table<VP>(x.h_max[1], x.c_bad[1]);
-    if (searching) {
-      load_operands<VP, G>(a.cb, a.k, a.v, len, main_table.f, lane, wave, A);
-      if constexpr (GR) load_operands<VP, GR>(a.cb_res, a.k_res, a.v, len, res_table.f, lane, wave, AR);
-    }
   }
-  const __half *entries_res = entries + (size_t)a.k * EH;
 
-  for (int s = 0; s < a.cols; s += a.block) {
-    const int s_end = min(s + a.block, a.cols), nb = s_end - s;
-    if (searching) {
-      // (lanes of vectors past the last repeat the first)
-      const int n = ((lane >> 2) & 3) < P ? (lane >> 2) & 3 : 0, j = lane & 3;
-      const LaneMasks in = lane_masks<VP>(lane);
-      float t[EPL], e_last[EPL];
+  // Barriers of a block, the same ones for searching and keeping waves: its first column's weights and constants are there; one a column (two
+  // with a residual table); the last column's errors are there.
+  if (searching) {
+    const __half *entries_res = entries + (size_t)a.k * EH;
+    half8v A[G][group_tiles(VP)], AR[GR ? GR : 1][group_tiles(VP)];
+    main_table = loop_table<VP>(x.h_max[0], x.c_bad[0]);
+    load_operands<VP, G>(a.cb, a.k, a.v, len, main_table.f, lane, wave, A);
+    if constexpr (GR) {
+      res_table = loop_table<VP>(x.h_max[1], x.c_bad[1]);
+      load_operands<VP, GR>(a.cb_res, a.k_res, a.v, len, res_table.f, lane, wave, AR);
+    }
+    // (lanes of vectors past the last repeat the first)
+    const int n = ((lane >> 2) & 3) < P ? (lane >> 2) & 3 : 0, j = lane & 3;
+    const int own = EPL * j < VP ? n * VP + EPL * j : 32;     // its elements' rows (past a vector: zeros)
+    const LaneMasks in = lane_masks<VP>(lane);
+    // an entry's elements, in the lanes that hold them of the vector that took it
+    auto elements = [&](const __half *table, unsigned i, float (&q)[EPL]) {
+      unsigned at = i * EH + (EPL == 2 ? 2 * j : 4 * j);
+      if constexpr (VP == 4) at = i * EH + 2 * (j & 1);
+      const uint2v y = EPL == 2 ? uint2v{*reinterpret_cast<const unsigned *>(table + at), 0u} : *reinterpret_cast<const uint2v *>(table + at);
 #pragma unroll
       for (int r = 0; r < EPL; ++r) {
-        t[r] = EPL * j + r < len ? a.W[(long long)((first + n) * a.v + EPL * j + r) * a.ldw + s] : 0.0f;
-        e_last[r] = 0.0f;
+        q[r] = half_of(r < 2 ? y.x : y.y, r & 1);
+        if constexpr (VP == 4) q[r] = j < 2 ? q[r] : 0.0f;
       }
-      // an entry's elements, in the lanes that hold them of the vector that took it
-      auto elements = [&](const __half *table, unsigned i, float (&q)[EPL]) {
-        unsigned at = i * EH + (EPL == 2 ? 2 * j : 4 * j);
-        if constexpr (VP == 4) at = i * EH + 2 * (j & 1);
-        const uint2v y = EPL == 2 ? uint2v{*reinterpret_cast<const unsigned *>(table + at), 0u} : *reinterpret_cast<const uint2v *>(table + at);
+    };
+    // What a finished column leaves in memory: T from one wave, the quantized weights from another, the indices of either table from the other two.
+    // (These waves never wait for memory.)  One row of lanes does it, for the vectors that are there; the offsets of all others are past the
+    // end: a store that does nothing takes less than a branch.
+    const bool files = lane < 4 * P;
+    const bool files_t = wave == 1 && a.T, files_q = wave == 2;
+    const int ld_mine = files_t ? (int)a.ldt : (int)a.ldw;
+    const auto rows_mine = __builtin_amdgcn_make_buffer_rsrc((files_t ? a.T : a.W) + (long long)first * a.v * ld_mine, 0, P * a.v * ld_mine * 4, 0x00020000);
+    const unsigned any_t = files_t ? ~0u : 0u;
+    unsigned to[EPL];
 #pragma unroll
-        for (int r = 0; r < EPL; ++r) {
-          q[r] = half_of(r < 2 ? y.x : y.y, r & 1);
-          if constexpr (VP == 4) q[r] = j < 2 ? q[r] : 0.0f;
-        }
-      };
-      const int own = n * 16 + j * 4;                        // lane layout
+    for (int r = 0; r < EPL; ++r) to[r] = (files_t || files_q) && files && EPL * j + r < len ? (unsigned)((n * a.v + EPL * j + r) * ld_mine) * 4u : 0x7FFFFFFFu;
+    // indices, a stream to a lane: whole dwords of them (no other workgroup writes these streams, which were cleared beforehand)
+    struct Stream { unsigned *to, bits; int filled; };
+    const bool streams = files && j == 0;
+    auto stream = [&](unsigned *idx, long long dwords) { return Stream{idx + (long long)(first + n) * dwords, 0u, 0}; };
+    auto append = [&](Stream &st, unsigned code, int bits) {
+      st.bits |= code << st.filled;
+      st.filled += bits;
+      if (st.filled >= 32) {
+        if (streams) *st.to = st.bits;
+        ++st.to;
+        st.filled -= 32;
+        st.bits = st.filled ? code >> (bits - st.filled) : 0u;
+      }
+    };
+    Stream main_stream = stream(a.idx, a.idx_dwords), res_stream = GR ? stream(a.idx_res, a.idx_res_dwords) : main_stream;
+    for (int s = 0; s < a.cols; s += a.block) {
+      const int nb = min(a.block, a.cols - s);
+      float t[EPL], e_last[EPL];
+      lds_barrier();
+#pragma unroll
+      for (int r = 0; r < EPL; ++r) { t[r] = x.first_t[own + r]; e_last[r] = 0.0f; }
       for (int nn = 0; nn < nb; ++nn) {
         Posted<VP> p = post_vectors<VP>(t, main_table, in, lane);
         bool odd = p.brute;
+        // (a t - q below 2^-80 is t, as entries are multiples of 2^-24; from there on the quotient is no subnormal number either)
+        unsigned least = ~0u;
+#pragma unroll
+        for (int r = 0; r < EPL; ++r) least = min(least, 2u * __float_as_uint(t[r]) - 1u);     // (but zero)
+        odd |= least < 2u * __float_as_uint(0x1p-80f) - 1u;
+        const ColumnConstants at = x.column[nn];
+        odd |= at.inverse == 0.0f;
         if (SHORT && narrow) search_narrow<VP, G>(x.nearest[0][nn & 3], A, a.k, t, P, lane, wave);
         else search_table<VP, G>(&x.nearest[0][nn & 3][n], A, smem, a.k, p, main_table, lane, wave);
         lds_barrier();
-        const ColumnConstants at = x.column[nn];
         float next[EPL], q[EPL], e[EPL];
-        elements(entries, (unsigned)x.nearest[0][nn & 3][n], q);
+        const unsigned code = (unsigned)x.nearest[0][nn & 3][n];
 #pragma unroll
         for (int r = 0; r < EPL; ++r) next[r] = x.next_w[nn & 1][own + r];
+        unsigned code_res = 0u;
+        elements(entries, code, q);
         if constexpr (GR) {
           float rest[EPL], more[EPL];
 #pragma unroll
@@ -495,7 +545,8 @@ __global__ __launch_bounds__(LOOP_THREADS) void qcol_loop_kernel(LoopArgs a) {
           if (SHORT && narrow) search_narrow<VP, GR>(x.nearest[1][nn & 3], AR, a.k_res, rest, P, lane, wave);
           else search_table<VP, GR>(&x.nearest[1][nn & 3][n], AR, smem + (size_t)a.k * EH * 2, a.k_res, p, res_table, lane, wave);
           lds_barrier();
-          elements(entries_res, (unsigned)x.nearest[1][nn & 3][n], more);
+          code_res = (unsigned)x.nearest[1][nn & 3][n];
+          elements(entries_res, code_res, more);
 #pragma unroll
           for (int r = 0; r < EPL; ++r) {
             // what inference restores: the binary32 sum of the two centroids, rounded to binary16 (Sec. 3.2.2)
@@ -507,41 +558,74 @@ __global__ __launch_bounds__(LOOP_THREADS) void qcol_loop_kernel(LoopArgs a) {
         // e = (t - q) / diag.  With the correctly rounded reciprocal, one correction of the rounded product gives the correctly rounded
         // quotient (Markstein, IBM J. Res. Dev. 34, 1990), where nothing overflows and the remainder, some 2^-47 of t - q, is a
         // binary32 number: not for numbers out of the ordinary.
-        // (a t - q below 2^-80 is t, as entries are multiples of 2^-24; from there on the quotient is no subnormal number either)
-        unsigned least = ~0u;
-#pragma unroll
-        for (int r = 0; r < EPL; ++r) least = min(least, 2u * __float_as_uint(t[r]) - 1u);     // (but zero)
-        odd |= least < 2u * __float_as_uint(0x1p-80f) - 1u;
 #pragma unroll
         for (int r = 0; r < EPL; ++r) {
           const float diff = __fsub_rn(t[r], q[r]), about = __fmul_rn(diff, at.inverse);
           e[r] = __fmaf_rn(-__fmaf_rn(about, at.diag, -diff), at.inverse, about);
         }
-        if (__builtin_expect(__builtin_amdgcn_ballot_w64(odd | (at.inverse == 0.0f)) != 0ull, 0)) {
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(odd) != 0ull, 0)) {
 #pragma unroll
           for (int r = 0; r < EPL; ++r) e[r] = __fdiv_rn(__fsub_rn(t[r], q[r]), at.diag);
         }
-        // (every wave writes the same)
 #pragma unroll
-        for (int r = 0; r < EPL; ++r) { x.e[nn & 1][own + r] = e[r]; x.t[nn & 1][own + r] = t[r]; }
+        for (int r = 0; r < EPL; ++r) {
+          x.e[nn & 1][own + r] = e[r];                       // (every wave writes the same)
+          const unsigned y = (__float_as_uint(t[r]) & any_t) | (__float_as_uint(q[r]) & ~any_t);
+          __builtin_amdgcn_raw_buffer_store_b32((int)y, rows_mine, to[r], (s + nn) * 4, 0);
+        }
+        if (wave == 3) append(main_stream, code, a.bits);
+        if constexpr (GR) { if (wave == 0) append(res_stream, code_res, a.bits_res); }
 #pragma unroll
         for (int r = 0; r < EPL; ++r) {
           t[r] = __fmaf_rn(-e[r], at.beside, __fmaf_rn(-e_last[r], at.beside2, next[r]));
           e_last[r] = e[r];
         }
       }
-    } else {
-      // Keeping waves: thread c, and c + 128, hold column c of every other position's rows.
-      const int c = (tid - SEARCH * 64) & (QB - 1);
-      const int odd = __builtin_amdgcn_readfirstlane((tid - SEARCH * 64) / QB);
-      float w[(POS + 1) / 2][VP];
+      lds_barrier();
+    }
+    if (wave == 3 && streams && main_stream.filled) *main_stream.to = main_stream.bits;
+    if constexpr (GR) { if (wave == 0 && streams && res_stream.filled) *res_stream.to = res_stream.bits; }
+    return;
+  }
+
+  // Keeping waves: 64 columns each, two waves those of the running block, two those of the next one, and in the next block the other way round.
+  // A column of the block is one row of H^-1 for them: row 4 b + i of its errors in lane 4 b + i of operand A, of which an instruction
+  // (4x4x1, 16 blocks) takes block b; the row's columns in operand B, one to a lane; the lane gets back rows 4 b .. 4 b + 3 of its column.
+  auto keep = [&](auto positions) {
+    constexpr int NP = decltype(positions)::value, RG = (NP * VP + 3) / 4;
+    const int kw = wave - SEARCH;
+    const int pitch_h = (int)a.ldh * 4, pitch_w = (int)a.ldw * 4;
+    const auto rows_of_W = __builtin_amdgcn_make_buffer_rsrc(a.W + (long long)first * a.v * a.ldw, 0, ((NP - 1) * a.v + len) * pitch_w, 0x00020000);
+    auto row_of_W = [&](int p, int el) { return (p * a.v + min(el, len - 1)) * pitch_w; };     // (past a position's rows: its last one)
+    // W[:, column] + w where a position has the row, else 0
+    float4v w[RG];
+    auto add_weights = [&](int col) {
+      float y[RG * 4];
 #pragma unroll
-      for (int h = 0; h < (POS + 1) / 2; ++h)
+      for (int r = 0; r < NP * VP; ++r) y[r] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rows_of_W, min(col, a.cols - 1) * 4, row_of_W(r / VP, r % VP), 0));
 #pragma unroll
-        for (int el = 0; el < VP; ++el)
-          w[h][el] = c < nb && 2 * h + odd < P && el < len ? a.W[(long long)((first + 2 * h + odd) * a.v + el) * a.ldw + s + c] : 0.0f;
-      auto hinv = [&](int row, int col) -> float { return row >= 0 && row < nb && col < nb ? a.Hinv[(long long)(s + row) * a.ldh + s + col] : 0.0f; };
-      if (odd == 0 && c < nb) {
+      for (int r = 0; r < RG * 4; ++r) w[r / 4][r % 4] = r < NP * VP && r % VP < len ? y[r < NP * VP ? r : 0] + w[r / 4][r % 4] : 0.0f;
+    };
+    auto clear = [&] {
+#pragma unroll
+      for (int g = 0; g < RG; ++g) w[g] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
+    };
+    auto post = [&](float *to) {
+#pragma unroll
+      for (int g = 0; g < RG; ++g) *reinterpret_cast<float4v *>(to + 4 * g) = w[g];
+    };
+    const int e_row = min(lane & 31, NP * VP - 1);           // operand A
+    clear();
+    if (kw < 2) add_weights(kw * 64 + lane);
+    int parity = 0;                                          // of the block: which half of E, which waves have its columns
+    for (int s = 0; s < a.cols; s += a.block, parity ^= 1) {
+      const int s_end = min(s + a.block, a.cols), nb = s_end - s;
+      const bool running = kw / 2 == parity;
+      const int mine = (running ? s : s_end) + kw % 2 * 64 + lane;          // column
+      float *E_now = E + parity * E_ROWS * pitch_e + e_row * pitch_e;
+      auto hinv = [&](int row, int col) -> float { return row >= 0 && col < nb ? a.Hinv[(long long)(s + row) * a.ldh + s + col] : 0.0f; };
+      const int c = tid - SEARCH * 64;
+      if (c < nb) {
         ColumnConstants at;
         at.diag = hinv(c, c);
         const float size = fabsf(at.diag);
@@ -550,148 +634,118 @@ __global__ __launch_bounds__(LOOP_THREADS) void qcol_loop_kernel(LoopArgs a) {
         at.beside2 = hinv(c - 1, c + 1);
         x.column[c] = at;
       }
-      // what a finished column leaves: E, T and the indices
-      const int i = tid - SEARCH * 64;                       // lane layout
-      const int ip = i >> 4, iel = EPL * (i >> 2 & 3) + (i & 3);
-      const bool files = i < PMAX * 16 && ip < P && (i & 3) < EPL && iel < len;
-      auto file = [&](int nn) {
-        if (files) {
-          E[(ip * VP + iel) * E_PITCH + nn] = x.e[nn & 1][i];
-          if (a.T) a.T[(long long)((first + ip) * a.v + iel) * a.ldt + s + nn] = x.t[nn & 1][i];
+      if (mine == s) post(x.first_t);
+      // The update of the columns beyond this block by the block before: W[:, later] -= E * Hinv[block before, later], 128 columns a wave at a
+      // time, FAR rows of H^-1 a column of the running block: row 4 b + i of E in lane 4 b + i of operand A, of which an instruction takes block b;
+      // a row of H^-1 in operand B, two neighbouring columns to a lane; the lane gets back rows 4 b .. 4 b + 3 of either.
+      const float *E_before = E + (parity ^ 1) * E_ROWS * pitch_e + min(lane & 31, E_ROWS - 1) * pitch_e;
+      const int far_groups = s > 0 ? (a.cols - s_end + 127) / 128 : 0;
+      const auto rows_before = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.Hinv + (long long)max(s - a.block, 0) * a.ldh), 0,
+                                                                 min(a.block, a.cols) * pitch_h, 0x00020000);
+      const int far_pitch = far_groups ? pitch_h : 0;        // (where there is nothing to do, the loads repeat the first row)
+      int fg = kw, fk = 0;
+      float4v acc[2][RG];
+      float2v hv[FAR];
+      float4v ev[FAR / 4];
+      // (a lane whose pair ends past the matrix computes the last pair once more)
+      auto far_offset = [&] { return min(s_end + fg * 128 + 2 * lane, max(a.cols - 2, 0)) * 4; };
+      auto far_loads = [&] {
+        const int off = far_offset();
+        int row = fk * far_pitch;
+#pragma unroll
+        for (int u = 0; u < FAR; ++u) {
+          hv[u] = __builtin_bit_cast(float2v, __builtin_amdgcn_raw_buffer_load_b64(rows_before, off, row, 0));
+          row += far_pitch;
         }
-        if (i < (GR ? 2 : 1) * PMAX) codes[i * QB + nn] = min((unsigned)x.nearest[i / PMAX][nn & 3][i % PMAX], (unsigned)(i / PMAX ? a.k_res : a.k) - 1u);
+#pragma unroll
+        for (int u = 0; u < FAR / 4; ++u) ev[u] = *reinterpret_cast<const float4v *>(E_before + fk + 4 * u);
       };
-      constexpr int RING = 8;
-      float row[RING], ahead[RING];
+      auto far_clear = [&] {
 #pragma unroll
-      for (int u = 0; u < RING; ++u) row[u] = hinv(u - 2, c);
+        for (int g = 0; g < RG; ++g) acc[0][g] = acc[1][g] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
+      };
+      auto far_step = [&] {
+#pragma unroll
+        for (int u = 0; u < FAR; ++u)
+#pragma unroll
+          for (int half = 0; half < 2; ++half) {
+#define VQ_ROWS(B) if constexpr (B < RG) acc[half][B < RG ? B : 0] = __builtin_amdgcn_mfma_f32_4x4x1f32(ev[u / 4][u % 4], hv[u][half], acc[half][B < RG ? B : 0], 4, B, 0);
+            VQ_ROWS(0) VQ_ROWS(1) VQ_ROWS(2) VQ_ROWS(3) VQ_ROWS(4) VQ_ROWS(5) VQ_ROWS(6) VQ_ROWS(7)
+#undef VQ_ROWS
+          }
+        fk += FAR;
+        if (fk < a.block) return;
+        if (s_end + fg * 128 + 2 * lane < a.cols) {
+          const int off = far_offset();
+          float2v fw[NP * VP];
+#pragma unroll
+          for (int r = 0; r < NP * VP; ++r) fw[r] = __builtin_bit_cast(float2v, __builtin_amdgcn_raw_buffer_load_b64(rows_of_W, off, row_of_W(r / VP, r % VP), 0));
+          auto store = [&](int r) {
+            const float2v y = {fw[r].x - acc[0][r / 4][r % 4], fw[r].y - acc[1][r / 4][r % 4]};
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uint2v, y), rows_of_W, off, row_of_W(r / VP, r % VP), 0);
+          };
+          if (len == VP) {
+#pragma unroll
+            for (int r = 0; r < NP * VP; ++r) store(r);
+          } else {
+#pragma unroll
+            for (int r = 0; r < NP * VP; ++r)
+              if (r % VP < len) store(r);
+          }
+        }
+        far_clear();
+        fg += KEEP; fk = 0;
+      };
+      far_clear();
+      far_loads();
+      constexpr int RING = 2;
+      float row[RING];
+      // (columns past the matrix are its last one, whose weights are not in use here)
+      const auto rows_now = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.Hinv + (long long)s * a.ldh), 0, nb * pitch_h, 0x00020000);
+      const int off_mine = min(mine, a.cols - 1) * 4;
+      auto ring = [&](int nr) { return __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rows_now, off_mine, min(max(nr, 0), nb - 1) * pitch_h, 0)); };
+      const float last2 = ring(nb - 2), last = ring(nb - 1);
+#pragma unroll
+      for (int u = 0; u < RING; ++u) row[u] = ring(u - 2);
+      auto update = [&](int nn, float h) {                   // by column nn
+        const float e = x.e[nn & 1][e_row];
+#define VQ_ROWS(B) if constexpr (B < RG) w[B < RG ? B : 0] = __builtin_amdgcn_mfma_f32_4x4x1f32(-e, h, w[B < RG ? B : 0], 4, B, 0);
+        VQ_ROWS(0) VQ_ROWS(1) VQ_ROWS(2) VQ_ROWS(3) VQ_ROWS(4) VQ_ROWS(5) VQ_ROWS(6) VQ_ROWS(7)
+#undef VQ_ROWS
+        if (kw == 0 && lane < NP * VP) E_now[nn] = e;
+      };
+      lds_barrier();
       for (int n0 = 0; n0 < nb; n0 += RING) {
-#pragma unroll
-        for (int u = 0; u < RING; ++u) ahead[u] = hinv(n0 + RING + u - 2, c);
 #pragma unroll
         for (int u = 0; u < RING; ++u) {
           const int nn = n0 + u;
           if (nn >= nb) break;
-          if (nn >= 2) {
-#pragma unroll
-            for (int h = 0; h < (POS + 1) / 2; ++h)
-#pragma unroll
-              for (int el = 0; el < VP; ++el)
-                w[h][el] = __fmaf_rn(-x.e[nn & 1][(2 * h + odd) % PMAX * 16 + el / EPL * 4 + el % EPL], row[u], w[h][el]);
-            file(nn - 2);
-          }
-          if (c == nn + 1)
-#pragma unroll
-            for (int h = 0; h < (POS + 1) / 2; ++h)
-#pragma unroll
-              for (int el = 0; el < VP; ++el) x.next_w[nn & 1][(2 * h + odd) % PMAX * 16 + el / EPL * 4 + el % EPL] = w[h][el];
-          if (i < 2 * PMAX) x.nearest[i / PMAX][(nn + 1) & 3][i % PMAX] = ~0ull;
-          lds_barrier();
+          if (nn >= 2) update(nn - 2, row[u]);
+          row[u] = ring(nn + RING - 2);
+          if (mine == s + nn + 1) post(x.next_w[nn & 1]);
+          if (kw == 3 && lane < 2 * PMAX) x.nearest[lane / PMAX][(nn + 1) & 3][lane % PMAX] = ~0ull;
           if constexpr (GR) lds_barrier();
+          // (the loads are there in every column, so that the compiler can count what it need not wait for)
+          if (fg < far_groups) far_step();
+          far_loads();
+          lds_barrier();
         }
-#pragma unroll
-        for (int u = 0; u < RING; ++u) row[u] = ahead[u];
       }
-      if (nb > 1) file(nb - 2);
+      while (fg < far_groups) { far_step(); far_loads(); }
+      // (the next block's columns are other waves' work: their stores have to be out)
+      __builtin_amdgcn_s_waitcnt(0);
+      lds_barrier();
+      if (kw == 3 && lane < 8 * PMAX) (&x.nearest[0][0][0])[lane] = ~0ull;       // (the next block's columns count from 0 again)
+      if (nb > 1) update(nb - 2, last2);
+      update(nb - 1, last);
+      if (running) clear();
+      else add_weights(mine);
     }
-    __syncthreads();
-    if (tid >= SEARCH * 64) {                                // (the last column)
-      const int i = tid - SEARCH * 64, nn = nb - 1;
-      const int ip = i >> 4, iel = EPL * (i >> 2 & 3) + (i & 3);
-      if (i < PMAX * 16 && ip < P && (i & 3) < EPL && iel < len) {
-        E[(ip * VP + iel) * E_PITCH + nn] = x.e[nn & 1][i];
-        if (a.T) a.T[(long long)((first + ip) * a.v + iel) * a.ldt + s + nn] = x.t[nn & 1][i];
-      }
-      if (i < (GR ? 2 : 1) * PMAX) codes[i * QB + nn] = min((unsigned)x.nearest[i / PMAX][nn & 3][i % PMAX], (unsigned)(i / PMAX ? a.k_res : a.k) - 1u);
-    }
-    __syncthreads();
-    if (tid < 8 * PMAX) (&x.nearest[0][0][0])[tid] = ~0ull;  // (the next block's columns count from 0 again)
-
-    // (what follows computes its addresses from copies of the thread's numbers that the compiler cannot see through: hoisted out
-    // of the block loop they would take the registers that the columns need)
-    int tid_e = tid, lane_e = lane;
-    asm volatile("" : "+v"(tid_e), "+v"(lane_e));
-    // the block's quantized columns and their indices (one per column: stream p, position n; the streams were cleared
-    // beforehand and no other workgroup touches these)
-    for (int i = tid_e; i < P * VP * QB; i += threads) {
-      const int c = i & (QB - 1), r = i / QB, p = r / VP, j = r - p * VP;
-      if (c >= nb || j >= len) continue;
-      float q = __half2float(entries[(size_t)codes[p * QB + c] * EH + entry_place<VP>(j)]);
-      if constexpr (GR) {
-        float sum = __fadd_rn(q, __half2float(entries_res[(size_t)codes[(PMAX + p) * QB + c] * EH + entry_place<VP>(j)]));
-        asm volatile("" : "+v"(sum));
-        q = __half2float(__float2half_rn(sum));
-      }
-      a.W[(long long)((first + p) * a.v + j) * a.ldw + s + c] = q;
-    }
-    for (int i = tid_e; i < P * QB * (GR ? 2 : 1); i += threads) {
-      const int c = i & (QB - 1), p = (i / QB) % P;
-      const bool res = i >= P * QB;
-      if (c >= nb) continue;
-      const int bits = res ? a.bits_res : a.bits;
-      const unsigned code = codes[((res ? PMAX : 0) + p) * QB + c];
-      const unsigned long long bit = (unsigned long long)(s + c) * (unsigned)bits;
-      unsigned *row = (res ? a.idx_res + (long long)(first + p) * a.idx_res_dwords : a.idx + (long long)(first + p) * a.idx_dwords) + (bit >> 5);
-      const unsigned sh = (unsigned)(bit & 31u);
-      atomicOr(row, code << sh);
-      if (sh + bits > 32) atomicOr(row + 1, code >> (32u - sh));
-    }
-    // W[:, later] -= E * Hinv[block, later], 64 columns a wave: row 4 b + i of E in lane 4 b + i of operand A, of which an instruction takes
-    // block b; row k of H^-1 in operand B, a column to a lane; the lane gets back rows 4 b .. 4 b + 3 of its column.
-    const int pitch = (int)a.ldh * 4;
-    const auto rows_of_block = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.Hinv + (long long)s * a.ldh), 0, nb * pitch, 0x00020000);
-    auto later = [&](auto positions) {
-      constexpr int NP = decltype(positions)::value, RG = (NP * VP + 3) / 4;
-      constexpr int UN = 16;                                 // rows on their way at once, and as many in use
-      const float *row_e = E + (lane_e & 31) * E_PITCH;
-      for (int c0 = s_end + wave * 64; c0 < a.cols; c0 += SEARCH * 64 + KEEP * 64) {
-        const int c = c0 + lane_e;
-        const bool in = c < a.cols;
-        const int off = (in ? c : a.cols - 1) * 4;
-        constexpr bool EARLY = G * group_tiles(VP) <= 16;    // (else the tables leave no registers for it)
-        float w[NP * VP];
-        auto weights = [&] {
-#pragma unroll
-          for (int r = 0; r < NP * VP; ++r) w[r] = in && r % VP < len ? a.W[(long long)((first + r / VP) * a.v + r % VP) * a.ldw + c] : 0.0f;
-        };
-        if constexpr (EARLY) weights();
-        float4v acc[RG];
-#pragma unroll
-        for (int g = 0; g < RG; ++g) acc[g] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
-        float hv[UN];
-        // (past the block E has zeros, which add nothing)
-        auto rows = [&](int k0, float (&y)[UN]) {
-#pragma unroll
-          for (int u = 0; u < UN; ++u)
-            y[u] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rows_of_block, off, min(k0 + u, nb - 1) * pitch, 0));
-        };
-        rows(0, hv);
-        for (int k0 = 0; k0 < nb; k0 += UN) {
-          float ahead[UN], ev[UN];
-          rows(k0 + UN, ahead);
-#pragma unroll
-          for (int u = 0; u < UN; ++u) ev[u] = row_e[k0 + u];
-#pragma unroll
-          for (int u = 0; u < UN; ++u) {
-#define VQ_ROWS(B) if constexpr (B < RG) acc[B < RG ? B : 0] = __builtin_amdgcn_mfma_f32_4x4x1f32(ev[u], hv[u], acc[B < RG ? B : 0], 4, B, 0);
-            VQ_ROWS(0) VQ_ROWS(1) VQ_ROWS(2) VQ_ROWS(3) VQ_ROWS(4) VQ_ROWS(5) VQ_ROWS(6) VQ_ROWS(7)
-#undef VQ_ROWS
-          }
-#pragma unroll
-          for (int u = 0; u < UN; ++u) hv[u] = ahead[u];
-        }
-        if constexpr (!EARLY) weights();
-#pragma unroll
-        for (int r = 0; r < NP * VP; ++r)
-          if (in && r % VP < len) a.W[(long long)((first + r / VP) * a.v + r % VP) * a.ldw + c] = w[r] - acc[r / 4][r % 4];
-      }
-    };
-    if (P == 1) later(std::integral_constant<int, 1>{});
-    if constexpr (POS >= 2) { if (P == 2) later(std::integral_constant<int, 2>{}); }
-    if constexpr (POS >= 3) { if (P == 3) later(std::integral_constant<int, 3>{}); }
-    if constexpr (POS >= 4) { if (P == 4) later(std::integral_constant<int, 4>{}); }
-    __syncthreads();
-  }
+  };
+  if (P == 1) keep(std::integral_constant<int, 1>{});
+  if constexpr (POS >= 2) { if (P == 2) keep(std::integral_constant<int, 2>{}); }
+  if constexpr (POS >= 3) { if (P == 3) keep(std::integral_constant<int, 3>{}); }
+  if constexpr (POS >= 4) { if (P == 4) keep(std::integral_constant<int, 4>{}); }
 }
 
 template <int VP, int G, int GR, bool SHORT = false>
@@ -703,14 +757,17 @@ int launch_loop(LoopArgs a, hipStream_t st) {
   auto kernel = qcol_loop_kernel<VP, G, GR, SHORT>;
   VQ_ALLOW_FULL_LDS(kernel);
   const unsigned grid = (unsigned)((a.whole + a.P - 1) / a.P + cut);
-  hipLaunchKernelGGL(kernel, dim3(grid), dim3(LOOP_THREADS), loop_lds_bytes<VP>(a.k, a.k_res), st, a);
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(LOOP_THREADS), loop_lds_bytes<VP>(a.k, a.k_res, a.block), st, a);
   return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
 }
 
 // Groups of 64 centroids a search wave holds of each table: one up to 256 entries, four up to 1024, sixteen up to 4096.
 template <int VP>
 int launch_loop_vp(LoopArgs a, hipStream_t st) {
-  if (loop_lds_bytes<VP>(a.k, a.k_res) > 160 * 1024 || a.ldh > (1 << 21)) return VQ_ERR_UNSUPPORTED;    // (a block of H^-1: 32-bit offsets)
+  a.block = (a.block + FAR - 1) / FAR * FAR;
+  // (the block decides no more than where sums are split: where two large tables leave too little LDS for E, a smaller one)
+  while (loop_lds_bytes<VP>(a.k, a.k_res, a.block) > 160 * 1024 && a.block > 64) a.block -= 16;
+  if (loop_lds_bytes<VP>(a.k, a.k_res, a.block) > 160 * 1024 || a.ldh > (1 << 21) || a.ldw > (1 << 22) || a.ldt > (1 << 22)) return VQ_ERR_UNSUPPORTED;    // (a block of H^-1, the rows of a workgroup: 32-bit offsets)
   a.whole = a.rows / a.v;
   // positions per workgroup: as few as let every workgroup have a compute unit; E has 32 rows
   a.P = min(min(PMAX, 32 / VP), max(1, (a.whole + cu_count() - 2) / (cu_count() - 1)));

@@ -180,6 +180,46 @@ TIGHT = {
 }
 
 
+# What a block leaves to the columns beyond the next one is applied beside the next block's columns, 128 columns a wave and eight rows of H^-1 a step:
+# widths that end inside a pair of columns, inside 128 of them, in the first and in later turns of the four waves; blocks that are not whole
+# steps; one to four positions a workgroup and a cut-off one; tables that leave too little LDS for a block of 128.
+LATER = {
+    "one_column_beyond": dict(M=13, N=257, v=6, k=64, k_res=0, B=128),
+    "odd_pair": dict(M=13, N=385, v=6, k=64, k_res=16, B=128),
+    "two_turns_two_positions": dict(M=1603, N=905, v=6, k=16, k_res=0, B=128),
+    "three_positions": dict(M=3100, N=300, v=6, k=16, k_res=0, B=64),
+    "four_positions": dict(M=4203, N=261, v=4, k=16, k_res=0, B=64),
+    "v5_in_six": dict(M=1604, N=300, v=5, k=64, k_res=0, B=96),
+    "v16_two_positions": dict(M=4200, N=150, v=16, k=16, k_res=0, B=40),
+    "block_of_three": dict(M=20, N=150, v=6, k=64, k_res=0, B=3),
+    "block_of_100": dict(M=20, N=420, v=8, k=64, k_res=0, B=100),
+    "many_turns_of_a_short_block": dict(M=7, N=1500, v=6, k=16, k_res=0, B=8),
+    "v12_smaller_block_than_asked": dict(M=30, N=300, v=12, k=4096, k_res=200, B=128),
+}
+
+
+@pytest.mark.parametrize("name", list(LATER))
+def test_quantize_columns_later_columns(gpu_lib, name):
+    import torch
+    case = LATER[name]
+    M, N, v, k, k_res, B = (case[n] for n in ("M", "N", "v", "k", "k_res", "B"))
+    seed = 160 + list(LATER).index(name)
+    W0 = s.make_weights(600 + seed, M, N)
+    H = s.make_hessian(600 + seed, N)
+    U = np.ascontiguousarray(np.linalg.cholesky(np.linalg.inv(H)).T, dtype=np.float32)
+    C, R = _tables(seed, k, v, k_res)
+    Wd = torch.from_numpy(W0.astype(np.float32)).cuda()
+    idx_b, idx_res_b, T = gpu_lib.quantize_columns(Wd, torch.from_numpy(U).cuda(), torch.from_numpy(C).cuda(),
+                                                   torch.from_numpy(R).cuda() if k_res else None, block=B)
+    torch.cuda.synchronize()
+    idx = _unpack(idx_b.cpu().numpy(), oracle.index_bits(k), N)
+    idx_res = _unpack(idx_res_b.cpu().numpy(), oracle.index_bits(k_res), N) if k_res else None
+    replay = oracle.quantize_columns(W0, U, C, R, block=B, given=(idx, idx_res))
+    rms = np.sqrt((W0 ** 2).mean())
+    assert np.abs(replay["T"] - T.cpu().numpy().astype(np.float64)).max() <= TOL_T * rms
+    assert np.array_equal(replay["What"], Wd.cpu().numpy().astype(np.float64))
+
+
 def _tight_tables(seed, case):
     C, R = _tables(seed, case["k"], case["v"], case["k_res"])
     for T in (C, R):
