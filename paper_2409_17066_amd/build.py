@@ -38,16 +38,17 @@ AUDITED = ["vq_gemv_mfma.hip", "vq_gemm_fused.hip", "vq_gemm_dense.hip", "vq_gem
 # this group") and c < n_chunks ("chunks left") once per copy of its body.  A pass that is skipped in one copy and taken in the next would
 # meet fewer loads in flight than its wait counts on; my_passes does not change inside the loop, and the loads of a taken pass are issued
 # whether or not chunks are left.  groups, multi and parts are the same body (gemv_v6_mfma_body) in other grids: the findings of
-# parts<R, 2> are, instruction by instruction and register by register, those of kernel<R, 8, 2, false, false>, and stand behind the same
-# two tests, as a part of the columns is what a group is there.
+# parts<R, 2> are, instruction by instruction and register by register, those of kernel<R, 8, 2, false, SIX>, and stand behind the same
+# two tests, as a part of the columns is what a group is there; so are those of the three with activations through LDS (STAGED, 2).
 CROSS_BLOCK_KNOWN = {"vq_gemv_mfma.hip": {
-    "gemv_v6_mfma_kernelILi0ELi8ELi2ELb0ELb1E": 64, "gemv_v6_mfma_kernelILi0ELi8ELi2ELb0ELb0E": 20, "gemv_v6_mfma_kernelILi0ELi8ELi2ELb1ELb0E": 20,
-    "gemv_v6_mfma_kernelILi8ELi8ELi2ELb0ELb0E": 16, "gemv_v6_mfma_kernelILi8ELi8ELi2ELb1ELb0E": 128, "gemv_v6_mfma_kernelILi12ELi8ELi2ELb0ELb0E": 24,
-    "gemv_v6_mfma_kernelILi12ELi8ELi2ELb1ELb0E": 128, "gemv_v6_mfma_parts_kernelILi0ELi2E": 20, "gemv_v6_mfma_parts_kernelILi8ELi2E": 16,
-    "gemv_v6_mfma_parts_kernelILi12ELi2E": 24, "gemv_v6_mfma_groups_kernelILi0ELi8ELi2E": 20, "gemv_v6_mfma_groups_kernelILi8ELi8ELi2E": 16,
+    "gemv_v6_mfma_kernelILi0ELi8ELi2ELb0ELi1E": 64, "gemv_v6_mfma_kernelILi0ELi8ELi2ELb0ELi0E": 20, "gemv_v6_mfma_kernelILi0ELi8ELi2ELb1ELi0E": 20,
+    "gemv_v6_mfma_kernelILi8ELi8ELi2ELb0ELi0E": 16, "gemv_v6_mfma_kernelILi8ELi8ELi2ELb1ELi0E": 128, "gemv_v6_mfma_kernelILi12ELi8ELi2ELb0ELi0E": 24,
+    "gemv_v6_mfma_kernelILi12ELi8ELi2ELb1ELi0E": 128, "gemv_v6_mfma_parts_kernelILi0ELi2ELi0E": 20, "gemv_v6_mfma_parts_kernelILi8ELi2ELi0E": 16,
+    "gemv_v6_mfma_parts_kernelILi12ELi2ELi0E": 24, "gemv_v6_mfma_groups_kernelILi0ELi8ELi2E": 20, "gemv_v6_mfma_groups_kernelILi8ELi8ELi2E": 16,
     "gemv_v6_mfma_groups_kernelILi12ELi8ELi2E": 128, "gemv_v6_mfma_groups_kernelILi0ELi4ELi2E": 20, "gemv_v6_mfma_groups_kernelILi8ELi4ELi2E": 16,
-    "gemv_v6_mfma_multi_kernelILi0ELi8ELi2ELb1E": 64, "gemv_v6_mfma_multi_kernelILi0ELi8ELi2ELb0E": 20, "gemv_v6_mfma_multi_kernelILi8ELi8ELi2ELb0E": 16,
-    "gemv_v6_mfma_multi_kernelILi12ELi8ELi2ELb0E": 24}}
+    "gemv_v6_mfma_multi_kernelILi0ELi8ELi2ELi1E": 64, "gemv_v6_mfma_multi_kernelILi0ELi8ELi2ELi0E": 20, "gemv_v6_mfma_multi_kernelILi8ELi8ELi2ELi0E": 16,
+    "gemv_v6_mfma_multi_kernelILi12ELi8ELi2ELi0E": 24,
+    "gemv_v6_mfma_kernelILi0ELi8ELi2ELb0ELi2E": 20, "gemv_v6_mfma_multi_kernelILi0ELi8ELi2ELi2E": 20, "gemv_v6_mfma_parts_kernelILi0ELi2ELi2E": 20}}
 # The compiler whose generated code the counted waits were last checked against (first line of `hipcc --version`).
 VERIFIED_HIPCC = "HIP version: 7.2.26015-fc0010cf6a"
 

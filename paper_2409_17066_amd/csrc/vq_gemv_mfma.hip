@@ -23,7 +23,6 @@
 // binary32, from one group to the next, and the last group applies scale and bias and stores.
 #include "vq_common.hpp"
 #include "vq_v6.hpp"
-#include <cstdlib>
 
 namespace vq {
 namespace {
@@ -33,13 +32,18 @@ using namespace v6;
 constexpr int MW = 8;            // waves per workgroup
 constexpr int NBMAX = 6;         // 16-row blocks per chunk
 constexpr int VPL = 8;           // vectors per lane per pass: 8 x 12 bits = 3 dwords, 8 x 8 bits = 2 dwords
+constexpr int SIX = 0, DIRECT = 1, STAGED = 2;              // ways of a pass's activations into the operands (see gemv_v6_mfma_body)
+// (blocks a chunk that STAGED is compiled for, see stages(); the others, which no launch asks for, stand for one)
+constexpr int STAGED_NB(int res_bits, int nb) { return nb <= (res_bits ? 1 : 5) ? nb : 1; }
+constexpr unsigned STAGE_TOKEN = 13 * 16, STAGE_BYTES = 16 * STAGE_TOKEN;    // four lanes' 48 bytes, and 16 between the tokens' banks
 
 struct MfmaPlan {
-  int rows_per_wg;               // multiple of 16
+  int rows_per_wg;               // multiple of 4: the last of its blocks of 16 rows may be short
   int nb;                        // blocks per chunk, 1 .. NBMAX
   int part_bufs;                 // 1: barrier after the reduction as well; 2: chunks alternate buffers; 0: there is one chunk, and its partials
-                                 // lie over the tables, which a barrier has found to be done with
-  unsigned lds_out, lds_part, lds_xs;
+                                 // lie over the tables, which a barrier has found to be done with; 3 (STAGED): as 1, over the activations
+                                 // on their way
+  unsigned lds_out, lds_part, lds_xs;   // (behind lds_xs, STAGED: the activations on their way to a wave's lanes, STAGE_BYTES a wave)
   unsigned x_bytes;              // bytes from x[0][0] to the end of the last batch row
   int y_wide;                    // y rows allow 8-byte stores
   unsigned lds_sb;               // scale | bias << 16 of the workgroup's rows
@@ -68,18 +72,20 @@ __device__ __forceinline__ float4v mfma16(uint4v a, uint4v b, float4v c) {
 // LDS address, activations loaded straight into MFMA operand registers, load addresses advanced by
 // additions, end-of-row masking only in the one column group that needs it.
 // `wg` is the workgroup's number within its layer (a launch may hold the workgroups of several layers).
+// STAGED: a pass's activations by six loads of which adjacent lanes take adjacent pieces, and through LDS to the lanes that multiply them: a quarter
+// of the accesses to L1 for twelve accesses to LDS, which does the lookups.  The time no longer depends on the rows: see stages().
 // DIRECT: a pass's activations by eight loads straight into the operands, not by six and moves.  For few rows (see few_rows), and for a group
 // a workgroup with a 12-bit residual table, where a chunk has two blocks and a group a pass or two: six loads are 4 to 16 % slower there at any
 // number of rows (eight groups, 9536 x 4352, one row 24.2 against 26.3 us, sixteen 26.8 against 29.4; 16 groups, 11008 x 4096 41 against 48; but a
 // workgroup that walks four groups, 16 rows: 38.6 against 36.3).
-template <int RES_BITS, int MW, int NB, bool GROUPED, bool DIRECT = false, bool PART = false>
+template <int RES_BITS, int MW, int NB, bool GROUPED, int XM = SIX, bool PART = false>
 __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPlan &plan, const __half *__restrict__ x, long long ldx,
                                                   int batch, __half *__restrict__ y, long long ldy, int wg,
                                                   const GroupRange gr = GroupRange{0, 1, nullptr, nullptr}) {
   typedef Layout<RES_BITS> LY;
   constexpr int RB = RES_BITS ? RES_BITS : 8;
   constexpr int PA = NB == 2 ? 4 : 2;                   // passes whose index words are in flight or in registers
-  constexpr int XL = DIRECT ? 8 : 6;                    // loads of a pass's activations, which run one pass ahead
+  constexpr int XL = XM == DIRECT ? 8 : 6;                    // loads of a pass's activations, which run one pass ahead
   static_assert(PA % 2 == 0, "the unrolled pass loop must map passes to activation sets statically");
   constexpr int R = PA * NB;                            // ring of index-word slots: slot (j, b) = j * NB + b
   constexpr int S = RES_BITS ? 2 : 1;                   // loads per slot
@@ -93,7 +99,7 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
   const int n = lane & 15, g = lane >> 4;       // A: row n of the block, vector group g.  B: token n.  D: token n, rows 4g..4g+3
   const int row0 = wg * plan.rows_per_wg;
   const int rows_here = min(p.out_features - row0, plan.rows_per_wg);
-  const int n_blocks = (rows_here + 15) >> 4;
+  const int n_blocks = (rows_here + 15) >> 4, row_end = row0 + rows_here;
   const int n_chunks = (n_blocks + NB - 1) / NB;
   const unsigned a_out = lds_address(lds) + plan.lds_out;
 
@@ -111,11 +117,24 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
   // first row so that every activation load keeps a lane in range (rule 2 above; with 16 tokens the rows before the
   // last one do that).  What it feeds into the MFMA only reaches an output column that is never stored.
   const bool token_on = n < batch;
+  // STAGED: the sixteen-byte pieces that a lane loads, two runs of three (piece l = 64 k + lane: token l / 12, four lanes' 48 bytes, in order), and
+  // where in LDS they go.  Tokens past the batch are earlier ones once more, of two or more of which one is not the last: a lane in range.
+  unsigned xpiece[3], xto[3];
+  const unsigned stage = plan.lds_xs + MW * 64u + (unsigned)wv * STAGE_BYTES;
+  const unsigned xfrom = stage + (unsigned)n * STAGE_TOKEN + (unsigned)g * 48u;
+  if constexpr (XM == STAGED) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const unsigned l = (unsigned)(k * 64 + lane), t = l / 12u, of = l - t * 12u;
+      xpiece[k] = (unsigned)((long long)(t % (unsigned)batch) * ldx * 2) + of / 3u * 96u + of % 3u * 16u;
+      xto[k] = stage + t * STAGE_TOKEN + of * 16u;
+    }
+  }
   const unsigned xrow = token_on ? (unsigned)((long long)n * ldx * 2) : n == 15 ? 0u : 0x80000000u;
 
   uint3v win[R], wres[RES_BITS == 12 ? R : 1];   // index words, PA passes deep
   uint2v wres8[RES_BITS == 8 ? R : 1];
-  uint4v xq[DIRECT ? 1 : XL], bxs[DIRECT ? 2 : 1][VPL];    // activations of the next pass as loaded; B operands of the current one (and the next)
+  uint4v xq[XM == DIRECT ? 1 : XL], bxs[XM == DIRECT ? 2 : 1][VPL];    // activations of the next pass as loaded; B operands of the current one (and the next)
 #pragma unroll
   for (int i = 0; i < R; ++i) {
     win[i] = uint3v{0u, 0u, 0u};
@@ -123,9 +142,9 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
     if (RES_BITS == 8) wres8[i] = uint2v{0u, 0u};
   }
 #pragma unroll
-  for (int i = 0; i < (DIRECT ? 1 : XL); ++i) xq[i] = uint4v{0u, 0u, 0u, 0u};
+  for (int i = 0; i < (XM == DIRECT ? 1 : XL); ++i) xq[i] = uint4v{0u, 0u, 0u, 0u};
 #pragma unroll
-  for (int i = 0; i < (DIRECT ? 2 : 1); ++i)
+  for (int i = 0; i < (XM == DIRECT ? 2 : 1); ++i)
 #pragma unroll
     for (int u = 0; u < VPL; ++u) bxs[i][u] = uint4v{0u, 0u, 0u, 0u};
 
@@ -199,7 +218,13 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
   // a pass cost more than that at few rows: DIRECT.)
   auto issue_x = [&](int pass, uint4v (&to)[VPL]) {
     const unsigned off = token_on ? xrow + ((unsigned)col_lo + (unsigned)((pass * MW + wl) * 4 + g) * (VPL * 6u)) * 2u : xrow;
-    if constexpr (DIRECT) {      // (they overlap: the fourth dword belongs to the next vector)
+    if constexpr (XM == STAGED) {
+      const unsigned base = ((unsigned)col_lo + (unsigned)((pass * MW + wl) * 4) * (VPL * 6u)) * 2u;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) async_load_b128_at<0>(xq[k], r_xa, xpiece[k] + base);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) async_load_b128_at<48>(xq[XL - 3 + k], r_xa, xpiece[k] + base);
+    } else if constexpr (XM == DIRECT) {      // (they overlap: the fourth dword belongs to the next vector)
       async_load_b128_at<0>(to[0], r_xa, off);  async_load_b128_at<12>(to[1], r_xa, off);
       async_load_b128_at<24>(to[2], r_xa, off); async_load_b128_at<36>(to[3], r_xa, off);
       async_load_b128_at<48>(to[4], r_xa, off); async_load_b128_at<60>(to[5], r_xa, off);
@@ -306,14 +331,26 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
           // ---- one pass over this wave's 32 vectors of every block of the chunk
           // Every pass issues the same number of loads, also past the end of the sequence (the loader then starts
           // over), so the counted waits hold throughout.
-          uint4v (&bx)[VPL] = bxs[DIRECT ? j % 2 : 0];
+          uint4v (&bx)[VPL] = bxs[XM == DIRECT ? j % 2 : 0];
           wait_vmem_at_most<AFTER_X>();
-          if constexpr (DIRECT) {
+          if constexpr (XM == DIRECT) {
 #pragma unroll
             for (int u = 0; u < VPL; ++u) { settle(bx[u]); bx[u].w = 0u; }      // (the next vector's: infinite ones would meet the padding's zeros)
           } else {
 #pragma unroll
             for (int i = 0; i < XL; ++i) settle(xq[i]);
+            if constexpr (XM == STAGED) {
+              // (a wave's own accesses to LDS take effect in order: the second run is written where the first one has been read)
+#pragma unroll
+              for (int run = 0; run < 2; ++run) {
+#pragma unroll
+                for (int k = 0; k < 3; ++k) *reinterpret_cast<uint4v *>(lds + xto[k]) = xq[run * (XL - 3) + k];
+                asm volatile("" ::: "memory");
+#pragma unroll
+                for (int k = 0; k < 3; ++k) xq[run * (XL - 3) + k] = *reinterpret_cast<const uint4v *>(lds + xfrom + 16u * k);
+                asm volatile("" ::: "memory");
+              }
+            }
             const unsigned xd[XL * 4] = {xq[0].x, xq[0].y, xq[0].z, xq[0].w, xq[1].x, xq[1].y, xq[1].z, xq[1].w, xq[2].x, xq[2].y, xq[2].z, xq[2].w,
                                          xq[3].x, xq[3].y, xq[3].z, xq[3].w, xq[4].x, xq[4].y, xq[4].z, xq[4].w, xq[5].x, xq[5].y, xq[5].z, xq[5].w};
 #pragma unroll
@@ -338,7 +375,7 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
             for (int u = 0; u < VPL; ++u) xs = mfma16(ones, bx[u], xs);
             if (g == 0) xs_part[wv * 16 + n] += xs.x;
           }
-          issue_x((pass + 1) % my_passes, bxs[DIRECT ? (j + 1) % 2 : 0]);
+          issue_x((pass + 1) % my_passes, bxs[XM == DIRECT ? (j + 1) % 2 : 0]);
 #pragma unroll
           for (int b = 0; b < NB; ++b) {
             const int slot = j * NB + b;
@@ -385,15 +422,17 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
         if (pass == eff_passes - 1) {
           // ---- chunk end: partial sums to LDS; wave b adds up block b, applies scale and bias, stores
           if (plan.part_bufs == 0) lds_barrier();
-          unsigned char *pbase = lds + plan.lds_part + (unsigned)(buf * NB) * (MW * 1024u);
+          unsigned char *pbase = lds + plan.lds_part + (unsigned)(buf * NB) * (MW * 1024u) + lane * 16u;
+          const bool over = XM == STAGED && plan.part_bufs == 3;
+          const unsigned to_wave = over ? STAGE_BYTES : 1024u, to_block = over ? 1024u : MW * 1024u;
 #pragma unroll
           for (int b = 0; b < NB; ++b)
-            if (b < nb_c) *reinterpret_cast<float4v *>(pbase + (unsigned)(b * MW + wv) * 1024u + lane * 16u) = acc[b];
+            if (b < nb_c) *reinterpret_cast<float4v *>(pbase + (unsigned)b * to_block + (unsigned)wv * to_wave) = acc[b];
           lds_barrier();
           if (wv < nb_c) {
             float4v s = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-            for (int w = 0; w < MW; ++w) s += *reinterpret_cast<const float4v *>(pbase + (unsigned)(wv * MW + w) * 1024u + lane * 16u);
+            for (int w = 0; w < MW; ++w) s += *reinterpret_cast<const float4v *>(pbase + (unsigned)wv * to_block + (unsigned)w * to_wave);
             // sums of the groups so far: this lane of this wave is the only one that ever touches its slot
             float4v *ya = reinterpret_cast<float4v *>(lds + plan.lds_yacc + (unsigned)((c * NB + wv) * 64 + lane) * 16u);
             if (GROUPED && grp > gr.begin) s += *ya;
@@ -406,12 +445,12 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
             } else if (partial) {
               if (n < batch) {
                 float *dst = gr.part + (long long)n * p.out_features + ep_o;
-                if (ep_o + 3 < p.out_features && (p.out_features & 3) == 0) {
+                if (ep_o + 3 < row_end && (p.out_features & 3) == 0) {
                   *reinterpret_cast<float4v *>(dst) = s;
                 } else {
 #pragma unroll
                   for (int r = 0; r < 4; ++r)
-                    if (ep_o + r < p.out_features) dst[r] = sv[r];
+                    if (ep_o + r < row_end) dst[r] = sv[r];
                 }
                 if (wg == 0 && c == 0 && wv == 0 && g == 0) gr.part_xs[grp * 16 + n] = xsum;
               }
@@ -427,7 +466,7 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
             }
             if (n < batch) {
               __half *dst = y + (long long)n * ldy + ep_o;
-              if (plan.y_wide && ep_o + 3 < p.out_features) {
+              if (plan.y_wide && ep_o + 3 < row_end) {
                 uint2v pk;
                 pk.x = (unsigned)__half_as_ushort(out[0]) | ((unsigned)__half_as_ushort(out[1]) << 16);
                 pk.y = (unsigned)__half_as_ushort(out[2]) | ((unsigned)__half_as_ushort(out[3]) << 16);
@@ -435,12 +474,12 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
               } else {
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                  if (ep_o + r < p.out_features) dst[r] = out[r];
+                  if (ep_o + r < row_end) dst[r] = out[r];
               }
             }
             }
           }
-          if (plan.part_bufs == 1) lds_barrier(); else if (plan.part_bufs == 2) buf ^= 1;
+          if (plan.part_bufs & 1) lds_barrier(); else if (plan.part_bufs == 2) buf ^= 1;
           pass = 0; ++c;
         } else {
           ++pass;
@@ -454,11 +493,11 @@ __device__ __forceinline__ void gemv_v6_mfma_body(const Params &p, const MfmaPla
   }
 }
 
-template <int RES_BITS, int MW, int NB, bool GROUPED, bool DIRECT>
+template <int RES_BITS, int MW, int NB, bool GROUPED, int XM>
 __global__ __launch_bounds__(MW * 64) void gemv_v6_mfma_kernel(Params p, MfmaPlan plan, const __half *__restrict__ x, long long ldx,
                                                                 int batch, __half *__restrict__ y, long long ldy) {
   warm_kernel_arguments();
-  gemv_v6_mfma_body<RES_BITS, MW, NB, GROUPED, DIRECT>(p, plan, x, ldx, batch, y, ldy, (int)blockIdx.x, GroupRange{0, p.n_groups, nullptr, nullptr});
+  gemv_v6_mfma_body<RES_BITS, MW, NB, GROUPED, XM>(p, plan, x, ldx, batch, y, ldy, (int)blockIdx.x, GroupRange{0, p.n_groups, nullptr, nullptr});
 }
 
 // A layer with codebook groups when the caller lends a workspace: every workgroup takes one group (its tables go into
@@ -471,17 +510,17 @@ __global__ __launch_bounds__(MW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
                                                                        int wgs_per_group) {
   warm_kernel_arguments();
   const int grp = (int)blockIdx.x / wgs_per_group, wg = (int)blockIdx.x - grp * wgs_per_group;
-  gemv_v6_mfma_body<RES_BITS, MW, NB, true, RES_BITS == 12>(p, plan, x, ldx, batch, nullptr, 0, wg,
+  gemv_v6_mfma_body<RES_BITS, MW, NB, true, RES_BITS == 12 ? DIRECT : SIX>(p, plan, x, ldx, batch, nullptr, 0, wg,
                                                   GroupRange{grp, grp + 1, part + (long long)grp * batch * p.out_features, part_xs});
 }
 
 // A layer of one table and few blocks of rows, the caller's workspace lent: every workgroup takes a part of the columns and so many more blocks.
-template <int RES_BITS, int NB>
+template <int RES_BITS, int NB, int XM>
 __global__ __launch_bounds__(MW * 64) void gemv_v6_mfma_parts_kernel(Params p, MfmaPlan plan, const __half *__restrict__ x, long long ldx, int batch,
                                                                      float *__restrict__ part, float *__restrict__ part_xs, int wgs_per_part) {
   warm_kernel_arguments();
   const int i = (int)blockIdx.x / wgs_per_part, wg = (int)blockIdx.x - i * wgs_per_part;
-  gemv_v6_mfma_body<RES_BITS, MW, NB, false, false, true>(p, plan, x, ldx, batch, nullptr, 0, wg, GroupRange{i, i + 1, part + (long long)i * batch * p.out_features, part_xs});
+  gemv_v6_mfma_body<RES_BITS, MW, NB, false, XM, true>(p, plan, x, ldx, batch, nullptr, 0, wg, GroupRange{i, i + 1, part + (long long)i * batch * p.out_features, part_xs});
 }
 
 // y[t][o] = fp16(scale[o] * sum_g part[g][t][o] + bias[o] * sum_g part_xs[g][t]), groups in ascending order.
@@ -540,20 +579,20 @@ struct MultiArgs {
   MultiLayer layer[MULTI_MAX];
 };
 
-template <int RES_BITS, int MW, int NB, bool DIRECT>
+template <int RES_BITS, int MW, int NB, int XM>
 __global__ __launch_bounds__(MW * 64) void gemv_v6_mfma_multi_kernel(MultiArgs a, const __half *__restrict__ x, long long ldx, int batch) {
   warm_kernel_arguments();
   int i = 0;
   while (i + 1 < a.n && (int)blockIdx.x >= a.first_wg[i + 1]) ++i;
   const MultiLayer &l = a.layer[i];
-  gemv_v6_mfma_body<RES_BITS, MW, NB, false, DIRECT>(l.p, l.plan, x, ldx, batch, l.y, l.ldy, (int)blockIdx.x - a.first_wg[i]);
+  gemv_v6_mfma_body<RES_BITS, MW, NB, false, XM>(l.p, l.plan, x, ldx, batch, l.y, l.ldy, (int)blockIdx.x - a.first_wg[i]);
 }
 
 
-template <int RES_BITS, int MW, int NB, bool GROUPED, bool DIRECT = false>
+template <int RES_BITS, int MW, int NB, bool GROUPED, int XM = SIX>
 int launch_one(const Params &p, const MfmaPlan &plan, unsigned lds_bytes, unsigned grid, const __half *x, long long ldx, int batch,
                __half *y, long long ldy, hipStream_t s) {
-  auto kernel = gemv_v6_mfma_kernel<RES_BITS, MW, NB, GROUPED, DIRECT>;
+  auto kernel = gemv_v6_mfma_kernel<RES_BITS, MW, NB, GROUPED, XM>;
   VQ_ALLOW_FULL_LDS(kernel);
   hipLaunchKernelGGL(kernel, dim3(grid), dim3(MW * 64), lds_bytes, s, p, plan, x, ldx, batch, y, ldy);
   return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
@@ -573,12 +612,19 @@ struct Planned {
   bool grouped;
 };
 
-// Work split and LDS layout of one layer when every workgroup takes `blocks_per_wg` 16-row blocks.  nb_force > 0
+// Rows of a workgroup where `wgs` of them share `rows`: every one as many as the others, to a multiple of four (whole 8-byte stores), and a block at
+// least.  In whole blocks of sixteen as well, workgroups have one block more or less than others, and compute units stay idle for it; rows
+// that a block does not have are lookups of entry 0 that meet no conflicts.  4096 columns, two 4096-entry tables, three / sixteen rows: 4500 outputs
+// 11.5 -> 10.5 us, 12.4 -> 11.7; 5120 11.6 -> 10.7, 12.5 -> 11.9; 14336 17.0 -> 16.4, 18.0 -> 17.5; of one table level.  With fewer rows than a
+// block (3000 and fewer outputs, one table) 3 % slower.
+int rows_each(int rows, int wgs) { return max(16, ((rows + wgs - 1) / wgs + 3) / 4 * 4); }
+
+// Work split and LDS layout of one layer when every workgroup takes `rows_per_wg` rows (a multiple of 4).  nb_force > 0
 // fixes the blocks per chunk (several layers in one launch share one kernel instantiation).
 // `waves` and `lds_cap`: the workgroup's size and its share of the compute unit's LDS (the defaults: one workgroup of
 // MW waves per compute unit).
-int make_plan(const Params &p, int batch, long long ldx, const __half *y, long long ldy, int blocks_per_wg, int nb_force, Planned *out,
-              bool partial = false, int waves = MW, unsigned lds_cap = 160u * 1024u, bool column_parts = false) {
+int make_plan(const Params &p, int batch, long long ldx, const __half *y, long long ldy, int rows_per_wg, int nb_force, Planned *out,
+              bool partial = false, int waves = MW, unsigned lds_cap = 160u * 1024u, bool column_parts = false, bool staged = false) {
   MfmaPlan plan{};
   if (p.in_features < 64) return VQ_ERR_UNSUPPORTED;      // idle lanes load the first 100 bytes of the first activation row
   const int rb = p.k_res ? p.bits_res : 0;
@@ -586,17 +632,19 @@ int make_plan(const Params &p, int batch, long long ldx, const __half *y, long l
   // the 32 KB outlier table goes into LDS too, unless two 64 KB tables are already there
   plan.out_global = p.Q && rb == 12 ? 1 : 0;
   plan.lds_out = off; off += p.Q && !plan.out_global ? 4096u * 8u : 0u;
-  plan.lds_xs = off; off += (unsigned)waves * 16u * 4u;
-  const int blocks_total = (p.out_features + 15) / 16;
-  plan.rows_per_wg = blocks_per_wg * 16;
-  out->grid = (unsigned)((blocks_total + blocks_per_wg - 1) / blocks_per_wg);
-  plan.lds_sb = off; off += partial ? 0u : (unsigned)plan.rows_per_wg * 4u;
+  plan.lds_xs = off; off += (unsigned)waves * (16u * 4u + (staged ? STAGE_BYTES : 0u));
+  const int blocks_per_wg = (rows_per_wg + 15) / 16;
+  plan.rows_per_wg = rows_per_wg;
+  out->grid = (unsigned)((p.out_features + rows_per_wg - 1) / rows_per_wg);
+  plan.lds_sb = off; off += partial ? 0u : (unsigned)blocks_per_wg * 64u;
   const bool grouped = p.n_groups > 1 && !column_parts;
   if (grouped && (p.Pg & 7)) return VQ_ERR_UNSUPPORTED;   // a group must start on a dword of the 12- and 8-bit streams
   plan.lds_yacc = off; off += grouped && !partial ? (unsigned)blocks_per_wg * 1024u : 0u;
   plan.lds_part = off;
-  if (off + (unsigned)waves * 1024u > lds_cap) return VQ_ERR_UNSUPPORTED;
-  const int fit = (int)((lds_cap - off) / ((unsigned)waves * 1024u));    // 16-row partial blocks that fit
+  // (STAGED: a wave's partials of up to three blocks lie where its activations pass through)
+  constexpr int over_stage = (int)(STAGE_BYTES / 1024u);
+  if (off + (staged ? 0u : (unsigned)waves * 1024u) > lds_cap) return VQ_ERR_UNSUPPORTED;
+  const int fit = max((int)((lds_cap - off) / ((unsigned)waves * 1024u)), staged ? over_stage : 0);    // 16-row partial blocks that fit
   // Blocks per chunk: as many as the kernel's 256 registers allow.  More would spill, which these kernels must not (see the build
   // script).  (with codebook groups fewer: the group loop costs registers of its own)  Every chunk loads the activations again: a
   // workgroup's blocks go in one chunk where they can, then in even ones.  But with a residual table, whose lookups take longer than
@@ -613,11 +661,16 @@ int make_plan(const Params &p, int batch, long long ldx, const __half *y, long l
     const int chunks = (blocks_per_wg + plan.nb - 1) / plan.nb;
     plan.nb = (blocks_per_wg + chunks - 1) / chunks;
     if (nb_force > 0) { if (nb_force > min(min(nb_regs, blocks_per_wg), fit)) return VQ_ERR_UNSUPPORTED; plan.nb = nb_force; }
+    if (staged && plan.nb <= over_stage) {
+      plan.part_bufs = 3;
+      plan.lds_part = plan.lds_xs + (unsigned)waves * 64u;
+    } else {
     plan.part_bufs = (fit >= 2 * plan.nb && blocks_per_wg > plan.nb) ? 2 : 1;
     off += (unsigned)(plan.part_bufs * plan.nb) * ((unsigned)waves * 1024u);
+    }
   }
   const long long max_stride = max(p.stride, max(p.stride_res, p.stride_out));
-  if ((long long)(plan.rows_per_wg + 16 * NBMAX * 8) * max_stride >= (1LL << 31)) return VQ_ERR_UNSUPPORTED;   // 32-bit buffer offsets
+  if ((long long)(plan.rows_per_wg + 16 * (NBMAX + 1) * 8) * max_stride >= (1LL << 31)) return VQ_ERR_UNSUPPORTED;   // 32-bit buffer offsets
   const long long x_bytes = ((long long)(batch - 1) * ldx + p.in_features) * 2;
   if (ldx < 0 || x_bytes >= (1LL << 31) - (1 << 20)) return VQ_ERR_UNSUPPORTED;
   plan.x_bytes = (unsigned)x_bytes;
@@ -636,9 +689,9 @@ bool narrow_groups(const Params &p) {
   return p.n_groups > 1 && (p.Pg + 31) / 32 <= NARROW_WAVES && !(p.k_res && p.bits_res == 12) && p.Q == 0;
 }
 
-template <int RES_BITS, int NB, bool DIRECT = false>
+template <int RES_BITS, int NB, int XM = SIX>
 int launch_multi(const MultiArgs &a, unsigned lds_bytes, unsigned grid, const __half *x, long long ldx, int batch, hipStream_t s) {
-  auto kernel = gemv_v6_mfma_multi_kernel<RES_BITS, MW, NB, DIRECT>;
+  auto kernel = gemv_v6_mfma_multi_kernel<RES_BITS, MW, NB, XM>;
   VQ_ALLOW_FULL_LDS(kernel);
   hipLaunchKernelGGL(kernel, dim3(grid), dim3(MW * 64), lds_bytes, s, a, x, ldx, batch);
   return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
@@ -651,23 +704,40 @@ int launch_multi(const MultiArgs &a, unsigned lds_bytes, unsigned grid, const __
 // than 2 % (140 sets of layers; against the line, 5120 x 13824, three rows 15.8 -> 15.2).
 bool few_rows(const Params &p, int batch, int nb) { return nb >= 2 && p.in_features >= 8000 && batch <= (nb >= 3 ? 5 : 3); }
 
+// Whether the activations pass through LDS (STAGED): from as many rows on that the accesses of the six loads take longer than eleven clocks for each of
+// twelve LDS accesses, which the more blocks share.  Six loads / staged, in us, 4096 columns, one table: one block 12 rows 7.03 / 6.92, 16 rows 7.89 / 6.92;
+// two 12 rows 8.66 / 8.60, 16 rows 9.42 / 8.69; three 13 rows 9.49 / 9.61, 14 9.71 / 9.63, 16 10.15 / 9.71.  With residual lookups as many accesses
+// again are left to LDS: one block 14 rows 9.49 / 9.46 (1000 outputs 8.89 / 9.08), 16 9.96 / 9.50, of 11008 columns 12 rows 15.25 / 15.12, 16 17.12 /
+// 15.10; two 16 rows 13.40 / 13.70; from a 256-entry table, one block 14 rows 8.78 / 8.28.
+bool stages(const Params &p, int batch, int nb) {
+  if (!p.k_res) return nb <= 5 && batch >= 11 + nb;
+  return nb == 1 && batch >= (p.bits_res == 8 ? 13 : p.P >= 1500 ? 12 : 15);
+}
+
 }  // namespace
 
 // Launch for batch 1..16.  The caller has checked gemv_fast_applicable().
 int launch_gemv_mfma(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, hipStream_t s) {
-  const int blocks_total = (p.out_features + 15) / 16;
-  const int cus = cu_count();
   Planned pl;
-  const int rc = make_plan(p, batch, ldx, y, ldy, (blocks_total + cus - 1) / cus, 0, &pl);
+  const int rows = rows_each(p.out_features, cu_count());
+  const int rc = make_plan(p, batch, ldx, y, ldy, rows, 0, &pl);
   if (rc != VQ_OK) return rc;
+  bool staged = false;
+  if (!pl.grouped && stages(p, batch, pl.plan.nb)) {
+    Planned with;
+    staged = make_plan(p, batch, ldx, y, ldy, rows, 0, &with, false, MW, 160u * 1024u, false, true) == VQ_OK && with.plan.nb == pl.plan.nb;
+    if (staged) pl = with;
+  }
   const MfmaPlan &plan = pl.plan;
   const int rb = pl.rb;
   const bool grouped = pl.grouped;
   const unsigned off = pl.lds_bytes, grid = pl.grid;
-#define VQ_CASE(NBLK) if (plan.nb == NBLK) return launch_one<0, MW, NBLK, false, true>(p, plan, off, grid, x, ldx, batch, y, ldy, s);
-  if (rb == 0 && !grouped && few_rows(p, batch, plan.nb)) { VQ_CASE(2) VQ_CASE(3) VQ_CASE(4) }
+#define VQ_CASE(NBLK) if (plan.nb == NBLK) return launch_one<0, MW, NBLK, false, DIRECT>(p, plan, off, grid, x, ldx, batch, y, ldy, s);
+  if (rb == 0 && !grouped && !staged && few_rows(p, batch, plan.nb)) { VQ_CASE(2) VQ_CASE(3) VQ_CASE(4) }
 #undef VQ_CASE
 #define VQ_CASE(RBITS, NBLK) \
+  if (rb == RBITS && plan.nb == NBLK && staged)                                                                                           \
+    return launch_one<RBITS, MW, STAGED_NB(RBITS, NBLK), false, STAGED>(p, plan, off, grid, x, ldx, batch, y, ldy, s);                     \
   if (rb == RBITS && plan.nb == NBLK && !grouped) return launch_one<RBITS, MW, NBLK, false>(p, plan, off, grid, x, ldx, batch, y, ldy, s); \
   if (rb == RBITS && plan.nb == NBLK && grouped && NBLK <= (RBITS == 12 ? 2 : 3)) \
     return launch_one<RBITS, MW, (NBLK <= (RBITS == 12 ? 2 : 3) ? NBLK : 1), true>(p, plan, off, grid, x, ldx, batch, y, ldy, s);
@@ -708,19 +778,26 @@ size_t gemv_mfma_groups_workspace_bytes(const Params &p, int batch) {
 
 // One table, parts of the columns: a workgroup takes a part of them and so many more blocks of rows.
 static int launch_column_parts(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, void *workspace, hipStream_t s) {
-  const int parts = column_parts(p, batch), blocks_total = (p.out_features + 15) / 16, wgs_per_part = cu_count() / parts;
+  const int parts = column_parts(p, batch), wgs_per_part = cu_count() / parts;
   if (parts < 2 || wgs_per_part < 1) return VQ_ERR_UNSUPPORTED;
   Params q = p;
   q.Pg = part_vectors(p, parts);
   q.n_groups = (p.P + q.Pg - 1) / q.Pg;
   Planned pl;
-  const int rc = make_plan(q, batch, ldx, y, ldy, (blocks_total + wgs_per_part - 1) / wgs_per_part, 0, &pl, true, MW, 160u * 1024u, true);
+  const int rows = rows_each(p.out_features, wgs_per_part);
+  const int rc = make_plan(q, batch, ldx, y, ldy, rows, 0, &pl, true, MW, 160u * 1024u, true);
   if (rc != VQ_OK) return rc;
+  bool staged = false;
+  if (stages(q, batch, pl.plan.nb)) {
+    Planned with;
+    staged = make_plan(q, batch, ldx, y, ldy, rows, 0, &with, true, MW, 160u * 1024u, true, true) == VQ_OK && with.plan.nb == pl.plan.nb;
+    if (staged) pl = with;
+  }
   float *part = static_cast<float *>(workspace), *part_xs = part + (size_t)q.n_groups * (size_t)batch * (size_t)p.out_features;
 #define VQ_CASE(RBITS, NBLK)                                                                                                              \
   if (pl.rb == RBITS && pl.plan.nb == NBLK) {                                                                                             \
-    auto kernel = gemv_v6_mfma_parts_kernel<RBITS, NBLK>;                                                                                 \
-    VQ_ALLOW_FULL_LDS(kernel);                                                                                                            \
+    const auto kernel = staged ? gemv_v6_mfma_parts_kernel<RBITS, STAGED_NB(RBITS, NBLK), STAGED> : gemv_v6_mfma_parts_kernel<RBITS, NBLK, SIX>;            \
+    if (staged) { VQ_ALLOW_FULL_LDS((gemv_v6_mfma_parts_kernel<RBITS, STAGED_NB(RBITS, NBLK), STAGED>)); } else { VQ_ALLOW_FULL_LDS((gemv_v6_mfma_parts_kernel<RBITS, NBLK, SIX>)); } \
     hipLaunchKernelGGL(kernel, dim3(pl.grid * (unsigned)q.n_groups), dim3(MW * 64), pl.lds_bytes, s, q, pl.plan, x, ldx, batch, part, part_xs, (int)pl.grid); \
     launch_finish(part, part_xs, q.n_groups, batch, p, y, ldy, s);                                                                        \
     return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;                                                                          \
@@ -736,19 +813,18 @@ static int launch_column_parts(const Params &p, const __half *x, long long ldx, 
 int launch_gemv_mfma_groups(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, void *workspace,
                             hipStream_t s) {
   if (p.n_groups == 1) return launch_column_parts(p, x, ldx, batch, y, ldy, workspace, s);
-  const int blocks_total = (p.out_features + 15) / 16;
   bool narrow = narrow_groups(p) && 2 * cu_count() / p.n_groups >= 1;
   Planned pl;
   int rc = VQ_ERR_UNSUPPORTED;
   if (narrow) {
     const int wgs_per_group = 2 * cu_count() / p.n_groups;
-    rc = make_plan(p, batch, ldx, y, ldy, (blocks_total + wgs_per_group - 1) / wgs_per_group, 0, &pl, true, NARROW_WAVES, 80u * 1024u);
+    rc = make_plan(p, batch, ldx, y, ldy, rows_each(p.out_features, wgs_per_group), 0, &pl, true, NARROW_WAVES, 80u * 1024u);
     if (rc != VQ_OK) narrow = false;
   }
   if (!narrow) {
     const int wgs_per_group = cu_count() / p.n_groups;
     if (wgs_per_group < 1) return VQ_ERR_UNSUPPORTED;
-    rc = make_plan(p, batch, ldx, y, ldy, (blocks_total + wgs_per_group - 1) / wgs_per_group, 0, &pl, true);
+    rc = make_plan(p, batch, ldx, y, ldy, rows_each(p.out_features, wgs_per_group), 0, &pl, true);
     if (rc != VQ_OK) return rc;
   }
   float *part = static_cast<float *>(workspace);
@@ -789,29 +865,39 @@ int launch_gemv_mfma_multi(const Params *ps, int n, const __half *x, long long l
                            const long long *ldys, hipStream_t s) {
   if (n < 2 || n > MULTI_MAX) return VQ_ERR_UNSUPPORTED;
   const int cus = cu_count();
-  long long blocks_all = 0;
+  long long rows_all = 0;
   for (int i = 0; i < n; ++i) {
     if (ps[i].in_features != ps[0].in_features || ps[i].n_groups > 1) return VQ_ERR_UNSUPPORTED;
     if ((ps[i].k_res ? ps[i].bits_res : 0) != (ps[0].k_res ? ps[0].bits_res : 0)) return VQ_ERR_UNSUPPORTED;
-    blocks_all += (ps[i].out_features + 15) / 16;
+    rows_all += ps[i].out_features;
   }
-  // every workgroup takes the same number of 16-row blocks of one layer: the smallest number with which all the
-  // workgroups run at once, one per compute unit
-  int b = (int)((blocks_all + cus - 1) / cus);
-  for (;; ++b) {
+  // every workgroup takes the same number of rows of one layer: the smallest number with which all the workgroups run at once, one per compute
+  // unit
+  int rows = rows_each((int)min(rows_all, 0x7FFFFF00LL), cus);
+  for (;; rows += 4) {
     long long wgs = 0;
-    for (int i = 0; i < n; ++i) wgs += ((ps[i].out_features + 15) / 16 + b - 1) / b;
+    for (int i = 0; i < n; ++i) wgs += (ps[i].out_features + rows - 1) / rows;
     if (wgs <= cus) break;
   }
   MultiArgs a{};
   Planned pl[MULTI_MAX];
   int nb = NBMAX;
-  for (int pass = 0; pass < 2; ++pass) {                  // first the blocks per chunk every layer admits, then the plans with it
-    for (int i = 0; i < n; ++i) {
-      const int rc = make_plan(ps[i], batch, ldx, ys[i], ldys[i], b, pass ? nb : 0, &pl[i]);
-      if (rc != VQ_OK) return rc;
-      if (!pass) nb = min(nb, pl[i].plan.nb);
-    }
+  auto plan_all = [&](bool staged) -> int {
+    nb = NBMAX;
+    for (int pass = 0; pass < 2; ++pass)                  // first the blocks per chunk every layer admits, then the plans with it
+      for (int i = 0; i < n; ++i) {
+        const int rc = make_plan(ps[i], batch, ldx, ys[i], ldys[i], rows, pass ? nb : 0, &pl[i], false, MW, 160u * 1024u, false, staged);
+        if (rc != VQ_OK) return rc;
+        if (!pass) nb = min(nb, pl[i].plan.nb);
+      }
+    return VQ_OK;
+  };
+  const int rc = plan_all(false);
+  if (rc != VQ_OK) return rc;
+  bool staged = false;
+  if (const int without = nb; stages(ps[0], batch, nb)) {
+    staged = plan_all(true) == VQ_OK && nb == without;
+    if (!staged) plan_all(false);
   }
   unsigned lds_bytes = 0;
   a.n = n;
@@ -822,10 +908,11 @@ int launch_gemv_mfma_multi(const Params *ps, int n, const __half *x, long long l
   }
   const unsigned grid = (unsigned)a.first_wg[n];
   const int rb = pl[0].rb;
-#define VQ_CASE(NBLK) if (nb == NBLK) return launch_multi<0, NBLK, true>(a, lds_bytes, grid, x, ldx, batch, s);
-  if (rb == 0 && few_rows(ps[0], batch, nb)) { VQ_CASE(2) VQ_CASE(3) VQ_CASE(4) }
+#define VQ_CASE(NBLK) if (nb == NBLK) return launch_multi<0, NBLK, DIRECT>(a, lds_bytes, grid, x, ldx, batch, s);
+  if (rb == 0 && !staged && few_rows(ps[0], batch, nb)) { VQ_CASE(2) VQ_CASE(3) VQ_CASE(4) }
 #undef VQ_CASE
-#define VQ_CASE(RBITS, NBLK) if (rb == RBITS && nb == NBLK) return launch_multi<RBITS, NBLK>(a, lds_bytes, grid, x, ldx, batch, s);
+#define VQ_CASE(RBITS, NBLK)                                                                                                   \
+  if (rb == RBITS && nb == NBLK) return staged ? launch_multi<RBITS, STAGED_NB(RBITS, NBLK), STAGED>(a, lds_bytes, grid, x, ldx, batch, s) : launch_multi<RBITS, NBLK>(a, lds_bytes, grid, x, ldx, batch, s);
   VQ_CASE(0, 1) VQ_CASE(0, 2) VQ_CASE(0, 3) VQ_CASE(0, 4) VQ_CASE(0, 5) VQ_CASE(0, 6)
   VQ_CASE(8, 1) VQ_CASE(8, 2) VQ_CASE(8, 3) VQ_CASE(8, 4) VQ_CASE(8, 5)
   VQ_CASE(12, 1) VQ_CASE(12, 2) VQ_CASE(12, 3) VQ_CASE(12, 4) VQ_CASE(12, 5)

@@ -1222,3 +1222,33 @@ def test_gemv_v8_last_vector_of_any_length(gpu_lib, last, batch):
     y = gpu_lib.gemv(gpu_lib.DeviceLayer(L), rows).float()
     torch.cuda.synchronize()
     assert torch.isinf(y[batch - 1]).all() and torch.isfinite(y[: batch - 1]).all()
+
+
+@pytest.mark.parametrize("out_features,in_features,batch,more", [
+    (37, 70, 12, {}), (37, 1190, 16, {}), (4101, 203 * 2, 13, {}), (4101, 3074, 16, {}), (10242, 390, 14, {}), (15003, 70, 15, {}), (20000, 202, 16, {}),
+    (37, 390, 15, dict(k_res=4096)), (1001, 1540, 13, dict(k_res=256)), (40, 9010, 12, dict(k_res=4096)),
+    (61, 1030, 16, dict(k_res=256, n_outlier_cols=24, v_out=4, k_out=4096)),
+    (4101, 390, 3, dict(k_res=4096)), (9999, 202, 5, dict(k_res=256)), (8197, 66, 3, {}),
+])
+def test_gemv_activations_through_lds_and_short_blocks(gpu_lib, out_features, in_features, batch, more):
+    """Rows of v = 6 vectors on the matrix cores: one to five blocks of rows a workgroup, the last of them short, activations through LDS from the rows on
+    that each number of blocks takes, one and several passes of the waves, the last of them of part of a wave; rows of y that several
+    workgroups share none of, by 8-byte stores and by single ones."""
+    import torch
+    L = s.make_layer(317, "short", out_features, in_features, 6, 4096, **more)
+    dl = gpu_lib.DeviceLayer(L)
+    x_np = s.make_activations(317, L, batch)
+    ref = oracle.gemv(L, x_np)
+    x = torch.from_numpy(x_np).cuda()
+    for pad in (0, 3):
+        y = torch.full((batch, out_features + pad), 7.0, dtype=torch.float16, device="cuda")
+        gpu_lib.gemv(dl, x, out=y)
+        torch.cuda.synchronize()
+        _check_matmul(y[:, :out_features], ref, "pad %d" % pad)
+        assert (y[:, out_features:] == 7.0).all()
+    if "n_outlier_cols" not in more:
+        second = s.make_layer(318, "second", 333, in_features, 6, 4096, **more)
+        ya, yb = gpu_lib.gemv_multi([dl, gpu_lib.DeviceLayer(second)], x)
+        torch.cuda.synchronize()
+        _check_matmul(ya, ref, "first of two")
+        _check_matmul(yb, oracle.gemv(second, x_np), "second of two")
