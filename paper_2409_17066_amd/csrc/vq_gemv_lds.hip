@@ -133,10 +133,39 @@ __global__ __launch_bounds__(LW * 64) void gemv_lds_kernel(Params p, LdsPlan pla
 // 32 bytes, so that an entry is one aligned read (two for V = 12).
 constexpr bool two_pass_compiled(int v, int bits) { return v >= 8 && bits == 12; }   // where two padded tables can exceed LDS
 
+// What the kernel cannot derive.  A launch with up to 112 bytes of arguments takes the host 2.9 us, one with more 3.5 to 3.8 (calls one after the
+// other, arguments in device memory as the runtime has them by default), and the smallest calls are nothing but that: 256 x 384, v = 6,
+// k = 256, one row, with 232 bytes of arguments 3.9 us a call of vq_gemv and 4.8 of gemv(), with 104 2.9 and 4.55.
+struct WindowArgs {
+  const __half *cb, *cb_res;
+  const uint8_t *idx, *idx_res;
+  const __half *scale, *bias;
+  const int *perm;
+  const __half *x;
+  __half *y;
+  int out_features, in_features, ldx, ldy;
+  unsigned stride, stride_res;
+  unsigned short k, k_res;
+  int rows_per_wg;
+};
+static_assert(sizeof(WindowArgs) <= 112, "arguments of a quick launch");
+
+// Bytes in LDS: tables, activations (a row's pitch: whole windows), their sums, and with MODE 2 the first pass's sums of the rows.
+struct WindowLds { unsigned off_res, off_x, x_pitch, off_xsum, off_ypart; };
+__host__ __device__ constexpr WindowLds window_lds(int v, int bits, int mode, int batch, int k, int k_res, int in_features) {
+  const unsigned entry = (unsigned)entry_halfs(v) * 2u, main = ((unsigned)k * entry + 15u) / 16u * 16u, res = ((unsigned)k_res * entry + 15u) / 16u * 16u;
+  const unsigned columns = (unsigned)win_vectors(bits) * (unsigned)v, pitch = (((unsigned)in_features + columns - 1u) / columns * columns * 2u + 15u) / 16u * 16u;
+  const unsigned tables = mode == 2 ? (main > res ? main : res) : main + res, xsum = tables + pitch * (unsigned)batch;
+  return {main, tables, pitch, xsum, xsum + (4u * 4u * (1u + LW) + 15u) / 16u * 16u};
+}
+
 template <int V, int BITS, int MODE, int B>      // MODE 0: no residual; 1: both tables in LDS; 2: one table at a time, two passes over the rows
-__global__ __launch_bounds__(LW * 64) void gemv_lds_window_kernel(Params p, LdsPlan plan, const __half *__restrict__ x, long long ldx,
-                                                                  __half *__restrict__ y, long long ldy) {
+__global__ __launch_bounds__(LW * 64) void gemv_lds_window_kernel(WindowArgs p) {
   constexpr int U = win_vectors(BITS), ND = U * BITS / 32, EH = entry_halfs(V), ED = EH / 2, VD = V / 2;
+  const WindowLds plan = window_lds(V, BITS, MODE, B, p.k, MODE ? p.k_res : 0, p.in_features);
+  const __half *__restrict__ x = p.x;
+  __half *__restrict__ y = p.y;
+  const long long ldx = p.ldx, ldy = p.ldy;
   constexpr bool BOTH = MODE == 1;
   constexpr int PASSES = MODE == 2 ? 2 : 1;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
@@ -145,9 +174,9 @@ __global__ __launch_bounds__(LW * 64) void gemv_lds_window_kernel(Params p, LdsP
   float *ypart = reinterpret_cast<float *>(lds + plan.off_ypart);        // MODE 2: the first pass's row sums [rows_per_wg][B]
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 
-  const int row0 = blockIdx.x * plan.rows_per_wg;
-  const int row1 = min(p.out_features, row0 + plan.rows_per_wg);
-  const int windows = (p.P + U - 1) / U;
+  const int row0 = blockIdx.x * p.rows_per_wg;
+  const int row1 = min(p.out_features, row0 + p.rows_per_wg);
+  const int windows = (p.in_features + U * V - 1) / (U * V);
   const __amdgpu_buffer_rsrc_t r_i = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(p.idx), 0, (unsigned)((long long)p.out_features * p.stride), 0x00020000);
   const __amdgpu_buffer_rsrc_t r_r = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(MODE ? p.idx_res : p.idx), 0,
                                                                        MODE ? (unsigned)((long long)p.out_features * p.stride_res) : 0u, 0x00020000);
@@ -279,34 +308,25 @@ __global__ __launch_bounds__(LW * 64) void gemv_lds_window_kernel(Params p, LdsP
   }
 }
 
-// (two_pass: the residual table takes the main table's place for a second pass over the rows, whose first-pass sums wait in LDS)
-bool make_window_plan(const Params &p, int batch, int u, int eh, bool two_pass, LdsPlan *plan) {
-  auto up16 = [](size_t v) { return (v + 15) / 16 * 16; };
-  const size_t main = up16((size_t)p.k * eh * 2), res = up16((size_t)p.k_res * eh * 2);
-  const size_t tables = two_pass ? (main > res ? main : res) : main + res;
-  const size_t windows = ((size_t)p.P + u - 1) / u;
-  const size_t pitch = up16(windows * u * p.v * 2);
-  const int wgs = cu_count();
-  plan->rows_per_wg = (p.out_features + wgs - 1) / wgs;
-  if (plan->rows_per_wg < LW) plan->rows_per_wg = LW;
-  const size_t sums = up16(4 * 4 * (1 + LW));
-  const size_t total = tables + pitch * batch + sums + (two_pass ? (size_t)plan->rows_per_wg * batch * 4 : 0);
-  if (total > 160 * 1024) return false;
-  if ((long long)p.out_features * p.stride >= (1LL << 32) || (long long)p.out_features * p.stride_res >= (1LL << 32)) return false;
-  plan->off_res = (unsigned)main; plan->off_out = (unsigned)tables; plan->off_x = (unsigned)tables;
-  plan->off_xsum = (unsigned)(tables + pitch * batch); plan->off_ypart = (unsigned)(tables + pitch * batch + sums);
-  plan->bytes = (unsigned)total; plan->x_pitch = (unsigned)pitch;
-  return true;
+// rows of a workgroup; its LDS, 0 where it or the streams are too large
+int window_rows(const Params &p) { return max(LW, (p.out_features + cu_count() - 1) / cu_count()); }
+unsigned window_bytes(const Params &p, int batch, int mode) {
+  if (p.in_features > 80 * 1024) return 0;
+  const WindowLds plan = window_lds(p.v, p.bits, mode, batch, p.k, p.k_res, p.in_features);
+  const long long bytes = plan.off_ypart + (mode == 2 ? (long long)window_rows(p) * batch * 4 : 0);
+  return bytes > 160 * 1024 || (long long)p.out_features * p.stride >= (1LL << 32) || (long long)p.out_features * p.stride_res >= (1LL << 32) ? 0u : (unsigned)bytes;
 }
 
 template <int V, int BITS, int MODE, int B>
 int launch_window(const Params &p, const __half *x, long long ldx, __half *y, long long ldy, hipStream_t s) {
-  LdsPlan plan;
-  if (!make_window_plan(p, B, win_vectors(BITS), entry_halfs(V), MODE == 2, &plan)) return VQ_ERR_UNSUPPORTED;
+  const int rows = window_rows(p);
+  const unsigned bytes = window_bytes(p, B, MODE);
+  if (!bytes || ldx > 0x7FFFFFFFLL || ldy > 0x7FFFFFFFLL || ldx < 0 || ldy < 0) return VQ_ERR_UNSUPPORTED;
   auto kernel = gemv_lds_window_kernel<V, BITS, MODE, B>;
   VQ_ALLOW_FULL_LDS(kernel);
-  const unsigned grid = (unsigned)((p.out_features + plan.rows_per_wg - 1) / plan.rows_per_wg);
-  hipLaunchKernelGGL(kernel, dim3(grid), dim3(LW * 64), plan.bytes, s, p, plan, x, ldx, y, ldy);
+  const WindowArgs a = {p.cb, p.cb_res, p.idx, p.idx_res, p.scale, p.bias, p.perm, x, y, p.out_features, p.in_features, (int)ldx, (int)ldy,
+                        (unsigned)p.stride, (unsigned)p.stride_res, (unsigned short)p.k, (unsigned short)p.k_res, rows};
+  hipLaunchKernelGGL(kernel, dim3((unsigned)((p.out_features + rows - 1) / rows)), dim3(LW * 64), bytes, s, a);
   return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
 }
 
@@ -724,7 +744,7 @@ bool gemv_lds_applicable(const Params &p, int batch) {
   if (p.orientation != 0) return false;
   if (p.n_groups == 1) {
     if (make_plan(p, batch, &plan)) return true;
-    if (window_pair(p) && (batch == 1 || batch == 2 || batch == 4) && make_window_plan(p, batch, win_vectors(p.bits), entry_halfs(p.v), false, &plan))
+    if (window_pair(p) && (batch == 1 || batch == 2 || batch == 4) && window_bytes(p, batch, p.k_res ? 1 : 0))
       return true;
   }
   return pass_pair(p) && (batch == 1 || batch == 2 || batch == 4) && make_pass_plan(p, batch, win_vectors(p.bits), entry_halfs(p.v), &pplan);
