@@ -141,7 +141,7 @@ int launch_groups_finish(const float *part, const float *part_xs, int n_groups, 
                          hipStream_t s);
 bool gemv_down_mfma_applicable(const Params &p, const __half *x, long long ldx, int batch);
 int gemv_down_mfma_parts(const Params &p);
-float gemv_down_mfma_us(const Params &p, int parts, int batch);
+float gemv_down_mfma_us(const Params &p, int parts, int batch, bool fold = true);
 float gemv_down_streams_us(const Params &p, int batch);
 int launch_gemv_down_mfma(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, hipStream_t s,
                           float *part, float *part_xs, int parts);
@@ -177,7 +177,10 @@ static bool down_mfma_alone_wanted(const Params &p, const __half *x, long long l
     if (!gemv_down_lds_applicable(p, 1)) return 1.9f * groups + walk < 1.0f + 0.03f * (float)p.P * std::max(1.0f, 1e-3f * (float)p.S);
     return (p.k_res ? 3.1f : 1.55f) * groups + walk < (p.k_res ? 5.0f : 2.5f) * groups + (p.k_res ? 1.3f : 0.65f) * vectors;
   }
-  return batch >= 5 || forced_kernel() == 'm' || 1.02f * gemv_down_mfma_us(p, 1, batch) < gemv_down_streams_us(p, batch);      // (of five rows and more a launch of four is one of two)
+  if (batch >= 5 || forced_kernel() == 'm') return true;      // (of five rows and more a launch of four is one of two)
+  const float whole = gemv_down_mfma_us(p, 1, batch, false), folded = gemv_down_mfma_us(p, 1, batch);
+  // (one row of 11008 x 4096, folded 9.0 us by the clock, 8.3 by the estimate, 8.7 here)
+  return (folded < whole ? 1.08f : 1.02f) * folded < gemv_down_streams_us(p, batch) || 1.02f * whole < gemv_down_streams_us(p, batch);
 }
 // Whether parts of the columns, which a workspace is there for, are worth the second launch, or with the activations copied in front a third one
 // (4096 x 4096, two rows, parts 8.4, without 8.6; 6513 x 2176, three rows 8.7 and 8.0; 539 x 3101, sixteen copied rows 13.4 and 12.0).
@@ -185,8 +188,10 @@ static bool down_mfma_parts_pay(const Params &p, int batch, bool copied) {
   if (p.n_groups > 1 || forced_kernel() == 'm' || !gemv_down_fits(p)) return true;
   const float copy = copied ? 1.8f : 0.0f;
   const int launches = copied ? 2 : 1;
-  const float alone = launched(gemv_down_mfma_us(p, 1, batch) + copy, launches);
-  const float parts = launched(gemv_down_mfma_us(p, gemv_down_mfma_parts(p), batch) + copy, launches + 1);
+  // (more than five parts spread a layer further than four folds of the columns do)
+  const int n = gemv_down_mfma_parts(p);
+  const float alone = launched(gemv_down_mfma_us(p, 1, batch, n <= 5) + copy, launches);
+  const float parts = launched(gemv_down_mfma_us(p, n, batch) + copy, launches + 1);
   return parts < alone && (batch > 4 || 1.06f * parts < gemv_down_streams_us(p, batch) + copy);
 }
 

@@ -66,7 +66,11 @@ __device__ __forceinline__ float4v mfma16(uint4v a, uint4v b, float4v c) {
 // FEW: up to two tokens of a layer with a residual table: 48 permutes a window are more than those tokens are worth.  Operand A is the entry as it
 // is, operand B has (token, row) pairs for columns, the activation in place j of eight for row j and zeros elsewhere, and serves both tables: 16
 // instructions and 24 permutes a window (two rows, 384 x 18752 13.1 -> 12.6 us; a decoder layer's one row, 832 and 2752 wide, 33.9 -> 33.1).
-template <int RES_BITS, bool WALK, bool FEW>
+// LOG_FOLDS: rows 0..15 of operand A, and columns 0..15 of operand B, are (stream or token, fold) pairs: a block has 16, 8 or 4 streams and their
+// columns come in one, two or four folds, window w of a fold being window w * folds + fold of the stream.  Of a result only what has the same fold on
+// both sides counts, and the folds' sums are added where the waves meet.  Up to eight (four) tokens find room beside one another, and a layer has
+// twice (four times) as many blocks of half (a quarter) the windows, without a second launch to add parts of the columns up.
+template <int RES_BITS, bool WALK, bool FEW, int LOG_FOLDS>
 __device__ __forceinline__ void gemv_down_mfma_body(const Params &p, const DownMfmaPlan &plan, const __half *__restrict__ x, long long ldx,
                                                     __half *__restrict__ y, long long ldy, int wg) {
   typedef Layout<RES_BITS> LY;
@@ -78,9 +82,12 @@ __device__ __forceinline__ void gemv_down_mfma_body(const Params &p, const DownM
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr int FOLDS = 1 << LOG_FOLDS, STREAMS = 16 / FOLDS;
+  static_assert(!(FEW && FOLDS > 1), "FEW has other columns in operand B");
   const int n = lane & 15, g = lane >> 4;                // A: stream n of the block, column group g.  B: token n.  D: token n, streams 4g..4g+3
+  const int fold = n / STREAMS;
   constexpr int PLANES = FEW ? 1 : 6;                    // sums a lane holds of its four streams
-  const int token = FEW ? n / 6 : n;
+  const int token = FEW ? n / 6 : n % STREAMS;
   const int blk = wg / plan.ksplit, part_i = wg - blk * plan.ksplit;
   // A part belongs to one codebook group; without a workspace the workgroup walks all groups, one set of tables after the
   // other in LDS, and its sums simply keep running (the tables change with the column, the output rows do not).
@@ -93,8 +100,8 @@ __device__ __forceinline__ void gemv_down_mfma_body(const Params &p, const DownM
   // index streams, one to the table, for all of them at once -- and multiplied from there once the barrier below has passed.
   // Without a workspace the rows are the block's own and their sums wait in LDS for the end; with one, the outlier columns
   // are one more part of the workspace and every workgroup of the launch takes a share of ALL rows.
-  const int o_row_lo = plan.part ? wg * plan.o_rpw : blk * OROWS;
-  const int o_rows = p.Q ? max(0, min(plan.part ? plan.o_rpw : OROWS, p.out_features - o_row_lo)) : 0;
+  const int o_row_lo = plan.part ? wg * plan.o_rpw : blk * (STREAMS * 6);
+  const int o_rows = p.Q ? max(0, min(plan.part ? plan.o_rpw : STREAMS * 6, p.out_features - o_row_lo)) : 0;
   const int Q2 = 2 * plan.o_pitch;                       // halves per tile row
   unsigned short *o_tile = reinterpret_cast<unsigned short *>(lds + plan.lds_o);
   unsigned short *o_x = o_tile + OROWS * Q2;
@@ -124,7 +131,7 @@ __device__ __forceinline__ void gemv_down_mfma_body(const Params &p, const DownM
     // the group's stream positions [pos_lo, pos_hi) -- pos_lo a multiple of 8, a dword boundary of the streams -- and the
     // part's windows, counted from pos_lo; a part past a short last group has none and leaves zeros
     const int pos_lo = grp * p.Pg, pos_hi = min(p.P, pos_lo + p.Pg);
-    const int windows = (pos_hi - pos_lo + 31) >> 5;
+    const int windows = (pos_hi - pos_lo + 32 * FOLDS - 1) / (32 * FOLDS);      // (of all folds together)
     const int w_lo = sub_i * plan.wpp, w_hi = min(windows, w_lo + plan.wpp);
     const int my_n = w_hi - w_lo > wv ? (w_hi - w_lo - wv + MW - 1) / MW : 0;  // this wave's windows: w_lo + wv + i * MW
     if (WALK && grp > g_lo) __syncthreads();             // every wave is done with the tables of the group before
@@ -176,11 +183,12 @@ __device__ __forceinline__ void gemv_down_mfma_body(const Params &p, const DownM
 
     // byte offset of this lane's first activation of window 0; a token past the batch reads out of range, i.e. zeros
     const int col0 = p.n_out + pos_lo;                     // column of x that meets the part's window 0
-    const unsigned xoff = token < plan.batch ? (unsigned)(((long long)token * ldx + col0 + 8 * g) * 2) : 0x80000000u;
+    const unsigned xoff = token < plan.batch ? (unsigned)(((long long)token * ldx + col0 + 32 * fold + 8 * g) * 2) : 0x80000000u;
 
     // a stream past the last one reads out of range: index 0, whose products land in rows that are never stored
-    const unsigned srow_main = (unsigned)(blk * 16 + n) * st_main + (unsigned)(pos_lo >> 3) * 12u;
-    const unsigned srow_res = (unsigned)(blk * 16 + n) * st_res + (unsigned)(pos_lo >> 3) * (unsigned)RB;
+    const unsigned octet = (unsigned)(fold * 4 + g), stream_a = (unsigned)(blk * STREAMS + n % STREAMS);
+    const unsigned srow_main = stream_a * st_main + ((unsigned)(pos_lo >> 3) + octet) * 12u;
+    const unsigned srow_res = stream_a * st_res + ((unsigned)(pos_lo >> 3) + octet) * (unsigned)RB;
 
     // The loaders run DEPTH windows ahead of the consumer.  A slot's index words are refilled as soon as the gather
     // addresses have been formed from them; so are its activations, from a copy.
@@ -188,14 +196,14 @@ __device__ __forceinline__ void gemv_down_mfma_body(const Params &p, const DownM
     auto load_idx = [&](Window<3> &wm, Window<NR> &wr) {
       const unsigned wq = (unsigned)(lw < w_hi ? lw : w_lo);                   // past the end: any window in range, never used
       lw += MW;
-      load_window(wm, r_main, srow_main + (wq * 4u + (unsigned)g) * 12u, 0u);
-      if (RES_BITS == 12) load_window(wr, r_res, srow_res + (wq * 4u + (unsigned)g) * 12u, 0u);
-      if (RES_BITS == 8) load_window(wr, r_res, srow_res + (wq * 4u + (unsigned)g) * 8u, 0u);
+      load_window(wm, r_main, srow_main + wq * (4u * FOLDS) * 12u, 0u);
+      if (RES_BITS == 12) load_window(wr, r_res, srow_res + wq * (4u * FOLDS) * 12u, 0u);
+      if (RES_BITS == 8) load_window(wr, r_res, srow_res + wq * (4u * FOLDS) * 8u, 0u);
     };
     auto load_x = [&](uint4v &xx) {
       const unsigned wq = (unsigned)(lwx < w_hi ? lwx : w_lo);
       lwx += MW;
-      xx = __builtin_amdgcn_raw_buffer_load_b128(r_x, xoff + wq * 64u, 0, 0);
+      xx = __builtin_amdgcn_raw_buffer_load_b128(r_x, xoff + wq * (64u * FOLDS), 0, 0);
     };
 
     Window<3> win[DEPTH];
@@ -258,7 +266,7 @@ __device__ __forceinline__ void gemv_down_mfma_body(const Params &p, const DownM
             for (int u = 0; u < VPL; ++u) lds_gather16<LY::RES_OFF>(f[u], field_addr<RB, LY::RES_SH>(cr, u) + LY::RES_ADD);
           }
           if (w == windows - 1) {                          // the window that holds the end of the stream or of the group: zero what lies past it
-            const int left = pos_hi - pos_lo - (w * 32 + g * 8);               // of this lane's eight positions
+            const int left = pos_hi - pos_lo - ((w * FOLDS + fold) * 32 + g * 8);      // of this lane's eight positions
             unsigned xd[4] = {xv.x, xv.y, xv.z, xv.w};
 #pragma unroll
             for (int q = 0; q < 4; ++q) xd[q] = left >= 2 * q + 2 ? xd[q] : left == 2 * q + 1 ? xd[q] & 0xFFFFu : 0u;
@@ -268,6 +276,12 @@ __device__ __forceinline__ void gemv_down_mfma_body(const Params &p, const DownM
           lds_gather_wait();
 #pragma unroll
           for (int u = 0; u < VPL; ++u) { settle(e[u]); if (RES_BITS) settle(f[u]); }
+          if (w == windows - 1) {                          // (the entries too: past a stream's end lie the next one's indices, whose entries need not be finite)
+            const int left = pos_hi - pos_lo - ((w * FOLDS + fold) * 32 + g * 8);
+#pragma unroll
+            for (int u = 0; u < VPL; ++u)
+              if (u >= left) { e[u] = uint4v{0u, 0u, 0u, 0u}; if (RES_BITS) f[u] = uint4v{0u, 0u, 0u, 0u}; }
+          }
           if constexpr (FEW) {
 #pragma unroll
             for (int u = 0; u < VPL; ++u) {
@@ -299,23 +313,35 @@ __device__ __forceinline__ void gemv_down_mfma_body(const Params &p, const DownM
   // ---- the waves meet: sums per output row of the streams, 1 KB per wave and row, in the space of the tables
   __syncthreads();
   float4v *pbuf = reinterpret_cast<float4v *>(lds);                           // [6][MW][64]
-  float *xsb = reinterpret_cast<float *>(lds + 6 * MW * 1024);                // [MW][16 tokens][4]
+  float *xsb = reinterpret_cast<float *>(lds + 6 * MW * 1024);                // [MW][16 tokens]
 #pragma unroll
-  for (int j = 0; j < PLANES; ++j) pbuf[(j * MW + wv) * 64 + lane] = acc[j];
-  if (!FEW || n % 6 == 0) xsb[(wv * 16 + token) * 4 + g] = xs;
+  for (int j = 0; j < PLANES; ++j)
+    if (FOLDS == 1 || 4 * g / STREAMS == fold) pbuf[(j * MW + wv) * 64 + lane] = acc[j];      // (of a result what has the same fold on both sides)
+  if (need_xs) {                                         // (the lanes of a token meet here: read one by one their sums would take the finishing waves 0.5 us)
+    xs += __shfl_xor(xs, 16, 64); xs += __shfl_xor(xs, 32, 64);
+    if (FOLDS > 1) xs += __shfl_xor(xs, 8, 64);
+    if (FOLDS > 2) xs += __shfl_xor(xs, 4, 64);
+    if (g == 0 && fold == 0 && (!FEW || n % 6 == 0)) xsb[wv * 16 + token] = xs;
+  }
   __syncthreads();
   if (wv < PLANES) {                                     // wave j finishes row j
     const int t = token, plane = wv, j = FEW ? n % 6 : wv;
     float4v s = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int w = 0; w < MW; ++w) s += pbuf[(plane * MW + w) * 64 + lane];
-    if (t < plan.batch) {
+    if constexpr (FOLDS > 1) {                           // streams 4g.. and token n of fold f are 5 STREAMS lanes behind those of fold f - 1
+      float4v one = s;
+#pragma unroll
+      for (int f = 1; f < FOLDS; ++f) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) s[r] += __shfl(one[r], (lane + f * 5 * STREAMS) & 63, 64);
+      }
+    }
+    if (t < plan.batch && (FOLDS == 1 || (n < STREAMS && 4 * g < STREAMS))) {
       float xsum = 0.0f;
       if (need_xs) {
 #pragma unroll
-        for (int w = 0; w < MW; ++w)
-#pragma unroll
-          for (int gg = 0; gg < 4; ++gg) xsum += xsb[(w * 16 + t) * 4 + gg];
+        for (int w = 0; w < MW; ++w) xsum += xsb[w * 16 + t];
       }
       float sv[4] = {s.x, s.y, s.z, s.w};
       if (p.Q && !plan.part) {                           // the block's own outlier sums, left in LDS before the main loop
@@ -325,7 +351,7 @@ __device__ __forceinline__ void gemv_down_mfma_body(const Params &p, const DownM
       }
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int stream = blk * 16 + 4 * g + r, o = stream * 6 + j;
+        const int stream = blk * STREAMS + 4 * g + r, o = stream * 6 + j;
         if (stream < p.S && o < p.out_features) {
           if (plan.part) {
             plan.part[((long long)part_i * plan.batch + t) * p.out_features + o] = sv[r];
@@ -340,10 +366,10 @@ __device__ __forceinline__ void gemv_down_mfma_body(const Params &p, const DownM
   }
 }
 
-template <int RES_BITS, bool WALK, bool FEW>
+template <int RES_BITS, bool WALK, bool FEW, int LOG_FOLDS>
 __global__ __launch_bounds__(MW * 64) void gemv_down_mfma_kernel(Params p, DownMfmaPlan plan, const __half *__restrict__ x, long long ldx,
                                                                  __half *__restrict__ y, long long ldy) {
-  gemv_down_mfma_body<RES_BITS, WALK, FEW>(p, plan, x, ldx, y, ldy, (int)blockIdx.x);
+  gemv_down_mfma_body<RES_BITS, WALK, FEW, LOG_FOLDS>(p, plan, x, ldx, y, ldy, (int)blockIdx.x);
 }
 
 // Several layers that read the same activations (the query, key and value projections of a decoder layer; its gate and up
@@ -363,11 +389,11 @@ struct DownMultiArgs {
   DownMultiLayer layer[DMULTI_MAX];
 };
 
-template <int RES_BITS, bool FEW>
+template <int RES_BITS, bool FEW, int LOG_FOLDS>
 __global__ __launch_bounds__(MW * 64) void gemv_down_mfma_multi_kernel(DownMultiArgs a, const __half *__restrict__ x, long long ldx) {
   int i = 0;
   while (i + 1 < a.n && (int)blockIdx.x >= a.first_wg[i + 1]) ++i;
-  gemv_down_mfma_body<RES_BITS, false, FEW>(a.layer[i].p, a.layer[i].plan, x, ldx, a.layer[i].y, a.layer[i].ldy, (int)blockIdx.x - a.first_wg[i]);
+  gemv_down_mfma_body<RES_BITS, false, FEW, LOG_FOLDS>(a.layer[i].p, a.layer[i].plan, x, ldx, a.layer[i].y, a.layer[i].ldy, (int)blockIdx.x - a.first_wg[i]);
 }
 
 
@@ -375,16 +401,16 @@ __global__ __launch_bounds__(MW * 64) void gemv_down_mfma_multi_kernel(DownMulti
 template <int RES_BITS>
 unsigned place_lds(const Params &p, DownMfmaPlan &plan) {
   unsigned lds_bytes = Layout<RES_BITS>::BYTES;
-  const unsigned meet = (unsigned)(6 * MW) * 1024u + (unsigned)(MW * 16 * 4) * 4u;
+  const unsigned meet = (unsigned)(6 * MW) * 1024u + (unsigned)(MW * 16) * 4u;
   if (lds_bytes < meet) lds_bytes = meet;
   plan.lds_o = lds_bytes;
   if (p.Q) lds_bytes += (unsigned)((OROWS + 16) * plan.o_pitch + 16 * OROWS + 16) * 4u;
   return lds_bytes;
 }
 
-template <int RES_BITS, bool FEW>
+template <int RES_BITS, bool FEW, int LOG_FOLDS>
 int launch_multi(DownMultiArgs &a, const __half *x, long long ldx, hipStream_t s) {
-  auto kernel = gemv_down_mfma_multi_kernel<RES_BITS, FEW>;
+  auto kernel = gemv_down_mfma_multi_kernel<RES_BITS, FEW, LOG_FOLDS>;
   VQ_ALLOW_FULL_LDS(kernel);
   unsigned lds_bytes = 0;
   for (int i = 0; i < a.n; ++i) {
@@ -396,10 +422,10 @@ int launch_multi(DownMultiArgs &a, const __half *x, long long ldx, hipStream_t s
   return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
 }
 
-template <int RES_BITS, bool WALK, bool FEW>
+template <int RES_BITS, bool WALK, bool FEW, int LOG_FOLDS>
 int launch_one(const Params &p, DownMfmaPlan &plan, unsigned grid, const __half *x, long long ldx, __half *y, long long ldy,
                hipStream_t s) {
-  auto kernel = gemv_down_mfma_kernel<RES_BITS, WALK, FEW>;
+  auto kernel = gemv_down_mfma_kernel<RES_BITS, WALK, FEW, LOG_FOLDS>;
   VQ_ALLOW_FULL_LDS(kernel);
   const unsigned lds_bytes = place_lds<RES_BITS>(p, plan);
   if (lds_bytes > 160u * 1024u) return VQ_ERR_UNSUPPORTED;                  // too many outlier columns to hold beside the tables
@@ -439,22 +465,37 @@ int gemv_down_mfma_parts(const Params &p) { return p.n_groups * parts_per_group(
 // Estimated time in microseconds of `batch` rows of a layer without codebook groups in `parts` parts, from 1560 layers (256 to 14336 outputs, 256 to
 // 28672 columns, one to sixteen rows; 4 % off in the mean, sixteen rows 7): a workgroup's start and its waves' windows, as often as compute units take
 // one; the second launch and its sums; the outlier columns, which a block's rows have one workgroup for, or one a part.
-float gemv_down_mfma_us(const Params &p, int parts, int batch) {
-  const int blocks = (p.S + 15) / 16, windows = (p.P + 31) / 32, rounds = (blocks * parts + cu_count() - 1) / cu_count();
+static float estimate_us(const Params &p, int parts, int folds, int batch) {
+  const int blocks = (int)(((long long)p.S * folds + 15) / 16), windows = (p.P + 32 * folds - 1) / (32 * folds), rounds = (blocks * parts + cu_count() - 1) / cu_count();
   const int steps = ((windows + parts - 1) / parts + MW - 1) / MW;
-  const bool few = p.k_res && batch <= 2, long_table = p.bits_res == 12;
+  const bool few = p.k_res && batch <= 2 && folds == 1, long_table = p.bits_res == 12;
   const float start = (!p.k_res ? 2.5f : long_table ? (few ? 2.7f : 3.03f) : few ? 2.25f : 2.55f) + (batch > 8 ? 0.2f : 0.0f);
   const float step = !p.k_res ? 0.335f : !long_table ? 0.7f : few ? 0.715f : 0.73f, outputs = (float)p.out_features;
-  // (sixteen rows that begin on one of few lines of L1 each get in one another's way; a part of them less so)
-  const float pitch = parts == 1 && batch > 8 && !p.k_res && p.in_features % 256 == 0 ? 1.18f : 1.0f;
+  // (sixteen rows, or folds of rows, that begin on one of few lines of L1 each get in one another's way; a part of them less so)
+  const float pitch = parts == 1 && batch * folds > 8 && !p.k_res && p.in_features % 256 == 0 ? (folds > 1 ? 1.25f : 1.18f) : 1.0f;
   float us = start * (float)(1 + rounds) + pitch * step * (float)(rounds * steps);
+  // (47 layers with each number of folds, one, four and eight rows, 2 to 4 % off: half the streams or a quarter are that many more workgroups after the
+  // tables, and two tables of 4096 entries leave a compute unit no room for a second one)
+  if (folds > 1) us += (folds == 2 ? 0.55f : 0.8f) + (long_table ? 2.1f * (float)(rounds - 1) : 0.0f);
   if (parts > 1) us += 0.85f + (float)parts * (0.12f + outputs * (1.7e-5f + 5.2e-6f * (float)batch));
   if (p.Q) us += 1.2f + (float)p.Q * (parts > 1 ? 0.03f + 2.2e-6f * outputs : p.k_res ? 0.06f : 0.08f);
   return us;
 }
 
-static int make_plan(const Params &p, long long ldx, int batch, float *part, float *part_xs, int parts, DownMfmaPlan &plan, long long *grid_out) {
-  const int blocks = (p.S + 15) / 16, windows = (min(p.P, p.Pg) + 31) / 32;                // windows of the widest group
+// Folds of the columns of one launch without parts.
+static int folds_of(const Params &p, int batch) {
+  int best = 1;
+  if (p.n_groups > 1) return best;
+  for (int folds = 2; folds <= 4 && batch * folds <= 16; folds *= 2)
+    if (estimate_us(p, 1, folds, batch) < 0.96f * estimate_us(p, 1, best, batch)) best = folds;      // (as close as the estimates are)
+  return best;
+}
+float gemv_down_mfma_us(const Params &p, int parts, int batch, bool fold) {
+  return estimate_us(p, parts, parts == 1 && fold ? folds_of(p, batch) : 1, batch);
+}
+
+static int make_plan(const Params &p, long long ldx, int batch, float *part, float *part_xs, int parts, int folds, DownMfmaPlan &plan, long long *grid_out) {
+  const int blocks = (int)(((long long)p.S * folds + 15) / 16), windows = (min(p.P, p.Pg) + 32 * folds - 1) / (32 * folds);      // windows of the widest group
   if (blocks < 1 || windows < 1) return VQ_ERR_UNSUPPORTED;
   plan.ksplit = part ? parts : 1;
   if (part && plan.ksplit % p.n_groups) return VQ_ERR_UNSUPPORTED;
@@ -481,13 +522,16 @@ int launch_gemv_down_mfma(const Params &p, const __half *x, long long ldx, int b
                           float *part, float *part_xs, int parts) {
   DownMfmaPlan plan{};
   long long grid = 0;
-  const int rc_plan = make_plan(p, ldx, batch, part, part_xs, parts, plan, &grid);
+  const int folds = part ? 1 : folds_of(p, batch), rc_plan = make_plan(p, ldx, batch, part, part_xs, parts, folds, plan, &grid);
   if (rc_plan != VQ_OK) return rc_plan;
   const int rb = p.k_res ? p.bits_res : 0;
   const bool walk = !part && p.n_groups > 1;
-#define VQ_CASE(R) if (rb == R) \
-    return batch <= 2 && R ? (walk ? launch_one<R, true, R != 0>(p, plan, (unsigned)grid, x, ldx, y, ldy, s) : launch_one<R, false, R != 0>(p, plan, (unsigned)grid, x, ldx, y, ldy, s)) \
-                           : (walk ? launch_one<R, true, false>(p, plan, (unsigned)grid, x, ldx, y, ldy, s) : launch_one<R, false, false>(p, plan, (unsigned)grid, x, ldx, y, ldy, s));
+#define VQ_CASE(R) if (rb == R) { \
+    if (folds == 4) return launch_one<R, false, false, 2>(p, plan, (unsigned)grid, x, ldx, y, ldy, s); \
+    if (folds == 2) return launch_one<R, false, false, 1>(p, plan, (unsigned)grid, x, ldx, y, ldy, s); \
+    return batch <= 2 && R ? (walk ? launch_one<R, true, R != 0, 0>(p, plan, (unsigned)grid, x, ldx, y, ldy, s) : launch_one<R, false, R != 0, 0>(p, plan, (unsigned)grid, x, ldx, y, ldy, s)) \
+                           : (walk ? launch_one<R, true, false, 0>(p, plan, (unsigned)grid, x, ldx, y, ldy, s) : launch_one<R, false, false, 0>(p, plan, (unsigned)grid, x, ldx, y, ldy, s)); \
+  }
   VQ_CASE(0) VQ_CASE(8) VQ_CASE(12)
 #undef VQ_CASE
   return VQ_ERR_UNSUPPORTED;
@@ -502,11 +546,15 @@ int launch_gemv_down_mfma_multi(const Params *ps, int n, const __half *x, long l
   DownMultiArgs a{};
   a.n = n;
   const int rb = ps[0].k_res ? ps[0].bits_res : 0;
-  long long total = 0;
+  long long total = 0, streams = 0;
+  for (int i = 0; i < n; ++i) streams += ps[i].S;
+  Params all = ps[0];                                      // (as one layer of all their streams; beside other layers outlier columns cost what they do alone)
+  all.S = (int)min(streams, 1LL << 24);
+  const int folds = folds_of(all, batch);
   for (int i = 0; i < n; ++i) {
     if (ps[i].in_features != ps[0].in_features || ps[i].n_groups > 1 || (ps[i].k_res ? ps[i].bits_res : 0) != rb) return VQ_ERR_UNSUPPORTED;
     long long grid = 0;
-    const int rc = make_plan(ps[i], ldx, batch, nullptr, nullptr, 1, a.layer[i].plan, &grid);
+    const int rc = make_plan(ps[i], ldx, batch, nullptr, nullptr, 1, folds, a.layer[i].plan, &grid);
     if (rc != VQ_OK) return rc;
     a.layer[i].p = ps[i]; a.layer[i].y = ys[i]; a.layer[i].ldy = ldys[i];
     a.first_wg[i] = (int)total;
@@ -514,7 +562,9 @@ int launch_gemv_down_mfma_multi(const Params *ps, int n, const __half *x, long l
     if (total > 0x7FFFFFFFLL) return VQ_ERR_UNSUPPORTED;
   }
   a.first_wg[n] = (int)total;
-#define VQ_CASE(R) if (rb == R) return batch <= 2 && R ? launch_multi<R, R != 0>(a, x, ldx, s) : launch_multi<R, false>(a, x, ldx, s);
+#define VQ_CASE(R) if (rb == R) \
+    return folds == 4 ? launch_multi<R, false, 2>(a, x, ldx, s) : folds == 2 ? launch_multi<R, false, 1>(a, x, ldx, s) : \
+           batch <= 2 && R ? launch_multi<R, R != 0, 0>(a, x, ldx, s) : launch_multi<R, false, 0>(a, x, ldx, s);
   VQ_CASE(0) VQ_CASE(8) VQ_CASE(12)
 #undef VQ_CASE
   return VQ_ERR_UNSUPPORTED;

@@ -1252,3 +1252,34 @@ def test_gemv_activations_through_lds_and_short_blocks(gpu_lib, out_features, in
         torch.cuda.synchronize()
         _check_matmul(ya, ref, "first of two")
         _check_matmul(yb, oracle.gemv(second, x_np), "second of two")
+
+
+@pytest.mark.parametrize("out_features,in_features,more,batch", [
+    (37, 1300, {}, 4), (1501, 2018, {}, 3), (3001, 1030, dict(k_res=4096), 4), (95, 1282, dict(k_res=256), 1), (49, 2000, dict(k_res=4096, n_outlier_cols=24, v_out=4, k_out=4096), 2),
+    (3100, 1170, {}, 8), (9605, 1300, {}, 2), (9700, 1160, dict(k_res=4096), 5), (71, 1345, dict(k_res=256, n_outlier_cols=10, v_out=4, k_out=4096), 7),
+])
+def test_gemv_down_folds(gpu_lib, monkeypatch, out_features, in_features, more, batch):
+    """Vectors down the outputs, two and four folds of the columns in one instruction: blocks of eight and four streams, the last one short, and windows of
+    which some folds lie past the columns, where they meet the next stream's indices: its entries, infinite ones, are that stream's alone."""
+    import torch
+    monkeypatch.setenv("VQ_SWITCHES", "gemv=m")
+    L = s.make_layer(323, "folds", out_features, in_features, 6, 4096, orientation=1, **more)
+    L.codebook[1::2] = np.inf
+    bits = np.unpackbits(L.idx, axis=1, bitorder="little")
+    bits[:, 0 : L.vectors_per_row * 12 : 12] = 0
+    bits[1, 0] = 1                                       # one odd index, the first of the second stream
+    L.idx = np.packbits(bits, axis=1, bitorder="little")
+    pitch = (in_features + 7) // 8 * 8 + 8
+    x_np = s.make_activations(323, L, batch)
+    x = torch.full((batch, pitch), float("nan"), dtype=torch.float16, device="cuda")
+    x[:, :in_features] = torch.from_numpy(x_np)
+    dl, second = gpu_lib.DeviceLayer(L), s.make_layer(324, "second", 100, in_features, 6, 4096, orientation=1, **more)
+    rows = np.r_[0:6, 12:out_features]
+    ref = oracle.gemv(L, x_np)[:, rows]
+    y = gpu_lib.gemv(dl, x[:, :in_features])
+    ya, yb = gpu_lib.gemv_multi([dl, gpu_lib.DeviceLayer(second)], x[:, :in_features])
+    torch.cuda.synchronize()
+    for what, one in (("alone", y), ("first of two", ya)):
+        assert not torch.isfinite(one[:, 6:12]).any()
+        _check_matmul(one[:, rows], ref, what)
+    _check_matmul(yb, oracle.gemv(second, x_np), "second of two")

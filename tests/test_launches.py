@@ -199,3 +199,14 @@ def test_gemv_borrows_only_what_its_rows_use():
     unused = [call for call, answer, without in zip(calls[4:], odd, plain) if answer["lent"] and answer["launches"] == without["launches"]]
     # (of some layers of few vectors the size is asked for, for activations that begin elsewhere)
     assert sum(answer["lent"] > 0 for answer in odd) > 100 and len(unused) < 20
+
+
+@pytest.mark.parametrize("out,inp,rows,more,streams", [
+    (11008, 4096, 8, {}, 8), (11008, 4096, 9, {}, 16), (11008, 4096, 2, dict(k_res=4096), 8), (4096, 4096, 4, {}, 4), (4096, 4096, 5, {}, 8), (14080, 4096, 4, {}, 16),
+    (95, 1282, 7, dict(k_res=256), 8), (3001, 1030, 4, dict(k_res=4096), 4), (9605, 1300, 2, {}, 8), (512, 256, 4, dict(k_res=4096), 16),
+])
+def test_gemv_down_folds_of_the_columns(out, inp, rows, more, streams):
+    """How many index streams a workgroup takes of a layer whose vectors run down the outputs."""
+    answer, = launches.run([dict(entry="gemv", rows=rows, pitch=inp + inp % 2, layer=dict(out_features=out, in_features=inp, orientation=1, **more))])
+    grids = [launch["grid"] for launch in answer["launches"] if launch["name"].startswith("gemv_down_mfma")]
+    assert [list(grid)[0] for grid in grids] == [-(-(-(-out // 6)) // streams)], answer
