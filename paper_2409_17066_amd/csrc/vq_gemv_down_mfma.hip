@@ -11,8 +11,10 @@
 // and three permutes each: sixteen rows, 11008 x 4096 with column parts 18.4 -> 12.5 us, four 11.3 -> 9.9; two 4096-entry tables, without
 // parts, 4096 x 11008, 93 -> 38 and 40 -> 37; a whole decoder layer, sixteen rows 89 -> 52 us, with residual tables 125 -> 70.)
 //
-// What bounds it: eleven of the 17 thousand clocks of 11008 x 4096 in two parts are the windows', 160 of a compute unit each, of which LDS
-// takes 106 for the lookups.  Sixteen waves instead of eight (9.9 -> 10.8 us) and lookups a window ahead of the products (10.3) are slower.
+// What bounds it: eleven of the 17 thousand clocks of 11008 x 4096 in two parts were the windows', 160 of a compute unit each, of which LDS
+// takes 106 for the lookups; the rest is the start-up, tables first.  Folds of the columns (LOG_FOLDS below) in place of two to five parts spare the second
+// launch: four rows 10.4 -> 9.5 us.  Without a workspace, where blocks of sixteen streams left compute units idle, 10.8 -> 9.1, 4096 x 11008 with two tables
+// 37.8 -> 16.5, 8192 x 28672 48.4 -> 26.7.  Sixteen waves instead of eight (9.9 -> 10.8 us) and lookups a window ahead of the products (10.3) are slower.
 //
 // Work split: a workgroup of eight waves owns one block of 16 index streams (96 output rows) and one part of the
 // columns; wave w takes the part's windows w, w + 8, ... of 32 columns (eight per lane: 96 index bits, three aligned
@@ -20,7 +22,8 @@
 // with range-checked buffer loads).  Index words and activations run a few windows ahead in a register ring.  At the
 // end the waves' 16 x 16 sums per output row of the streams meet in LDS, in the space of the tables, which are no longer needed.
 // With one part the workgroup applies y = scale * sum + bias * sum(x) itself; a block of 16 streams is a coarse unit,
-// though (a 4096 x 4096 layer has 43 of them for 256 compute units), so when the caller lends a workspace the columns
+// though (a 4096 x 4096 layer has 43 of them for 256 compute units), so up to eight rows may take half of one or a quarter, the columns in folds, and
+// where that is not enough and the caller lends a workspace the columns
 // are cut into parts, every (block, part) is a workgroup, the binary32 sums go to the workspace [part][token][row] and
 // the kernel that adds up codebook groups (vq_gemv_mfma.hip) adds up the parts.  Codebook groups (Sec. 3.1: ranges of
 // columns with tables of their own) are parts by nature -- a part stages the tables of its group -- and are cut further
@@ -76,13 +79,13 @@ __device__ __forceinline__ void gemv_down_mfma_body(const Params &p, const DownM
   typedef Layout<RES_BITS> LY;
   constexpr int RB = RES_BITS ? RES_BITS : 8;
   constexpr int NR = RES_BITS == 12 ? 3 : 2;             // dwords of a lane's residual indices
-  // (measured: a ring deeper than this only adds start-up loads -- a wave of a column part has few windows -- and the
-  // refill of a slot already runs a window ahead of its use)
-  constexpr int DEPTH = 1;
+  constexpr int FOLDS = 1 << LOG_FOLDS, STREAMS = 16 / FOLDS;
+  // (measured: in the few windows of a part a deeper ring only adds start-up loads; with folds, whose waves have a whole row's, two windows ahead
+  // 11008 x 4096, four rows, streams in memory 9.7 -> 9.5 us, 8192 x 28672 28.0 -> 26.7, four 9.8; not beside a residual table, 698 x 1216 8.6 -> 9.0)
+  constexpr int DEPTH = FOLDS > 1 && RES_BITS == 0 ? 2 : 1;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  constexpr int FOLDS = 1 << LOG_FOLDS, STREAMS = 16 / FOLDS;
   static_assert(!(FEW && FOLDS > 1), "FEW has other columns in operand B");
   const int n = lane & 15, g = lane >> 4;                // A: stream n of the block, column group g.  B: token n.  D: token n, streams 4g..4g+3
   const int fold = n / STREAMS;
