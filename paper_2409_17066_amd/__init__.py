@@ -199,7 +199,7 @@ def _native():
         from . import _binding as b
         b.bind({name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value
                 for name in ("vq_gemv", "vq_gemv_with_workspace", "vq_gemv_multi", "vq_gemm", "vq_gemm_default", "vq_gemm_workspace_bytes",
-                             "vq_gemm_default_workspace_bytes", "vq_lend_gemv_bytes", "vq_lend_gemm_least_bytes", "vq_dequant", "vq_assign", "vq_assign_down")})
+                             "vq_gemm_default_workspace_bytes", "vq_lend_gemv_bytes", "vq_lend_gemm_least_bytes", "vq_dequant", "vq_lend_assign")})
         _bound = b
     return _bound
 

@@ -5,7 +5,6 @@
 // errors --, the status code when the library refused, and the result otherwise.
 #include <Python.h>
 #include <ATen/hip/EmptyTensor.h>
-#include <ATen/ops/zeros.h>
 #include <c10/hip/HIPCachingAllocator.h>
 #include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
@@ -23,7 +22,7 @@ decltype(&vq_gemv_multi) p_gemv_multi;
 decltype(&vq_gemm) p_gemm, p_gemm_default;
 decltype(&vq_gemm_workspace_bytes) p_gemm_workspace_bytes, p_gemm_default_workspace_bytes, p_lend_gemm_least_bytes;
 decltype(&vq_dequant) p_dequant;
-decltype(&vq_assign) p_assign, p_assign_down;
+decltype(&vq_lend_assign) p_lend_assign;
 
 PyObject *s_desc, *s_places;
 
@@ -242,12 +241,11 @@ PyObject *assign(PyObject *, PyObject *const *args, Py_ssize_t n) {
   while ((int64_t(1) << bits) < k) ++bits;
   const int64_t streams = down ? (rows + v - 1) / v : rows, per_stream = down ? cols : (cols + v - 1) / v;
   const int64_t stride = (per_stream * bits + 127) / 128 * 16;
-  at::Tensor idx = at::zeros({streams, stride}, at::TensorOptions().dtype(at::kByte).device(c10::Device(c10::kCUDA, c10::hip::current_device())));
+  at::TensorBase idx = empty({streams, stride}, at::kByte);
   const void *wp = W->data_ptr(), *bp = B ? B->data_ptr() : nullptr, *cp = C->data_ptr();
   void *ip = idx.data_ptr(), *s = stream();
   const int64_t ld = W->stride(0);
-  const auto call = down ? p_assign_down : p_assign;
-  const int rc = released([&] { return call(wp, bp, ld, (int32_t)rows, (int32_t)cols, cp, (int32_t)v, (int32_t)k, ip, stride, s); });
+  const int rc = released([&] { return p_lend_assign(wp, bp, ld, (int32_t)rows, (int32_t)cols, cp, (int32_t)v, (int32_t)k, ip, stride, down, s); });
   if (rc != VQ_OK) return PyLong_FromLong(rc);
   return THPVariable_Wrap(std::move(idx));
   VQ_CATCH
@@ -271,7 +269,7 @@ PyObject *bind(PyObject *, PyObject *addresses) {
   if (!at("vq_gemv", p_gemv) || !at("vq_gemv_with_workspace", p_gemv_ws) || !at("vq_gemv_multi", p_gemv_multi) || !at("vq_gemm", p_gemm) || !at("vq_gemm_default", p_gemm_default) ||
       !at("vq_gemm_workspace_bytes", p_gemm_workspace_bytes) || !at("vq_lend_gemv_bytes", p_lend_gemv_bytes) || !at("vq_gemm_default_workspace_bytes", p_gemm_default_workspace_bytes) ||
       !at("vq_lend_gemm_least_bytes", p_lend_gemm_least_bytes) ||
-       !at("vq_dequant", p_dequant) || !at("vq_assign", p_assign) || !at("vq_assign_down", p_assign_down)) {
+       !at("vq_dequant", p_dequant) || !at("vq_lend_assign", p_lend_assign)) {
     if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "an entry point is missing");
     return nullptr;
   }

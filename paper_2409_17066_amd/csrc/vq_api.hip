@@ -305,33 +305,36 @@ extern "C" int vq_gemm_default(const vq_layer_desc *desc, const void *X, int64_t
   return vq::checked_gemm(desc, X, ldx, tokens, Y, ldy, workspace, workspace_bytes, hip_stream, vq::launch_gemm_default);
 }
 
-extern "C" int vq_assign(const void *W, const void *B, int64_t ld, int32_t rows, int32_t cols, const void *codebook, int32_t v, int32_t k,
-                         void *idx, int64_t idx_row_stride, void *hip_stream) {
+static int checked_assign(const void *W, const void *B, int64_t ld, int32_t rows, int32_t cols, const void *codebook, int32_t v, int32_t k, void *idx,
+                          int64_t idx_row_stride, bool down, bool clear, void *hip_stream) {
   if (!W || !codebook || !idx) return VQ_ERR_NULL;
   const int lim = 1 << 24;
   if (rows < 1 || rows > lim || cols < 1 || cols > lim || ld < cols || v < 1 || v > 16 || k < 2 || k > 65536) return VQ_ERR_SHAPE;
-  const long long P = ((long long)cols + v - 1) / v;
+  const long long P = down ? cols : ((long long)cols + v - 1) / v;
   const long long need = ((P * vq::index_bits(k) + 31) / 32) * 4;             // whole dwords
   if (idx_row_stride < need) return VQ_ERR_SHAPE;
   if (!aligned(W, 2) || (B && !aligned(B, 2)) || !aligned(codebook, 2)) return VQ_ERR_ALIGNMENT;
   if (!aligned(idx, 16) || idx_row_stride % 16 != 0) return VQ_ERR_ALIGNMENT;
-  return vq::launch_assign(static_cast<const __half *>(W), static_cast<const __half *>(B), ld, rows, cols,
-                           static_cast<const __half *>(codebook), v, k, static_cast<unsigned char *>(idx), idx_row_stride,
-                           static_cast<hipStream_t>(hip_stream));
+  return (down ? vq::launch_assign_down : vq::launch_assign)(static_cast<const __half *>(W), static_cast<const __half *>(B), ld, rows, cols,
+                                                             static_cast<const __half *>(codebook), v, k, static_cast<unsigned char *>(idx), idx_row_stride,
+                                                             clear, static_cast<hipStream_t>(hip_stream));
+}
+
+extern "C" int vq_assign(const void *W, const void *B, int64_t ld, int32_t rows, int32_t cols, const void *codebook, int32_t v, int32_t k,
+                         void *idx, int64_t idx_row_stride, void *hip_stream) {
+  return checked_assign(W, B, ld, rows, cols, codebook, v, k, idx, idx_row_stride, false, false, hip_stream);
 }
 
 extern "C" int vq_assign_down(const void *W, const void *B, int64_t ld, int32_t rows, int32_t cols, const void *codebook, int32_t v,
                               int32_t k, void *idx, int64_t idx_row_stride, void *hip_stream) {
-  if (!W || !codebook || !idx) return VQ_ERR_NULL;
-  const int lim = 1 << 24;
-  if (rows < 1 || rows > lim || cols < 1 || cols > lim || ld < cols || v < 1 || v > 16 || k < 2 || k > 65536) return VQ_ERR_SHAPE;
-  const long long need = (((long long)cols * vq::index_bits(k) + 31) / 32) * 4;             // whole dwords
-  if (idx_row_stride < need) return VQ_ERR_SHAPE;
-  if (!aligned(W, 2) || (B && !aligned(B, 2)) || !aligned(codebook, 2)) return VQ_ERR_ALIGNMENT;
-  if (!aligned(idx, 16) || idx_row_stride % 16 != 0) return VQ_ERR_ALIGNMENT;
-  return vq::launch_assign_down(static_cast<const __half *>(W), static_cast<const __half *>(B), ld, rows, cols,
-                                static_cast<const __half *>(codebook), v, k, static_cast<unsigned char *>(idx), idx_row_stride,
-                                static_cast<hipStream_t>(hip_stream));
+  return checked_assign(W, B, ld, rows, cols, codebook, v, k, idx, idx_row_stride, true, false, hip_stream);
+}
+
+extern "C" int vq_lend_assign(const void *W, const void *B, int64_t ld, int32_t rows, int32_t cols, const void *codebook, int32_t v, int32_t k,
+                              void *idx, int64_t idx_row_stride, int32_t down, void *hip_stream) {
+  const long long bits = (down ? (long long)cols : ((long long)cols + v - 1) / std::max(v, 1)) * vq::index_bits(std::max(k, 2));
+  if (idx_row_stride > (bits + 127) / 128 * 16) return VQ_ERR_SHAPE;          // (three dwords of padding at most)
+  return checked_assign(W, B, ld, rows, cols, codebook, v, k, idx, idx_row_stride, down != 0, true, hip_stream);
 }
 
 extern "C" size_t vq_quantize_columns_workspace_bytes(int32_t rows, int32_t v, int32_t k, int32_t k_res) {

@@ -37,6 +37,15 @@ struct Vectors {
   long long scatter_bit;
 };
 
+// What follows the streams' last dwords, `count` dwords from number `from` on of each of `rows` strides, as zeros for a caller whose buffer is as the
+// allocator left it (count = 0: left alone).  Every thread of a launch takes some; a launch of its own that cleared the whole buffer in front took
+// 11008 x 4096 4 us of 958, 880 x 3712, v = 4, k = 256 5 of 25.
+struct Padding { unsigned char *idx; long long stride; int rows, from, count; };
+__device__ __forceinline__ void clear_padding(const Padding &p) {
+  for (int i = (int)(blockIdx.x * blockDim.x + threadIdx.x); i < p.rows * p.count; i += (int)(gridDim.x * blockDim.x))
+    reinterpret_cast<unsigned *>(p.idx + (long long)(i / p.count) * p.stride)[p.from + i % p.count] = 0u;
+}
+
 // Writes `count` bits of a dword that another lane may be writing other bits of.
 __device__ __forceinline__ void put_bits(unsigned *w, unsigned value, int from, int count) {
   const unsigned mask = (count >= 32 ? 0xFFFFFFFFu : (1u << count) - 1u) << from;
@@ -396,9 +405,10 @@ __device__ __forceinline__ void set_slots(half8 &b, int half, _Float16 factor) {
 // NT: tiles of 32 vectors a wave holds.  WIDE: blocks of 32 centroids.  CHUNKED: more than SCREEN_ROWS entries, a chunk of them after the other.  SPLIT: `split` waves (a power of two) share a tile of vectors, each taking its share
 // of the table.  The first last_wgs workgroups take `last`, the others `first`.
 template <int V, bool BASE, int NT, bool SPLIT, bool WIDE, bool CHUNKED>
-__global__ __launch_bounds__(WAVES * 64, 4) void assign_screen_kernel(Vectors first, Vectors last, int last_wgs, const __half *__restrict__ codebook,
+__global__ __launch_bounds__(WAVES * 64, 4) void assign_screen_kernel(Vectors first, Vectors last, Padding padding, int last_wgs, const __half *__restrict__ codebook,
                                                                        int stride, int k, int bits, int seg_len, int split) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  clear_padding(padding);
   const int rows_lds = screen_rows(k);
   half8 *plane = reinterpret_cast<half8 *>(smem);                                     // [2][rows_lds]
   float *red = reinterpret_cast<float *>(smem + (size_t)rows_lds * 32);               // [2 * WAVES]
@@ -772,10 +782,11 @@ __global__ __launch_bounds__(WAVES * 64, 4) void assign_screen_kernel(Vectors fi
 constexpr int SHORT_TABLE = 64, SHORT_THREADS = 256;
 
 template <int V>
-__global__ __launch_bounds__(SHORT_THREADS) void assign_short_kernel(Vectors first, Vectors last, int last_wgs, const __half *__restrict__ codebook,
+__global__ __launch_bounds__(SHORT_THREADS) void assign_short_kernel(Vectors first, Vectors last, Padding padding, int last_wgs, const __half *__restrict__ codebook,
                                                                      int stride, int k, int bits, int seg_len) {
   __shared__ __attribute__((aligned(16))) float table[SHORT_TABLE * V];
   __shared__ unsigned codes[SHORT_THREADS];
+  clear_padding(padding);
   const bool is_last = (int)blockIdx.x < last_wgs;
   const Vectors a = is_last ? last : first;
   const long long items = items_of(a, seg_len), g0 = (long long)(is_last ? blockIdx.x : blockIdx.x - last_wgs) * SHORT_THREADS;
@@ -817,10 +828,11 @@ constexpr unsigned LDS_TABLE_BYTES = 128u * 1024u;
 constexpr int table_stride(int v) { return v <= 2 ? v : v <= 4 ? 4 : v <= 8 ? 8 : 16; }
 
 template <int V, int VB>
-__global__ __launch_bounds__(AT) void assign_kernel(Vectors first, Vectors last, int last_wgs, const __half *__restrict__ codebook, int stride, int k,
+__global__ __launch_bounds__(AT) void assign_kernel(Vectors first, Vectors last, Padding padding, int last_wgs, const __half *__restrict__ codebook, int stride, int k,
                                                     int bits, int chunk, int seg_len) {
   extern __shared__ __attribute__((aligned(16))) float table[];       // [chunk][TS]: rows padded to 16-byte reads
   constexpr int TS = table_stride(V);
+  clear_padding(padding);
   const bool is_last = (int)blockIdx.x < last_wgs;
   const Vectors a = is_last ? last : first;
   const int segs = (a.per_row + seg_len - 1) / seg_len;
@@ -883,7 +895,7 @@ __global__ __launch_bounds__(AT) void assign_kernel(Vectors first, Vectors last,
 int segment(int bits) { return bits % 4 == 0 ? 8 : bits % 2 == 0 ? 16 : 32; }
 
 template <int V>
-int launch_plain(const Vectors &first, const Vectors &last, const __half *codebook, int k, int bits, hipStream_t s) {
+int launch_plain(const Vectors &first, const Vectors &last, const Padding &padding, const __half *codebook, int k, int bits, hipStream_t s) {
   constexpr int VB = V <= 8 ? 8 : 4;       // vectors a lane holds at once: each centroid read from LDS serves VB x 64 distances
   auto kernel = assign_kernel<V, VB>;
   VQ_ALLOW_FULL_LDS(kernel);
@@ -892,23 +904,23 @@ int launch_plain(const Vectors &first, const Vectors &last, const __half *codebo
   auto wgs = [&](const Vectors &a) { return (items_of(a, seg_len) / seg_len + AT - 1) / AT; };
   const long long blocks = wgs(first) + wgs(last);
   if (blocks > 0x7fffffffLL) return VQ_ERR_UNSUPPORTED;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(AT), (size_t)chunk * table_stride(V) * sizeof(float), s, first, last, (int)wgs(last),
+  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(AT), (size_t)chunk * table_stride(V) * sizeof(float), s, first, last, padding, (int)wgs(last),
                      codebook, V, k, bits, chunk, seg_len);
   return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
 }
 
 template <int V>
-int launch_short(const Vectors &first, const Vectors &last, const __half *codebook, int k, int bits, hipStream_t s) {
+int launch_short(const Vectors &first, const Vectors &last, const Padding &padding, const __half *codebook, int k, int bits, hipStream_t s) {
   const int seg_len = segment(bits);
   const long long last_wgs = (items_of(last, seg_len) + SHORT_THREADS - 1) / SHORT_THREADS;
   const long long blocks = (items_of(first, seg_len) + SHORT_THREADS - 1) / SHORT_THREADS + last_wgs;
   if (blocks > 0x7fffffffLL) return VQ_ERR_UNSUPPORTED;
-  hipLaunchKernelGGL((assign_short_kernel<V>), dim3((unsigned)blocks), dim3(SHORT_THREADS), 0, s, first, last, (int)last_wgs, codebook, V, k, bits, seg_len);
+  hipLaunchKernelGGL((assign_short_kernel<V>), dim3((unsigned)blocks), dim3(SHORT_THREADS), 0, s, first, last, padding, (int)last_wgs, codebook, V, k, bits, seg_len);
   return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
 }
 
 template <int V, bool BASE, int NT, bool SPLIT, bool WIDE, bool CHUNKED>
-int launch_screen_nt(const Vectors &first, const Vectors &last, const __half *codebook, int k, int bits, int split, hipStream_t s) {
+int launch_screen_nt(const Vectors &first, const Vectors &last, const Padding &padding, const __half *codebook, int k, int bits, int split, hipStream_t s) {
   auto kernel = assign_screen_kernel<V, BASE, NT, SPLIT, WIDE, CHUNKED>;
   VQ_ALLOW_FULL_LDS(kernel);
   const int seg_len = segment(bits), block_items = WAVES / split * NT * 32;
@@ -924,41 +936,41 @@ int launch_screen_nt(const Vectors &first, const Vectors &last, const __half *co
     if (items_of(last, seg_len) == 0) last_wgs = 0;
     wgs = min(blocks, cu_count() - last_wgs);
   }
-  hipLaunchKernelGGL(kernel, dim3((unsigned)(wgs + last_wgs)), dim3(WAVES * 64), lds, s, first, last, (int)last_wgs, codebook, V, k, bits, seg_len, split);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(wgs + last_wgs)), dim3(WAVES * 64), lds, s, first, last, padding, (int)last_wgs, codebook, V, k, bits, seg_len, split);
   return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;
 }
 
 template <int V, bool BASE>
-int launch_screen(const Vectors &first, const Vectors &last, const __half *codebook, int k, int bits, hipStream_t s) {
+int launch_screen(const Vectors &first, const Vectors &last, const Padding &padding, const __half *codebook, int k, int bits, hipStream_t s) {
   const long long tiles = (items_of(first, segment(bits)) + items_of(last, segment(bits))) / 32;
   // 64 vectors of a wave share every table read, 32 where that leaves fewer waves idle in the last round (a round of the
   // smaller blocks takes about 0.6 of the time), and with less than one round of those the waves of a workgroup
   // share the table's rows until there is about one
   const long long waves = (long long)cu_count() * WAVES, rounds2 = (tiles + 2 * waves - 1) / (2 * waves), rounds1 = (tiles + waves - 1) / waves;
   if (10 * rounds2 <= 6 * rounds1)
-    return k > SCREEN_ROWS    ? launch_screen_nt<V, BASE, 2, false, true, true>(first, last, codebook, k, bits, 1, s)
-           : k == SCREEN_ROWS ? launch_screen_nt<V, BASE, 2, false, true, false>(first, last, codebook, k, bits, 1, s)
-                              : launch_screen_nt<V, BASE, 2, false, false, false>(first, last, codebook, k, bits, 1, s);
+    return k > SCREEN_ROWS    ? launch_screen_nt<V, BASE, 2, false, true, true>(first, last, padding, codebook, k, bits, 1, s)
+           : k == SCREEN_ROWS ? launch_screen_nt<V, BASE, 2, false, true, false>(first, last, padding, codebook, k, bits, 1, s)
+                              : launch_screen_nt<V, BASE, 2, false, false, false>(first, last, padding, codebook, k, bits, 1, s);
   int split = 1;
   while (split < WAVES && tiles * split * 2 <= waves && split * 128 < min(k, SCREEN_ROWS)) split *= 2;
-  return k > SCREEN_ROWS ? launch_screen_nt<V, BASE, 1, true, false, true>(first, last, codebook, k, bits, split, s)
-                         : launch_screen_nt<V, BASE, 1, true, false, false>(first, last, codebook, k, bits, split, s);
+  return k > SCREEN_ROWS ? launch_screen_nt<V, BASE, 1, true, false, true>(first, last, padding, codebook, k, bits, split, s)
+                         : launch_screen_nt<V, BASE, 1, true, false, false>(first, last, padding, codebook, k, bits, split, s);
 }
 
 template <int V>
-int launch_v(const Vectors &first, const Vectors &last, const __half *codebook, int k, int bits, hipStream_t s) {
+int launch_v(const Vectors &first, const Vectors &last, const Padding &padding, const __half *codebook, int k, int bits, hipStream_t s) {
   // (a table of one or two blocks of 32 is compared as fast as it is screened; 13: three slots for |c|^2 beside the elements)
-  if (k < SHORT_TABLE) return launch_short<V>(first, last, codebook, k, bits, s);
+  if (k < SHORT_TABLE) return launch_short<V>(first, last, padding, codebook, k, bits, s);
   if constexpr (V <= 13) {
-    return first.B ? launch_screen<V, true>(first, last, codebook, k, bits, s) : launch_screen<V, false>(first, last, codebook, k, bits, s);
+    return first.B ? launch_screen<V, true>(first, last, padding, codebook, k, bits, s) : launch_screen<V, false>(first, last, padding, codebook, k, bits, s);
   } else {
-    return launch_plain<V>(first, last, codebook, k, bits, s);
+    return launch_plain<V>(first, last, padding, codebook, k, bits, s);
   }
 }
 
-int launch(int v, const Vectors &first, const Vectors &last, const __half *codebook, int k, int bits, hipStream_t s) {
+int launch(int v, const Vectors &first, const Vectors &last, const Padding &padding, const __half *codebook, int k, int bits, hipStream_t s) {
   switch (v) {
-#define VQ_V(N) case N: return launch_v<N>(first, last, codebook, k, bits, s);
+#define VQ_V(N) case N: return launch_v<N>(first, last, padding, codebook, k, bits, s);
     VQ_V(1) VQ_V(2) VQ_V(3) VQ_V(4) VQ_V(5) VQ_V(6) VQ_V(7) VQ_V(8) VQ_V(9) VQ_V(10) VQ_V(11) VQ_V(12) VQ_V(13) VQ_V(14) VQ_V(15) VQ_V(16)
 #undef VQ_V
     default: return VQ_ERR_UNSUPPORTED;
@@ -968,24 +980,26 @@ int launch(int v, const Vectors &first, const Vectors &last, const __half *codeb
 }  // namespace
 
 int launch_assign(const __half *W, const __half *B, long long ld, int rows, int cols, const __half *codebook, int v, int k,
-                  unsigned char *idx, long long idx_stride, hipStream_t s) {
+                  unsigned char *idx, long long idx_stride, bool clear, hipStream_t s) {
   const int bits = index_bits(k), full = cols / v, len = cols % v;
   const long long at = (long long)full * v, end = (long long)full * bits;
   const Vectors whole = {W, B, ld, v, 1, full ? rows : 0, full, v, idx, idx_stride, len ? end : (end + 31) / 32 * 32, -1};
   // the cut-off last vector of every row, compared over its own elements
   const Vectors last = {W + at, B ? B + at : nullptr, 0, ld, 1, len ? 1 : 0, rows, len, idx, idx_stride, 0, end};
-  return launch(v, whole, last, codebook, k, bits, s);
+  const int used = (int)(((long long)(full + (len ? 1 : 0)) * bits + 31) / 32);
+  return launch(v, whole, last, Padding{idx, idx_stride, rows, used, clear ? (int)(idx_stride / 4) - used : 0}, codebook, k, bits, s);
 }
 
 // Vectors down the columns of W [rows][ld] (Sec. 3.1, Algorithm 1): index streams [ceil(rows / v)][idx_stride], one index per column.
 int launch_assign_down(const __half *W, const __half *B, long long ld, int rows, int cols, const __half *codebook, int v, int k,
-                       unsigned char *idx, long long idx_stride, hipStream_t s) {
+                       unsigned char *idx, long long idx_stride, bool clear, hipStream_t s) {
   const int bits = index_bits(k), full = rows / v, len = rows % v;
   const long long at = (long long)full * v * ld, end = ((long long)cols * bits + 31) / 32 * 32;
   const Vectors whole = {W, B, v * ld, 1, ld, full, cols, v, idx, idx_stride, end, -1};
   // the cut-off last block of rows: one stream of shorter vectors
   const Vectors last = {W + at, B ? B + at : nullptr, 0, 1, ld, len ? 1 : 0, cols, len, idx + (long long)full * idx_stride, idx_stride, end, -1};
-  return launch(v, whole, last, codebook, k, bits, s);
+  const int used = (int)(end / 32);
+  return launch(v, whole, last, Padding{idx, idx_stride, full + (len ? 1 : 0), used, clear ? (int)(idx_stride / 4) - used : 0}, codebook, k, bits, s);
 }
 
 }  // namespace vq

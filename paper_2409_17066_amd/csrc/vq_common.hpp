@@ -75,9 +75,9 @@ int launch_gemv_multi(const Params *ps, int n, const __half *x, long long ldx, i
 int launch_gemm(const Params &p, const __half *X, long long ldx, int tokens, __half *Y, long long ldy,
                 void *workspace, size_t workspace_bytes, hipStream_t s);
 int launch_assign(const __half *W, const __half *B, long long ld, int rows, int cols, const __half *codebook, int v, int k,
-                  unsigned char *idx, long long idx_stride, hipStream_t s);
+                  unsigned char *idx, long long idx_stride, bool clear, hipStream_t s);
 int launch_assign_down(const __half *W, const __half *B, long long ld, int rows, int cols, const __half *codebook, int v, int k,
-                       unsigned char *idx, long long idx_stride, hipStream_t s);
+                       unsigned char *idx, long long idx_stride, bool clear, hipStream_t s);
 // Column order (Sec. 3.2.3): dst[t][c] = src[t][perm[c]] for c < cols (entries outside [0, cols) give zero), dst rows
 // ld_dst halfs apart; and the inverse on a matrix restored in stored order: W[o][perm[c]] = W_stored[o][c], row by row
 // through LDS, in place (VQ_ERR_UNSUPPORTED when a row does not fit LDS).

@@ -250,3 +250,20 @@ def test_assign_of_cut_off_vectors_of_one_element(gpu_lib, v, k, with_base):
         torch.cuda.synchronize()
         want = oracle.assign(W, C, base=B, orientation=orientation)
         assert np.array_equal(idx.cpu().numpy(), s.pack_indices(want, oracle.index_bits(k), idx.shape[1])), (v, k, orientation)
+
+
+@pytest.mark.parametrize("rows,cols,v,k", [(37, 390, 6, 4096), (13, 3, 6, 300), (700, 4096, 6, 256), (19, 77, 2, 16), (9, 200, 16, 300), (21, 130, 8, 65536), (5, 128, 4, 256)])
+@pytest.mark.parametrize("orientation", [0, 1])
+def test_assign_fills_the_whole_stride_of_a_buffer_of_its_own(gpu_lib, rows, cols, v, k, orientation):
+    """Streams of no, one, two and three dwords of padding, cut-off vectors whose dword two launches share, each of the three kernels; the buffer is one
+    that the allocator hands out again."""
+    import torch
+    W = torch.from_numpy(s.to_fp16(s.normal(7300, rows * cols, 0.02)).reshape(rows, cols)).cuda()
+    C = torch.from_numpy(s.to_fp16(s.normal(7301, k * v, 0.02)).reshape(k, v)).cuda()
+    want = gpu_lib.assign(W, C, cols=cols, orientation=orientation).cpu()
+    used = torch.full(want.shape, 0xFF, dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    del used
+    got = gpu_lib.assign(W, C, orientation=orientation)
+    torch.cuda.synchronize()
+    assert torch.equal(got.cpu(), want)
