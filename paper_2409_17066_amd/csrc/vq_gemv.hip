@@ -218,7 +218,8 @@ bool gemv_rows_takes(const Params &p, const __half *x, long long ldx, int batch)
 int gemv_rows_parts(const Params &p);
 size_t gemv_rows_workspace_bytes(const Params &p, int batch);
 int launch_gemv_rows(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, float *part, float *part_xs,
-                     int parts_per_group, hipStream_t s);
+                     int parts_per_group, hipStream_t s, int folds = 0);
+int gemv_rows_folds(const Params &p, int batch, bool parts);
 // When vq_gemv_rows.hip's kernel takes over from the ones that run four (v = 8: eight) rows a launch.  Its lookups do for any number
 // of rows, but a single row needs no matrix cores: from three rows on (two tables of v = 12, 6739 x 9664, 10 rows: 174 -> 22 us;
 // v = 4, 448 x 1872, 3 rows: 7.7 -> 5.5 us; 2 rows: level), and
@@ -586,7 +587,8 @@ static int launch_stored_order(const Params &p, const __half *x, long long ldx, 
   const size_t need = force_generic() ? 0 : stored_order_workspace_bytes(p, x, ldx, batch, least);
   if (rows_wanted(p, batch, workspace != nullptr) && gemv_rows_takes(p, x, ldx, batch)) {
     const int per_group = workspace && workspace_bytes >= gemv_rows_workspace_bytes(p, batch) ? gemv_rows_parts(p) : 0, parts = per_group * p.n_groups;
-    if (parts == 0) return launch_gemv_rows(p, x, ldx, batch, y, ldy, nullptr, nullptr, 0, s);
+    const int folds = parts ? gemv_rows_folds(p, batch, true) : 0;
+    if (parts == 0 || folds > 1) return launch_gemv_rows(p, x, ldx, batch, y, ldy, nullptr, nullptr, 0, s, folds);
     float *part = static_cast<float *>(workspace), *part_xs = part + (size_t)parts * (size_t)batch * (size_t)p.out_features;
     const int rc = launch_gemv_rows(p, x, ldx, batch, nullptr, 0, part, part_xs, per_group, s);
     return rc == VQ_OK ? launch_groups_finish(part, part_xs, parts, batch, p, y, ldy, s) : rc;

@@ -58,7 +58,10 @@ template <int N, class F> __device__ __forceinline__ void for_each(F &&f) { for_
 
 constexpr int acc_units(int v, bool down, int rb) { return down ? v : rb; }
 
-template <int V, int BITS, bool DOWN, int RB, int RW, bool PERM>
+// LOG_FOLDS: rows of operand A and columns of operand B are (stream, fold) and (batch row, fold) pairs, a block has 8 or 4 streams and their columns come in
+// two or four folds, step s of a fold being step s * folds + fold of the stream.  Of a result what has the same fold on both sides counts; the folds' sums
+// are added with the waves'.  For layers of few blocks and up to eight (four) batch rows, in one launch (see rows_folds).
+template <int V, int BITS, bool DOWN, int RB, int RW, bool PERM, int LOG_FOLDS>
 __global__ __launch_bounds__(RW * 64, 4) void gemv_rows_kernel(Params p, RowsArgs a) {
   constexpr bool GLOBAL = BITS == 16;
   constexpr int ND = BITS / 4, VD = V / 2, ED = entry_halfs(V) / 2, NU = acc_units(V, DOWN, RB);
@@ -66,7 +69,10 @@ __global__ __launch_bounds__(RW * 64, 4) void gemv_rows_kernel(Params p, RowsArg
   constexpr bool AHEAD = DOWN || V * (RB + 1) <= 15;      // whether the registers hold two steps' activations
   constexpr int EPC = V == 8 ? 1 : V == 12 ? 2 : V == 4 ? 2 : 4, HPC = EPC * V / 8;      // entries and operands of a piece of a window
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  const int lane = threadIdx.x & 63, slot = lane & 15, g = lane >> 4;
+  constexpr int FOLDS = 1 << LOG_FOLDS, STREAMS = 16 / FOLDS, WIDTH = STEP * FOLDS;      // (positions of a step)
+  static_assert(FOLDS == 1 || RB == 1, "one block where there are few");
+  const int lane = threadIdx.x & 63, slot = (lane & 15) % STREAMS, g = lane >> 4;
+  const int lead = (lane & 15) / STREAMS * STEP + 8 * g;      // the lane's first position in a step
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int blk0 = (int)(blockIdx.x % (unsigned)a.row_wgs) * RB, part = (int)(blockIdx.x / (unsigned)a.row_wgs);
   const bool parts = a.parts_per_group != 0;
@@ -77,7 +83,7 @@ __global__ __launch_bounds__(RW * 64, 4) void gemv_rows_kernel(Params p, RowsArg
   for (int i = 0; i < NU; ++i) acc[i] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
   int stream[RB];
 #pragma unroll
-  for (int i = 0; i < RB; ++i) stream[i] = min((blk0 + i) * 16 + slot, p.S - 1);
+  for (int i = 0; i < RB; ++i) stream[i] = min((blk0 + i) * STREAMS + slot, p.S - 1);
 
   // Eight activations from stored column c (even) on; past a row's end they may be the next row's, past the last one's zeros:
   // cut() clears those from `limit` on.
@@ -103,7 +109,7 @@ __global__ __launch_bounds__(RW * 64, 4) void gemv_rows_kernel(Params p, RowsArg
 
   const int group_lo = parts ? part / a.parts_per_group : 0, group_hi = parts ? group_lo + 1 : p.n_groups;
   for (int group = group_lo; group < group_hi; ++group) {
-    const int pos0 = group * p.Pg, pos_end = min(p.P, pos0 + p.Pg), steps = (pos_end - pos0 + STEP - 1) / STEP;
+    const int pos0 = group * p.Pg, pos_end = min(p.P, pos0 + p.Pg), steps = (pos_end - pos0 + WIDTH - 1) / WIDTH;
     int step_lo = 0, step_hi = steps;
     if (parts) {
       const int sub = part - group * a.parts_per_group;
@@ -119,14 +125,14 @@ __global__ __launch_bounds__(RW * 64, 4) void gemv_rows_kernel(Params p, RowsArg
       // (past a row's end: the next row's indices, or zeros; those vectors do not count)
       const __amdgpu_buffer_rsrc_t r_i = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(idx), 0, (unsigned)((long long)p.S * stride), 0x00020000);
       auto load_window = [&](unsigned (&w)[ND], int i, int s) {
-        const unsigned at = (unsigned)stream[i] * (unsigned)stride + (unsigned)((pos0 + s * STEP + 8 * g) >> 3) * BITS;
+        const unsigned at = (unsigned)stream[i] * (unsigned)stride + (unsigned)((pos0 + s * WIDTH + lead) >> 3) * BITS;
         load_dwords<ND>(w, r_i, at);
       };
       auto is_last = [&](int s) {
-        return pos0 + (s + 1) * STEP > pos_end || (!DOWN && p.n_out + (long long)(pos0 + (s + 1) * STEP) * V > p.in_features);
+        return pos0 + (s + 1) * WIDTH > pos_end || (!DOWN && p.n_out + (long long)(pos0 + (s + 1) * WIDTH) * V > p.in_features);
       };
       auto load_step_x = [&](auto &xw, int s) {
-        const int pos = pos0 + s * STEP + 8 * g;
+        const int pos = pos0 + s * WIDTH + lead;
 #pragma unroll
         for (int h = 0; h < NX; ++h) xw[h] = load_x(p.n_out + (DOWN ? pos : pos * V + 8 * h));
       };
@@ -165,7 +171,7 @@ __global__ __launch_bounds__(RW * 64, 4) void gemv_rows_kernel(Params p, RowsArg
 #pragma unroll
           for (int i = 0; i < RB; ++i) load_window(far[i], i, s2);
         }
-        const int pos = pos0 + s * STEP + 8 * g;
+        const int pos = pos0 + s * WIDTH + lead;
         const bool last = is_last(s);
         if (AHEAD && last)
 #pragma unroll
@@ -272,8 +278,8 @@ __global__ __launch_bounds__(RW * 64, 4) void gemv_rows_kernel(Params p, RowsArg
 
   // ---- outlier columns (vectors of four, a table of up to 64 K entries): looked up through the caches
   if (p.Q && (!parts || part == 0)) {
-    for (int c0 = wave * 32; c0 < p.n_out; c0 += RW * 32) {
-      const int c = c0 + 8 * g;
+    for (int c0 = wave * WIDTH; c0 < p.n_out; c0 += RW * WIDTH) {
+      const int c = c0 + lead;
       const half8 xo = operand(cut(load_x(c), p.n_out - c));
       if (want_xs) xacc = product(ones, xo, xacc);
       if constexpr (DOWN) {
@@ -314,12 +320,14 @@ __global__ __launch_bounds__(RW * 64, 4) void gemv_rows_kernel(Params p, RowsArg
   // ---- the waves' sums, in wave order: [wave][unit][lane][4] in LDS, a unit for every 256 threads at a time; sum(x) first
   float *red = reinterpret_cast<float *>(lds);
   float xs = 0.0f;
-  const int column = (threadIdx.x & 255) >> 2 & 15;      // the batch row of the sum that this thread adds up
+  const int column = ((threadIdx.x & 255) >> 2 & 15) % STREAMS;      // the batch row of the sum that this thread adds up
   if (want_xs) {
     __syncthreads();
     if (lane < 16) red[wave * 16 + lane] = xacc[0];
     __syncthreads();
-    for (int w = 0; w < RW; ++w) xs += red[w * 16 + column];
+    for (int w = 0; w < RW; ++w)
+#pragma unroll
+      for (int f = 0; f < FOLDS; ++f) xs += red[w * 16 + f * STREAMS + column];
     if (parts && threadIdx.x < 16) {
       float sum = 0.0f;
       for (int w = 0; w < RW; ++w) sum += red[w * 16 + threadIdx.x];
@@ -336,12 +344,15 @@ __global__ __launch_bounds__(RW * 64, 4) void gemv_rows_kernel(Params p, RowsArg
     for (int u = 0; u < units; ++u) *reinterpret_cast<float4v *>(lds + (unsigned)(wave * units + u) * UNIT + (unsigned)lane * 16u) = acc[u0 + u];
     __syncthreads();
     const int u = threadIdx.x >> 8, e = threadIdx.x & 255;
-    if (u < units && column < a.batch) {
+    const bool first_fold = FOLDS == 1 || ((e >> 2 & 15) < STREAMS && 4 * (e >> 6) < STREAMS);
+    if (u < units && column < a.batch && first_fold) {
       float sum = 0.0f;
 #pragma unroll
-      for (int w = 0; w < RW; ++w) sum += red[(w * units + u) * 256 + e];
+      for (int w = 0; w < RW; ++w)
+#pragma unroll
+        for (int f = 0; f < FOLDS; ++f) sum += red[(w * units + u) * 256 + e + f * (20 * STREAMS)];      // (a fold is 5 STREAMS lanes behind the one before)
       const int row = 4 * (e >> 6) + (e & 3);              // e = 4 lane + r: result row 4 (lane >> 4) + r, column lane & 15
-      const int str = (blk0 + (DOWN ? 0 : u0 + u)) * 16 + row, o = DOWN ? str * V + u0 + u : str;
+      const int str = (blk0 + (DOWN ? 0 : u0 + u)) * STREAMS + row, o = DOWN ? str * V + u0 + u : str;
       if (str < p.S && o < p.out_features) {
         if (parts) {
           a.part[((long long)part * a.batch + column) * p.out_features + o] = sum;
@@ -378,10 +389,10 @@ Split rows_split(const Params &p) {
   return t;
 }
 
-template <int V, int BITS, bool DOWN, int RB, int RW, bool PERM = false>
+template <int V, int BITS, bool DOWN, int RB, int RW, bool PERM = false, int LOG_FOLDS = 0>
 int launch_one(const Params &p, const RowsArgs &a, hipStream_t s) {
-  if constexpr (V == 12 && !PERM) if (p.perm) return launch_one<V, BITS, DOWN, RB, RW, true>(p, a, s);
-  auto kernel = gemv_rows_kernel<V, BITS, DOWN, RB, RW, PERM>;
+  if constexpr (V == 12 && !PERM && LOG_FOLDS == 0) if (p.perm) return launch_one<V, BITS, DOWN, RB, RW, true>(p, a, s);
+  auto kernel = gemv_rows_kernel<V, BITS, DOWN, RB, RW, PERM, LOG_FOLDS>;
   VQ_ALLOW_FULL_LDS(kernel);
   constexpr int NU = acc_units(V, DOWN, RB), AT_ONCE = RW / 4;
   const unsigned sums = RW * (NU < AT_ONCE ? NU : AT_ONCE) * UNIT;
@@ -392,7 +403,11 @@ int launch_one(const Params &p, const RowsArgs &a, hipStream_t s) {
 }
 
 template <int V, int BITS>
-int launch_pair(const Params &p, const RowsArgs &a, const Split &t, hipStream_t s) {
+int launch_pair(const Params &p, const RowsArgs &a, const Split &t, int folds, hipStream_t s) {
+  if constexpr (V == 8 ? BITS == 16 : V == 4 || V == 6 ? BITS == 8 : true) {
+    if (folds == 4) return p.orientation == 1 ? launch_one<V, BITS, true, 1, 16, false, 2>(p, a, s) : launch_one<V, BITS, false, 1, 16, false, 2>(p, a, s);
+    if (folds == 2) return p.orientation == 1 ? launch_one<V, BITS, true, 1, 16, false, 1>(p, a, s) : launch_one<V, BITS, false, 1, 16, false, 1>(p, a, s);
+  }
   constexpr bool TWO = BITS == 16 || V * (1 << BITS) * 2 < 80 * 1024;      // (pairs that never run eight waves need no such kernel)
   if (p.orientation == 1) {
     if constexpr (TWO) if (t.rw == 8) return launch_one<V, BITS, true, 1, 8>(p, a, s);
@@ -444,18 +459,53 @@ int gemv_rows_parts(const Params &p) {
   return parts < 1 ? 1 : parts;
 }
 
+// Folds of the columns (LOG_FOLDS) that up to eight rows take in one launch; `parts`: in place of column parts.  A fold has half or a quarter of the steps
+// and costs a start 0.3 or 1 us, so: not for the fewest steps, nor where the blocks are more than compute units then (two rounds: 4096 x 4096,
+// v = 4, 8.1 -> 12.2 us).  Of 15 shapes (306 to 10944 columns) with each of five settings, four and eight rows, in us without and with two / four folds: vectors
+// down the outputs, v = 8 / 65536, 1024 x 1024 12.9, 9.7 / 8.9, v = 12 with two tables 14.5, 12.0 / 12.3, v = 6 / 256 of 32 steps 7.5, 7.0 / 7.2, of 128 12.2, 9.5 / 9.2;
+// along the rows, where operand B's loads grow with the folds, 1000 x 8000 14.0, 11.8 / 12.4, 14.9, 12.8 / 13.0, v = 4 9.3, 8.0 / 8.7, v = 2 10.3, 7.8 / 8.1,
+// v = 6 eight rows 10.7, 11.0.  Parts have a second launch, but as many as there are compute units for: 4096 x 4096 down the outputs, v = 2, two parts
+// 9.5, folds 7.5, v = 4, four parts 9.0, 8.1, v = 8 / 65536, eight parts 16.4, 17.9.  Settings that were not measured keep to one.
+int gemv_rows_folds(const Params &p, int batch, bool parts) {
+  const bool measured = p.v == 12 ? p.k_res != 0 : !p.k_res && (p.v == 8 ? p.bits == 16 : p.v == 4 || p.v == 6 ? p.bits == 8 : p.v == 2);
+  if (!measured || p.n_groups > 1 || p.perm || batch > 8) return 1;
+  const int steps = (p.P + STEP - 1) / STEP, blocks4 = (int)(((long long)p.S * 4 + 15) / 16);
+  const bool room = blocks4 <= cu_count(), four = room && batch <= 4;
+  if (((long long)p.S * 2 + 15) / 16 > cu_count()) return 1;
+  constexpr int NONE = 1 << 30;
+  int from2, from4, to2 = NONE, to4 = NONE;                // steps
+  if (p.orientation == 1) {
+    from2 = p.v >= 8 ? 10 : 17;
+    from4 = p.v == 8 ? 24 : p.v == 12 ? 48 : 112;
+    if (parts) {
+      if (p.v >= 8) return 1;
+      if (room) to2 = p.v == 2 ? 160 : p.v == 4 ? 120 : 115;      // (else there are four parts at most)
+      to4 = p.v == 6 ? 200 : 350;                          // (v = 4, 1216 x 18816, 588 steps: parts 10.8, folds 13.6)
+    }
+  } else {
+    from2 = p.v == 8 ? 12 : p.v == 12 ? 8 : p.v == 4 ? (batch > 4 ? 40 : 24) : p.v == 2 ? 14 : batch > 4 ? NONE : 18;
+    from4 = p.v == 12 ? 24 : p.v == 8 ? 36 : NONE;
+    if (parts) {
+      if (batch > 4 || (p.v != 2 && p.v != 8)) return 1;
+      if (p.v == 8) from2 = NONE;
+    }
+  }
+  return four && steps >= from4 && steps <= to4 ? 4 : steps >= from2 && steps <= to2 ? 2 : 1;
+}
+
 size_t gemv_rows_workspace_bytes(const Params &p, int batch) {
   const size_t parts = (size_t)gemv_rows_parts(p) * (size_t)p.n_groups;
   return (parts * ((size_t)batch * (size_t)p.out_features + 16) * sizeof(float) + 255) / 256 * 256;
 }
 
-// parts_per_group = 0: y complete.  Else the parts' sums into part [n_groups * parts_per_group][batch][out_features] and part_xs
+// parts_per_group = 0: y complete, in `folds` folds (0: gemv_rows_folds says).  Else the parts' sums into part [n_groups * parts_per_group][batch][out_features] and part_xs
 // [..][16], for launch_groups_finish.
 int launch_gemv_rows(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, float *part, float *part_xs,
-                     int parts_per_group, hipStream_t s) {
+                     int parts_per_group, hipStream_t s, int folds) {
   const Split t = rows_split(p);
-  RowsArgs a = {x, ldx, batch, y, ldy, part, part_xs, t.wgs, parts_per_group};
-#define VQ_PAIR(V, BITS) if (p.v == V && p.bits == BITS) return launch_pair<V, BITS>(p, a, t, s);
+  if (!folds) folds = parts_per_group ? 1 : gemv_rows_folds(p, batch, false);
+  RowsArgs a = {x, ldx, batch, y, ldy, part, part_xs, folds > 1 ? (int)(((long long)p.S * folds + 15) / 16) : t.wgs, parts_per_group};
+#define VQ_PAIR(V, BITS) if (p.v == V && p.bits == BITS) return launch_pair<V, BITS>(p, a, t, folds, s);
   VQ_PAIR(2, 4) VQ_PAIR(4, 8) VQ_PAIR(6, 8) VQ_PAIR(8, 8) VQ_PAIR(4, 12) VQ_PAIR(8, 12) VQ_PAIR(12, 12) VQ_PAIR(8, 16)
 #undef VQ_PAIR
   return VQ_ERR_UNSUPPORTED;

@@ -1283,3 +1283,29 @@ def test_gemv_down_folds(gpu_lib, monkeypatch, out_features, in_features, more, 
         assert not torch.isfinite(one[:, 6:12]).any()
         _check_matmul(one[:, rows], ref, what)
     _check_matmul(yb, oracle.gemv(second, x_np), "second of two")
+
+
+@pytest.mark.parametrize("out_features,in_features,v,k,more,orientation,batch", [
+    (700, 900, 8, 65536, {}, 1, 3), (701, 333, 8, 65536, {}, 1, 8), (130, 10001, 8, 65536, {}, 0, 4), (1001, 3205, 8, 65536, {}, 0, 7),
+    (301, 1700, 12, 4096, dict(k_res=4096), 1, 4), (301, 505, 12, 4096, dict(k_res=4096, n_outlier_cols=24, v_out=4, k_out=4096), 1, 6),
+    (77, 9509, 12, 4096, dict(k_res=4096), 0, 2), (900, 3300, 12, 4096, dict(k_res=4096, n_outlier_cols=40, v_out=4, k_out=4096), 0, 5),
+    (131, 4099, 4, 256, {}, 1, 4), (2003, 700, 4, 256, {}, 1, 8), (130, 3209, 4, 256, {}, 0, 4), (1003, 6001, 4, 256, {}, 0, 8),
+    (515, 3900, 2, 16, {}, 1, 1), (3001, 1001, 2, 16, {}, 1, 8), (333, 1035, 2, 16, {}, 0, 3),
+    (131, 4099, 6, 256, {}, 1, 4), (131, 777, 6, 256, {}, 1, 8), (1002, 3461, 6, 256, {}, 0, 4),
+])
+def test_gemv_rows_folds(gpu_lib, monkeypatch, out_features, in_features, v, k, more, orientation, batch):
+    """Two and four folds of the columns, with and without a workspace: short last blocks, folds that lie past the columns, outlier columns of several folds,
+    rows followed by what is no number."""
+    import torch
+    monkeypatch.setenv("VQ_SWITCHES", "rows=1")
+    L = s.make_layer(325, "folds", out_features, in_features, v, k, orientation=orientation, **more)
+    pitch = (in_features + 7) // 8 * 8 + 8
+    x_np = s.make_activations(325, L, batch)
+    x = torch.full((batch, pitch), float("nan"), dtype=torch.float16, device="cuda")
+    x[:, :in_features] = torch.from_numpy(x_np)
+    dl = gpu_lib.DeviceLayer(L)
+    ref = oracle.gemv(L, x_np)
+    for workspace in (torch.empty(0, dtype=torch.uint8, device="cuda"), "fast"):
+        y = gpu_lib.gemv(dl, x[:, :in_features], workspace=workspace)
+        torch.cuda.synchronize()
+        _check_matmul(y, ref, "workspace %s" % (workspace if isinstance(workspace, str) else None))
