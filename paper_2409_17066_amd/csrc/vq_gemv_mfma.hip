@@ -709,9 +709,13 @@ bool few_rows(const Params &p, int batch, int nb) { return nb >= 2 && p.in_featu
 // two 12 rows 8.66 / 8.60, 16 rows 9.42 / 8.69; three 13 rows 9.49 / 9.61, 14 9.71 / 9.63, 16 10.15 / 9.71.  With residual lookups as many accesses
 // again are left to LDS: one block 14 rows 9.49 / 9.46 (1000 outputs 8.89 / 9.08), 16 9.96 / 9.50, of 11008 columns 12 rows 15.25 / 15.12, 16 17.12 /
 // 15.10; two 16 rows 13.40 / 13.70; from a 256-entry table, one block 14 rows 8.78 / 8.28.
+// Not in rows of so few vectors that a wave has a pass or less of them, whose start then waits for LDS: 704 x 928, sixteen rows, no residual table 4.54 / 4.94,
+// 4096 entries 5.99 / 6.35, 256 5.64 / 5.85; 2048 columns, 4096 outputs, 13 rows 5.70 / 5.83, sixteen 6.03 / 5.84, with 4096 residual entries 7.42 / 7.62, with 256
+// 7.69 / 7.28; 3072 columns 8.96 / 8.65.
 bool stages(const Params &p, int batch, int nb) {
-  if (!p.k_res) return nb <= 5 && batch >= 11 + nb;
-  return nb == 1 && batch >= (p.bits_res == 8 ? 13 : p.P >= 1500 ? 12 : 15);
+  if (p.P < 256) return false;
+  if (!p.k_res) return nb <= 5 && batch >= max(p.P < 500 ? 15 : 0, 11 + nb);
+  return nb == 1 && batch >= (p.bits_res == 8 ? 13 : p.P >= 1500 ? 12 : 15) && (p.bits_res == 8 || p.P >= 500);
 }
 
 }  // namespace
