@@ -279,7 +279,7 @@ __device__ __forceinline__ void gemv_down_mfma_body(const Params &p, const DownM
           lds_gather_wait();
 #pragma unroll
           for (int u = 0; u < VPL; ++u) { settle(e[u]); if (RES_BITS) settle(f[u]); }
-          if (w == windows - 1) {                          // (the entries too: past a stream's end lie the next one's indices, whose entries need not be finite)
+          if (FOLDS > 1 && w == windows - 1) {             // (the entries too: past a stream's end a fold reads the next one's indices, whose entries need not be finite)
             const int left = pos_hi - pos_lo - ((w * FOLDS + fold) * 32 + g * 8);
 #pragma unroll
             for (int u = 0; u < VPL; ++u)

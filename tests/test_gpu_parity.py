@@ -1256,7 +1256,7 @@ def test_gemv_activations_through_lds_and_short_blocks(gpu_lib, out_features, in
 
 @pytest.mark.parametrize("out_features,in_features,more,batch", [
     (37, 1300, {}, 4), (1501, 2018, {}, 3), (3001, 1030, dict(k_res=4096), 4), (95, 1282, dict(k_res=256), 1), (49, 2000, dict(k_res=4096, n_outlier_cols=24, v_out=4, k_out=4096), 2),
-    (3100, 1170, {}, 8), (9605, 1300, {}, 2), (9700, 1160, dict(k_res=4096), 5), (71, 1345, dict(k_res=256, n_outlier_cols=10, v_out=4, k_out=4096), 7),
+    (3100, 1500, {}, 8), (9605, 1300, {}, 2), (9700, 1160, dict(k_res=4096), 5), (71, 1345, dict(k_res=256, n_outlier_cols=10, v_out=4, k_out=4096), 7),
 ])
 def test_gemv_down_folds(gpu_lib, monkeypatch, out_features, in_features, more, batch):
     """Vectors down the outputs, two and four folds of the columns in one instruction: blocks of eight and four streams, the last one short, and windows of
