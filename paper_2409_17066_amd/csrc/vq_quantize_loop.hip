@@ -647,7 +647,7 @@ __global__ __launch_bounds__(LOOP_THREADS) void qcol_loop_kernel(LoopArgs a) {
       float4v acc[2][RG];
       float2v hv[FAR];
       float4v ev[FAR / 4];
-      // (a lane whose pair ends past the matrix computes the last pair once more)
+      // (the sums of a pair that ends past the matrix are those of the last pair)
       auto far_offset = [&] { return min(s_end + fg * 128 + 2 * lane, max(a.cols - 2, 0)) * 4; };
       auto far_loads = [&] {
         const int off = far_offset();
@@ -675,23 +675,33 @@ __global__ __launch_bounds__(LOOP_THREADS) void qcol_loop_kernel(LoopArgs a) {
           }
         fk += FAR;
         if (fk < a.block) return;
-        if (s_end + fg * 128 + 2 * lane < a.cols) {
-          const int off = far_offset();
-          float2v fw[NP * VP];
-#pragma unroll
-          for (int r = 0; r < NP * VP; ++r) fw[r] = __builtin_bit_cast(float2v, __builtin_amdgcn_raw_buffer_load_b64(rows_of_W, off, row_of_W(r / VP, r % VP), 0));
-          auto store = [&](int r) {
-            const float2v y = {fw[r].x - acc[0][r / 4][r % 4], fw[r].y - acc[1][r / 4][r % 4]};
-            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uint2v, y), rows_of_W, off, row_of_W(r / VP, r % VP), 0);
-          };
+        // (a column has one owner, as the groups are other waves' or later turns: a lane whose pair begins at the last column stores that one alone)
+        const int at = s_end + fg * 128 + 2 * lane;
+        auto each_row = [&](auto row) {
           if (len == VP) {
 #pragma unroll
-            for (int r = 0; r < NP * VP; ++r) store(r);
+            for (int r = 0; r < NP * VP; ++r) row(r);
           } else {
 #pragma unroll
             for (int r = 0; r < NP * VP; ++r)
-              if (r % VP < len) store(r);
+              if (r % VP < len) row(r);
           }
+        };
+        if (at < a.cols - 1) {
+          float2v fw[NP * VP];
+#pragma unroll
+          for (int r = 0; r < NP * VP; ++r) fw[r] = __builtin_bit_cast(float2v, __builtin_amdgcn_raw_buffer_load_b64(rows_of_W, at * 4, row_of_W(r / VP, r % VP), 0));
+          each_row([&](int r) {
+            const float2v y = {fw[r].x - acc[0][r / 4][r % 4], fw[r].y - acc[1][r / 4][r % 4]};
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uint2v, y), rows_of_W, at * 4, row_of_W(r / VP, r % VP), 0);
+          });
+        } else if (at < a.cols) {                          // (its sums are the second of the pair that far_offset moved back)
+          float fw[NP * VP];
+#pragma unroll
+          for (int r = 0; r < NP * VP; ++r) fw[r] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rows_of_W, at * 4, row_of_W(r / VP, r % VP), 0));
+          each_row([&](int r) {
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(fw[r] - acc[1][r / 4][r % 4]), rows_of_W, at * 4, row_of_W(r / VP, r % VP), 0);
+          });
         }
         far_clear();
         fg += KEEP; fk = 0;

@@ -220,6 +220,41 @@ def test_quantize_columns_later_columns(gpu_lib, name):
     assert np.array_equal(replay["What"], Wd.cpu().numpy().astype(np.float64))
 
 
+# Later columns of which a whole number of 128s and one are left, which is the first of a group of 128: it once went with the last of the group before,
+# another wave's (385, 513, 641 of the block's end) or a later turn's (769, 1025, 833); one left alone (257); and more of them than a block has columns for
+# steps, whose rest follows at its end (4481).
+ONE_MORE = {
+    "left_alone": dict(M=13, N=257, v=6, k=64, k_res=0, B=128),
+    "another_wave": dict(M=13, N=641, v=6, k=64, k_res=0, B=128),
+    "later_turn": dict(M=13, N=769, v=6, k=64, k_res=16, B=128),
+    "two_turns_v4_two_positions": dict(M=1603, N=1025, v=4, k=16, k_res=0, B=128),
+    "blocks_of_64": dict(M=19, N=833, v=8, k=16, k_res=0, B=64),
+    "blocks_of_8": dict(M=7, N=1553, v=6, k=16, k_res=0, B=8),
+    "rest_at_the_end": dict(M=7, N=4481, v=6, k=16, k_res=0, B=128),
+}
+
+
+@pytest.mark.parametrize("name", list(ONE_MORE))
+def test_quantize_columns_one_more_than_whole_groups(gpu_lib, name):
+    import torch
+    case = ONE_MORE[name]
+    M, N, v, k, k_res, B = (case[n] for n in ("M", "N", "v", "k", "k_res", "B"))
+    seed = 190 + list(ONE_MORE).index(name)
+    W0 = s.make_weights(600 + seed, M, N)
+    U = np.triu(np.random.default_rng(seed).standard_normal((N, N), dtype=np.float32) * np.float32(0.02), 1) + np.eye(N, dtype=np.float32)
+    C, R = _tables(seed, k, v, k_res)
+    Wd = torch.from_numpy(W0.astype(np.float32)).cuda()
+    idx_b, idx_res_b, T = gpu_lib.quantize_columns(Wd, torch.from_numpy(U).cuda(), torch.from_numpy(C).cuda(),
+                                                   torch.from_numpy(R).cuda() if k_res else None, block=B)
+    torch.cuda.synchronize()
+    idx = _unpack(idx_b.cpu().numpy(), oracle.index_bits(k), N)
+    idx_res = _unpack(idx_res_b.cpu().numpy(), oracle.index_bits(k_res), N) if k_res else None
+    replay = oracle.quantize_columns(W0, U, C, R, block=B, given=(idx, idx_res))
+    rms = np.sqrt((W0 ** 2).mean())
+    assert np.abs(replay["T"] - T.cpu().numpy().astype(np.float64)).max() <= TOL_T * rms
+    assert np.array_equal(replay["What"], Wd.cpu().numpy().astype(np.float64))
+
+
 def _tight_tables(seed, case):
     C, R = _tables(seed, case["k"], case["v"], case["k_res"])
     for T in (C, R):
