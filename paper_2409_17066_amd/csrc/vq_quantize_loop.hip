@@ -707,7 +707,7 @@ __global__ __launch_bounds__(LOOP_THREADS) void qcol_loop_kernel(LoopArgs a) {
         fg += KEEP; fk = 0;
       };
       far_clear();
-      far_loads();
+      far_loads();                                           // (ahead of the barrier: columns 0 .. FAR - 1 of E, which has 2 FAR at least)
       constexpr int RING = 2;
       float row[RING];
       // (columns past the matrix are its last one, whose weights are not in use here)
@@ -774,7 +774,9 @@ int launch_loop(LoopArgs a, hipStream_t st) {
 // Groups of 64 centroids a search wave holds of each table: one up to 256 entries, four up to 1024, sixteen up to 4096.
 template <int VP>
 int launch_loop_vp(LoopArgs a, hipStream_t st) {
-  a.block = (a.block + FAR - 1) / FAR * FAR;
+  // (whole steps of the later update, and two of them at least: its first one is read ahead of a block's first barrier, when the last two columns of
+  // the block before may still be on their way into E)
+  a.block = max(2 * FAR, (a.block + FAR - 1) / FAR * FAR);
   // (the block decides no more than where sums are split: where two large tables leave too little LDS for E, a smaller one)
   while (loop_lds_bytes<VP>(a.k, a.k_res, a.block) > 160 * 1024 && a.block > 64) a.block -= 16;
   if (loop_lds_bytes<VP>(a.k, a.k_res, a.block) > 160 * 1024 || a.ldh > (1 << 21) || a.ldw > (1 << 22) || a.ldt > (1 << 22)) return VQ_ERR_UNSUPPORTED;    // (a block of H^-1, the rows of a workgroup: 32-bit offsets)

@@ -233,13 +233,20 @@ ONE_MORE = {
     "rest_at_the_end": dict(M=7, N=4481, v=6, k=16, k_res=0, B=128),
 }
 
+# Blocks of up to eight columns: all four keeping waves have a step of the later update in every block.
+SHORTEST = {
+    "one_column": dict(M=25, N=1100, v=6, k=16, k_res=0, B=1),
+    "seven": dict(M=25, N=1101, v=6, k=64, k_res=16, B=7),
+    "eight_two_positions": dict(M=1603, N=700, v=4, k=16, k_res=0, B=8),
+}
 
-@pytest.mark.parametrize("name", list(ONE_MORE))
+
+@pytest.mark.parametrize("name", list(ONE_MORE) + list(SHORTEST))
 def test_quantize_columns_one_more_than_whole_groups(gpu_lib, name):
     import torch
-    case = ONE_MORE[name]
+    case = {**ONE_MORE, **SHORTEST}[name]
     M, N, v, k, k_res, B = (case[n] for n in ("M", "N", "v", "k", "k_res", "B"))
-    seed = 190 + list(ONE_MORE).index(name)
+    seed = 190 + (list(ONE_MORE) + list(SHORTEST)).index(name)
     W0 = s.make_weights(600 + seed, M, N)
     U = np.triu(np.random.default_rng(seed).standard_normal((N, N), dtype=np.float32) * np.float32(0.02), 1) + np.eye(N, dtype=np.float32)
     C, R = _tables(seed, k, v, k_res)
