@@ -675,33 +675,30 @@ __global__ __launch_bounds__(LOOP_THREADS) void qcol_loop_kernel(LoopArgs a) {
           }
         fk += FAR;
         if (fk < a.block) return;
-        // (a column has one owner, as the groups are other waves' or later turns: a lane whose pair begins at the last column stores that one alone)
         const int at = s_end + fg * 128 + 2 * lane;
-        auto each_row = [&](auto row) {
-          if (len == VP) {
+        if (at < a.cols) {
+          // (a column has one owner, as the groups are other waves' or later turns: of the last pair moved back, which begins at another lane's column,
+          // the second column alone is stored, and the first is loaded and dropped.  Branches of their own for pairs and the last column, loads and
+          // stores, 1 % slower: 4096 x 4096, v = 6, k = 4096 4108 against 4027 us)
+          const int off = far_offset(), to = at < a.cols - 1 ? off : 0x7FFFFFFF;
+          auto each_row = [&](auto row) {
+            if (len == VP) {
 #pragma unroll
-            for (int r = 0; r < NP * VP; ++r) row(r);
-          } else {
+              for (int r = 0; r < NP * VP; ++r) row(r);
+            } else {
 #pragma unroll
-            for (int r = 0; r < NP * VP; ++r)
-              if (r % VP < len) row(r);
-          }
-        };
-        if (at < a.cols - 1) {
+              for (int r = 0; r < NP * VP; ++r)
+                if (r % VP < len) row(r);
+            }
+          };
           float2v fw[NP * VP];
 #pragma unroll
-          for (int r = 0; r < NP * VP; ++r) fw[r] = __builtin_bit_cast(float2v, __builtin_amdgcn_raw_buffer_load_b64(rows_of_W, at * 4, row_of_W(r / VP, r % VP), 0));
+          for (int r = 0; r < NP * VP; ++r) fw[r] = __builtin_bit_cast(float2v, __builtin_amdgcn_raw_buffer_load_b64(rows_of_W, off, row_of_W(r / VP, r % VP), 0));
           each_row([&](int r) {
-            const float2v y = {fw[r].x - acc[0][r / 4][r % 4], fw[r].y - acc[1][r / 4][r % 4]};
-            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uint2v, y), rows_of_W, at * 4, row_of_W(r / VP, r % VP), 0);
+            fw[r] = float2v{fw[r].x - acc[0][r / 4][r % 4], fw[r].y - acc[1][r / 4][r % 4]};
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uint2v, fw[r]), rows_of_W, to, row_of_W(r / VP, r % VP), 0);
           });
-        } else if (at < a.cols) {                          // (its sums are the second of the pair that far_offset moved back)
-          float fw[NP * VP];
-#pragma unroll
-          for (int r = 0; r < NP * VP; ++r) fw[r] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rows_of_W, at * 4, row_of_W(r / VP, r % VP), 0));
-          each_row([&](int r) {
-            __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(fw[r] - acc[1][r / 4][r % 4]), rows_of_W, at * 4, row_of_W(r / VP, r % VP), 0);
-          });
+          if (at == a.cols - 1) each_row([&](int r) { __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(fw[r].y), rows_of_W, at * 4, row_of_W(r / VP, r % VP), 0); });
         }
         far_clear();
         fg += KEEP; fk = 0;
