@@ -11,6 +11,7 @@
 // compute every distance on the vector ALUs, 2 v + 3 instructions per (vector, centroid) pair: assign_short_kernel for
 // tables of fewer entries, assign_kernel for longer vectors.
 #include "vq_common.hpp"
+#include "vq_padding.hpp"
 #include <type_traits>
 
 namespace vq {
@@ -37,14 +38,7 @@ struct Vectors {
   long long scatter_bit;
 };
 
-// What follows the streams' last dwords, `count` dwords from number `from` on of each of `rows` strides, as zeros for a caller whose buffer is as the
-// allocator left it (count = 0: left alone).  Every thread of a launch takes some; a launch of its own that cleared the whole buffer in front took
-// 2766 x 384, v = 2, k = 16 1.6 us of 8.9, 2967 x 419, v = 6, k = 256 1.2 of 13.1, 1554 x 448, k = 4096, down the columns 1.5 of 32.3.
-struct Padding { unsigned char *idx; long long stride; int rows, from, count; };
-__device__ __forceinline__ void clear_padding(const Padding &p) {
-  for (int i = (int)(blockIdx.x * blockDim.x + threadIdx.x); i < p.rows * p.count; i += (int)(gridDim.x * blockDim.x))
-    reinterpret_cast<unsigned *>(p.idx + (long long)(i / p.count) * p.stride)[p.from + i % p.count] = 0u;
-}
+__device__ __forceinline__ void clear_padding(const Padding &p) { vq::clear_padding(p, blockIdx.x, blockDim.x, threadIdx.x, gridDim.x); }
 
 // Writes `count` bits of a dword that another lane may be writing other bits of.
 __device__ __forceinline__ void put_bits(unsigned *w, unsigned value, int from, int count) {
