@@ -143,7 +143,8 @@ struct WindowArgs {
   const int *perm;
   const __half *x;
   __half *y;
-  int out_features, in_features, ldx, ldy;
+  long long ldx, ldy;
+  int out_features, in_features;
   unsigned stride, stride_res;
   unsigned short k, k_res;
   int rows_per_wg;
@@ -321,10 +322,10 @@ template <int V, int BITS, int MODE, int B>
 int launch_window(const Params &p, const __half *x, long long ldx, __half *y, long long ldy, hipStream_t s) {
   const int rows = window_rows(p);
   const unsigned bytes = window_bytes(p, B, MODE);
-  if (!bytes || ldx > 0x7FFFFFFFLL || ldy > 0x7FFFFFFFLL || ldx < 0 || ldy < 0) return VQ_ERR_UNSUPPORTED;
+  if (!bytes) return VQ_ERR_UNSUPPORTED;
   auto kernel = gemv_lds_window_kernel<V, BITS, MODE, B>;
   VQ_ALLOW_FULL_LDS(kernel);
-  const WindowArgs a = {p.cb, p.cb_res, p.idx, p.idx_res, p.scale, p.bias, p.perm, x, y, p.out_features, p.in_features, (int)ldx, (int)ldy,
+  const WindowArgs a = {p.cb, p.cb_res, p.idx, p.idx_res, p.scale, p.bias, p.perm, x, y, ldx, ldy, p.out_features, p.in_features,
                         (unsigned)p.stride, (unsigned)p.stride_res, (unsigned short)p.k, (unsigned short)p.k_res, rows};
   hipLaunchKernelGGL(kernel, dim3((unsigned)((p.out_features + rows - 1) / rows)), dim3(LW * 64), bytes, s, a);
   return hipGetLastError() == hipSuccess ? VQ_OK : VQ_ERR_HIP;

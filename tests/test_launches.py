@@ -210,3 +210,11 @@ def test_gemv_down_folds_of_the_columns(out, inp, rows, more, streams):
     answer, = launches.run([dict(entry="gemv", rows=rows, pitch=inp + inp % 2, layer=dict(out_features=out, in_features=inp, orientation=1, **more))])
     grids = [launch["grid"] for launch in answer["launches"] if launch["name"].startswith("gemv_down_mfma")]
     assert [list(grid)[0] for grid in grids] == [-(-(-(-out // 6)) // streams)], answer
+
+
+@pytest.mark.parametrize("rows", [1, 2, 4])
+def test_gemv_of_rows_far_apart_keeps_its_kernel(rows):
+    """Rows of activations, or of results, more than 2^31 elements apart: the kernel for small tables as for any others."""
+    layer = dict(out_features=256, in_features=384, k=256)
+    near, far = launches.run([dict(entry="gemv", rows=rows, layer=layer, pitch=pitch) for pitch in (384, (1 << 31) + 8)], switches="rows=0")
+    assert near["status"] == 0 and far["launches"] == near["launches"] and near["launches"][0]["name"].startswith("gemv_lds_window_kernel")
