@@ -228,17 +228,20 @@ int gemv_rows_folds(const Params &p, int batch, bool parts);
 //  * orientation 1, whose workgroups take 16 streams, i.e. 16 v rows, over all the columns: with a workspace, whose parts fill the
 //    chip, from two rows on (v = 12, 12275 x 1728: 18 -> 13 us), one row of at least 16384 columns (644 x 22848: 26 -> 18 us);
 //    without, from two rows on where the workgroups alone are half as many as compute units, else from five (v = 12, 717 x 5520,
-//    2 rows: 18 against 37 us);
+//    2 rows: 18 against 37 us), and where folds of the columns take the place of parts as with one (v = 2, 206 x 3308, four rows 10.1 -> 6.3 us;
+//    v = 4, 3000 x 3300, two 9.9 -> 7.2; v = 6 / 256, 245 x 2394, two 8.2 -> 7.4);
 //  * v = 8 with 16-bit indices, orientation 1, whose lookups go through L2: with a workspace from five rows, or two of at least
 //    4096 columns, on (768 x 7872, 5 rows: 35 -> 13 us), without from nine (5 rows: 60 us).
 // Switch rows=0 / rows=1: never / wherever it can.
+// Whether rows that would be taken in column parts, were there a workspace, are taken in folds of the columns, which need none.
+static bool folds_spare_parts(const Params &p, int batch) { return gemv_rows_parts(p) > 0 && gemv_rows_folds(p, batch, true) > 1; }
 static bool rows_wanted(const Params &p, int batch, bool workspace) {
   if (switches().rows == 0 || forced_kernel() != '\0' || !gemv_rows_applicable(p)) return false;
   if (switches().rows == 1) return true;
   if (p.orientation == 1 && p.bits == 16) return batch >= (!workspace ? 9 : p.P >= 4096 ? 2 : 5);
   if (p.n_groups > 1) return batch >= 3;
   if (p.orientation == 1) {
-    if (workspace) return batch >= 2 || p.P >= 16384;
+    if (workspace || folds_spare_parts(p, batch)) return batch >= 2 || p.P >= 16384;
     return batch >= (2 * ((p.S + 15) / 16) >= cu_count() ? 2 : 5);
   }
   if (p.v == 12) return true;
@@ -461,7 +464,7 @@ static bool even_width_wanted(const Params &p, int batch) {
   if (p.n_groups > 1) return batch >= 2 && !groups_taken_odd(p, batch);
   return batch >= 3 || p.in_features >= (batch == 2 && p.Q ? 400 : p.k_res ? 512 : batch == 2 ? 700 : 1024);
 }
-static size_t stored_order_workspace_bytes(const Params &p, const __half *x, long long ldx, int batch, bool least);
+static size_t stored_order_workspace_bytes(const Params &p, const __half *x, long long ldx, int batch, bool least, bool copied);
 static Params gathered(const Params &p, int batch) {
   Params q = p;
   q.perm = nullptr;
@@ -473,7 +476,7 @@ static bool rows_gathered(const Params &p, int batch) {
   if (!(p.in_features & 1) || p.in_features >= (1 << 18) || forced_kernel() != '\0') return false;
   if (batch >= 5 && rows_wanted(p, batch, true)) return true;
   if ((long long)p.S * p.P < 1 << 17 || !((even_width_wanted(p, batch) && (batch >= 2 || p.n_groups == 1)) || (batch >= 2 && down_mfma_wanted(p, nullptr, p.in_features + 1, batch)))) return false;
-  return permuted_x_bytes(p, batch) + stored_order_workspace_bytes(gathered(p, batch), nullptr, (p.in_features + 7) & ~7, batch, false) <= VQ_GEMV_STATIC_WORKSPACE_BYTES;
+  return permuted_x_bytes(p, batch) + stored_order_workspace_bytes(gathered(p, batch), nullptr, (p.in_features + 7) & ~7, batch, false, false) <= VQ_GEMV_STATIC_WORKSPACE_BYTES;
 }
 // ... unless the rows can be taken as they are
 static bool taken_as_they_are(const Params &p, const __half *x, long long ldx, int batch) {
@@ -485,16 +488,20 @@ size_t gemv_products_workspace_bytes(const Params &p, int batch);
 int launch_gemv_products(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, void *workspace, size_t workspace_bytes,
                          hipStream_t s);
 
-static size_t stored_order_workspace_bytes(const Params &p, const __half *x, long long ldx, int batch, bool least) {
+// (the outlier columns are one more set of sums to add up)
+static size_t down_parts_bytes(const Params &p, int batch) {
+  const int parts = gemv_down_mfma_parts(p);
+  return parts > 1 ? ((size_t)(parts + (p.Q ? 1 : 0)) * ((size_t)batch * (size_t)p.out_features + 16) * sizeof(float) + 255) / 256 * 256 : 0;
+}
+static size_t stored_order_workspace_bytes(const Params &p, const __half *x, long long ldx, int batch, bool least, bool copied) {
   if (rows_wanted(p, batch, true) && (batch == 1 || !(ldx & 1))) {
     // (0 with codebook groups that the kernel walks by itself: the slots of the kernels below are asked for instead, which run where
     // this one does not take x)
     const size_t need = gemv_rows_workspace_bytes(p, batch);
-    if (need) return need;
+    if (need) return folds_spare_parts(p, batch) ? 0 : need;
   }
   if (p.orientation == 1 && down_mfma_parts_wanted(p, x, ldx, batch)) {   // the matrix cores: the workspace lets parts of the columns run side by side
-    const int parts = gemv_down_mfma_parts(p);            // the outlier columns are one more set of sums to add up
-    return parts > 1 ? ((size_t)(parts + (p.Q ? 1 : 0)) * ((size_t)batch * (size_t)p.out_features + 16) * sizeof(float) + 255) / 256 * 256 : 0;
+    return gemv_down_mfma_parts(p) > 1 && down_mfma_parts_pay(p, batch, copied) ? down_parts_bytes(p, batch) : 0;
   }
   if (p.orientation == 1) {         // vectors down the output dimension: the same workspace layout, filled by that orientation's kernel
     if (p.n_groups > 1 && p.n_groups <= 256 && gemv_down_applicable(p, x, ldx))
@@ -514,22 +521,33 @@ static size_t workspace_bytes_of(const Params &p, const __half *x, long long ldx
   if (p.perm || rows_gathered(p, batch)) {
     if (p.perm && permuted_in_kernel(p, x, ldx, batch)) return 0;
     const Params q = gathered(p, batch);
-    const size_t head = permuted_x_bytes(p, batch), rest = stored_order_workspace_bytes(q, nullptr, (p.in_features + 7) & ~7, batch, least);
+    const size_t head = permuted_x_bytes(p, batch), rest = stored_order_workspace_bytes(q, nullptr, (p.in_features + 7) & ~7, batch, least, p.perm != nullptr);
     // (the column parts of vq_gemv_rows.hip are done without where the two together are more than vq_gemv_static_workspace has)
     return rows_wanted(q, batch, true) && head + rest > VQ_GEMV_STATIC_WORKSPACE_BYTES ? head : head + rest;
   }
-  return stored_order_workspace_bytes(p, x, ldx, batch, least);
+  return stored_order_workspace_bytes(p, x, ldx, batch, least, false);
 }
 
 // (One and two rows of a layer with two tables a group take a slot a table, whose workspace may be larger than that of three rows, which
 // another kernel takes.  What holds a slot a group of fewer rows is made to hold that, so that a loop can lend its calls the workspace of the
-// largest batch.)
+// largest batch.  For the same loop: down the outputs other rows may be taken in parts of the columns where these, whose folds or launch
+// without parts are estimated to be as fast, are not.  They ask for what fewer rows do; v = 6 from two rows on for what their own parts would.)
 static size_t other_workspace_bytes(const Params &p, const __half *x, long long ldx, int batch) {
   const size_t own = workspace_bytes_of(p, x, ldx, batch, false);
   size_t bytes = own;
   if (p.orientation == 0 && p.k_res && p.n_groups > 1)
     for (int rows = 1; rows < batch; ++rows)
       if (own >= workspace_bytes_of(p, x, ldx, rows, true)) bytes = std::max(bytes, workspace_bytes_of(p, x, ldx, rows, false));
+  auto copy = [&](int rows) { return p.perm || rows_gathered(p, rows) ? permuted_x_bytes(p, rows) : 0; };
+  if (p.orientation == 1 && p.n_groups == 1 && own == copy(batch)) {
+    const Params q = own ? gathered(p, batch) : p;
+    const bool v6 = batch >= 2 && down_mfma_parts_wanted(q, own ? nullptr : x, own ? (p.in_features + 7) & ~7 : ldx, batch);
+    for (int rows = 1; rows < (v6 ? 17 : batch); ++rows) {
+      const size_t other = workspace_bytes_of(p, x, ldx, rows, false);
+      if (v6 && other > copy(rows)) return own + down_parts_bytes(q, batch);
+      if (rows < batch) bytes = std::max(bytes, other);
+    }
+  }
   return bytes;
 }
 // (one and two rows from tables of products, vq_gemv_products.hip, may take more than the other kernels do of more rows; for the same loop that is
@@ -544,6 +562,7 @@ size_t gemv_workspace_bytes(const Params &p, const __half *x, long long ldx, int
 // of products are one row's; 11008 x 4096, 16 rows: 1.9 MB).
 size_t gemv_lent_bytes(const Params &p, int batch) {
   const long long ldx = p.in_features + (p.in_features & 1);
+  if (p.orientation == 1 && p.n_groups == 1) return workspace_bytes_of(p, nullptr, ldx, batch, false);
   return gemv_products_workspace_bytes(p, batch) || workspace_bytes_of(p, nullptr, ldx, batch, false) ? gemv_workspace_bytes(p, nullptr, ldx, batch) : 0;
 }
 
@@ -584,7 +603,7 @@ static int launch_with_workspace(const Params &p, const __half *x, long long ldx
 // the workspace with what its kernels write.
 static int launch_stored_order(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, void *workspace,
                                size_t workspace_bytes, bool least, bool copied, hipStream_t s) {
-  const size_t need = force_generic() ? 0 : stored_order_workspace_bytes(p, x, ldx, batch, least);
+  const size_t need = force_generic() ? 0 : stored_order_workspace_bytes(p, x, ldx, batch, least, copied);
   if (rows_wanted(p, batch, workspace != nullptr) && gemv_rows_takes(p, x, ldx, batch)) {
     const int per_group = workspace && workspace_bytes >= gemv_rows_workspace_bytes(p, batch) ? gemv_rows_parts(p) : 0, parts = per_group * p.n_groups;
     const int folds = parts ? gemv_rows_folds(p, batch, true) : 0;
@@ -641,13 +660,15 @@ static int launch_stored_order(const Params &p, const __half *x, long long ldx, 
 int launch_gemv_ws(const Params &p, const __half *x, long long ldx, int batch, __half *y, long long ldy, void *workspace,
                    size_t workspace_bytes, hipStream_t s) {
   const long long even = p.in_features + (p.in_features & 1);
-  const bool enough = workspace && workspace_bytes >= gemv_workspace_bytes(p, nullptr, even, batch);
+  // (down the outputs what is asked for beyond the bytes of these rows is for others)
+  const bool down = p.orientation == 1 && p.n_groups == 1;
+  const bool enough = workspace && workspace_bytes >= (down ? workspace_bytes_of(p, nullptr, even, batch, false) : gemv_workspace_bytes(p, nullptr, even, batch));
   if (enough) {
     const int rc = launch_gemv_products(p, x, ldx, batch, y, ldy, workspace, workspace_bytes, s);
     if (rc != VQ_ERR_UNSUPPORTED) return rc;
   }
   // less than vq_gemv_workspace_bytes asks for, though not for these rows alone: vq_gemv
-  if (workspace && !enough && workspace_bytes >= workspace_bytes_of(p, nullptr, even, batch, false)) return launch_gemv(p, x, ldx, batch, y, ldy, s);
+  if (workspace && !enough && !down && workspace_bytes >= workspace_bytes_of(p, nullptr, even, batch, false)) return launch_gemv(p, x, ldx, batch, y, ldy, s);
   // (rows of an odd width may go to other kernels than the size was asked for, which make do with what it is)
   return launch_with_workspace(p, x, ldx, batch, y, ldy, workspace, workspace_bytes, enough && !p.perm && (ldx & 1), s);
 }

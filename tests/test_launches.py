@@ -218,3 +218,35 @@ def test_gemv_of_rows_far_apart_keeps_its_kernel(rows):
     layer = dict(out_features=256, in_features=384, k=256)
     near, far = launches.run([dict(entry="gemv", rows=rows, layer=layer, pitch=pitch) for pitch in (384, (1 << 31) + 8)], switches="rows=0")
     assert near["status"] == 0 and far["launches"] == near["launches"] and near["launches"][0]["name"].startswith("gemv_lds_window_kernel")
+
+
+@pytest.mark.parametrize("out,inp,rows,more,used", [
+    (11008, 4096, 4, {}, False), (4096, 4097, 8, dict(col_perm=True), False), (1811, 3052, 3, {}, True), (7614, 7226, 5, {}, True), (7614, 7226, 6, {}, False),
+    (515, 3900, 3, dict(v=2, k=16), False), (131, 4098, 4, dict(v=4, k=256), False), (131, 3500, 8, dict(v=6, k=256), False), (515, 3900, 12, dict(v=2, k=16), True),
+    (130, 10000, 4, dict(v=8, k=65536, orientation=0), False), (130, 10000, 8, dict(v=8, k=65536, orientation=0), True), (14336, 512, 16, {}, False),
+])
+def test_gemv_in_folds_of_the_columns_uses_no_workspace(out, inp, rows, more, used):
+    """Folds need no sums of parts: such rows are lent none, and run the same kernel with any workspace and without.  Only layers of which some number of rows
+    is taken in parts ask for sums."""
+    layer = dict(dict(out_features=out, in_features=inp, orientation=1), **more)
+    call = dict(entry="gemv_with_workspace", layer=layer, rows=rows, pitch=inp)
+    asked, lent, generous, none = launches.run([dict(call, workspace="asked"), dict(call, workspace="lent"), dict(call, workspace=16 << 20), dict(call, entry="gemv")])
+    copy = (rows * (inp + 7) // 8 * 8 * 2 + 255) // 256 * 256 if layer.get("col_perm") else 0
+    assert asked["launches"] == generous["launches"] and any("finish" in launch["name"] for launch in asked["launches"]) == used
+    if not used:
+        assert lent["lent"] <= copy + 256 and (copy or none["launches"] == asked["launches"])
+        others = launches.run([dict(call, rows=r, workspace="asked") for r in range(1, 17)])
+        assert asked["asked"] <= copy + 256 or any("finish" in launch["name"] for other in others for launch in other["launches"])
+
+
+def test_gemv_asks_for_what_fewer_rows_use():
+    """A loop may lend its calls the workspace of the largest number of rows."""
+    rng = random.Random(12)
+    calls = []
+    for _ in range(60):
+        layer = dict(_layer(rng, rng.randint(0, 1)), orientation=1, group_vectors=0)
+        calls += [dict(entry="gemv_with_workspace", layer=layer, rows=rows, workspace="asked") for rows in range(1, 17)]
+    sizes = [answer["asked"] for answer in launches.run(calls)]
+    assert sum(size > 0 for size in sizes) > 300
+    for i in range(0, len(sizes), 16):
+        assert sizes[i:i + 16] == sorted(sizes[i:i + 16]), calls[i]
