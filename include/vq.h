@@ -160,7 +160,7 @@ int vq_gemv(const vq_layer_desc *desc, const void *x, int64_t ldx, int32_t batch
  * groups on the kernel that keeps one table in LDS at a time, whose workgroups gather theirs by themselves; rows of an odd width that a kernel of
  * dwords is the faster one for are copied into it.  vq_gemv_workspace_bytes returns 0 when
  * no kernel would use a workspace for this layer, and never less for more rows; in orientation 1 it may be more than these rows use,
- * or these may use none, where other numbers of rows are taken in parts.  With workspace NULL or smaller than that (in orientation 1, one group: than what these rows use), and for every other layer, the
+ * as other numbers of rows are taken in parts (v = 6: whenever the columns can be cut, from two rows on).  With workspace NULL or smaller than that (in orientation 1, one group: than what these rows use), and for every other layer, the
  * call is vq_gemv.  Same arguments, bar and errors as vq_gemv; a workspace that is not 256-byte aligned is
  * VQ_ERR_ALIGNMENT.  Calls that share a workspace must not overlap.                                          */
 size_t vq_gemv_workspace_bytes(const vq_layer_desc *desc, int32_t batch);

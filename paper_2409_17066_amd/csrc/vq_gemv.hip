@@ -531,22 +531,19 @@ static size_t workspace_bytes_of(const Params &p, const __half *x, long long ldx
 // (One and two rows of a layer with two tables a group take a slot a table, whose workspace may be larger than that of three rows, which
 // another kernel takes.  What holds a slot a group of fewer rows is made to hold that, so that a loop can lend its calls the workspace of the
 // largest batch.  For the same loop: down the outputs other rows may be taken in parts of the columns where these, whose folds or launch
-// without parts are estimated to be as fast, are not.  They ask for what fewer rows do; v = 6 from two rows on for what their own parts would.)
+// without parts are estimated to be as fast, are not.  They ask for what fewer rows do; v = 6 for what parts of its own would.)
 static size_t other_workspace_bytes(const Params &p, const __half *x, long long ldx, int batch) {
   const size_t own = workspace_bytes_of(p, x, ldx, batch, false);
   size_t bytes = own;
   if (p.orientation == 0 && p.k_res && p.n_groups > 1)
     for (int rows = 1; rows < batch; ++rows)
       if (own >= workspace_bytes_of(p, x, ldx, rows, true)) bytes = std::max(bytes, workspace_bytes_of(p, x, ldx, rows, false));
-  auto copy = [&](int rows) { return p.perm || rows_gathered(p, rows) ? permuted_x_bytes(p, rows) : 0; };
-  if (p.orientation == 1 && p.n_groups == 1 && own == copy(batch)) {
-    const Params q = own ? gathered(p, batch) : p;
-    const bool v6 = batch >= 2 && down_mfma_parts_wanted(q, own ? nullptr : x, own ? (p.in_features + 7) & ~7 : ldx, batch);
-    for (int rows = 1; rows < (v6 ? 17 : batch); ++rows) {
-      const size_t other = workspace_bytes_of(p, x, ldx, rows, false);
-      if (v6 && other > copy(rows)) return own + down_parts_bytes(q, batch);
-      if (rows < batch) bytes = std::max(bytes, other);
-    }
+  if (p.orientation == 1 && p.n_groups == 1) {
+    const size_t copy = p.perm || rows_gathered(p, batch) ? permuted_x_bytes(p, batch) : 0;
+    if (own > copy) return own;
+    const Params q = copy ? gathered(p, batch) : p;
+    if (down_mfma_parts_wanted(q, copy ? nullptr : x, copy ? (p.in_features + 7) & ~7 : ldx, batch)) return copy + down_parts_bytes(q, batch);
+    for (int rows = 1; rows < batch; ++rows) bytes = std::max(bytes, workspace_bytes_of(p, x, ldx, rows, false));
   }
   return bytes;
 }
