@@ -250,3 +250,22 @@ def test_gemv_asks_for_what_fewer_rows_use():
     assert sum(size > 0 for size in sizes) > 300
     for i in range(0, len(sizes), 16):
         assert sizes[i:i + 16] == sorted(sizes[i:i + 16]), calls[i]
+
+
+@pytest.mark.parametrize("out,inp,v,k,more,orientation,rows,streams", [
+    (700, 900, 8, 65536, {}, 1, 3, 4), (701, 333, 8, 65536, {}, 1, 8, 8), (130, 10001, 8, 65536, {}, 0, 4, 4), (1001, 3205, 8, 65536, {}, 0, 7, 8),
+    (301, 1700, 12, 4096, dict(k_res=4096), 1, 4, 4), (301, 505, 12, 4096, dict(k_res=4096, n_outlier_cols=24), 1, 6, 8),
+    (77, 9509, 12, 4096, dict(k_res=4096), 0, 2, 4), (900, 3300, 12, 4096, dict(k_res=4096, n_outlier_cols=40), 0, 5, 8),
+    (131, 4099, 4, 256, {}, 1, 4, 4), (2003, 700, 4, 256, {}, 1, 8, 8), (130, 3209, 4, 256, {}, 0, 4, 8), (1003, 6001, 4, 256, {}, 0, 8, 8),
+    (515, 3900, 2, 16, {}, 1, 1, 4), (3001, 1001, 2, 16, {}, 1, 8, 8), (333, 1035, 2, 16, {}, 0, 3, 8),
+    (131, 4099, 6, 256, {}, 1, 4, 4), (131, 777, 6, 256, {}, 1, 8, 8), (1002, 3461, 6, 256, {}, 0, 4, 8),
+])
+def test_gemv_rows_folds_of_the_columns(out, inp, v, k, more, orientation, rows, streams):
+    """How many index streams a workgroup takes of the layers and rows whose results test_gemv_rows_folds compares, with the workspace of the size asked for and without."""
+    layer = dict(out_features=out, in_features=inp, v=v, k=k, orientation=orientation, **more)
+    call = dict(entry="gemv", rows=rows, pitch=(inp + 7) // 8 * 8 + 8, layer=layer)
+    count = -(-out // v) if orientation else out
+    plain, asked = launches.run([call, dict(call, entry="gemv_with_workspace", workspace="asked")], switches="rows=1")
+    assert [launch["grid"][0] for launch in plain["launches"]] == [-(-count // streams)] and plain["launches"][0]["name"].startswith("gemv_rows_kernel")
+    names = [launch["name"].split("<")[0] for launch in asked["launches"]]
+    assert "gemv_rows_kernel" in names and (asked["launches"] == plain["launches"] or names[-1] == "gemv_groups_finish_kernel" or names[0] == "gather_cols_kernel")
