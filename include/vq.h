@@ -229,7 +229,8 @@ int vq_assign_down(const void *W, const void *B, int64_t ld, int32_t rows, int32
  * and bias 0.  idx / idx_res: the packed index streams of orientation 1, [ceil(rows / v)][stride] bytes, one index per
  * column, written as vq_assign_down writes them (same stride and alignment rules; idx_res and codebook_res NULL and
  * k_res 0 without a residual codebook).  T, optional (NULL): binary32 [rows][ldt], column n as it stood when it was
- * quantized.  block in [1, 128].  workspace: vq_quantize_columns_workspace_bytes(rows, v, k, k_res) bytes of device
+ * quantized.  block in [1, 128]; where the sums are split is all it decides, and the kernel may take another (sixteen columns
+ * at least, multiples of eight, fewer than asked for beside large tables).  workspace: vq_quantize_columns_workspace_bytes(rows, v, k, k_res) bytes of device
  * memory, 256-byte aligned, contents undefined afterwards, else VQ_ERR_WORKSPACE.
  * Arithmetic: binary32 throughout.  The distance is the one of vq_assign (one subtraction and one fused multiply-add per
  * element into a sum that starts at +0, elements ascending; the smallest index among the smallest distances; a cut-off

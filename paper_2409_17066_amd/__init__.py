@@ -279,8 +279,8 @@ def dequant(dl: DeviceLayer, ldw=None):
 def gemv(dl: DeviceLayer, x, out=None, workspace=None):
     """x: fp16 [batch][>=in] device tensor -> fp16 [batch][out].  workspace: a uint8 device tensor; "fast" allocates the one
     vq_gemv_workspace_bytes asks for, if any (torch's allocator hands it out and takes it back in stream order), and so does
-    None except for layers with codebook groups and v = 6 / 12-bit ones in stored order, whose kernels without one sum in the order of gemv_multi
-    (v = 6 rows of an odd width: in that of a workspace); an empty tensor leaves the library without."""
+    None, as far as these rows use it, except for layers with codebook groups and v = 6 / 12-bit ones in stored order, whose kernels without one
+    along the rows sum in the order of gemv_multi (v = 6 rows of an odd width: in that of a workspace); an empty tensor leaves the library without."""
     y = (_bound or _native()).gemv(dl, x, out, workspace)
     if y.__class__ is int:
         raise VQError(y, "vq_gemv")

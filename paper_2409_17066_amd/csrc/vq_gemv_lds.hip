@@ -133,9 +133,9 @@ __global__ __launch_bounds__(LW * 64) void gemv_lds_kernel(Params p, LdsPlan pla
 // 32 bytes, so that an entry is one aligned read (two for V = 12).
 constexpr bool two_pass_compiled(int v, int bits) { return v >= 8 && bits == 12; }   // where two padded tables can exceed LDS
 
-// What the kernel cannot derive.  A launch with up to 112 bytes of arguments takes the host 2.9 us, one with more 3.5 to 3.8 (calls one after the
-// other, arguments in device memory as the runtime has them by default), and the smallest calls are nothing but that: 256 x 384, v = 6,
-// k = 256, one row, with 232 bytes of arguments 3.9 us a call of vq_gemv and 4.8 of gemv(), with 104 2.9 and 4.55.
+// What the kernel cannot derive.  The smallest calls are nothing but their launch: 256 x 384, v = 6, k = 256, one row, calls one after the other, takes
+// 2.88 us a call of vq_gemv with 112 bytes of arguments in any process, and with 232 bytes 2.91 in one and 3.4 in the next; gemv() 3.7 or 4.15, and
+// 3.84 or 4.6.
 struct WindowArgs {
   const __half *cb, *cb_res;
   const uint8_t *idx, *idx_res;

@@ -9,7 +9,8 @@ extern "C" {
 #endif
 
 /* Of vq_gemv_with_workspace.  0 where no kernel of exactly these rows would use it, and for layers with codebook groups and v = 6 / 12-bit layers in
- * stored order: their kernels without one are good, and sum in the same order with vq_gemv_multi or a workspace that is too small.  Of v = 6 rows of an
+ * stored order: their kernels without one are good, and those along the rows sum in the same order with vq_gemv_multi (one row, and from three on) or a
+ * workspace that is too small.  Of v = 6 rows of an
  * odd width, which those kernels take far more slowly than a copy of them, or than group by group, that order is given up. */
 size_t vq_lend_gemv_bytes(const vq_layer_desc *desc, int32_t batch);
 /* Of vq_gemm_default, on a card without room for what it asks for: the same route without the sums of a product in parts. */

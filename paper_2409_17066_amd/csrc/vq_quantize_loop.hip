@@ -35,14 +35,14 @@ namespace {
 //
 // What bounds it: the chain of a column.  A wave on its own issues an instruction every five clocks or so, and what counts is how many
 // stand on the path between one column's t and the next (about 200 with a 4096-entry table), the LDS round trips (130 clocks, four of
-// them) and the barrier, not any rate: 2000 clocks a column (of 2.4 GHz), of which the comparisons of the scores are 500.  Whatever else a SIMD
+// them) and the barrier, not any rate: 2300 clocks a column (of 2.35 GHz), of which the comparisons of the scores are 500.  Whatever else a SIMD
 // executes adds to that, binary32 products above all: they keep the search wave from issuing for as long as they take, wherever in a column
 // they stand and whatever the waves' priorities (80 instructions of 8 clocks a column: search 1910 -> 2460 clocks; without any later columns
-// 4096 x 4096 would take 3.5 ms, 0.5 of the 0.6 between are the products).  Eight search waves of half the table each are slower (4.8 ms against 4.6
+// 4096 x 4096 would take 3.5 ms, nearly all of the 0.5 between are the products).  Eight search waves of half the table each are slower (4.8 ms against 4.6
 // then): everything but the comparisons is issued twice on every SIMD.
 // With the later columns' update at the end of each block, by all waves and waiting for H^-1 and W, 94 of a block's 340 thousand clocks:
-// v = 6, k = 4096, 4096 x 4096 4.57 -> 4.10 ms; 3000 x 2000 1833 -> 1737 us; v = 8, k = 4096 2670 -> 2267; v = 12, k = 4096 2799 -> 2440; v = 4, k = 256
-// 1347 -> 1191.  The same update as 16 x 16 x 1 products in place of 4 x 4 x 1 took as long, and so did one ahead of the kept columns' update
+// v = 6, k = 4096, 4096 x 4096 4.57 -> 4.03 ms; 3000 x 2000 1831 -> 1714 us; v = 8, k = 4096 2680 -> 2247; v = 12, k = 4096 2803 -> 2393; v = 4, k = 256
+// 1348 -> 1200.  The same update as 16 x 16 x 1 products in place of 4 x 4 x 1 took as long, and so did one ahead of the kept columns' update
 // in place of behind it; sums in the vector ALUs for the kept columns 2 % longer; stores of T, weights and indices by the keeping waves,
 // whose loads then wait for them, 2 % longer.
 typedef _Float16 half8v __attribute__((ext_vector_type(8)));
