@@ -153,14 +153,16 @@ int vq_gemv(const vq_layer_desc *desc, const void *x, int64_t ldx, int32_t batch
  * take half of one or a quarter and the columns in two or four folds, side by side in one instruction, which needs no
  * workspace; where more than that pays, and for more rows, the columns are cut into parts, one workgroup per (block,
  * part), whose sums go to the workspace and the same second kernel adds up (one row too when a row of x does not fit the
- * one-row kernel's LDS beside the tables: about 15000 columns with a 12-bit residual table); so does the matrix-core kernel of the paper's other settings along the rows and, from three
- * rows on, that of v = 6 / 12-bit layers along the rows with one group and few blocks of rows.  v = 12 layers with 12-bit indices take
- * one and two rows from tables of products of their entries and the activations, whose sums over runs of columns a second kernel adds up in
+ * one-row kernel's LDS beside the tables: about 15000 columns with a 12-bit residual table).  So does the matrix-core kernel of
+ * the paper's other settings along the rows and, from three rows on, that of v = 6 / 12-bit layers along the rows with one group
+ * and few blocks of rows.  v = 12 layers with 12-bit indices take one and two rows from tables of products of their
+ * entries and the activations, whose sums over runs of columns a second kernel adds up in
  * ascending order.  Layers with a column permutation gather the activations into it first, but for one and two rows of layers with codebook
  * groups on the kernel that keeps one table in LDS at a time, whose workgroups gather theirs by themselves; rows of an odd width that a kernel of
  * dwords is the faster one for are copied into it.  vq_gemv_workspace_bytes returns 0 when
- * no kernel would use a workspace for this layer, and never less for more rows; in orientation 1 it may be more than these rows use,
- * as other numbers of rows are taken in parts (v = 6: whenever the columns can be cut, from two rows on).  With workspace NULL or smaller than that (in orientation 1, one group: than what these rows use), and for every other layer, the
+ * no kernel would use a workspace for this layer, and never less for more rows; in orientation 1 it may be more than these
+ * rows use, as other numbers of rows are taken in parts (v = 6: whenever the columns can be cut, from two rows on).  With
+ * workspace NULL or smaller than that (in orientation 1, one group: than what these rows use), and for every other layer, the
  * call is vq_gemv.  Same arguments, bar and errors as vq_gemv; a workspace that is not 256-byte aligned is
  * VQ_ERR_ALIGNMENT.  Calls that share a workspace must not overlap.                                          */
 size_t vq_gemv_workspace_bytes(const vq_layer_desc *desc, int32_t batch);
